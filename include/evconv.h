@@ -110,7 +110,9 @@ typedef enum {
 
 /* dtype of the weights and of the increments inside the channel contraction; accumulation and
  * every cached tensor are always fp32.
- *   EVCONV_F32        fp32 operands on the fp32 matrix-core (or vector) path.
+ *   EVCONV_F32        fp32 operands, all 24 bits: on the matrix cores as three bf16 parts that add up
+ *                     to the value exactly, six partial products of a product (the rest is below
+ *                     half the rounding step of an fp32 product), or on the vector path.
  *   EVCONV_BF16       weights rounded to bf16 at create, increments rounded to bf16 inside the
  *                     contraction: relative error of a product about 2^-8.
  *   EVCONV_F32_SPLIT  fp32 weights and increments, each written as bf16 high part + bf16 low part
@@ -224,7 +226,7 @@ evconv_status evconv_create(const evconv_net_desc* desc, const void* weights, si
  * would overwrite each other.  The array keeps the previous net's contents; the part a new net
  * uses is cleared by this call.  The pointers in evconv_out point into the array.  Otherwise as
  * evconv_create. */
-#define EVCONV_STATIC_WORKSPACE_BYTES (32u << 20)
+#define EVCONV_STATIC_WORKSPACE_BYTES (48u << 20)
 evconv_status evconv_create_static(const evconv_net_desc* desc, const void* weights, size_t weight_bytes,
                                    void* hip_stream, evconv_net** out);
 

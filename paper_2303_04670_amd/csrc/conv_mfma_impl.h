@@ -4,21 +4,21 @@
 // channel chunk is zero-padded), c_out >= 16 (any count: the last block of 32 is zero-padded).
 // Implicit GEMM per touched output tile (8 x 8 sites): M = 32 * MB sites (MB = 2: the whole
 // tile as two 32-row MFMA blocks, rows 0-3 and 4-7; MB = 1: one workgroup per half tile),
-// N = 32 output channels per workgroup (16 in the fp32 variant for launches that fill the chip
-// unevenly, see NB below), K = taps x c_in.
+// N = 32 output channels per workgroup, K = taps x c_in.
 //
-//   fp32 mode : fp32 operands, v_mfma_f32_32x32x2_f32; a unit = one tap x 8 channels (4 MFMA
-//               steps per block); MFMA j of a unit contracts channels {j, 4+j}: lanes 0-31 hold
-//               channel j, lanes 32-63 channel 4+j, for both operands.
 //   bf16 mode : the gather rounds increments to bf16 on their way into LDS, weights are bf16,
 //               v_mfma_f32_32x32x16_bf16 with fp32 accumulation; a unit = one tap x 16 channels
 //               (one MFMA per block); lanes 0-31 hold channels 0-7, lanes 32-63 channels 8-15.
-//   split mode: fp32 accuracy from the bf16 matrix cores.  Each fp32 operand is written as
-//               hi + lo with hi = bf16(x), lo = bf16(x - hi) (16 significant bits together); the
-//               gather does that for the increments, the host for the weights; a product is
-//               lo*hi + hi*lo + hi*hi, three bf16 MFMAs with fp32 accumulation (relative error of
-//               a product about 2^-16, against 2^-8 in bf16 mode).  16 times the fp32 MFMA rate
-//               at 3 MFMAs per product.
+//   fp32 mode : the same instruction on operands written exactly as the sum of three bf16 parts,
+//               x = hi + mid + lo with hi = bf16(x), mid = bf16(x - hi), lo = x - hi - mid (3 x 8
+//               signed significant bits hold the 24 of an fp32 value); the gather does that for
+//               the increments, the host for the weights.  A product is the six partial products
+//               down to 2^-16 of it (lo*hi, mid*mid, hi*lo, mid*hi, hi*mid, hi*hi); the three left
+//               out are 2^-25 of it, half the rounding step of an fp32 product.  Six MFMAs at 16
+//               times the rate of the chip's fp32 matrix instruction, which besides runs on the
+//               vector pipeline and takes its time from every address and epilogue instruction.
+//   split mode: two parts and three products (lo*hi, hi*lo, hi*hi): 16 significant bits, relative
+//               error of a product about 2^-16, against 2^-8 in bf16 mode.
 //
 // Workgroup = NW (4 or 8) wavefronts that split K: the units of every channel chunk are dealt
 // round-robin to the waves; each wave keeps the MB accumulators and the partial sums are added
@@ -33,9 +33,9 @@
 //     next chunk's patch is fetched into registers while the current one is being contracted.
 //     A lane reads its fragment with one ds_read_b128; the LDS site stride keeps that
 //     conflict-free for stride-1 layers.
-//   B operand: weights re-laid as [tap][c_in/4][c_out][4] (fp32) or [tap][c_in/8][c_out][8]
-//     (bf16) so that a lane's fragment is one 16-byte buffer load (L2-resident), held in a
-//     three-register ring two units ahead, across chunk boundaries.
+//   B operand: weights re-laid as one plane [tap][c_in/8][c_out][8] of bf16 per part, so that a
+//     lane's fragment is one 16-byte buffer load per part (L2-resident), held in a three-fragment
+//     ring two units ahead, across chunk boundaries.
 // Epilogue: lane = output channel, so every z / increment access is a 128-byte row segment; the
 // old z values are requested before the contraction starts.  ADD nodes that consume the conv
 // output (residual add + activation, skip adds) run here as well, writing their own buffers.
@@ -48,10 +48,9 @@
 // the stored tensor directly and writes its 64 outputs two sites apart.  Which workgroup does
 // which is read from a list made at set-up (ConvParams::fold_list).
 //
-// The fp32 matrix instruction executes on the SIMD's vector pipeline: a vector instruction of any
-// wave of the SIMD takes time from the MFMAs.  Hence the addressing style throughout: per-lane
-// parts of an address are computed once and kept, per-unit / per-row parts live in scalar
-// registers (buffer instructions with a scalar offset), masks are tested where their bits sit.
+// Vector instructions are kept few throughout: per-lane parts of an address are computed once and
+// kept, per-unit / per-row parts live in scalar registers (buffer instructions with a scalar
+// offset), masks are tested where their bits sit.
 // (This header holds the kernel template and its launchers; one translation unit per operand
 // mode instantiates it, so that the three modes compile in parallel.)
 #pragma once
@@ -66,7 +65,6 @@ namespace evk {
 namespace {
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
-typedef float floatx4 __attribute__((ext_vector_type(4)));
 // Phase stamps.  In a build with -DEVCONV_PHASE_STAMPS (never the product build) one lane per
 // workgroup writes the 100 MHz wall clock at the boundaries of the kernel's phases into a device
 // array of the translation unit; evconv_debug_phase_stamps copies the records out.  Without the
@@ -103,15 +101,14 @@ static __device__ unsigned g_phase_n;
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 // operand modes of the contraction
-constexpr int kOpF32 = 0;    // fp32 operands, v_mfma_f32_32x32x2_f32
+constexpr int kOpF32 = 0;    // fp32 operands, each written exactly as three bf16 parts, six bf16 MFMAs per product
 constexpr int kOpBf16 = 1;   // bf16 operands (increments rounded in the gather), v_mfma_f32_32x32x16_bf16
 constexpr int kOpSplit = 2;  // fp32 operands split into bf16 high + low parts, three bf16 MFMAs per product
 
-// one weight fragment of a lane; .l is the low-part plane in split mode, unused otherwise
-struct BFrag { float4 h, l; };
-// one patch fragment of a lane: both 32-row blocks (h1: second block, two-block workgroups only)
-// and their low parts (split mode only)
-struct AFrag { float4 h0, h1, l0, l1; };
+// one weight fragment of a lane: the high, (fp32 mode) middle and (fp32, split mode) low parts
+struct BFrag { float4 h, m, l; };
+// one patch fragment of a lane: the parts of both 32-row blocks (second block: two-block workgroups only)
+struct AFrag { float4 h0, h1, m0, m1, l0, l1; };
 
 __device__ __forceinline__ float act_m(int act, float v) {
   if (act == kActRelu) return fmaxf(v, 0.0f);
@@ -133,9 +130,36 @@ __device__ __forceinline__ unsigned pack_bf16x2(float lo, float hi) {
 
 // Largest halo patch (sites) a variant can meet: 64- and 128-channel chunks are used with stride 1
 // and taps <= 3, 32-channel chunks with stride 1 (taps <= 7), 16-channel chunks also with stride 2.
-constexpr int max_patch_sites(int chunk, int mb) {
+// (s2k: 0, or the largest kernel of a stride-2 variant with chunks of more than 16 channels)
+constexpr int max_patch_sites(int chunk, int mb, int s2k) {
   const int rows = 4 * mb - 1;
+  if (s2k) return (rows * 2 + s2k) * (14 + s2k);
   return chunk >= 64 ? (rows + 3) * 10 : chunk == 32 ? (rows + 7) * 14 : (rows * 2 + 7) * 21;
+}
+
+constexpr int op_parts(int opm) { return opm == kOpF32 ? 3 : opm == kOpSplit ? 2 : 1; }
+// 4-byte words of a patch site in LDS
+constexpr int patch_site_words(int chunk, int opm) { return chunk / 2 * op_parts(opm) + 4; }
+
+// The three parts of a value beyond the bf16 rounding range, into bits [shift, shift + 16) of h, m,
+// l.  A finite one: the high part is cut off instead of rounded up to infinity.  An infinity goes
+// into the low part alone: the low part is multiplied with the weight's high part only, which is
+// zero for zero weights only, so the product is the IEEE one (inf * 0 of a weight's zero low
+// parts would be NaN).
+constexpr float kBf16Overflow = 3.3961775e38f;  // 0x7f7f8000: the smallest value that rounds to an infinite bf16
+__device__ __forceinline__ void split3_large(float x, int shift, unsigned& h, unsigned& m, unsigned& l) {
+  if (!(fabsf(x) >= kBf16Overflow)) return;
+  unsigned ph = 0, pm = 0, pl = __float_as_uint(x) >> 16;
+  if (fabsf(x) != INFINITY) {
+    ph = __float_as_uint(x) >> 16;
+    const float r = x - __uint_as_float(ph << 16);
+    pm = __float_as_uint(r) >> 16;
+    pl = __float_as_uint(r - __uint_as_float(pm << 16)) >> 16;
+  }
+  const unsigned keep = ~(0xffffu << shift);
+  h = (h & keep) | (ph << shift);
+  m = (m & keep) | (pm << shift);
+  l = (l & keep) | (pl << shift);
 }
 
 // The register budget is held to 4 (half tiles) or 3 (whole tiles) waves per SIMD: the bf16 and
@@ -148,37 +172,32 @@ constexpr int max_patch_sites(int chunk, int mb) {
 // four of them on its way into the patch buffer.  p.gi describes the up-sampled tensor, p.lo_h x
 // p.lo_w the stored one; p.occ_in are the stored tensor's occupancy words, and an up-sampled
 // site is active where one of its four sources is.
-// NB: output channels per workgroup.  32 is the normal shape.  16 (fp32, half tiles, no up-sampling)
-// is for launches that would otherwise leave the chip unevenly filled: the same half tile as two
-// 16-row blocks of v_mfma_f32_16x16x4_f32 (a unit = one tap x 16 channels, MFMA j of a unit
-// contracts channels {j, 4+j, 8+j, 12+j}: lanes 16 q .. 16 q + 15 hold channel 4 q + j), twice the
-// workgroups at half the work each.
-template <int CHUNK, int NW, int OPM, int MB, bool UPS, int NB = 32>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NB == 16 ? 4 : MB == 1 && !(UPS && NW == 4) ? 4 : 3)))
+//
+// KSP: the channels are split over p.ks workgroups as well (chunk ranges of p.ks_chunks chunks).
+template <int CHUNK, int NW, int OPM, int MB, bool UPS, bool KSP = false, int S2K = 0>
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(MB == 1 && !(UPS && NW == 4) ? 4 : 3)))
 void conv_mfma_kernel(ConvParams p) {
   // this workgroup's stream: every state pointer of p is used through at_stream(.., so); p itself
   // stays untouched so that it remains in the kernel-argument segment
   const size_t so = (size_t)blockIdx.z * p.st.stride;
-  constexpr bool BF16 = OPM != kOpF32;     // bf16 MFMA, 16 channels per unit
-  constexpr bool SPLIT = OPM == kOpSplit;  // operands as bf16 high + low parts, three products
+  constexpr int PARTS = op_parts(OPM);     // bf16 parts of an operand
+  constexpr int NB = 32;                   // output channels per workgroup
   constexpr int NT = NW * 64;
   // LDS site stride in 4-byte words; stride / 4 is odd (the eight sites of a patch row fall into
-  // eight distinct 16-byte slots of the banks).  Split mode keeps a high plane and a low plane of
-  // CHUNK bf16 each per site.
-  constexpr int CS = (BF16 && !SPLIT) ? CHUNK / 2 + 4 : CHUNK + 4;
-  constexpr int LO = CHUNK / 2;  // word offset of the low plane inside a site (split mode)
-  static_assert(NB == 32 || (NB == 16 && OPM == kOpF32 && MB == 1 && !UPS), "16-channel blocks: fp32 half tiles only");
-  constexpr int UCH = (BF16 || NB == 16) ? 16 : 8;  // channels per unit
+  // eight distinct 16-byte slots of the banks).  A site holds one plane of CHUNK bf16 per part.
+  constexpr int CS = patch_site_words(CHUNK, OPM);
+  constexpr int LO = CHUNK / 2;  // word offset between the planes of a site
+  constexpr int UCH = 16;        // channels per unit
   constexpr int KG = CHUNK / UCH;     // units per tap and chunk
   constexpr int NV = CHUNK / 4;       // float4 per patch site
-  constexpr int MAXV = (max_patch_sites(CHUNK, MB) * NV + NT - 1) / NT;  // patch float4 per thread
+  constexpr int MAXV = (max_patch_sites(CHUNK, MB, S2K) * NV + NT - 1) / NT;  // patch float4 per thread
   constexpr int SUBS = 2 / MB;        // workgroups per tile
   constexpr int NROWS = 4 * MB;       // output rows of this workgroup
   constexpr int NSITES = 32 * MB;
   constexpr int EP_SITES = NT / NB;   // sites per epilogue pass
   constexpr int EP_ITERS = NSITES / EP_SITES;
   static_assert(EP_ITERS >= 1 && EP_SITES <= 32, "epilogue mapping");
-  constexpr int NACC = NB == 16 ? 8 : MB * 16;  // accumulator registers of a lane
+  constexpr int NACC = MB * 16;  // accumulator registers of a lane
   constexpr int SLOT = NACC * 64;     // floats per partial-sum slot
   constexpr int CSL = CHUNK + 4;      // UPS: site stride of the low-resolution fp32 buffer
   constexpr int LPMAX = 10;           // UPS: a 14-row patch has sources in at most 14 / 2 + 3 rows
@@ -212,7 +231,9 @@ void conv_mfma_kernel(ConvParams p) {
   // x over tiles: an XCD sees every eighth tile and all of the weights; x over the blocks of
   // output channels (wg_swap): an XCD sees all tiles and one in eight (four, two) of the weight
   // blocks.  The launcher picks whichever of the two operands is larger to be split.
-  const int wg_tile = p.wg_swap ? blockIdx.y : blockIdx.x, wg_co = p.wg_swap ? blockIdx.x : blockIdx.y;
+  const int wg_tile = p.wg_swap ? blockIdx.y : blockIdx.x, wg_ck = p.wg_swap ? blockIdx.x : blockIdx.y;
+  const int n_co = p.c_out_pad / NB;
+  const int ks = KSP ? wg_ck / n_co : 0, wg_co = KSP ? wg_ck - ks * n_co : wg_ck;
   int tile = wg_tile / SUBS;
   const int sub = wg_tile % SUBS;
   // Weight-folded workgroup (UPS variants with a fold list): its 8 x 8 "tile" is a tile of stored
@@ -301,7 +322,7 @@ void conv_mfma_kernel(ConvParams p) {
     if (e < total_v) {
       const int site = e / NV, v = e - site * NV;
       const int py = (site * gw_magic) >> 16, px = site - py * GW;
-      lds_off[j] = (ups ? site * CSL + v * 4 : py * RP + px * CS + v * (BF16 ? 2 : 4)) | (py << 16) | (px << 24);
+      lds_off[j] = (ups ? site * CSL + v * 4 : py * RP + px * CS + v * 2) | (py << 16) | (px << 24);
       g_off[j] = (unsigned)((((gy0 + py) * SW + gx0 + px) * Cin + v * 4) * 4);
     }
   }
@@ -338,7 +359,7 @@ void conv_mfma_kernel(ConvParams p) {
         ib_src[b] = (((cy0 - gy0) * GW + (cx0 - gx0)) * CSL + v * 4) | (((cy1 - cy0) * GW * CSL) << 12) |
                     (((cx1 - cx0) * CSL) << 22);
         const int py = 2 * i + 1 - iy0, px = 2 * j + 1 - ix0;  // patch coordinates of the block, -1 at least
-        const int dst = py * RP + px * CS + v * (BF16 ? 2 : 4) + 4096;
+        const int dst = py * RP + px * CS + v * 2 + 4096;
         int mask = 0;
 #pragma unroll
         for (int r = 0; r < 2; ++r)
@@ -430,6 +451,9 @@ void conv_mfma_kernel(ConvParams p) {
   }
   if (site_word == 0) return;
   const bool conv_on = touched_word != 0;
+  if (KSP && ks != 0 && !conv_on) return;  // nothing to contract: the first workgroup runs the epilogue alone
+  const int c_lo = KSP ? ks * p.ks_chunks * CHUNK : 0;
+  const int c_hi = KSP ? min(p.gi.c, c_lo + p.ks_chunks * CHUNK) : p.gi.c;
 
   // Epilogue addressing.  Thread = output channel co0 + tid % 32 at the EP_ITERS sites
   // r0 * 8 + it * EP_SITES + tid / 32 (EP_SITES = 8 or 16: consecutive `it` are one or two tile rows
@@ -464,9 +488,13 @@ void conv_mfma_kernel(ConvParams p) {
   const __amdgpu_buffer_rsrc_t z_rsrc = out_rsrc(at_stream(p.z, so));
 
   // old z values of the epilogue, requested now so that they arrive during the contraction
+  // (KSP: by the one workgroup that runs the epilogue, when it knows that it does)
   float z_old[EP_ITERS];
+  auto request_z = [&]() {
 #pragma unroll
-  for (int it = 0; it < EP_ITERS; ++it) z_old[it] = ep_load(z_rsrc, !p.dense && has(touched_mine, it), it);
+    for (int it = 0; it < EP_ITERS; ++it) z_old[it] = ep_load(z_rsrc, !p.dense && has(touched_mine, it), it);
+  };
+  if (!KSP) request_z();
 
   // the gather's offsets, now conditioned on the occupancy (out of range where the site is inactive)
 #pragma unroll
@@ -497,25 +525,35 @@ void conv_mfma_kernel(ConvParams p) {
       pre[j] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(in_rsrc, off, c0 * 4, 0));
     }
   };
-  // one float4 of patch channels into the patch buffer, in the operand mode's format
+  // one float4 of patch channels into the patch buffer, as the operand mode's bf16 parts
   auto put = [&](int off, const float4& x) {
-    if (SPLIT) {
-      // x = hi + lo + O(2^-17 |x|): hi = bf16(x), lo = bf16(x - hi)
-      uint2 h, l;
-      h.x = pack_bf16x2(x.x, x.y);
-      h.y = pack_bf16x2(x.z, x.w);
-      l.x = pack_bf16x2(x.x - __uint_as_float(h.x << 16), x.y - __uint_as_float(h.x & 0xffff0000u));
-      l.y = pack_bf16x2(x.z - __uint_as_float(h.y << 16), x.w - __uint_as_float(h.y & 0xffff0000u));
+    uint2 h, m, l;
+    h.x = pack_bf16x2(x.x, x.y);
+    h.y = pack_bf16x2(x.z, x.w);
+    if (PARTS == 1) {
       *(uint2*)&s_mem[off] = h;
-      *(uint2*)&s_mem[off + LO] = l;
-    } else if (BF16) {
-      uint2 w;
-      w.x = pack_bf16x2(x.x, x.y);
-      w.y = pack_bf16x2(x.z, x.w);
-      *(uint2*)&s_mem[off] = w;
-    } else {
-      *(float4*)&s_mem[off] = x;
+      return;
     }
+    // x = hi + mid (+ lo): each part the bf16 rounding of what the parts before it leave (the
+    // subtractions are exact); three parts hold all 24 bits of an fp32 value
+    float4 r = make_float4(x.x - __uint_as_float(h.x << 16), x.y - __uint_as_float(h.x & 0xffff0000u),
+                           x.z - __uint_as_float(h.y << 16), x.w - __uint_as_float(h.y & 0xffff0000u));
+    m.x = pack_bf16x2(r.x, r.y);
+    m.y = pack_bf16x2(r.z, r.w);
+    if (PARTS == 3) {
+      l.x = pack_bf16x2(r.x - __uint_as_float(m.x << 16), r.y - __uint_as_float(m.x & 0xffff0000u));
+      l.y = pack_bf16x2(r.z - __uint_as_float(m.y << 16), r.w - __uint_as_float(m.y & 0xffff0000u));
+      // values that a bf16 cannot round without overflow, and infinities (a NaN makes every part NaN)
+      if (fmaxf(fmaxf(fabsf(x.x), fabsf(x.y)), fmaxf(fabsf(x.z), fabsf(x.w))) >= kBf16Overflow) {
+        split3_large(x.x, 0, h.x, m.x, l.x);
+        split3_large(x.y, 16, h.x, m.x, l.x);
+        split3_large(x.z, 0, h.y, m.y, l.y);
+        split3_large(x.w, 16, h.y, m.y, l.y);
+      }
+      *(uint2*)&s_mem[off + 2 * LO] = l;
+    }
+    *(uint2*)&s_mem[off] = h;
+    *(uint2*)&s_mem[off + LO] = m;
   };
   auto stash = [&](int c0) {
     if (tail) {  // (uniform; nets with c_in % 4 == 0 pay nothing)
@@ -564,16 +602,15 @@ void conv_mfma_kernel(ConvParams p) {
   floatx16 acc0, acc1;
 #pragma unroll
   for (int i = 0; i < 16; ++i) { acc0[i] = 0.0f; acc1[i] = 0.0f; }
-  floatx4 c16a = {0.f, 0.f, 0.f, 0.f}, c16b = {0.f, 0.f, 0.f, 0.f};  // NB == 16: the two 16-row blocks
-  // operand lane: k-group `half` (two groups of 32 lanes, or four of 16), row / column m of the block
-  const int half = NB == 16 ? lane >> 4 : lane >> 5, m = NB == 16 ? lane & 15 : lane & 31;
+  // operand lane: k-group `half` (two groups of 32 lanes), row / column m of the block
+  const int half = lane >> 5, m = lane & 31;
   const int mly = m >> 3, mlx = m & 7;  // site of this lane inside a block
   const int cop = p.c_out_pad;
   const int n_units = K * K * KG;
   const int cin_pad = (Cin + CHUNK - 1) / CHUNK * CHUNK;    // the weights are zero-padded to whole chunks
-  const int cin_rows = BF16 ? cin_pad >> 3 : cin_pad >> 2;  // 16-byte weight rows per tap: 8 bf16 or 4 floats
+  const int cin_rows = cin_pad >> 3;                        // 16-byte weight rows per tap: 8 bf16
   const int a_lane_off = mly * s * RP + mlx * s * CS + half * 4;
-  const int a_blk1 = (NB == 16 ? 2 : 4) * s * RP;  // the second block starts four (two) tile rows further down
+  const int a_blk1 = 4 * s * RP;  // the second block starts four tile rows further down
   // units of this wave: u_j = wave + j * NW, j < n_mine
   const int n_mine = (n_units - wave + NW - 1) / NW;
   const int last = n_mine - 1;
@@ -584,8 +621,8 @@ void conv_mfma_kernel(ConvParams p) {
   // unit costs one vector add: vector-ALU time is taken from the fp32 matrix instructions.
   // B: buffer load with the lane part as vector offset and the unit part as scalar offset
   // (bytes; the launcher checks that the re-laid weights stay below 2 GiB).
-  const unsigned w_plane = (unsigned)(K * K * cin_rows * cop) * 16u;  // split mode: the low-part plane follows
-  const unsigned w_set = w_plane * (SPLIT ? 2u : 1u);  // one weight set; a folded workgroup takes its phase's
+  const unsigned w_plane = (unsigned)(K * K * cin_rows * cop) * 16u;  // the planes of the parts follow each other
+  const unsigned w_set = w_plane * PARTS;  // one weight set; a folded workgroup takes its phase's
   const char* const w_base = fold ? (const char*)p.w_fold + (size_t)(fpy * 2 + fpx) * w_set : (const char*)p.w;
   const __amdgpu_buffer_rsrc_t w_rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)w_base, 0, (int)w_set, 0x00020000);
   const unsigned w_lane = (unsigned)(half * cop + co0 + m) * 16u;
@@ -594,12 +631,15 @@ void conv_mfma_kernel(ConvParams p) {
   auto b_load = [&](int c0, int j) {
     const int u = wave + min(j, last) * NW;
     const int tap = u / KG, kg = u % KG;
-    const int row0 = BF16 ? (c0 >> 3) : (c0 >> 2);
-    constexpr int kRowsPerUnit = BF16 ? UCH / 8 : UCH / 4;  // 16-byte weight rows of a unit
-    const unsigned soff = (unsigned)__builtin_amdgcn_readfirstlane(((tap * cin_rows + row0 + kg * kRowsPerUnit) * cop) << 4);
+    constexpr int kRowsPerUnit = UCH / 8;  // 16-byte weight rows of a unit
+    const unsigned soff =
+        (unsigned)__builtin_amdgcn_readfirstlane(((tap * cin_rows + (c0 >> 3) + kg * kRowsPerUnit) * cop) << 4);
     BFrag f;
     f.h = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(w_rsrc, w_lane, soff, 0));
-    f.l = SPLIT ? __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(w_rsrc, w_lane, soff + w_plane, 0)) : f.h;
+    f.m = f.l = f.h;
+    if (PARTS == 3) f.m = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(w_rsrc, w_lane, soff + w_plane, 0));
+    if (PARTS >= 2)
+      f.l = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(w_rsrc, w_lane, soff + (PARTS - 1) * w_plane, 0));
     return f;
   };
   // ... and LDS offset of its A fragment
@@ -607,86 +647,74 @@ void conv_mfma_kernel(ConvParams p) {
     const int u = wave + j * NW;
     const int tap = u / KG, kg = u % KG;
     const int ky = (tap * k_magic) >> 16, kx = tap - ky * K;
-    return a_lane_off + __builtin_amdgcn_readfirstlane(ky * RP + kx * CS + kg * (NB == 16 ? 16 : 8));  // words of a unit: 8 floats, 16 bf16 or 16 floats
+    return a_lane_off + __builtin_amdgcn_readfirstlane(ky * RP + kx * CS + kg * 8);  // words of a unit's 16 bf16
   };
-  // A fragment of unit j (clamped like the B fragments): the patch values of this lane's site
-  // for both 32-row blocks, and their low parts in split mode; unused members cost nothing
+  // A fragment of unit j (clamped like the B fragments): the parts of this lane's site in both
+  // 32-row blocks; unused members cost nothing
   auto a_load = [&](int j) {
     AFrag f;
     const float* ap = &s_mem[a_off(min(j, last))];
     f.h0 = *(const float4*)ap;
-    f.h1 = (MB == 2 || NB == 16) ? *(const float4*)(ap + a_blk1) : f.h0;
-    f.l0 = SPLIT ? *(const float4*)(ap + LO) : f.h0;
-    f.l1 = (SPLIT && MB == 2) ? *(const float4*)(ap + a_blk1 + LO) : f.h0;
+    f.h1 = MB == 2 ? *(const float4*)(ap + a_blk1) : f.h0;
+    f.m0 = PARTS == 3 ? *(const float4*)(ap + LO) : f.h0;
+    f.m1 = (PARTS == 3 && MB == 2) ? *(const float4*)(ap + a_blk1 + LO) : f.h0;
+    f.l0 = PARTS >= 2 ? *(const float4*)(ap + (PARTS - 1) * LO) : f.h0;
+    f.l1 = (PARTS >= 2 && MB == 2) ? *(const float4*)(ap + a_blk1 + (PARTS - 1) * LO) : f.h0;
     return f;
   };
-  auto unit = [&](const AFrag& af, const BFrag& bf) {
-    const float4& b = bf.h;
-    const float4 a0 = af.h0, a1 = af.h1;
-    if (NB == 16) {
-      c16a = __builtin_amdgcn_mfma_f32_16x16x4f32(a0.x, b.x, c16a, 0, 0, 0);
-      c16b = __builtin_amdgcn_mfma_f32_16x16x4f32(a1.x, b.x, c16b, 0, 0, 0);
-      c16a = __builtin_amdgcn_mfma_f32_16x16x4f32(a0.y, b.y, c16a, 0, 0, 0);
-      c16b = __builtin_amdgcn_mfma_f32_16x16x4f32(a1.y, b.y, c16b, 0, 0, 0);
-      c16a = __builtin_amdgcn_mfma_f32_16x16x4f32(a0.z, b.z, c16a, 0, 0, 0);
-      c16b = __builtin_amdgcn_mfma_f32_16x16x4f32(a1.z, b.z, c16b, 0, 0, 0);
-      c16a = __builtin_amdgcn_mfma_f32_16x16x4f32(a0.w, b.w, c16a, 0, 0, 0);
-      c16b = __builtin_amdgcn_mfma_f32_16x16x4f32(a1.w, b.w, c16b, 0, 0, 0);
-      return;
+  auto mm = [](floatx16& acc, const float4& a, const float4& b) {
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), acc, 0, 0, 0);
+  };
+  // products of one unit, the smallest terms first; what is left out is 2^-16 (split) or 2^-25
+  // (fp32 mode: the order of the rounding of an fp32 product) of the product
+  auto unit = [&](const AFrag& a, const BFrag& b) {
+    if (PARTS == 3) {
+      mm(acc0, a.l0, b.h);
+      if (MB == 2) mm(acc1, a.l1, b.h);
+      mm(acc0, a.m0, b.m);
+      if (MB == 2) mm(acc1, a.m1, b.m);
+      mm(acc0, a.h0, b.l);
+      if (MB == 2) mm(acc1, a.h1, b.l);
+      mm(acc0, a.m0, b.h);
+      if (MB == 2) mm(acc1, a.m1, b.h);
+      mm(acc0, a.h0, b.m);
+      if (MB == 2) mm(acc1, a.h1, b.m);
     }
-    if (SPLIT) {
-      // a * b ~ a_lo * b_hi + a_hi * b_lo + a_hi * b_hi (the low x low term, 2^-16 smaller, is dropped)
-      const bf16x8 bh = __builtin_bit_cast(bf16x8, bf.h), bl = __builtin_bit_cast(bf16x8, bf.l);
-      const bf16x8 a0h = __builtin_bit_cast(bf16x8, a0);
-      const bf16x8 a0l = __builtin_bit_cast(bf16x8, af.l0);
-      acc0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0l, bh, acc0, 0, 0, 0);
-      acc0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0h, bl, acc0, 0, 0, 0);
-      acc0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0h, bh, acc0, 0, 0, 0);
+    if (PARTS == 2) {
+      mm(acc0, a.l0, b.h);
+      mm(acc0, a.h0, b.l);
+      mm(acc0, a.h0, b.h);
       if (MB == 2) {
-        const bf16x8 a1h = __builtin_bit_cast(bf16x8, a1);
-        const bf16x8 a1l = __builtin_bit_cast(bf16x8, af.l1);
-        acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1l, bh, acc1, 0, 0, 0);
-        acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1h, bl, acc1, 0, 0, 0);
-        acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1h, bh, acc1, 0, 0, 0);
+        mm(acc1, a.l1, b.h);
+        mm(acc1, a.h1, b.l);
+        mm(acc1, a.h1, b.h);
       }
       return;
     }
-    if (BF16) {
-      const bf16x8 bb = __builtin_bit_cast(bf16x8, b);
-      acc0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a0), bb, acc0, 0, 0, 0);
-      if (MB == 2) acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a1), bb, acc1, 0, 0, 0);
-      return;
-    }
-    acc0 = __builtin_amdgcn_mfma_f32_32x32x2f32(a0.x, b.x, acc0, 0, 0, 0);
-    if (MB == 2) acc1 = __builtin_amdgcn_mfma_f32_32x32x2f32(a1.x, b.x, acc1, 0, 0, 0);
-    acc0 = __builtin_amdgcn_mfma_f32_32x32x2f32(a0.y, b.y, acc0, 0, 0, 0);
-    if (MB == 2) acc1 = __builtin_amdgcn_mfma_f32_32x32x2f32(a1.y, b.y, acc1, 0, 0, 0);
-    acc0 = __builtin_amdgcn_mfma_f32_32x32x2f32(a0.z, b.z, acc0, 0, 0, 0);
-    if (MB == 2) acc1 = __builtin_amdgcn_mfma_f32_32x32x2f32(a1.z, b.z, acc1, 0, 0, 0);
-    acc0 = __builtin_amdgcn_mfma_f32_32x32x2f32(a0.w, b.w, acc0, 0, 0, 0);
-    if (MB == 2) acc1 = __builtin_amdgcn_mfma_f32_32x32x2f32(a1.w, b.w, acc1, 0, 0, 0);
+    mm(acc0, a.h0, b.h);
+    if (MB == 2) mm(acc1, a.h1, b.h);
   };
 
   // Ring of three weight fragments, two units of look-ahead, no register copies: vector loads
   // complete in order, so each wait only covers loads issued two units earlier.  The first two
   // fragments of a chunk are requested before the barriers that precede it.
   BFrag bq0, bq1, bq2;
-  bq0.h = bq0.l = make_float4(0.f, 0.f, 0.f, 0.f);
+  bq0.h = bq0.m = bq0.l = make_float4(0.f, 0.f, 0.f, 0.f);
   bq1 = bq0;
   bq2 = bq0;
   EVK_PHASE(kPhAddressed);
   if (conv_on) {
-    fetch(0);
+    fetch(c_lo);
     if (n_mine > 0) {
-      bq0 = b_load(0, 0);
-      bq1 = b_load(0, 1);
+      bq0 = b_load(c_lo, 0);
+      bq1 = b_load(c_lo, 1);
     }
   }
   EVK_PHASE(kPhFirstIssued);
 #ifdef EVCONV_PHASE_STAMPS
   unsigned long long ph_contract = 0, ph_change = 0;
 #endif
-  for (int c0 = 0; conv_on && c0 < Cin; c0 += CHUNK) {
+  for (int c0 = c_lo; conv_on && c0 < c_hi; c0 += CHUNK) {
 #ifdef EVCONV_PHASE_STAMPS
     const unsigned long long ph_a = wall_clock64();
 #endif
@@ -697,18 +725,18 @@ void conv_mfma_kernel(ConvParams p) {
       interpolate();
       __syncthreads();
     }
-    const bool more = c0 + CHUNK < Cin;
+    const bool more = c0 + CHUNK < c_hi;
     if (more) fetch(c0 + CHUNK);  // next chunk's patch, in flight during the contraction
 #ifdef EVCONV_PHASE_STAMPS
     const unsigned long long ph_b = wall_clock64();
     ph_change += ph_b - ph_a;
-    if (c0 == 0) EVK_PHASE(kPhFirstPatchInLds);
+    if (c0 == c_lo) EVK_PHASE(kPhFirstPatchInLds);
 #endif
     if (n_mine <= 0) continue;    // more waves than units (1 x 1 taps): only help with the gather
-    // fp32 and bf16 modes: the A fragments run one unit ahead of their use (three names, two alive
-    // at a time), so that an LDS read is in flight during the matrix instructions of the unit
-    // before it.  Split mode has no registers to spare for that and reads each fragment at its use.
-    constexpr bool APIPE = !SPLIT;
+    // bf16 mode: the A fragments run one unit ahead of their use (three names, two alive at a time),
+    // so that an LDS read is in flight during the matrix instructions of the unit before it.  The
+    // modes with several parts have no registers to spare for that and read each fragment at its use.
+    constexpr bool APIPE = PARTS == 1;
     int j = 0;
     AFrag aq0 = a_load(0), aq1 = aq0, aq2 = aq0;
     auto step = [&](AFrag& cur, AFrag& nxt, int jj, const BFrag& b) {
@@ -744,6 +772,9 @@ void conv_mfma_kernel(ConvParams p) {
   // operands of the fused ADD stages, requested together now so that one memory latency covers
   // all of them and the reduction below hides part of it
   float f_skip[kMaxFusedAdds][EP_ITERS], f_zold[kMaxFusedAdds][EP_ITERS];
+  float sp_delta[EP_ITERS];  // residuals and rounding step of a fused sparsification layer
+  float sp_k = 0.0f;
+  auto request_fused = [&]() {
 #pragma unroll
   for (int f = 0; f < kMaxFusedAdds; ++f) {
 #pragma unroll
@@ -760,9 +791,6 @@ void conv_mfma_kernel(ConvParams p) {
     }
   }
 
-  // residuals and rounding step of a fused sparsification layer
-  float sp_delta[EP_ITERS];
-  float sp_k = 0.0f;
 #pragma unroll
   for (int it = 0; it < EP_ITERS; ++it) sp_delta[it] = 0.0f;
   if (p.sp.delta && !p.dense) {
@@ -772,44 +800,32 @@ void conv_mfma_kernel(ConvParams p) {
     for (int it = 0; it < EP_ITERS; ++it) sp_delta[it] = ep_load(d_rsrc, sp_k > 0.0f && has(site_mine, it), it);
   }
 
+  };
+  if (!KSP) request_fused();
   EVK_PHASE(kPhFusedRequested);
   // ---- reduce the NW partial sums through LDS: slots [4][block*16 + reg][lane]
-  auto spill = [&](float* part) {
-    if (NB == 16) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        part[i * 64 + lane] = c16a[i];
-        part[(4 + i) * 64 + lane] = c16b[i];
-      }
-      return;
-    }
+  // (fp32 mode: the weights of the odd waves' units are stored negated, see conv_mfma_negated)
+  auto spill = [&](float* part, bool negate) {
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
-      part[i * 64 + lane] = acc0[i];
-      if (MB == 2) part[(16 + i) * 64 + lane] = acc1[i];
+      part[i * 64 + lane] = negate ? -acc0[i] : acc0[i];
+      if (MB == 2) part[(16 + i) * 64 + lane] = negate ? -acc1[i] : acc1[i];
     }
   };
   __syncthreads();
   if (NW == 8) {
-    if (wave >= 4) spill(s_mem + (wave - 4) * SLOT);
+    if (wave >= 4) spill(s_mem + (wave - 4) * SLOT, false);
     __syncthreads();
     if (wave < 4) {
       const float* part = s_mem + wave * SLOT;
-      if (NB == 16) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          c16a[i] += part[i * 64 + lane];
-          c16b[i] += part[(4 + i) * 64 + lane];
-        }
-      }
-#pragma unroll
-      for (int i = 0; i < (NB == 16 ? 0 : 16); ++i) {
+      for (int i = 0; i < 16; ++i) {
         acc0[i] += part[i * 64 + lane];
         if (MB == 2) acc1[i] += part[(16 + i) * 64 + lane];
       }
     }
   }
-  if (wave < 4) spill(s_mem + wave * SLOT);
+  if (wave < 4) spill(s_mem + wave * SLOT, PARTS == 3 && (wave & 1));
   __syncthreads();
   EVK_PHASE(kPhReduced);
 #ifdef EVCONV_PHASE_STAMPS
@@ -827,9 +843,7 @@ void conv_mfma_kernel(ConvParams p) {
   const __amdgpu_buffer_rsrc_t o_rsrc = out_rsrc(at_stream(p.out, so));
   // partial sum of local site ls = it * EP_SITES + es: the part of the LDS offset that depends on
   // the thread (es < 16), the rest is a constant per `it`
-  // (NB == 16: element (block b, register i, lane l) is local site 16 b + 4 (l / 16) + i, channel l % 16)
-  const int off_mine = NB == 16 ? ((es >> 4) * 4 + (es & 3)) * 64 + ((es >> 2) & 3) * 16 + co
-                                : ((es >> 3) * 4 + (es & 3)) * 64 + ((es >> 2) & 1) * 32 + co;
+  const int off_mine = ((es >> 3) * 4 + (es & 3)) * 64 + ((es >> 2) & 1) * 32 + co;
   const float bias = (p.dense && p.bias && co_ok) ? p.bias[co0 + co] : 0.0f;
   // Straight-line code: a site this thread does not own gets an out-of-range offset (its stores
   // are dropped) instead of a branch around it, and the partial sums of all passes are read from
@@ -838,9 +852,50 @@ void conv_mfma_kernel(ConvParams p) {
 #pragma unroll
   for (int it = 0; it < EP_ITERS; ++it) {
     constexpr int kRow = EP_SITES / 8;  // tile rows per `it`
-    const int off = NB == 16 ? off_mine + it * (EP_SITES / 16) * 4 * 64
-                             : off_mine + (((it * kRow) >> 2) * 16 + ((it * kRow) & 3) * 4) * 64;
+    const int off = off_mine + (((it * kRow) >> 2) * 16 + ((it * kRow) & 3) * 4) * 64;
     v_sum[it] = (s_mem[off] + s_mem[off + SLOT]) + (s_mem[off + 2 * SLOT] + s_mem[off + 3 * SLOT]);
+  }
+  if (KSP) {
+    if (conv_on) {
+      // This workgroup's share of the sums goes to memory; the last of the p.ks workgroups to arrive
+      // (a counter that it resets) adds all shares in the order of the channels, whatever the order
+      // of arrival, and runs the epilogue; nobody waits for anybody.  Shares and counter are
+      // written and read with device-scope accesses, which go past the XCDs' own L2s, and a share
+      // is complete (s_waitcnt, all waves) before the counter is touched.  A fence would instead
+      // write back and invalidate a whole L2, weights included.
+      const size_t out_blk = (size_t)wg_tile * n_co + wg_co;
+      float* const share = at_stream(p.ks_part, so) + out_blk * p.ks * (NSITES * NB) + tid;
+#pragma unroll
+      for (int it = 0; it < EP_ITERS; ++it)
+        __hip_atomic_store(share + (size_t)ks * (NSITES * NB) + it * NT, v_sum[it], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      __syncthreads();
+      if (tid == 0) {
+        unsigned* const cnt = at_stream(p.ks_count, so) + out_blk;
+        const unsigned before = __hip_atomic_fetch_add(cnt, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (before == (unsigned)p.ks - 1u) __hip_atomic_store(cnt, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        s_rows[0] = before;
+      }
+      __syncthreads();
+      if (s_rows[0] != (unsigned)p.ks - 1u) return;
+      request_z();
+      request_fused();
+      asm volatile("" ::: "memory");
+      float add[EP_ITERS];
+#pragma unroll
+      for (int it = 0; it < EP_ITERS; ++it) v_sum[it] = 0.0f;
+#pragma unroll 2
+      for (int q = 0; q < p.ks; ++q) {
+#pragma unroll
+        for (int it = 0; it < EP_ITERS; ++it)
+          add[it] = __hip_atomic_load(share + (size_t)q * (NSITES * NB) + it * NT, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+        for (int it = 0; it < EP_ITERS; ++it) v_sum[it] += add[it];
+      }
+    } else {
+      request_z();
+      request_fused();
+    }
   }
   auto ep_store_at = [&](const __amdgpu_buffer_rsrc_t& r, unsigned voff, int it, float v) {
     __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), r, voff, it * ep_step, 0);
@@ -986,11 +1041,7 @@ void conv_mfma_kernel(ConvParams p) {
 #pragma unroll
     for (int it = 0; it < EP_ITERS; ++it) {
       const uint64_t b = __ballot(((mine_bits >> (it * EP_SITES)) & 1ull) != 0);
-      if (NB == 16)  // four sites of 16 lanes each
-        w |= (uint64_t)(((b & 0xffffull) ? 1u : 0u) | ((b & 0xffff0000ull) ? 2u : 0u) | ((b & 0xffff00000000ull) ? 4u : 0u) |
-                        ((b >> 48) ? 8u : 0u)) << (it * EP_SITES);
-      else
-        w |= (uint64_t)(((unsigned)b != 0 ? 1u : 0u) | ((unsigned)(b >> 32) != 0 ? 2u : 0u)) << (it * EP_SITES);
+      w |= (uint64_t)(((unsigned)b != 0 ? 1u : 0u) | ((unsigned)(b >> 32) != 0 ? 2u : 0u)) << (it * EP_SITES);
     }
     if (lane == 0) s_nz[slot * NW + wave] = w << (r0 * 8 + (64 / NB) * wave);
   };
@@ -1069,11 +1120,11 @@ inline int chunk_for(const ConvParams& p) {
   return 16;
 }
 
-template <int CHUNK, int NW, int OPM, int MB, int NB = 32>
+template <int CHUNK, int NW, int OPM, int MB, bool KSP = false, int S2K = 0>
 void launch_variant(const ConvParams& p, hipStream_t s) {
   const int PH = (4 * MB - 1) * p.stride + p.k, PW = 7 * p.stride + p.k;
   // (rows of the patch are padded to a pitch of 32 modulo 64 words: at most 64 more per row)
-  size_t lds = (size_t)PH * (PW * (OPM == kOpBf16 ? CHUNK / 2 + 4 : CHUNK + 4) + 64) * sizeof(float);
+  size_t lds = (size_t)PH * (PW * patch_site_words(CHUNK, OPM) + 64) * sizeof(float);
   const size_t part = (size_t)4 * MB * 16 * 64 * sizeof(float);  // partial sums reuse the patch
   // The operand that is read by every XCD in full should be the smaller one: the weights of the
   // high-resolution layers, the input of the low-resolution ones (k * k * c_out weights per input
@@ -1082,8 +1133,9 @@ void launch_variant(const ConvParams& p, hipStream_t s) {
   ConvParams q = p;
   const long long in_sites = p.upsample ? (long long)p.lo_h * p.lo_w : (long long)p.gi.h * p.gi.w;
   q.wg_swap = (long long)p.k * p.k * p.go.c > in_sites && p.go.tiles() * (2 / MB) <= 65535;
-  dim3 grid(p.go.tiles() * (2 / MB), p.c_out_pad / NB, p.st.n);
-  if (q.wg_swap) grid = dim3(p.c_out_pad / NB, p.go.tiles() * (2 / MB), p.st.n);
+  const int n_ck = p.c_out_pad / 32 * (KSP ? p.ks : 1);
+  dim3 grid(p.go.tiles() * (2 / MB), n_ck, p.st.n);
+  if (q.wg_swap) grid = dim3(n_ck, p.go.tiles() * (2 / MB), p.st.n);
   if (CHUNK == 32 && p.upsample) {
     // the low-resolution source region behind the patch buffer
     lds += (size_t)(PH / 2 + 3) * (PW / 2 + 3) * (CHUNK + 4) * sizeof(float);
@@ -1092,7 +1144,7 @@ void launch_variant(const ConvParams& p, hipStream_t s) {
     return;
   }
   if (lds < part) lds = part;
-  hipLaunchKernelGGL((conv_mfma_kernel<CHUNK, NW, OPM, MB, false, NB>), grid, dim3(NW * 64), lds, s, q);
+  hipLaunchKernelGGL((conv_mfma_kernel<CHUNK, NW, OPM, MB, false, KSP, S2K>), grid, dim3(NW * 64), lds, s, q);
 }
 
 // share of the chip's 256 CUs kept busy when n equally long workgroups run at once
@@ -1108,32 +1160,54 @@ void launch_shape(const ConvParams& p, hipStream_t s) {
   bool halves = !(n2 >= 512 && p.k * p.k * p.gi.c >= 1600) || fill(2 * n2) > fill(n2) + 0.1;
   const long long n = halves ? 2 * n2 : n2;
   bool eight = n < 512;  // few workgroups: 8 waves each split K further
-  // fp32, few half-tile workgroups that fill the chip unevenly (384 on 256 CUs: half of the CUs get
-  // two; 32 or 128: most CUs get none): blocks of 16 output channels instead of 32, twice the
-  // workgroups at half the work.  Four waves each where that gives three workgroups per CU, eight
-  // where the chip still is not full.  Measured: the 32 x 44 layers of the depth net 37 / 28 -> 32 /
-  // 26 us, the 16 x 16 x 512 layers of the flow net 30 -> 23.5 us, ResNet-18's 7 x 7 x 512 layers
-  // 29 -> 21 us.
-  constexpr int kNarrowBlock = OPM == kOpF32 ? 16 : 32;
-  if (OPM == kOpF32 && halves && eight && !p.upsample && fill(2 * n) > fill(n) + 0.1) {
-    if (2 * n <= 256) launch_variant<CHUNK, 8, OPM, 1, kNarrowBlock>(p, s);
-    else launch_variant<CHUNK, 4, OPM, 1, kNarrowBlock>(p, s);
+  if (CHUNK == 128) {  // chosen only for few workgroups: other variants are not built
+    launch_variant<CHUNK, 8, OPM, 1>(p, s);
     return;
   }
-  if (CHUNK == 128) {  // chosen only for few workgroups: the 4-wave variants are not built
-    if (halves) launch_variant<CHUNK, 8, OPM, 1>(p, s); else launch_variant<CHUNK, 8, OPM, 2>(p, s);
-    return;
-  }
-  constexpr int NW4 = CHUNK == 128 ? 8 : 4;
+  constexpr int NW4 = CHUNK == 128 ? 8 : 4, MB2 = CHUNK == 128 ? 1 : 2;
   if (halves) {
     if (eight) launch_variant<CHUNK, 8, OPM, 1>(p, s); else launch_variant<CHUNK, NW4, OPM, 1>(p, s);
   } else {
-    if (eight) launch_variant<CHUNK, 8, OPM, 2>(p, s); else launch_variant<CHUNK, NW4, OPM, 2>(p, s);
+    if (eight) launch_variant<CHUNK, 8, OPM, MB2>(p, s); else launch_variant<CHUNK, NW4, OPM, MB2>(p, s);
   }
+}
+
+// Launches with few workgroups (maps of a few tiles) are bound by what one workgroup does in
+// sequence: a round trip per channel chunk, and weights that only the occupied CUs stream in (a 7 x 7
+// x 512 layer: 32 workgroups, 0.9 MB of fp32-mode weights through each CU's L1).  Splitting the
+// channels over workgroups too turns the chunks into parallel round trips and spreads the weights;
+// it costs the exchange of the shares, about 3 us at the end of the workgroup.  The split fills the
+// chip's 512 resident 8-wave workgroups and stops there: beyond them it only adds exchanges
+// (measured, us per layer in fp32 mode, not split / 512 / 768 workgroups: 512 channels on 7 x 7
+// 22.2 / 14.4 / 14.3; 512 on 16 x 16 23.9 / 18.7 / 18.5; 256 on 14 x 14 15.2 / 13.0 / 13.2; 768 -> 256 on 32 x
+// 32 33.2 / 31.4 / 38.8; 256 on 32 x 44 20.4 / not split / 27.3; four waves per workgroup are slower
+// on all of them).  Chunks of 64 channels (5 x 5 at stride 2: 32).
+struct KSplit { int chunk = 0, chunks_each = 0, ks = 0; };  // ks == 0: not split
+inline KSplit ksplit_for(const ConvParams& p) {
+  KSplit r;
+  const long long n = 2ll * p.go.tiles() * (p.c_out_pad / 32) * p.st.n;  // half-tile workgroups
+  if (p.k <= 3 && p.gi.c % 64 == 0) r.chunk = 64;
+  else if (p.stride == 2 && p.k <= 5 && p.gi.c % 32 == 0) r.chunk = 32;
+  else return r;
+  const int chunks = p.gi.c / r.chunk;
+  const int want = (int)std::min<long long>(chunks, 512 / n);
+  if (want < 2) return r;
+  r.chunks_each = (chunks + want - 1) / want;
+  r.ks = (chunks + r.chunks_each - 1) / r.chunks_each;
+  return r;
 }
 
 template <int OPM>
 void launch_any(const ConvParams& p, hipStream_t s) {
+  const KSplit r = p.upsample ? KSplit() : ksplit_for(p);
+  if (r.ks) {
+    ConvParams q = p;
+    q.ks = r.ks; q.ks_chunks = r.chunks_each;
+    if (r.chunk == 64 && p.stride == 1) launch_variant<64, 8, OPM, 1, true, 0>(q, s);
+    else if (r.chunk == 64) launch_variant<64, 8, OPM, 1, true, 3>(q, s);
+    else launch_variant<32, 8, OPM, 1, true, 5>(q, s);
+    return;
+  }
   switch (chunk_for(p)) {
     case 128: launch_shape<128, OPM>(p, s); break;
     case 64: launch_shape<64, OPM>(p, s); break;

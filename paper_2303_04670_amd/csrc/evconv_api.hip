@@ -43,6 +43,33 @@ uint16_t to_bf16(float x) {
   return (uint16_t)((u + 0x7fffu + ((u >> 16) & 1u)) >> 16);
 }
 
+// Eight weights, each as the sum of `parts` bf16 values (matrix-core kernels): a part is the
+// rounding of what the ones before it leave, so three of them hold an fp32 value exactly; part q
+// of the eight goes to at[q * plane ..].  Three parts are for finite values only: one that would
+// round to an infinite bf16 is cut off instead.  (Loops without branches: a net has millions of
+// weights and this is most of the time that create takes.)
+void weight_parts8(const float* v, int parts, uint16_t* at, size_t plane) {
+  float rest[8];
+  memcpy(rest, v, sizeof rest);
+  for (int q = 0; q < parts; ++q) {
+    uint16_t h[8];
+    for (int e = 0; e < 8; ++e) {
+      uint32_t u;
+      memcpy(&u, &rest[e], 4);
+      uint32_t b = (u + 0x7fffu + ((u >> 16) & 1u)) >> 16;
+      b = (u & 0x7fffffffu) > 0x7f800000u ? 0x7fc0u : b;
+      b -= parts == 3 && (b & 0x7fffu) == 0x7f80u ? 1u : 0u;
+      h[e] = (uint16_t)b;
+      const uint32_t back = b << 16;
+      float f;
+      memcpy(&f, &back, 4);
+      rest[e] -= f;
+    }
+    memcpy(at + q * plane, h, sizeof h);
+  }
+}
+int weight_part_count(int wdtype) { return wdtype == EVCONV_F32 ? 3 : wdtype == EVCONV_F32_SPLIT ? 2 : 1; }
+
 struct NodePlan {
   evconv_node_desc d;
   Geo ga, gb, go;
@@ -85,6 +112,7 @@ struct Layout {
   size_t off_x_prev = 0, off_dx = 0, off_occ_in = 0, off_idx_in = 0, off_count_in = 0, off_bitmap_in = 0;
   size_t off_occ_nodes = 0, n_occ_words = 0;  // contiguous occupancy region of all nodes
   size_t off_sets = 0, off_rms = 0;
+  size_t off_ks_part = 0, off_ks_count = 0;  // scratch of convs whose channels are split over workgroups
   size_t stride = 0;   // bytes of one stream's state (the weights live in stream 0's copy)
   int n_streams = 1;
   size_t total = 0;
@@ -269,14 +297,16 @@ evconv_status make_layout(const evconv_net_desc* desc, size_t weight_bytes, bool
     n.off_bitmap = b.take(((size_t)n.go.tiles() + 63) / 64 * 8);
     if (n.d.op == EVCONV_OP_CONV2D || n.d.op == EVCONV_OP_LINEAR) {
       const int k = n.d.kh;
-      // room for input channels padded to whole chunks (at most 64) or a padded flattened contraction
-      n.off_w = b.take(std::max(((size_t)k * k * ((n.d.c_in + 63) / 64 * 64) + 16) * n.c_out_pad * 4,
-                                conv_narrow_weight_floats(n.c_out_pad) * 4));  // (the narrow-input kernel's per-lane layout)
+      // room for input channels padded to whole chunks (at most 64), three bf16 parts each at most,
+      // or a padded flattened contraction (the narrow-input kernel's per-lane layout)
+      n.off_w = b.take(std::max(((size_t)k * k * ((n.d.c_in + 63) / 64 * 64) + 16) * n.c_out_pad *
+                                    (n.d.wdtype == EVCONV_F32 ? 6 : 4),
+                                conv_narrow_weight_floats(n.c_out_pad) * 4));
       if (n.d.bias_off >= 0) n.off_bias = b.take((size_t)n.d.c_out * 4);
       if (n.d.op == EVCONV_OP_CONV2D && k == 5 && n.d.stride == 1 && n.d.pad == 2 && n.d.in0 >= 0 &&
           L->nodes[n.d.in0].d.op == EVCONV_OP_UPSAMPLE_BILINEAR2X) {
         // four phases x (4 x 4 taps) x input channels padded to 32 (see the planner in evconv_create)
-        n.off_w_fold = b.take((size_t)4 * 16 * ((n.d.c_in + 31) / 32 * 32) * n.c_out_pad * 4);
+        n.off_w_fold = b.take((size_t)4 * 16 * ((n.d.c_in + 31) / 32 * 32) * n.c_out_pad * (n.d.wdtype == EVCONV_F32 ? 6 : 4));
         n.off_fold_list = b.take((size_t)n.go.tiles() * 4);
       }
     }
@@ -285,6 +315,20 @@ evconv_status make_layout(const evconv_net_desc* desc, size_t weight_bytes, bool
       n.off_dy = b.take(elems * 4);
     }
   }
+  size_t ks_floats = 0, ks_counters = 0;  // (the layers run one after the other: one scratch for all)
+  for (int i = 0; i < desc->n_nodes; ++i) {
+    const NodePlan& n = L->nodes[i];
+    if (n.d.op != EVCONV_OP_CONV2D && n.d.op != EVCONV_OP_LINEAR) continue;
+    ConvParams probe;
+    probe.gi = n.ga; probe.go = n.go; probe.k = n.d.kh; probe.stride = n.d.stride; probe.c_out_pad = n.c_out_pad;
+    probe.n_fused = 0; probe.pad = n.d.pad; probe.st = Streams{0, desc->n_streams > 0 ? desc->n_streams : 1};
+    size_t f = 0, c = 0;
+    if (conv_mfma_f32_supported(probe)) conv_mfma_split_scratch(probe, &f, &c);
+    ks_floats = std::max(ks_floats, f);
+    ks_counters = std::max(ks_counters, c);
+  }
+  L->off_ks_part = b.take(ks_floats * sizeof(float));
+  L->off_ks_count = b.take(ks_counters * sizeof(unsigned));
   L->off_rms = b.take(sizeof(float) * kRmsBlocks);
   L->off_sets = b.take(sizeof(SetDesc) * (size_t)(desc->n_nodes + 1));
   L->stride = (b.cur + 255) / 256 * 256;  // one stream's copy of everything
@@ -429,6 +473,9 @@ evconv_status run_pass(evconv_net* net, const float* input, int builder_mode, Pa
         p.n_fused = n.n_fused;
         p.st = net->st;
         p.upsample = 0; p.lo_h = 0; p.lo_w = 0;
+        p.ks = 0; p.ks_chunks = 0;
+        p.ks_part = (float*)(net->ws + net->L.off_ks_part);
+        p.ks_count = (unsigned*)(net->ws + net->L.off_ks_count);
         p.y = nullptr; p.dy = nullptr; p.int_mode = 0;
         p.fold_list = n.fold_list; p.w_fold = n.w_fold; p.fold_k = n.fold_k; p.wg_swap = 0;
         p.fold_base[0] = n.fold_base[0]; p.fold_base[1] = n.fold_base[1];
@@ -628,32 +675,25 @@ hipError_t prepare_fold(evconv_net* net, NodePlan& n, const void* weights, const
                   dst[(size_t)ci * co_n + co] += coef * (double)src[((size_t)co * ci_n + ci) * k * k + ky * k + kx];
             }
   const int ci_p = (ci_n + 31) / 32 * 32;
-  const size_t set = (size_t)taps * ci_p * cop;  // fp32 words per phase (two bf16 planes in split mode)
-  std::vector<float> staging(4 * set, 0.0f);
+  const int parts = weight_part_count(n.d.wdtype);
+  const size_t plane = (size_t)taps * ci_p * cop;  // values per part and phase; a phase's planes follow each other
+  std::vector<uint16_t> staging(4 * parts * plane, 0);
   for (int ph = 0; ph < 4; ++ph)
     for (int t = 0; t < taps; ++t)
-      for (int ci = 0; ci < ci_n; ++ci)
+      for (int c8 = 0; c8 < ci_n; c8 += 8)
         for (int co = 0; co < co_n; ++co) {
-          const float w = (float)folded[(((size_t)ph * taps + t) * ci_n + ci) * co_n + co];
-          if (n.kernel == kKernConvMfmaSplit) {
-            uint16_t* h16 = (uint16_t*)(staging.data() + ph * set);
-            const size_t at = (((size_t)t * (ci_p / 8) + ci / 8) * cop + co) * 8 + (ci & 7);
-            const uint16_t hi = to_bf16(w);
-            const uint32_t hu = (uint32_t)hi << 16;
-            float hf;
-            memcpy(&hf, &hu, 4);
-            h16[at] = hi;
-            h16[set + at] = to_bf16(w - hf);  // the low plane follows the high plane: `set` bf16 each
-          } else {
-            staging[ph * set + (((size_t)t * (ci_p / 4) + ci / 4) * cop + co) * 4 + (ci & 3)] = w;
-          }
+          float v[8];
+          const float sign = parts == 3 && ((c8 >> 4) & 1) ? -1.0f : 1.0f;  // conv_mfma_negated, chunks of 32 channels
+          for (int e = 0; e < 8; ++e)
+            v[e] = c8 + e < ci_n ? sign * (float)folded[(((size_t)ph * taps + t) * ci_n + c8 + e) * co_n + co] : 0.0f;
+          weight_parts8(v, parts, staging.data() + ph * parts * plane + (((size_t)t * (ci_p / 8) + c8 / 8) * cop + co) * 8, plane);
         }
   n.w_fold = net->ws + n.off_w_fold;
   n.fold_list = (int*)(net->ws + n.off_fold_list);
   n.fold_k = kf;
   n.fold_base[0] = base[0];
   n.fold_base[1] = base[1];
-  hipError_t e = hipMemcpy(n.w_fold, staging.data(), staging.size() * 4, hipMemcpyHostToDevice);
+  hipError_t e = hipMemcpy(n.w_fold, staging.data(), staging.size() * 2, hipMemcpyHostToDevice);
   if (e == hipSuccess) e = hipMemcpy(n.fold_list, list.data(), list.size() * 4, hipMemcpyHostToDevice);
   return e;
 }
@@ -754,7 +794,15 @@ evconv_status create_impl(const evconv_net_desc* desc, const void* weights, size
       probe.gi = n.ga; probe.go = n.go; probe.k = k; probe.stride = n.d.stride; probe.c_out_pad = cop;
       probe.n_fused = 0; probe.pad = n.d.pad; probe.st = Streams{L.stride, L.n_streams};
       const bool force_valu = (net->flags & EVCONV_FLAG_FORCE_VALU) != 0;
-      if (!force_valu && n.d.wdtype == EVCONV_F32 && conv_mfma_f32_supported(probe)) n.kernel = kKernConvMfmaF32;
+      // (a weight that is infinite or NaN: the vector kernel, which multiplies it as it is)
+      bool finite = true;
+      if (n.d.wdtype == EVCONV_F32) {
+        const uint32_t* wv = (const uint32_t*)((const char*)weights + n.d.weight_off);
+        uint32_t special = 0;
+        for (size_t q = 0, nw = (size_t)k * k * ci_n * co_n; q < nw; ++q) special |= (wv[q] & 0x7f800000u) == 0x7f800000u ? 1u : 0u;
+        finite = special == 0;
+      }
+      if (!force_valu && n.d.wdtype == EVCONV_F32 && finite && conv_mfma_f32_supported(probe)) n.kernel = kKernConvMfmaF32;
       if (!force_valu && n.d.wdtype == EVCONV_BF16 && conv_mfma_bf16_supported(probe)) n.kernel = kKernConvMfmaBf16;
       if (!force_valu && n.d.wdtype == EVCONV_F32_SPLIT && conv_mfma_split_supported(probe)) n.kernel = kKernConvMfmaSplit;
       if (!force_valu && n.kernel == kKernConvValu && conv_narrow_supported(probe)) n.kernel = kKernConvNarrow;
@@ -787,37 +835,24 @@ evconv_status create_impl(const evconv_net_desc* desc, const void* weights, size
               }
               staging[conv_narrow_weight_index(t * ci_n + ci, co)] = w;
             }
-      } else if (n.kernel == kKernConvMfmaSplit) {
-        // two bf16 planes [tap][c_in/8][c_out][8]: hi = bf16(w), then lo = bf16(w - hi)
-        uint16_t* h16 = (uint16_t*)staging.data();
+      } else if (n.kernel != kKernConvValu) {
+        // matrix-core layout, one plane [tap][c_in/8][c_out][8] of bf16 per part: a lane's 8 input
+        // channels are 16 bytes
+        const int parts = weight_part_count(n.d.wdtype);
         const size_t plane = (size_t)k * k * ci_p * cop;
-        for (int co = 0; co < co_n; ++co)
-          for (int ci = 0; ci < ci_n; ++ci)
-            for (int t = 0; t < k * k; ++t) {
-              const float w = src[((size_t)co * ci_n + ci) * k * k + t];
-              const uint16_t hi = to_bf16(w);
-              float hf;
-              const uint32_t hu = (uint32_t)hi << 16;
-              memcpy(&hf, &hu, 4);
-              const size_t at = (((size_t)t * (ci_p / 8) + ci / 8) * cop + co) * 8 + (ci & 7);
-              h16[at] = hi;
-              h16[plane + at] = to_bf16(w - hf);
-            }
-      } else if (n.kernel == kKernConvMfmaBf16) {
-        // bf16 matrix-core layout [tap][c_in/8][c_out][8]: a lane's 8 input channels are 16 bytes
+        staging.assign((parts * plane + 1) / 2, 0.0f);
         uint16_t* h16 = (uint16_t*)staging.data();
+        std::vector<char> neg(2 * k * k);  // [tap][parity of the group of 16 channels]
+        for (int t = 0; t < k * k; ++t)
+          for (int g = 0; g < 2; ++g) neg[t * 2 + g] = conv_mfma_negated(probe, t, 16 * g);
         for (int co = 0; co < co_n; ++co)
-          for (int ci = 0; ci < ci_n; ++ci)
-            for (int t = 0; t < k * k; ++t)
-              h16[(((size_t)t * (ci_p / 8) + ci / 8) * cop + co) * 8 + (ci & 7)] =
-                  to_bf16(src[((size_t)co * ci_n + ci) * k * k + t]);
-      } else if (n.kernel == kKernConvMfmaF32) {
-        // matrix-core layout [tap][c_in/4][c_out][4]: a lane's 4 input channels are 16 bytes
-        for (int co = 0; co < co_n; ++co)
-          for (int ci = 0; ci < ci_n; ++ci)
-            for (int t = 0; t < k * k; ++t)
-              staging[(((size_t)t * (ci_p / 4) + ci / 4) * cop + co) * 4 + (ci & 3)] =
-                  src[((size_t)co * ci_n + ci) * k * k + t];
+          for (int c8 = 0; c8 < ci_n; c8 += 8)
+            for (int t = 0; t < k * k; ++t) {
+              float v[8];
+              const float sign = parts == 3 && neg[t * 2 + ((c8 >> 4) & 1)] ? -1.0f : 1.0f;
+              for (int e = 0; e < 8; ++e) v[e] = c8 + e < ci_n ? sign * src[((size_t)co * ci_n + c8 + e) * k * k + t] : 0.0f;
+              weight_parts8(v, parts, h16 + (((size_t)t * (ci_p / 8) + c8 / 8) * cop + co) * 8, plane);
+            }
       } else {
         // vector-ALU layout [tap][c_in][c_out_pad] (zero padded output channels)
         for (int co = 0; co < co_n; ++co)

@@ -83,7 +83,7 @@ struct FusedSparsify {
 struct ConvParams {
   const float* in;          // H x W x C increment of the input node (full values if dense)
   const uint64_t* occ_in;   // its occupancy words
-  const void* w;            // re-laid weights [k*k][c_in][c_out_pad] (fp32 or bf16)
+  const void* w;            // re-laid weights (layout: the kernel's own header)
   const float* bias;        // fp32 [c_out] or null; used by the dense pass only
   float* z;                 // H x W x C accumulated pre-activation
   float* out;               // H x W x C output increment (value in dense mode)
@@ -112,17 +112,25 @@ struct ConvParams {
   // matrix-core kernel only, set by its launcher: the grid's x dimension runs over the blocks of
   // 32 output channels and y over the tiles, instead of the other way round
   int wg_swap;
+  // matrix-core kernel only, set by its launcher: the channels are split over ks workgroups per
+  // output block (0: not), ks_chunks channel chunks each; their shares of the sums and the arrival
+  // counters (zero between launches) lie in ks_part and ks_count, of the sizes that
+  // conv_mfma_split_scratch gives
+  int ks, ks_chunks;
+  float* ks_part; unsigned* ks_count;
   // few-channel pointwise kernel only: the node is a network output and the kernel keeps the
   // public tensors itself (y += increment, dy = increment; C x H x W); null otherwise.
   // int_mode is one of kIntStep / kIntReset / kIntRecompute.
   float* y; float* dy; int int_mode;
 };
 void launch_conv_valu(const ConvParams& p, hipStream_t s);
-// fp32 MFMA variant; requires c_in >= 9 and c_out >= 16 (c_out_pad = c_out rounded up to 32).  The re-laid weights
+// fp32 variant (operands as three exact bf16 parts, six bf16 MFMAs per product); requires c_in >= 9 and c_out >= 16 (c_out_pad = c_out rounded up to 32).  The re-laid weights
 // of all matrix-core variants carry conv_mfma_padded_cin input channels (zero rows beyond c_in).
 bool conv_mfma_f32_supported(const ConvParams& p);
 int conv_mfma_padded_cin(const ConvParams& p);
 bool conv_mfma_upsample_supported(const ConvParams& p);
+bool conv_mfma_negated(const ConvParams& p, int tap, int ci);
+void conv_mfma_split_scratch(const ConvParams& p, size_t* part_floats, size_t* counters);
 void launch_conv_mfma_f32(const ConvParams& p, hipStream_t s);
 // bf16 MFMA variant (increments rounded to bf16 in the gather, bf16 weights, fp32 accumulation)
 bool conv_mfma_bf16_supported(const ConvParams& p);

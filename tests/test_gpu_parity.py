@@ -1410,3 +1410,97 @@ def test_large_frame_720p():
     frames = list(wl.stream_voxel(1010, 720, 1280, 2, 0.01, n_prim=12))
     rep = run_stream(net, frames[0], frames[1:], "frame", check_nodes_at={2}, label="720p", max_flips=400)
     _say(f"720p: max rel z err {rep.max_rel_z:.2e}, y err {rep.max_rel_y:.2e}, flips {rep.flips}")
+
+
+@pytest.mark.parametrize("ci,co,k,s,hw,streams", [
+    (128, 64, 3, 1, (8, 8), 1), (192, 40, 3, 1, (17, 9), 1), (448, 32, 3, 1, (9, 7), 1),    # 2, 3, 7 chunks of 64
+    (256, 96, 1, 1, (5, 20), 1), (128, 32, 3, 2, (15, 30), 1), (192, 64, 1, 2, (11, 9), 1),  # 1 x 1, stride 2
+    (64, 32, 5, 2, (20, 9), 1), (96, 48, 5, 2, (33, 16), 1), (1024, 128, 3, 1, (16, 24), 1),  # chunks of 32; several chunks each
+    (256, 32, 3, 1, (11, 13), 3)])
+def test_channels_split_over_workgroups(ci, co, k, s, hw, streams):
+    """Convs on maps of a few tiles split their input channels over several workgroups, the last of
+    which to arrive runs the epilogue (residual ADD, ReLU, a second conv behind it).  Sparse steps
+    with untouched tiles, tiles that only the ADD's other input touches, a dense step, a refresh;
+    every net twice in the same state (run-to-run identical whatever the order of arrival)."""
+    import torch
+    h, w = hw
+    _say(f"channels split over workgroups: {ci} -> {co}, {k} x {k} stride {s}, {h} x {w}, {streams} streams")
+    b = wl._NetBuilder("ksplit", ci, h, w, ci + k, bias=True)
+    a = b.conv(-1, co, 1, s, 0, act=wl.ACT_RELU)
+    c = b.conv(-1, co, k, s, act=wl.ACT_NONE)
+    b.simple(wl.OP_ADD, c, a, act=wl.ACT_RELU, out=1)
+    net = b.finish()
+    rng = np.random.default_rng(ci + k)
+    nets = [ev.EvConvNet(net, n_streams=streams) for _ in range(2)]
+    assert nets[0].kernel_name(c) == "conv_mfma_f32"
+    oras = [Oracle(net) for _ in range(streams)]
+    rep = cmp.Report()
+    x0 = rng.standard_normal((streams, ci, h, w)).astype(np.float32)
+    for g in nets:
+        g.reset(_dev(x0 if streams > 1 else x0[0]))
+    for q, o in enumerate(oras):
+        o.reset(x0[q])
+    for t in range(5):
+        m = rng.random((streams, 1, h, w)) < (1.0 if t == 2 else 0.02)
+        d = (rng.standard_normal(x0.shape) * m).astype(np.float32)
+        for g in nets:
+            g.step(_dev(d if streams > 1 else d[0]))
+        torch.cuda.synchronize()
+        for q, o in enumerate(oras):
+            o.step_increment(d[q])
+            for i in range(len(net.nodes)):
+                z, zr = nets[0].state(i, ev.STATE_Z, q).astype(np.float64), o.z(i)
+                assert np.abs(z - zr).max() <= 2e-6 * np.abs(zr).max(), f"step {t} node {i} z"
+                np.testing.assert_array_equal(nets[0].state(i, ev.STATE_OCC_TOUCHED, q), nets[1].state(i, ev.STATE_OCC_TOUCHED, q))
+                np.testing.assert_array_equal(z, nets[1].state(i, ev.STATE_Z, q).astype(np.float64))
+        if streams == 1:
+            for i in range(len(net.nodes)):
+                cmp.compare_node(nets[0], oras[0], i, rep)
+    assert rep.flips <= 2
+    for g in nets:
+        g.destroy()
+
+
+@pytest.mark.parametrize("k,s,ci,co", [(3, 1, 64, 32), (5, 2, 16, 64), (5, 1, 20, 32), (1, 1, 96, 32)])
+def test_fp32_contraction_keeps_24_bits_and_ieee_specials(k, s, ci, co):
+    """The fp32 matrix-core conv writes every operand as three bf16 parts.  Against 64 bits the sums
+    are within 2^-21 of the sum of the absolute products (three dropped partial products of 2^-25
+    each at most, and fp32 accumulation); finite values that a bf16 would round to infinity stay
+    finite; infinities and NaN come out where IEEE products put them, zero weights included."""
+    _say(f"fp32 contraction: {k} x {k} stride {s}, {ci} -> {co}")
+    h, w = 18, 21
+    b = wl._NetBuilder("bits24", ci, h, w, 5 + k)
+    b.conv(-1, co, k, s, act=wl.ACT_NONE, out=1)
+    net = b.finish()
+    rng = np.random.default_rng(9)
+    wt = net.weights
+    wt *= np.exp2(rng.integers(-6, 7, wt.shape)).astype(np.float32)     # mixed magnitudes
+    wt[rng.random(wt.shape) < 0.1] = 0.0
+    wt[rng.random(wt.shape) < 0.1] = 1.0                                # one part only
+    x = (rng.standard_normal((ci, h, w)) * np.exp2(rng.integers(-20, 8, (ci, h, w)))).astype(np.float32)
+    gpu, ora, absolute = ev.EvConvNet(net), Oracle(net), Oracle(dataclasses.replace(net, weights=np.abs(wt)))
+    assert gpu.kernel_name(0) == "conv_mfma_f32"
+    gpu.reset(_dev(x))
+    ora.reset(x)
+    absolute.reset(np.abs(x))
+    err = np.abs(gpu.state(0, ev.STATE_Z).astype(np.float64) - ora.z(0))
+    assert (err <= 2.0 ** -21 * absolute.z(0)).all(), float((err / absolute.z(0)).max())
+    # 3.4e38 is above the largest value that a bf16 rounds to a finite one
+    wt[:] = np.where(np.abs(wt) > 0, np.sign(wt) * 1e-3, 0).astype(np.float32)
+    gpu.destroy()
+    gpu, ora = ev.EvConvNet(net), Oracle(net)
+    x0 = np.zeros((ci, h, w), np.float32)
+    d = np.zeros_like(x0)
+    d[0, 2, 3], d[ci - 1, 2, 12], d[1, 9, 4], d[2, 15, 15] = 3.4e38, -np.finfo(np.float32).max, np.inf, np.nan
+    d[3, 9, 12] = -np.inf
+    gpu.reset(_dev(x0))
+    ora.reset(x0)
+    gpu.step(_dev(d))
+    ora.step_increment(d)
+    z, zr = gpu.state(0, ev.STATE_Z).astype(np.float64), ora.z(0)
+    np.testing.assert_array_equal(np.isnan(z), np.isnan(zr))
+    np.testing.assert_array_equal(z[np.isinf(zr)], zr[np.isinf(zr)])
+    fin = np.isfinite(zr)
+    assert np.isfinite(z[fin]).all() and np.abs(z[fin] - zr[fin]).max() <= 2.0 ** -21 * np.abs(zr[fin]).max()
+    assert np.abs(zr[fin]).max() > 1e35
+    gpu.destroy()
