@@ -48,6 +48,8 @@ struct BuilderParams {
   uint64_t* occ;      // per-tile occupancy of the input increment
   uint64_t* clear;    // words to zero before the layers run (all nodes' occupancy), or null
   int n_clear;
+  uint64_t* tile_or;   // wide inputs: per-tile scratch word and counter, zero between launches
+  unsigned* tile_count;
   Geo g;
   int mode;
   Streams st;

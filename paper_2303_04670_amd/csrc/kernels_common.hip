@@ -36,7 +36,38 @@ __device__ __forceinline__ uint64_t inbounds_word(int h, int w, int tile_y, int 
 }  // namespace
 
 // =============================================================================== builder
-// One workgroup = 8 wavefronts = an 8-row x 64-column strip (8 tiles).  Wave r reads row r with
+// N elements of a thread, element j at ok[j] ? e[j] : nowhere (d[j] = 0).  All loads are requested before
+// the first store: a store to the cached frame between two loads of it would keep them in order,
+// one round trip per channel.
+constexpr int kBuilderFewChannels = 8;
+template <int N>
+__device__ __forceinline__ void build_elements(const BuilderParams& p, const int* e, const bool* ok, float* d) {
+  float in[N], prev[N];
+  const bool needs_prev = p.mode != kBuildReset;
+#pragma unroll
+  for (int j = 0; j < N; ++j) in[j] = ok[j] ? p.in[e[j]] : 0.0f;
+#pragma unroll
+  for (int j = 0; j < N; ++j) prev[j] = (ok[j] && needs_prev) ? p.x_prev[e[j]] : 0.0f;
+#pragma unroll
+  for (int j = 0; j < N; ++j) {
+    // Eq.1: one binary32 subtraction; a supplied increment advances the cached frame (dense
+    // recompute emits the new frame); a reset emits the frame
+    const float sum = prev[j] + in[j];
+    const float x = (p.mode == kBuildIncrement || p.mode == kBuildIncrementDense) ? sum : in[j];
+    d[j] = p.mode == kBuildFrame ? in[j] - prev[j] : p.mode == kBuildIncrementDense ? sum : in[j];
+    if (ok[j]) p.x_prev[e[j]] = x;
+  }
+}
+
+// clear the per-node occupancy words that the layer kernels OR into
+__device__ __forceinline__ void clear_words(const BuilderParams& p) {
+  if (!p.clear) return;
+  const int nthreads = gridDim.x * gridDim.y * blockDim.x;
+  const int gtid = (blockIdx.y * gridDim.x + blockIdx.x) * blockDim.x + threadIdx.x;
+  for (int i = gtid; i < p.n_clear; i += nthreads) p.clear[i] = 0;
+}
+
+// Frames of few channels: one workgroup = 8 wavefronts = an 8-row x 64-column strip (8 tiles).  Wave r reads row r with
 // 256-byte coalesced loads per channel; its ballot is the 64-column activity of that row.  The
 // eight ballots are transposed through LDS into eight tile occupancy words.
 __global__ __launch_bounds__(512) void builder_kernel(BuilderParams p) {
@@ -56,25 +87,19 @@ __global__ __launch_bounds__(512) void builder_kernel(BuilderParams p) {
   bool any = false;
   if (inb) {
     const int site = y * p.g.w + x;
-    for (int c = 0; c < p.g.c; ++c) {
-      const int e = c * hw + site;
-      float d;
-      if (p.mode == kBuildFrame) {
-        const float xt = p.in[e];
-        d = xt - p.x_prev[e];          // Eq.1: one binary32 subtraction
-        p.x_prev[e] = xt;
-      } else if (p.mode == kBuildIncrement) {
-        d = p.in[e];
-        p.x_prev[e] = p.x_prev[e] + d;
-      } else if (p.mode == kBuildIncrementDense) {
-        d = p.x_prev[e] + p.in[e];     // dense recompute of a supplied increment: emit x(n)
-        p.x_prev[e] = d;
-      } else {
-        d = p.in[e];
-        p.x_prev[e] = d;
-      }
-      p.dx[(size_t)site * p.g.c + c] = d;
-      any |= (d != 0.0f);
+    int e[kBuilderFewChannels];
+    bool ok[kBuilderFewChannels];
+    float d[kBuilderFewChannels];
+#pragma unroll
+    for (int c = 0; c < kBuilderFewChannels; ++c) {
+      ok[c] = c < p.g.c;
+      e[c] = c * hw + site;
+    }
+    build_elements<kBuilderFewChannels>(p, e, ok, d);
+#pragma unroll
+    for (int c = 0; c < kBuilderFewChannels; ++c) {
+      if (ok[c]) p.dx[(size_t)site * p.g.c + c] = d[c];
+      any |= ok[c] && d[c] != 0.0f;
     }
   }
   const uint64_t row_mask = __ballot(any);
@@ -90,15 +115,86 @@ __global__ __launch_bounds__(512) void builder_kernel(BuilderParams p) {
       p.occ[blockIdx.y * p.g.tx + tile_x] = word;
     }
   }
-  // clear the per-node occupancy words that the layer kernels OR into
-  if (p.clear) {
-    const int nthreads = gridDim.x * gridDim.y * blockDim.x;
-    const int gtid = (blockIdx.y * gridDim.x + blockIdx.x) * blockDim.x + threadIdx.x;
-    for (int i = gtid; i < p.n_clear; i += nthreads) p.clear[i] = 0;
+  clear_words(p);
+}
+
+// Wide inputs (a network that starts inside another one): workgroup = one 8 x 8 tile x 64 channels,
+// lane = site, the channels dealt to the 8 waves.  They pass through LDS, so that the channel-major
+// input is read row by row of the tile and the site-major increment is written in runs of 64
+// channels; with one thread per site the channels were a serial loop of 4-byte stores a site's
+// length apart (256 x 32 x 44, four workgroups: 260 us; a workgroup per tile: 15 us; this way 10 us).
+// The tile's word is the OR over its workgroups: they meet in p.tile_or, and the last to arrive
+// (p.tile_count) writes it and leaves both zero for the next launch.
+constexpr int kWideChunk = 64;
+__global__ __launch_bounds__(512) void builder_wide_kernel(BuilderParams p) {
+  {
+    const size_t so = (size_t)blockIdx.z * p.st.stride;
+    p.in = at_stream(p.in, (size_t)blockIdx.z * p.in_stride);
+    p.x_prev = at_stream(p.x_prev, so); p.dx = at_stream(p.dx, so);
+    p.occ = at_stream(p.occ, so); p.clear = at_stream(p.clear, so);
+    p.tile_or = at_stream(p.tile_or, so); p.tile_count = at_stream(p.tile_count, so);
   }
+  __shared__ float s_d[64][kWideChunk + 1];
+  __shared__ uint64_t s_any[8];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int ty = blockIdx.x / p.g.tx, tx = blockIdx.x - ty * p.g.tx;
+  const int y = ty * 8 + (lane >> 3), x = tx * 8 + (lane & 7);
+  const int hw = p.g.h * p.g.w, C = p.g.c;
+  const int c0 = blockIdx.y * kWideChunk, nc = min(kWideChunk, C - c0);
+  const bool inb = y < p.g.h && x < p.g.w;
+  constexpr int N = kWideChunk / 8;
+  int e[N];
+  bool ok[N], any = false;
+  float d[N];
+#pragma unroll
+  for (int j = 0; j < N; ++j) {
+    const int c = wave + 8 * j;
+    ok[j] = inb && c < nc;
+    e[j] = (c0 + c) * hw + y * p.g.w + x;
+  }
+  build_elements<N>(p, e, ok, d);
+#pragma unroll
+  for (int j = 0; j < N; ++j)
+    if (ok[j]) {
+      s_d[lane][wave + 8 * j] = d[j];
+      any |= d[j] != 0.0f;
+    }
+  const uint64_t b = __ballot(any);
+  if (lane == 0) s_any[wave] = b;
+  __syncthreads();
+  // wave w writes sites w, w + 8, ..: lanes along the channels
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    const int q = wave + 8 * j;
+    const int qy = ty * 8 + (q >> 3), qx = tx * 8 + (q & 7);
+    if (qy < p.g.h && qx < p.g.w && lane < nc) p.dx[(size_t)(qy * p.g.w + qx) * C + c0 + lane] = s_d[q][lane];
+  }
+  if (threadIdx.x == 0) {
+    uint64_t word = 0;
+    for (int i = 0; i < 8; ++i) word |= s_any[i];
+    if (p.mode >= kBuildReset) word = 0;
+    if (gridDim.y == 1) {
+      p.occ[blockIdx.x] = word;
+    } else {
+      // (the OR's result is waited for before the counter is touched)
+      unsigned long long* const acc = (unsigned long long*)&p.tile_or[blockIdx.x];
+      const unsigned long long old = __hip_atomic_fetch_or(acc, (unsigned long long)word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      asm volatile("s_waitcnt vmcnt(0)" ::"v"((unsigned)old) : "memory");
+      if (__hip_atomic_fetch_add(&p.tile_count[blockIdx.x], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.y - 1) {
+        p.occ[blockIdx.x] = __hip_atomic_exchange(acc, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&p.tile_count[blockIdx.x], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+    }
+  }
+  clear_words(p);
 }
 
 void launch_builder(const BuilderParams& p, hipStream_t s) {
+  if (p.g.c > kBuilderFewChannels) {
+    const dim3 grid(p.g.tiles(), (p.g.c + kWideChunk - 1) / kWideChunk, p.st.n);
+    hipLaunchKernelGGL(builder_wide_kernel, grid, dim3(512), 0, s, p);
+    return;
+  }
   dim3 grid((p.g.w + 63) / 64, (p.g.h + 7) / 8, p.st.n);
   hipLaunchKernelGGL(builder_kernel, grid, dim3(512), 0, s, p);
 }
@@ -482,6 +578,21 @@ void launch_gap(const GapParams& p, hipStream_t s) {
 }
 
 // =============================================================================== Eq.2
+// One element of the public tensors; on: the site is in the active set.
+__device__ __forceinline__ void integrate_element(const IntegrateParams& p, int e, float v, bool on) {
+  if (p.mode == kIntStep) {
+    if (on) p.y[e] += v;
+    p.dy[e] = v;
+  } else if (p.mode == kIntReset) {
+    p.y[e] = v;
+    p.dy[e] = 0.0f;
+  } else {
+    p.dy[e] = v - p.y[e];
+    p.y[e] = v;
+  }
+}
+
+// Few channels: one thread per site.
 __global__ __launch_bounds__(256) void integrate_kernel(IntegrateParams p) {
   {
     const size_t so = (size_t)blockIdx.z * p.st.stride;
@@ -494,22 +605,47 @@ __global__ __launch_bounds__(256) void integrate_kernel(IntegrateParams p) {
   const int y = site / p.g.w, x = site - y * p.g.w;
   const bool on = p.mode != kIntStep || occ_bit(p.occ, p.g.tx, y, x);
   for (int c = 0; c < p.g.c; ++c) {
-    const int e = c * hw + site;
     const float v = on ? p.delta[(size_t)site * p.g.c + c] : 0.0f;
-    if (p.mode == kIntStep) {
-      if (on) p.y[e] += v;
-      p.dy[e] = v;
-    } else if (p.mode == kIntReset) {
-      p.y[e] = v;
-      p.dy[e] = 0.0f;
-    } else {
-      p.dy[e] = v - p.y[e];
-      p.y[e] = v;
-    }
+    integrate_element(p, c * hw + site, v, on);
+  }
+}
+
+// More channels: a workgroup takes 64 sites x 16 channels, read in runs of a site's channels and
+// turned through LDS to be written in runs of sites.  (One thread per site walked the channels one
+// round trip after the other: 101 channels on one site 35 us, now 4.)
+constexpr int kIntChannels = 16;
+__global__ __launch_bounds__(256) void integrate_wide_kernel(IntegrateParams p) {
+  {
+    const size_t so = (size_t)blockIdx.z * p.st.stride;
+    p.delta = at_stream(p.delta, so); p.occ = at_stream(p.occ, so);
+    p.y = at_stream(p.y, so); p.dy = at_stream(p.dy, so);
+  }
+  __shared__ float s_v[64][kIntChannels + 1];
+  const int hw = p.g.h * p.g.w, C = p.g.c;
+  const int s0 = blockIdx.x * 64, c0 = blockIdx.y * kIntChannels;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int c = threadIdx.x & (kIntChannels - 1), q = (threadIdx.x >> 4) + 16 * i;
+    s_v[q][c] = (s0 + q < hw && c0 + c < C) ? p.delta[(size_t)(s0 + q) * C + c0 + c] : 0.0f;
+  }
+  __syncthreads();
+  const int q = threadIdx.x & 63, site = s0 + q;
+  if (site >= hw) return;
+  const int y = site / p.g.w, x = site - y * p.g.w;
+  const bool on = p.mode != kIntStep || occ_bit(p.occ, p.g.tx, y, x);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int c = (threadIdx.x >> 6) + 4 * i;
+    if (c0 + c < C) integrate_element(p, (c0 + c) * hw + site, on ? s_v[q][c] : 0.0f, on);
   }
 }
 
 void launch_integrate(const IntegrateParams& p, hipStream_t s) {
+  if (p.g.c > 4) {
+    const dim3 grid((p.g.sites() + 63) / 64, (p.g.c + kIntChannels - 1) / kIntChannels, p.st.n);
+    hipLaunchKernelGGL(integrate_wide_kernel, grid, dim3(256), 0, s, p);
+    return;
+  }
   hipLaunchKernelGGL(integrate_kernel, dim3((p.g.sites() + 255) / 256, 1, p.st.n), dim3(256), 0, s, p);
 }
 

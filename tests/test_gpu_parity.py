@@ -1504,3 +1504,45 @@ def test_fp32_contraction_keeps_24_bits_and_ieee_specials(k, s, ci, co):
     assert np.isfinite(z[fin]).all() and np.abs(z[fin] - zr[fin]).max() <= 2.0 ** -21 * np.abs(zr[fin]).max()
     assert np.abs(zr[fin]).max() > 1e35
     gpu.destroy()
+
+
+@pytest.mark.parametrize("c,co,hw", [(8, 4, (9, 65)), (9, 5, (8, 8)), (64, 16, (17, 23)), (65, 17, (7, 9)), (200, 101, (9, 5))])
+def test_wide_inputs_and_wide_outputs(c, co, hw):
+    """The increment builder's two forms (up to 8 channels: strips of 64 columns; more: tiles x 64
+    channels whose words meet through a scratch word) and the output integration's two (up to 4
+    channels, more): cached frame, increment, words and lists bit-exact through frames, supplied
+    increments, a refresh and dense recompute."""
+    h, w = hw
+    _say(f"wide inputs and outputs: {c} -> {co}, {h} x {w}")
+    b = wl._NetBuilder("wide", c, h, w, c + co, bias=True)
+    b.conv(-1, co, 1, 1, 0, act=wl.ACT_RELU, out=1)
+    net = b.finish()
+    rng = np.random.default_rng(c)
+    gpu, ora, rep = ev.EvConvNet(net), Oracle(net), cmp.Report()
+    x = rng.standard_normal((c, h, w)).astype(np.float32)
+    gpu.reset(_dev(x))
+    ora.reset(x)
+    cmp.compare_outputs(gpu, ora, rep)
+    for t in range(6):
+        d = np.zeros_like(x)
+        for _ in range(3):   # single elements: a site's bit comes from one channel group only
+            d[rng.integers(c), rng.integers(h), rng.integers(w)] = rng.standard_normal()
+        if t == 3:
+            d = (rng.standard_normal(x.shape) * (rng.random((1, h, w)) < 0.5)).astype(np.float32)
+        if t % 2:
+            gpu.step(_dev(d))
+            ora.step_increment(d)
+            x = x + d
+        else:
+            x = x + d
+            gpu.step_frame(_dev(x))
+            ora.step_frame(x)
+        cmp.compare_input_stage(gpu, ora, rep)
+        cmp.compare_outputs(gpu, ora, rep)
+        cmp.compare_node(gpu, ora, 0, rep)
+    y_inc = gpu.outputs()[0]["y"].clone()
+    gpu.set_mode(ev.MODE_DENSE_RECOMPUTE)
+    gpu.step(_dev(np.zeros_like(x)))       # a regular pass of the cached frame
+    y_dense = gpu.outputs()[0]["y"]
+    assert float((y_dense - y_inc).abs().max()) <= 1e-5 * max(1.0, float(y_dense.abs().max()))
+    gpu.destroy()
