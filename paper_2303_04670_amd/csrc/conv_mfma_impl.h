@@ -137,6 +137,12 @@ constexpr int max_patch_sites(int chunk, int mb, int s2k) {
   return chunk >= 64 ? (rows + 3) * 10 : chunk == 32 ? (rows + 7) * 14 : (rows * 2 + 7) * 21;
 }
 
+// n / d with magic = ceil(2^32 / d): exact while n * d < 2^32 (the launcher passes 0 where that may
+// not hold, and for d == 1)
+__device__ __forceinline__ int fast_div(int n, int d, unsigned magic) {
+  return magic ? (int)__umulhi((unsigned)n, magic) : n / d;
+}
+
 constexpr int op_parts(int opm) { return opm == kOpF32 ? 3 : opm == kOpSplit ? 2 : 1; }
 // 4-byte words of a patch site in LDS
 constexpr int patch_site_words(int chunk, int opm) { return chunk / 2 * op_parts(opm) + 4; }
@@ -233,7 +239,7 @@ void conv_mfma_kernel(ConvParams p) {
   // blocks.  The launcher picks whichever of the two operands is larger to be split.
   const int wg_tile = p.wg_swap ? blockIdx.y : blockIdx.x, wg_ck = p.wg_swap ? blockIdx.x : blockIdx.y;
   const int n_co = p.c_out_pad / NB;
-  const int ks = KSP ? wg_ck / n_co : 0, wg_co = KSP ? wg_ck - ks * n_co : wg_ck;
+  const int ks = KSP ? fast_div(wg_ck, n_co, p.co_magic) : 0, wg_co = KSP ? wg_ck - ks * n_co : wg_ck;
   int tile = wg_tile / SUBS;
   const int sub = wg_tile % SUBS;
   // Weight-folded workgroup (UPS variants with a fold list): its 8 x 8 "tile" is a tile of stored
@@ -256,7 +262,7 @@ void conv_mfma_kernel(ConvParams p) {
   const int r0 = sub * NROWS;  // first tile row of this workgroup
   const uint64_t row_mask = MB == 2 ? ~0ull : (0xffffffffull << (32 * sub));
   const int n_tx = fold ? (p.lo_w + 7) >> 3 : p.go.tx;
-  const int tile_y = tile / n_tx, tile_x = tile - tile_y * n_tx;
+  const int tile_y = fast_div(tile, n_tx, fold ? p.lo_tx_magic : p.tx_magic), tile_x = tile - tile_y * n_tx;
   const int s = p.stride, K = fold ? p.fold_k : p.k;
   const int H = p.gi.h, W = p.gi.w, Cin = p.gi.c, Cout = p.go.c;
   const int iy0 = fold ? tile_y * 8 + r0 + p.fold_base[fpy] : (tile_y * 8 + r0) * s - p.pad;
@@ -311,7 +317,8 @@ void conv_mfma_kernel(ConvParams p) {
   const int RP = s == 1 ? ((PW * CS + 31) / 64) * 64 + 32 : PW * CS;
   float* const s_low = s_mem + PH * RP;  // UPS only
   const int total_v = GH * GW * NV;
-  const int gw_magic = (65536 + GW - 1) / GW;  // site / GW == (site * gw_magic) >> 16 for site < 441
+  const int gw_magic = p.gw_magic[fold ? 1 : ups ? 2 : 0];  // site / GW == (site * gw_magic) >> 16 for site < 441
+  const unsigned row_bytes = (unsigned)(SW * Cin) * 4u, g_origin = (unsigned)gy0 * row_bytes + (unsigned)(gx0 * Cin) * 4u;
   int lds_off[MAXG];     // (until the occupancy is known: patch row and column in bits 16-23 and 24-31)
   unsigned g_off[MAXG];
 #pragma unroll
@@ -321,9 +328,10 @@ void conv_mfma_kernel(ConvParams p) {
     g_off[j] = kOob;
     if (e < total_v) {
       const int site = e / NV, v = e - site * NV;
-      const int py = (site * gw_magic) >> 16, px = site - py * GW;
-      lds_off[j] = (ups ? site * CSL + v * 4 : py * RP + px * CS + v * 2) | (py << 16) | (px << 24);
-      g_off[j] = (unsigned)((((gy0 + py) * SW + gx0 + px) * Cin + v * 4) * 4);
+      // (24-bit products: full rate, unlike 32-bit ones)
+      const int py = __umul24(site, gw_magic) >> 16, px = site - __umul24(py, GW);
+      lds_off[j] = (ups ? site * CSL + v * 4 : __umul24(py, RP) + px * CS + v * 2) | (py << 16) | (px << 24);
+      g_off[j] = g_origin + (unsigned)py * row_bytes + __umul24(px, Cin) * 4u + v * 16u;
     }
   }
   // UPS: every patch element from its four sources in the low-resolution buffer, with the
@@ -345,14 +353,14 @@ void conv_mfma_kernel(ConvParams p) {
   if (ups) {
     const int by0 = (iy0 - 1) >> 1, bx0 = (ix0 - 1) >> 1;
     const int nby = ((iy0 + PH - 2) >> 1) - by0 + 1, nbx = ((ix0 + PW - 2) >> 1) - bx0 + 1;
-    const int nbx_magic = (65536 + nbx - 1) / nbx;  // blk / nbx == (blk * nbx_magic) >> 16 for blk < 64
+    const int nbx_magic = p.nbx_magic;  // blk / nbx == (blk * nbx_magic) >> 16 for blk < 64
 #pragma unroll
     for (int b = 0; b < MAXB; ++b) {
       const int e = tid + b * NT;
       const int blk = e / NV, v = e - blk * NV;
       ib_src[b] = ib_dst[b] = 0;
       if (blk < nby * nbx) {
-        const int bi = (blk * nbx_magic) >> 16, bj = blk - bi * nbx;
+        const int bi = __umul24(blk, nbx_magic) >> 16, bj = blk - __umul24(bi, nbx);
         const int i = by0 + bi, j = bx0 + bj;
         const int cy0 = min(max(i, 0), SH - 1), cy1 = min(max(i + 1, 0), SH - 1);
         const int cx0 = min(max(j, 0), SW - 1), cx1 = min(max(j + 1, 0), SW - 1);
@@ -606,19 +614,21 @@ void conv_mfma_kernel(ConvParams p) {
   const int half = lane >> 5, m = lane & 31;
   const int mly = m >> 3, mlx = m & 7;  // site of this lane inside a block
   const int cop = p.c_out_pad;
-  const int n_units = K * K * KG;
   const int cin_pad = (Cin + CHUNK - 1) / CHUNK * CHUNK;    // the weights are zero-padded to whole chunks
   const int cin_rows = cin_pad >> 3;                        // 16-byte weight rows per tap: 8 bf16
   const int a_lane_off = mly * s * RP + mlx * s * CS + half * 4;
   const int a_blk1 = 4 * s * RP;  // the second block starts four tile rows further down
-  // units of this wave: u_j = wave + j * NW, j < n_mine
-  const int n_mine = (n_units - wave + NW - 1) / NW;
-  const int last = n_mine - 1;
-  const int k_magic = (65536 + K - 1) / K;  // tap / K == (tap * k_magic) >> 16 for tap < 49
-
+  // Units of this wave: u_j = wave + j * NW, unit u = (tap u / KG, channel group u % KG).  KG divides
+  // NW, so a wave keeps one channel group and steps through the taps.
+  static_assert(NW % KG == 0, "a wave's units share one channel group");
+  const int kg = wave % KG, tap0 = wave / KG;
+  constexpr int TSTEP = NW / KG;
+  const int n_mine = max(0, (K * K - tap0 + TSTEP - 1) / TSTEP);
   // Both fragment addresses are a per-lane constant plus a per-unit part that is the same in all
-  // lanes; the latter is kept in scalar registers (pinned there with readfirstlane), so that a
-  // unit costs one vector add: vector-ALU time is taken from the fp32 matrix instructions.
+  // lanes.  Lane j of a table register holds unit j's part (beyond the last unit: the last one's, so
+  // that look-ahead loads stay unconditional and in bounds) and a readlane brings it into a scalar
+  // register: worked out per unit in scalar arithmetic, the two parts were 20 scalar instructions a
+  // unit, in a kernel whose vector and scalar units are both more than half busy.
   // B: buffer load with the lane part as vector offset and the unit part as scalar offset
   // (bytes; the launcher checks that the re-laid weights stay below 2 GiB).
   const unsigned w_plane = (unsigned)(K * K * cin_rows * cop) * 16u;  // the planes of the parts follow each other
@@ -626,14 +636,17 @@ void conv_mfma_kernel(ConvParams p) {
   const char* const w_base = fold ? (const char*)p.w_fold + (size_t)(fpy * 2 + fpx) * w_set : (const char*)p.w;
   const __amdgpu_buffer_rsrc_t w_rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)w_base, 0, (int)w_set, 0x00020000);
   const unsigned w_lane = (unsigned)(half * cop + co0 + m) * 16u;
-  // unit j of the chunk starting at channel c0 (j clamped to the last unit so that look-ahead
-  // loads stay unconditional and in bounds)
+  unsigned w_table;  // byte offset of unit `lane`'s weight rows in a chunk that starts at channel 0
+  int a_table;       // offset of its patch sites, words
+  {
+    const int tap = min(tap0 + __umul24(lane, TSTEP), tap0 + __umul24(n_mine - 1, TSTEP));
+    const int ky = __umul24(tap, p.k_magic[fold ? 1 : 0]) >> 16, kx = tap - __umul24(ky, K);  // tap < 49
+    a_table = __umul24(ky, RP) + kx * CS + kg * 8;  // a unit's 16 bf16 are 8 words
+    w_table = (__umul24(tap, cin_rows) + kg * (UCH / 8)) * (unsigned)(cop * 16);  // 16-byte rows of 8 bf16
+  }
+  // fragments of unit j of the chunk starting at channel c0
   auto b_load = [&](int c0, int j) {
-    const int u = wave + min(j, last) * NW;
-    const int tap = u / KG, kg = u % KG;
-    constexpr int kRowsPerUnit = UCH / 8;  // 16-byte weight rows of a unit
-    const unsigned soff =
-        (unsigned)__builtin_amdgcn_readfirstlane(((tap * cin_rows + (c0 >> 3) + kg * kRowsPerUnit) * cop) << 4);
+    const unsigned soff = __builtin_amdgcn_readlane(w_table, j) + (unsigned)((c0 >> 3) * (cop * 16));
     BFrag f;
     f.h = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(w_rsrc, w_lane, soff, 0));
     f.m = f.l = f.h;
@@ -642,18 +655,11 @@ void conv_mfma_kernel(ConvParams p) {
       f.l = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(w_rsrc, w_lane, soff + (PARTS - 1) * w_plane, 0));
     return f;
   };
-  // ... and LDS offset of its A fragment
-  auto a_off = [&](int j) {
-    const int u = wave + j * NW;
-    const int tap = u / KG, kg = u % KG;
-    const int ky = (tap * k_magic) >> 16, kx = tap - ky * K;
-    return a_lane_off + __builtin_amdgcn_readfirstlane(ky * RP + kx * CS + kg * 8);  // words of a unit's 16 bf16
-  };
-  // A fragment of unit j (clamped like the B fragments): the parts of this lane's site in both
+  // A fragment of unit j: the parts of this lane's site in both
   // 32-row blocks; unused members cost nothing
   auto a_load = [&](int j) {
     AFrag f;
-    const float* ap = &s_mem[a_off(min(j, last))];
+    const float* ap = &s_mem[a_lane_off + __builtin_amdgcn_readlane(a_table, j)];
     f.h0 = *(const float4*)ap;
     f.h1 = MB == 2 ? *(const float4*)(ap + a_blk1) : f.h0;
     f.m0 = PARTS == 3 ? *(const float4*)(ap + LO) : f.h0;
@@ -909,19 +915,22 @@ void conv_mfma_kernel(ConvParams p) {
   for (int f = 0; f < kMaxFusedAdds; ++f)
     if (f < p.n_fused && p.fused[f].keeps_z && !(p.fused[f].act == kActNone || p.fused[f].act == kActRelu))
       simple_acts = false;
-  auto epilogue_simple = [&](auto sp_tag) {
+  // (one copy per number of fused ADDs, for one ADD with and without an accumulated tensor: a stage
+  // that does not exist would still issue its stores)
+  auto epilogue_simple = [&](auto sp_tag, auto nf_tag, auto kz_tag) {
     constexpr bool HAS_SP = decltype(sp_tag)::value;
+    constexpr int NF = decltype(nf_tag)::value;   // fused ADDs
+    constexpr int KZ = decltype(kz_tag)::value;   // they keep a z: 0 no, 1 yes, 2 looked up
     const bool dense = p.dense != 0;
     const bool relu0 = p.act == kActRelu;
-    bool f_on[kMaxFusedAdds], f_kz[kMaxFusedAdds], f_relu[kMaxFusedAdds];
+    bool f_kz[kMaxFusedAdds], f_relu[kMaxFusedAdds];
     __amdgpu_buffer_rsrc_t f_out_r[kMaxFusedAdds], f_z_r[kMaxFusedAdds];
 #pragma unroll
-    for (int f = 0; f < kMaxFusedAdds; ++f) {
-      f_on[f] = f < p.n_fused;
-      f_kz[f] = f_on[f] && p.fused[f].keeps_z;
+    for (int f = 0; f < NF; ++f) {
+      f_kz[f] = KZ == 2 ? p.fused[f].keeps_z != 0 : KZ == 1;
       f_relu[f] = f_kz[f] && p.fused[f].act == kActRelu;
-      // (a stage that does not exist stores nowhere: its offsets are out of range)
-      f_out_r[f] = out_rsrc(at_stream(f_on[f] ? p.fused[f].out : p.out, so));
+      // (a z that does not exist is stored nowhere: its offsets are out of range)
+      f_out_r[f] = out_rsrc(at_stream(p.fused[f].out, so));
       f_z_r[f] = out_rsrc(at_stream(f_kz[f] ? p.fused[f].z : p.out, so));
     }
     const __amdgpu_buffer_rsrc_t sp_delta_r = out_rsrc(at_stream(HAS_SP ? p.sp.delta : p.out, so));
@@ -941,15 +950,18 @@ void conv_mfma_kernel(ConvParams p) {
       if (o != 0.0f) nz_mine |= 1ull << (it * EP_SITES);
       // fused ADD nodes (Eq.11 followed by Eq.12-14): a = the value just produced, b = skip input
 #pragma unroll
-      for (int f = 0; f < kMaxFusedAdds; ++f) {
+      for (int f = 0; f < NF; ++f) {
         const float lin = o + f_skip[f][it];
-        const float z2_new = dense ? lin : f_zold[f][it] + lin;
-        ep_store_at(f_z_r[f], f_kz[f] ? at_site : kSkipAccess, it, z2_new);
-        float o2 = f_relu[f] ? fmaxf(z2_new, 0.0f) - fmaxf(f_zold[f][it], 0.0f) : lin;
+        float o2 = lin;
+        if (KZ != 0) {
+          const float z2_new = dense ? lin : f_zold[f][it] + lin;
+          ep_store_at(f_z_r[f], f_kz[f] ? at_site : kSkipAccess, it, z2_new);
+          o2 = f_relu[f] ? fmaxf(z2_new, 0.0f) - fmaxf(f_zold[f][it], 0.0f) : lin;
+        }
         o2 = on_site ? o2 : 0.0f;
-        ep_store_at(f_out_r[f], f_on[f] ? at_site : kSkipAccess, it, o2);
-        if (f_on[f] && o2 != 0.0f) nz_fused_mine[f] |= 1ull << (it * EP_SITES);
-        o = f_on[f] ? o2 : o;
+        ep_store_at(f_out_r[f], at_site, it, o2);
+        if (o2 != 0.0f) nz_fused_mine[f] |= 1ull << (it * EP_SITES);
+        o = o2;
       }
       // fused sparsification layer on the last stage's increment (Eq.3-8): x_corr = delta + x_inc,
       // y_inc = k floor(0.5 + x_corr / k), delta = x_corr - y_inc where x_inc is nonzero; elsewhere
@@ -967,7 +979,17 @@ void conv_mfma_kernel(ConvParams p) {
     }
   };
   if (simple_acts) {
-    if (p.sp.delta) epilogue_simple(std::true_type{}); else epilogue_simple(std::false_type{});
+    using std::integral_constant;
+    if (p.sp.delta) {
+      if (p.n_fused == 0) epilogue_simple(std::true_type{}, integral_constant<int, 0>{}, integral_constant<int, 0>{});
+      else if (p.n_fused == 1) epilogue_simple(std::true_type{}, integral_constant<int, 1>{}, integral_constant<int, 2>{});
+      else epilogue_simple(std::true_type{}, integral_constant<int, 2>{}, integral_constant<int, 2>{});
+    } else {
+      if (p.n_fused == 0) epilogue_simple(std::false_type{}, integral_constant<int, 0>{}, integral_constant<int, 0>{});
+      else if (p.n_fused == 1 && !p.fused[0].keeps_z) epilogue_simple(std::false_type{}, integral_constant<int, 1>{}, integral_constant<int, 0>{});
+      else if (p.n_fused == 1) epilogue_simple(std::false_type{}, integral_constant<int, 1>{}, integral_constant<int, 1>{});
+      else epilogue_simple(std::false_type{}, integral_constant<int, 2>{}, integral_constant<int, 2>{});
+    }
   } else {
 #pragma unroll
   for (int it = 0; it < EP_ITERS; ++it) {
@@ -1134,6 +1156,20 @@ void launch_variant(const ConvParams& p, hipStream_t s) {
   const long long in_sites = p.upsample ? (long long)p.lo_h * p.lo_w : (long long)p.gi.h * p.gi.w;
   q.wg_swap = (long long)p.k * p.k * p.go.c > in_sites && p.go.tiles() * (2 / MB) <= 65535;
   const int n_ck = p.c_out_pad / 32 * (KSP ? p.ks : 1);
+  // divisors of the kernel's index arithmetic
+  auto magic32 = [](long long n, int d) {  // for dividends below n
+    return d == 1 || n * d >= (1ll << 32) ? 0u : (unsigned)((0x100000000ull + (unsigned)d - 1) / (unsigned)d);
+  };
+  auto magic16 = [](int d) { return (65536 + d - 1) / d; };
+  q.tx_magic = magic32(p.go.tiles(), p.go.tx);
+  q.lo_tx_magic = p.upsample ? magic32(p.go.tiles(), (p.lo_w + 7) >> 3) : 0u;
+  q.co_magic = magic32(n_ck, p.c_out_pad / 32);
+  q.k_magic[0] = magic16(p.k);
+  q.k_magic[1] = p.fold_list ? magic16(p.fold_k) : 0;
+  q.gw_magic[0] = magic16(PW);
+  q.gw_magic[1] = p.fold_list ? magic16(7 + p.fold_k) : 0;
+  q.gw_magic[2] = magic16(PW / 2 + 3);
+  q.nbx_magic = magic16(((PW - p.pad - 2) >> 1) - ((-p.pad - 1) >> 1) + 1);  // (a tile's first column is even)
   dim3 grid(p.go.tiles() * (2 / MB), n_ck, p.st.n);
   if (q.wg_swap) grid = dim3(n_ck, p.go.tiles() * (2 / MB), p.st.n);
   if (CHUNK == 32 && p.upsample) {

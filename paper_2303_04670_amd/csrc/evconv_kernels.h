@@ -119,6 +119,11 @@ struct ConvParams {
   // counters (zero between launches) lie in ks_part and ks_count, of the sizes that
   // conv_mfma_split_scratch gives
   int ks, ks_chunks;
+  // divisors of the kernel's index arithmetic as magic factors, set by its launcher: tiles per row of
+  // the output and of the stored tensor, blocks of output channels, taps per row [plain, folded],
+  // gathered sites per row [plain, folded, up-sampled], 2 x 2 blocks per row of an up-sampled patch
+  unsigned tx_magic, lo_tx_magic, co_magic;
+  int k_magic[2], gw_magic[3], nbx_magic;
   float* ks_part; unsigned* ks_count;
   // few-channel pointwise kernel only: the node is a network output and the kernel keeps the
   // public tensors itself (y += increment, dy = increment; C x H x W); null otherwise.
