@@ -1137,6 +1137,17 @@ inline int chunk_for(const ConvParams& p) {
   // gather round trips, which is what these latency-bound launches consist of
   if (p.stride == 1 && p.k <= 3 && p.gi.c % 128 == 0 &&
       (long long)p.go.tiles() * (p.c_out_pad / 32) * p.st.n * 2 < 512) return 128;
+  // Stride-2 layers of few half-tile workgroups: a patch of 64 (3 x 3) or 32 (5 x 5) channels still fits
+  // the gather registers and saves chunk changes; where the chip is full several times over the
+  // smaller patch's extra workgroups per CU win.  Measured in fp32 mode, chunks of 16 -> larger:
+  // 128 -> 256 on 32 x 44 (384 workgroups) 31.5 -> 28.3 us, 64 -> 128 on 64 x 88 (704) 23.7 -> 22.9, 32 ->
+  // 64 on 128 x 176 (1408) 27.1 -> 27.7; ResNet-18's 64 -> 128 on 28 x 28 (128) 13.2 -> 11.5; with 16
+  // streams (6144 to 22528) 218 -> 252, 215 -> 250 and 294 -> 325.
+  const long long n_half = (long long)p.go.tiles() * (p.c_out_pad / 32) * p.st.n * 2;
+  if (p.stride == 2 && n_half <= 1024) {
+    if (p.k <= 3 && p.gi.c % 64 == 0 && n_half < 512) return 64;
+    if (p.k <= 5 && p.gi.c % 32 == 0) return 32;
+  }
   if (p.stride == 1 && p.k <= 3 && p.gi.c % 64 == 0) return 64;
   if (p.stride == 1 && (p.gi.c % 32 == 0 || (p.gi.c % 16 != 0 && p.gi.c > 32))) return 32;  // ragged: fewer, padded chunks
   return 16;
@@ -1196,6 +1207,12 @@ void launch_shape(const ConvParams& p, hipStream_t s) {
   bool halves = !(n2 >= 512 && p.k * p.k * p.gi.c >= 1600) || fill(2 * n2) > fill(n2) + 0.1;
   const long long n = halves ? 2 * n2 : n2;
   bool eight = n < 512;  // few workgroups: 8 waves each split K further
+  if (p.stride == 2 && (CHUNK == 32 || CHUNK == 64)) {
+    constexpr int C2 = CHUNK == 32 ? 32 : 64, K2 = CHUNK == 32 ? 5 : 3;
+    if (2 * n2 < 512) launch_variant<C2, 8, OPM, 1, false, K2>(p, s);
+    else launch_variant<32, 4, OPM, 1, false, 5>(p, s);
+    return;
+  }
   if (CHUNK == 128) {  // chosen only for few workgroups: other variants are not built
     launch_variant<CHUNK, 8, OPM, 1>(p, s);
     return;

@@ -1546,3 +1546,18 @@ def test_wide_inputs_and_wide_outputs(c, co, hw):
     y_dense = gpu.outputs()[0]["y"]
     assert float((y_dense - y_inc).abs().max()) <= 1e-5 * max(1.0, float(y_dense.abs().max()))
     gpu.destroy()
+
+
+@pytest.mark.parametrize("ci,co,k,hw", [(32, 48, 5, (31, 45)), (64, 80, 3, (33, 50)), (64, 32, 1, (9, 7)), (96, 128, 3, (141, 150)),
+                                        (32, 128, 5, (140, 153)), (160, 256, 5, (60, 66))])
+def test_stride2_convs_in_larger_channel_chunks(ci, co, k, hw):
+    """Stride-2 layers of few workgroups take chunks of 64 (3 x 3, 1 x 1) or 32 channels; with eight
+    waves per workgroup and, from 512 workgroups on, four.  Ragged sizes, sparse and dense steps."""
+    h, w = hw
+    b = wl._NetBuilder("s2", ci, h, w, ci + k, bias=True)
+    b.conv(-1, co, k, 2, act=wl.ACT_RELU, out=1)
+    net = b.finish()
+    rng = np.random.default_rng(ci + h)
+    x0 = rng.standard_normal((ci, h, w)).astype(np.float32)
+    incs = [(rng.standard_normal(x0.shape) * (rng.random((1, h, w)) < d)).astype(np.float32) for d in (0.01, 1.0, 0.02)]
+    run_stream(net, x0, incs, "increment", label=f"stride 2, {ci} -> {co}, {k} x {k}", max_flips=3, tol=1e-5)
