@@ -316,23 +316,24 @@ void conv_mfma_kernel(ConvParams p) {
   // conflicts, they keep the dense pitch.)
   const int RP = s == 1 ? ((PW * CS + 31) / 64) * 64 + 32 : PW * CS;
   float* const s_low = s_mem + PH * RP;  // UPS only
-  const int total_v = GH * GW * NV;
+  const int last_site = GH * GW - 1;
   const int gw_magic = p.gw_magic[fold ? 1 : ups ? 2 : 0];  // site / GW == (site * gw_magic) >> 16 for site < 441
   const unsigned row_bytes = (unsigned)(SW * Cin) * 4u, g_origin = (unsigned)gy0 * row_bytes + (unsigned)(gx0 * Cin) * 4u;
+  // (a thread whose j-th item lies beyond the region repeats the last site's: the same value goes to
+  // the same place twice, and no item needs a test of its own, only one that is the same for the
+  // whole workgroup where no thread has a j-th item)
+  static_assert(NT % NV == 0, "a thread's items are of one channel group");
+  const int v4 = tid % NV;  // channel group of this thread's items
+  auto has_item = [&](int j) { return (UPS && PARTS != 1) || j * (NT / NV) <= last_site; };
   int lds_off[MAXG];     // (until the occupancy is known: patch row and column in bits 16-23 and 24-31)
   unsigned g_off[MAXG];
 #pragma unroll
   for (int j = 0; j < MAXG; ++j) {
-    const int e = tid + j * NT;
-    lds_off[j] = -1;
-    g_off[j] = kOob;
-    if (e < total_v) {
-      const int site = e / NV, v = e - site * NV;
-      // (24-bit products: full rate, unlike 32-bit ones)
-      const int py = __umul24(site, gw_magic) >> 16, px = site - __umul24(py, GW);
-      lds_off[j] = (ups ? site * CSL + v * 4 : __umul24(py, RP) + px * CS + v * 2) | (py << 16) | (px << 24);
-      g_off[j] = g_origin + (unsigned)py * row_bytes + __umul24(px, Cin) * 4u + v * 16u;
-    }
+    const int site = min(tid / NV + j * (NT / NV), last_site);
+    // (24-bit products: full rate, unlike 32-bit ones)
+    const int py = __umul24(site, gw_magic) >> 16, px = site - __umul24(py, GW);
+    lds_off[j] = (ups ? site * CSL + v4 * 4 : __umul24(py, RP) + px * CS + v4 * 2) | (py << 16) | (px << 24);
+    g_off[j] = g_origin + (unsigned)py * row_bytes + __umul24(px, Cin) * 4u + v4 * 16u;
   }
   // UPS: every patch element from its four sources in the low-resolution buffer, with the
   // weights and the summation order of the stand-alone up-sampling operator
@@ -441,7 +442,12 @@ void conv_mfma_kernel(ConvParams p) {
     // (a weight-folded workgroup's tile lies inside the stored image, all of its outputs exist)
     if (lr >= 0 && lr < NROWS && (fold || (oy < p.go.h && ox < p.go.w))) {
       unsigned rows = 0;
-      for (int ky = 0; ky < K; ++ky) rows |= s_rows[lr * s + ky];
+      // (all seven possible rows at once instead of a chain of K reads; s_rows is long enough)
+#pragma unroll
+      for (int ky = 0; ky < 7; ++ky) {
+        const unsigned row = s_rows[lr * s + ky];
+        rows |= ky < K ? row : 0u;
+      }
       touched = p.dense || ((rows >> (lx * s)) & ((1u << K) - 1u)) != 0;
     }
     touched_word = __ballot(touched);
@@ -507,7 +513,7 @@ void conv_mfma_kernel(ConvParams p) {
   // the gather's offsets, now conditioned on the occupancy (out of range where the site is inactive)
 #pragma unroll
   for (int j = 0; j < MAXG; ++j) {
-    if (lds_off[j] < 0) continue;
+    if (!has_item(j)) continue;
     const int py = (lds_off[j] >> 16) & 0xff, px = lds_off[j] >> 24;
     lds_off[j] &= 0xffff;
     const unsigned row = ups ? s_lrows[py] : s_rows[py];
@@ -528,8 +534,9 @@ void conv_mfma_kernel(ConvParams p) {
   auto fetch = [&](int c0) {
 #pragma unroll
     for (int j = 0; j < MAXG; ++j) {
+      if (!has_item(j)) continue;
       unsigned off = g_off[j];
-      if (ragged && c0 + ((tid + j * NT) % NV) * 4 >= Cin) off = kOob;
+      if (ragged && c0 + v4 * 4 >= Cin) off = kOob;
       pre[j] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(in_rsrc, off, c0 * 4, 0));
     }
   };
@@ -565,10 +572,10 @@ void conv_mfma_kernel(ConvParams p) {
   };
   auto stash = [&](int c0) {
     if (tail) {  // (uniform; nets with c_in % 4 == 0 pay nothing)
+      const int left = Cin - (c0 + v4 * 4);  // channels of this thread's group inside c_in
+      if (left > 0 && left < 4) {
 #pragma unroll
-      for (int j = 0; j < MAXG; ++j) {
-        const int left = Cin - (c0 + ((tid + j * NT) % NV) * 4);  // channels of this group inside c_in
-        if (left > 0 && left < 4) {
+        for (int j = 0; j < MAXG; ++j) {
           if (left < 2) pre[j].y = 0.0f;
           if (left < 3) pre[j].z = 0.0f;
           pre[j].w = 0.0f;
@@ -576,15 +583,18 @@ void conv_mfma_kernel(ConvParams p) {
       }
     }
 #pragma unroll
-    for (int j = 0; j < MAXG; ++j)
-      if (lds_off[j] >= 0) {
-        if (ups) *(float4*)&s_low[lds_off[j]] = pre[j];
-        else put(lds_off[j], pre[j]);
-      }
+    for (int j = 0; j < MAXG; ++j) {
+      if (!has_item(j)) continue;
+      if (ups) *(float4*)&s_low[lds_off[j]] = pre[j];
+      else put(lds_off[j], pre[j]);
+    }
   };
   auto interpolate = [&]() {
 #pragma unroll
     for (int b = 0; b < MAXB; ++b) {
+      // (fp32 mode, whole tiles: unpacked here and not once before the chunk loop, where the unpacked
+      // values, kept across the contraction, do not fit the registers)
+      if (PARTS == 3 && MB == 2) asm volatile("" : "+v"(ib_src[b]), "+v"(ib_dst[b]));
       const int mask = ib_dst[b] >> 16;
       if (mask == 0) continue;
       const float* q = &s_low[ib_src[b] & 0xfff];
