@@ -628,12 +628,11 @@ void conv_mfma_kernel(ConvParams p) {
   const int cin_rows = cin_pad >> 3;                        // 16-byte weight rows per tap: 8 bf16
   const int a_lane_off = mly * s * RP + mlx * s * CS + half * 4;
   const int a_blk1 = 4 * s * RP;  // the second block starts four tile rows further down
-  // Units of this wave: u_j = wave + j * NW, unit u = (tap u / KG, channel group u % KG).  KG divides
-  // NW, so a wave keeps one channel group and steps through the taps.
-  static_assert(NW % KG == 0, "a wave's units share one channel group");
-  const int kg = wave % KG, tap0 = wave / KG;
-  constexpr int TSTEP = NW / KG;
-  const int n_mine = max(0, (K * K - tap0 + TSTEP - 1) / TSTEP);
+  // Units of a chunk: (tap u / kgn, channel group u % kgn), kgn = KG groups of 16 channels or, with
+  // p.tail_units in a last chunk that c_in does not fill, as many as hold channels; unit
+  // u_j = wave + j * NW is this wave's j-th.
+  constexpr bool TAIL = !UPS && !KSP && S2K == 0 && CHUNK == 32;  // the other variants' chunks are full or one group
+  int n_mine = 0;
   // Both fragment addresses are a per-lane constant plus a per-unit part that is the same in all
   // lanes.  Lane j of a table register holds unit j's part (beyond the last unit: the last one's, so
   // that look-ahead loads stay unconditional and in bounds) and a readlane brings it into a scalar
@@ -646,14 +645,20 @@ void conv_mfma_kernel(ConvParams p) {
   const char* const w_base = fold ? (const char*)p.w_fold + (size_t)(fpy * 2 + fpx) * w_set : (const char*)p.w;
   const __amdgpu_buffer_rsrc_t w_rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)w_base, 0, (int)w_set, 0x00020000);
   const unsigned w_lane = (unsigned)(half * cop + co0 + m) * 16u;
-  unsigned w_table;  // byte offset of unit `lane`'s weight rows in a chunk that starts at channel 0
-  int a_table;       // offset of its patch sites, words
-  {
-    const int tap = min(tap0 + __umul24(lane, TSTEP), tap0 + __umul24(n_mine - 1, TSTEP));
+  unsigned w_table = 0;  // byte offset of unit `lane`'s weight rows in a chunk that starts at channel 0
+  int a_table = 0;       // offset of its patch sites, words
+  auto set_units = [&](int c0) {  // for the chunk starting at channel c0
+    const int kgn = TAIL && p.tail_units ? min(KG, (Cin - c0 + UCH - 1) / UCH) : KG;
+    const int n_units = K * K * kgn;
+    const int u = min(wave + lane * NW, n_units - 1);
+    static_assert(!TAIL || KG == 2, "one or two groups per chunk");
+    const int tap = kgn == KG ? u / KG : u, kg = kgn == KG ? u % KG : 0;
     const int ky = __umul24(tap, p.k_magic[fold ? 1 : 0]) >> 16, kx = tap - __umul24(ky, K);  // tap < 49
     a_table = __umul24(ky, RP) + kx * CS + kg * 8;  // a unit's 16 bf16 are 8 words
     w_table = (__umul24(tap, cin_rows) + kg * (UCH / 8)) * (unsigned)(cop * 16);  // 16-byte rows of 8 bf16
-  }
+    n_mine = max(0, (n_units - wave + NW - 1) / NW);
+  };
+  set_units(c_lo);
   // fragments of unit j of the chunk starting at channel c0
   auto b_load = [&](int c0, int j) {
     const unsigned soff = __builtin_amdgcn_readlane(w_table, j) + (unsigned)((c0 >> 3) * (cop * 16));
@@ -770,6 +775,7 @@ void conv_mfma_kernel(ConvParams p) {
     if (j < n_mine) step(aq0, aq1, j, bq0);
     if (j + 1 < n_mine) step(aq1, aq2, j + 1, bq1);
     if (more) {
+      if (TAIL && p.tail_units && c0 + 2 * CHUNK > Cin) set_units(c0 + CHUNK);  // (uniform; the next chunk is not full)
       bq0 = b_load(c0 + CHUNK, 0);
       bq1 = b_load(c0 + CHUNK, 1);
     }

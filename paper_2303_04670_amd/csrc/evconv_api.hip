@@ -76,6 +76,7 @@ struct NodePlan {
   bool keeps_z = false, structural = false;
   int kernel = 0;
   int c_out_pad = 0;
+  int tail_units = 0;       // ConvParams::tail_units
   int fused_into = -1;      // ADD or SPARSIFY node executed in the epilogue of that conv node
   int fused_sp = -1;        // conv node: the SPARSIFY node it executes behind its last epilogue stage
   int n_fused = 0;          // conv node: ADD nodes it executes, in order
@@ -96,6 +97,7 @@ struct NodePlan {
   float* z2 = nullptr;
   size_t off_occ_saved = 0;  // DELAY: S_out words of the delayed node as the previous step left them
   uint64_t* occ_saved = nullptr;
+  bool saved_in_lists = false;  // DELAY: its words are copied by the compaction kernel
   float* step = nullptr;
   float step_fixed = -1.0f; // >= 0: k supplied by the description
   size_t off_z = 0, off_out = 0, off_pool = 0, off_occ = 0, off_touched = 0, off_idx = 0, off_count = 0,
@@ -477,6 +479,7 @@ evconv_status run_pass(evconv_net* net, const float* input, int builder_mode, Pa
         p.n_fused = n.n_fused;
         p.st = net->st;
         p.upsample = 0; p.lo_h = 0; p.lo_w = 0;
+        p.tail_units = n.tail_units;
         p.ks = 0; p.ks_chunks = 0;
         p.ks_part = (float*)(net->ws + net->L.off_ks_part);
         p.ks_count = (unsigned*)(net->ws + net->L.off_ks_count);
@@ -578,10 +581,12 @@ evconv_status run_pass(evconv_net* net, const float* input, int builder_mode, Pa
     }
   }
   // recurrent state: keep the delayed nodes' active sets for the next pass (the occupancy words
-  // are cleared when it starts)
+  // are cleared when it starts).  The compaction of the masks does that on its way, except where
+  // the words are cleared before it runs or a node is delayed a second time.
+  const bool save_in_lists = !reinit;
   for (size_t i = 0; i < net->L.nodes.size(); ++i) {
     const NodePlan& n = net->L.nodes[i];
-    if (n.kernel == kKernDelay) launch_copy_u64(n.occ_saved, net->L.nodes[n.d.in0].occ, (size_t)n.go.tiles(), net->st, s);
+    if (n.kernel == kKernDelay && !(save_in_lists && n.saved_in_lists)) launch_copy_u64(n.occ_saved, net->L.nodes[n.d.in0].occ, (size_t)n.go.tiles(), net->st, s);
   }
   net->last_dense = dense != 0;
   if (pass == kPassReset) launch_fill_u64(net->occ_nodes, net->L.n_occ_words, 0, net->st, s);
@@ -599,7 +604,7 @@ evconv_status run_pass(evconv_net* net, const float* input, int builder_mode, Pa
   }
   {
     const bool timed = timed_begin();
-    launch_build_lists(net->sets_dev, (int)net->L.nodes.size() + 1, net->L.max_ty, net->st, s);
+    launch_build_lists(net->sets_dev, (int)net->L.nodes.size() + 1, net->L.max_ty, save_in_lists, net->st, s);
     timed_end(timed, (int)net->L.nodes.size());
   }
   hipError_t e = hipGetLastError();
@@ -679,19 +684,23 @@ hipError_t prepare_fold(evconv_net* net, NodePlan& n, const void* weights, const
                   dst[(size_t)ci * co_n + co] += coef * (double)src[((size_t)co * ci_n + ci) * k * k + ky * k + kx];
             }
   const int ci_p = (ci_n + 31) / 32 * 32;
+  ConvParams probe;
+  probe.gi = n.ga; probe.go = n.go; probe.k = k; probe.stride = n.d.stride; probe.c_out_pad = cop; probe.n_fused = 0;
+  probe.pad = pad; probe.st = Streams{net->L.stride, net->L.n_streams}; probe.tail_units = n.tail_units;
   const int parts = weight_part_count(n.d.wdtype);
   const size_t plane = (size_t)taps * ci_p * cop;  // values per part and phase; a phase's planes follow each other
   std::vector<uint16_t> staging(4 * parts * plane, 0);
   for (int ph = 0; ph < 4; ++ph)
     for (int t = 0; t < taps; ++t)
-      for (int c8 = 0; c8 < ci_n; c8 += 8)
+      for (int c8 = 0; c8 < ci_n; c8 += 8) {
+        const float sign = parts == 3 && conv_mfma_negated(probe, t, c8) ? -1.0f : 1.0f;
         for (int co = 0; co < co_n; ++co) {
           float v[8];
-          const float sign = parts == 3 && ((c8 >> 4) & 1) ? -1.0f : 1.0f;  // conv_mfma_negated, chunks of 32 channels
           for (int e = 0; e < 8; ++e)
             v[e] = c8 + e < ci_n ? sign * (float)folded[(((size_t)ph * taps + t) * ci_n + c8 + e) * co_n + co] : 0.0f;
           weight_parts8(v, parts, staging.data() + ph * parts * plane + (((size_t)t * (ci_p / 8) + c8 / 8) * cop + co) * 8, plane);
         }
+      }
   n.w_fold = net->ws + n.off_w_fold;
   n.fold_list = (int*)(net->ws + n.off_fold_list);
   n.fold_k = kf;
@@ -758,7 +767,7 @@ evconv_status create_impl(const evconv_net_desc* desc, const void* weights, size
   if (e != hipSuccess) { g_create_error = std::string("clearing the workspace: ") + hipGetErrorString(e); delete net; return EVCONV_ERR_HIP; }
 
   std::vector<SetDesc> sets(L.nodes.size() + 1);
-  sets[0] = SetDesc{net->occ_in, net->idx_in, net->count_in, net->bitmap_in, L.gin.h, L.gin.w, L.gin.tx, L.gin.ty};
+  sets[0] = SetDesc{net->occ_in, net->idx_in, net->count_in, net->bitmap_in, L.gin.h, L.gin.w, L.gin.tx, L.gin.ty, nullptr};
   std::vector<float> staging;
   for (size_t i = 0; i < L.nodes.size(); ++i) {
     NodePlan& n = L.nodes[i];
@@ -791,12 +800,14 @@ evconv_status create_impl(const evconv_net_desc* desc, const void* weights, size
       n.dy = (float*)(ws + n.off_dy);
       net->outputs.push_back((int)i);
     }
-    sets[i + 1] = SetDesc{n.occ, n.idx, n.count, n.bitmap, n.go.h, n.go.w, n.go.tx, n.go.ty};
+    sets[i + 1] = SetDesc{n.occ, n.idx, n.count, n.bitmap, n.go.h, n.go.w, n.go.tx, n.go.ty, nullptr};
     if (n.d.op == EVCONV_OP_CONV2D || n.d.op == EVCONV_OP_LINEAR) {
       const int k = n.d.kh, ci_n = n.d.c_in, co_n = n.d.c_out, cop = n.c_out_pad;
       ConvParams probe;
       probe.gi = n.ga; probe.go = n.go; probe.k = k; probe.stride = n.d.stride; probe.c_out_pad = cop;
       probe.n_fused = 0; probe.pad = n.d.pad; probe.st = Streams{L.stride, L.n_streams};
+      n.tail_units = n.d.in0 < 0 || L.nodes[n.d.in0].d.op != EVCONV_OP_UPSAMPLE_BILINEAR2X;
+      probe.tail_units = n.tail_units;
       const bool force_valu = (net->flags & EVCONV_FLAG_FORCE_VALU) != 0;
       // (a weight that is infinite or NaN: the vector kernel, which multiplies it as it is)
       bool finite = true;
@@ -846,15 +857,16 @@ evconv_status create_impl(const evconv_net_desc* desc, const void* weights, size
         const size_t plane = (size_t)k * k * ci_p * cop;
         staging.assign((parts * plane + 1) / 2, 0.0f);
         uint16_t* h16 = (uint16_t*)staging.data();
-        std::vector<char> neg(2 * k * k);  // [tap][parity of the group of 16 channels]
-        for (int t = 0; t < k * k; ++t)
-          for (int g = 0; g < 2; ++g) neg[t * 2 + g] = conv_mfma_negated(probe, t, 16 * g);
+        const int groups = (ci_n + 15) / 16;
+        std::vector<float> sign((size_t)k * k * groups, 1.0f);  // [tap][group of 16 channels]
+        for (int t = 0; t < k * k && parts == 3; ++t)
+          for (int g = 0; g < groups; ++g) sign[(size_t)t * groups + g] = conv_mfma_negated(probe, t, 16 * g) ? -1.0f : 1.0f;
         for (int co = 0; co < co_n; ++co)
           for (int c8 = 0; c8 < ci_n; c8 += 8)
             for (int t = 0; t < k * k; ++t) {
               float v[8];
-              const float sign = parts == 3 && neg[t * 2 + ((c8 >> 4) & 1)] ? -1.0f : 1.0f;
-              for (int e = 0; e < 8; ++e) v[e] = c8 + e < ci_n ? sign * src[((size_t)co * ci_n + c8 + e) * k * k + t] : 0.0f;
+              const float sg = sign[(size_t)t * groups + c8 / 16];
+              for (int e = 0; e < 8; ++e) v[e] = c8 + e < ci_n ? sg * src[((size_t)co * ci_n + c8 + e) * k * k + t] : 0.0f;
               weight_parts8(v, parts, h16 + (((size_t)t * (ci_p / 8) + c8 / 8) * cop + co) * 8, plane);
             }
       } else {
@@ -873,6 +885,11 @@ evconv_status create_impl(const evconv_net_desc* desc, const void* weights, size
       }
       if (e != hipSuccess) { g_create_error = std::string("weight upload: ") + hipGetErrorString(e); delete net; return EVCONV_ERR_HIP; }
     }
+  }
+  for (NodePlan& n : L.nodes) {
+    if (n.d.op != EVCONV_OP_DELAY || sets[n.d.in0 + 1].save) continue;
+    sets[n.d.in0 + 1].save = n.occ_saved;
+    n.saved_in_lists = true;
   }
   e = hipMemcpyAsync(net->sets_dev, sets.data(), sets.size() * sizeof(SetDesc), hipMemcpyHostToDevice, net->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(net->stream);

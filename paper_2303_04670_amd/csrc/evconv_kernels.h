@@ -114,6 +114,10 @@ struct ConvParams {
   // matrix-core kernel only, set by its launcher: the grid's x dimension runs over the blocks of
   // 32 output channels and y over the tiles, instead of the other way round
   int wg_swap;
+  // matrix-core kernel only: a last channel chunk that c_in does not fill is contracted over the
+  // groups of 16 channels that exist (not in convs that may read through an up-sampling: their
+  // variants have no registers to spare for it); part of the weights' layout (conv_mfma_negated)
+  int tail_units;
   // matrix-core kernel only, set by its launcher: the channels are split over ks workgroups per
   // output block (0: not), ks_chunks channel chunks each; their shares of the sums and the arrival
   // counters (zero between launches) lie in ks_part and ks_count, of the sizes that
@@ -221,6 +225,7 @@ struct DelayParams {
   int dense;                  // this pass is a regular forward pass
   int last_dense;             // the previous pass was one
   int zero_state;             // reset: the state before the first frame is zero
+  unsigned cv_magic;          // set by the launcher: ceil(2^32 / channel vectors per site), or 0
   Streams st;
 };
 void launch_delay(const DelayParams& p, hipStream_t s);
@@ -231,8 +236,9 @@ void launch_copy_u64(uint64_t* dst, const uint64_t* src, size_t n, Streams st, h
 struct SetDesc {
   const uint64_t* occ; int32_t* idx; int32_t* count; uint64_t* bitmap;
   int h, w, tx, ty;
+  uint64_t* save;  // copy of the words for the next pass (a node that a DELAY reads), or null
 };
-void launch_build_lists(const SetDesc* sets_dev, int n_sets, int max_ty, Streams st, hipStream_t s);
+void launch_build_lists(const SetDesc* sets_dev, int n_sets, int max_ty, bool save, Streams st, hipStream_t s);
 
 void launch_fill_u64(uint64_t* p, size_t n, uint64_t v, Streams st, hipStream_t s);
 

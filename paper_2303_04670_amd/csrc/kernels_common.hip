@@ -307,12 +307,13 @@ __global__ __launch_bounds__(256) void elementwise_kernel(EwParams p) {
   const int v0 = blockIdx.y * kEwVecPerBlock;
   const int cv = min(kEwVecPerBlock, cv_all - v0);
   const int total = n_sites * cv;
+  const int cv_magic = (65536 + cv - 1) / cv;  // e / cv == (e * cv_magic) >> 16 for e < 1024 (cv <= 16)
 
   // sites at which this thread produced a nonzero element; the waves' ORs meet in LDS afterwards
   // (one LDS atomic per element would be served lane by lane where the lanes share a site)
   uint64_t nz_sites = 0;
   for (int e = tid; e < total; e += 256) {
-    const int r = e / cv, v = v0 + (e - r * cv);
+    const int r = __umul24(e, cv_magic) >> 16, v = v0 + (e - __umul24(r, cv));
     const int site = s_sites[r];
     const int oy = tile_y * 8 + (site >> 3), ox = tile_x * 8 + (site & 7);
     const size_t q = (size_t)oy * p.go.w + ox;
@@ -650,7 +651,9 @@ void launch_integrate(const IntegrateParams& p, hipStream_t s) {
 }
 
 // =============================================================================== recurrent state
-// Workgroup = one 8 x 8 tile; thread = (site, channel) pairs strided over the tile's active sites.
+// Workgroup = one 8 x 8 tile; thread = (site, channel vector) pairs strided over the tile's active
+// sites.  Bound by HBM (reads the delayed increment and the state, writes both).
+template <int VEC>
 __global__ __launch_bounds__(256) void delay_kernel(DelayParams p) {
   const size_t so = (size_t)blockIdx.z * p.st.stride;
   const float* src = at_stream(p.src_out, so);
@@ -658,12 +661,7 @@ __global__ __launch_bounds__(256) void delay_kernel(DelayParams p) {
   float* out = at_stream(p.out, so);
   const int tile = blockIdx.x;
   const int tile_y = tile / p.g.tx, tile_x = tile - tile_y * p.g.tx;
-  const int rows = min(8, p.g.h - tile_y * 8), cols = min(8, p.g.w - tile_x * 8);
-  uint64_t inb = 0;
-  {
-    const uint64_t rowbits = cols >= 8 ? 0xffull : ((1ull << cols) - 1ull);
-    for (int r = 0; r < rows; ++r) inb |= rowbits << (8 * r);
-  }
+  const uint64_t inb = inbounds_word(p.g.h, p.g.w, tile_y, tile_x);
   const uint64_t saved = at_stream(p.occ_saved, so)[tile] & inb;
   // sites visited: all of the tile in or after a regular pass, the delayed node's active set otherwise
   const uint64_t word = (p.dense || p.last_dense) ? inb : saved;
@@ -671,33 +669,53 @@ __global__ __launch_bounds__(256) void delay_kernel(DelayParams p) {
     at_stream(p.occ_out, so)[tile] = word;
     at_stream(p.occ_touched, so)[tile] = word;
   }
-  const int C = p.g.c;
+  const int C = p.g.c, cv = C / VEC;
   const int n_active = __popcll(word);
   __shared__ unsigned char s_site[64];  // the visited sites in ascending order
   if (threadIdx.x < 64 && ((word >> threadIdx.x) & 1ull))
     s_site[__popcll(word & ((1ull << threadIdx.x) - 1ull))] = (unsigned char)threadIdx.x;
   __syncthreads();
-  for (int e = threadIdx.x; e < n_active * C; e += 256) {
-    const int k = e / C, c = e - k * C;
+  for (int e = threadIdx.x; e < n_active * cv; e += 256) {
+    const int k = p.cv_magic ? (int)__umulhi((unsigned)e, p.cv_magic) : e / cv, c = (e - k * cv) * VEC;
     const int site = s_site[k];
     const int oy = tile_y * 8 + (site >> 3), ox = tile_x * 8 + (site & 7);
     const size_t q = ((size_t)oy * p.g.w + ox) * C + c;
+    VecT<VEC> o, n;
     if (p.dense) {
-      float v = 0.0f;
-      if (!p.zero_state) v = p.last_dense ? src[q] : z[q] + (((saved >> site) & 1ull) ? src[q] : 0.0f);
-      out[q] = v;
-      z[q] = v;
+      o = zerov<VEC>();
+      if (!p.zero_state) {
+        if (p.last_dense) {
+          o = ldv<VEC>(&src[q]);
+        } else {
+          const VecT<VEC> zo = ldv<VEC>(&z[q]);
+          const VecT<VEC> d = ((saved >> site) & 1ull) ? ldv<VEC>(&src[q]) : zerov<VEC>();
+#pragma unroll
+          for (int i = 0; i < VEC; ++i) o.v[i] = zo.v[i] + d.v[i];
+        }
+      }
+      n = o;
     } else {
-      const float zo = z[q];
-      const float inc = p.last_dense ? src[q] - zo : src[q];
-      out[q] = inc;
-      z[q] = zo + inc;
+      const VecT<VEC> zo = ldv<VEC>(&z[q]), x = ldv<VEC>(&src[q]);
+#pragma unroll
+      for (int i = 0; i < VEC; ++i) {
+        o.v[i] = p.last_dense ? x.v[i] - zo.v[i] : x.v[i];
+        n.v[i] = zo.v[i] + o.v[i];
+      }
     }
+    stv<VEC>(&out[q], o);
+    stv<VEC>(&z[q], n);
   }
 }
 
 void launch_delay(const DelayParams& p, hipStream_t s) {
-  hipLaunchKernelGGL(delay_kernel, dim3(p.g.tiles(), 1, p.st.n), dim3(256), 0, s, p);
+  const dim3 grid(p.g.tiles(), 1, p.st.n);
+  const bool vec4 = p.g.c % 4 == 0;
+  const int cv = p.g.c / (vec4 ? 4 : 1);
+  DelayParams q = p;
+  // e / cv by a factor, exact while e * cv < 2^32 (e < 64 * cv)
+  q.cv_magic = cv > 1 && cv < 8192 ? (unsigned)((0x100000000ull + (unsigned)cv - 1) / (unsigned)cv) : 0u;
+  if (vec4) hipLaunchKernelGGL(delay_kernel<4>, grid, dim3(256), 0, s, q);
+  else hipLaunchKernelGGL(delay_kernel<1>, grid, dim3(256), 0, s, q);
 }
 
 __global__ __launch_bounds__(256) void copy_u64_kernel(uint64_t* dst, const uint64_t* src, size_t n, size_t stride) {
@@ -715,7 +733,8 @@ void launch_copy_u64(uint64_t* dst, const uint64_t* src, size_t n, Streams st, h
 // the number of active sites in all earlier strips (a reduction over their occupancy words);
 // inside the strip wave r owns image row r and scans the per-tile byte popcounts with a
 // wave-wide prefix sum, so indices come out strictly ascending in y*W + x.
-__global__ __launch_bounds__(512) void build_lists_kernel(const SetDesc* sets, size_t stream_stride) {
+// A recurrent net's delayed nodes have their words copied to SetDesc::save on the way.
+__global__ __launch_bounds__(512) void build_lists_kernel(const SetDesc* sets, size_t stream_stride, int save) {
   __shared__ int s_part[8];
   __shared__ int s_rowcnt[8];
   SetDesc d = sets[blockIdx.y];  // the descriptors hold stream 0's pointers
@@ -723,10 +742,13 @@ __global__ __launch_bounds__(512) void build_lists_kernel(const SetDesc* sets, s
     const size_t so = (size_t)blockIdx.z * stream_stride;
     d.occ = at_stream(d.occ, so); d.idx = at_stream(d.idx, so);
     d.count = at_stream(d.count, so); d.bitmap = at_stream(d.bitmap, so);
+    d.save = at_stream(d.save, so);
   }
   const int strip = blockIdx.x;
   if (strip >= d.ty) return;
   const int tid = threadIdx.x, lane = tid & 63, r = tid >> 6;
+  if (save && d.save)
+    for (int t = tid; t < d.tx; t += 512) d.save[strip * d.tx + t] = d.occ[strip * d.tx + t];
 
   int cnt = 0;
   for (int t = tid; t < strip * d.tx; t += 512) cnt += __popcll(d.occ[t]);
@@ -787,8 +809,8 @@ __global__ __launch_bounds__(512) void build_lists_kernel(const SetDesc* sets, s
   }
 }
 
-void launch_build_lists(const SetDesc* sets_dev, int n_sets, int max_ty, Streams st, hipStream_t s) {
-  hipLaunchKernelGGL(build_lists_kernel, dim3(max_ty, n_sets, st.n), dim3(512), 0, s, sets_dev, st.stride);
+void launch_build_lists(const SetDesc* sets_dev, int n_sets, int max_ty, bool save, Streams st, hipStream_t s) {
+  hipLaunchKernelGGL(build_lists_kernel, dim3(max_ty, n_sets, st.n), dim3(512), 0, s, sets_dev, st.stride, save ? 1 : 0);
 }
 
 // =============================================================================== rounding step

@@ -26,11 +26,13 @@ int conv_mfma_padded_cin(const ConvParams& p) {
 // survives where random ones average out, as in a global mean: ResNet-18's logits were off by 4.0e-7
 // against 64 bits, 1.2e-7 with the chip's fp32 instruction.  So the units of the odd waves
 // contract negated weights and their sums are negated again where the waves' sums meet.  A unit is
-// 16 channels of one tap, dealt round-robin to an even number of waves: its parity is that of the
-// channel group, or of the tap where a chunk is one group.
+// 16 channels of one tap, dealt round-robin to an even number of waves: the parity of its number
+// inside its chunk, tap * (groups of 16 channels in the chunk) + group, is its wave's.
 bool conv_mfma_negated(const ConvParams& p, int tap, int ci) {
   const KSplit r = ksplit_for(p);
-  return ((r.ks ? r.chunk : chunk_for(p)) >= 32 ? ci >> 4 : tap) & 1;
+  const int chunk = r.ks ? r.chunk : chunk_for(p), c0 = ci / chunk * chunk;
+  const int groups = p.tail_units ? std::min(chunk, (p.gi.c - c0 + 15) / 16 * 16) / 16 : chunk / 16;
+  return (tap * groups + (ci - c0) / 16) & 1;
 }
 // per stream: shares of the sums and arrival counters of a conv whose channels are split over workgroups
 void conv_mfma_split_scratch(const ConvParams& p, size_t* part_floats, size_t* counters) {

@@ -1561,3 +1561,37 @@ def test_stride2_convs_in_larger_channel_chunks(ci, co, k, hw):
     x0 = rng.standard_normal((ci, h, w)).astype(np.float32)
     incs = [(rng.standard_normal(x0.shape) * (rng.random((1, h, w)) < d)).astype(np.float32) for d in (0.01, 1.0, 0.02)]
     run_stream(net, x0, incs, "increment", label=f"stride 2, {ci} -> {co}, {k} x {k}", max_flips=3, tol=1e-5)
+
+
+@pytest.mark.parametrize("mode", ["f32", "split", "bf16"])
+@pytest.mark.parametrize("ci,k", [(33, 3), (47, 5), (69, 3), (96, 1), (37, 7)])
+def test_last_channel_chunk_of_one_group(mode, ci, k):
+    """Input channels that leave the last chunk of 32 with 1..16 channels: its units are the taps
+    alone (in fp32 mode the signs of its stored weights follow).  The same conv behind an
+    up-sampling that is not folded keeps both groups."""
+    _say(f"last chunk of one group: {ci} channels, {k} x {k}, {mode}")
+    h, w = 26, 35
+    b = wl._NetBuilder("tail", ci, h, w, ci, bf16=mode == "bf16", bias=True)
+    c = b.conv(-1, 40, k, 1, act=wl.ACT_RELU)
+    u = b.simple(wl.OP_UPSAMPLE2X, -1)
+    d = b.conv(u, 32, k, 1, act=wl.ACT_NONE)
+    b.simple(wl.OP_ACT, c, act=wl.ACT_NONE, out=1)
+    b.simple(wl.OP_ACT, d, act=wl.ACT_RELU, out=1)
+    net = b.finish()
+    if mode == "split":
+        net = wl.with_weight_dtype(net, wl.WD_F32_SPLIT)
+    rng = np.random.default_rng(ci)
+    x0 = rng.standard_normal((ci, h, w)).astype(np.float32)
+    dx = [(rng.standard_normal(x0.shape) * (rng.random((1, h, w)) < q)).astype(np.float32) for q in (0.02, 1.0)]
+    for flags in (0, ev.FLAG_NO_FUSION):
+        gpu, ora = ev.EvConvNet(net, flags=flags), Oracle(net)
+        gpu.reset(_dev(x0))
+        ora.reset(x0)
+        for inc in dx:
+            gpu.step(_dev(inc))
+            ora.step_increment(inc)
+            for i in (c, d):
+                z, zr = gpu.state(i, ev.STATE_Z).astype(np.float64), ora.z(i)
+                lim = {"f32": 2e-6, "split": 1e-4, "bf16": 2e-2}[mode]
+                assert np.linalg.norm(z - zr) <= lim * np.linalg.norm(zr), (flags, i)
+        gpu.destroy()
