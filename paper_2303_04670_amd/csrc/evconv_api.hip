@@ -97,6 +97,7 @@ struct NodePlan {
   float* z2 = nullptr;
   size_t off_occ_saved = 0;  // DELAY: S_out words of the delayed node as the previous step left them
   uint64_t* occ_saved = nullptr;
+  bool integrates = false;      // output node whose kernel keeps the public tensors itself
   bool saved_in_lists = false;  // DELAY: its words are copied by the compaction kernel
   float* step = nullptr;
   float step_fixed = -1.0f; // >= 0: k supplied by the description
@@ -113,7 +114,7 @@ struct Layout {
   Geo gin;
   size_t off_x_prev = 0, off_dx = 0, off_occ_in = 0, off_idx_in = 0, off_count_in = 0, off_bitmap_in = 0;
   size_t off_occ_nodes = 0, n_occ_words = 0;  // contiguous occupancy region of all nodes
-  size_t off_sets = 0, off_rms = 0;
+  size_t off_sets = 0, off_rms = 0, off_int = 0;
   size_t off_tile_or = 0, off_tile_count = 0;  // scratch of the increment builder (wide inputs)
   size_t off_ks_part = 0, off_ks_count = 0;  // scratch of convs whose channels are split over workgroups
   size_t stride = 0;   // bytes of one stream's state (the weights live in stream 0's copy)
@@ -335,6 +336,7 @@ evconv_status make_layout(const evconv_net_desc* desc, size_t weight_bytes, bool
   L->off_ks_part = b.take(ks_floats * sizeof(float));
   L->off_ks_count = b.take(ks_counters * sizeof(unsigned));
   L->off_rms = b.take(sizeof(float) * kRmsBlocks);
+  L->off_int = b.take(sizeof(IntegrateDesc) * (size_t)desc->n_nodes);
   L->off_sets = b.take(sizeof(SetDesc) * (size_t)(desc->n_nodes + 1));
   L->stride = (b.cur + 255) / 256 * 256;  // one stream's copy of everything
   L->n_streams = desc->n_streams > 0 ? desc->n_streams : 1;
@@ -374,6 +376,8 @@ struct evconv_net {
   uint64_t *occ_in = nullptr, *bitmap_in = nullptr, *occ_nodes = nullptr;
   int32_t *idx_in = nullptr, *count_in = nullptr;
   SetDesc* sets_dev = nullptr;
+  IntegrateDesc* int_dev = nullptr;  // outputs integrated at the end of a pass
+  int n_int = 0, int_blocks = 0;
   // optional per-node timing with HIP events on the net's stream
   bool prof = false;
   std::vector<hipEvent_t> prof_ev;
@@ -441,30 +445,15 @@ evconv_status run_pass(evconv_net* net, const float* input, int builder_mode, Pa
       p.dense = dense; p.last_dense = net->last_dense; p.zero_state = net->zero_state;
       p.st = net->st;
       launch_delay(p, s);
-      if (d.is_output) {
-        IntegrateParams ip;
-        ip.delta = n.out; ip.occ = n.occ; ip.y = n.y; ip.dy = n.dy; ip.g = n.go;
-        ip.mode = int_mode;
-        ip.st = net->st;
-        launch_integrate(ip, s);
-      }
       continue;
     }
     if (n.fused_into >= 0) {  // computed by the producing conv's epilogue
       if (d.op == EVCONV_OP_SPARSIFY && reinit && n.step_fixed < 0.0f)
         // refresh: k = t_p * RMS of the layer input, which the producer has just written in full
         launch_rms_step(a, (size_t)n.ga.c * n.ga.sites(), net->sparsify_tp, net->rms_partial, n.step, net->st, s);
-      if (d.is_output) {
-        IntegrateParams ip;
-        ip.delta = n.out; ip.occ = n.occ; ip.y = n.y; ip.dy = n.dy; ip.g = n.go;
-        ip.mode = int_mode;
-        ip.st = net->st;
-        launch_integrate(ip, s);
-      }
       continue;
     }
     const bool timed = timed_begin();
-    bool integrated = false;  // an output node whose kernel keeps the public tensors itself
     switch (n.kernel) {
       case kKernConvValu:
       case kKernConvNarrow:
@@ -511,10 +500,9 @@ evconv_status run_pass(evconv_net* net, const float* input, int builder_mode, Pa
           fa.z = a_node.z; fa.out = a_node.out; fa.occ_out = a_node.occ; fa.occ_touched = a_node.touched;
           fa.act = a_node.d.act; fa.keeps_z = a_node.keeps_z; fa.structural = a_node.structural;
         }
-        if (n.kernel == kKernConvPointwise && d.is_output && conv_pointwise_integrates(p)) {
+        if (n.integrates) {
           p.y = n.y; p.dy = n.dy;
           p.int_mode = int_mode;
-          integrated = true;
         }
         if (n.kernel == kKernConvMfmaF32) launch_conv_mfma_f32(p, s);
         else if (n.kernel == kKernConvMfmaBf16) launch_conv_mfma_bf16(p, s);
@@ -572,13 +560,6 @@ evconv_status run_pass(evconv_net* net, const float* input, int builder_mode, Pa
       }
     }
     timed_end(timed, (int)i);
-    if (d.is_output && !integrated) {
-      IntegrateParams ip;
-      ip.delta = n.out; ip.occ = n.occ; ip.y = n.y; ip.dy = n.dy; ip.g = n.go;
-      ip.mode = int_mode;
-      ip.st = net->st;
-      launch_integrate(ip, s);
-    }
   }
   // recurrent state: keep the delayed nodes' active sets for the next pass (the occupancy words
   // are cleared when it starts).  The compaction of the masks does that on its way, except where
@@ -604,7 +585,12 @@ evconv_status run_pass(evconv_net* net, const float* input, int builder_mode, Pa
   }
   {
     const bool timed = timed_begin();
-    launch_build_lists(net->sets_dev, (int)net->L.nodes.size() + 1, net->L.max_ty, save_in_lists, net->st, s);
+    FinishParams fp;
+    fp.sets = net->sets_dev; fp.n_sets = (int)net->L.nodes.size() + 1; fp.max_ty = net->L.max_ty;
+    fp.save = save_in_lists;
+    fp.outputs = net->int_dev; fp.n_outputs = net->n_int; fp.int_blocks = net->int_blocks; fp.int_mode = int_mode;
+    fp.st = net->st;
+    launch_finish(fp, s);
     timed_end(timed, (int)net->L.nodes.size());
   }
   hipError_t e = hipGetLastError();
@@ -822,6 +808,7 @@ evconv_status create_impl(const evconv_net_desc* desc, const void* weights, size
       if (!force_valu && n.d.wdtype == EVCONV_F32_SPLIT && conv_mfma_split_supported(probe)) n.kernel = kKernConvMfmaSplit;
       if (!force_valu && n.kernel == kKernConvValu && conv_narrow_supported(probe)) n.kernel = kKernConvNarrow;
       if (!force_valu && conv_pointwise_supported(probe)) n.kernel = kKernConvPointwise;
+      n.integrates = n.kernel == kKernConvPointwise && n.d.is_output && conv_pointwise_integrates(probe);
       const float* src = (const float*)((const char*)weights + n.d.weight_off);
       staging.assign(((size_t)k * k * ((ci_n + 63) / 64 * 64) + 16) * cop, 0.0f);
       const int ci_p = conv_mfma_padded_cin(probe);  // matrix-core kinds: channels padded with zero rows
@@ -886,6 +873,17 @@ evconv_status create_impl(const evconv_net_desc* desc, const void* weights, size
       if (e != hipSuccess) { g_create_error = std::string("weight upload: ") + hipGetErrorString(e); delete net; return EVCONV_ERR_HIP; }
     }
   }
+  std::vector<IntegrateDesc> ints;
+  for (int i : net->outputs) {
+    const NodePlan& n = L.nodes[i];
+    if (n.integrates) continue;
+    ints.push_back(IntegrateDesc{n.out, n.occ, n.y, n.dy, n.go.h, n.go.w, n.go.c, n.go.tx, net->int_blocks});
+    net->int_blocks += integrate_blocks(n.go.c, n.go.sites());
+  }
+  net->n_int = (int)ints.size();
+  net->int_dev = (IntegrateDesc*)(ws + L.off_int);
+  if (e == hipSuccess && !ints.empty()) e = hipMemcpy(net->int_dev, ints.data(), ints.size() * sizeof(IntegrateDesc), hipMemcpyHostToDevice);
+  if (e != hipSuccess) { g_create_error = std::string("upload: ") + hipGetErrorString(e); delete net; return EVCONV_ERR_HIP; }
   for (NodePlan& n : L.nodes) {
     if (n.d.op != EVCONV_OP_DELAY || sets[n.d.in0 + 1].save) continue;
     sets[n.d.in0 + 1].save = n.occ_saved;

@@ -204,14 +204,14 @@ void launch_gap(const GapParams& p, hipStream_t s);
 
 // ---- output integration (Eq.2) -------------------------------------------------------------
 enum IntegrateMode { kIntStep = 0, kIntReset = 1, kIntRecompute = 2 };
-struct IntegrateParams {
+struct IntegrateDesc {
   const float* delta;       // H x W x C node output (increment, or value in reset/recompute)
   const uint64_t* occ;      // S_out words
   float* y; float* dy;      // C x H x W
-  Geo g; int mode;
-  Streams st;
+  int h, w, c, tx;
+  int first_block;          // of the end-of-pass kernel's integration blocks
 };
-void launch_integrate(const IntegrateParams& p, hipStream_t s);
+int integrate_blocks(int c, int sites);  // blocks that an output of this size takes
 
 // ---- recurrent state: the previous step's output of a later node -----------------------------
 struct DelayParams {
@@ -238,7 +238,14 @@ struct SetDesc {
   int h, w, tx, ty;
   uint64_t* save;  // copy of the words for the next pass (a node that a DELAY reads), or null
 };
-void launch_build_lists(const SetDesc* sets_dev, int n_sets, int max_ty, bool save, Streams st, hipStream_t s);
+// ---- end of a pass: output integrations, then the lists of all sets, in one launch ----------------
+struct FinishParams {
+  const SetDesc* sets; int n_sets, max_ty;  // DEVICE array; tile rows of the tallest set
+  int save;                                 // copy the words of sets with a SetDesc::save
+  const IntegrateDesc* outputs; int n_outputs, int_blocks, int_mode;  // DEVICE array, ascending first_block
+  Streams st;
+};
+void launch_finish(const FinishParams& p, hipStream_t s);
 
 void launch_fill_u64(uint64_t* p, size_t n, uint64_t v, Streams st, hipStream_t s);
 

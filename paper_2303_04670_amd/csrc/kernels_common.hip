@@ -5,6 +5,8 @@
 // bit (y%8)*8 + x%8 set for an active site; tiles are row-major.  Nothing here uses
 // floating-point atomics: every accumulated element has exactly one writer, so results are
 // run-to-run bit-reproducible.
+#include <algorithm>
+
 #include "evconv_kernels.h"
 
 namespace evk {
@@ -578,78 +580,6 @@ void launch_gap(const GapParams& p, hipStream_t s) {
   hipLaunchKernelGGL(gap_kernel, dim3((p.ga.c + 63) / 64, 1, p.st.n), dim3(256), 0, s, p);
 }
 
-// =============================================================================== Eq.2
-// One element of the public tensors; on: the site is in the active set.
-__device__ __forceinline__ void integrate_element(const IntegrateParams& p, int e, float v, bool on) {
-  if (p.mode == kIntStep) {
-    if (on) p.y[e] += v;
-    p.dy[e] = v;
-  } else if (p.mode == kIntReset) {
-    p.y[e] = v;
-    p.dy[e] = 0.0f;
-  } else {
-    p.dy[e] = v - p.y[e];
-    p.y[e] = v;
-  }
-}
-
-// Few channels: one thread per site.
-__global__ __launch_bounds__(256) void integrate_kernel(IntegrateParams p) {
-  {
-    const size_t so = (size_t)blockIdx.z * p.st.stride;
-    p.delta = at_stream(p.delta, so); p.occ = at_stream(p.occ, so);
-    p.y = at_stream(p.y, so); p.dy = at_stream(p.dy, so);
-  }
-  const int site = blockIdx.x * 256 + threadIdx.x;
-  const int hw = p.g.h * p.g.w;
-  if (site >= hw) return;
-  const int y = site / p.g.w, x = site - y * p.g.w;
-  const bool on = p.mode != kIntStep || occ_bit(p.occ, p.g.tx, y, x);
-  for (int c = 0; c < p.g.c; ++c) {
-    const float v = on ? p.delta[(size_t)site * p.g.c + c] : 0.0f;
-    integrate_element(p, c * hw + site, v, on);
-  }
-}
-
-// More channels: a workgroup takes 64 sites x 16 channels, read in runs of a site's channels and
-// turned through LDS to be written in runs of sites.  (One thread per site walked the channels one
-// round trip after the other: 101 channels on one site 35 us, now 4.)
-constexpr int kIntChannels = 16;
-__global__ __launch_bounds__(256) void integrate_wide_kernel(IntegrateParams p) {
-  {
-    const size_t so = (size_t)blockIdx.z * p.st.stride;
-    p.delta = at_stream(p.delta, so); p.occ = at_stream(p.occ, so);
-    p.y = at_stream(p.y, so); p.dy = at_stream(p.dy, so);
-  }
-  __shared__ float s_v[64][kIntChannels + 1];
-  const int hw = p.g.h * p.g.w, C = p.g.c;
-  const int s0 = blockIdx.x * 64, c0 = blockIdx.y * kIntChannels;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int c = threadIdx.x & (kIntChannels - 1), q = (threadIdx.x >> 4) + 16 * i;
-    s_v[q][c] = (s0 + q < hw && c0 + c < C) ? p.delta[(size_t)(s0 + q) * C + c0 + c] : 0.0f;
-  }
-  __syncthreads();
-  const int q = threadIdx.x & 63, site = s0 + q;
-  if (site >= hw) return;
-  const int y = site / p.g.w, x = site - y * p.g.w;
-  const bool on = p.mode != kIntStep || occ_bit(p.occ, p.g.tx, y, x);
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int c = (threadIdx.x >> 6) + 4 * i;
-    if (c0 + c < C) integrate_element(p, (c0 + c) * hw + site, on ? s_v[q][c] : 0.0f, on);
-  }
-}
-
-void launch_integrate(const IntegrateParams& p, hipStream_t s) {
-  if (p.g.c > 4) {
-    const dim3 grid((p.g.sites() + 63) / 64, (p.g.c + kIntChannels - 1) / kIntChannels, p.st.n);
-    hipLaunchKernelGGL(integrate_wide_kernel, grid, dim3(256), 0, s, p);
-    return;
-  }
-  hipLaunchKernelGGL(integrate_kernel, dim3((p.g.sites() + 255) / 256, 1, p.st.n), dim3(256), 0, s, p);
-}
-
 // =============================================================================== recurrent state
 // Workgroup = one 8 x 8 tile; thread = (site, channel vector) pairs strided over the tile's active
 // sites.  Bound by HBM (reads the delayed increment and the state, writes both).
@@ -728,23 +658,82 @@ void launch_copy_u64(uint64_t* dst, const uint64_t* src, size_t n, Streams st, h
   hipLaunchKernelGGL(copy_u64_kernel, dim3((unsigned)((n + 255) / 256), st.n), dim3(256), 0, s, dst, src, n, st.stride);
 }
 
-// =============================================================================== ordered lists
+// =============================================================================== end of a pass
+// One launch at the end of a pass: the output integrations (Eq.2) and the ordered lists of all
+// sets.  They depend on the nodes' results only, not on each other, and as launches of their own
+// they were 4 us each with about 2 us between them.
+
+// One element of the public tensors; on: the site is in the active set.
+__device__ __forceinline__ void integrate_element(const IntegrateDesc& p, int mode, int e, float v, bool on) {
+  if (mode == kIntStep) {
+    if (on) p.y[e] += v;
+    p.dy[e] = v;
+  } else if (mode == kIntReset) {
+    p.y[e] = v;
+    p.dy[e] = 0.0f;
+  } else {
+    p.dy[e] = v - p.y[e];
+    p.y[e] = v;
+  }
+}
+
+// Block `b` of an output's integration.  Up to 4 channels: 512 sites, a thread each; more: 64 sites x
+// 32 channels, read in runs of a site's channels and turned through LDS to be written in runs of
+// sites.  (One thread per site walked the channels one round trip after the other: 101 channels
+// on one site 35 us.)
+constexpr int kIntFew = 4, kIntChannels = 32;
+__device__ __forceinline__ void integrate_block(const IntegrateDesc& p, int mode, int b) {
+  __shared__ float s_v[64][kIntChannels + 1];
+  const int hw = p.h * p.w, C = p.c, tid = threadIdx.x;
+  if (C <= kIntFew) {
+    const int site = b * 512 + tid;
+    if (site >= hw) return;
+    const int y = site / p.w, x = site - y * p.w;
+    const bool on = mode != kIntStep || occ_bit(p.occ, p.tx, y, x);
+    float v[kIntFew];
+#pragma unroll
+    for (int c = 0; c < kIntFew; ++c) v[c] = on && c < C ? p.delta[(size_t)site * C + c] : 0.0f;
+#pragma unroll
+    for (int c = 0; c < kIntFew; ++c)
+      if (c < C) integrate_element(p, mode, c * hw + site, v[c], on);
+    return;
+  }
+  const int cb = (C + kIntChannels - 1) / kIntChannels;
+  const int s0 = b / cb * 64, c0 = b % cb * kIntChannels;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int c = tid & (kIntChannels - 1), q = (tid >> 5) + 16 * i;
+    s_v[q][c] = (s0 + q < hw && c0 + c < C) ? p.delta[(size_t)(s0 + q) * C + c0 + c] : 0.0f;
+  }
+  __syncthreads();
+  const int q = tid & 63, site = s0 + q;
+  if (site >= hw) return;
+  const int y = site / p.w, x = site - y * p.w;
+  const bool on = mode != kIntStep || occ_bit(p.occ, p.tx, y, x);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int c = (tid >> 6) + 8 * i;
+    if (c0 + c < C) integrate_element(p, mode, (c0 + c) * hw + site, on ? s_v[q][c] : 0.0f, on);
+  }
+}
+
+int integrate_blocks(int c, int sites) {
+  return c <= kIntFew ? (sites + 511) / 512 : (sites + 63) / 64 * ((c + kIntChannels - 1) / kIntChannels);
+}
+
 // Workgroup (strip, set): strip = one row of tiles = 8 image rows.  Its first list position is
 // the number of active sites in all earlier strips (a reduction over their occupancy words);
 // inside the strip wave r owns image row r and scans the per-tile byte popcounts with a
 // wave-wide prefix sum, so indices come out strictly ascending in y*W + x.
 // A recurrent net's delayed nodes have their words copied to SetDesc::save on the way.
-__global__ __launch_bounds__(512) void build_lists_kernel(const SetDesc* sets, size_t stream_stride, int save) {
+__device__ __forceinline__ void lists_block(SetDesc d, int strip, size_t so, int save) {
   __shared__ int s_part[8];
   __shared__ int s_rowcnt[8];
-  SetDesc d = sets[blockIdx.y];  // the descriptors hold stream 0's pointers
   {
-    const size_t so = (size_t)blockIdx.z * stream_stride;
     d.occ = at_stream(d.occ, so); d.idx = at_stream(d.idx, so);
     d.count = at_stream(d.count, so); d.bitmap = at_stream(d.bitmap, so);
     d.save = at_stream(d.save, so);
   }
-  const int strip = blockIdx.x;
   if (strip >= d.ty) return;
   const int tid = threadIdx.x, lane = tid & 63, r = tid >> 6;
   if (save && d.save)
@@ -809,8 +798,29 @@ __global__ __launch_bounds__(512) void build_lists_kernel(const SetDesc* sets, s
   }
 }
 
-void launch_build_lists(const SetDesc* sets_dev, int n_sets, int max_ty, bool save, Streams st, hipStream_t s) {
-  hipLaunchKernelGGL(build_lists_kernel, dim3(max_ty, n_sets, st.n), dim3(512), 0, s, sets_dev, st.stride, save ? 1 : 0);
+__global__ __launch_bounds__(512) void finish_kernel(FinishParams p) {
+  const size_t so = (size_t)blockIdx.y * p.st.stride;  // the descriptors hold stream 0's pointers
+  const int total = p.int_blocks + p.n_sets * p.max_ty;
+  for (int blk = blockIdx.x; blk < total; blk += gridDim.x) {
+    if (blk < p.int_blocks) {
+      int i = 0;
+      while (i + 1 < p.n_outputs && blk >= p.outputs[i + 1].first_block) ++i;
+      IntegrateDesc d = p.outputs[i];
+      d.delta = at_stream(d.delta, so); d.occ = at_stream(d.occ, so);
+      d.y = at_stream(d.y, so); d.dy = at_stream(d.dy, so);
+      integrate_block(d, p.int_mode, blk - d.first_block);
+    } else {
+      const int b = blk - p.int_blocks, set = b / p.max_ty;
+      lists_block(p.sets[set], b - set * p.max_ty, so, p.save);
+    }
+    __syncthreads();  // (the next block reuses the shared memory)
+  }
+}
+
+void launch_finish(const FinishParams& p, hipStream_t s) {
+  // (a launch holds less than 2^32 threads; the loop takes what is left of a very tall input)
+  const int blocks = std::min(p.int_blocks + p.n_sets * p.max_ty, 1 << 22);
+  hipLaunchKernelGGL(finish_kernel, dim3(blocks, p.st.n), dim3(512), 0, s, p);
 }
 
 // =============================================================================== rounding step
