@@ -184,6 +184,7 @@ struct EwParams {
   uint64_t* occ_out; uint64_t* occ_touched;
   int k, stride, pad;       // pooling window
   const float* step;        // sparsification layer: device scalar, the rounding step k
+  int vec_per_block;        // channel vectors per workgroup, set by the launcher
   Streams st;
 };
 void launch_elementwise(const EwParams& p, hipStream_t s);

@@ -43,6 +43,10 @@ __device__ __forceinline__ float finish_element(const ConvParams& p, float* z, f
   return o;
 }
 
+// NOUT: output channels rounded up to 1, 2, 4 or 8 (rows beyond c_out repeat the last one and are not
+// used), so that the loads of several channel pieces are in flight together: with a loop over c_out
+// inside, a site's channels were a chain of round trips (256 channels on 32 x 32: 11.6 us, now 7.4).
+template <int NOUT>
 __global__ __launch_bounds__(256) void conv_pointwise_few_kernel(ConvParams p) {
   __shared__ unsigned s_nz[2];
   const size_t so = (size_t)blockIdx.z * p.st.stride;  // this workgroup's stream
@@ -79,19 +83,19 @@ __global__ __launch_bounds__(256) void conv_pointwise_few_kernel(ConvParams p) {
   }
   __syncthreads();
 
-  float acc[kMaxFew];
+  float acc[NOUT];
 #pragma unroll
-  for (int j = 0; j < kMaxFew; ++j) acc[j] = 0.0f;
+  for (int j = 0; j < NOUT; ++j) acc[j] = 0.0f;
   if (on) {
     const float* __restrict__ x = at_stream(p.in, so) + ((size_t)oy * p.gi.w + ox) * Cin;
     const float* __restrict__ w = (const float*)p.w;  // [c_out][c_in]
     if ((Cin & 3) == 0) {
+#pragma unroll 4
       for (int c = q4 * 4; c < Cin; c += 16) {
         const float4 xv = *(const float4*)&x[c];
 #pragma unroll
-        for (int j = 0; j < kMaxFew; ++j) {
-          if (j >= Cout) break;
-          const float4 wv = *(const float4*)&w[(size_t)j * Cin + c];
+        for (int j = 0; j < NOUT; ++j) {
+          const float4 wv = *(const float4*)&w[(size_t)min(j, Cout - 1) * Cin + c];
           acc[j] = fmaf(xv.x, wv.x, acc[j]);
           acc[j] = fmaf(xv.y, wv.y, acc[j]);
           acc[j] = fmaf(xv.z, wv.z, acc[j]);
@@ -102,16 +106,15 @@ __global__ __launch_bounds__(256) void conv_pointwise_few_kernel(ConvParams p) {
       for (int c = q4; c < Cin; c += 4) {
         const float xv = x[c];
 #pragma unroll
-        for (int j = 0; j < kMaxFew; ++j) {
-          if (j >= Cout) break;
-          acc[j] = fmaf(xv, w[(size_t)j * Cin + c], acc[j]);
+        for (int j = 0; j < NOUT; ++j) {
+          acc[j] = fmaf(xv, w[(size_t)min(j, Cout - 1) * Cin + c], acc[j]);
         }
       }
     }
   }
   // add the four lanes of a site: (0 + 1) + (2 + 3), every lane ends with the full sum
 #pragma unroll
-  for (int j = 0; j < kMaxFew; ++j) {
+  for (int j = 0; j < NOUT; ++j) {
     acc[j] += __shfl_xor(acc[j], 1);
     acc[j] += __shfl_xor(acc[j], 2);
   }
@@ -121,7 +124,7 @@ __global__ __launch_bounds__(256) void conv_pointwise_few_kernel(ConvParams p) {
     float* out = at_stream(p.out, so);
     const size_t q0 = ((size_t)oy * p.go.w + ox) * Cout;
 #pragma unroll
-    for (int j = 0; j < kMaxFew; ++j) {
+    for (int j = 0; j < NOUT; ++j) {
       if (j >= Cout) break;
       float o = 0.0f;
       if (on) {
@@ -188,8 +191,13 @@ bool conv_pointwise_supported(const ConvParams& p) {
 void launch_conv_pointwise(const ConvParams& p, hipStream_t s) {
   if (p.go.h == 1 && p.go.w == 1 && p.go.c > kMaxFew)
     hipLaunchKernelGGL(linear_site_kernel, dim3((p.go.c + 3) / 4, 1, p.st.n), dim3(256), 0, s, p);
-  else
-    hipLaunchKernelGGL(conv_pointwise_few_kernel, dim3(p.go.tiles(), 1, p.st.n), dim3(256), 0, s, p);
+  else {
+    const dim3 grid(p.go.tiles(), 1, p.st.n);
+    if (p.go.c == 1) hipLaunchKernelGGL(conv_pointwise_few_kernel<1>, grid, dim3(256), 0, s, p);
+    else if (p.go.c == 2) hipLaunchKernelGGL(conv_pointwise_few_kernel<2>, grid, dim3(256), 0, s, p);
+    else if (p.go.c <= 4) hipLaunchKernelGGL(conv_pointwise_few_kernel<4>, grid, dim3(256), 0, s, p);
+    else hipLaunchKernelGGL(conv_pointwise_few_kernel<8>, grid, dim3(256), 0, s, p);
+  }
 }
 
 }  // namespace evk

@@ -1595,3 +1595,17 @@ def test_last_channel_chunk_of_one_group(mode, ci, k):
                 lim = {"f32": 2e-6, "split": 1e-4, "bf16": 2e-2}[mode]
                 assert np.linalg.norm(z - zr) <= lim * np.linalg.norm(zr), (flags, i)
         gpu.destroy()
+
+
+@pytest.mark.parametrize("ci,co", [(256, 1), (20, 2), (19, 3), (64, 4), (48, 5), (33, 7), (16, 8)])
+def test_pointwise_heads_of_one_to_eight_channels(ci, co):
+    """Prediction heads: output channels rounded up to 1, 2, 4 or 8 inside the kernel, input channels
+    that do and do not fill the unrolled pieces."""
+    _say(f"pointwise head: {ci} -> {co}")
+    b = wl._NetBuilder("head", ci, 11, 18, ci + co, bias=True)
+    b.conv(-1, co, 1, 1, 0, act=wl.ACT_SIGMOID if co % 2 else wl.ACT_NONE, out=1)
+    net = b.finish()
+    rng = np.random.default_rng(ci)
+    x0 = rng.standard_normal((ci, 11, 18)).astype(np.float32)
+    incs = [(rng.standard_normal(x0.shape) * (rng.random((1, 11, 18)) < q)).astype(np.float32) for q in (0.05, 1.0, 0.1)]
+    run_stream(net, x0, incs, "increment", label=f"head {ci} -> {co}", max_flips=6, tol=1e-5)
