@@ -55,7 +55,6 @@
 // mode instantiates it, so that the three modes compile in parallel.)
 #pragma once
 #include <algorithm>
-#include <cstdlib>
 #include <type_traits>
 
 #include "evconv_kernels.h"
@@ -343,8 +342,7 @@ void conv_mfma_kernel(ConvParams p) {
   // clamped to the image), so the four reads and the two horizontal sums per stored row are
   // shared; a site without an active source comes out as zero because inactive sources are
   // stored as zeros.  The items of a thread are the same for every chunk: offsets and masks are
-  // worked out once (this arithmetic would otherwise take vector-ALU time from the fp32 matrix
-  // instructions, which run on the same pipeline).
+  // worked out once.
   constexpr int MAXB = UPS ? (8 * (MB == 2 ? 8 : 6) * NV + NT - 1) / NT : 1;  // <= 8 x 8 blocks (K <= 7)
   // per item two packed words: ib_src = source offset (12 bits) | row step (10) | column step (6);
   // ib_dst = patch offset + 4096 (16 bits) | write mask (4) | inside-the-image mask (4)
