@@ -630,6 +630,12 @@ void conv_mfma_kernel(ConvParams p) {
   // p.tail_units in a last chunk that c_in does not fill, as many as hold channels; unit
   // u_j = wave + j * NW is this wave's j-th.
   constexpr bool TAIL = !UPS && !KSP && S2K == 0 && CHUNK == 32;  // the other variants' chunks are full or one group
+  // bf16 and split modes, stride 2: the order of the sums is that of chunks of 16 channels (the taps
+  // dealt to the waves, one group of 16 channels after the other), whichever chunk the launcher
+  // takes.  The rounding of the next layer's operands turns a last-bit difference of an fp32 sum
+  // into one of 16 (8) bits, so a launch shape that reordered them would show: the depth net in bf16
+  // by 3.5e-3.
+  constexpr bool GROUPS_IN_ORDER = S2K != 0 && !KSP && PARTS != 3;
   int n_mine = 0;
   // Both fragment addresses are a per-lane constant plus a per-unit part that is the same in all
   // lanes.  Lane j of a table register holds unit j's part (beyond the last unit: the last one's, so
@@ -650,11 +656,19 @@ void conv_mfma_kernel(ConvParams p) {
     const int n_units = K * K * kgn;
     const int u = min(wave + lane * NW, n_units - 1);
     static_assert(!TAIL || KG == 2, "one or two groups per chunk");
-    const int tap = kgn == KG ? u / KG : u, kg = kgn == KG ? u % KG : 0;
+    int tap = kgn == KG ? u / KG : u, kg = kgn == KG ? u % KG : 0;
+    n_mine = max(0, (n_units - wave + NW - 1) / NW);
+    if (GROUPS_IN_ORDER) {
+      const int n_taps = max(0, (K * K - wave + NW - 1) / NW);
+      kg = 0;
+#pragma unroll
+      for (int g = 1; g < KG; ++g) kg += lane >= g * n_taps ? 1 : 0;
+      tap = min(wave + (lane - kg * n_taps) * NW, K * K - 1);
+      n_mine = n_taps * KG;
+    }
     const int ky = __umul24(tap, p.k_magic[fold ? 1 : 0]) >> 16, kx = tap - __umul24(ky, K);  // tap < 49
     a_table = __umul24(ky, RP) + kx * CS + kg * 8;  // a unit's 16 bf16 are 8 words
     w_table = (__umul24(tap, cin_rows) + kg * (UCH / 8)) * (unsigned)(cop * 16);  // 16-byte rows of 8 bf16
-    n_mine = max(0, (n_units - wave + NW - 1) / NW);
   };
   set_units(c_lo);
   // fragments of unit j of the chunk starting at channel c0

@@ -1609,3 +1609,34 @@ def test_pointwise_heads_of_one_to_eight_channels(ci, co):
     x0 = rng.standard_normal((ci, 11, 18)).astype(np.float32)
     incs = [(rng.standard_normal(x0.shape) * (rng.random((1, 11, 18)) < q)).astype(np.float32) for q in (0.05, 1.0, 0.1)]
     run_stream(net, x0, incs, "increment", label=f"head {ci} -> {co}", max_flips=6, tol=1e-5)
+
+
+@pytest.mark.parametrize("mode", ["split", "bf16"])
+@pytest.mark.parametrize("ci,co,k,hw", [(32, 32, 5, (256, 250)), (64, 40, 3, (190, 185)), (96, 32, 1, (250, 256))])
+def test_stride2_sums_do_not_depend_on_the_channel_chunk(mode, ci, co, k, hw):
+    """bf16 and split modes: a stride-2 layer of 512 to 1024 half-tile workgroups takes chunks of 32
+    channels, with more streams (more workgroups) chunks of 16; the sums come out bit for bit the
+    same, sparse and dense."""
+    import torch
+    h, w = hw
+    _say(f"stride-2 chunks: {ci} -> {co}, {k} x {k}, {mode}")
+    b = wl._NetBuilder("s2order", ci, h, w, ci + k, bf16=mode == "bf16")
+    b.conv(-1, co, k, 2, act=wl.ACT_NONE, out=1)
+    net = wl.with_weight_dtype(b.finish(), wl.WD_F32_SPLIT if mode == "split" else wl.WD_BF16)
+    c, oh, ow = ev.EvConvNet(net).shape(0)
+    per_stream = -(-oh // 8) * -(-ow // 8) * -(-co // 32) * 2
+    streams = 1024 // per_stream + 1
+    assert 512 <= per_stream <= 1024
+    rng = np.random.default_rng(ci)
+    x0 = rng.standard_normal((ci, h, w)).astype(np.float32)
+    d = (rng.standard_normal(x0.shape) * (rng.random((1, h, w)) < 0.05)).astype(np.float32)
+    one, many = ev.EvConvNet(net), ev.EvConvNet(net, n_streams=streams)
+    one.reset(_dev(x0))
+    many.reset(_dev(np.stack([x0] * streams)))
+    np.testing.assert_array_equal(one.state(0, ev.STATE_Z), many.state(0, ev.STATE_Z, streams - 1))
+    one.step(_dev(d))
+    many.step(_dev(np.stack([d] * streams)))
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(one.state(0, ev.STATE_Z), many.state(0, ev.STATE_Z, streams - 1))
+    one.destroy()
+    many.destroy()
