@@ -110,9 +110,15 @@ typedef enum {
 
 /* dtype of the weights and of the increments inside the channel contraction; accumulation and
  * every cached tensor are always fp32.
- *   EVCONV_F32        fp32 operands, all 24 bits: on the matrix cores as three bf16 parts that add up
- *                     to the value exactly, six partial products of a product (the rest is below
- *                     half the rounding step of an fp32 product), or on the vector path.
+ *   EVCONV_F32        fp32 operands: on the matrix cores as three bf16 parts, six partial products of
+ *                     a product, or on the vector path.  The parts add up to the value exactly, all
+ *                     24 bits, for every finite weight and for increments of 2^-110 (7.7e-34) and more;
+ *                     a bf16 has no bits below 2^-133, so smaller increments are rounded to multiples
+ *                     of that.  The three partial products left out add up to less than 2^-24 of the
+ *                     product, the largest rounding error of one fp32 product.  A conv that has
+ *                     weights with bits below 2^-133 works on weights and sums times 2^16: its sums
+ *                     overflow from 2^112 (5.2e33) on.  A conv with an infinite or NaN weight, or with such
+ *                     weights beside some of 2^112 and more, takes the vector path.
  *   EVCONV_BF16       weights rounded to bf16 at create, increments rounded to bf16 inside the
  *                     contraction: relative error of a product about 2^-8.
  *   EVCONV_F32_SPLIT  fp32 weights and increments, each written as bf16 high part + bf16 low part

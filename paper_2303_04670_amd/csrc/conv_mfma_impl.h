@@ -149,8 +149,8 @@ constexpr int patch_site_words(int chunk, int opm) { return chunk / 2 * op_parts
 // The three parts of a value beyond the bf16 rounding range, into bits [shift, shift + 16) of h, m,
 // l.  A finite one: the high part is cut off instead of rounded up to infinity.  An infinity goes
 // into the low part alone: the low part is multiplied with the weight's high part only, which is
-// zero for zero weights only, so the product is the IEEE one (inf * 0 of a weight's zero low
-// parts would be NaN).
+// zero for zero weights only (weights too small for a bf16 are stored times a power of two), so the
+// product is the IEEE one (inf * 0 of a weight's zero low parts would be NaN).
 constexpr float kBf16Overflow = 3.3961775e38f;  // 0x7f7f8000: the smallest value that rounds to an infinite bf16
 __device__ __forceinline__ void split3_large(float x, int shift, unsigned& h, unsigned& m, unsigned& l) {
   if (!(fabsf(x) >= kBf16Overflow)) return;
@@ -838,12 +838,14 @@ void conv_mfma_kernel(ConvParams p) {
   if (!KSP) request_fused();
   EVK_PHASE(kPhFusedRequested);
   // ---- reduce the NW partial sums through LDS: slots [4][block*16 + reg][lane]
-  // (fp32 mode: the weights of the odd waves' units are stored negated, see conv_mfma_negated)
-  auto spill = [&](float* part, bool negate) {
+  // (fp32 mode: the weights are stored times a power of two, those of the odd waves' units negated;
+  // see conv_mfma_negated and ConvParams::w_unscale)
+  const float unscale = (wave & 1) ? -(fold ? p.w_fold_unscale : p.w_unscale) : (fold ? p.w_fold_unscale : p.w_unscale);
+  auto spill = [&](float* part, bool last) {
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
-      part[i * 64 + lane] = negate ? -acc0[i] : acc0[i];
-      if (MB == 2) part[(16 + i) * 64 + lane] = negate ? -acc1[i] : acc1[i];
+      part[i * 64 + lane] = last ? acc0[i] * unscale : acc0[i];
+      if (MB == 2) part[(16 + i) * 64 + lane] = last ? acc1[i] * unscale : acc1[i];
     }
   };
   __syncthreads();
@@ -859,7 +861,7 @@ void conv_mfma_kernel(ConvParams p) {
       }
     }
   }
-  if (wave < 4) spill(s_mem + wave * SLOT, PARTS == 3 && (wave & 1));
+  if (wave < 4) spill(s_mem + wave * SLOT, PARTS == 3);
   __syncthreads();
   EVK_PHASE(kPhReduced);
 #ifdef EVCONV_PHASE_STAMPS

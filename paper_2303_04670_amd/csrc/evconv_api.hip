@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -68,6 +69,34 @@ void weight_parts8(const float* v, int parts, uint16_t* at, size_t plane) {
     memcpy(at + q * plane, h, sizeof h);
   }
 }
+// Power of two that a conv's fp32 weights are multiplied with so that three bf16 parts hold them: a bf16
+// has no bits below 2^-133, and weights of less than about 2^-110 have bits there (those below 2^-134
+// would even become zero, and an infinite increment times them NaN).  With 2^16 every one of them
+// is exact; the sums are then finite up to 2^112 instead of 2^128, so weights that do not need it are
+// taken as they are.  `fits` becomes false for weights that are not finite or lie too far apart:
+// those go to the vector kernel.
+constexpr int kTinyWeightExponent = 16;
+float weight_scale(const float* w, size_t n, bool* fits) {
+  uint32_t special = 0, small = 0, largest = 0;
+  for (size_t i = 0; i < n; ++i) {
+    uint32_t u;
+    memcpy(&u, &w[i], 4);
+    u &= 0x7fffffffu;
+    special |= u >= 0x7f800000u ? 1u : 0u;
+    small |= u - 1u < (17u << 23) - 1u ? 1u : 0u;  // nonzero, below 2^-110
+    largest = std::max(largest, u);
+  }
+  *fits = !special;
+  if (special || !small) return 1.0f;
+  bool exact = true;
+  for (size_t i = 0; i < n && exact; ++i) {
+    const float up = ldexpf(w[i], 133);  // its integer part is what a bf16 can hold (0 < |w| < 2^-110: no overflow)
+    if (fabsf(w[i]) < 0x1p-110f) exact = up == truncf(up);
+  }
+  if (exact) return 1.0f;
+  *fits = largest < (uint32_t)(127 + 112) << 23;
+  return ldexpf(1.0f, kTinyWeightExponent);
+}
 int weight_part_count(int wdtype) { return wdtype == EVCONV_F32 ? 3 : wdtype == EVCONV_F32_SPLIT ? 2 : 1; }
 
 struct NodePlan {
@@ -77,6 +106,7 @@ struct NodePlan {
   int kernel = 0;
   int c_out_pad = 0;
   int tail_units = 0;       // ConvParams::tail_units
+  float w_scale = 1.0f, w_fold_scale = 1.0f;  // fp32 matrix-core weights (and folded ones) are stored times these
   int fused_into = -1;      // ADD or SPARSIFY node executed in the epilogue of that conv node
   int fused_sp = -1;        // conv node: the SPARSIFY node it executes behind its last epilogue stage
   int n_fused = 0;          // conv node: ADD nodes it executes, in order
@@ -469,6 +499,7 @@ evconv_status run_pass(evconv_net* net, const float* input, int builder_mode, Pa
         p.st = net->st;
         p.upsample = 0; p.lo_h = 0; p.lo_w = 0;
         p.tail_units = n.tail_units;
+        p.w_unscale = 1.0f / n.w_scale; p.w_fold_unscale = 1.0f / n.w_fold_scale;
         p.ks = 0; p.ks_chunks = 0;
         p.ks_part = (float*)(net->ws + net->L.off_ks_part);
         p.ks_count = (unsigned*)(net->ws + net->L.off_ks_count);
@@ -669,21 +700,26 @@ hipError_t prepare_fold(evconv_net* net, NodePlan& n, const void* weights, const
                 for (int ci = 0; ci < ci_n; ++ci)
                   dst[(size_t)ci * co_n + co] += coef * (double)src[((size_t)co * ci_n + ci) * k * k + ky * k + kx];
             }
+  const std::vector<float> values(folded.begin(), folded.end());
+  const int parts = weight_part_count(n.d.wdtype);
+  if (parts == 3) {
+    bool fits = true;
+    n.w_fold_scale = weight_scale(values.data(), values.size(), &fits);
+  }
   const int ci_p = (ci_n + 31) / 32 * 32;
   ConvParams probe;
   probe.gi = n.ga; probe.go = n.go; probe.k = k; probe.stride = n.d.stride; probe.c_out_pad = cop; probe.n_fused = 0;
   probe.pad = pad; probe.st = Streams{net->L.stride, net->L.n_streams}; probe.tail_units = n.tail_units;
-  const int parts = weight_part_count(n.d.wdtype);
   const size_t plane = (size_t)taps * ci_p * cop;  // values per part and phase; a phase's planes follow each other
   std::vector<uint16_t> staging(4 * parts * plane, 0);
   for (int ph = 0; ph < 4; ++ph)
     for (int t = 0; t < taps; ++t)
       for (int c8 = 0; c8 < ci_n; c8 += 8) {
-        const float sign = parts == 3 && conv_mfma_negated(probe, t, c8) ? -1.0f : 1.0f;
+        const float factor = parts == 3 && conv_mfma_negated(probe, t, c8) ? -n.w_fold_scale : n.w_fold_scale;
         for (int co = 0; co < co_n; ++co) {
           float v[8];
           for (int e = 0; e < 8; ++e)
-            v[e] = c8 + e < ci_n ? sign * (float)folded[(((size_t)ph * taps + t) * ci_n + c8 + e) * co_n + co] : 0.0f;
+            v[e] = c8 + e < ci_n ? factor * values[(((size_t)ph * taps + t) * ci_n + c8 + e) * co_n + co] : 0.0f;
           weight_parts8(v, parts, staging.data() + ph * parts * plane + (((size_t)t * (ci_p / 8) + c8 / 8) * cop + co) * 8, plane);
         }
       }
@@ -796,14 +832,11 @@ evconv_status create_impl(const evconv_net_desc* desc, const void* weights, size
       probe.tail_units = n.tail_units;
       const bool force_valu = (net->flags & EVCONV_FLAG_FORCE_VALU) != 0;
       // (a weight that is infinite or NaN: the vector kernel, which multiplies it as it is)
-      bool finite = true;
-      if (n.d.wdtype == EVCONV_F32) {
-        const uint32_t* wv = (const uint32_t*)((const char*)weights + n.d.weight_off);
-        uint32_t special = 0;
-        for (size_t q = 0, nw = (size_t)k * k * ci_n * co_n; q < nw; ++q) special |= (wv[q] & 0x7f800000u) == 0x7f800000u ? 1u : 0u;
-        finite = special == 0;
+      if (!force_valu && n.d.wdtype == EVCONV_F32 && conv_mfma_f32_supported(probe)) {
+        bool fits = true;
+        n.w_scale = weight_scale((const float*)((const char*)weights + n.d.weight_off), (size_t)k * k * ci_n * co_n, &fits);
+        if (fits) n.kernel = kKernConvMfmaF32;
       }
-      if (!force_valu && n.d.wdtype == EVCONV_F32 && finite && conv_mfma_f32_supported(probe)) n.kernel = kKernConvMfmaF32;
       if (!force_valu && n.d.wdtype == EVCONV_BF16 && conv_mfma_bf16_supported(probe)) n.kernel = kKernConvMfmaBf16;
       if (!force_valu && n.d.wdtype == EVCONV_F32_SPLIT && conv_mfma_split_supported(probe)) n.kernel = kKernConvMfmaSplit;
       if (!force_valu && n.kernel == kKernConvValu && conv_narrow_supported(probe)) n.kernel = kKernConvNarrow;
@@ -852,7 +885,7 @@ evconv_status create_impl(const evconv_net_desc* desc, const void* weights, size
           for (int c8 = 0; c8 < ci_n; c8 += 8)
             for (int t = 0; t < k * k; ++t) {
               float v[8];
-              const float sg = sign[(size_t)t * groups + c8 / 16];
+              const float sg = sign[(size_t)t * groups + c8 / 16] * (parts == 3 ? n.w_scale : 1.0f);
               for (int e = 0; e < 8; ++e) v[e] = c8 + e < ci_n ? sg * src[((size_t)co * ci_n + c8 + e) * k * k + t] : 0.0f;
               weight_parts8(v, parts, h16 + (((size_t)t * (ci_p / 8) + c8 / 8) * cop + co) * 8, plane);
             }

@@ -86,6 +86,7 @@ struct ConvParams {
   const float* in;          // H x W x C increment of the input node (full values if dense)
   const uint64_t* occ_in;   // its occupancy words
   const void* w;            // re-laid weights (layout: the kernel's own header)
+  float w_unscale, w_fold_unscale;  // fp32 matrix-core mode: sums over w (w_fold) are multiplied by these powers of two
   const float* bias;        // fp32 [c_out] or null; used by the dense pass only
   float* z;                 // H x W x C accumulated pre-activation
   float* out;               // H x W x C output increment (value in dense mode)

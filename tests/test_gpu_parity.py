@@ -1640,3 +1640,90 @@ def test_stride2_sums_do_not_depend_on_the_channel_chunk(mode, ci, co, k, hw):
     np.testing.assert_array_equal(one.state(0, ev.STATE_Z), many.state(0, ev.STATE_Z, streams - 1))
     one.destroy()
     many.destroy()
+
+
+def _conv64(net, x, co, ci, k, s):
+    import torch
+    w = torch.from_numpy(net.weights[:co * ci * k * k].reshape(co, ci, k, k)).double()
+    run = lambda a, b: torch.nn.functional.conv2d(torch.from_numpy(a).double()[None], b, None, s, k // 2)[0].numpy()
+    return run(x, w), run(np.abs(x), w.abs())
+
+
+@pytest.mark.parametrize("k,s,ci,co", [(3, 1, 64, 32), (5, 2, 32, 48), (1, 1, 40, 32)])
+@pytest.mark.parametrize("exp", [-100, -112, -120, -133, -141])
+def test_fp32_contraction_of_tiny_weights(k, s, ci, co, exp):
+    """fp32 matrix-core conv, weights around 2^exp, where a bf16 (no bits below 2^-133) runs out of
+    them: in every channel, and in one channel beside ordinary weights.  Sums within 2^-21 of the sum
+    of the absolute products as for other weights (and two steps of the subnormal range for results
+    in it); an infinite increment times a nonzero weight is infinite."""
+    _say(f"tiny weights: {k} x {k} stride {s}, {ci} -> {co}, 2^{exp}")
+    h, w = 18, 21
+    b = wl._NetBuilder("tinyw", ci, h, w, 5 + k)
+    b.conv(-1, co, k, s, act=wl.ACT_NONE, out=1)
+    net = b.finish()
+    base = net.weights.copy().reshape(co, ci, k, k)
+    rng = np.random.default_rng(3)
+    x = (rng.standard_normal((ci, h, w)) * 2.0 ** 12).astype(np.float32)
+    mixed = base.copy()
+    mixed[:, 2] = (base[:, 2].astype(np.float64) * 2.0 ** exp).astype(np.float32)
+    mixed[:, 2] = np.where(mixed[:, 2] == 0, np.float32(1.4e-45), mixed[:, 2])
+    only2 = np.zeros_like(x)
+    only2[2] = x[2]
+    for wt, xx in (((base.astype(np.float64) * 2.0 ** exp).astype(np.float32), x), (mixed, only2), (mixed, x)):
+        net.weights[:] = wt.ravel()
+        ref, absolute = _conv64(net, xx, co, ci, k, s)
+        gpu = ev.EvConvNet(net)
+        assert gpu.kernel_name(0) == "conv_mfma_f32"
+        gpu.reset(_dev(xx))
+        z = gpu.state(0, ev.STATE_Z).astype(np.float64).transpose(2, 0, 1)
+        assert (np.abs(z - ref) <= 2.0 ** -21 * absolute + 2.0 ** -148).all(), float(np.abs(z - ref).max())
+        gpu.destroy()
+    gpu = ev.EvConvNet(net)
+    x0 = np.zeros_like(x)
+    d = x0.copy()
+    d[2, 8, 8] = np.inf
+    gpu.reset(_dev(x0))
+    gpu.step(_dev(d))
+    z = gpu.state(0, ev.STATE_Z)[8 // s, 8 // s]
+    np.testing.assert_array_equal(z, np.copysign(np.inf, mixed[:, 2, k // 2, k // 2]))
+    gpu.destroy()
+
+
+@pytest.mark.parametrize("exp", [-60, -109, -118, -127, -140])
+def test_fp32_contraction_of_tiny_increments(exp):
+    """Increments around 2^exp: exact down to 2^-110, below it each is rounded to a multiple of 2^-133
+    (an error of at most 2^-134 times the weight), the bound that the header states."""
+    _say(f"tiny increments: 2^{exp}")
+    ci, co, k, h, w = 48, 32, 3, 18, 21
+    b = wl._NetBuilder("tinyx", ci, h, w, 8)
+    b.conv(-1, co, k, 1, act=wl.ACT_NONE, out=1)
+    net = b.finish()
+    net.weights[:] *= np.float32(4096)
+    x = (np.random.default_rng(4).standard_normal((ci, h, w)) * 2.0 ** exp).astype(np.float32)
+    ref, absolute = _conv64(net, x, co, ci, k, 1)
+    step = _conv64(net, (x != 0).astype(np.float32), co, ci, k, 1)[1] * 2.0 ** -134
+    gpu = ev.EvConvNet(net)
+    gpu.reset(_dev(x))
+    err = np.abs(gpu.state(0, ev.STATE_Z).astype(np.float64).transpose(2, 0, 1) - ref)
+    assert (err <= 2.0 ** -21 * absolute + (step if exp < -104 else 0.0)).all(), float((err / absolute).max())
+    gpu.destroy()
+
+
+def test_fp32_weights_too_far_apart_take_the_vector_path():
+    """Weights with bits below 2^-133 beside weights of 2^112: no power of two holds both in three bf16
+    parts; the conv runs on the vector kernel, as with an infinite weight."""
+    ci, co, h, w = 32, 32, 9, 11
+    b = wl._NetBuilder("apart", ci, h, w, 8)
+    b.conv(-1, co, 3, 1, act=wl.ACT_NONE, out=1)
+    net = b.finish()
+    wt = net.weights.reshape(co, ci, 3, 3)
+    wt[:, 0], wt[:, 1] = 1e-41, 2.0 ** 113
+    x = np.zeros((ci, h, w), np.float32)
+    x[0, 4, 4], x[1, 2, 8] = 2.0 ** 120, 2.0 ** -100
+    ref, absolute = _conv64(net, x, co, ci, 3, 1)
+    gpu = ev.EvConvNet(net)
+    assert gpu.kernel_name(0) == "conv_valu_f32"
+    gpu.reset(_dev(x))
+    err = np.abs(gpu.state(0, ev.STATE_Z).astype(np.float64).transpose(2, 0, 1) - ref)
+    assert (err <= 2.0 ** -21 * absolute + 2.0 ** -148).all()
+    gpu.destroy()
