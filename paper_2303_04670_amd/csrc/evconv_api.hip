@@ -73,9 +73,13 @@ void weight_parts8(const float* v, int parts, uint16_t* at, size_t plane) {
 // has no bits below 2^-133, and weights of less than about 2^-110 have bits there (those below 2^-134
 // would even become zero, and an infinite increment times them NaN).  With 2^16 every one of them
 // is exact; the sums are then finite up to 2^112 instead of 2^128, so weights that do not need it are
-// taken as they are.  `fits` becomes false for weights that are not finite or lie too far apart:
-// those go to the vector kernel.
+// taken as they are, with one exception: the high parts of two operands may be up to 2^-8 larger
+// than the operands, so a product just below the largest fp32 value would overflow on its way.  It
+// needs a weight of nearly 1 or more; such weights are halved (exactly, if no weight has a bit at
+// 2^-133).  `fits` becomes false for weights that are not finite or lie too far apart: those go to
+// the vector kernel.
 constexpr int kTinyWeightExponent = 16;
+constexpr uint32_t kHalvedFrom = 0x3f7d70a4u;  // 0.99: below it a weight's high part is 0.9922 at most, an increment's 3.39e38: 3.37e38
 float weight_scale(const float* w, size_t n, bool* fits) {
   uint32_t special = 0, small = 0, largest = 0;
   for (size_t i = 0; i < n; ++i) {
@@ -83,17 +87,19 @@ float weight_scale(const float* w, size_t n, bool* fits) {
     memcpy(&u, &w[i], 4);
     u &= 0x7fffffffu;
     special |= u >= 0x7f800000u ? 1u : 0u;
-    small |= u - 1u < (17u << 23) - 1u ? 1u : 0u;  // nonzero, below 2^-110
+    small |= u - 1u < (18u << 23) - 1u ? 1u : 0u;  // nonzero, below 2^-109
     largest = std::max(largest, u);
   }
   *fits = !special;
-  if (special || !small) return 1.0f;
+  const float scale = largest >= kHalvedFrom ? 0.5f : 1.0f;
+  if (special || !small) return scale;
   bool exact = true;
-  for (size_t i = 0; i < n && exact; ++i) {
-    const float up = ldexpf(w[i], 133);  // its integer part is what a bf16 can hold (0 < |w| < 2^-110: no overflow)
-    if (fabsf(w[i]) < 0x1p-110f) exact = up == truncf(up);
-  }
-  if (exact) return 1.0f;
+  for (size_t i = 0; i < n && exact; ++i)
+    if (fabsf(w[i]) < 0x1p-109f) {
+      const float up = ldexpf(w[i], 133) * scale;  // its integer part is what a bf16 can hold
+      exact = up == truncf(up);
+    }
+  if (exact) return scale;
   *fits = largest < (uint32_t)(127 + 112) << 23;
   return ldexpf(1.0f, kTinyWeightExponent);
 }

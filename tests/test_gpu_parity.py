@@ -1727,3 +1727,26 @@ def test_fp32_weights_too_far_apart_take_the_vector_path():
     err = np.abs(gpu.state(0, ev.STATE_Z).astype(np.float64).transpose(2, 0, 1) - ref)
     assert (err <= 2.0 ** -21 * absolute + 2.0 ** -148).all()
     gpu.destroy()
+
+
+def test_fp32_products_just_below_the_largest_value():
+    """A product whose operands' high parts multiply to more than the largest fp32 value while the
+    product itself does not: finite, and within 2^-21 of the exact one."""
+    rng = np.random.default_rng(6)
+    top = float(np.finfo(np.float32).max)
+    for t in range(40):
+        b = wl._NetBuilder("top", 16, 4, 4, t)
+        b.conv(-1, 32, 1, 1, 0, act=wl.ACT_NONE, out=1)
+        net = b.finish()
+        a = np.float32(min(2.0 ** rng.uniform(-0.01, 127.9), top))
+        net.weights[:] = 0
+        wt = np.float32((0.99, 0.996, 0.998, 0.9999)[t % 4] * top / float(a))
+        net.weights.reshape(32, 16)[:, 3] = wt
+        x = np.zeros((16, 4, 4), np.float32)
+        x[3, 1, 2] = -a
+        gpu = ev.EvConvNet(net)
+        gpu.reset(_dev(x))
+        z = gpu.state(0, ev.STATE_Z)[1, 2].astype(np.float64)
+        want = -float(a) * float(wt)
+        assert (np.abs(z - want) <= 2.0 ** -21 * abs(want)).all(), (t, float(a), float(wt), z[0])
+        gpu.destroy()
