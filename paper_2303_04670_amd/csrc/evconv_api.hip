@@ -708,10 +708,10 @@ hipError_t prepare_fold(evconv_net* net, NodePlan& n, const void* weights, const
             }
   const std::vector<float> values(folded.begin(), folded.end());
   const int parts = weight_part_count(n.d.wdtype);
-  if (parts == 3) {
-    bool fits = true;
-    n.w_fold_scale = weight_scale(values.data(), values.size(), &fits);
-  }
+  bool fits = true;
+  const float scale = weight_scale(values.data(), values.size(), &fits);
+  if (!fits) return hipSuccess;  // (a sum of finite weights can overflow: not folded then)
+  if (parts == 3) n.w_fold_scale = scale;
   const int ci_p = (ci_n + 31) / 32 * 32;
   ConvParams probe;
   probe.gi = n.ga; probe.go = n.go; probe.k = k; probe.stride = n.d.stride; probe.c_out_pad = cop; probe.n_fused = 0;

@@ -1750,3 +1750,28 @@ def test_fp32_products_just_below_the_largest_value():
         want = -float(a) * float(wt)
         assert (np.abs(z - want) <= 2.0 ** -21 * abs(want)).all(), (t, float(a), float(wt), z[0])
         gpu.destroy()
+
+
+@pytest.mark.parametrize("mode", ["f32", "split"])
+def test_folded_weights_that_would_overflow_are_not_folded(mode):
+    """A 5x5 conv behind an up-sampling whose finite weights add up to more than the largest fp32 value
+    when the up-sampling is folded into them: the results are those of the unfolded form, finite."""
+    _say(f"fold overflow, {mode}")
+    b = wl._NetBuilder("foldmax", 32, 40, 35, 3)
+    u = b.simple(wl.OP_UPSAMPLE2X, -1)
+    c = b.conv(u, 32, 5, 1, act=wl.ACT_NONE, out=1)
+    net = b.finish()
+    if mode == "split":
+        net = wl.with_weight_dtype(net, wl.WD_F32_SPLIT)
+    net.weights.reshape(32, 32, 5, 5)[:, 7] = 3e38
+    rng = np.random.default_rng(1)
+    x0 = np.zeros((32, 40, 35), np.float32)
+    d = (rng.standard_normal(x0.shape) * 1e-3).astype(np.float32)
+    gpu, ora = ev.EvConvNet(net), Oracle(net)
+    gpu.reset(_dev(x0))
+    ora.reset(x0)
+    gpu.step(_dev(d))
+    ora.step_increment(d)
+    z, zr = gpu.state(c, ev.STATE_Z).astype(np.float64), ora.z(c)
+    assert np.abs(z - zr).max() <= (3e-6 if mode == "f32" else 1e-4) * np.abs(zr).max()
+    gpu.destroy()
