@@ -636,6 +636,9 @@ void conv_mfma_kernel(ConvParams p) {
   // into one of 16 (8) bits, so a launch shape that reordered them would show: the depth net in bf16
   // by 3.5e-3.
   constexpr bool GROUPS_IN_ORDER = S2K != 0 && !KSP && PARTS != 3;
+  // fp32 mode, chunks of one unit (1 x 1 taps, 16 channels): waves 0 and 1 contract all of them, wave 1
+  // with the weights negated in registers, and half of their difference is the sum (conv_mfma_negated)
+  const bool pair = PARTS == 3 && CHUNK == 16 && K == 1;
   int n_mine = 0;
   // Both fragment addresses are a per-lane constant plus a per-unit part that is the same in all
   // lanes.  Lane j of a table register holds unit j's part (beyond the last unit: the last one's, so
@@ -666,6 +669,7 @@ void conv_mfma_kernel(ConvParams p) {
       tap = min(wave + (lane - kg * n_taps) * NW, K * K - 1);
       n_mine = n_taps * KG;
     }
+    if (pair) n_mine = wave < 2 ? 1 : 0;
     const int ky = __umul24(tap, p.k_magic[fold ? 1 : 0]) >> 16, kx = tap - __umul24(ky, K);  // tap < 49
     a_table = __umul24(ky, RP) + kx * CS + kg * 8;  // a unit's 16 bf16 are 8 words
     w_table = (__umul24(tap, cin_rows) + kg * (UCH / 8)) * (unsigned)(cop * 16);  // 16-byte rows of 8 bf16
@@ -784,6 +788,14 @@ void conv_mfma_kernel(ConvParams p) {
       bq1 = b_load(c0, j + 4);
       step(aq2, aq0, j + 2, bq2);
     }
+    if (pair && wave == 1) {  // (uniform; its only unit)
+      auto flip = [](float4& v) {  // the signs of eight bf16
+        uint4 u = __builtin_bit_cast(uint4, v);
+        u.x ^= 0x80008000u; u.y ^= 0x80008000u; u.z ^= 0x80008000u; u.w ^= 0x80008000u;
+        v = __builtin_bit_cast(float4, u);
+      };
+      flip(bq0.h); flip(bq0.m); flip(bq0.l);
+    }
     if (j < n_mine) step(aq0, aq1, j, bq0);
     if (j + 1 < n_mine) step(aq1, aq2, j + 1, bq1);
     if (more) {
@@ -840,7 +852,7 @@ void conv_mfma_kernel(ConvParams p) {
   // ---- reduce the NW partial sums through LDS: slots [4][block*16 + reg][lane]
   // (fp32 mode: the weights are stored times a power of two, those of the odd waves' units negated;
   // see conv_mfma_negated and ConvParams::w_unscale)
-  const float unscale = (wave & 1) ? -(fold ? p.w_fold_unscale : p.w_unscale) : (fold ? p.w_fold_unscale : p.w_unscale);
+  const float unscale = (fold ? p.w_fold_unscale : p.w_unscale) * (wave & 1 ? -1.0f : 1.0f) * (pair ? 0.5f : 1.0f);
   auto spill = [&](float* part, bool last) {
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
