@@ -1276,18 +1276,27 @@ void launch_shape(const ConvParams& p, hipStream_t s) {
 // (measured, us per layer in fp32 mode, not split / 512 / 768 workgroups: 512 channels on 7 x 7
 // 22.2 / 14.4 / 14.3; 512 on 16 x 16 23.9 / 18.7 / 18.5; 256 on 14 x 14 15.2 / 13.0 / 13.2; 768 -> 256 on 32 x
 // 32 33.2 / 31.4 / 38.8; 256 on 32 x 44 20.4 / not split / 27.3; four waves per workgroup are slower
-// on all of them).  Chunks of 64 channels (5 x 5 at stride 2: 32).
+// on all of them).  Chunks of 64 channels (5 x 5 at stride 2 and, in fp32 mode, larger kernels at
+// stride 1: 32; fp32, not split / split: 288 -> 96, 5 x 5 on 20 x 20 31.9 / 16.3, 512 -> 256 on 28 x 28 56 / 45).
+// What a workgroup saves, channels times taps, has to be worth the exchange: 512 in fp32 mode (256 in
+// launches of up to 16 workgroups), 1024 (640 up to 64) in the modes whose contraction is shorter.
+// Measured, not split / split: 1 x 1 in fp32 mode, 128 -> 128 on 14 x 14 8.9 / 10.3, 512 -> 128 on 14 x 14 11.7 /
+// 12.5 and on 7 x 7 11.9 / 11.1, 768 -> 128 on 7 x 7 14.1 / 11.8; bf16, 128 -> 128, 3 x 3 on 20 x 20 10.0 / 10.4, 64 -> 64, 5 x
+// 5 at stride 2 on 112 x 112 11.3 / 12.4, 128 -> 256 on 48 x 48 14.9 / 13.8.
 struct KSplit { int chunk = 0, chunks_each = 0, ks = 0; };  // ks == 0: not split
 inline KSplit ksplit_for(const ConvParams& p) {
   KSplit r;
   const long long n = 2ll * p.go.tiles() * (p.c_out_pad / 32) * p.st.n;  // half-tile workgroups
   if (p.k <= 3 && p.gi.c % 64 == 0) r.chunk = 64;
   else if (p.stride == 2 && p.k <= 5 && p.gi.c % 32 == 0) r.chunk = 32;
+  else if (p.fp32 && p.stride == 1 && p.k > 3 && p.gi.c % 32 == 0) r.chunk = 32;
   else return r;
   const int chunks = p.gi.c / r.chunk;
   const int want = (int)std::min<long long>(chunks, 512 / n);
   if (want < 2) return r;
   r.chunks_each = (chunks + want - 1) / want;
+  const int saved = (chunks - r.chunks_each) * r.chunk * p.k * p.k;
+  if (saved < (p.fp32 ? (n <= 16 ? 256 : 512) : (n <= 64 ? 640 : 1024))) return r;
   r.ks = (chunks + r.chunks_each - 1) / r.chunks_each;
   return r;
 }
@@ -1300,6 +1309,7 @@ void launch_any(const ConvParams& p, hipStream_t s) {
     q.ks = r.ks; q.ks_chunks = r.chunks_each;
     if (r.chunk == 64 && p.stride == 1) launch_variant<64, 8, OPM, 1, true, 0>(q, s);
     else if (r.chunk == 64) launch_variant<64, 8, OPM, 1, true, 3>(q, s);
+    else if (p.stride == 1) launch_variant<32, 8, OPM, 1, true, OPM == kOpF32 ? 0 : 5>(q, s);  // (fp32 mode only)
     else launch_variant<32, 8, OPM, 1, true, 5>(q, s);
     return;
   }

@@ -362,6 +362,7 @@ evconv_status make_layout(const evconv_net_desc* desc, size_t weight_bytes, bool
     ConvParams probe;
     probe.gi = n.ga; probe.go = n.go; probe.k = n.d.kh; probe.stride = n.d.stride; probe.c_out_pad = n.c_out_pad;
     probe.n_fused = 0; probe.pad = n.d.pad; probe.st = Streams{0, desc->n_streams > 0 ? desc->n_streams : 1};
+    probe.fp32 = n.d.wdtype == EVCONV_F32;
     size_t f = 0, c = 0;
     if (conv_mfma_f32_supported(probe)) conv_mfma_split_scratch(probe, &f, &c);
     ks_floats = std::max(ks_floats, f);
@@ -504,7 +505,7 @@ evconv_status run_pass(evconv_net* net, const float* input, int builder_mode, Pa
         p.n_fused = n.n_fused;
         p.st = net->st;
         p.upsample = 0; p.lo_h = 0; p.lo_w = 0;
-        p.tail_units = n.tail_units;
+        p.tail_units = n.tail_units; p.fp32 = d.wdtype == EVCONV_F32;
         p.w_unscale = 1.0f / n.w_scale; p.w_fold_unscale = 1.0f / n.w_fold_scale;
         p.ks = 0; p.ks_chunks = 0;
         p.ks_part = (float*)(net->ws + net->L.off_ks_part);
@@ -716,6 +717,7 @@ hipError_t prepare_fold(evconv_net* net, NodePlan& n, const void* weights, const
   ConvParams probe;
   probe.gi = n.ga; probe.go = n.go; probe.k = k; probe.stride = n.d.stride; probe.c_out_pad = cop; probe.n_fused = 0;
   probe.pad = pad; probe.st = Streams{net->L.stride, net->L.n_streams}; probe.tail_units = n.tail_units;
+  probe.fp32 = n.d.wdtype == EVCONV_F32;
   const size_t plane = (size_t)taps * ci_p * cop;  // values per part and phase; a phase's planes follow each other
   std::vector<uint16_t> staging(4 * parts * plane, 0);
   for (int ph = 0; ph < 4; ++ph)
@@ -834,6 +836,7 @@ evconv_status create_impl(const evconv_net_desc* desc, const void* weights, size
       ConvParams probe;
       probe.gi = n.ga; probe.go = n.go; probe.k = k; probe.stride = n.d.stride; probe.c_out_pad = cop;
       probe.n_fused = 0; probe.pad = n.d.pad; probe.st = Streams{L.stride, L.n_streams};
+      probe.fp32 = n.d.wdtype == EVCONV_F32;
       n.tail_units = n.d.in0 < 0 || L.nodes[n.d.in0].d.op != EVCONV_OP_UPSAMPLE_BILINEAR2X;
       probe.tail_units = n.tail_units;
       const bool force_valu = (net->flags & EVCONV_FLAG_FORCE_VALU) != 0;
@@ -1007,6 +1010,7 @@ evconv_status create_impl(const evconv_net_desc* desc, const void* weights, size
       probe.gi = c_node.ga; probe.go = c_node.go; probe.k = c_node.d.kh; probe.stride = c_node.d.stride;
       probe.c_out_pad = c_node.c_out_pad; probe.n_fused = 0; probe.pad = c_node.d.pad;
       probe.st = Streams{L.stride, L.n_streams};
+      probe.fp32 = c_node.d.wdtype == EVCONV_F32;
       if (!conv_mfma_upsample_supported(probe)) continue;
       u_node.gather_fused_into = (int)i;
       c_node.upsampled_from = u_node.d.in0;

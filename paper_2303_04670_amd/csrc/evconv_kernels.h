@@ -115,6 +115,7 @@ struct ConvParams {
   // matrix-core kernel only, set by its launcher: the grid's x dimension runs over the blocks of
   // 32 output channels and y over the tiles, instead of the other way round
   int wg_swap;
+  int fp32;  // matrix-core kernel only: fp32 mode (part of the rule that splits the channels over workgroups)
   // matrix-core kernel only: a last channel chunk that c_in does not fill is contracted over the
   // groups of 16 channels that exist (not in convs that may read through an up-sampling: their
   // variants have no registers to spare for it); part of the weights' layout (conv_mfma_negated)

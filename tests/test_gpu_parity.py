@@ -1801,3 +1801,37 @@ def test_fp32_sums_have_no_error_of_one_sign(ci, co, k, s, hw, streams):
             mean.append((err.mean((1, 2)) / np.abs(ref).mean((1, 2))).mean())
         gpu.destroy()
     assert abs(np.mean(mean)) < 5e-9, np.mean(mean)
+
+
+@pytest.mark.parametrize("ci,co,k,hw,streams", [(64, 32, 5, (9, 7), 1), (96, 40, 5, (17, 9), 1), (288, 96, 5, (20, 20), 1),
+                                                (160, 32, 7, (8, 21), 1), (96, 32, 7, (5, 6), 3)])
+def test_channels_of_large_kernels_split_over_workgroups(ci, co, k, hw, streams):
+    """fp32 convs of 5 x 5 and more taps on few tiles split their channels in chunks of 32: against the
+    oracle through sparse and dense steps, twice in the same state (run-to-run identical)."""
+    import torch
+    h, w = hw
+    _say(f"channels of large kernels: {ci} -> {co}, {k} x {k}, {h} x {w}, {streams} streams")
+    b = wl._NetBuilder("ksplit5", ci, h, w, ci + k, bias=True)
+    b.conv(-1, co, k, 1, act=wl.ACT_RELU, out=1)
+    net = b.finish()
+    rng = np.random.default_rng(ci + k)
+    nets = [ev.EvConvNet(net, n_streams=streams) for _ in range(2)]
+    oras = [Oracle(net) for _ in range(streams)]
+    x0 = rng.standard_normal((streams, ci, h, w)).astype(np.float32)
+    for g in nets:
+        g.reset(_dev(x0 if streams > 1 else x0[0]))
+    for q, o in enumerate(oras):
+        o.reset(x0[q])
+    for t in range(4):
+        m = rng.random((streams, 1, h, w)) < (1.0 if t == 2 else 0.03)
+        d = (rng.standard_normal(x0.shape) * m).astype(np.float32)
+        for g in nets:
+            g.step(_dev(d if streams > 1 else d[0]))
+        torch.cuda.synchronize()
+        for q, o in enumerate(oras):
+            o.step_increment(d[q])
+            z, zr = nets[0].state(0, ev.STATE_Z, q).astype(np.float64), o.z(0)
+            assert np.abs(z - zr).max() <= 2e-6 * np.abs(zr).max(), f"step {t}"
+            np.testing.assert_array_equal(z, nets[1].state(0, ev.STATE_Z, q).astype(np.float64))
+    for g in nets:
+        g.destroy()
