@@ -1185,7 +1185,10 @@ inline int chunk_for(const ConvParams& p) {
   // 128 -> 256 on 32 x 44 (384 workgroups) 31.5 -> 28.3 us, 64 -> 128 on 64 x 88 (704) 23.7 -> 22.9, 32 ->
   // 64 on 128 x 176 (1408) 27.1 -> 27.7; ResNet-18's 64 -> 128 on 28 x 28 (128) 13.2 -> 11.5; with 16
   // streams (6144 to 22528) 218 -> 252, 215 -> 250 and 294 -> 325.
+  // (1 x 1: the patch is small whatever the chunk, and a chunk of 16 channels is a single unit: chunks of 32
+  // there too; 128 -> 256 on 192 x 192 35.6 -> 30.3 us, 256 -> 512 on 256 x 256 155 -> 127)
   const long long n_half = (long long)p.go.tiles() * (p.c_out_pad / 32) * p.st.n * 2;
+  if (p.stride == 2 && p.k == 1 && n_half > 1024 && p.gi.c % 32 == 0) return 32;
   if (p.stride == 2 && n_half <= 1024) {
     if (p.k <= 3 && p.gi.c % 64 == 0 && n_half < 512) return 64;
     if (p.k <= 5 && p.gi.c % 32 == 0) return 32;

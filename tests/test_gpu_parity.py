@@ -1835,3 +1835,28 @@ def test_channels_of_large_kernels_split_over_workgroups(ci, co, k, hw, streams)
             np.testing.assert_array_equal(z, nets[1].state(0, ev.STATE_Z, q).astype(np.float64))
     for g in nets:
         g.destroy()
+
+
+@pytest.mark.parametrize("mode", ["f32", "split", "bf16"])
+@pytest.mark.parametrize("ci,co,hw,streams", [(64, 128, (181, 190), 1), (96, 32, (63, 70), 21), (32, 16, (360, 355), 1)])
+def test_large_stride2_1x1_convs(mode, ci, co, hw, streams):
+    """1 x 1 convs at stride 2 of more than 1024 half-tile workgroups, one or many streams: chunks of 32
+    channels.  Against 64 bits (bf16 weights and increments: products are exact in fp32)."""
+    _say(f"large 1 x 1 stride 2: {ci} -> {co}, {hw}, {streams} streams, {mode}")
+    h, w = hw
+    b = wl._NetBuilder("k1s2", ci, h, w, ci, bf16=mode == "bf16")
+    b.conv(-1, co, 1, 2, act=wl.ACT_NONE, out=1)
+    net = b.finish()
+    if mode == "split":
+        net = wl.with_weight_dtype(net, wl.WD_F32_SPLIT)
+    x = np.random.default_rng(ci).standard_normal((streams, ci, h, w)).astype(np.float32)
+    if mode == "bf16":
+        x = wl.round_to_bf16(x)
+    gpu = ev.EvConvNet(net, n_streams=streams)
+    gpu.reset(_dev(x if streams > 1 else x[0]))
+    for q in (0, streams - 1):
+        ref, absolute = _conv64(net, x[q], co, ci, 1, 2)
+        err = np.abs(gpu.state(0, ev.STATE_Z, q).astype(np.float64).transpose(2, 0, 1) - ref)
+        # split: 2^-17 per operand and the dropped low x low product; the others: fp32 sums
+        assert (err <= (2.0 ** -15 if mode == "split" else 2.0 ** -20) * absolute).all(), float((err / absolute).max())
+    gpu.destroy()
