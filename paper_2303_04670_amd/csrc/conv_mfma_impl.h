@@ -179,8 +179,9 @@ __device__ __forceinline__ void split3_large(float x, int shift, unsigned& h, un
 // site is active where one of its four sources is.
 //
 // KSP: the channels are split over p.ks workgroups as well (chunk ranges of p.ks_chunks chunks).
-template <int CHUNK, int NW, int OPM, int MB, bool UPS, bool KSP = false, int S2K = 0>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(MB == 1 && !(UPS && NW == 4) ? 4 : 3)))
+// FIVE: registers for five waves per SIMD instead of four (see launch_shape).
+template <int CHUNK, int NW, int OPM, int MB, bool UPS, bool KSP = false, int S2K = 0, bool FIVE = false>
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(FIVE ? 5 : MB == 1 && !(UPS && NW == 4) ? 4 : 3)))
 void conv_mfma_kernel(ConvParams p) {
   // this workgroup's stream: every state pointer of p is used through at_stream(.., so); p itself
   // stays untouched so that it remains in the kernel-argument segment
@@ -1198,7 +1199,7 @@ inline int chunk_for(const ConvParams& p) {
   return 16;
 }
 
-template <int CHUNK, int NW, int OPM, int MB, bool KSP = false, int S2K = 0>
+template <int CHUNK, int NW, int OPM, int MB, bool KSP = false, int S2K = 0, bool FIVE = false>
 void launch_variant(const ConvParams& p, hipStream_t s) {
   const int PH = (4 * MB - 1) * p.stride + p.k, PW = 7 * p.stride + p.k;
   // (rows of the patch are padded to a pitch of 32 modulo 64 words: at most 64 more per row)
@@ -1236,7 +1237,7 @@ void launch_variant(const ConvParams& p, hipStream_t s) {
     return;
   }
   if (lds < part) lds = part;
-  hipLaunchKernelGGL((conv_mfma_kernel<CHUNK, NW, OPM, MB, false, KSP, S2K>), grid, dim3(NW * 64), lds, s, q);
+  hipLaunchKernelGGL((conv_mfma_kernel<CHUNK, NW, OPM, MB, false, KSP, S2K, FIVE>), grid, dim3(NW * 64), lds, s, q);
 }
 
 // share of the chip's 256 CUs kept busy when n equally long workgroups run at once
@@ -1263,8 +1264,17 @@ void launch_shape(const ConvParams& p, hipStream_t s) {
     return;
   }
   constexpr int NW4 = CHUNK == 128 ? 8 : 4, MB2 = CHUNK == 128 ? 1 : 2;
+  // Four-wave half tiles with the shorter contractions are 5 registers above what five workgroups per
+  // CU leave; held to those (2 to 4 spilled) they lose 5 to 8 %, but a launch of 1024 to 1280 workgroups is
+  // then one round on the chip instead of two, one of 2048 to 2560 two instead of three (bf16, 5 x 5:
+  // 320 -> 320 on 64 x 64, 1280 workgroups, 60.0 -> 46.1 us, 96 -> 96 on 96 x 96, 864, 17.1 -> 17.9; split, 3 x 3: 320 -> 320
+  // on 64 x 64 44.3 -> 37.7, 64 -> 64 on 96 x 96, 576, 11.7 -> 12.6).
+  constexpr bool kFive = (OPM == kOpBf16 && CHUNK == 32) || (OPM == kOpSplit && CHUNK == 64);
+  const bool five = kFive && !p.upsample && n <= 2560 && (n + 1279) / 1280 < (n + 1023) / 1024;
   if (halves) {
-    if (eight) launch_variant<CHUNK, 8, OPM, 1>(p, s); else launch_variant<CHUNK, NW4, OPM, 1>(p, s);
+    if (eight) launch_variant<CHUNK, 8, OPM, 1>(p, s);
+    else if (five) launch_variant<CHUNK, NW4, OPM, 1, false, 0, kFive>(p, s);
+    else launch_variant<CHUNK, NW4, OPM, 1>(p, s);
   } else {
     if (eight) launch_variant<CHUNK, 8, OPM, MB2>(p, s); else launch_variant<CHUNK, NW4, OPM, MB2>(p, s);
   }

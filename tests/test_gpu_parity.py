@@ -1860,3 +1860,37 @@ def test_large_stride2_1x1_convs(mode, ci, co, hw, streams):
         # split: 2^-17 per operand and the dropped low x low product; the others: fp32 sums
         assert (err <= (2.0 ** -15 if mode == "split" else 2.0 ** -20) * absolute).all(), float((err / absolute).max())
     gpu.destroy()
+
+
+@pytest.mark.parametrize("mode,ci,co,k,hw", [("bf16", 96, 96, 5, (100, 109)), ("bf16", 33, 64, 3, (136, 139)),
+                                             ("split", 64, 128, 3, (95, 90)), ("split", 128, 96, 1, (159, 160))])
+def test_launches_of_five_workgroups_per_cu(mode, ci, co, k, hw):
+    """Four-wave half tiles whose launch takes one round less with five workgroups per CU run a variant
+    held to fewer registers: bit for bit what four per CU give (more streams: another number of
+    rounds), and within rounding of 64 bits."""
+    _say(f"five workgroups per CU: {ci} -> {co}, {k} x {k}, {hw}, {mode}")
+    h, w = hw
+    n = -(-h // 8) * -(-w // 8) * -(-co // 32) * 2
+    assert 1024 < n <= 1280 or 2048 < n <= 2560
+    streams = next(q for q in range(2, 9) if not (1024 < q * n <= 1280 or 2048 < q * n <= 2560))
+    b = wl._NetBuilder("five", ci, h, w, ci, bf16=mode == "bf16")
+    b.conv(-1, co, k, 1, act=wl.ACT_RELU, out=1)
+    net = b.finish()
+    if mode == "split":
+        net = wl.with_weight_dtype(net, wl.WD_F32_SPLIT)
+    rng = np.random.default_rng(ci)
+    x = wl.round_to_bf16(rng.standard_normal((ci, h, w)).astype(np.float32))
+    d = (rng.standard_normal(x.shape) * (rng.random((1, h, w)) < 0.05)).astype(np.float32)
+    one, many = ev.EvConvNet(net), ev.EvConvNet(net, n_streams=streams)
+    one.reset(_dev(x))
+    many.reset(_dev(np.stack([x] * streams)))
+    ref, absolute = _conv64(net, x, co, ci, k, 1)
+    err = np.abs(one.state(0, ev.STATE_Z).astype(np.float64).transpose(2, 0, 1) - ref)
+    assert (err <= (2.0 ** -15 if mode == "split" else 2.0 ** -20) * absolute).all(), float((err / absolute).max())
+    for _ in range(2):
+        np.testing.assert_array_equal(one.state(0, ev.STATE_Z), many.state(0, ev.STATE_Z, streams - 1))
+        np.testing.assert_array_equal(one.state(0, ev.STATE_OCC), many.state(0, ev.STATE_OCC, streams - 1))
+        one.step(_dev(d))
+        many.step(_dev(np.stack([d] * streams)))
+    one.destroy()
+    many.destroy()
