@@ -46,7 +46,11 @@ __device__ __forceinline__ float finish_element(const ConvParams& p, float* z, f
 // NOUT: output channels rounded up to 1, 2, 4 or 8 (rows beyond c_out repeat the last one and are not
 // used), so that the loads of several channel pieces are in flight together: with a loop over c_out
 // inside, a site's channels were a chain of round trips (256 channels on 32 x 32: 11.6 us, now 7.4).
-template <int NOUT>
+// UNROLL pieces are in flight: four with eight rows take the registers of half the waves, which
+// launches that fill the chip (more than 1024 tiles) need more; those take two, and exactly c_out
+// rows (256 x 352: 16 -> 8 channels 17.9 us before, 25.2 with four pieces, 17.5 with two; 256 -> 5
+// channels 34.6, 38.9, 30.4; 64 x 88, 88 tiles: 512 -> 8 channels 53.7, 25.6, 27.5).
+template <int NOUT, int UNROLL>
 __global__ __launch_bounds__(256) void conv_pointwise_few_kernel(ConvParams p) {
   __shared__ unsigned s_nz[2];
   const size_t so = (size_t)blockIdx.z * p.st.stride;  // this workgroup's stream
@@ -90,7 +94,7 @@ __global__ __launch_bounds__(256) void conv_pointwise_few_kernel(ConvParams p) {
     const float* __restrict__ x = at_stream(p.in, so) + ((size_t)oy * p.gi.w + ox) * Cin;
     const float* __restrict__ w = (const float*)p.w;  // [c_out][c_in]
     if ((Cin & 3) == 0) {
-#pragma unroll 4
+#pragma unroll UNROLL
       for (int c = q4 * 4; c < Cin; c += 16) {
         const float4 xv = *(const float4*)&x[c];
 #pragma unroll
@@ -193,10 +197,15 @@ void launch_conv_pointwise(const ConvParams& p, hipStream_t s) {
     hipLaunchKernelGGL(linear_site_kernel, dim3((p.go.c + 3) / 4, 1, p.st.n), dim3(256), 0, s, p);
   else {
     const dim3 grid(p.go.tiles(), 1, p.st.n);
-    if (p.go.c == 1) hipLaunchKernelGGL(conv_pointwise_few_kernel<1>, grid, dim3(256), 0, s, p);
-    else if (p.go.c == 2) hipLaunchKernelGGL(conv_pointwise_few_kernel<2>, grid, dim3(256), 0, s, p);
-    else if (p.go.c <= 4) hipLaunchKernelGGL(conv_pointwise_few_kernel<4>, grid, dim3(256), 0, s, p);
-    else hipLaunchKernelGGL(conv_pointwise_few_kernel<8>, grid, dim3(256), 0, s, p);
+    const bool many = (long long)p.go.tiles() * p.st.n > 1024;
+    if (p.go.c == 1) hipLaunchKernelGGL((conv_pointwise_few_kernel<1, 4>), grid, dim3(256), 0, s, p);
+    else if (p.go.c == 2) hipLaunchKernelGGL((conv_pointwise_few_kernel<2, 4>), grid, dim3(256), 0, s, p);
+    else if (p.go.c <= 4) hipLaunchKernelGGL((conv_pointwise_few_kernel<4, 4>), grid, dim3(256), 0, s, p);
+    else if (!many) hipLaunchKernelGGL((conv_pointwise_few_kernel<8, 4>), grid, dim3(256), 0, s, p);
+    else if (p.go.c == 5) hipLaunchKernelGGL((conv_pointwise_few_kernel<5, 2>), grid, dim3(256), 0, s, p);
+    else if (p.go.c == 6) hipLaunchKernelGGL((conv_pointwise_few_kernel<6, 2>), grid, dim3(256), 0, s, p);
+    else if (p.go.c == 7) hipLaunchKernelGGL((conv_pointwise_few_kernel<7, 2>), grid, dim3(256), 0, s, p);
+    else hipLaunchKernelGGL((conv_pointwise_few_kernel<8, 2>), grid, dim3(256), 0, s, p);
   }
 }
 

@@ -1894,3 +1894,17 @@ def test_launches_of_five_workgroups_per_cu(mode, ci, co, k, hw):
         many.step(_dev(np.stack([d] * streams)))
     one.destroy()
     many.destroy()
+
+
+@pytest.mark.parametrize("ci,co", [(20, 5), (19, 6), (64, 7), (36, 8), (20, 4)])
+def test_pointwise_heads_on_many_tiles(ci, co):
+    """Prediction heads of more than 1024 tiles: the variants of exactly five to eight channels."""
+    _say(f"pointwise head on many tiles: {ci} -> {co}")
+    h, w = 257, 259
+    b = wl._NetBuilder("heads", ci, h, w, ci + co, bias=True)
+    b.conv(-1, co, 1, 1, 0, act=wl.ACT_SIGMOID if co % 2 else wl.ACT_NONE, out=1)
+    net = b.finish()
+    rng = np.random.default_rng(ci)
+    x0 = rng.standard_normal((ci, h, w)).astype(np.float32)
+    incs = [(rng.standard_normal(x0.shape) * (rng.random((1, h, w)) < q)).astype(np.float32) for q in (0.05, 1.0)]
+    run_stream(net, x0, incs, "increment", label=f"head {ci} -> {co}", max_flips=12, tol=1e-5)
