@@ -510,12 +510,16 @@ void launch_elementwise(const EwParams& p, hipStream_t s) {
   bool vec4 = (p.go.c % 4) == 0;
   if (p.op == kEwConcat || p.op == kEwConcatUp) vec4 = vec4 && (p.ga.c % 4) == 0;
   const int cv_all = p.go.c / (vec4 ? 4 : 1);
-  // Maps of few tiles are split over the channels down to one pass of the 256 threads over a full
-  // tile (4 vectors of 64 sites): ResNet-18's 56 x 56 x 64 max-pool, 49 workgroups of four passes
-  // in sequence, 11.8 -> 6.8 us.
+  // Maps of few tiles are split over the channels, down to one pass of the 256 threads over a full tile
+  // (4 vectors of 64 sites), until there are 384 workgroups: ResNet-18's 56 x 56 x 64 max-pool, 49
+  // workgroups of four passes in sequence, 11.8 -> 6.8 us.  More cost sparse steps more than they give
+  // dense ones (three nodes on 32 x 44 x 512 with 5 % of the sites active: 21.5 us in 192 workgroups, 22.8 in 384,
+  // 26.8 in 768; on 64 x 88 x 128, all sites: 37.5 in 176, 28.9 in 352, 25.8 in 704).
   EwParams q = p;
-  const long long wgs = (long long)p.go.tiles() * ((cv_all + kEwVecPerBlock - 1) / kEwVecPerBlock) * p.st.n;
-  q.vec_per_block = wgs < 256 ? kEwVecPerBlock / 4 : kEwVecPerBlock;
+  q.vec_per_block = kEwVecPerBlock;
+  while (q.vec_per_block > kEwVecPerBlock / 4 &&
+         (long long)p.go.tiles() * ((cv_all + q.vec_per_block - 1) / q.vec_per_block) * p.st.n < 384)
+    q.vec_per_block /= 2;
   dim3 grid(p.go.tiles(), (cv_all + q.vec_per_block - 1) / q.vec_per_block, p.st.n);
   if (vec4) hipLaunchKernelGGL(elementwise_kernel<4>, grid, dim3(256), 0, s, q);
   else hipLaunchKernelGGL(elementwise_kernel<1>, grid, dim3(256), 0, s, q);

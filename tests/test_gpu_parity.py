@@ -1908,3 +1908,21 @@ def test_pointwise_heads_on_many_tiles(ci, co):
     x0 = rng.standard_normal((ci, h, w)).astype(np.float32)
     incs = [(rng.standard_normal(x0.shape) * (rng.random((1, h, w)) < q)).astype(np.float32) for q in (0.05, 1.0)]
     run_stream(net, x0, incs, "increment", label=f"head {ci} -> {co}", max_flips=12, tol=1e-5)
+
+
+@pytest.mark.parametrize("c,hw", [(128, (50, 61)), (20, (9, 17)), (33, (56, 56)), (256, (64, 65))])
+def test_elementwise_maps_split_over_the_channels(c, hw):
+    """Elementwise nodes on maps of few tiles in workgroups of 16, 8 and 4 channel vectors (4-wide and
+    single channels): activations, product and max-pool against the oracle, sparse and dense."""
+    _say(f"elementwise channel split: {c} channels, {hw}")
+    h, w = hw
+    b = wl._NetBuilder("ewsplit", c, h, w, c)
+    a = b.simple(wl.OP_ACT, -1, act=wl.ACT_RELU)
+    m = b.simple(wl.OP_MUL, a, -1)
+    b.simple(wl.OP_ADD, m, a, act=wl.ACT_TANH, out=1)
+    b.simple(wl.OP_MAXPOOL, a, k=3, stride=2, pad=1, out=1)
+    net = b.finish()
+    rng = np.random.default_rng(c)
+    x0 = rng.standard_normal((c, h, w)).astype(np.float32)
+    incs = [(rng.standard_normal(x0.shape) * (rng.random((1, h, w)) < q)).astype(np.float32) for q in (0.03, 1.0, 0.02)]
+    run_stream(net, x0, incs, "increment", label=f"elementwise {c}", max_flips=6, tol=1e-5)
