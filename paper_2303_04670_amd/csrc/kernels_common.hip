@@ -41,7 +41,6 @@ __device__ __forceinline__ uint64_t inbounds_word(int h, int w, int tile_y, int 
 // N elements of a thread, element j at ok[j] ? e[j] : nowhere (d[j] = 0).  All loads are requested before
 // the first store: a store to the cached frame between two loads of it would keep them in order,
 // one round trip per channel.
-constexpr int kBuilderFewChannels = 8;
 template <int N>
 __device__ __forceinline__ void build_elements(const BuilderParams& p, const int* e, const bool* ok, float* d) {
   float in[N], prev[N];
@@ -69,9 +68,11 @@ __device__ __forceinline__ void clear_words(const BuilderParams& p) {
   for (int i = gtid; i < p.n_clear; i += nthreads) p.clear[i] = 0;
 }
 
-// Frames of few channels: one workgroup = 8 wavefronts = an 8-row x 64-column strip (8 tiles).  Wave r reads row r with
-// 256-byte coalesced loads per channel; its ballot is the 64-column activity of that row.  The
-// eight ballots are transposed through LDS into eight tile occupancy words.
+// Strips: one workgroup = 8 wavefronts = an 8-row x 64-column strip (8 tiles).  Wave r reads row r with
+// 256-byte coalesced loads per channel, N channels in flight; its ballot is the 64-column activity of
+// that row.  The eight ballots are transposed through LDS into eight tile occupancy words.
+// ALL: the input has exactly N channels.
+template <int N, bool ALL>
 __global__ __launch_bounds__(512) void builder_kernel(BuilderParams p) {
   {
     const size_t so = (size_t)blockIdx.z * p.st.stride;
@@ -89,19 +90,22 @@ __global__ __launch_bounds__(512) void builder_kernel(BuilderParams p) {
   bool any = false;
   if (inb) {
     const int site = y * p.g.w + x;
-    int e[kBuilderFewChannels];
-    bool ok[kBuilderFewChannels];
-    float d[kBuilderFewChannels];
+    const int C = ALL ? N : p.g.c;
+    for (int c0 = 0; c0 < C; c0 += N) {
+      int e[N];
+      bool ok[N];
+      float d[N];
 #pragma unroll
-    for (int c = 0; c < kBuilderFewChannels; ++c) {
-      ok[c] = c < p.g.c;
-      e[c] = c * hw + site;
-    }
-    build_elements<kBuilderFewChannels>(p, e, ok, d);
+      for (int j = 0; j < N; ++j) {
+        ok[j] = c0 + j < C;
+        e[j] = (c0 + j) * hw + site;
+      }
+      build_elements<N>(p, e, ok, d);
 #pragma unroll
-    for (int c = 0; c < kBuilderFewChannels; ++c) {
-      if (ok[c]) p.dx[(size_t)site * p.g.c + c] = d[c];
-      any |= ok[c] && d[c] != 0.0f;
+      for (int j = 0; j < N; ++j) {
+        if (ok[j]) p.dx[(size_t)site * C + c0 + j] = d[j];
+        any |= ok[j] && d[j] != 0.0f;
+      }
     }
   }
   const uint64_t row_mask = __ballot(any);
@@ -192,13 +196,33 @@ __global__ __launch_bounds__(512) void builder_wide_kernel(BuilderParams p) {
 }
 
 void launch_builder(const BuilderParams& p, hipStream_t s) {
-  if (p.g.c > kBuilderFewChannels) {
-    const dim3 grid(p.g.tiles(), (p.g.c + kWideChunk - 1) / kWideChunk, p.st.n);
-    hipLaunchKernelGGL(builder_wide_kernel, grid, dim3(512), 0, s, p);
+  dim3 grid((p.g.w + 63) / 64, (p.g.h + 7) / 8, p.st.n);
+  // Strips for up to 8 channels, and for more where there are enough of them (each is a serial chain over
+  // the channels) and the site-major increments, written 4 bytes at a time, stay in the caches until
+  // their lines are full; otherwise tiles x 64 channels.  Measured, strips / tiles, us: 9 channels on 100 x
+  // 100 (26 strips) 8.1 / 6.8 and on 260 x 346 (198) 9.7 / 14.4; 24 on 480 x 640 (600) 49 / 57; 32 there 99 / 81; 100 on
+  // 260 x 346 70 / 81; 256 there 260 / 188.
+  const long long strips = (long long)grid.x * grid.y * p.st.n;
+  const bool enough = strips >= (p.g.c <= 12 ? 64 : 128);
+  const bool cached = p.g.c <= 24 || (p.g.c <= 128 && strips <= 400);
+  if (p.g.c > 8 && !(enough && cached)) {
+    const dim3 tiles(p.g.tiles(), (p.g.c + kWideChunk - 1) / kWideChunk, p.st.n);
+    hipLaunchKernelGGL(builder_wide_kernel, tiles, dim3(512), 0, s, p);
     return;
   }
-  dim3 grid((p.g.w + 63) / 64, (p.g.h + 7) / 8, p.st.n);
-  hipLaunchKernelGGL(builder_kernel, grid, dim3(512), 0, s, p);
+  switch (p.g.c) {
+    case 1: hipLaunchKernelGGL((builder_kernel<1, true>), grid, dim3(512), 0, s, p); return;
+    case 2: hipLaunchKernelGGL((builder_kernel<2, true>), grid, dim3(512), 0, s, p); return;
+    case 3: hipLaunchKernelGGL((builder_kernel<3, true>), grid, dim3(512), 0, s, p); return;
+    case 4: hipLaunchKernelGGL((builder_kernel<4, true>), grid, dim3(512), 0, s, p); return;
+    case 5: hipLaunchKernelGGL((builder_kernel<5, true>), grid, dim3(512), 0, s, p); return;
+    case 6: hipLaunchKernelGGL((builder_kernel<6, true>), grid, dim3(512), 0, s, p); return;
+    case 7: hipLaunchKernelGGL((builder_kernel<7, true>), grid, dim3(512), 0, s, p); return;
+    case 8: hipLaunchKernelGGL((builder_kernel<8, true>), grid, dim3(512), 0, s, p); return;
+  }
+  // (the number in flight that leaves fewer loads without a channel)
+  if ((p.g.c - 1) % 8 < 4) hipLaunchKernelGGL((builder_kernel<4, false>), grid, dim3(512), 0, s, p);
+  else hipLaunchKernelGGL((builder_kernel<8, false>), grid, dim3(512), 0, s, p);
 }
 
 // =============================================================================== elementwise

@@ -1926,3 +1926,34 @@ def test_elementwise_maps_split_over_the_channels(c, hw):
     x0 = rng.standard_normal((c, h, w)).astype(np.float32)
     incs = [(rng.standard_normal(x0.shape) * (rng.random((1, h, w)) < q)).astype(np.float32) for q in (0.03, 1.0, 0.02)]
     run_stream(net, x0, incs, "increment", label=f"elementwise {c}", max_flips=6, tol=1e-5)
+
+
+@pytest.mark.parametrize("c,hw", [(9, (70, 1030)), (12, (1030, 65)), (16, (130, 513)), (33, (500, 130)), (2, (40, 70)), (4, (33, 129))])
+def test_wide_inputs_in_strips(c, hw):
+    """Inputs of more than 8 channels on maps of 128 strips and more go through the strip form of the
+    increment builder, 4 or 8 channels at a time: cached frame, increment, words and lists bit-exact
+    through frames and supplied increments, elements in single channels."""
+    h, w = hw
+    _say(f"wide inputs in strips: {c} channels, {h} x {w}")
+    b = wl._NetBuilder("strips", c, h, w, c)
+    b.conv(-1, 2, 1, 1, 0, act=wl.ACT_RELU, out=1)
+    net = b.finish()
+    rng = np.random.default_rng(c)
+    gpu, ora, rep = ev.EvConvNet(net), Oracle(net), cmp.Report()
+    x = rng.standard_normal((c, h, w)).astype(np.float32)
+    gpu.reset(_dev(x))
+    ora.reset(x)
+    for t in range(4):
+        d = np.zeros_like(x)
+        for _ in range(40):
+            d[rng.integers(c), rng.integers(h), rng.integers(w)] = rng.standard_normal()
+        x = x + d
+        if t % 2:
+            gpu.step(_dev(d))
+            ora.step_increment(d)
+        else:
+            gpu.step_frame(_dev(x))
+            ora.step_frame(x)
+        cmp.compare_input_stage(gpu, ora, rep)
+        cmp.compare_outputs(gpu, ora, rep)
+    gpu.destroy()
