@@ -1957,3 +1957,37 @@ def test_wide_inputs_in_strips(c, hw):
         cmp.compare_input_stage(gpu, ora, rep)
         cmp.compare_outputs(gpu, ora, rep)
     gpu.destroy()
+
+
+@pytest.mark.parametrize("mode", ["step", "dense"])
+def test_large_wide_outputs_read_active_sites_only(mode):
+    """An output of more than 12 Mi values (97 channels on 352 x 370, ragged in both): y and dy bit for bit
+    those of the increments and words that the conv left, through sparse steps and regular passes."""
+    import torch
+    c, h, w = 97, 352, 370
+    assert c * h * w > 12 << 20
+    b = wl._NetBuilder("largeout", 9, h, w, 3)
+    n = b.conv(-1, c, 3, 1, act=wl.ACT_RELU, out=1)
+    net = b.finish()
+    rng = np.random.default_rng(5)
+    gpu = ev.EvConvNet(net)
+    gpu.reset(_dev(rng.standard_normal((9, h, w)).astype(np.float32)))
+    if mode == "dense":
+        gpu.set_mode(ev.MODE_DENSE_RECOMPUTE)
+    for q in (0.002, 0.3):
+        d = (rng.standard_normal((9, h, w)) * (rng.random((1, h, w)) < q)).astype(np.float32)
+        before = gpu.outputs()[0]["y"].clone()
+        gpu.step(_dev(d))
+        torch.cuda.synchronize()
+        out = gpu.outputs()[0]
+        inc = np.ascontiguousarray(gpu.state(n, ev.STATE_DY).transpose(2, 0, 1))
+        if mode == "dense":
+            np.testing.assert_array_equal(out["y"].cpu().numpy(), inc)
+            np.testing.assert_array_equal(out["dy"].cpu().numpy(), inc - before.cpu().numpy())
+            continue
+        mask = cmp.words_to_mask(gpu.state(n, ev.STATE_OCC), h, w) != 0
+        want = np.where(mask, inc, np.float32(0))
+        np.testing.assert_array_equal(out["dy"].cpu().numpy(), want)
+        np.testing.assert_array_equal(out["y"].cpu().numpy(), before.cpu().numpy() + want)
+        assert 0 < mask.sum() < h * w
+    gpu.destroy()
