@@ -308,6 +308,23 @@ evconv_status make_layout(const evconv_net_desc* desc, size_t weight_bytes, bool
       return fail(err, EVCONV_ERR_SHAPE, where);
     }
   }
+  size_t ks_floats = 0, ks_counters = 0;  // (the layers run one after the other: one scratch for all)
+  for (int i = 0; i < desc->n_nodes; ++i) {
+    const NodePlan& n = L->nodes[i];
+    if (n.d.op != EVCONV_OP_CONV2D && n.d.op != EVCONV_OP_LINEAR) continue;
+    ConvParams probe;
+    probe.gi = n.ga; probe.go = n.go; probe.k = n.d.kh; probe.stride = n.d.stride; probe.c_out_pad = n.c_out_pad;
+    probe.n_fused = 0; probe.pad = n.d.pad; probe.st = Streams{0, desc->n_streams > 0 ? desc->n_streams : 1};
+    probe.fp32 = n.d.wdtype == EVCONV_F32;
+    size_t f = 0, c = 0;
+    if (conv_mfma_f32_supported(probe)) conv_mfma_split_scratch(probe, &f, &c);
+    ks_floats = std::max(ks_floats, f);
+    ks_counters = std::max(ks_counters, c);
+  }
+  // the arrival counters lie behind the occupancy words and are cleared with them at the start of a pass
+  // (every launch leaves them zero; a pass that did not run to its end need not have)
+  L->off_ks_count = L->off_occ_nodes + words * sizeof(uint64_t);
+  words += (ks_counters * sizeof(unsigned) + 7) / 8;
   L->n_occ_words = words;
   b.take(words * sizeof(uint64_t));
   for (int i = 0; i < desc->n_nodes; ++i) {
@@ -355,23 +372,9 @@ evconv_status make_layout(const evconv_net_desc* desc, size_t weight_bytes, bool
       n.off_dy = b.take(elems * 4);
     }
   }
-  size_t ks_floats = 0, ks_counters = 0;  // (the layers run one after the other: one scratch for all)
-  for (int i = 0; i < desc->n_nodes; ++i) {
-    const NodePlan& n = L->nodes[i];
-    if (n.d.op != EVCONV_OP_CONV2D && n.d.op != EVCONV_OP_LINEAR) continue;
-    ConvParams probe;
-    probe.gi = n.ga; probe.go = n.go; probe.k = n.d.kh; probe.stride = n.d.stride; probe.c_out_pad = n.c_out_pad;
-    probe.n_fused = 0; probe.pad = n.d.pad; probe.st = Streams{0, desc->n_streams > 0 ? desc->n_streams : 1};
-    probe.fp32 = n.d.wdtype == EVCONV_F32;
-    size_t f = 0, c = 0;
-    if (conv_mfma_f32_supported(probe)) conv_mfma_split_scratch(probe, &f, &c);
-    ks_floats = std::max(ks_floats, f);
-    ks_counters = std::max(ks_counters, c);
-  }
   L->off_tile_or = b.take((size_t)L->gin.tiles() * 8);
   L->off_tile_count = b.take((size_t)L->gin.tiles() * 4);
   L->off_ks_part = b.take(ks_floats * sizeof(float));
-  L->off_ks_count = b.take(ks_counters * sizeof(unsigned));
   L->off_rms = b.take(sizeof(float) * kRmsBlocks);
   L->off_int = b.take(sizeof(IntegrateDesc) * (size_t)desc->n_nodes);
   L->off_sets = b.take(sizeof(SetDesc) * (size_t)(desc->n_nodes + 1));

@@ -178,8 +178,13 @@ __global__ __launch_bounds__(512) void builder_wide_kernel(BuilderParams p) {
   if (threadIdx.x == 0) {
     uint64_t word = 0;
     for (int i = 0; i < 8; ++i) word |= s_any[i];
-    if (p.mode >= kBuildReset) word = 0;
-    if (gridDim.y == 1) {
+    if (p.mode >= kBuildReset) {  // no active set; scratch as a launch of another kind expects it
+      if (blockIdx.y == 0) {
+        p.occ[blockIdx.x] = 0;
+        p.tile_or[blockIdx.x] = 0;
+        p.tile_count[blockIdx.x] = 0;
+      }
+    } else if (gridDim.y == 1) {
       p.occ[blockIdx.x] = word;
     } else {
       // (the OR's result is waited for before the counter is touched)

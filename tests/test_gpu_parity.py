@@ -1991,3 +1991,49 @@ def test_large_wide_outputs_read_active_sites_only(mode):
         np.testing.assert_array_equal(out["y"].cpu().numpy(), before.cpu().numpy() + want)
         assert 0 < mask.sum() < h * w
     gpu.destroy()
+
+
+def test_reset_clears_arrival_counters():
+    """Counters that a pass cut short leaves behind (here: written by hand, behind the last node's
+    occupancy words and behind the last output) are cleared by a reset, those of the channel split by
+    every pass: the results are those of a fresh net."""
+    import torch
+    c, h, w = 256, 11, 20
+    b = wl._NetBuilder("counters", c, h, w, 3)
+    n = b.conv(-1, 32, 3, 1, act=wl.ACT_RELU, out=1)
+    net = b.finish()
+    rng = np.random.default_rng(5)
+    x0 = rng.standard_normal((c, h, w)).astype(np.float32)
+    incs = [(rng.standard_normal(x0.shape) * (rng.random((1, h, w)) < q)).astype(np.float32) for q in (0.2, 0.1, 0.3)]
+    tiles = -(-h // 8) * -(-w // 8)
+    gpu, clean = ev.EvConvNet(net), ev.EvConvNet(net)
+    for g in (gpu, clean):
+        g.reset(_dev(x0))
+        g.step(_dev(incs[0]))
+    torch.cuda.synchronize()
+    words = gpu.state(n, ev.STATE_OCC).tobytes() + gpu.state(n, ev.STATE_OCC_TOUCHED).tobytes()
+    counters = gpu.workspace.cpu().numpy().tobytes().index(words) + len(words)
+    align = lambda p: (p + 255) // 256 * 256
+    dy = gpu.outputs()[0]["dy"]
+    tile_or = align(dy.data_ptr() + dy.numel() * 4) - gpu.workspace.data_ptr()
+    tile_count = align(tile_or + gpu.workspace.data_ptr() + tiles * 8) - gpu.workspace.data_ptr()
+    split = gpu.workspace[counters:counters + 8 * tiles].view(torch.int32)      # one per half tile and block of 32 channels
+    builder = [gpu.workspace[tile_or:tile_or + 8 * tiles].view(torch.int32), gpu.workspace[tile_count:tile_count + 4 * tiles].view(torch.int32)]
+    assert not any(int(t.abs().sum()) for t in [split] + builder)
+    split.fill_(1)
+    for t in builder:
+        t.fill_(1)
+    for g in (gpu, clean):
+        g.reset(_dev(x0))
+    np.testing.assert_array_equal(gpu.state(n, ev.STATE_Z), clean.state(n, ev.STATE_Z))
+    for k, d in enumerate(incs):
+        split.fill_(1 + k)
+        for g in (gpu, clean):
+            g.step(_dev(d))
+        torch.cuda.synchronize()
+        for kind in (ev.STATE_Z, ev.STATE_OCC, ev.STATE_OCC_TOUCHED):
+            np.testing.assert_array_equal(gpu.state(n, kind), clean.state(n, kind))
+        np.testing.assert_array_equal(gpu.state(-1, ev.STATE_OCC), clean.state(-1, ev.STATE_OCC))
+        assert torch.equal(gpu.outputs()[0]["y"], clean.outputs()[0]["y"])
+    gpu.destroy()
+    clean.destroy()
