@@ -1,6 +1,7 @@
 """Host-side checks of the C ABI that need no GPU: the library loads, exports every symbol the
 header declares, sizes workspaces, and rejects bad descriptions before any GPU work."""
 import ctypes
+import dataclasses
 import os
 import re
 
@@ -138,3 +139,17 @@ def test_product_package_does_not_import_the_oracle():
                 src = open(os.path.join(dirpath, f)).read()
                 assert not re.search(r"^\s*(from|import)\s+oracle", src, flags=re.M), f
                 assert "libevconv_oracle" not in src, f
+
+
+def test_static_workspace_holds_what_four_bytes_per_weight_and_32_mib_held():
+    """fp32 matrix-core weights take six bytes in the workspace; the static array is large enough for every
+    description that fits 32 MiB with four (which split-mode weights take), also when it is almost
+    all weights and its convs need scratch for the channel split."""
+    conv = lambda i, co: wl.Node(wl.OP_CONV2D, wl.ACT_RELU, i - 1, -2, 512, co, 3, 1, 1, 0, -1, int(i == 3))
+    nodes = [conv(0, 512), conv(1, 512), conv(2, 512), conv(3, 256)]
+    split = [dataclasses.replace(nd, wdtype=wl.WD_F32_SPLIT) for nd in nodes]
+    net = lambda nds: wl.Net("weights", 512, 3, 3, nds, np.zeros(0, np.float32))
+    query = lambda nds: ev.evconv_query_workspace(ev.marshal_desc(net(nds))[0])
+    scratch = 32 * 8 * 32 * 32 * 4   # 32 half-tile workgroups x 8 shares of 32 x 32 sums
+    assert (31 << 20) < query(split) - scratch < (32 << 20)
+    assert query(nodes) <= ev.STATIC_WORKSPACE_BYTES

@@ -53,7 +53,7 @@ def _run_pair(net, frames, label):
 
 
 def test_static_workspace_net_equals_a_net_in_a_caller_workspace_twice_in_a_row():
-    big = wl.net_conv_stack(1002, h=180, w=240)                 # 19.6 MiB of the 32 MiB array
+    big = wl.net_conv_stack(1002, h=180, w=240)                 # 19.9 MiB of the 52 MiB array
     frames_big = list(wl.stream_voxel(1002, 180, 240, 6, 0.03))
     _run_pair(big, frames_big, "conv stack 5x180x240")
     small = wl.net_unet_depth(1003, h=40, w=56, width=8)         # every op of the UNet, a few MiB
