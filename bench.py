@@ -10,7 +10,9 @@ Prints ONE JSON line.  `value` is 1000 / the median of the per-step durations of
 each measured with HIP events on the library's stream (`step_time_ms` gives median, min, max and
 the wall-clock mean of the same K steps).  Extra keys:
   roofline            dominant kernel family (matrix-core conv): algorithmic FLOPs of its timed launches
-                      over their HIP-event durations; `traffic` is read from the committed rocprofv3
+                      over their HIP-event durations, against the peak of the instruction divided by
+                      the instruction products per conv product; `executed` counts those, over the
+                      taps that run; `traffic` is read from the committed rocprofv3
                       counter summary under profiles/
   roofline_hbm        the gather/scatter-bound kernels (increment builder, narrow first-layer conv,
                       1x1 prediction head, list compaction): algorithmic bytes over HIP-event
@@ -39,16 +41,16 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
-PEAKS = {  # MI355X published dense peaks
-    # six bf16 MFMAs per fp32 product: executed flops = 6 x algorithmic, priced against the bf16 peak
-    "conv_mfma_f32": ("mfma", 2500.0, "TFLOP/s"),
-    "conv_mfma_bf16": ("mfma", 2500.0, "TFLOP/s"),
-    # three bf16 MFMAs per fp32 product: executed flops = 3 x algorithmic, priced against the bf16 peak
-    "conv_mfma_f32_split_bf16x3": ("mfma", 2500.0, "TFLOP/s"),
+# MI355X published dense peaks of the instructions a kernel family runs, and how many of their products
+# make one product of the conv (fp32 mode: six partial products of bf16 parts, split mode: three)
+PEAKS = {
+    "conv_mfma_f32": ("mfma", 2500.0, "TFLOP/s", 6),
+    "conv_mfma_bf16": ("mfma", 2500.0, "TFLOP/s", 1),
+    "conv_mfma_f32_split_bf16x3": ("mfma", 2500.0, "TFLOP/s", 3),
     # vector ALU fp32: 256 CUs x 4 SIMDs x 16 lanes x 2 flop x 2 (packed) x 2.4 GHz
-    "conv_valu_f32": ("alu", 157.3, "TFLOP/s"),
-    "conv_narrow_mfma_f32": ("mfma", 157.3, "TFLOP/s"),
-    "conv_pointwise_f32": ("hbm", 8000.0, "GB/s"),
+    "conv_valu_f32": ("alu", 157.3, "TFLOP/s", 1),
+    "conv_narrow_mfma_f32": ("mfma", 157.3, "TFLOP/s", 1),
+    "conv_pointwise_f32": ("hbm", 8000.0, "GB/s", 1),
 }
 PROFILE_FILES = {"conv_mfma_f32": "unet_depth_f32_incremental_kernels.md",
                  "conv_mfma_f32_split_bf16x3": "unet_depth_f32_split_incremental_kernels.md",
@@ -191,11 +193,14 @@ def run_variant(args, np, torch, ev, wl, variant, dframes, with_dense, with_laye
                            active=st.n_active, touched_tiles=st.n_touched_tiles, tiles=st.n_tiles,
                            gflop_alg=flops / 1e9))
     dom = max((k for k in fam if k.startswith("conv")), key=lambda k: fam[k]["ms"])
-    bound, peak, unit = PEAKS[dom]
+    bound, peak, unit, products = PEAKS[dom]
     achieved = fam[dom]["flops"] / (fam[dom]["ms"] * 1e-3) / 1e12 if fam[dom]["ms"] > 0 else 0.0
-    executed = fam[dom]["executed"] / (fam[dom]["ms"] * 1e-3) / 1e12 if fam[dom]["ms"] > 0 else 0.0
-    roofline = dict(kernel=dom, bound=bound, achieved=achieved, peak=peak, unit=unit, frac=achieved / peak,
-                    executed=executed, executed_frac=executed / peak,
+    executed = products * fam[dom]["executed"] / (fam[dom]["ms"] * 1e-3) / 1e12 if fam[dom]["ms"] > 0 else 0.0
+    # achieved / peak: the conv's own products, against the rate at which the instruction's peak yields
+    # them; executed / executed_peak: what the matrix cores run, partial products included
+    roofline = dict(kernel=dom, bound=bound, achieved=achieved, peak=peak / products, unit=unit,
+                    frac=achieved * products / peak, products=products,
+                    executed=executed, executed_peak=peak, executed_frac=executed / peak,
                     traffic=traffic_from_profile(dom), traffic_source="profiles/" + PROFILE_FILES.get(dom, "-"),
                     avg_launch_ms=fam[dom]["ms"] / max(fam[dom]["launches"], 1),
                     launches=fam[dom]["launches"], share_of_step=fam[dom]["ms"] / (dt_prof * 1e3),
