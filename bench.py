@@ -6,7 +6,8 @@ integration and list compaction, on one frame of a synthetic event-voxel stream 
 resident in HBM.  Workload: the UNet depth network on 5x256x352 at 2 % changed pixels per step,
 fp32 weights (headline); the fp32-through-bf16-parts and bf16-weight variants are reported beside it.
 
-Prints ONE JSON line.  `value` is 1000 / the median of the per-step durations of the K timed steps,
+Prints ONE short JSON line on stdout; the full record with the keys below goes to stderr or to
+--detail FILE.  `value` is 1000 / the median of the per-step durations of the K timed steps,
 each measured with HIP events on the library's stream (`step_time_ms` gives median, min, max and
 the wall-clock mean of the same K steps).  Extra keys:
   roofline            dominant kernel family (matrix-core conv): algorithmic FLOPs of its timed launches
@@ -252,6 +253,8 @@ def main():
     ap.add_argument("--density", type=float, default=0.02, help="changed pixels per step of the synthetic event stream")
     ap.add_argument("--variant", choices=["f32", "bf16", "f32_split"], default="f32",
                     help="contraction of the headline run: fp32 (three exact bf16 parts), bf16 weights, or fp32 through bf16 high/low parts")
+    ap.add_argument("--detail", metavar="FILE", default="-",
+                    help="where the full record of all legs goes: a file, - for stderr (default), or empty for nowhere")
     ap.add_argument("--no-cpu-baseline", action="store_true", help="skip the timed CPU oracle leg")
     ap.add_argument("--cpu-steps", type=int, default=20, help="frames of the stream the CPU oracle is timed on (all cores)")
     ap.add_argument("--cpu-steps-1t", type=int, default=3, help="frames the CPU oracle is timed on with one thread")
@@ -369,7 +372,30 @@ def main():
     if not args.no_cpu_baseline:
         out["cpu_baseline"] = cpu_baseline(args, np, net, frames)
     out["layers"] = res["layers"]
-    print(json.dumps(out), flush=True)
+    if args.detail == "-":
+        print(json.dumps(out), file=sys.stderr, flush=True)
+    elif args.detail:
+        with open(args.detail, "w") as f:
+            json.dump(out, f, indent=1)
+    print(json.dumps(short_record(out)), flush=True)
+
+
+def short_record(out):
+    """The contract's keys and one number per leg, short enough for a reader that keeps the end of
+    the output only; the full record goes where --detail says."""
+    num = lambda x: float(f"{x:.5g}") if isinstance(x, float) else x
+    keep = ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step", "higher_is_better", "scaling", "vs_baseline",
+            "dtype", "data", "config")
+    rec = {k: out[k] for k in keep}
+    rec["step_time_ms"] = {k: num(v) for k, v in out["step_time_ms"].items()}
+    rec["roofline"] = {k: num(out["roofline"][k]) for k in
+                       ("kernel", "bound", "achieved", "peak", "unit", "frac", "products", "executed_frac", "share_of_step")}
+    for leg in ("dense_recompute", "auto_mode", "f32_variant", "f32_split_variant", "bf16_variant", "hip_graph_replay"):
+        if leg in out and "ms_per_step" in out[leg]:
+            rec[leg + "_ms"] = num(out[leg]["ms_per_step"])
+    if "cpu_baseline" in out:
+        rec["cpu_baseline"] = {k: num(out["cpu_baseline"][k]) for k in ("value", "unit", "cores", "kind")}
+    return rec
 
 
 def cpu_model():
