@@ -2037,3 +2037,87 @@ def test_reset_clears_arrival_counters():
         assert torch.equal(gpu.outputs()[0]["y"], clean.outputs()[0]["y"])
     gpu.destroy()
     clean.destroy()
+
+
+def test_channel_split_with_sparsification_layers_exact_arithmetic():
+    """Convs whose channels are split over workgroups, with sparsification layers and an ADD folded into
+    their epilogues: exact arithmetic (dyadic weights and inputs, k = 0.5), so the GPU equals the fp64
+    oracle on every tensor and every list."""
+    _say("channel split with folded sparsification layers, exact arithmetic")
+    b = wl._NetBuilder("sp_ks", 128, 13, 19, 5, sparsify=True, sparsify_k=0.5)
+    c1 = b.conv(-1, 128, 3)                      # 2 x 3 tiles x 4 blocks: 48 half-tile workgroups
+    c2 = b.conv(c1, 128, 5)
+    c3 = b.conv(c2, 128, 3, act=wl.ACT_NONE)
+    a = b.simple(wl.OP_ADD, c1, c3, act=wl.ACT_RELU)
+    b.conv(a, 32, 3, out=1)
+    net = b.finish()
+    rng = np.random.default_rng(8)
+    wts = net.weights.copy()
+    for nd in net.nodes:
+        if nd.op == wl.OP_CONV2D:
+            n = nd.c_out * nd.c_in * nd.k * nd.k
+            wts[nd.w_off:nd.w_off + n] = rng.integers(-1, 2, n) * (rng.random(n) < 0.03) / 8.0
+    net.weights = wts
+    x0 = (rng.integers(-8, 9, (128, 13, 19)) / 4.0).astype(np.float32)
+    incs = [((rng.integers(-4, 5, x0.shape) / 4.0) * (rng.random((1, 13, 19)) < q)).astype(np.float32) for q in (0.05, 0.05, 1.0, 0.1)]
+    gpu, ora, rep = ev.EvConvNet(net), Oracle(net), cmp.Report()
+    names = [gpu.kernel_name(i) for i in range(len(net.nodes))]
+    assert [names[i] for i, nd in enumerate(net.nodes) if nd.op == wl.OP_SPARSIFY] == ["fused_into_conv_epilogue"] * 3, names
+    gpu.reset(_dev(x0))
+    ora.reset(x0)
+    for d in incs:
+        gpu.step(_dev(d))
+        ora.step_increment(d)
+        cmp.compare_outputs(gpu, ora, rep, 1e-7)
+        for i in range(len(net.nodes)):
+            cmp.compare_node(gpu, ora, i, rep, tol=1e-7, exact_sets=True)
+    assert rep.flips == 0
+    gpu.destroy()
+
+
+@pytest.mark.parametrize("act", [wl.ACT_SIGMOID, wl.ACT_TANH, wl.ACT_ONE_MINUS])
+def test_channel_split_with_other_activations(act):
+    """The general epilogue (activations other than ReLU) behind a channel split, with a folded ADD."""
+    b = wl._NetBuilder("ks_act", 192, 9, 20, 5, bias=True)
+    a = b.conv(-1, 40, 1, act=wl.ACT_NONE)
+    c = b.conv(-1, 40, 3, act=act)
+    b.simple(wl.OP_ADD, c, a, act=wl.ACT_TANH, out=1)
+    net = b.finish()
+    rng = np.random.default_rng(act)
+    x0 = (rng.standard_normal((192, 9, 20)) * 0.5).astype(np.float32)
+    incs = [(rng.standard_normal(x0.shape) * 0.3 * (rng.random((1, 9, 20)) < q)).astype(np.float32) for q in (0.05, 1.0, 0.1)]
+    run_stream(net, x0, incs, "increment", label=f"channel split, activation {act}", max_flips=4, tol=1e-5)
+
+
+@pytest.mark.parametrize("where", ["split", "gather"])
+def test_infinities_through_the_channel_split_and_the_up_sampling_gather(where):
+    """Infinite and NaN increments through a conv whose channels are split over workgroups, and through
+    the interpolating gather of a conv behind an up-sampling: infinities and NaN where the oracle's
+    IEEE products put them, every other site as without them."""
+    _say(f"infinities: {where}")
+    if where == "split":
+        ci, h, w, flags = 256, 12, 21, 0
+        b = wl._NetBuilder("inf_ks", ci, h, w, 5)
+        c = b.conv(-1, 32, 3, act=wl.ACT_NONE, out=1)
+    else:
+        ci, h, w, flags = 32, 12, 21, ev.FLAG_NO_FOLD
+        b = wl._NetBuilder("inf_ups", ci, h, w, 5)
+        c = b.conv(b.simple(wl.OP_UPSAMPLE2X, -1), 32, 5, act=wl.ACT_NONE, out=1)
+    net = b.finish()
+    net.weights[::7] = 0.0
+    gpu, ora = ev.EvConvNet(net, flags=flags), Oracle(net)
+    rng = np.random.default_rng(2)
+    x0 = np.zeros((ci, h, w), np.float32)
+    d = (rng.standard_normal(x0.shape) * (rng.random((1, h, w)) < 0.2)).astype(np.float32)
+    d[ci - 1, 2, 3], d[1, 9, 4], d[ci // 2, 6, 17] = np.inf, np.nan, -np.inf
+    gpu.reset(_dev(x0))
+    ora.reset(x0)
+    gpu.step(_dev(d))
+    ora.step_increment(d)
+    z, zr = gpu.state(c, ev.STATE_Z).astype(np.float64), ora.z(c)
+    np.testing.assert_array_equal(np.isnan(z), np.isnan(zr))
+    np.testing.assert_array_equal(z[np.isinf(zr)], zr[np.isinf(zr)])
+    fin = np.isfinite(zr)
+    assert fin.any() and (~fin).any()
+    assert np.isfinite(z[fin]).all() and np.abs(z[fin] - zr[fin]).max() <= 2e-6 * np.abs(zr[fin]).max()
+    gpu.destroy()
