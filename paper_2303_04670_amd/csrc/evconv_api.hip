@@ -417,7 +417,7 @@ struct evconv_net {
   int32_t *idx_in = nullptr, *count_in = nullptr;
   SetDesc* sets_dev = nullptr;
   IntegrateDesc* int_dev = nullptr;  // outputs integrated at the end of a pass
-  int n_int = 0, int_blocks = 0;
+  int n_int = 0, int_blocks = 0, int_large = 0;
   // optional per-node timing with HIP events on the net's stream
   bool prof = false;
   std::vector<hipEvent_t> prof_ev;
@@ -630,6 +630,7 @@ evconv_status run_pass(evconv_net* net, const float* input, int builder_mode, Pa
     fp.sets = net->sets_dev; fp.n_sets = (int)net->L.nodes.size() + 1; fp.max_ty = net->L.max_ty;
     fp.save = save_in_lists;
     fp.outputs = net->int_dev; fp.n_outputs = net->n_int; fp.int_blocks = net->int_blocks; fp.int_mode = int_mode;
+    fp.int_large = net->int_large;
     fp.st = net->st;
     launch_finish(fp, s);
     timed_end(timed, (int)net->L.nodes.size());
@@ -924,6 +925,7 @@ evconv_status create_impl(const evconv_net_desc* desc, const void* weights, size
     if (n.integrates) continue;
     ints.push_back(IntegrateDesc{n.out, n.occ, n.y, n.dy, n.go.h, n.go.w, n.go.c, n.go.tx, net->int_blocks});
     net->int_blocks += integrate_blocks(n.go.c, n.go.sites());
+    if (integrate_large(n.go.c, n.go.sites())) net->int_large = 1;
   }
   net->n_int = (int)ints.size();
   net->int_dev = (IntegrateDesc*)(ws + L.off_int);

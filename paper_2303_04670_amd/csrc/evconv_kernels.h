@@ -215,6 +215,7 @@ struct IntegrateDesc {
   int first_block;          // of the end-of-pass kernel's integration blocks
 };
 int integrate_blocks(int c, int sites);  // blocks that an output of this size takes
+bool integrate_large(int c, int sites);  // whether a step reads its active sites only
 
 // ---- recurrent state: the previous step's output of a later node -----------------------------
 struct DelayParams {
@@ -246,6 +247,7 @@ struct FinishParams {
   const SetDesc* sets; int n_sets, max_ty;  // DEVICE array; tile rows of the tallest set
   int save;                                 // copy the words of sets with a SetDesc::save
   const IntegrateDesc* outputs; int n_outputs, int_blocks, int_mode;  // DEVICE array, ascending first_block
+  int int_large;                            // one of them is integrate_large
   Streams st;
 };
 void launch_finish(const FinishParams& p, hipStream_t s);

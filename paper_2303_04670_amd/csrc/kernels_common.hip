@@ -722,6 +722,7 @@ __device__ __forceinline__ void integrate_element(const IntegrateDesc& p, int mo
 // on one site 35 us.)
 constexpr int kIntFew = 4, kIntChannels = 32;
 constexpr long long kIntSparseReads = 12ll << 20;  // elements
+template <bool LARGE>
 __device__ __forceinline__ void integrate_block(const IntegrateDesc& p, int mode, int b) {
   __shared__ float s_v[64][kIntChannels + 1];
   const int hw = p.h * p.w, C = p.c, tid = threadIdx.x;
@@ -749,15 +750,16 @@ __device__ __forceinline__ void integrate_block(const IntegrateDesc& p, int mode
   // are requested pays where the increments come from HBM; smaller tensors lie in the caches and are
   // read alongside the words (2 % of the sites active, a step of one conv: 64 channels on 480 x 640, 79 MB, 224 us
   // reading all, 182 reading the active ones; on 260 x 346, 23 MB, 65.9 and 69.6).
-  const bool sparse_reads = (long long)hw * C >= kIntSparseReads;
+  // LARGE: the net has such an output (a variant of its own: the test alone costs 0.2 us)
+  const bool sparse_reads = LARGE && (long long)hw * C >= kIntSparseReads;
   const uint64_t wanted = sparse_reads ? __ballot(active()) : ~0ull;
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int c = tid & (kIntChannels - 1), r = (tid >> 5) + 16 * i;
     s_v[r][c] = (s0 + r < hw && c0 + c < C && ((wanted >> r) & 1ull)) ? p.delta[(size_t)(s0 + r) * C + c0 + c] : 0.0f;
   }
-  const bool on = sparse_reads ? ((wanted >> q) & 1ull) != 0 : active();
   __syncthreads();
+  const bool on = sparse_reads ? ((wanted >> q) & 1ull) != 0 : active();
   if (site >= hw) return;
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
@@ -766,6 +768,7 @@ __device__ __forceinline__ void integrate_block(const IntegrateDesc& p, int mode
   }
 }
 
+bool integrate_large(int c, int sites) { return c > kIntFew && (long long)c * sites >= kIntSparseReads; }
 int integrate_blocks(int c, int sites) {
   return c <= kIntFew ? (sites + 511) / 512 : (sites + 63) / 64 * ((c + kIntChannels - 1) / kIntChannels);
 }
@@ -847,6 +850,7 @@ __device__ __forceinline__ void lists_block(SetDesc d, int strip, size_t so, int
   }
 }
 
+template <bool LARGE>
 __global__ __launch_bounds__(512) void finish_kernel(FinishParams p) {
   const size_t so = (size_t)blockIdx.y * p.st.stride;  // the descriptors hold stream 0's pointers
   const int total = p.int_blocks + p.n_sets * p.max_ty;
@@ -857,7 +861,7 @@ __global__ __launch_bounds__(512) void finish_kernel(FinishParams p) {
       IntegrateDesc d = p.outputs[i];
       d.delta = at_stream(d.delta, so); d.occ = at_stream(d.occ, so);
       d.y = at_stream(d.y, so); d.dy = at_stream(d.dy, so);
-      integrate_block(d, p.int_mode, blk - d.first_block);
+      integrate_block<LARGE>(d, p.int_mode, blk - d.first_block);
     } else {
       const int b = blk - p.int_blocks, set = b / p.max_ty;
       lists_block(p.sets[set], b - set * p.max_ty, so, p.save);
@@ -879,7 +883,8 @@ void launch_finish(const FinishParams& p, hipStream_t s) {
   }
   // (a launch holds less than 2^32 threads; the loop takes what is left of a very tall input)
   const int blocks = std::min(p.int_blocks + p.n_sets * p.max_ty, 1 << 22);
-  hipLaunchKernelGGL(finish_kernel, dim3(blocks, p.st.n), dim3(512), 0, s, p);
+  if (p.int_large) hipLaunchKernelGGL(finish_kernel<true>, dim3(blocks, p.st.n), dim3(512), 0, s, p);
+  else hipLaunchKernelGGL(finish_kernel<false>, dim3(blocks, p.st.n), dim3(512), 0, s, p);
 }
 
 // =============================================================================== rounding step
