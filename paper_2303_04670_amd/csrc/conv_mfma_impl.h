@@ -9,13 +9,17 @@
 //   bf16 mode : the gather rounds increments to bf16 on their way into LDS, weights are bf16,
 //               v_mfma_f32_32x32x16_bf16 with fp32 accumulation; a unit = one tap x 16 channels
 //               (one MFMA per block); lanes 0-31 hold channels 0-7, lanes 32-63 channels 8-15.
-//   fp32 mode : the same instruction on operands written exactly as the sum of three bf16 parts,
-//               x = hi + mid + lo with hi = bf16(x), mid = bf16(x - hi), lo = x - hi - mid (3 x 8
-//               signed significant bits hold the 24 of an fp32 value); the gather does that for
-//               the increments, the host for the weights.  A product is the six partial products
-//               down to 2^-16 of it (lo*hi, mid*mid, hi*lo, mid*hi, hi*mid, hi*hi); the three left
-//               out are 2^-25 of it, half the rounding step of an fp32 product.  Six MFMAs at 16
-//               times the rate of the chip's fp32 matrix instruction, which besides runs on the
+//   fp32 mode : the same instruction on operands written as the sum of three bf16 parts (Henry, Tang,
+//               Heinecke: "Leveraging the bfloat16 Artificial Intelligence Datatype For
+//               Higher-Precision Computations", 2019): x = hi + mid + lo with hi = bf16(x), mid =
+//               bf16(x - hi), lo = x - hi - mid.  3 x 8 signed significant bits hold the 24 of an
+//               fp32 value, as long as it has no bits below 2^-133, where bf16 ends: every value of
+//               2^-110 and more.  The gather does that for the increments (smaller ones are rounded
+//               to multiples of 2^-133), the host for the weights (if some are smaller, all of a
+//               conv's are stored times 2^16).  A product is the six partial products down to 2^-16
+//               of it (lo*hi, mid*mid, hi*lo, mid*hi, hi*mid, hi*hi); the three left out add up to
+//               less than 2^-24 of it, the largest rounding error of one fp32 product.  Six MFMAs at
+//               16 times the rate of the chip's fp32 matrix instruction, which besides runs on the
 //               vector pipeline and takes its time from every address and epilogue instruction.
 //   split mode: two parts and three products (lo*hi, hi*lo, hi*hi): 16 significant bits, relative
 //               error of a product about 2^-16, against 2^-8 in bf16 mode.
@@ -549,7 +553,7 @@ void conv_mfma_kernel(ConvParams p) {
       return;
     }
     // x = hi + mid (+ lo): each part the bf16 rounding of what the parts before it leave (the
-    // subtractions are exact); three parts hold all 24 bits of an fp32 value
+    // subtractions are exact); three parts hold all 24 bits of an fp32 value of 2^-110 and more
     float4 r = make_float4(x.x - __uint_as_float(h.x << 16), x.y - __uint_as_float(h.x & 0xffff0000u),
                            x.z - __uint_as_float(h.y << 16), x.w - __uint_as_float(h.y & 0xffff0000u));
     m.x = pack_bf16x2(r.x, r.y);
@@ -703,8 +707,8 @@ void conv_mfma_kernel(ConvParams p) {
   auto mm = [](floatx16& acc, const float4& a, const float4& b) {
     acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), acc, 0, 0, 0);
   };
-  // products of one unit, the smallest terms first; what is left out is 2^-16 (split) or 2^-25
-  // (fp32 mode: the order of the rounding of an fp32 product) of the product
+  // products of one unit, the smallest terms first; what is left out is 2^-16 (split) or less than 2^-24
+  // (fp32 mode: the largest rounding error of an fp32 product) of the product
   auto unit = [&](const AFrag& a, const BFrag& b) {
     if (PARTS == 3) {
       mm(acc0, a.l0, b.h);
