@@ -511,7 +511,9 @@ void conv_mfma_kernel(ConvParams p) {
 #pragma unroll
     for (int it = 0; it < EP_ITERS; ++it) z_old[it] = ep_load(z_rsrc, !p.dense && has(touched_mine, it), it);
   };
-  if (!KSP) request_z();
+  // (variants without registers to spare: after it)
+  constexpr bool LATE_Z = FIVE || (PARTS == 3 && NW == 4 && S2K != 0);
+  if (!KSP && !LATE_Z) request_z();
 
   // the gather's offsets, now conditioned on the occupancy (out of range where the site is inactive)
 #pragma unroll
@@ -852,6 +854,7 @@ void conv_mfma_kernel(ConvParams p) {
   }
 
   };
+  if (!KSP && LATE_Z) request_z();
   if (!KSP) request_fused();
   EVK_PHASE(kPhFusedRequested);
   // ---- reduce the NW partial sums through LDS: slots [4][block*16 + reg][lane]
@@ -1269,10 +1272,10 @@ void launch_shape(const ConvParams& p, hipStream_t s) {
   }
   constexpr int NW4 = CHUNK == 128 ? 8 : 4, MB2 = CHUNK == 128 ? 1 : 2;
   // Four-wave half tiles with the shorter contractions are 5 registers above what five workgroups per
-  // CU leave; held to those (2 to 4 spilled) they lose 5 to 8 %, but a launch of 1024 to 1280 workgroups is
-  // then one round on the chip instead of two, one of 2048 to 2560 two instead of three (bf16, 5 x 5:
-  // 320 -> 320 on 64 x 64, 1280 workgroups, 60.0 -> 46.1 us, 96 -> 96 on 96 x 96, 864, 17.1 -> 17.9; split, 3 x 3: 320 -> 320
-  // on 64 x 64 44.3 -> 37.7, 64 -> 64 on 96 x 96, 576, 11.7 -> 12.6).
+  // CU leave.  A variant that requests the old z values after the contraction instead of before it fits;
+  // it takes the launches of 1024 to 1280 workgroups, which are then one round on the chip instead of
+  // two, and those of 2048 to 2560, two instead of three (bf16, 5 x 5: 320 -> 320 on 64 x 64, 1280 workgroups,
+  // 60.0 -> 46.1 us; split, 3 x 3: 320 -> 320 on 64 x 64 44.3 -> 37.7).
   constexpr bool kFive = (OPM == kOpBf16 && CHUNK == 32) || (OPM == kOpSplit && CHUNK == 64);
   const bool five = kFive && !p.upsample && n <= 2560 && (n + 1279) / 1280 < (n + 1023) / 1024;
   if (halves) {

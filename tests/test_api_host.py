@@ -153,3 +153,12 @@ def test_static_workspace_holds_what_four_bytes_per_weight_and_32_mib_held():
     scratch = 32 * 8 * 32 * 32 * 4   # 32 half-tile workgroups x 8 shares of 32 x 32 sums
     assert (31 << 20) < query(split) - scratch < (32 << 20)
     assert query(nodes) <= ev.STATIC_WORKSPACE_BYTES
+
+
+def test_no_kernel_uses_scratch_memory():
+    """Registers spilled to scratch would make the runtime allocate device memory at a kernel's first
+    launch, which the library promises not to: the metadata of every kernel in the built library
+    states a private segment of 0 bytes (a small msgpack integer behind its key)."""
+    blob = open(ev.LIB_PATH, "rb").read()
+    sizes = [blob[m.end()] for m in re.finditer(rb"\.private_segment_fixed_size", blob)]
+    assert len(sizes) > 50 and set(sizes) == {0}, sizes
