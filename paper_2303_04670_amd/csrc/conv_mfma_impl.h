@@ -187,6 +187,7 @@ __device__ __forceinline__ void split3_large(float x, int shift, unsigned& h, un
 template <int CHUNK, int NW, int OPM, int MB, bool UPS, bool KSP = false, int S2K = 0, bool FIVE = false>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(FIVE ? 5 : MB == 1 && !(UPS && NW == 4) ? 4 : 3)))
 void conv_mfma_kernel(ConvParams p) {
+  touch_params<ConvParams>();
   // this workgroup's stream: every state pointer of p is used through at_stream(.., so); p itself
   // stays untouched so that it remains in the kernel-argument segment
   const size_t so = (size_t)blockIdx.z * p.st.stride;

@@ -39,6 +39,21 @@ __device__ __forceinline__ T* at_stream(T* q, size_t off) {
   return q ? (T*)((uintptr_t)q + off) : nullptr;
 }
 
+// A kernel's arguments are read on demand by scalar loads, each waited for where its value is needed.
+// The first touch of each of their 64-byte lines misses the scalar cache (about 0.45 us: they lie in
+// memory that the host has just written), one line after the other.  Touching all lines together at
+// the start makes that a single miss.
+template <class P>
+__device__ __forceinline__ void touch_params() {
+  typedef const unsigned __attribute__((address_space(4))) Word;
+  Word* const q = (Word*)__builtin_amdgcn_kernarg_segment_ptr();
+  constexpr int kLast = (int)sizeof(P) / 4 - 1;
+  constexpr auto at = [](int line) { return line * 16 < kLast ? line * 16 : kLast; };
+  static_assert(sizeof(P) <= 9 * 64, "touch more lines");
+  asm volatile("" ::"s"(q[at(0)]), "s"(q[at(1)]), "s"(q[at(2)]), "s"(q[at(3)]), "s"(q[at(4)]), "s"(q[at(5)]), "s"(q[at(6)]),
+               "s"(q[at(7)]), "s"(q[at(8)]), "s"(q[kLast]));
+}
+
 // ---- increment builder (Eq.1 + mask) ---------------------------------------------------
 enum BuilderMode { kBuildFrame = 0, kBuildIncrement = 1, kBuildReset = 2, kBuildIncrementDense = 3 };
 struct BuilderParams {

@@ -74,6 +74,7 @@ __device__ __forceinline__ void clear_words(const BuilderParams& p) {
 // ALL: the input has exactly N channels.
 template <int N, bool ALL>
 __global__ __launch_bounds__(512) void builder_kernel(BuilderParams p) {
+  touch_params<BuilderParams>();
   {
     const size_t so = (size_t)blockIdx.z * p.st.stride;
     p.in = at_stream(p.in, (size_t)blockIdx.z * p.in_stride);
@@ -133,6 +134,7 @@ __global__ __launch_bounds__(512) void builder_kernel(BuilderParams p) {
 // (p.tile_count) writes it and leaves both zero for the next launch.
 constexpr int kWideChunk = 64;
 __global__ __launch_bounds__(512) void builder_wide_kernel(BuilderParams p) {
+  touch_params<BuilderParams>();
   {
     const size_t so = (size_t)blockIdx.z * p.st.stride;
     p.in = at_stream(p.in, (size_t)blockIdx.z * p.in_stride);
@@ -265,6 +267,7 @@ template <int VEC> __device__ __forceinline__ VecT<VEC> zerov() {
 
 template <int VEC>
 __global__ __launch_bounds__(256) void elementwise_kernel(EwParams p) {
+  touch_params<EwParams>();
   {
     const size_t so = (size_t)blockIdx.z * p.st.stride;
     p.a = at_stream(p.a, so); p.occ_a = at_stream(p.occ_a, so);
@@ -559,6 +562,7 @@ void launch_elementwise(const EwParams& p, hipStream_t s) {
 // of every tile, a row's eight loads in flight together; the four partial sums are added in a
 // fixed order.  Sites are visited in a fixed order throughout, so the fp32 sum is reproducible.
 __global__ __launch_bounds__(256) void gap_kernel(GapParams p) {
+  touch_params<GapParams>();
   {
     const size_t so = (size_t)blockIdx.z * p.st.stride;
     p.a = at_stream(p.a, so); p.occ_a = at_stream(p.occ_a, so); p.z = at_stream(p.z, so);
@@ -624,6 +628,7 @@ void launch_gap(const GapParams& p, hipStream_t s) {
 // sites.  Bound by HBM (reads the delayed increment and the state, writes both).
 template <int VEC>
 __global__ __launch_bounds__(256) void delay_kernel(DelayParams p) {
+  touch_params<DelayParams>();
   const size_t so = (size_t)blockIdx.z * p.st.stride;
   const float* src = at_stream(p.src_out, so);
   float* z = at_stream(p.z, so);
@@ -852,6 +857,7 @@ __device__ __forceinline__ void lists_block(SetDesc d, int strip, size_t so, int
 
 template <bool LARGE>
 __global__ __launch_bounds__(512) void finish_kernel(FinishParams p) {
+  touch_params<FinishParams>();
   const size_t so = (size_t)blockIdx.y * p.st.stride;  // the descriptors hold stream 0's pointers
   const int total = p.int_blocks + p.n_sets * p.max_ty;
   for (int blk = blockIdx.x; blk < total; blk += gridDim.x) {

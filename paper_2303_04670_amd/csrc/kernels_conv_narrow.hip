@@ -47,6 +47,7 @@ __device__ __forceinline__ float act_n(int act, float v) {
 
 template <int MAXE>  // patch elements per thread
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MAXE <= 3 ? 4 : 3))) void conv_narrow_kernel(ConvParams p) {
+  touch_params<ConvParams>();
   const size_t so = (size_t)blockIdx.z * p.st.stride;  // this workgroup's stream
   constexpr int NT = 256;
   extern __shared__ __align__(16) float s_patch[];

@@ -52,6 +52,7 @@ __device__ __forceinline__ float finish_element(const ConvParams& p, float* z, f
 // channels 34.6, 38.9, 30.4; 64 x 88, 88 tiles: 512 -> 8 channels 53.7, 25.6, 27.5).
 template <int NOUT, int UNROLL>
 __global__ __launch_bounds__(256) void conv_pointwise_few_kernel(ConvParams p) {
+  touch_params<ConvParams>();
   __shared__ unsigned s_nz[2];
   const size_t so = (size_t)blockIdx.z * p.st.stride;  // this workgroup's stream
   const int tid = threadIdx.x;
@@ -162,6 +163,7 @@ __global__ __launch_bounds__(256) void conv_pointwise_few_kernel(ConvParams p) {
 // one wavefront per output channel: the lanes stride through c_in (coalesced weight row), then a
 // butterfly adds the 64 partial sums in a fixed order
 __global__ __launch_bounds__(256) void linear_site_kernel(ConvParams p) {
+  touch_params<ConvParams>();
   const size_t so = (size_t)blockIdx.z * p.st.stride;
   const int lane = threadIdx.x & 63;
   const int co = blockIdx.x * 4 + (threadIdx.x >> 6);

@@ -32,6 +32,7 @@ __device__ __forceinline__ float act_f(int act, float v) {
 }
 
 __global__ __launch_bounds__(256) void conv_valu_kernel(ConvParams p) {
+  touch_params<ConvParams>();
   const size_t so = (size_t)blockIdx.z * p.st.stride;  // this workgroup's stream
   const float* const in_s = at_stream(p.in, so);
   float* const z_s = at_stream(p.z, so);
