@@ -36,7 +36,9 @@ struct Streams {
 };
 template <class T>
 __device__ __forceinline__ T* at_stream(T* q, size_t off) {
-  return q ? (T*)((uintptr_t)q + off) : nullptr;
+  // (pointer arithmetic, not integer arithmetic: an address made from an integer is a generic one to the
+  // compiler, and generic loads also count as LDS accesses, so that every wait for one waits for the other)
+  return q ? (T*)((char*)q + off) : nullptr;
 }
 
 // A kernel's arguments are read on demand by scalar loads, each waited for where its value is needed.

@@ -13,7 +13,26 @@ namespace evk {
 
 namespace {
 
-__device__ __forceinline__ bool occ_bit(const uint64_t* __restrict__ occ, int tx, int y, int x) {
+// pointers read from memory are generic ones to the compiler (see at_stream)
+template <class T>
+__device__ __forceinline__ T __attribute__((address_space(1)))* as_global(T* q) {
+  return (T __attribute__((address_space(1)))*)q;
+}
+
+// inclusive sum over the lanes of a wave (all of them active), by lane shifts in the vector ALU: the
+// same through __shfl_up is six round trips through the LDS
+__device__ __forceinline__ int wave_scan(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);  // row_shr:1, 2, 4, 8 inside rows of 16 lanes
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);  // row_bcast:15 into rows 1 and 3
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);  // row_bcast:31 into rows 2 and 3
+  return v;
+}
+
+template <class WORDS>
+__device__ __forceinline__ bool occ_bit(WORDS occ, int tx, int y, int x) {
   uint64_t w = occ[(y >> 3) * tx + (x >> 3)];
   return (w >> (((y & 7) << 3) | (x & 7))) & 1ull;
 }
@@ -708,7 +727,14 @@ void launch_copy_u64(uint64_t* dst, const uint64_t* src, size_t n, Streams st, h
 // they were 4 us each with about 2 us between them.
 
 // One element of the public tensors; on: the site is in the active set.
-__device__ __forceinline__ void integrate_element(const IntegrateDesc& p, int mode, int e, float v, bool on) {
+struct IntegrateAt {
+  const float __attribute__((address_space(1)))* delta;
+  const uint64_t __attribute__((address_space(1)))* occ;
+  float __attribute__((address_space(1)))* y;
+  float __attribute__((address_space(1)))* dy;
+  int h, w, c, tx;
+};
+__device__ __forceinline__ void integrate_element(const IntegrateAt& p, int mode, int e, float v, bool on) {
   if (mode == kIntStep) {
     if (on) p.y[e] += v;
     p.dy[e] = v;
@@ -728,7 +754,7 @@ __device__ __forceinline__ void integrate_element(const IntegrateDesc& p, int mo
 constexpr int kIntFew = 4, kIntChannels = 32;
 constexpr long long kIntSparseReads = 12ll << 20;  // elements
 template <bool LARGE>
-__device__ __forceinline__ void integrate_block(const IntegrateDesc& p, int mode, int b) {
+__device__ __forceinline__ void integrate_block(const IntegrateAt& p, int mode, int b) {
   __shared__ float s_v[64][kIntChannels + 1];
   const int hw = p.h * p.w, C = p.c, tid = threadIdx.x;
   if (C <= kIntFew) {
@@ -783,34 +809,39 @@ int integrate_blocks(int c, int sites) {
 // inside the strip wave r owns image row r and scans the per-tile byte popcounts with a
 // wave-wide prefix sum, so indices come out strictly ascending in y*W + x.
 // A recurrent net's delayed nodes have their words copied to SetDesc::save on the way.
-__device__ __forceinline__ void lists_block(SetDesc d, int strip, size_t so, int save) {
+__device__ __forceinline__ void lists_block(const SetDesc& d, int strip, size_t so, int save) {
   __shared__ int s_part[8];
   __shared__ int s_rowcnt[8];
-  {
-    d.occ = at_stream(d.occ, so); d.idx = at_stream(d.idx, so);
-    d.count = at_stream(d.count, so); d.bitmap = at_stream(d.bitmap, so);
-    d.save = at_stream(d.save, so);
-  }
   if (strip >= d.ty) return;
+  const auto occ = as_global(at_stream(d.occ, so));
+  const auto idx = as_global(at_stream(d.idx, so));
   const int tid = threadIdx.x, lane = tid & 63, r = tid >> 6;
-  if (save && d.save)
-    for (int t = tid; t < d.tx; t += 512) d.save[strip * d.tx + t] = d.occ[strip * d.tx + t];
-
-  int cnt = 0;
-  for (int t = tid; t < strip * d.tx; t += 512) cnt += __popcll(d.occ[t]);
-  for (int o = 32; o > 0; o >>= 1) cnt += __shfl_down(cnt, o);
-  if (lane == 0) s_part[r] = cnt;
-
-  // row r of this strip: per-tile 8-bit masks
-  int row_total = 0;
-  for (int j0 = 0; j0 < d.tx; j0 += 64) {
-    const int j = j0 + lane;
-    const unsigned byte = j < d.tx ? (unsigned)((d.occ[strip * d.tx + j] >> (8 * r)) & 0xffull) : 0u;
-    int c = __popc(byte);
-    for (int o = 32; o > 0; o >>= 1) c += __shfl_down(c, o);
-    row_total += __shfl(c, 0);
+  if (save && d.save) {
+    const auto copy = as_global(at_stream(d.save, so));
+    for (int t = tid; t < d.tx; t += 512) copy[strip * d.tx + t] = occ[strip * d.tx + t];
   }
-  if (lane == 0) s_rowcnt[r] = row_total;
+
+  // active sites of the earlier strips, four words of a thread in flight
+  int cnt = 0;
+  const int before = strip * d.tx;
+  for (int t = tid; t < before; t += 4 * 512) {
+    uint64_t w[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) w[i] = t + i * 512 < before ? occ[t + i * 512] : 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) cnt += __popcll(w[i]);
+  }
+  // row r of this strip: per-tile 8-bit masks (bytes of the words)
+  const auto row_bytes = (const unsigned char __attribute__((address_space(1)))*)(occ + before) + r;
+  unsigned byte = lane < d.tx ? row_bytes[lane * 8] : 0u;
+  int incl = wave_scan(__popc(byte));
+  int row_total = __builtin_amdgcn_readlane(incl, 63);
+  for (int j0 = 64; j0 < d.tx; j0 += 64) {
+    const int j = j0 + lane;
+    row_total += __builtin_amdgcn_readlane(wave_scan(j < d.tx ? __popc((unsigned)row_bytes[j * 8]) : 0), 63);
+  }
+  cnt = __builtin_amdgcn_readlane(wave_scan(cnt), 63);
+  if (lane == 0) { s_part[r] = cnt; s_rowcnt[r] = row_total; }
   __syncthreads();
 
   int base = 0;
@@ -820,37 +851,34 @@ __device__ __forceinline__ void lists_block(SetDesc d, int strip, size_t so, int
     if (i < r) base += s_rowcnt[i];
     strip_total += s_rowcnt[i];
   }
-  const int total_before = base;  // list position of the first active site of row r
-  int running = total_before;
+  int running = base;  // list position of the first active site of row r
   const int y = strip * 8 + r;
-  for (int j0 = 0; j0 < d.tx; j0 += 64) {
-    const int j = j0 + lane;
-    unsigned byte = j < d.tx ? (unsigned)((d.occ[strip * d.tx + j] >> (8 * r)) & 0xffull) : 0u;
-    const int c = __popc(byte);
-    int incl = c;  // inclusive wave scan
-    for (int o = 1; o < 64; o <<= 1) {
-      const int v = __shfl_up(incl, o);
-      if (lane >= o) incl += v;
-    }
-    int pos = running + incl - c;
+  for (int j0 = 0;;) {
+    int pos = running + incl - __popc(byte);
+    const int at = y * d.w + (j0 + lane) * 8;
     while (byte) {
       const int bit = __ffs(byte) - 1;
       byte &= byte - 1;
-      d.idx[pos++] = y * d.w + j * 8 + bit;
+      idx[pos++] = at + bit;
     }
-    running += __shfl(incl, 63);
+    running += __builtin_amdgcn_readlane(incl, 63);
+    j0 += 64;
+    if (j0 >= d.tx) break;
+    byte = j0 + lane < d.tx ? row_bytes[(j0 + lane) * 8] : 0u;
+    incl = wave_scan(__popc(byte));
   }
   if (strip == d.ty - 1 && tid == 0) {
     int s = 0;
     for (int i = 0; i < 8; ++i) s += s_part[i];
-    *d.count = s + strip_total;
+    *as_global(at_stream(d.count, so)) = s + strip_total;
   }
   if (strip == 0) {  // tile bitmap: one ballot per 64 tiles
     const int n_tiles = d.tx * d.ty;
+    const auto bitmap = as_global(at_stream(d.bitmap, so));
     for (int w0 = r * 64; w0 < n_tiles; w0 += 512) {
       const int t = w0 + lane;
-      const uint64_t b = __ballot(t < n_tiles && d.occ[t] != 0);
-      if (lane == 0) d.bitmap[w0 >> 6] = b;
+      const uint64_t b = __ballot(t < n_tiles && occ[t] != 0);
+      if (lane == 0) bitmap[w0 >> 6] = b;
     }
   }
 }
@@ -864,10 +892,10 @@ __global__ __launch_bounds__(512) void finish_kernel(FinishParams p) {
     if (blk < p.int_blocks) {
       int i = 0;
       while (i + 1 < p.n_outputs && blk >= p.outputs[i + 1].first_block) ++i;
-      IntegrateDesc d = p.outputs[i];
-      d.delta = at_stream(d.delta, so); d.occ = at_stream(d.occ, so);
-      d.y = at_stream(d.y, so); d.dy = at_stream(d.dy, so);
-      integrate_block<LARGE>(d, p.int_mode, blk - d.first_block);
+      const IntegrateDesc& d = p.outputs[i];
+      const IntegrateAt at = {as_global(at_stream(d.delta, so)), as_global(at_stream(d.occ, so)), as_global(at_stream(d.y, so)),
+                              as_global(at_stream(d.dy, so)), d.h, d.w, d.c, d.tx};
+      integrate_block<LARGE>(at, p.int_mode, blk - d.first_block);
     } else {
       const int b = blk - p.int_blocks, set = b / p.max_ty;
       lists_block(p.sets[set], b - set * p.max_ty, so, p.save);
