@@ -188,9 +188,15 @@ template <int CHUNK, int NW, int OPM, int MB, bool UPS, bool KSP = false, int S2
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(FIVE ? 5 : MB == 1 && !(UPS && NW == 4) ? 4 : 3)))
 void conv_mfma_kernel(ConvParams p) {
   touch_params<ConvParams>();
+  // (what the prologue needs is loaded together, too: on demand it was a dozen loads, each waited for)
+  if (!UPS)
+    asm volatile("" ::"s"(p.gi.h), "s"(p.gi.w), "s"(p.gi.c), "s"(p.go.h), "s"(p.go.w), "s"(p.go.c), "s"(p.go.tx), "s"(p.k),
+               "s"(p.stride), "s"(p.pad), "s"(p.dense), "s"(p.n_fused), "s"(p.c_out_pad), "s"(p.occ_in), "s"(p.in), "s"(p.z),
+               "s"(p.w), "s"(p.st.stride), "s"(p.wg_swap), "s"(p.tx_magic), "s"(p.gw_magic[0]), "s"(p.k_magic[0]));
   // this workgroup's stream: every state pointer of p is used through at_stream(.., so); p itself
   // stays untouched so that it remains in the kernel-argument segment
   const size_t so = (size_t)blockIdx.z * p.st.stride;
+  const bool dense = p.dense != 0;
   constexpr int PARTS = op_parts(OPM);     // bf16 parts of an operand
   constexpr int NB = 32;                   // output channels per workgroup
   constexpr int NT = NW * 64;
@@ -216,9 +222,7 @@ void conv_mfma_kernel(ConvParams p) {
   // a weight-folded workgroup gathers an (NROWS + 3) x 11 patch (4 x 4 taps) through the same registers
   static_assert(!UPS || MAXG * NT >= (4 * MB + 3) * 11 * NV, "folded patch does not fit the gather registers");
   extern __shared__ __align__(16) float s_mem[];
-  __shared__ uint64_t s_occ[16];
-  __shared__ unsigned s_rows[24];  // bit px of s_rows[py]: patch site (py, px) is active
-  __shared__ unsigned s_lrows[UPS ? LPMAX : 1];  // UPS: the same for the low-resolution source region
+  __shared__ unsigned s_arrived;  // KSP: shares of the block that were there before this one
   __shared__ uint64_t s_nz[(2 + kMaxFusedAdds) * NW];  // nonzero-site bits per wave: conv, each fused ADD, fused sparsification
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -280,8 +284,24 @@ void conv_mfma_kernel(ConvParams p) {
   const int s_ty = (SH + 7) >> 3, s_tx = (SW + 7) >> 3;
   const int gy0 = ups ? (iy0 >> 1) - 1 : iy0, gx0 = ups ? (ix0 >> 1) - 1 : ix0;
   const int GH = ups ? PH / 2 + 3 : PH, GW = ups ? PW / 2 + 3 : PW;
-  const int rty0 = gy0 >> 3, rtx0 = gx0 >> 3;
-  const int rny = ((gy0 + GH - 1) >> 3) - rty0 + 1, rnx = ((gx0 + GW - 1) >> 3) - rtx0 + 1;
+
+  // Activity of the region as one row of bits per lane: bit x of lane y's `bits` is site (y, x).  A row
+  // is a byte of each of at most four occupancy words, so every wave reads the bytes of its lanes' rows
+  // itself and nothing before the first patch goes through LDS or a barrier.  (For a tile beyond the left
+  // or right border a neighbour's byte is read; it is cut off with the columns outside the image.)
+  const int rtx0 = gx0 >> 3, gy = gy0 + lane;
+  const bool row_ok = lane < GH && (unsigned)gy < (unsigned)SH;
+  // (read in a regular pass too, where they are not used: without a branch the loads are in flight while
+  // the addresses below are worked out)
+  unsigned row_byte[4];
+  {
+    const __amdgpu_buffer_rsrc_t occ_rsrc =
+        __builtin_amdgcn_make_buffer_rsrc((void*)at_stream(p.occ_in, so), 0, s_ty * s_tx * 8, 0x00020000);
+    const unsigned off = row_ok ? (unsigned)(__mul24(gy >> 3, s_tx) * 8 + (gy & 7)) : 0x80000000u;
+#pragma unroll
+    for (int rx = 0; rx < 4; ++rx)
+      row_byte[rx] = (unsigned char)__builtin_amdgcn_raw_buffer_load_b8(occ_rsrc, off, min(max(rtx0 + rx, 0), s_tx - 1) * 8, 0);
+  }
 
   // occupancy words of the fused ADD nodes' other inputs: requested first, so that their latency
   // runs alongside that of the input's occupancy words instead of after it
@@ -289,7 +309,7 @@ void conv_mfma_kernel(ConvParams p) {
 #pragma unroll
   for (int f = 0; f < kMaxFusedAdds; ++f) {
     skip_raw[f] = 0;
-    if (f >= p.n_fused || p.dense) continue;
+    if (f >= p.n_fused || dense) continue;
     if (fold) {
       // per lane (= site of the stored tile) the word of the up-sampled tile its output lies in;
       // turned into this phase's site bits further down
@@ -299,14 +319,6 @@ void conv_mfma_kernel(ConvParams p) {
       skip_raw[f] = at_stream(p.fused[f].occ_skip, so)[tile];
     }
   }
-  uint64_t occ_w = 0;
-  if (tid < 16) {
-    const int ry = tid >> 2, rx = tid & 3;
-    const int ty = rty0 + ry, tx = rtx0 + rx;
-    if (ry < rny && rx < rnx && ty >= 0 && ty < s_ty && tx >= 0 && tx < s_tx)
-      occ_w = p.dense ? ~0ull : at_stream(p.occ_in, so)[ty * s_tx + tx];
-  }
-
   // While the occupancy words are on their way: everything about the gather that depends on the
   // tile's position only.
   // ---- patch gather: per thread a fixed list of (LDS offset, byte offset into the input)
@@ -329,7 +341,8 @@ void conv_mfma_kernel(ConvParams p) {
   // whole workgroup where no thread has a j-th item)
   static_assert(NT % NV == 0, "a thread's items are of one channel group");
   const int v4 = tid % NV;  // channel group of this thread's items
-  auto has_item = [&](int j) { return (UPS && PARTS != 1) || j * (NT / NV) <= last_site; };
+  // (items go in pairs, so that the work of two of them overlaps)
+  auto has_pair = [&](int j) { return j == 0 || (UPS && PARTS != 1) || j * (NT / NV) <= last_site; };
   int lds_off[MAXG];     // (until the occupancy is known: patch row and column in bits 16-23 and 24-31)
   unsigned g_off[MAXG];
 #pragma unroll
@@ -388,53 +401,66 @@ void conv_mfma_kernel(ConvParams p) {
     }
   }
 
-  if (tid < 16) s_occ[tid] = occ_w;
-  __syncthreads();
+  // columns [lo, hi) of a region whose first one is image column x0, as a mask
+  auto inside = [](int x0, int n, int width) {
+    const int lo = max(0, -x0), hi = min(n, width - x0);
+    return (hi >= 32 ? ~0u : ((1u << max(hi, 0)) - 1u)) & ~((1u << min(lo, 31)) - 1u);
+  };
+  auto of_lane = [](int i, unsigned v) { return (unsigned)__builtin_amdgcn_ds_bpermute(i * 4, (int)v); };
+  const unsigned span = row_byte[0] | (row_byte[1] << 8) | (row_byte[2] << 16) | (row_byte[3] << 24);
+  const unsigned src_bits = (dense ? ~0u : span >> (gx0 - rtx0 * 8)) & (row_ok ? inside(gx0, GW, SW) : 0u);  // the gathered region's
   EVK_PHASE(kPhOccInLds);
-  if (tid < GH) {  // one bit row per row of the region; out-of-image sites are 0
-    const int gy = gy0 + tid;
-    unsigned bits = 0;
-    if ((unsigned)gy < (unsigned)SH) {
-      const int ry = (gy >> 3) - rty0;
-      // 32 consecutive columns starting at image column rtx0 * 8
-      uint64_t span = 0;
-#pragma unroll
-      for (int rx = 0; rx < 4; ++rx)
-        span |= ((s_occ[ry * 4 + rx] >> ((gy & 7) * 8)) & 0xffull) << (8 * rx);
-      bits = (unsigned)(span >> (gx0 - rtx0 * 8));
-      // clear columns outside the image (dense mode sets every bit) and beyond the region
-      const int lo = max(0, -gx0), hi = min(GW, SW - gx0);  // valid columns in [lo, hi)
-      unsigned m = hi >= 32 ? ~0u : ((1u << max(hi, 0)) - 1u);
-      m &= ~((1u << lo) - 1u);
-      bits &= m;
-    }
-    if (ups) s_lrows[tid] = bits; else s_rows[tid] = bits;
-  }
-  __syncthreads();
+  unsigned bits = src_bits;  // the patch's
   if (ups) {
-    // an up-sampled site is active where one of its four sources is: OR of two source rows, then
-    // of two source columns; sites outside the up-sampled image stay 0
-    if (tid < PH) {
-      const int iy = iy0 + tid;
-      unsigned bits = 0;
-      if ((unsigned)iy < (unsigned)H) {
-        const int hy = iy >> 1;
-        const int y0 = (iy & 1) ? hy : max(hy - 1, 0), y1 = (iy & 1) ? min(hy + 1, SH - 1) : hy;
-        const unsigned src = s_lrows[y0 - gy0] | s_lrows[y1 - gy0];
-        for (int px = 0; px < PW; ++px) {
-          const int ix = ix0 + px;
-          if ((unsigned)ix >= (unsigned)W) continue;
-          const int hx = ix >> 1;
-          const int x0 = (ix & 1) ? hx : max(hx - 1, 0), x1 = (ix & 1) ? min(hx + 1, SW - 1) : hx;
-          bits |= (((src >> (x0 - gx0)) | (src >> (x1 - gx0))) & 1u) << px;
-        }
-      }
-      s_rows[tid] = bits;
-    }
-    __syncthreads();
+    // an up-sampled site is active where one of its four sources is: OR of two source rows, then of two
+    // source columns (column 2b: stored columns b - 1 and b; column 2b + 1: b and b + 1; a column that
+    // the clamped border replaces is the other one, and out of image it is a zero bit), interleaved
+    const int iy = iy0 + lane, hy = iy >> 1;
+    const int y0 = (iy & 1) ? hy : max(hy - 1, 0), y1 = (iy & 1) ? min(hy + 1, SH - 1) : hy;
+    const unsigned src = of_lane(y0 - gy0, src_bits) | of_lane(y1 - gy0, src_bits);
+    auto spread = [](unsigned v) {
+      v = (v | (v << 8)) & 0x00ff00ffu;
+      v = (v | (v << 4)) & 0x0f0f0f0fu;
+      v = (v | (v << 2)) & 0x33333333u;
+      return (v | (v << 1)) & 0x55555555u;
+    };
+    const unsigned up = spread((src | (src << 1)) & 0xffffu) | (spread((src | (src >> 1)) & 0xffffu) << 1);
+    bits = lane < PH && (unsigned)iy < (unsigned)H ? (up >> (ix0 - 2 * gx0)) & inside(ix0, PW, W) : 0u;
   }
 
   EVK_PHASE(kPhBitRows);
+  const int c_lo = KSP ? ks * p.ks_chunks * CHUNK : 0;
+  // the gather's offsets, now conditioned on the occupancy (out of range where the site is inactive)
+#pragma unroll
+  for (int j = 0; j < MAXG; ++j) {
+    const int py = (lds_off[j] >> 16) & 0xff, px = lds_off[j] >> 24;
+    lds_off[j] &= 0xffff;
+    const unsigned row = of_lane(py, src_bits);
+    if (!((row >> px) & 1u)) g_off[j] = kOob;
+  }
+  // c_in need not be a multiple of four: the 16-byte load of a site's last channel group then
+  // runs into the next site (buffer loads of dwords need dword alignment only); the foreign
+  // components are zeroed on the way into LDS.  The range is extended by those 12 bytes so that
+  // the last site's group is not rejected as a whole (every tensor of the workspace is followed
+  // by padding or by another buffer of the workspace).
+  const int tail = Cin & 3;
+  const __amdgpu_buffer_rsrc_t in_rsrc = __builtin_amdgcn_make_buffer_rsrc(
+      (void*)at_stream(p.in, so), 0, SH * SW * Cin * 4 + (tail ? 12 : 0), 0x00020000);
+  float4 pre[MAXG];
+  // c_in need not be a multiple of the chunk: channel groups beyond c_in read as zeros (their
+  // weight rows are zero padding as well)
+  const bool ragged = (Cin % CHUNK) != 0;
+  auto fetch = [&](int c0) {
+#pragma unroll
+    for (int j = 0; j < MAXG; ++j) {
+      if (!has_pair(j & ~1)) continue;
+      unsigned off = g_off[j];
+      if (ragged && c0 + v4 * 4 >= Cin) off = kOob;
+      pre[j] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(in_rsrc, off, c0 * 4, 0));
+    }
+  };
+  // (requested before the touched set is worked out: where no site of the patch is active, nothing is read)
+  fetch(c_lo);
   // touched word of this workgroup's rows (identical in all waves): OR of the K bit rows under a
   // site, then any of the K columns
   uint64_t touched_word;
@@ -442,18 +468,16 @@ void conv_mfma_kernel(ConvParams p) {
     const int ly = lane >> 3, lx = lane & 7;
     const int oy = tile_y * 8 + ly, ox = tile_x * 8 + lx;
     const int lr = ly - r0;
-    bool touched = false;
-    // (a weight-folded workgroup's tile lies inside the stored image, all of its outputs exist)
-    if (lr >= 0 && lr < NROWS && (fold || (oy < p.go.h && ox < p.go.w))) {
-      unsigned rows = 0;
-      // (all seven possible rows at once instead of a chain of K reads; s_rows is long enough)
+    unsigned rows = 0;
 #pragma unroll
-      for (int ky = 0; ky < 7; ++ky) {
-        const unsigned row = s_rows[lr * s + ky];
-        rows |= ky < K ? row : 0u;
-      }
-      touched = p.dense || ((rows >> (lx * s)) & ((1u << K) - 1u)) != 0;
+    for (int ky = 0; ky < 7; ++ky) {
+      const unsigned row = of_lane(lr * s + ky, bits);
+      rows |= ky < K ? row : 0u;
     }
+    // (a weight-folded workgroup's tile lies inside the stored image, all of its outputs exist)
+    // (no short circuits: they would become branches)
+    const bool exists = ((unsigned)lr < (unsigned)NROWS) & (fold | ((oy < p.go.h) & (ox < p.go.w)));
+    const bool touched = exists & (dense | (((rows >> (lx * s)) & ((1u << K) - 1u)) != 0));
     touched_word = __ballot(touched);
   }
   // fused ADD nodes: their other input may be active where the conv is not
@@ -462,15 +486,14 @@ void conv_mfma_kernel(ConvParams p) {
 #pragma unroll
   for (int f = 0; f < kMaxFusedAdds; ++f) {
     skip_word[f] = 0;
-    if (f < p.n_fused && fold && !p.dense)
+    if (f < p.n_fused && fold && !dense)
       skip_raw[f] = __ballot(((skip_raw[f] >> ((2 * ((lane >> 3) & 3) + fpy) * 8 + 2 * (lane & 3) + fpx)) & 1ull) != 0);
-    if (f < p.n_fused) skip_word[f] = p.dense ? touched_word : (skip_raw[f] & row_mask);
+    if (f < p.n_fused) skip_word[f] = dense ? touched_word : (skip_raw[f] & row_mask);
     site_word |= skip_word[f];
   }
   if (site_word == 0) return;
   const bool conv_on = touched_word != 0;
   if (KSP && ks != 0 && !conv_on) return;  // nothing to contract: the first workgroup runs the epilogue alone
-  const int c_lo = KSP ? ks * p.ks_chunks * CHUNK : 0;
   const int c_hi = KSP ? min(p.gi.c, c_lo + p.ks_chunks * CHUNK) : p.gi.c;
 
   // Epilogue addressing.  Thread = output channel co0 + tid % 32 at the EP_ITERS sites
@@ -510,44 +533,15 @@ void conv_mfma_kernel(ConvParams p) {
   float z_old[EP_ITERS];
   auto request_z = [&]() {
 #pragma unroll
-    for (int it = 0; it < EP_ITERS; ++it) z_old[it] = ep_load(z_rsrc, !p.dense && has(touched_mine, it), it);
+    for (int it = 0; it < EP_ITERS; ++it) z_old[it] = ep_load(z_rsrc, !dense && has(touched_mine, it), it);
   };
   // (variants without registers to spare: after it)
   constexpr bool LATE_Z = FIVE || (PARTS == 3 && NW == 4 && S2K != 0);
   if (!KSP && !LATE_Z) request_z();
 
-  // the gather's offsets, now conditioned on the occupancy (out of range where the site is inactive)
-#pragma unroll
-  for (int j = 0; j < MAXG; ++j) {
-    if (!has_item(j)) continue;
-    const int py = (lds_off[j] >> 16) & 0xff, px = lds_off[j] >> 24;
-    lds_off[j] &= 0xffff;
-    const unsigned row = ups ? s_lrows[py] : s_rows[py];
-    if (!((row >> px) & 1u)) g_off[j] = kOob;
-  }
-  // c_in need not be a multiple of four: the 16-byte load of a site's last channel group then
-  // runs into the next site (buffer loads of dwords need dword alignment only); the foreign
-  // components are zeroed on the way into LDS.  The range is extended by those 12 bytes so that
-  // the last site's group is not rejected as a whole (every tensor of the workspace is followed
-  // by padding or by another buffer of the workspace).
-  const int tail = Cin & 3;
-  const __amdgpu_buffer_rsrc_t in_rsrc = __builtin_amdgcn_make_buffer_rsrc(
-      (void*)at_stream(p.in, so), 0, SH * SW * Cin * 4 + (tail ? 12 : 0), 0x00020000);
-  float4 pre[MAXG];
-  // c_in need not be a multiple of the chunk: channel groups beyond c_in read as zeros (their
-  // weight rows are zero padding as well)
-  const bool ragged = (Cin % CHUNK) != 0;
-  auto fetch = [&](int c0) {
-#pragma unroll
-    for (int j = 0; j < MAXG; ++j) {
-      if (!has_item(j)) continue;
-      unsigned off = g_off[j];
-      if (ragged && c0 + v4 * 4 >= Cin) off = kOob;
-      pre[j] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(in_rsrc, off, c0 * 4, 0));
-    }
-  };
   // one float4 of patch channels into the patch buffer, as the operand mode's bf16 parts
-  auto put = [&](int off, const float4& x) {
+  // (large: some of the values a bf16 cannot round without overflow, or are infinite; a NaN makes every part NaN)
+  auto put = [&](int off, const float4& x, bool large) __attribute__((always_inline)) {
     uint2 h, m, l;
     h.x = pack_bf16x2(x.x, x.y);
     h.y = pack_bf16x2(x.z, x.w);
@@ -564,8 +558,7 @@ void conv_mfma_kernel(ConvParams p) {
     if (PARTS == 3) {
       l.x = pack_bf16x2(r.x - __uint_as_float(m.x << 16), r.y - __uint_as_float(m.x & 0xffff0000u));
       l.y = pack_bf16x2(r.z - __uint_as_float(m.y << 16), r.w - __uint_as_float(m.y & 0xffff0000u));
-      // values that a bf16 cannot round without overflow, and infinities (a NaN makes every part NaN)
-      if (fmaxf(fmaxf(fabsf(x.x), fabsf(x.y)), fmaxf(fabsf(x.z), fabsf(x.w))) >= kBf16Overflow) {
+      if (large) {
         split3_large(x.x, 0, h.x, m.x, l.x);
         split3_large(x.y, 16, h.x, m.x, l.x);
         split3_large(x.z, 0, h.y, m.y, l.y);
@@ -575,6 +568,9 @@ void conv_mfma_kernel(ConvParams p) {
     }
     *(uint2*)&s_mem[off] = h;
     *(uint2*)&s_mem[off + LO] = m;
+  };
+  auto max4 = [](const float4& x, float m) {
+    return fmaxf(fmaxf(fmaxf(fabsf(x.x), fabsf(x.y)), fmaxf(fabsf(x.z), fabsf(x.w))), m);
   };
   auto stash = [&](int c0) {
     if (tail) {  // (uniform; nets with c_in % 4 == 0 pay nothing)
@@ -590,9 +586,22 @@ void conv_mfma_kernel(ConvParams p) {
     }
 #pragma unroll
     for (int j = 0; j < MAXG; ++j) {
-      if (!has_item(j)) continue;
+      if (!has_pair(j & ~1)) continue;
       if (ups) *(float4*)&s_low[lds_off[j]] = pre[j];
-      else put(lds_off[j], pre[j]);
+      else put(lds_off[j], pre[j], false);
+    }
+    // the rare large values are looked for once for all items: a branch per item would keep the items'
+    // work apart
+    if (PARTS == 3 && !ups) {
+      float largest = 0.0f;
+#pragma unroll
+      for (int j = 0; j < MAXG; ++j)
+        if (has_pair(j & ~1)) largest = max4(pre[j], largest);
+      if (__builtin_expect(largest >= kBf16Overflow, 0)) {
+#pragma unroll
+        for (int j = 0; j < MAXG; ++j)
+          if (has_pair(j & ~1)) put(lds_off[j], pre[j], true);
+      }
     }
   };
   auto interpolate = [&]() {
@@ -616,10 +625,15 @@ void conv_mfma_kernel(ConvParams p) {
       const float4 a1 = hsum(0.75f, v10, 0.25f, v11), b1 = hsum(0.25f, v10, 0.75f, v11);
       const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
       const int dst = (ib_dst[b] & 0xffff) - 4096;
-      if (mask & 1) put(dst, (mask & 16) ? hsum(0.75f, a0, 0.25f, a1) : zero);
-      if (mask & 2) put(dst + CS, (mask & 32) ? hsum(0.75f, b0, 0.25f, b1) : zero);
-      if (mask & 4) put(dst + RP, (mask & 64) ? hsum(0.25f, a0, 0.75f, a1) : zero);
-      if (mask & 8) put(dst + RP + CS, (mask & 128) ? hsum(0.25f, b0, 0.75f, b1) : zero);
+      auto block = [&](bool large) __attribute__((always_inline)) {
+        if (mask & 1) put(dst, (mask & 16) ? hsum(0.75f, a0, 0.25f, a1) : zero, large);
+        if (mask & 2) put(dst + CS, (mask & 32) ? hsum(0.75f, b0, 0.25f, b1) : zero, large);
+        if (mask & 4) put(dst + RP, (mask & 64) ? hsum(0.25f, a0, 0.75f, a1) : zero, large);
+        if (mask & 8) put(dst + RP + CS, (mask & 128) ? hsum(0.25f, b0, 0.75f, b1) : zero, large);
+      };
+      block(false);
+      // (an interpolated value is no larger than its sources)
+      if (PARTS == 3 && __builtin_expect(max4(v00, max4(v01, max4(v10, max4(v11, 0.0f)))) >= kBf16Overflow, 0)) block(true);
     }
   };
 
@@ -748,12 +762,9 @@ void conv_mfma_kernel(ConvParams p) {
   bq1 = bq0;
   bq2 = bq0;
   EVK_PHASE(kPhAddressed);
-  if (conv_on) {
-    fetch(c_lo);
-    if (n_mine > 0) {
-      bq0 = b_load(c_lo, 0);
-      bq1 = b_load(c_lo, 1);
-    }
+  if (conv_on && n_mine > 0) {
+    bq0 = b_load(c_lo, 0);
+    bq1 = b_load(c_lo, 1);
   }
   EVK_PHASE(kPhFirstIssued);
 #ifdef EVCONV_PHASE_STAMPS
@@ -763,7 +774,7 @@ void conv_mfma_kernel(ConvParams p) {
 #ifdef EVCONV_PHASE_STAMPS
     const unsigned long long ph_a = wall_clock64();
 #endif
-    __syncthreads();  // all waves are done reading the previous chunk
+    if (c0 != c_lo) __syncthreads();  // all waves are done reading the previous chunk
     stash(c0);
     __syncthreads();
     if (ups) {
@@ -838,7 +849,7 @@ void conv_mfma_kernel(ConvParams p) {
     const __amdgpu_buffer_rsrc_t skip_rsrc = out_rsrc(at_stream(p.fused[f].skip, so));
 #pragma unroll
     for (int it = 0; it < EP_ITERS; ++it) f_skip[f][it] = ep_load(skip_rsrc, has(skip_mine, it), it);
-    if (p.fused[f].keeps_z && !p.dense) {
+    if (p.fused[f].keeps_z && !dense) {
       const __amdgpu_buffer_rsrc_t fz_rsrc = out_rsrc(at_stream(p.fused[f].z, so));
 #pragma unroll
       for (int it = 0; it < EP_ITERS; ++it) f_zold[f][it] = ep_load(fz_rsrc, has(site_mine, it), it);
@@ -847,7 +858,7 @@ void conv_mfma_kernel(ConvParams p) {
 
 #pragma unroll
   for (int it = 0; it < EP_ITERS; ++it) sp_delta[it] = 0.0f;
-  if (p.sp.delta && !p.dense) {
+  if (p.sp.delta && !dense) {
     sp_k = *at_stream(p.sp.step, so);
     const __amdgpu_buffer_rsrc_t d_rsrc = out_rsrc(at_stream(p.sp.delta, so));
 #pragma unroll
@@ -901,7 +912,7 @@ void conv_mfma_kernel(ConvParams p) {
   // partial sum of local site ls = it * EP_SITES + es: the part of the LDS offset that depends on
   // the thread (es < 16), the rest is a constant per `it`
   const int off_mine = ((es >> 3) * 4 + (es & 3)) * 64 + ((es >> 2) & 1) * 32 + co;
-  const float bias = (p.dense && p.bias && co_ok) ? p.bias[co0 + co] : 0.0f;
+  const float bias = (dense && p.bias && co_ok) ? p.bias[co0 + co] : 0.0f;
   // Straight-line code: a site this thread does not own gets an out-of-range offset (its stores
   // are dropped) instead of a branch around it, and the partial sums of all passes are read from
   // LDS up front, so that the passes are not a chain of LDS round trips.
@@ -931,10 +942,10 @@ void conv_mfma_kernel(ConvParams p) {
         unsigned* const cnt = at_stream(p.ks_count, so) + out_blk;
         const unsigned before = __hip_atomic_fetch_add(cnt, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (before == (unsigned)p.ks - 1u) __hip_atomic_store(cnt, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        s_rows[0] = before;
+        s_arrived = before;
       }
       __syncthreads();
-      if (s_rows[0] != (unsigned)p.ks - 1u) return;
+      if (s_arrived != (unsigned)p.ks - 1u) return;
       request_z();
       request_fused();
       asm volatile("" ::: "memory");
@@ -972,7 +983,6 @@ void conv_mfma_kernel(ConvParams p) {
     constexpr bool HAS_SP = decltype(sp_tag)::value;
     constexpr int NF = decltype(nf_tag)::value;   // fused ADDs
     constexpr int KZ = decltype(kz_tag)::value;   // they keep a z: 0 no, 1 yes, 2 looked up
-    const bool dense = p.dense != 0;
     const bool relu0 = p.act == kActRelu;
     bool f_kz[kMaxFusedAdds], f_relu[kMaxFusedAdds];
     __amdgpu_buffer_rsrc_t f_out_r[kMaxFusedAdds], f_z_r[kMaxFusedAdds];
@@ -1049,7 +1059,7 @@ void conv_mfma_kernel(ConvParams p) {
     float o;
     {
       const float v = v_sum[it];
-      if (p.dense) {
+      if (dense) {
         const float z = v + bias;
         ep_store_at(z_rsrc, at_conv, it, z);
         o = act_m(p.act, z);
@@ -1070,7 +1080,7 @@ void conv_mfma_kernel(ConvParams p) {
       const float lin = o + f_skip[f][it];
       if (fa.keeps_z) {
         const __amdgpu_buffer_rsrc_t fz_rsrc = out_rsrc(at_stream(fa.z, so));
-        if (p.dense) {
+        if (dense) {
           ep_store_at(fz_rsrc, at_site, it, lin);
           o = act_m(fa.act, lin);
         } else {
@@ -1092,7 +1102,7 @@ void conv_mfma_kernel(ConvParams p) {
     if (p.sp.delta) {
 #pragma clang fp contract(off)  // the residual is x_corr minus the rounded product, not a fused form
       float y = o;
-      if (p.dense) {
+      if (dense) {
         ep_store_at(out_rsrc(at_stream(p.sp.delta, so)), at_site, it, 0.0f);
       } else if (sp_k > 0.0f) {
         const float x_corr = sp_delta[it] + o;
@@ -1143,7 +1153,7 @@ void conv_mfma_kernel(ConvParams p) {
     // per lane; otherwise the first of the four lanes writes the tile's own word.
     const int set = tid >> 2, part = tid & 3;
     // S of the producer as seen by this workgroup's rows and channels
-    uint64_t s_prev = p.dense ? touched_word : nz_word(0);
+    uint64_t s_prev = dense ? touched_word : nz_word(0);
     uint64_t bits = set == 0 ? s_prev : (set == 1 && wg_co == 0) ? touched_word : 0ull;
     uint64_t* words = set == 0 ? p.occ_out : set == 1 ? p.occ_touched : nullptr;
 #pragma unroll
@@ -1152,7 +1162,7 @@ void conv_mfma_kernel(ConvParams p) {
       const FusedAdd& fa = p.fused[f];
       const uint64_t t_f = s_prev | skip_word[f];  // Eq.11b
       const uint64_t nz_f = nz_word(1 + f);
-      const uint64_t s_f = (fa.structural || p.dense) ? t_f : nz_f;
+      const uint64_t s_f = (fa.structural || dense) ? t_f : nz_f;
       if (set == 2 + 2 * f) { bits = t_f; words = fa.occ_touched; }
       if (set == 3 + 2 * f) { bits = s_f; words = fa.occ_out; }
       s_prev = s_f;
@@ -1160,7 +1170,7 @@ void conv_mfma_kernel(ConvParams p) {
     if (p.sp.delta) {
       const uint64_t nz_sp = nz_word(1 + kMaxFusedAdds);
       if (set == 2 + 2 * kMaxFusedAdds) { bits = s_prev; words = p.sp.occ_touched; }
-      if (set == 3 + 2 * kMaxFusedAdds) { bits = p.dense ? s_prev : nz_sp; words = p.sp.occ_out; }
+      if (set == 3 + 2 * kMaxFusedAdds) { bits = dense ? s_prev : nz_sp; words = p.sp.occ_out; }
     }
     if (bits && words) {
       words = at_stream(words, so);
