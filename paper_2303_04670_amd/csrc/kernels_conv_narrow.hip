@@ -48,67 +48,80 @@ __device__ __forceinline__ float act_n(int act, float v) {
 template <int MAXE>  // patch elements per thread
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MAXE <= 3 ? 4 : 3))) void conv_narrow_kernel(ConvParams p) {
   touch_params<ConvParams>();
+  asm volatile("" ::"s"(p.gi.h), "s"(p.gi.w), "s"(p.gi.c), "s"(p.gi.tx), "s"(p.gi.ty), "s"(p.go.h), "s"(p.go.w), "s"(p.go.c), "s"(p.go.tx),
+               "s"(p.go.ty), "s"(p.k), "s"(p.stride), "s"(p.pad), "s"(p.dense), "s"(p.occ_in), "s"(p.in), "s"(p.z), "s"(p.out), "s"(p.w),
+               "s"(p.st.stride), "s"(p.tx_magic), "s"(p.k_magic[0]), "s"(p.k_magic[1]), "s"(p.gw_magic[0]));
   const size_t so = (size_t)blockIdx.z * p.st.stride;  // this workgroup's stream
   constexpr int NT = 256;
   extern __shared__ __align__(16) float s_patch[];
-  __shared__ uint64_t s_occ[16];
-  __shared__ unsigned s_rows[24];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int half = wave & 1, cb = wave >> 1;  // this wave: tile rows 4 * half .. + 3, output channels 16 * cb .. + 15
   const int kq = lane >> 4, n16 = lane & 15;               // MFMA operand lane: k = 4 * step + kq; row / column n16
   const int s = p.stride, K = p.k;
   const int H = p.gi.h, W = p.gi.w, Cin = p.gi.c, Cout = p.go.c;
+  const bool dense = p.dense != 0;
   const int P = 7 * s + K;  // patch edge, <= 21
   const int CS = Cin | 1;   // odd LDS site stride
   const int k_tot = K * K * Cin, n_steps = (k_tot + 3) >> 2;
-  const int cin_magic = (65536 + Cin - 1) / Cin;  // e / Cin == (e * cin_magic) >> 16 for e < 3600 (Cin <= 8)
-  const int p_magic = (65536 + P - 1) / P;        // site / P likewise for site < 441
-  const int k_magic = (65536 + K - 1) / K;        // tap / K likewise for tap < 49
-  __shared__ int s_koff[kMaxK];
+  const int cin_magic = p.k_magic[1];  // e / Cin == (e * cin_magic) >> 16 for e < 3600 (Cin <= 8)
+  const int p_magic = p.gw_magic[0];   // site / P likewise for site < 441
+  const int k_magic = p.k_magic[0];    // tap / K likewise for tap < 49
+  __shared__ __align__(16) int s_koff[4][kMaxSteps];  // [k % 4][step]
 
-  // once per workgroup: per step the LDS position of the patch element this lane multiplies for
-  // its site of the first row block (the second block's lies `blk1` further on).  Beyond taps x
-  // c_in it is the position of a zero kept behind the patch: the operand is then an explicit
-  // zero, not a patch element times a zero weight (the element may be infinite or NaN).
+  // once per workgroup: the LDS position of the patch element that operand k multiplies, relative to the
+  // patch origin of the site (the second row block's lies `blk1` further on).  Beyond taps x c_in it is the
+  // position of a zero kept behind the patch: the operand is then an explicit zero, not a patch
+  // element times a zero weight (the element may be infinite or NaN).
   const int zero_at = P * P * CS;
   const int blk1 = 2 * s * P * CS;
   const int site0 = ((4 * half + (n16 >> 3)) * s * P + (n16 & 7) * s) * CS;
   if (tid == 0) s_patch[zero_at] = s_patch[zero_at + blk1] = 0.0f;  // (never overwritten: the patch ends before them)
-  // per patch element of this thread: where it goes in LDS, its bit in the row masks and its
+  if (tid < kMaxK) {
+    const int k = tid;
+    const int tap = (k * cin_magic) >> 16, ci = k - tap * Cin;
+    const int ky = (tap * k_magic) >> 16, kx = tap - ky * K;
+    s_koff[k & 3][k >> 2] = k < k_tot ? (ky * P + kx) * CS + ci : zero_at;
+  }
+  // per patch element of this thread: where it goes in LDS, its place in the rows of bits and its
   // offset in the input relative to the patch origin (the same for every tile)
-  int e_lds[MAXE], e_bit[MAXE], e_goff[MAXE];
+  int e_lds[MAXE], e_row[MAXE], e_px[MAXE], e_goff[MAXE];
   const int total = P * P * Cin;
 #pragma unroll
   for (int j = 0; j < MAXE; ++j) {
     const int e = tid + j * NT;
-    e_lds[j] = -1; e_bit[j] = 0; e_goff[j] = 0;
-    if (e < total) {
-      const int site = (e * cin_magic) >> 16, c = e - site * Cin;
-      const int py = (site * p_magic) >> 16, px = site - py * P;
-      e_lds[j] = site * CS + c;
-      e_bit[j] = py * 32 + px;
-      e_goff[j] = ((py * W + px) * Cin + c) * 4;
-    }
+    const int site = (e * cin_magic) >> 16, c = e - site * Cin;
+    const int py = (site * p_magic) >> 16, px = site - py * P;
+    e_lds[j] = e < total ? site * CS + c : -1;
+    e_row[j] = py * 4;
+    e_px[j] = px;
+    e_goff[j] = (py * (W * Cin) + px * Cin + c) * 4;
   }
   // the weights of this wave's lane, one per step, fetched when the first touched tile is met
   // (a workgroup without one leaves without reading them)
   float wreg[kMaxSteps];
   bool staged = false;
   const int co = blockIdx.y * 32 + cb * 16 + n16;
+  const unsigned site_bytes = (unsigned)Cout * 4u;
+  constexpr unsigned kNowhere = 0x80000000u;  // out of range: loads return 0, stores are dropped
 
+  bool first = true;
   for (int tile = blockIdx.x; tile < p.go.tiles(); tile += gridDim.x) {
-    const int tile_y = tile / p.go.tx, tile_x = tile - tile_y * p.go.tx;
+    const int tile_y = p.tx_magic ? (int)__umulhi((unsigned)tile, p.tx_magic) : tile / p.go.tx, tile_x = tile - tile_y * p.go.tx;
     const int iy0 = tile_y * 8 * s - p.pad, ix0 = tile_x * 8 * s - p.pad;
-    const int rty0 = iy0 >> 3, rtx0 = ix0 >> 3;
-    const int rny = ((iy0 + P - 1) >> 3) - rty0 + 1, rnx = ((ix0 + P - 1) >> 3) - rtx0 + 1;
-    // requests first: the occupancy words under the halo and every element of the patch
-    uint64_t occ_w = 0;
-    if (tid < 16) {
-      const int ry = tid >> 2, rx = tid & 3;
-      const int ty = rty0 + ry, tx = rtx0 + rx;
-      if (ry < rny && rx < rnx && ty >= 0 && ty < p.gi.ty && tx >= 0 && tx < p.gi.tx)
-        occ_w = p.dense ? ~0ull : at_stream(p.occ_in, so)[ty * p.gi.tx + tx];
+    // Requests first: the activity of the region, one row of bits per lane (a byte of each of at most four
+    // occupancy words; for a tile beyond the left or right border a neighbour's byte is read, which is
+    // cut off with the columns outside the image), and every element of the patch.
+    const int rtx0 = ix0 >> 3, iy = iy0 + lane;
+    const bool row_ok = lane < P && (unsigned)iy < (unsigned)H;
+    unsigned row_byte[4];
+    {
+      const __amdgpu_buffer_rsrc_t occ_rsrc =
+          __builtin_amdgcn_make_buffer_rsrc((void*)at_stream(p.occ_in, so), 0, p.gi.ty * p.gi.tx * 8, 0x00020000);
+      const unsigned off = row_ok ? (unsigned)(__mul24(iy >> 3, p.gi.tx) * 8 + (iy & 7)) : kNowhere;
+#pragma unroll
+      for (int rx = 0; rx < 4; ++rx)
+        row_byte[rx] = (unsigned char)__builtin_amdgcn_raw_buffer_load_b8(occ_rsrc, off, min(max(rtx0 + rx, 0), p.gi.tx - 1) * 8, 0);
     }
     const __amdgpu_buffer_rsrc_t in_rsrc =
         __builtin_amdgcn_make_buffer_rsrc((void*)at_stream(p.in, so), 0, H * W * Cin * 4, 0x00020000);
@@ -119,72 +132,51 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MAXE <= 3 ?
     float pre[MAXE];
 #pragma unroll
     for (int j = 0; j < MAXE; ++j) {
-      const unsigned off = e_lds[j] >= 0 ? (unsigned)(origin + e_goff[j]) : 0x80000000u;
+      const unsigned off = e_lds[j] >= 0 ? (unsigned)(origin + e_goff[j]) : kNowhere;
       pre[j] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(in_rsrc, off, 0, 0));
     }
-    __syncthreads();  // the previous tile's masks and patch are no longer in use
-    if (tid < 16) s_occ[tid] = occ_w;
-    __syncthreads();
-    if (tid < P) {  // one bit row per patch row; out-of-image sites are 0
-      const int iy = iy0 + tid;
-      unsigned bits = 0;
-      if ((unsigned)iy < (unsigned)H) {
-        const int ry = (iy >> 3) - rty0;
-        uint64_t span = 0;
-#pragma unroll
-        for (int rx = 0; rx < 4; ++rx) span |= ((s_occ[ry * 4 + rx] >> ((iy & 7) * 8)) & 0xffull) << (8 * rx);
-        bits = (unsigned)(span >> (ix0 - rtx0 * 8));
-        const int lo = max(0, -ix0), hi = min(P, W - ix0);  // valid px in [lo, hi)
-        unsigned m = hi >= 32 ? ~0u : ((1u << max(hi, 0)) - 1u);
-        m &= ~((1u << lo) - 1u);
-        bits &= m;
-      }
-      s_rows[tid] = bits;
-    }
-    __syncthreads();
+    const int lo = max(0, -ix0), hi = min(P, W - ix0);  // valid columns in [lo, hi)
+    const unsigned inside = ((1u << max(hi, 0)) - 1u) & ~((1u << lo) - 1u);  // (lo <= pad, hi <= 21)
+    const unsigned span = row_byte[0] | (row_byte[1] << 8) | (row_byte[2] << 16) | (row_byte[3] << 24);
+    const unsigned bits = (dense ? ~0u : span >> (ix0 - rtx0 * 8)) & (row_ok ? inside : 0u);
 
     uint64_t touched_word;  // whole tile, identical in all waves
     {
       const int ly = lane >> 3, lx = lane & 7;
       const int oy = tile_y * 8 + ly, ox = tile_x * 8 + lx;
-      bool touched = false;
-      if (oy < p.go.h && ox < p.go.w) {
-        unsigned rows = 0;
-        for (int ky = 0; ky < K; ++ky) rows |= s_rows[ly * s + ky];
-        touched = p.dense || ((rows >> (lx * s)) & ((1u << K) - 1u)) != 0;
+      unsigned rows = 0;
+#pragma unroll
+      for (int ky = 0; ky < 7; ++ky) {
+        const unsigned row = (unsigned)__builtin_amdgcn_ds_bpermute((ly * s + ky) * 4, (int)bits);
+        rows |= ky < K ? row : 0u;
       }
-      touched_word = __ballot(touched);
+      touched_word = __ballot((oy < p.go.h) & (ox < p.go.w) & (dense | (((rows >> (lx * s)) & ((1u << K) - 1u)) != 0)));
     }
     if (touched_word == 0) continue;
     const unsigned my_touched = (unsigned)(touched_word >> (32 * half));  // this wave's 32 sites
 
     // accumulator element (block r, register i, lane) = local site 16 * r + 4 * kq + i of the half
     // tile, channel n16 of this wave's 16
+    const unsigned site_bits = co < Cout ? my_touched >> (4 * kq) : 0u;  // bit 16 * r + i
+    // (offsets from the tile's first row, so that outputs of more than 2 GiB are in reach)
+    const size_t row0 = (size_t)(tile_y * 8) * p.go.w * Cout;
+    const int row_bytes = min(8, p.go.h - tile_y * 8) * p.go.w * Cout * 4;
+    const __amdgpu_buffer_rsrc_t z_rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)(at_stream(p.z, so) + row0), 0, row_bytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t o_rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)(at_stream(p.out, so) + row0), 0, row_bytes, 0x00020000);
+    const unsigned out_off = ((unsigned)((4 * half + (kq >> 1)) * p.go.w + tile_x * 8 + 4 * (kq & 1)) * (unsigned)Cout + (unsigned)co) * 4u;
+    const unsigned block_step = 2u * (unsigned)p.go.w * site_bytes;  // two tile rows
+    unsigned at[2][4];
+#pragma unroll
+    for (int r = 0; r < 2; ++r)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) at[r][i] = ((site_bits >> (16 * r + i)) & 1u) ? out_off + (r ? block_step : 0u) + i * site_bytes : kNowhere;
     float z_old[2][4];
 #pragma unroll
     for (int r = 0; r < 2; ++r)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int ls = 16 * r + 4 * kq + i;
-        z_old[r][i] = 0.0f;
-        if (!p.dense && co < Cout && ((my_touched >> ls) & 1u)) {
-          const int oy = tile_y * 8 + 4 * half + (ls >> 3), ox = tile_x * 8 + (ls & 7);
-          z_old[r][i] = at_stream(p.z, so)[((size_t)oy * p.go.w + ox) * Cout + co];
-        }
-      }
+      for (int i = 0; i < 4; ++i)
+        z_old[r][i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(z_rsrc, dense ? kNowhere : at[r][i], 0, 0));
     if (!staged) {
-      // k -> LDS position of the patch element it multiplies, relative to the output site's patch
-      // origin; beyond taps x c_in the position of the zero behind the patch, relative likewise
-      if (tid < kMaxK) {
-        const int k = tid;
-        int off = zero_at;
-        if (k < k_tot) {
-          const int tap = (k * cin_magic) >> 16, ci = k - tap * Cin;
-          const int ky = (tap * k_magic) >> 16, kx = tap - ky * K;
-          off = (ky * P + kx) * CS + ci;
-        }
-        s_koff[k] = off;
-      }
       // re-laid weights: [32-channel group][block of 16][lane][step]: a lane's share is 128 bytes
       const float4* wsrc = (const float4*)((const float*)p.w + (((size_t)blockIdx.y * 2 + cb) * 64 + lane) * kMaxSteps);
 #pragma unroll
@@ -195,10 +187,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MAXE <= 3 ?
       }
       staged = true;
     }
+    if (!first) __syncthreads();  // the previous tile's patch is no longer in use
+    first = false;
     // patch into LDS: inactive and out-of-image sites become zeros
 #pragma unroll
-    for (int j = 0; j < MAXE; ++j)
-      if (e_lds[j] >= 0) s_patch[e_lds[j]] = ((s_rows[e_bit[j] >> 5] >> (e_bit[j] & 31)) & 1u) ? pre[j] : 0.0f;
+    for (int j = 0; j < MAXE; ++j) {
+      const unsigned row = (unsigned)__builtin_amdgcn_ds_bpermute(e_row[j], (int)bits);
+      if (e_lds[j] >= 0) s_patch[e_lds[j]] = ((row >> e_px[j]) & 1u) ? pre[j] : 0.0f;
+    }
     __syncthreads();
     if (my_touched == 0) continue;  // (uniform per wave; the barriers of the next tile are met by all waves)
 
@@ -213,10 +209,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MAXE <= 3 ?
 #pragma unroll
       for (int s0 = 0; s0 < kMaxSteps; s0 += 8) {
         if (s0 >= n_steps) break;
-        int ko[8];
+        const int4 k0 = *(const int4*)&s_koff[kq][s0], k1 = *(const int4*)&s_koff[kq][s0 + 4];
+        const int ko[8] = {k0.x, k0.y, k0.z, k0.w, k1.x, k1.y, k1.z, k1.w};
         float a0[8], a1[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) ko[j] = s_koff[4 * (s0 + j) + kq];
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
           // (the zero behind the patch is addressed absolutely: site0 is taken off again)
@@ -234,35 +229,29 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MAXE <= 3 ?
 
     // epilogue straight from the accumulator registers
     unsigned nz = 0;  // nonzero output sites of this wave (bits of its 32-site half)
+    const float bias = (dense && p.bias && co < Cout) ? p.bias[co] : 0.0f;
+    auto epilogue = [&](auto&& increment) {
 #pragma unroll
-    for (int r = 0; r < 2; ++r)
+      for (int r = 0; r < 2; ++r)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int ls = 16 * r + 4 * kq + i;
-        const int oy = tile_y * 8 + 4 * half + (ls >> 3), ox = tile_x * 8 + (ls & 7);
-        const bool on = ((my_touched >> ls) & 1u) && co < Cout;  // (c_out rounded up to 32: surplus lanes own nothing)
-        float o = 0.0f;
-        if (on) {
-          const size_t e = ((size_t)oy * p.go.w + ox) * Cout + co;
+        for (int i = 0; i < 4; ++i) {
           const float v = r == 0 ? acc0[i] : acc1[i];
-          if (p.dense) {
-            const float z = v + (p.bias ? p.bias[co] : 0.0f);
-            at_stream(p.z, so)[e] = z;
-            o = act_n(p.act, z);
-          } else {
-            const float z_new = z_old[r][i] + v;
-            at_stream(p.z, so)[e] = z_new;
-            o = (p.act == kActNone) ? v : act_n(p.act, z_new) - act_n(p.act, z_old[r][i]);
-          }
-          at_stream(p.out, so)[e] = o;
-        }
-        const uint64_t bal = __ballot(on && o != 0.0f);  // 16 lanes (channels) per site: sites 16 * r + 4 * g + i
+          const float z_new = (dense ? bias : z_old[r][i]) + v;
+          __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(z_new), z_rsrc, at[r][i], 0, 0);
+          const float o = increment(v, z_new, z_old[r][i]);
+          __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(o), o_rsrc, at[r][i], 0, 0);
+          const uint64_t bal = __ballot(at[r][i] != kNowhere && o != 0.0f);  // 16 lanes (channels) per site: sites 16 * r + 4 * g + i
 #pragma unroll
-        for (int g = 0; g < 4; ++g)
-          if ((bal >> (16 * g)) & 0xffffull) nz |= 1u << (16 * r + 4 * g + i);
-      }
+          for (int g = 0; g < 4; ++g) nz |= ((bal >> (16 * g)) & 0xffffull) ? 1u << (16 * r + 4 * g + i) : 0u;
+        }
+    };
+    // regular pass: z = v + bias, o = act(z); incremental: z += v, o = act(z_new) - act(z_old) (z_old reads
+    // as 0 in a regular pass, so ReLU's difference serves both)
+    if (p.act == kActRelu) epilogue([](float, float z1, float z0) { return fmaxf(z1, 0.0f) - fmaxf(z0, 0.0f); });
+    else if (p.act == kActNone) epilogue([&](float v, float z1, float) { return dense ? z1 : v; });
+    else epilogue([&](float, float z1, float z0) { return dense ? act_n(p.act, z1) : act_n(p.act, z1) - act_n(p.act, z0); });
     if (lane == 0) {
-      const uint64_t mine = (uint64_t)(p.dense ? my_touched : nz) << (32 * half);
+      const uint64_t mine = (uint64_t)(dense ? my_touched : nz) << (32 * half);
       if (mine) atomicOr((unsigned long long*)&at_stream(p.occ_out, so)[tile], (unsigned long long)mine);  // pre-zeroed word
       if (blockIdx.y == 0 && cb == 0) {
         const uint64_t t = (uint64_t)my_touched << (32 * half);
@@ -297,8 +286,14 @@ void launch_conv_narrow(const ConvParams& p, hipStream_t s) {
   // workgroups walk the tiles with the grid's stride; enough of them to fill the chip's resident
   // slots (a tile is one chain of dependent memory round trips, so few long walks are slow)
   dim3 grid(std::min(p.go.tiles(), std::max(4096 / p.st.n, 256)), p.c_out_pad / 32, p.st.n);
-  if (P * P * p.gi.c <= 3 * 256) hipLaunchKernelGGL(conv_narrow_kernel<3>, grid, dim3(256), lds, s, p);
-  else hipLaunchKernelGGL(conv_narrow_kernel<kMaxPatchPerThread>, grid, dim3(256), lds, s, p);
+  // divisors of the kernel's index arithmetic (tiles per row: exact while the product fits 32 bits)
+  ConvParams q = p;
+  q.tx_magic = p.go.tx == 1 || (long long)p.go.tiles() * p.go.tx >= (1ll << 32) ? 0u : (unsigned)((0x100000000ull + (unsigned)p.go.tx - 1) / (unsigned)p.go.tx);
+  q.k_magic[0] = (65536 + p.k - 1) / p.k;
+  q.k_magic[1] = (65536 + p.gi.c - 1) / p.gi.c;
+  q.gw_magic[0] = (65536 + P - 1) / P;
+  if (P * P * p.gi.c <= 3 * 256) hipLaunchKernelGGL(conv_narrow_kernel<3>, grid, dim3(256), lds, s, q);
+  else hipLaunchKernelGGL(conv_narrow_kernel<kMaxPatchPerThread>, grid, dim3(256), lds, s, q);
 }
 
 }  // namespace evk
