@@ -150,6 +150,9 @@ constexpr int op_parts(int opm) { return opm == kOpF32 ? 3 : opm == kOpSplit ? 2
 // 4-byte words of a patch site in LDS
 constexpr int patch_site_words(int chunk, int opm) { return chunk / 2 * op_parts(opm) + 4; }
 
+// partial-sum slots of a workgroup in LDS
+constexpr int sum_slots(int nw, int mb) { return mb == 2 ? 4 : nw; }
+
 // The three parts of a value beyond the bf16 rounding range, into bits [shift, shift + 16) of h, m,
 // l.  A finite one: the high part is cut off instead of rounded up to infinity.  An infinity goes
 // into the low part alone: the low part is multiplied with the weight's high part only, which is
@@ -216,6 +219,7 @@ void conv_mfma_kernel(ConvParams p) {
   static_assert(EP_ITERS >= 1 && EP_SITES <= 32, "epilogue mapping");
   constexpr int NACC = MB * 16;  // accumulator registers of a lane
   constexpr int SLOT = NACC * 64;     // floats per partial-sum slot
+  constexpr int SLOTS = sum_slots(NW, MB);
   constexpr int CSL = CHUNK + 4;      // UPS: site stride of the low-resolution fp32 buffer
   constexpr int LPMAX = 10;           // UPS: a 14-row patch has sources in at most 14 / 2 + 3 rows
   constexpr int MAXG = UPS ? (LPMAX * LPMAX * NV + NT - 1) / NT : MAXV;  // gathered float4 per thread
@@ -866,23 +870,29 @@ void conv_mfma_kernel(ConvParams p) {
   }
 
   };
+  // (the arguments of the epilogue, loaded together)
+  asm volatile("" ::"s"(p.out), "s"(p.bias), "s"(p.act), "s"(p.occ_out), "s"(p.occ_touched), "s"(p.sp.delta), "s"(p.fused[0].skip),
+               "s"(p.fused[0].z), "s"(p.fused[0].out), "s"(p.fused[0].occ_out), "s"(p.fused[0].occ_touched), "s"(p.fused[0].act),
+               "s"(p.fused[0].keeps_z), "s"(p.fused[0].structural), "s"(p.fused[1].keeps_z), "s"(p.w_unscale));
   if (!KSP && LATE_Z) request_z();
   if (!KSP) request_fused();
   EVK_PHASE(kPhFusedRequested);
-  // ---- reduce the NW partial sums through LDS: slots [4][block*16 + reg][lane]
+  // ---- reduce the NW partial sums through LDS: slots [SLOTS][block*16 + reg][lane]
   // (fp32 mode: the weights are stored times a power of two, those of the odd waves' units negated;
   // see conv_mfma_negated and ConvParams::w_unscale)
-  const float unscale = (fold ? p.w_fold_unscale : p.w_unscale) * (wave & 1 ? -1.0f : 1.0f) * (pair ? 0.5f : 1.0f);
-  auto spill = [&](float* part, bool last) {
+  const float unscale = (fold ? p.w_fold_unscale : p.w_unscale) * (pair ? 0.5f : 1.0f);
+  auto spill = [&](float* part, float factor) {
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
-      part[i * 64 + lane] = last ? acc0[i] * unscale : acc0[i];
-      if (MB == 2) part[(16 + i) * 64 + lane] = last ? acc1[i] * unscale : acc1[i];
+      part[i * 64 + lane] = PARTS == 3 ? acc0[i] * factor : acc0[i];
+      if (MB == 2) part[(16 + i) * 64 + lane] = PARTS == 3 ? acc1[i] * factor : acc1[i];
     }
   };
   __syncthreads();
-  if (NW == 8) {
-    if (wave >= 4) spill(s_mem + (wave - 4) * SLOT, false);
+  if (SLOTS == NW) {
+    spill(s_mem + wave * SLOT, wave & 1 ? -unscale : unscale);
+  } else {  // (eight waves of whole tiles: in two steps, for the LDS)
+    if (wave >= 4) spill(s_mem + (wave - 4) * SLOT, 1.0f);
     __syncthreads();
     if (wave < 4) {
       const float* part = s_mem + wave * SLOT;
@@ -891,9 +901,9 @@ void conv_mfma_kernel(ConvParams p) {
         acc0[i] += part[i * 64 + lane];
         if (MB == 2) acc1[i] += part[(16 + i) * 64 + lane];
       }
+      spill(s_mem + wave * SLOT, wave & 1 ? -unscale : unscale);
     }
   }
-  if (wave < 4) spill(s_mem + wave * SLOT, PARTS == 3);
   __syncthreads();
   EVK_PHASE(kPhReduced);
 #ifdef EVCONV_PHASE_STAMPS
@@ -921,7 +931,10 @@ void conv_mfma_kernel(ConvParams p) {
   for (int it = 0; it < EP_ITERS; ++it) {
     constexpr int kRow = EP_SITES / 8;  // tile rows per `it`
     const int off = off_mine + (((it * kRow) >> 2) * 16 + ((it * kRow) & 3) * 4) * 64;
-    v_sum[it] = (s_mem[off] + s_mem[off + SLOT]) + (s_mem[off + 2 * SLOT] + s_mem[off + 3 * SLOT]);
+    float part[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) part[q] = SLOTS == 8 ? s_mem[off + q * SLOT] + s_mem[off + (q + 4) * SLOT] : s_mem[off + q * SLOT];
+    v_sum[it] = (part[0] + part[1]) + (part[2] + part[3]);
   }
   if (KSP) {
     if (conv_on) {
@@ -949,17 +962,28 @@ void conv_mfma_kernel(ConvParams p) {
       request_z();
       request_fused();
       asm volatile("" ::: "memory");
-      float add[EP_ITERS];
+      // (all shares in flight, eight at a time: one round trip to memory instead of one per two shares;
+      // those that do not exist are the last one again and not added)
 #pragma unroll
       for (int it = 0; it < EP_ITERS; ++it) v_sum[it] = 0.0f;
-#pragma unroll 2
-      for (int q = 0; q < p.ks; ++q) {
+      auto add_shares = [&](int q0, auto n_tag) {
+        constexpr int N = decltype(n_tag)::value;
+        float add[N][EP_ITERS];
 #pragma unroll
-        for (int it = 0; it < EP_ITERS; ++it)
-          add[it] = __hip_atomic_load(share + (size_t)q * (NSITES * NB) + it * NT, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        for (int q = 0; q < N; ++q)
 #pragma unroll
-        for (int it = 0; it < EP_ITERS; ++it) v_sum[it] += add[it];
-      }
+          for (int it = 0; it < EP_ITERS; ++it)
+            add[q][it] = __hip_atomic_load(share + (size_t)min(q0 + q, p.ks - 1) * (NSITES * NB) + it * NT, __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+        for (int q = 0; q < N; ++q)
+#pragma unroll
+          for (int it = 0; it < EP_ITERS; ++it)
+            if (q0 + q < p.ks) v_sum[it] += add[q][it];
+      };
+      if (p.ks == 2) add_shares(0, std::integral_constant<int, 2>{});
+      else if (p.ks <= 4) add_shares(0, std::integral_constant<int, 4>{});
+      else for (int q0 = 0; q0 < p.ks; q0 += 8) add_shares(q0, std::integral_constant<int, 8>{});
     } else {
       request_z();
       request_fused();
@@ -1222,7 +1246,7 @@ void launch_variant(const ConvParams& p, hipStream_t s) {
   const int PH = (4 * MB - 1) * p.stride + p.k, PW = 7 * p.stride + p.k;
   // (rows of the patch are padded to a pitch of 32 modulo 64 words: at most 64 more per row)
   size_t lds = (size_t)PH * (PW * patch_site_words(CHUNK, OPM) + 64) * sizeof(float);
-  const size_t part = (size_t)4 * MB * 16 * 64 * sizeof(float);  // partial sums reuse the patch
+  const size_t part = (size_t)sum_slots(NW, MB) * MB * 16 * 64 * sizeof(float);  // partial sums reuse the patch
   // The operand that is read by every XCD in full should be the smaller one: the weights of the
   // high-resolution layers, the input of the low-resolution ones (k * k * c_out weights per input
   // channel against one value per stored site per input channel).  Measured on the 32 x 44 -> 64 x
