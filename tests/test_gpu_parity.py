@@ -619,6 +619,37 @@ def test_run_to_run_bit_reproducible(width, h, w):
         np.testing.assert_array_equal(u, v)
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("n_streams", [1, 3])
+def test_outputs_are_fresh_aliases_of_the_same_memory(n_streams):
+    """Every call of outputs() returns tensors of its own over the streams' memory: changing one's
+    shape or autograd state leaves the next call's alone, values written by a step show in all."""
+    import torch
+    net = wl.net_single_conv(5, 16, 24, 40)
+    gpu = ev.EvConvNet(net, n_streams=n_streams)
+    shape = (net.in_c, net.in_h, net.in_w) if n_streams == 1 else (n_streams, net.in_c, net.in_h, net.in_w)
+    gen = torch.Generator().manual_seed(3)
+    gpu.reset(torch.randn(shape, generator=gen).cuda())
+    first = [gpu.outputs(s) for s in range(n_streams)]
+    with torch.inference_mode():
+        gpu.step(torch.randn(shape, generator=gen).cuda())
+        inside = gpu.outputs(0)[0]["y"]
+    second = [gpu.outputs(s) for s in range(n_streams)]
+    ptrs = set()
+    for a, b in zip(first, second):
+        for key in ("y", "dy", "idx", "count"):
+            assert a[0][key] is not b[0][key] and a[0][key].data_ptr() == b[0][key].data_ptr()
+            assert torch.equal(a[0][key], b[0][key])
+        ptrs.add(a[0]["y"].data_ptr())
+    assert len(ptrs) == n_streams and inside.data_ptr() == first[0][0]["y"].data_ptr()
+    first[0][0]["y"].unsqueeze_(0).requires_grad_()
+    third = gpu.outputs(0)[0]["y"]
+    assert not third.requires_grad and tuple(third.shape) == tuple(second[0][0]["y"].shape)
+    third.add_(1.0)
+    assert second[0][0]["y"]._version == 0
+    gpu.destroy()
+
+
 def test_step_before_reset_is_an_error():
     net = wl.net_single_conv(3, c=4, h=8, w=8)
     g = ev.EvConvNet(net)
