@@ -27,14 +27,13 @@ __device__ __forceinline__ float act_p(int act, float v) {
 }
 
 // z read-modify-write and output increment of one (site, channel) element
-__device__ __forceinline__ float finish_element(const ConvParams& p, float* z, float* out, size_t q, int co, float v) {
+__device__ __forceinline__ float finish_element(const ConvParams& p, float* z, float* out, size_t q, int co, float v, float z_old) {
   float o;
   if (p.dense) {
     const float zn = v + (p.bias ? p.bias[co] : 0.0f);
     z[q] = zn;
     o = act_p(p.act, zn);
   } else {
-    const float z_old = z[q];
     const float z_new = z_old + v;
     z[q] = z_new;
     o = (p.act == kActNone) ? v : act_p(p.act, z_new) - act_p(p.act, z_old);
@@ -53,29 +52,25 @@ __device__ __forceinline__ float finish_element(const ConvParams& p, float* z, f
 template <int NOUT, int UNROLL>
 __global__ __launch_bounds__(256) void conv_pointwise_few_kernel(ConvParams p) {
   touch_params<ConvParams>();
-  __shared__ unsigned s_nz[2];
+  asm volatile("" ::"s"(p.go.h), "s"(p.go.w), "s"(p.go.c), "s"(p.go.tx), "s"(p.gi.c), "s"(p.dense), "s"(p.occ_in), "s"(p.in), "s"(p.w), "s"(p.z),
+               "s"(p.out), "s"(p.y), "s"(p.dy), "s"(p.int_mode), "s"(p.act), "s"(p.bias), "s"(p.st.stride), "s"(p.tx_magic));
+  __shared__ unsigned s_nz[4];
   const size_t so = (size_t)blockIdx.z * p.st.stride;  // this workgroup's stream
   const int tid = threadIdx.x;
   const int tile = blockIdx.x;
-  const int tile_y = tile / p.go.tx, tile_x = tile - tile_y * p.go.tx;
+  const bool dense = p.dense != 0;
+  // same geometry in and out: the touched word is the input's occupancy word
+  const uint64_t word = dense ? ~0ull : at_stream(p.occ_in, so)[tile];
+  const int tile_y = p.tx_magic ? (int)__umulhi((unsigned)tile, p.tx_magic) : tile / p.go.tx, tile_x = tile - tile_y * p.go.tx;
   const int site = tid >> 2, q4 = tid & 3;  // site inside the tile, lane inside the site's group of four
   const int oy = tile_y * 8 + (site >> 3), ox = tile_x * 8 + (site & 7);
   const bool inb = oy < p.go.h && ox < p.go.w;
   const int Cin = p.gi.c, Cout = p.go.c;
-  // same geometry in and out: the touched word is the input's occupancy word
-  const uint64_t word = p.dense ? ~0ull : at_stream(p.occ_in, so)[tile];
-  const bool on = inb && ((word >> site) & 1ull);
-  if (tid < 2) s_nz[tid] = 0;
-  // all 256 threads see the same word (one broadcast load each); nothing to do for an empty tile
-  uint64_t touched_word = 0;
-  {
-    // in-bounds mask of the tile, so that dense mode and ragged borders agree with `on`
-    const int rows = min(8, p.go.h - tile_y * 8), cols = min(8, p.go.w - tile_x * 8);
-    const uint64_t rowbits = cols >= 8 ? 0xffull : ((1ull << cols) - 1ull);
-    uint64_t m = 0;
-    for (int r = 0; r < rows; ++r) m |= rowbits << (8 * r);
-    touched_word = word & m;
-  }
+  // in-bounds mask of the tile, so that dense mode and ragged borders agree with `on`
+  const int rows = min(8, p.go.h - tile_y * 8), cols = min(8, p.go.w - tile_x * 8);
+  const uint64_t rowbits = cols >= 8 ? 0xffull : ((1ull << cols) - 1ull);
+  const uint64_t touched_word = word & (rowbits * 0x0101010101010101ull) & (rows >= 8 ? ~0ull : ((1ull << (8 * rows)) - 1ull));
+  const bool on = (touched_word >> site) & 1ull;
   // output node kept by this kernel: public tensors are C x H x W
   const int hw = p.go.h * p.go.w;
   float* const pub_y = p.y ? at_stream(p.y, so) : nullptr;
@@ -86,7 +81,19 @@ __global__ __launch_bounds__(256) void conv_pointwise_few_kernel(ConvParams p) {
       for (int j = 0; j < Cout; ++j) pub_dy[(size_t)j * hw + oy * p.go.w + ox] = 0.0f;
     return;
   }
-  __syncthreads();
+
+  // old values of the elements this thread finishes, requested before the dot products
+  const bool mine = inb && q4 == 0;
+  float* const z = at_stream(p.z, so);
+  float* const out = at_stream(p.out, so);
+  const size_t q0 = ((size_t)oy * p.go.w + ox) * Cout, e0 = (size_t)oy * p.go.w + ox;
+  const bool reads_y = pub_y && (p.int_mode == kIntStep ? on : p.int_mode != kIntReset);
+  float z_old[NOUT], y_old[NOUT];
+#pragma unroll
+  for (int j = 0; j < NOUT; ++j) {
+    z_old[j] = mine && on && !dense && j < Cout ? z[q0 + j] : 0.0f;
+    y_old[j] = mine && reads_y && j < Cout ? pub_y[(size_t)j * hw + e0] : 0.0f;
+  }
 
   float acc[NOUT];
 #pragma unroll
@@ -124,37 +131,39 @@ __global__ __launch_bounds__(256) void conv_pointwise_few_kernel(ConvParams p) {
     acc[j] += __shfl_xor(acc[j], 2);
   }
   bool nz = false;
-  if (inb && q4 == 0) {
-    float* z = at_stream(p.z, so);
-    float* out = at_stream(p.out, so);
-    const size_t q0 = ((size_t)oy * p.go.w + ox) * Cout;
+  if (mine) {
 #pragma unroll
     for (int j = 0; j < NOUT; ++j) {
       if (j >= Cout) break;
       float o = 0.0f;
       if (on) {
-        o = finish_element(p, z, out, q0 + j, j, acc[j]);
+        o = finish_element(p, z, out, q0 + j, j, acc[j], z_old[j]);
         nz |= o != 0.0f;
       }
       if (pub_y) {  // the step's output and its increment, as the stand-alone integration writes them
-        const size_t e = (size_t)j * hw + oy * p.go.w + ox;
+        const size_t e = (size_t)j * hw + e0;
         if (p.int_mode == kIntStep) {
-          if (on) pub_y[e] += o;
+          if (on) pub_y[e] = y_old[j] + o;
           pub_dy[e] = o;
         } else if (p.int_mode == kIntReset) {
           pub_y[e] = o;
           pub_dy[e] = 0.0f;
         } else {
-          pub_dy[e] = o - pub_y[e];
+          pub_dy[e] = o - y_old[j];
           pub_y[e] = o;
         }
       }
     }
   }
-  if (nz) atomicOr(&s_nz[site >> 5], 1u << (site & 31));
+  // a site's bit is that of the first of its four lanes: the wave's 16 bits, four apart, closed up
+  uint64_t b = __ballot(nz) & 0x1111111111111111ull;
+  b = (b | (b >> 3)) & 0x0303030303030303ull;
+  b = (b | (b >> 6)) & 0x000f000f000f000full;
+  b = (b | (b >> 12)) & 0x000000ff000000ffull;
+  if ((tid & 63) == 0) s_nz[tid >> 6] = (unsigned)(b | (b >> 24)) & 0xffffu;
   __syncthreads();
   if (tid == 0) {
-    const uint64_t s_out = p.dense ? touched_word : ((uint64_t)s_nz[0] | ((uint64_t)s_nz[1] << 32));
+    const uint64_t s_out = dense ? touched_word : (s_nz[0] | (s_nz[1] << 16)) | ((uint64_t)(s_nz[2] | (s_nz[3] << 16)) << 32);
     at_stream(p.occ_out, so)[tile] = s_out;       // this workgroup is the tile's only writer
     at_stream(p.occ_touched, so)[tile] = touched_word;
   }
@@ -172,12 +181,24 @@ __global__ __launch_bounds__(256) void linear_site_kernel(ConvParams p) {
   if (!active || co >= Cout) return;  // uniform per wavefront
   const float* __restrict__ x = at_stream(p.in, so);
   const float* __restrict__ w = (const float*)p.w + (size_t)co * Cin;  // [c_out][c_in]
+  const float z_old = lane == 0 && !p.dense ? at_stream(p.z, so)[co] : 0.0f;  // (requested before the dot product)
   float acc = 0.0f;
-  for (int c = lane; c < Cin; c += 64) acc = fmaf(x[c], w[c], acc);
+  for (int c = lane; c < Cin; c += 8 * 64) {  // eight pieces in flight (beyond c_in: the last one again, not added)
+    float xv[8], wv[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int ci = min(c + 64 * i, Cin - 1);
+      xv[i] = x[ci];
+      wv[i] = w[ci];
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      if (c + 64 * i < Cin) acc = fmaf(xv[i], wv[i], acc);
+  }
 #pragma unroll
   for (int m = 1; m < 64; m <<= 1) acc += __shfl_xor(acc, m);
   if (lane == 0) {
-    const bool nz = finish_element(p, at_stream(p.z, so), at_stream(p.out, so), (size_t)co, co, acc) != 0.0f;
+    const bool nz = finish_element(p, at_stream(p.z, so), at_stream(p.out, so), (size_t)co, co, acc, z_old) != 0.0f;
     // pre-zeroed words; the wavefronts of one launch OR their share in
     if (p.dense || nz) atomicOr((unsigned long long*)at_stream(p.occ_out, so), 1ull);
     if (co == 0) at_stream(p.occ_touched, so)[0] = 1ull;
@@ -194,7 +215,11 @@ bool conv_pointwise_supported(const ConvParams& p) {
   return p.go.c <= kMaxFew || (p.go.h == 1 && p.go.w == 1);
 }
 
-void launch_conv_pointwise(const ConvParams& p, hipStream_t s) {
+void launch_conv_pointwise(const ConvParams& q, hipStream_t s) {
+  ConvParams p = q;
+  // tiles per row as a factor (exact while the product fits 32 bits)
+  p.tx_magic = p.go.tx == 1 || (long long)p.go.tiles() * p.go.tx >= (1ll << 32)
+                   ? 0u : (unsigned)((0x100000000ull + (unsigned)p.go.tx - 1) / (unsigned)p.go.tx);
   if (p.go.h == 1 && p.go.w == 1 && p.go.c > kMaxFew)
     hipLaunchKernelGGL(linear_site_kernel, dim3((p.go.c + 3) / 4, 1, p.st.n), dim3(256), 0, s, p);
   else {
