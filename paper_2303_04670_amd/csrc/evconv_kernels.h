@@ -204,6 +204,7 @@ struct EwParams {
   int k, stride, pad;       // pooling window
   const float* step;        // sparsification layer: device scalar, the rounding step k
   int vec_per_block;        // channel vectors per workgroup, set by the launcher
+  unsigned tx_magic;        // tiles per row as a factor (ceil(2^32 / tx), or 0), set by the launcher
   Streams st;
 };
 void launch_elementwise(const EwParams& p, hipStream_t s);

@@ -284,141 +284,167 @@ template <int VEC> __device__ __forceinline__ VecT<VEC> zerov() {
   return r;
 }
 
-template <int VEC>
+// One row of bits per lane: bit x of lane y's row is site (y0 + y, x0 + x) of a tensor with these words,
+// n_rows <= 24 rows of n_cols <= 24 columns; sites outside the image are zero bits.  A row is a byte of
+// each of at most four words (for a tile beyond the left or right border a neighbour's byte is read,
+// and cut off with the columns outside the image).
+__device__ __forceinline__ unsigned occ_rows(const uint64_t* occ, const Geo& g, int y0, int x0, int n_rows, int n_cols) {
+  const int lane = threadIdx.x & 63, y = y0 + lane, tx0 = x0 >> 3;
+  const bool row_ok = lane < n_rows && (unsigned)y < (unsigned)g.h;
+  const unsigned char* const bytes = (const unsigned char*)occ + (row_ok ? (size_t)(y >> 3) * g.tx * 8 + (y & 7) : 0);
+  unsigned b[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) b[i] = bytes[min(max(tx0 + i, 0), g.tx - 1) * 8];
+  const int lo = max(0, -x0), hi = min(n_cols, g.w - x0);
+  const unsigned inside = ((1u << max(hi, 0)) - 1u) & ~((1u << lo) - 1u);
+  return row_ok ? ((b[0] | (b[1] << 8) | (b[2] << 16) | (b[3] << 24)) >> (x0 - tx0 * 8)) & inside : 0u;
+}
+__device__ __forceinline__ unsigned row_of_lane(unsigned rows, int lane) {
+  return (unsigned)__builtin_amdgcn_ds_bpermute(lane * 4, (int)rows);
+}
+
+// The operator and the elements of a thread (N, known at compile time) leave no loop and no branch on
+// the way: all loads of a thread are in flight together, and no wave waits for another before its
+// last step.  With the operator looked up per element and a list of the touched sites in LDS, a tile
+// was a chain of up to four round trips (concatenation of an up-sampled tensor, 16 x 16 to 256 x 256: 5.8 /
+// 7.4 / 8.4 / 9.8 us, now 4.9 / 6.0 / 7.0 / 9.1; 5 + 64 channels on 256 x 352 15.4, now 10.2; max-pool of ResNet-18, two
+// launches, 10.9, now 7.7).
+// Element `it` of a thread is (site e / cv, vector e % cv), e = tid + it * 256, of the tile's 64 sites.
+template <int OP, int VEC, int N>
 __global__ __launch_bounds__(256) void elementwise_kernel(EwParams p) {
   touch_params<EwParams>();
-  {
-    const size_t so = (size_t)blockIdx.z * p.st.stride;
-    p.a = at_stream(p.a, so); p.occ_a = at_stream(p.occ_a, so);
-    p.b = at_stream(p.b, so); p.occ_b = at_stream(p.occ_b, so);
-    p.z = at_stream(p.z, so); p.z2 = at_stream(p.z2, so); p.out = at_stream(p.out, so);
-    p.occ_out = at_stream(p.occ_out, so); p.occ_touched = at_stream(p.occ_touched, so);
-    p.step = at_stream(p.step, so);
-  }
-  __shared__ int s_sites[64];
-  __shared__ unsigned char s_src[64];  // upsample: which of the four source sites are active
-  __shared__ unsigned s_flags[2];
-  __shared__ uint64_t s_word, s_wa, s_wb;
-  const int tid = threadIdx.x;
+  const size_t so = (size_t)blockIdx.z * p.st.stride;
+  const float* const pa = at_stream(p.a, so);
+  const float* const pb = at_stream(p.b, so);
+  float* const pz = at_stream(p.z, so);
+  float* const pz2 = at_stream(p.z2, so);
+  float* const pout = at_stream(p.out, so);
+  const bool dense = p.dense != 0;
+  constexpr bool TWO = OP == kEwAdd || OP == kEwConcat || OP == kEwMul;
+  constexpr bool UP = OP == kEwUp2x || OP == kEwConcatUp;
+  const int tid = threadIdx.x, lane = tid & 63;
   const int tile = blockIdx.x;
-  const int tile_y = tile / p.go.tx, tile_x = tile - tile_y * p.go.tx;
+  const int tile_y = p.tx_magic ? (int)__umulhi((unsigned)tile, p.tx_magic) : tile / p.go.tx, tile_x = tile - tile_y * p.go.tx;
 
-  if (tid < 64) {
-    const int ly = tid >> 3, lx = tid & 7;
-    const int oy = tile_y * 8 + ly, ox = tile_x * 8 + lx;
-    const bool inb = oy < p.go.h && ox < p.go.w;
-    bool t = false;
-    uint64_t wa = 0, wb = 0;
-    unsigned src = 15;
-    if (p.dense) {
-      t = inb;
-      wa = wb = ~0ull;
-    } else if (p.op == kEwAdd || p.op == kEwConcat || p.op == kEwMul) {
-      wa = p.occ_a[tile];
-      wb = p.occ_b[tile];
-      t = ((wa | wb) >> tid) & 1ull;
-    } else if (p.op == kEwAct || p.op == kEwPoolAcc || p.op == kEwSparsify) {
-      wa = p.occ_a[tile];
-      t = (wa >> tid) & 1ull;
-    } else if (p.op == kEwUp2x || p.op == kEwConcatUp) {
-      src = 0;
-      if (p.op == kEwConcatUp) wb = p.occ_b[tile];
-      if (inb) {
-        const int iy = oy >> 1, ix = ox >> 1;
-        const int y0 = (oy & 1) ? iy : max(iy - 1, 0), y1 = (oy & 1) ? min(iy + 1, p.ga.h - 1) : iy;
-        const int x0 = (ox & 1) ? ix : max(ix - 1, 0), x1 = (ox & 1) ? min(ix + 1, p.ga.w - 1) : ix;
-        src = (unsigned)occ_bit(p.occ_a, p.ga.tx, y0, x0) | ((unsigned)occ_bit(p.occ_a, p.ga.tx, y0, x1) << 1) |
-              ((unsigned)occ_bit(p.occ_a, p.ga.tx, y1, x0) << 2) | ((unsigned)occ_bit(p.occ_a, p.ga.tx, y1, x1) << 3);
-        t = src != 0 || (p.op == kEwConcatUp && ((wb >> tid) & 1ull));
-      }
-    } else {  // kEwPoolMax: windows that contain an active input site
-      if (inb) {
-        for (int ky = 0; ky < p.k; ++ky) {
-          const int iy = oy * p.stride - p.pad + ky;
-          if ((unsigned)iy >= (unsigned)p.ga.h) continue;
-          for (int kx = 0; kx < p.k; ++kx) {
-            const int ix = ox * p.stride - p.pad + kx;
-            if ((unsigned)ix >= (unsigned)p.ga.w) continue;
-            t |= occ_bit(p.occ_a, p.ga.tx, iy, ix);
-          }
-        }
-      }
+  // the tile's touched word and the operands' active sites, in every wave
+  const int rows = min(8, p.go.h - tile_y * 8), cols = min(8, p.go.w - tile_x * 8);
+  const uint64_t inb = ((cols >= 8 ? 0xffull : ((1ull << cols) - 1ull)) * 0x0101010101010101ull) &
+                       (rows >= 8 ? ~0ull : ((1ull << (8 * rows)) - 1ull));
+  uint64_t word, wa = ~0ull, wb = ~0ull;
+  unsigned src_rows = 0;  // UP: activity of the stored sites under the tile, from (tile_y * 4 - 1, tile_x * 4 - 1) on
+  if (TWO) {
+    if (!dense) {
+      wa = at_stream(p.occ_a, so)[tile];
+      wb = at_stream(p.occ_b, so)[tile];
     }
-    s_src[tid] = (unsigned char)src;
-    const uint64_t word = __ballot(t);
-    if (t) s_sites[__popcll(word & ((1ull << tid) - 1))] = tid;
-    if (tid == 0) { s_word = word; s_wa = wa; s_wb = wb; s_flags[0] = 0; s_flags[1] = 0; }
+    word = dense ? inb : wa | wb;
+  } else if (UP) {
+    if (OP == kEwConcatUp && !dense) wb = at_stream(p.occ_b, so)[tile];
+    src_rows = occ_rows(at_stream(p.occ_a, so), p.ga, tile_y * 4 - 1, tile_x * 4 - 1, 6, 6);
+    const int ly = lane >> 3, lx = lane & 7;
+    const int y0 = (ly + 1) >> 1, x0 = (lx + 1) >> 1;  // (rows and columns y0 and y0 + 1 of the region; outside the image: zero bits)
+    const unsigned r = row_of_lane(src_rows, y0) | row_of_lane(src_rows, y0 + 1);
+    word = __ballot(((r >> x0) & 3u) != 0);
+    if (OP == kEwConcatUp) word |= wb;
+    word = dense ? inb : word & inb;
+  } else if (OP == kEwPoolMax) {  // windows that contain an active input site
+    const int P = 7 * p.stride + p.k;
+    const unsigned in_rows = occ_rows(at_stream(p.occ_a, so), p.ga, tile_y * 8 * p.stride - p.pad, tile_x * 8 * p.stride - p.pad, P, P);
+    const int ly = lane >> 3, lx = lane & 7;
+    unsigned r = 0;
+#pragma unroll
+    for (int ky = 0; ky < 7; ++ky) {
+      const unsigned v = row_of_lane(in_rows, ly * p.stride + ky);
+      r |= ky < p.k ? v : 0u;
+    }
+    word = __ballot(((r >> (lx * p.stride)) & ((1u << p.k) - 1u)) != 0);
+    word = dense ? inb : word & inb;
+  } else {
+    word = dense ? inb : at_stream(p.occ_a, so)[tile];
   }
-  __syncthreads();
-  const uint64_t word = s_word;
   if (word == 0) return;
-  const uint64_t wa = s_wa, wb = s_wb;
-  const int n_sites = __popcll(word);
+
   const int C = p.go.c;
   // channel vectors [v0, v0 + cv) of every touched site belong to this workgroup
-  const int cv_all = C / VEC;
-  const int v0 = blockIdx.y * p.vec_per_block;
-  const int cv = min(p.vec_per_block, cv_all - v0);
-  const int total = n_sites * cv;
+  const int v0 = blockIdx.y * p.vec_per_block, cv = min(p.vec_per_block, C / VEC - v0);
   const int cv_magic = (65536 + cv - 1) / cv;  // e / cv == (e * cv_magic) >> 16 for e < 1024 (cv <= 16)
+  int site[N], c[N];
+  size_t q[N];
+  bool on[N];
+#pragma unroll
+  for (int it = 0; it < N; ++it) {
+    const int e = tid + it * 256, r = __umul24(e, cv_magic) >> 16;
+    site[it] = r & 63;
+    c[it] = (v0 + (e - __umul24(r, cv))) * VEC;
+    on[it] = r < 64 && ((word >> site[it]) & 1ull);
+    q[it] = (size_t)(tile_y * 8 + (site[it] >> 3)) * p.go.w + (tile_x * 8 + (site[it] & 7));
+  }
 
-  // sites at which this thread produced a nonzero element; the waves' ORs meet in LDS afterwards
-  // (one LDS atomic per element would be served lane by lane where the lanes share a site)
-  uint64_t nz_sites = 0;
-  for (int e = tid; e < total; e += 256) {
-    const int r = __umul24(e, cv_magic) >> 16, v = v0 + (e - __umul24(r, cv));
-    const int site = s_sites[r];
-    const int oy = tile_y * 8 + (site >> 3), ox = tile_x * 8 + (site & 7);
-    const size_t q = (size_t)oy * p.go.w + ox;
-    const int c = v * VEC;
-    VecT<VEC> lin, lin_b;
-    if (p.op == kEwMul) {  // the two factors' increments (full values in a regular forward pass)
-      const bool on_a = (wa >> site) & 1ull, on_b = (wb >> site) & 1ull;
-      lin = on_a ? ldv<VEC>(&p.a[q * C + c]) : zerov<VEC>();
-      lin_b = on_b ? ldv<VEC>(&p.b[q * C + c]) : zerov<VEC>();
-    } else if (p.op == kEwAdd) {
-      const bool on_a = (wa >> site) & 1ull, on_b = (wb >> site) & 1ull;
-      const VecT<VEC> va = on_a ? ldv<VEC>(&p.a[q * C + c]) : zerov<VEC>();
-      const VecT<VEC> vb = on_b ? ldv<VEC>(&p.b[q * C + c]) : zerov<VEC>();
+  // ---- loads: the operands' increments (full values in a regular forward pass) and the old state
+  VecT<VEC> lin[N], lin_b[N], z_old[N], z2_old[N];
 #pragma unroll
-      for (int i = 0; i < VEC; ++i) lin.v[i] = va.v[i] + vb.v[i];
-    } else if (p.op == kEwAct || p.op == kEwPoolAcc || p.op == kEwSparsify) {
-      lin = ldv<VEC>(&p.a[q * C + c]);
-    } else if (p.op == kEwConcat) {
-      const bool on_a = (wa >> site) & 1ull, on_b = (wb >> site) & 1ull;
-      const int ca = p.ga.c, cb = p.gb.c;
-      if (VEC == 4) {  // c_a % 4 == 0: a vector never straddles the two inputs
-        lin = c < ca ? (on_a ? ldv<VEC>(&p.a[q * ca + c]) : zerov<VEC>())
-                     : (on_b ? ldv<VEC>(&p.b[q * cb + c - ca]) : zerov<VEC>());
-      } else {
+  for (int it = 0; it < N; ++it) {
+    const bool on_a = on[it] && ((wa >> site[it]) & 1ull), on_b = on[it] && ((wb >> site[it]) & 1ull);
+    lin_b[it] = zerov<VEC>();
+    if (OP == kEwMul || OP == kEwAdd) {
+      lin[it] = on_a ? ldv<VEC>(&pa[q[it] * C + c[it]]) : zerov<VEC>();
+      lin_b[it] = on_b ? ldv<VEC>(&pb[q[it] * C + c[it]]) : zerov<VEC>();
+    } else if (OP == kEwConcat) {
+      const int ca = p.ga.c, cb = p.gb.c;  // (VEC 4: c_a % 4 == 0, a vector never straddles the two inputs)
+      const bool first = c[it] < ca;
+      lin[it] = (first ? on_a : on_b) ? ldv<VEC>(first ? &pa[q[it] * ca + c[it]] : &pb[q[it] * cb + c[it] - ca]) : zerov<VEC>();
+    } else if (OP == kEwAct || OP == kEwPoolAcc || OP == kEwSparsify) {
+      lin[it] = on[it] ? ldv<VEC>(&pa[q[it] * C + c[it]]) : zerov<VEC>();
+    }
+  }
+  constexpr bool STATE = OP == kEwMul || OP == kEwPoolMax || OP == kEwPoolAcc || OP == kEwAdd || OP == kEwAct;
+  const float sp_k = OP == kEwSparsify && !dense ? *at_stream(p.step, so) : 0.0f;
+  const bool reads_z = OP == kEwPoolMax || (OP == kEwSparsify ? sp_k > 0.0f : STATE && !dense && (OP == kEwMul || OP == kEwPoolAcc || p.keeps_z));
+  if (STATE || OP == kEwSparsify) {
 #pragma unroll
-        for (int i = 0; i < VEC; ++i) {
-          const int cc = c + i;
-          lin.v[i] = cc < ca ? (on_a ? p.a[q * ca + cc] : 0.0f) : (on_b ? p.b[q * cb + cc - ca] : 0.0f);
-        }
-      }
-    } else if (p.op == kEwUp2x || (p.op == kEwConcatUp && c < p.ga.c)) {
-      // (kEwConcatUp runs with whole vectors only: c_a % 4 == 0, so a vector is on one side)
-      const int CA = p.ga.c;  // channels of the stored tensor (== C for a bare up-sampling)
+    for (int it = 0; it < N; ++it) z_old[it] = on[it] && reads_z ? ldv<VEC>(&pz[q[it] * C + c[it]]) : zerov<VEC>();
+  }
+  if (OP == kEwMul) {
+#pragma unroll
+    for (int it = 0; it < N; ++it) z2_old[it] = on[it] && !dense ? ldv<VEC>(&pz2[q[it] * C + c[it]]) : zerov<VEC>();
+  }
+  if (UP) {
+    // bilinear x2 of the stored tensor (half-pixel centres, clamped borders): the four sources of a site
+    const int CA = p.ga.c;  // channels of the stored tensor (== C for a bare up-sampling)
+#pragma unroll
+    for (int it = 0; it < N; ++it) {
+      const int ly = site[it] >> 3, lx = site[it] & 7;
+      const int oy = tile_y * 8 + ly, ox = tile_x * 8 + lx;
       const int iy = oy >> 1, ix = ox >> 1;
       const int y0 = (oy & 1) ? iy : max(iy - 1, 0), y1 = (oy & 1) ? min(iy + 1, p.ga.h - 1) : iy;
       const int x0 = (ox & 1) ? ix : max(ix - 1, 0), x1 = (ox & 1) ? min(ix + 1, p.ga.w - 1) : ix;
       const float wy0 = (oy & 1) ? 0.75f : 0.25f, wy1 = 1.0f - wy0;
       const float wx0 = (ox & 1) ? 0.75f : 0.25f, wx1 = 1.0f - wx0;
-      const unsigned src = s_src[site];
-      const VecT<VEC> v00 = (src & 1) ? ldv<VEC>(&p.a[((size_t)y0 * p.ga.w + x0) * CA + c]) : zerov<VEC>();
-      const VecT<VEC> v01 = (src & 2) ? ldv<VEC>(&p.a[((size_t)y0 * p.ga.w + x1) * CA + c]) : zerov<VEC>();
-      const VecT<VEC> v10 = (src & 4) ? ldv<VEC>(&p.a[((size_t)y1 * p.ga.w + x0) * CA + c]) : zerov<VEC>();
-      const VecT<VEC> v11 = (src & 8) ? ldv<VEC>(&p.a[((size_t)y1 * p.ga.w + x1) * CA + c]) : zerov<VEC>();
+      const int by = tile_y * 4 - 1, bx = tile_x * 4 - 1;
+      // (the exchange between lanes stands before the branch: it needs all of them)
+      const unsigned s0 = row_of_lane(src_rows, y0 - by), s1 = row_of_lane(src_rows, y1 - by);
+      const unsigned r0 = dense ? ~0u : s0, r1 = dense ? ~0u : s1;
+      if (OP == kEwConcatUp && c[it] >= CA) {  // the second operand's channels (VEC 4: c_a % 4 == 0, a vector is on one side)
+        const bool on_b = on[it] && ((wb >> site[it]) & 1ull);
+        lin[it] = on_b ? ldv<VEC>(&pb[q[it] * p.gb.c + c[it] - CA]) : zerov<VEC>();
+        continue;
+      }
+      auto source = [&](unsigned row, int y, int x) {
+        return on[it] && ((row >> (x - bx)) & 1u) ? ldv<VEC>(&pa[((size_t)y * p.ga.w + x) * CA + c[it]]) : zerov<VEC>();
+      };
+      const VecT<VEC> v00 = source(r0, y0, x0), v01 = source(r0, y0, x1), v10 = source(r1, y1, x0), v11 = source(r1, y1, x1);
 #pragma unroll
       for (int i = 0; i < VEC; ++i)
-        lin.v[i] = wy0 * (wx0 * v00.v[i] + wx1 * v01.v[i]) + wy1 * (wx0 * v10.v[i] + wx1 * v11.v[i]);
-    } else if (p.op == kEwConcatUp) {  // the second operand's channels
-      const bool on_b = (wb >> site) & 1ull;
-      lin = on_b ? ldv<VEC>(&p.b[q * p.gb.c + c - p.ga.c]) : zerov<VEC>();
-    } else {  // kEwPoolMax: p.a is the accumulated pool input, p.z the cached window maximum
+        lin[it].v[i] = wy0 * (wx0 * v00.v[i] + wx1 * v01.v[i]) + wy1 * (wx0 * v10.v[i] + wx1 * v11.v[i]);
+    }
+  }
+  if (OP == kEwPoolMax) {  // pa is the accumulated pool input, pz the cached window maximum
 #pragma unroll
-      for (int i = 0; i < VEC; ++i) lin.v[i] = -INFINITY;
+    for (int it = 0; it < N; ++it) {
+      const int oy = tile_y * 8 + (site[it] >> 3), ox = tile_x * 8 + (site[it] & 7);
+#pragma unroll
+      for (int i = 0; i < VEC; ++i) lin[it].v[i] = -INFINITY;
+      if (!on[it]) continue;
       if (p.k == 3) {
         // the usual window: nine loads requested together (an out-of-image tap reads the window's
         // centre instead and is left out of the maximum), then the maxima in the same order
@@ -429,132 +455,136 @@ __global__ __launch_bounds__(256) void elementwise_kernel(EwParams p) {
         for (int j = 0; j < 9; ++j) {
           const int iy = oy * p.stride - p.pad + j / 3, ix = ox * p.stride - p.pad + j % 3;
           ok[j] = (unsigned)iy < (unsigned)p.ga.h && (unsigned)ix < (unsigned)p.ga.w;
-          t[j] = ldv<VEC>(&p.a[((size_t)(ok[j] ? iy : cy) * p.ga.w + (ok[j] ? ix : cx)) * C + c]);
+          t[j] = ldv<VEC>(&pa[((size_t)(ok[j] ? iy : cy) * p.ga.w + (ok[j] ? ix : cx)) * C + c[it]]);
         }
 #pragma unroll
         for (int j = 0; j < 9; ++j)
 #pragma unroll
-          for (int i = 0; i < VEC; ++i) lin.v[i] = ok[j] ? fmaxf(lin.v[i], t[j].v[i]) : lin.v[i];
-      } else
-      for (int ky = 0; ky < p.k; ++ky) {
-        const int iy = oy * p.stride - p.pad + ky;
-        if ((unsigned)iy >= (unsigned)p.ga.h) continue;
-        for (int kx = 0; kx < p.k; ++kx) {
-          const int ix = ox * p.stride - p.pad + kx;
-          if ((unsigned)ix >= (unsigned)p.ga.w) continue;
-          const VecT<VEC> t = ldv<VEC>(&p.a[((size_t)iy * p.ga.w + ix) * C + c]);
+          for (int i = 0; i < VEC; ++i) lin[it].v[i] = ok[j] ? fmaxf(lin[it].v[i], t[j].v[i]) : lin[it].v[i];
+      } else {
+        for (int ky = 0; ky < p.k; ++ky) {
+          const int iy = oy * p.stride - p.pad + ky;
+          if ((unsigned)iy >= (unsigned)p.ga.h) continue;
+          for (int kx = 0; kx < p.k; ++kx) {
+            const int ix = ox * p.stride - p.pad + kx;
+            if ((unsigned)ix >= (unsigned)p.ga.w) continue;
+            const VecT<VEC> t = ldv<VEC>(&pa[((size_t)iy * p.ga.w + ix) * C + c[it]]);
 #pragma unroll
-          for (int i = 0; i < VEC; ++i) lin.v[i] = fmaxf(lin.v[i], t.v[i]);
+            for (int i = 0; i < VEC; ++i) lin[it].v[i] = fmaxf(lin[it].v[i], t.v[i]);
+          }
         }
       }
     }
+  }
 
-    float* zq = p.z ? &p.z[q * C + c] : nullptr;
-    if (p.op == kEwPoolAcc) {
-      VecT<VEC> acc = lin;
-      if (!p.dense) {
-        const VecT<VEC> old = ldv<VEC>(zq);
+  // ---- results, state, and the sites at which this thread produced a nonzero element
+  uint64_t nz_sites = 0;
 #pragma unroll
-        for (int i = 0; i < VEC; ++i) acc.v[i] = old.v[i] + lin.v[i];
-      }
-      stv<VEC>(zq, acc);
+  for (int it = 0; it < N; ++it) {
+    if (!on[it]) continue;
+    float* const zq = &pz[q[it] * C + c[it]];
+    VecT<VEC> o = lin[it];
+    if (OP == kEwAdd) {
+#pragma unroll
+      for (int i = 0; i < VEC; ++i) o.v[i] = lin[it].v[i] + lin_b[it].v[i];
+    }
+    if (OP == kEwPoolAcc) {
+      // (a regular pass stores the value as it is: x + 0 is not x for x = -0)
+#pragma unroll
+      for (int i = 0; i < VEC; ++i) o.v[i] = dense ? lin[it].v[i] : z_old[it].v[i] + lin[it].v[i];
+      stv<VEC>(zq, o);
       continue;
     }
-    VecT<VEC> o;
-    bool nz = false;
-    if (p.op == kEwMul) {
+    if (OP == kEwMul) {
       // Eq.15-17: y_inc = (x1acc + x1_inc) * x2_inc + x2acc * x1_inc, then both accumulators
       // advance.  Explicitly rounded operations: no fused multiply-add, so the result is the
       // same single-rounded sequence on any implementation.
-      float* z2q = &p.z2[q * C + c];
-      if (p.dense) {
-        stv<VEC>(zq, lin);
-        stv<VEC>(z2q, lin_b);
-#pragma unroll
-        for (int i = 0; i < VEC; ++i) o.v[i] = lin.v[i] * lin_b.v[i];
-      } else {
 #pragma clang fp contract(off)
-        const VecT<VEC> a1 = ldv<VEC>(zq), a2 = ldv<VEC>(z2q);
-        VecT<VEC> n1, n2;
+      VecT<VEC> n1 = lin[it], n2 = lin_b[it];
 #pragma unroll
-        for (int i = 0; i < VEC; ++i) {
-          n1.v[i] = a1.v[i] + lin.v[i];
-          n2.v[i] = a2.v[i] + lin_b.v[i];
-          const float t1 = n1.v[i] * lin_b.v[i], t2 = a2.v[i] * lin.v[i];
+      for (int i = 0; i < VEC; ++i) {
+        if (dense) {
+          o.v[i] = lin[it].v[i] * lin_b[it].v[i];
+        } else {
+          n1.v[i] = z_old[it].v[i] + lin[it].v[i];
+          n2.v[i] = z2_old[it].v[i] + lin_b[it].v[i];
+          const float t1 = n1.v[i] * lin_b[it].v[i], t2 = z2_old[it].v[i] * lin[it].v[i];
           o.v[i] = t1 + t2;
         }
-        stv<VEC>(zq, n1);
-        stv<VEC>(z2q, n2);
       }
-    } else if (p.op == kEwSparsify) {
+      stv<VEC>(zq, n1);
+      stv<VEC>(&pz2[q[it] * C + c[it]], n2);
+    } else if (OP == kEwSparsify) {
       // Eq.3-8: x_corr = delta + x_inc; y_inc = k floor(0.5 + x_corr / k); delta = x_corr - y_inc
-      const float k = p.dense ? 0.0f : *p.step;
       VecT<VEC> d_new = zerov<VEC>();
-      o = lin;
-      if (k > 0.0f) {
+      if (sp_k > 0.0f) {
 #pragma clang fp contract(off)  // the residual is x_corr minus the rounded product, not a fused form
-        const VecT<VEC> d_old = ldv<VEC>(zq);
 #pragma unroll
         for (int i = 0; i < VEC; ++i) {
           // (an element with a zero increment emits nothing and keeps its residual: |delta| <= k/2)
-          const float x_corr = d_old.v[i] + lin.v[i];
-          const bool moved = lin.v[i] != 0.0f;
-          o.v[i] = moved ? k * floorf(0.5f + x_corr / k) : 0.0f;
-          d_new.v[i] = moved ? x_corr - o.v[i] : d_old.v[i];
+          const float x_corr = z_old[it].v[i] + lin[it].v[i];
+          const bool moved = lin[it].v[i] != 0.0f;
+          o.v[i] = moved ? sp_k * floorf(0.5f + x_corr / sp_k) : 0.0f;
+          d_new.v[i] = moved ? x_corr - o.v[i] : z_old[it].v[i];
         }
       }
-      if (p.dense || k > 0.0f) stv<VEC>(zq, d_new);  // a refresh clears the residual
-    } else if (p.op == kEwPoolMax) {
-      const VecT<VEC> m_old = ldv<VEC>(zq);
-      stv<VEC>(zq, lin);
+      if (dense || sp_k > 0.0f) stv<VEC>(zq, d_new);  // a refresh clears the residual
+    } else if (OP == kEwPoolMax) {
+      stv<VEC>(zq, lin[it]);
 #pragma unroll
-      for (int i = 0; i < VEC; ++i) o.v[i] = p.dense ? lin.v[i] : lin.v[i] - m_old.v[i];
-    } else if (p.keeps_z) {
-      if (p.dense) {
-        stv<VEC>(zq, lin);
+      for (int i = 0; i < VEC; ++i) o.v[i] = dense ? lin[it].v[i] : lin[it].v[i] - z_old[it].v[i];
+    } else if ((OP == kEwAdd || OP == kEwAct) && p.keeps_z) {
+      VecT<VEC> z_new = o;
 #pragma unroll
-        for (int i = 0; i < VEC; ++i) o.v[i] = apply_act(p.act, lin.v[i]);
-      } else {
-        const VecT<VEC> z_old = ldv<VEC>(zq);
-        VecT<VEC> z_new;
-#pragma unroll
-        for (int i = 0; i < VEC; ++i) {
-          z_new.v[i] = z_old.v[i] + lin.v[i];
-          o.v[i] = (p.act == kActNone) ? lin.v[i] : apply_act(p.act, z_new.v[i]) - apply_act(p.act, z_old.v[i]);
+      for (int i = 0; i < VEC; ++i) {
+        const float x = o.v[i];
+        if (dense) {
+          o.v[i] = apply_act(p.act, x);
+        } else {
+          z_new.v[i] = z_old[it].v[i] + x;
+          o.v[i] = (p.act == kActNone) ? x : apply_act(p.act, z_new.v[i]) - apply_act(p.act, z_old[it].v[i]);
         }
-        stv<VEC>(zq, z_new);
       }
-    } else {
-      o = lin;
+      stv<VEC>(zq, z_new);
     }
-    stv<VEC>(&p.out[q * C + c], o);
+    stv<VEC>(&pout[q[it] * C + c[it]], o);
+    bool nz = false;
 #pragma unroll
     for (int i = 0; i < VEC; ++i) nz |= (o.v[i] != 0.0f);
-    if (nz) nz_sites |= 1ull << site;
+    if (nz) nz_sites |= 1ull << site[it];
   }
-  if (p.op == kEwPoolAcc) return;
-  if (!p.structural) {
-    unsigned lo = (unsigned)nz_sites, hi = (unsigned)(nz_sites >> 32);
+  if (OP == kEwPoolAcc) return;
+  if (p.structural || dense) {
+    if (tid == 0 && blockIdx.y == 0) {
+      at_stream(p.occ_out, so)[tile] = word;
+      at_stream(p.occ_touched, so)[tile] = word;
+    }
+    return;
+  }
+  // the waves' ORs meet in LDS (one LDS atomic per element would be served lane by lane where the lanes
+  // share a site)
+  __shared__ uint64_t s_nz[4];
+  unsigned lo = (unsigned)nz_sites, hi = (unsigned)(nz_sites >> 32);
 #pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) {
-      lo |= __shfl_xor(lo, m);
-      hi |= __shfl_xor(hi, m);
-    }
-    if ((tid & 63) == 0) {
-      if (lo) atomicOr(&s_flags[0], lo);
-      if (hi) atomicOr(&s_flags[1], hi);
-    }
+  for (int m = 32; m >= 1; m >>= 1) {
+    lo |= __shfl_xor(lo, m);
+    hi |= __shfl_xor(hi, m);
   }
+  if (lane == 0) s_nz[tid >> 6] = (uint64_t)lo | ((uint64_t)hi << 32);
   __syncthreads();
   if (tid == 0) {
-    const uint64_t flags = (uint64_t)s_flags[0] | ((uint64_t)s_flags[1] << 32);
-    if (p.structural || p.dense) {
-      if (blockIdx.y == 0) p.occ_out[tile] = word;
-    } else if (flags) {
-      atomicOr((unsigned long long*)&p.occ_out[tile], (unsigned long long)flags);  // pre-zeroed word
-    }
-    if (blockIdx.y == 0) p.occ_touched[tile] = word;
+    const uint64_t flags = (s_nz[0] | s_nz[1]) | (s_nz[2] | s_nz[3]);
+    if (flags) atomicOr((unsigned long long*)&at_stream(p.occ_out, so)[tile], (unsigned long long)flags);  // pre-zeroed word
+    if (blockIdx.y == 0) at_stream(p.occ_touched, so)[tile] = word;
   }
+}
+
+template <int OP, int VEC>
+void launch_ew(const EwParams& q, const dim3& grid, hipStream_t s) {
+  const int n = (std::min(q.vec_per_block, q.go.c / VEC) * 64 + 255) / 256;  // elements of a thread
+  if (n <= 1) hipLaunchKernelGGL((elementwise_kernel<OP, VEC, 1>), grid, dim3(256), 0, s, q);
+  else if (n <= 2) hipLaunchKernelGGL((elementwise_kernel<OP, VEC, 2>), grid, dim3(256), 0, s, q);
+  else hipLaunchKernelGGL((elementwise_kernel<OP, VEC, 4>), grid, dim3(256), 0, s, q);
 }
 
 void launch_elementwise(const EwParams& p, hipStream_t s) {
@@ -572,8 +602,14 @@ void launch_elementwise(const EwParams& p, hipStream_t s) {
          (long long)p.go.tiles() * ((cv_all + q.vec_per_block - 1) / q.vec_per_block) * p.st.n < 384)
     q.vec_per_block /= 2;
   dim3 grid(p.go.tiles(), (cv_all + q.vec_per_block - 1) / q.vec_per_block, p.st.n);
-  if (vec4) hipLaunchKernelGGL(elementwise_kernel<4>, grid, dim3(256), 0, s, q);
-  else hipLaunchKernelGGL(elementwise_kernel<1>, grid, dim3(256), 0, s, q);
+  q.tx_magic = p.go.tx == 1 || (long long)p.go.tiles() * p.go.tx >= (1ll << 32)
+                   ? 0u : (unsigned)((0x100000000ull + (unsigned)p.go.tx - 1) / (unsigned)p.go.tx);
+#define EVK_EW(OP) case OP: if (vec4) launch_ew<OP, 4>(q, grid, s); else launch_ew<OP, 1>(q, grid, s); break;
+  switch (p.op) {
+    EVK_EW(kEwAdd) EVK_EW(kEwAct) EVK_EW(kEwConcat) EVK_EW(kEwUp2x) EVK_EW(kEwPoolAcc) EVK_EW(kEwPoolMax) EVK_EW(kEwSparsify)
+    EVK_EW(kEwMul) EVK_EW(kEwConcatUp)
+  }
+#undef EVK_EW
 }
 
 // =============================================================================== global avg pool
