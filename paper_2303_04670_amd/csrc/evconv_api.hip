@@ -117,6 +117,8 @@ struct NodePlan {
   int fused_sp = -1;        // conv node: the SPARSIFY node it executes behind its last epilogue stage
   int n_fused = 0;          // conv node: ADD nodes it executes, in order
   int fused_nodes[kMaxFusedAdds] = {-1, -1};
+  int pair = -1;            // conv node: a later conv of the same input that runs in its launch
+  int paired_into = -1;     // that later conv: the node whose launch it runs in
   int gather_fused_into = -1;  // UPSAMPLE node computed inside the gather of that conv node, never stored
   int upsampled_from = -2;     // conv node: the node (-1: network input) whose x2 up-sampling it reads through
                                // its gather, its in0 being the folded UPSAMPLE node; -2: none
@@ -468,6 +470,59 @@ evconv_status run_pass(evconv_net* net, const float* input, int builder_mode, Pa
     timed_end(timed, -1);
   }
 
+  // arguments of conv node i's launch
+  auto conv_params = [&](int i) {
+    const NodePlan& n = net->L.nodes[i];
+    const evconv_node_desc& d = n.d;
+    const float* a = d.in0 < 0 ? net->dx : net->L.nodes[d.in0].out;
+    const uint64_t* occ_a = d.in0 < 0 ? net->occ_in : net->L.nodes[d.in0].occ;
+    ConvParams p;
+    p.in = a; p.occ_in = occ_a; p.w = n.w; p.bias = n.bias; p.z = n.z; p.out = n.out;
+    p.occ_out = n.occ; p.occ_touched = n.touched; p.gi = n.ga; p.go = n.go; p.c_out_pad = n.c_out_pad;
+    p.k = d.kh; p.stride = d.stride; p.pad = d.pad; p.act = d.act; p.dense = dense;
+    p.n_fused = n.n_fused;
+    p.st = net->st;
+    p.upsample = 0; p.lo_h = 0; p.lo_w = 0;
+    p.tail_units = n.tail_units; p.fp32 = d.wdtype == EVCONV_F32;
+    p.w_unscale = 1.0f / n.w_scale; p.w_fold_unscale = 1.0f / n.w_fold_scale;
+    p.ks = 0; p.ks_chunks = 0;
+    p.ks_part = (float*)(net->ws + net->L.off_ks_part);
+    p.ks_count = (unsigned*)(net->ws + net->L.off_ks_count);
+    p.y = nullptr; p.dy = nullptr; p.int_mode = 0;
+    p.fold_list = n.fold_list; p.w_fold = n.w_fold; p.fold_k = n.fold_k; p.wg_swap = 0;
+    p.fold_base[0] = n.fold_base[0]; p.fold_base[1] = n.fold_base[1];
+    if (n.upsampled_from != -2) {
+      // read the stored low-resolution tensor; p.gi stays the up-sampled geometry
+      const int src = n.upsampled_from;
+      p.in = src < 0 ? net->dx : net->L.nodes[src].out;
+      p.occ_in = src < 0 ? net->occ_in : net->L.nodes[src].occ;
+      const Geo& gl = src < 0 ? net->L.gin : net->L.nodes[src].go;
+      p.upsample = 1; p.lo_h = gl.h; p.lo_w = gl.w;
+    }
+    p.sp = FusedSparsify{};
+    if (n.fused_sp >= 0) {
+      const NodePlan& sp = net->L.nodes[n.fused_sp];
+      p.sp.delta = sp.z; p.sp.out = sp.out; p.sp.occ_out = sp.occ; p.sp.occ_touched = sp.touched; p.sp.step = sp.step;
+    }
+    for (int f = 0; f < kMaxFusedAdds; ++f) p.fused[f] = FusedAdd{};
+    for (int f = 0; f < n.n_fused; ++f) {
+      const NodePlan& a_node = net->L.nodes[n.fused_nodes[f]];
+      // the ADD's other input: the one that is not the previous stage
+      const int prev = f == 0 ? i : n.fused_nodes[f - 1];
+      const int other = a_node.d.in0 == prev ? a_node.d.in1 : a_node.d.in0;
+      FusedAdd& fa = p.fused[f];
+      fa.skip = other < 0 ? net->dx : net->L.nodes[other].out;
+      fa.occ_skip = other < 0 ? net->occ_in : net->L.nodes[other].occ;
+      fa.z = a_node.z; fa.out = a_node.out; fa.occ_out = a_node.occ; fa.occ_touched = a_node.touched;
+      fa.act = a_node.d.act; fa.keeps_z = a_node.keeps_z; fa.structural = a_node.structural;
+    }
+    if (n.integrates) {
+      p.y = n.y; p.dy = n.dy;
+      p.int_mode = int_mode;
+    }
+    return p;
+  };
+
   for (size_t i = 0; i < net->L.nodes.size(); ++i) {
     NodePlan& n = net->L.nodes[i];
     const evconv_node_desc& d = n.d;
@@ -477,6 +532,7 @@ evconv_status run_pass(evconv_net* net, const float* input, int builder_mode, Pa
     const float* bptr = two ? (d.in1 < 0 ? net->dx : net->L.nodes[d.in1].out) : nullptr;
     const uint64_t* occ_b = two ? (d.in1 < 0 ? net->occ_in : net->L.nodes[d.in1].occ) : nullptr;
     if (n.gather_fused_into >= 0) continue;  // exists only inside the consuming conv's gather
+    if (n.paired_into >= 0) continue;        // has run in an earlier conv's launch
     if (n.kernel == kKernDelay) {
       const NodePlan& x = net->L.nodes[d.in0];  // not yet visited in this pass: holds the previous pass's results
       DelayParams p;
@@ -501,49 +557,13 @@ evconv_status run_pass(evconv_net* net, const float* input, int builder_mode, Pa
       case kKernConvMfmaSplit:
       case kKernConvMfmaBf16:
       case kKernConvMfmaF32: {
-        ConvParams p;
-        p.in = a; p.occ_in = occ_a; p.w = n.w; p.bias = n.bias; p.z = n.z; p.out = n.out;
-        p.occ_out = n.occ; p.occ_touched = n.touched; p.gi = n.ga; p.go = n.go; p.c_out_pad = n.c_out_pad;
-        p.k = d.kh; p.stride = d.stride; p.pad = d.pad; p.act = d.act; p.dense = dense;
-        p.n_fused = n.n_fused;
-        p.st = net->st;
-        p.upsample = 0; p.lo_h = 0; p.lo_w = 0;
-        p.tail_units = n.tail_units; p.fp32 = d.wdtype == EVCONV_F32;
-        p.w_unscale = 1.0f / n.w_scale; p.w_fold_unscale = 1.0f / n.w_fold_scale;
-        p.ks = 0; p.ks_chunks = 0;
-        p.ks_part = (float*)(net->ws + net->L.off_ks_part);
-        p.ks_count = (unsigned*)(net->ws + net->L.off_ks_count);
-        p.y = nullptr; p.dy = nullptr; p.int_mode = 0;
-        p.fold_list = n.fold_list; p.w_fold = n.w_fold; p.fold_k = n.fold_k; p.wg_swap = 0;
-        p.fold_base[0] = n.fold_base[0]; p.fold_base[1] = n.fold_base[1];
-        if (n.upsampled_from != -2) {
-          // read the stored low-resolution tensor; p.gi stays the up-sampled geometry
-          const int src = n.upsampled_from;
-          p.in = src < 0 ? net->dx : net->L.nodes[src].out;
-          p.occ_in = src < 0 ? net->occ_in : net->L.nodes[src].occ;
-          const Geo& gl = src < 0 ? net->L.gin : net->L.nodes[src].go;
-          p.upsample = 1; p.lo_h = gl.h; p.lo_w = gl.w;
-        }
-        p.sp = FusedSparsify{};
-        if (n.fused_sp >= 0) {
-          const NodePlan& sp = net->L.nodes[n.fused_sp];
-          p.sp.delta = sp.z; p.sp.out = sp.out; p.sp.occ_out = sp.occ; p.sp.occ_touched = sp.touched; p.sp.step = sp.step;
-        }
-        for (int f = 0; f < kMaxFusedAdds; ++f) p.fused[f] = FusedAdd{};
-        for (int f = 0; f < n.n_fused; ++f) {
-          const NodePlan& a_node = net->L.nodes[n.fused_nodes[f]];
-          // the ADD's other input: the one that is not the previous stage
-          const int prev = f == 0 ? (int)i : n.fused_nodes[f - 1];
-          const int other = a_node.d.in0 == prev ? a_node.d.in1 : a_node.d.in0;
-          FusedAdd& fa = p.fused[f];
-          fa.skip = other < 0 ? net->dx : net->L.nodes[other].out;
-          fa.occ_skip = other < 0 ? net->occ_in : net->L.nodes[other].occ;
-          fa.z = a_node.z; fa.out = a_node.out; fa.occ_out = a_node.occ; fa.occ_touched = a_node.touched;
-          fa.act = a_node.d.act; fa.keeps_z = a_node.keeps_z; fa.structural = a_node.structural;
-        }
-        if (n.integrates) {
-          p.y = n.y; p.dy = n.dy;
-          p.int_mode = int_mode;
+        const ConvParams p = conv_params((int)i);
+        if (n.pair >= 0) {
+          const ConvParams p2 = conv_params(n.pair);
+          if (n.kernel == kKernConvMfmaF32) launch_conv_mfma_f32_pair(p, p2, s);
+          else if (n.kernel == kKernConvMfmaBf16) launch_conv_mfma_bf16_pair(p, p2, s);
+          else launch_conv_mfma_split_pair(p, p2, s);
+          break;
         }
         if (n.kernel == kKernConvMfmaF32) launch_conv_mfma_f32(p, s);
         else if (n.kernel == kKernConvMfmaBf16) launch_conv_mfma_bf16(p, s);
@@ -943,12 +963,43 @@ evconv_status create_impl(const evconv_net_desc* desc, const void* weights, size
   // Fold ADD nodes into the epilogue of the matrix-core conv that produces their later input
   // (residual add + activation, skip adds).  Every buffer of the ADD node is still written.
   const bool fuse = !(net->flags & EVCONV_FLAG_NO_FUSION);
+  // A block's shortcut conv runs in the launch of the block's first conv, which reads the same tensor
+  // (pair_supported says where that keeps both convs' sums as they are).
+  if (fuse) {
+    auto is_mfma = [](const NodePlan& n) {
+      return n.kernel == kKernConvMfmaF32 || n.kernel == kKernConvMfmaBf16 || n.kernel == kKernConvMfmaSplit;
+    };
+    auto probe_of = [&](const NodePlan& n) {
+      ConvParams p = {};
+      p.gi = n.ga; p.go = n.go; p.c_out_pad = n.c_out_pad; p.k = n.d.kh; p.stride = n.d.stride; p.pad = n.d.pad;
+      p.st = net->st; p.tail_units = n.tail_units; p.fp32 = n.d.wdtype == EVCONV_F32;
+      return p;
+    };
+    for (int j = 0; j < (int)L.nodes.size(); ++j) {
+      NodePlan& sc = L.nodes[j];
+      if (!is_mfma(sc) || sc.d.kh != 1) continue;
+      for (int i = 0; i < j && sc.paired_into < 0; ++i) {
+        NodePlan& first = L.nodes[i];
+        if (first.kernel != sc.kernel || first.d.in0 != sc.d.in0 || first.pair >= 0 || first.paired_into >= 0) continue;
+        if (!conv_mfma_pair_supported(probe_of(first), probe_of(sc))) continue;
+        bool delayed_between = false;  // (a DELAY of the shortcut in between must see last step's buffers)
+        for (int dn = i + 1; dn < j; ++dn)
+          if (L.nodes[dn].d.op == EVCONV_OP_DELAY && L.nodes[dn].d.in0 == j) delayed_between = true;
+        if (delayed_between) continue;
+        first.pair = j;
+        sc.paired_into = i;
+      }
+    }
+  }
+  // where in a pass a node is computed
+  auto pos = [&](int i) { return i >= 0 && L.nodes[i].paired_into >= 0 ? L.nodes[i].paired_into : i; };
   if (fuse) {
     for (size_t i = 0; i < L.nodes.size(); ++i) {
       NodePlan& a_node = L.nodes[i];
       if (a_node.d.op != EVCONV_OP_ADD) continue;
-      const int later = a_node.d.in0 > a_node.d.in1 ? a_node.d.in0 : a_node.d.in1;
-      const int other = a_node.d.in0 > a_node.d.in1 ? a_node.d.in1 : a_node.d.in0;
+      const bool in0_later = pos(a_node.d.in0) > pos(a_node.d.in1);
+      const int later = in0_later ? a_node.d.in0 : a_node.d.in1;
+      const int other = in0_later ? a_node.d.in1 : a_node.d.in0;
       if (later < 0 || later == other) continue;
       const int host = L.nodes[later].fused_into >= 0 ? L.nodes[later].fused_into : later;
       NodePlan& c_node = L.nodes[host];
@@ -956,12 +1007,12 @@ evconv_status create_impl(const evconv_net_desc* desc, const void* weights, size
            c_node.kernel != kKernConvMfmaSplit) ||
           c_node.n_fused >= kMaxFusedAdds) continue;
       if (host != later && c_node.fused_nodes[c_node.n_fused - 1] != later) continue;  // chain must be contiguous
-      if (other >= host) continue;  // the other input must exist before the conv runs
+      if (pos(other) >= pos(host)) continue;  // the other input must exist before the conv runs
       // A DELAY node between the conv and the ADD that delays this ADD reads the ADD's buffers as
       // the previous step left them; computed in the conv's epilogue they would already hold
       // this step's values.
       bool delayed_between = false;
-      for (size_t dn = (size_t)host + 1; dn < i; ++dn)
+      for (size_t dn = (size_t)pos(host) + 1; dn < i; ++dn)
         if (L.nodes[dn].d.op == EVCONV_OP_DELAY && L.nodes[dn].d.in0 == (int)i) delayed_between = true;
       if (delayed_between) continue;
       c_node.fused_nodes[c_node.n_fused++] = (int)i;
@@ -986,7 +1037,7 @@ evconv_status create_impl(const evconv_net_desc* desc, const void* weights, size
       }
       if (host < 0 || L.nodes[host].fused_sp >= 0) continue;
       bool delayed_between = false;  // (a DELAY of this layer placed before it must see last step's buffers)
-      for (size_t dn = (size_t)host + 1; dn < i; ++dn)
+      for (size_t dn = (size_t)pos(host) + 1; dn < i; ++dn)
         if (L.nodes[dn].d.op == EVCONV_OP_DELAY && L.nodes[dn].d.in0 == (int)i) delayed_between = true;
       if (delayed_between) continue;
       L.nodes[host].fused_sp = (int)i;

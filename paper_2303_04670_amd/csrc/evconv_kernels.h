@@ -45,10 +45,11 @@ __device__ __forceinline__ T* at_stream(T* q, size_t off) {
 // The first touch of each of their 64-byte lines misses the scalar cache (about 0.45 us: they lie in
 // memory that the host has just written), one line after the other.  Touching all lines together at
 // the start makes that a single miss.
+// (first: byte offset of P in the arguments)
 template <class P>
-__device__ __forceinline__ void touch_params() {
+__device__ __forceinline__ void touch_params(unsigned first = 0) {
   typedef const unsigned __attribute__((address_space(4))) Word;
-  Word* const q = (Word*)__builtin_amdgcn_kernarg_segment_ptr();
+  Word* const q = (Word*)__builtin_amdgcn_kernarg_segment_ptr() + first / 4;
   constexpr int kLast = (int)sizeof(P) / 4 - 1;
   constexpr auto at = [](int line) { return line * 16 < kLast ? line * 16 : kLast; };
   static_assert(sizeof(P) <= 9 * 64, "touch more lines");
@@ -147,6 +148,7 @@ struct ConvParams {
   // gathered sites per row [plain, folded, up-sampled], 2 x 2 blocks per row of an up-sampled patch
   unsigned tx_magic, lo_tx_magic, co_magic;
   int k_magic[2], gw_magic[3], nbx_magic;
+  int grid_x;  // matrix-core kernel only, set by its launcher: workgroups along the grid's x
   float* ks_part; unsigned* ks_count;
   // few-channel pointwise kernel only: the node is a network output and the kernel keeps the
   // public tensors itself (y += increment, dy = increment; C x H x W); null otherwise.
@@ -162,6 +164,11 @@ bool conv_mfma_upsample_supported(const ConvParams& p);
 bool conv_mfma_negated(const ConvParams& p, int tap, int ci);
 void conv_mfma_split_scratch(const ConvParams& p, size_t* part_floats, size_t* counters);
 void launch_conv_mfma_f32(const ConvParams& p, hipStream_t s);
+// two convs of the same input in one launch (all three modes by their own launchers)
+bool conv_mfma_pair_supported(const ConvParams& a, const ConvParams& b);
+void launch_conv_mfma_f32_pair(const ConvParams& a, const ConvParams& b, hipStream_t s);
+void launch_conv_mfma_bf16_pair(const ConvParams& a, const ConvParams& b, hipStream_t s);
+void launch_conv_mfma_split_pair(const ConvParams& a, const ConvParams& b, hipStream_t s);
 // bf16 MFMA variant (increments rounded to bf16 in the gather, bf16 weights, fp32 accumulation)
 bool conv_mfma_bf16_supported(const ConvParams& p);
 void launch_conv_mfma_bf16(const ConvParams& p, hipStream_t s);

@@ -252,9 +252,9 @@ void launch_builder(const BuilderParams& p, hipStream_t s) {
 }
 
 // =============================================================================== elementwise
-// One workgroup per output tile.  Wave 0 derives the tile's touched word and the list of
-// touched sites; then the 256 threads walk (touched site, channel vector) pairs with the
-// channel index fastest, so global accesses are contiguous runs of C floats per site.
+// One workgroup per output tile and slice of the channels.  Every wave derives the tile's touched word;
+// the 256 threads take (site, channel vector) pairs with the channel index fastest, so global accesses
+// are contiguous runs of C floats per site.
 constexpr int kEwVecPerBlock = 16;  // channel vectors per workgroup at most: wide layers split over blockIdx.y
 
 template <int VEC> struct VecT { float v[VEC]; };

@@ -312,23 +312,19 @@ class EvConvNet:
         spans = self._out_spans.get(stream)
         if spans is None:
             # The tensors lie where they are for the life of the net; making a torch tensor of a bare
-            # pointer takes 3-4 us, a view of the workspace 2 us, an alias of an existing tensor less than
-            # 1 us.  Every call returns aliases of its own (`.data`: with a version counter of their
-            # own, too), whose shape, strides or autograd state the caller may change.
-            torch, ws, base = self.torch, self.workspace, stream * self.stream_stride
-            keep = all(o.y for o in self._outs) and not torch.is_inference_mode_enabled()  # (null before the first reset)
-            in_ws = keep and ws is not None and not ws.is_inference()
-            ws_at = ws.data_ptr() - base if in_ws else 0
+            # pointer takes 3-4 us, an alias of an existing tensor less than 1 us.  Every call returns
+            # aliases of its own (`.data`: with a version counter of their own, too), whose shape, strides
+            # or autograd state the caller may change.  (Not views of the workspace tensor: saving one
+            # of those would save all of it.)
+            torch, base, spans = self.torch, stream * self.stream_stride, []
 
             def span(ptr, nbytes, dtype, shape):
-                if in_ws:
-                    return ws[ptr - ws_at:ptr - ws_at + nbytes].view(dtype).view(shape)
                 return torch.as_tensor(_DeviceBytes((ptr or 0) + base, nbytes), device=self.device).view(dtype).view(shape)
-            spans = []
             for o in self._outs:
                 c, h, w = o.c, o.h, o.w
                 spans.append((o.node, span(o.y, c * h * w * 4, torch.float32, (c, h, w)), span(o.dy, c * h * w * 4, torch.float32, (c, h, w)),
                               span(o.dy_idx, h * w * 4, torch.int32, (h * w,)), span(o.dy_count, 4, torch.int32, (1,))))
-            if keep:
+            # (the pointers are null before the first reset; inference tensors are not for later calls)
+            if all(o.y for o in self._outs) and not torch.is_inference_mode_enabled():
                 self._out_spans[stream] = spans
         return [dict(node=node, y=y.data, dy=dy.data, idx=idx.data, count=count.data) for node, y, dy, idx, count in spans]
