@@ -436,9 +436,10 @@ void launch_any(const ConvParams& p, hipStream_t s) {
 
 // A block's first conv (3 x 3, stride 2) and its shortcut (1 x 1, stride 2) read the same tensor and need
 // nothing of each other.  As launches of their own each is a few microseconds of fixed latency with
-// most of the chip idle (ResNet-18, 128 -> 256 channels on 28 x 28: 9.7 and 7.7 us; in one launch PAIR_US).  Only
-// where both take the eight-wave half-tile variant with 64-channel chunks anyway, so that neither's sums
-// change, and at most one splits its channels over workgroups (they would share the scratch).
+// most of the chip idle (ResNet-18, 64 -> 128 channels on 56 x 56 8.3 and 6.8 us, in one launch 8.1; 128 ->
+// 256 on 28 x 28 10.1 and 7.8, now 9.1; 256 -> 512 on 14 x 14 9.6 and 10.8, now 9.8).  Only where both take the
+// eight-wave half-tile variant with 64-channel chunks anyway, so that neither's sums change, and at
+// most one splits its channels over workgroups (they would share the scratch).
 inline bool pairable(const ConvParams& p) {
   if (p.stride != 2 || p.upsample) return false;
   const KSplit r = ksplit_for(p);

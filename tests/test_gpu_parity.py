@@ -1443,6 +1443,87 @@ def test_large_frame_720p():
     _say(f"720p: max rel z err {rep.max_rel_z:.2e}, y err {rep.max_rel_y:.2e}, flips {rep.flips}")
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("c_in,c_out,h,w,wd,streams,one_launch", [
+    (64, 128, 56, 56, wl.WD_F32, 1, True),        # neither conv splits its channels
+    (128, 256, 28, 28, wl.WD_F32, 1, True),       # the first one does
+    (256, 512, 14, 14, wl.WD_F32_SPLIT, 1, True),
+    (64, 64, 27, 31, wl.WD_BF16, 1, True),
+    (128, 48, 21, 9, wl.WD_F32_SPLIT, 3, True),   # c_out that is not whole blocks, several streams
+    (1024, 64, 17, 15, wl.WD_F32, 1, False),      # both would split their channels
+    (96, 128, 28, 28, wl.WD_F32, 1, False),       # channels that are not whole chunks
+    (64, 128, 130, 120, wl.WD_F32, 1, False),     # too many workgroups for the common variant
+])
+def test_shortcut_conv_in_the_first_convs_launch(c_in, c_out, h, w, wd, streams, one_launch):
+    """A stride-2 block whose 1 x 1 shortcut runs in the launch of its first conv: every sum, set and
+    result bit for bit as with separate launches, and fp32 sums against the oracle, through a reset,
+    sparse steps, a dense step and a step without a change."""
+    b = wl._NetBuilder("block", c_in, h, w, c_in + c_out, bias=True, bf16=wd == wl.WD_BF16)
+    first = b.conv(-1, c_out, 3, 2)
+    second = b.conv(first, c_out, 3, 1, act=wl.ACT_NONE)
+    short = b.conv(-1, c_out, 1, 2, 0, act=wl.ACT_NONE)
+    b.simple(wl.OP_ADD, second, short, act=wl.ACT_RELU, out=1)
+    net = wl.with_weight_dtype(b.finish(), wd)
+    one, apart = ev.EvConvNet(net, n_streams=streams), ev.EvConvNet(net, n_streams=streams, flags=ev.FLAG_NO_FUSION)
+    oras = [Oracle(net) for _ in range(streams)]
+    rng = np.random.default_rng(c_in)
+    x0 = rng.standard_normal((streams, c_in, h, w)).astype(np.float32)
+    for g in (one, apart):
+        g.profile_begin(100)
+        g.reset(_dev(x0 if streams > 1 else x0[0]))
+        g.profile_end()
+    assert (one.node_time(short)[1] == 0) == one_launch and apart.node_time(short)[1] == 1
+    for q, o in enumerate(oras):
+        o.reset(x0[q])
+    for share in (None, 0.02, 0.3, 1.0, 0.0, 0.01):
+        if share is not None:
+            d = (rng.standard_normal(x0.shape) * (rng.random((streams, 1, h, w)) < share)).astype(np.float32)
+            for g in (one, apart):
+                g.step(_dev(d if streams > 1 else d[0]))
+            for q, o in enumerate(oras):
+                o.step_increment(d[q])
+        for q, o in enumerate(oras):
+            for i in range(len(net.nodes)):
+                for kind in (ev.STATE_Z, ev.STATE_OCC, ev.STATE_OCC_TOUCHED, ev.STATE_COUNT):
+                    np.testing.assert_array_equal(one.state(i, kind, q), apart.state(i, kind, q), err_msg=f"share {share} node {i} state {kind}")
+                if wd == wl.WD_F32:
+                    z, zr = one.state(i, ev.STATE_Z, q).astype(np.float64), o.z(i)
+                    assert np.abs(z - zr).max() <= 2e-6 * np.abs(zr).max(), f"share {share} node {i} z"
+            for key in ("y", "dy"):
+                np.testing.assert_array_equal(one.outputs(q)[0][key].cpu().numpy(), apart.outputs(q)[0][key].cpu().numpy())
+    one.destroy()
+    apart.destroy()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("c,h,w", [
+    (4, 5, 9),     # one vector per thread
+    (3, 9, 13),    # channels that are not whole vectors
+    (20, 8, 8),    # two vectors per thread, the second one beyond the tile for most
+    (64, 7, 11),   # four vectors per thread
+    (76, 3, 5),    # several workgroups per tile, the last one narrower
+])
+def test_elementwise_operators_by_channel_count(c, h, w):
+    """Up-sampling stored and inside a concatenation, concatenation, sum, product and activation over the
+    numbers of vectors per thread and channel counts that are not whole vectors, on odd sizes."""
+    b = wl._NetBuilder("ew", c, h, w, 7 + c)
+    up = b.simple(wl.OP_UPSAMPLE2X, -1, out=1)
+    two = b.conv(up, 2, 1, 1, 0, act=wl.ACT_NONE)
+    fused = b.simple(wl.OP_UPSAMPLE2X, -1)
+    cat_up = b.simple(wl.OP_CONCAT, fused, two, out=1)
+    cat = b.simple(wl.OP_CONCAT, two, up, out=1)
+    act = b.simple(wl.OP_ACT, up, act=wl.ACT_TANH, out=1)
+    total = b.simple(wl.OP_ADD, up, act, act=wl.ACT_RELU, out=1)
+    b.simple(wl.OP_MUL, up, total, out=1)
+    net = b.finish()
+    assert ev.EvConvNet(net).kernel_name(fused) == "fused_into_concat_gather" and cat_up < cat
+    rng = np.random.default_rng(c)
+    x0 = rng.standard_normal((c, h, w)).astype(np.float32)
+    incs = [(rng.standard_normal((c, h, w)) * (rng.random((1, h, w)) < p)).astype(np.float32) for p in (0.05, 0.0, 1.0, 0.2)]
+    # (a value-pruned set may differ where an increment is rounded to nothing on one side only)
+    run_stream(net, x0, incs, "increment", tol=1e-5, label=f"elementwise {c} x {h} x {w}", max_flips=4)
+
+
 @pytest.mark.parametrize("ci,co,k,s,hw,streams", [
     (128, 64, 3, 1, (8, 8), 1), (192, 40, 3, 1, (17, 9), 1), (448, 32, 3, 1, (9, 7), 1),    # 2, 3, 7 chunks of 64
     (256, 96, 1, 1, (5, 20), 1), (128, 32, 3, 2, (15, 30), 1), (192, 64, 1, 2, (11, 9), 1),  # 1 x 1, stride 2
