@@ -117,6 +117,7 @@ struct NodePlan {
   int fused_sp = -1;        // conv node: the SPARSIFY node it executes behind its last epilogue stage
   int n_fused = 0;          // conv node: ADD nodes it executes, in order
   int fused_nodes[kMaxFusedAdds] = {-1, -1};
+  int head_batch = -1;      // prediction head: the head whose launch it runs in (the last one of its batch)
   int pair = -1;            // conv node: a later conv of the same input that runs in its launch
   int paired_into = -1;     // that later conv: the node whose launch it runs in
   int gather_fused_into = -1;  // UPSAMPLE node computed inside the gather of that conv node, never stored
@@ -533,6 +534,7 @@ evconv_status run_pass(evconv_net* net, const float* input, int builder_mode, Pa
     const uint64_t* occ_b = two ? (d.in1 < 0 ? net->occ_in : net->L.nodes[d.in1].occ) : nullptr;
     if (n.gather_fused_into >= 0) continue;  // exists only inside the consuming conv's gather
     if (n.paired_into >= 0) continue;        // has run in an earlier conv's launch
+    if (n.head_batch >= 0 && n.head_batch != (int)i) continue;  // runs in a later head's launch
     if (n.kernel == kKernDelay) {
       const NodePlan& x = net->L.nodes[d.in0];  // not yet visited in this pass: holds the previous pass's results
       DelayParams p;
@@ -557,6 +559,14 @@ evconv_status run_pass(evconv_net* net, const float* input, int builder_mode, Pa
       case kKernConvMfmaSplit:
       case kKernConvMfmaBf16:
       case kKernConvMfmaF32: {
+        if (n.head_batch == (int)i) {  // the last head of a batch runs all of them
+          ConvParams heads[kMaxHeadBatch];
+          int n_heads = 0;
+          for (int h = 0; h <= (int)i; ++h)
+            if (net->L.nodes[h].head_batch == (int)i) heads[n_heads++] = conv_params(h);
+          launch_conv_pointwise_batch(heads, n_heads, s);
+          break;
+        }
         const ConvParams p = conv_params((int)i);
         if (n.pair >= 0) {
           const ConvParams p2 = conv_params(n.pair);
@@ -989,6 +999,34 @@ evconv_status create_impl(const evconv_net_desc* desc, const void* weights, size
         first.pair = j;
         sc.paired_into = i;
       }
+    }
+  }
+  // Prediction heads whose results nothing in the net reads run together, where the last one of them
+  // stands: their launches need not come between the layers.
+  if (fuse) {
+    std::vector<char> read(L.nodes.size(), 0);
+    for (const NodePlan& n : L.nodes) {
+      if (n.d.in0 >= 0) read[n.d.in0] = 1;
+      if (n.d.in1 >= 0) read[n.d.in1] = 1;
+    }
+    auto variant = [&](const NodePlan& n) {
+      ConvParams p = {};
+      p.go = n.go; p.st = net->st;
+      return conv_pointwise_variant(p);
+    };
+    auto open = [&](int i) {
+      return L.nodes[i].kernel == kKernConvPointwise && L.nodes[i].integrates && !read[i] && L.nodes[i].head_batch < 0;
+    };
+    for (int i = 0; i < (int)L.nodes.size(); ++i) {
+      if (!open(i)) continue;
+      int members[kMaxHeadBatch] = {i}, n = 1;
+      long long tiles = L.nodes[i].go.tiles();
+      for (int j = i + 1; j < (int)L.nodes.size() && n < kMaxHeadBatch; ++j) {
+        if (!open(j) || variant(L.nodes[j]) != variant(L.nodes[i]) || tiles + L.nodes[j].go.tiles() > (1ll << 23)) continue;
+        tiles += L.nodes[j].go.tiles();
+        members[n++] = j;
+      }
+      for (int k = 0; k < n && n > 1; ++k) L.nodes[members[k]].head_batch = members[n - 1];
     }
   }
   // where in a pass a node is computed

@@ -187,6 +187,11 @@ bool conv_pointwise_supported(const ConvParams& p);
 // public tensors (ConvParams::y, dy)
 bool conv_pointwise_integrates(const ConvParams& p);
 void launch_conv_pointwise(const ConvParams& p, hipStream_t s);
+// Up to kMaxHeadBatch convs that the per-tile kernel takes in the same variant (conv_pointwise_variant; the
+// same streams), in one launch
+constexpr int kMaxHeadBatch = 4;
+int conv_pointwise_variant(const ConvParams& p);
+void launch_conv_pointwise_batch(const ConvParams* heads, int n, hipStream_t s);
 // narrow-input variant: taps * c_in <= 128, c_out >= 16; weights re-laid per MFMA lane:
 // conv_narrow_weight_floats(c_out_pad) fp32 values, W[k = tap * c_in + ci][co] at
 // conv_narrow_weight_index(k, co), zeros elsewhere

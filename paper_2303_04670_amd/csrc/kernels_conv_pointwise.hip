@@ -10,6 +10,9 @@
 //   window has no footprint); z read-modify-write, activation increment (Eq.12-14), occupancy
 //   words as in the other convolution kernels.
 // linear_site_kernel: one wavefront per output channel of the single site.
+#include <cstddef>
+#include <type_traits>
+
 #include "evconv_kernels.h"
 
 namespace evk {
@@ -27,7 +30,8 @@ __device__ __forceinline__ float act_p(int act, float v) {
 }
 
 // z read-modify-write and output increment of one (site, channel) element
-__device__ __forceinline__ float finish_element(const ConvParams& p, float* z, float* out, size_t q, int co, float v, float z_old) {
+template <class P>
+__device__ __forceinline__ float finish_element(const P& p, float* z, float* out, size_t q, int co, float v, float z_old) {
   float o;
   if (p.dense) {
     const float zn = v + (p.bias ? p.bias[co] : 0.0f);
@@ -49,15 +53,13 @@ __device__ __forceinline__ float finish_element(const ConvParams& p, float* z, f
 // launches that fill the chip (more than 1024 tiles) need more; those take two, and exactly c_out
 // rows (256 x 352: 16 -> 8 channels 17.9 us before, 25.2 with four pieces, 17.5 with two; 256 -> 5
 // channels 34.6, 38.9, 30.4; 64 x 88, 88 tiles: 512 -> 8 channels 53.7, 25.6, 27.5).
-template <int NOUT, int UNROLL>
-__global__ __launch_bounds__(256) void conv_pointwise_few_kernel(ConvParams p) {
-  touch_params<ConvParams>();
+template <int NOUT, int UNROLL, class P>
+__device__ __forceinline__ void few_tile(const P& p, const int tile) {
   asm volatile("" ::"s"(p.go.h), "s"(p.go.w), "s"(p.go.c), "s"(p.go.tx), "s"(p.gi.c), "s"(p.dense), "s"(p.occ_in), "s"(p.in), "s"(p.w), "s"(p.z),
                "s"(p.out), "s"(p.y), "s"(p.dy), "s"(p.int_mode), "s"(p.act), "s"(p.bias), "s"(p.st.stride), "s"(p.tx_magic));
   __shared__ unsigned s_nz[4];
   const size_t so = (size_t)blockIdx.z * p.st.stride;  // this workgroup's stream
   const int tid = threadIdx.x;
-  const int tile = blockIdx.x;
   const bool dense = p.dense != 0;
   // same geometry in and out: the touched word is the input's occupancy word
   const uint64_t word = dense ? ~0ull : at_stream(p.occ_in, so)[tile];
@@ -169,6 +171,30 @@ __global__ __launch_bounds__(256) void conv_pointwise_few_kernel(ConvParams p) {
   }
 }
 
+template <int NOUT, int UNROLL>
+__global__ __launch_bounds__(256) void conv_pointwise_few_kernel(ConvParams p) {
+  touch_params<ConvParams>();
+  few_tile<NOUT, UNROLL>(p, blockIdx.x);
+}
+
+// Several heads in one launch: workgroups first[i] .. first[i + 1] - 1 are head i's tiles.  Nothing reads a
+// prediction, so the heads of an encoder-decoder's scales need not stand between its layers: four
+// launches of 6.2, 5.2, 5.0 and 6.2 us (32 x 32 to 256 x 256), in one 9.0.
+struct HeadBatch { ConvParams p[kMaxHeadBatch]; int first[kMaxHeadBatch]; int n; };
+template <int NOUT, int UNROLL>
+__global__ __launch_bounds__(256) void conv_pointwise_batch_kernel(HeadBatch q) {
+  int i = 0;
+#pragma unroll
+  for (int j = 1; j < kMaxHeadBatch; ++j)
+    if (j < q.n && (int)blockIdx.x >= q.first[j]) i = j;
+  const unsigned args = (unsigned)(offsetof(HeadBatch, p) + i * sizeof(ConvParams));
+  touch_params<ConvParams>(args);
+  typedef const char __attribute__((address_space(4))) Byte;
+  Byte* const base = (Byte*)__builtin_amdgcn_kernarg_segment_ptr();
+  const int first = *(const int __attribute__((address_space(4)))*)(base + offsetof(HeadBatch, first) + i * sizeof(int));
+  few_tile<NOUT, UNROLL>(*(const ConvParams __attribute__((address_space(4)))*)(base + args), (int)blockIdx.x - first);
+}
+
 // one wavefront per output channel: the lanes stride through c_in (coalesced weight row), then a
 // butterfly adds the 64 partial sums in a fixed order
 __global__ __launch_bounds__(256) void linear_site_kernel(ConvParams p) {
@@ -215,25 +241,63 @@ bool conv_pointwise_supported(const ConvParams& p) {
   return p.go.c <= kMaxFew || (p.go.h == 1 && p.go.w == 1);
 }
 
-void launch_conv_pointwise(const ConvParams& q, hipStream_t s) {
-  ConvParams p = q;
-  // tiles per row as a factor (exact while the product fits 32 bits)
+namespace {
+
+// tiles per row as a factor (exact while the product fits 32 bits)
+ConvParams with_magic(ConvParams p) {
   p.tx_magic = p.go.tx == 1 || (long long)p.go.tiles() * p.go.tx >= (1ll << 32)
                    ? 0u : (unsigned)((0x100000000ull + (unsigned)p.go.tx - 1) / (unsigned)p.go.tx);
-  if (p.go.h == 1 && p.go.w == 1 && p.go.c > kMaxFew)
+  return p;
+}
+
+// calls f(rows, pieces in flight) with the variant that takes p, as compile-time numbers
+template <class F>
+void with_few_variant(const ConvParams& p, F&& f) {
+  using std::integral_constant;
+  const bool many = (long long)p.go.tiles() * p.st.n > 1024;
+  if (p.go.c == 1) f(integral_constant<int, 1>{}, integral_constant<int, 4>{});
+  else if (p.go.c == 2) f(integral_constant<int, 2>{}, integral_constant<int, 4>{});
+  else if (p.go.c <= 4) f(integral_constant<int, 4>{}, integral_constant<int, 4>{});
+  else if (!many) f(integral_constant<int, 8>{}, integral_constant<int, 4>{});
+  else if (p.go.c == 5) f(integral_constant<int, 5>{}, integral_constant<int, 2>{});
+  else if (p.go.c == 6) f(integral_constant<int, 6>{}, integral_constant<int, 2>{});
+  else if (p.go.c == 7) f(integral_constant<int, 7>{}, integral_constant<int, 2>{});
+  else f(integral_constant<int, 8>{}, integral_constant<int, 2>{});
+}
+
+}  // namespace
+
+void launch_conv_pointwise(const ConvParams& q, hipStream_t s) {
+  const ConvParams p = with_magic(q);
+  if (p.go.h == 1 && p.go.w == 1 && p.go.c > kMaxFew) {
     hipLaunchKernelGGL(linear_site_kernel, dim3((p.go.c + 3) / 4, 1, p.st.n), dim3(256), 0, s, p);
-  else {
-    const dim3 grid(p.go.tiles(), 1, p.st.n);
-    const bool many = (long long)p.go.tiles() * p.st.n > 1024;
-    if (p.go.c == 1) hipLaunchKernelGGL((conv_pointwise_few_kernel<1, 4>), grid, dim3(256), 0, s, p);
-    else if (p.go.c == 2) hipLaunchKernelGGL((conv_pointwise_few_kernel<2, 4>), grid, dim3(256), 0, s, p);
-    else if (p.go.c <= 4) hipLaunchKernelGGL((conv_pointwise_few_kernel<4, 4>), grid, dim3(256), 0, s, p);
-    else if (!many) hipLaunchKernelGGL((conv_pointwise_few_kernel<8, 4>), grid, dim3(256), 0, s, p);
-    else if (p.go.c == 5) hipLaunchKernelGGL((conv_pointwise_few_kernel<5, 2>), grid, dim3(256), 0, s, p);
-    else if (p.go.c == 6) hipLaunchKernelGGL((conv_pointwise_few_kernel<6, 2>), grid, dim3(256), 0, s, p);
-    else if (p.go.c == 7) hipLaunchKernelGGL((conv_pointwise_few_kernel<7, 2>), grid, dim3(256), 0, s, p);
-    else hipLaunchKernelGGL((conv_pointwise_few_kernel<8, 2>), grid, dim3(256), 0, s, p);
+    return;
   }
+  with_few_variant(p, [&](auto rows, auto pieces) {
+    hipLaunchKernelGGL((conv_pointwise_few_kernel<decltype(rows)::value, decltype(pieces)::value>), dim3(p.go.tiles(), 1, p.st.n),
+                       dim3(256), 0, s, p);
+  });
+}
+
+int conv_pointwise_variant(const ConvParams& p) {
+  int v = 0;
+  with_few_variant(p, [&](auto rows, auto pieces) { v = rows() * 16 + pieces(); });
+  return v;
+}
+
+void launch_conv_pointwise_batch(const ConvParams* heads, int n, hipStream_t s) {
+  HeadBatch q = {};
+  int blocks = 0;
+  for (int i = 0; i < n; ++i) {
+    q.p[i] = with_magic(heads[i]);
+    q.first[i] = blocks;
+    blocks += heads[i].go.tiles();
+  }
+  q.n = n;
+  with_few_variant(heads[0], [&](auto rows, auto pieces) {
+    hipLaunchKernelGGL((conv_pointwise_batch_kernel<decltype(rows)::value, decltype(pieces)::value>), dim3(blocks, 1, heads[0].st.n),
+                       dim3(256), 0, s, q);
+  });
 }
 
 }  // namespace evk

@@ -1496,6 +1496,52 @@ def test_shortcut_conv_in_the_first_convs_launch(c_in, c_out, h, w, wd, streams,
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("heads,launches,streams", [
+    ([2, 2], [0, 1], 1),
+    ([2, 2, 2, 2, 2], [0, 0, 0, 1, 1], 1),   # more than a batch holds
+    ([1, 3, 1, 4, 8], [0, 0, 1, 1, 1], 2),   # 3 and 4 channels share a variant, 8 stands alone
+])
+def test_prediction_heads_in_one_launch(heads, launches, streams):
+    """Heads that nothing reads run in the launch of the last of their variant: results, sets and public
+    outputs bit for bit as from launches of their own, in regular passes, steps and dense recompute.
+    (A head that another node reads keeps its own launch: the last one of the net here.)"""
+    b = wl._NetBuilder("heads", 4, 43, 29, sum(heads), bias=True)
+    x, at = -1, []
+    for i, c in enumerate(heads):
+        x = b.conv(x, 12 + 8 * i, 3, 2 if i in (1, 3) else 1)
+        at.append(b.conv(x, c, 1, 1, 0, act=(wl.ACT_NONE, wl.ACT_SIGMOID)[i % 2], out=1))
+    own = b.conv(x, 2, 1, 1, 0, act=wl.ACT_NONE, out=1)
+    b.simple(wl.OP_ACT, own, act=wl.ACT_RELU, out=1)
+    net = b.finish()
+    one, apart = ev.EvConvNet(net, n_streams=streams), ev.EvConvNet(net, n_streams=streams, flags=ev.FLAG_NO_FUSION)
+    rng = np.random.default_rng(len(heads))
+    shape = (4, 43, 29) if streams == 1 else (streams, 4, 43, 29)
+    x0 = _dev(rng.standard_normal(shape))
+    for g in (one, apart):
+        g.profile_begin(100)
+        g.reset(x0)
+        g.profile_end()
+    assert [int(one.node_time(i)[1]) for i in at + [own]] == launches + [1]
+    assert all(apart.node_time(i)[1] == 1 for i in at + [own])
+    for share, mode in ((None, 0), (0.02, ev.MODE_INCREMENTAL), (1.0, ev.MODE_INCREMENTAL), (0.0, ev.MODE_INCREMENTAL),
+                        (0.1, ev.MODE_DENSE_RECOMPUTE), (0.05, ev.MODE_INCREMENTAL)):
+        if share is not None:
+            d = _dev(rng.standard_normal(shape) * (rng.random(shape[:-3] + (1, 43, 29)) < share))
+            for g in (one, apart):
+                g.set_mode(mode)
+                g.step(d)
+        for q in range(streams):
+            for i in range(len(net.nodes)):
+                for kind in (ev.STATE_Z, ev.STATE_OCC, ev.STATE_OCC_TOUCHED, ev.STATE_COUNT):
+                    np.testing.assert_array_equal(one.state(i, kind, q), apart.state(i, kind, q), err_msg=f"share {share} node {i} state {kind}")
+            for o, r in zip(one.outputs(q), apart.outputs(q)):
+                for key in ("y", "dy"):
+                    np.testing.assert_array_equal(o[key].cpu().numpy(), r[key].cpu().numpy(), err_msg=f"share {share} node {o['node']} {key}")
+    one.destroy()
+    apart.destroy()
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("c,h,w", [
     (4, 5, 9),     # one vector per thread
     (3, 9, 13),    # channels that are not whole vectors
