@@ -29,8 +29,10 @@
 // through LDS at the end.  K-splitting (rather than N-splitting), 8 waves and half tiles are what
 // spread the low-resolution layers (24-88 tiles) over 256 CUs; the launcher picks MB and NW from
 // the number of workgroups a layer yields.
-//   Masks: the occupancy words of the input tiles under the halo are turned into one bit row per
-//     patch row in LDS; the touched word of the tile and the gather predicates come from those.
+//   Masks: every wave has one bit row per patch row, in the lane of that number (a byte of each of at
+//     most four occupancy words); the touched word of the tile and the gather predicates come from
+//     rows fetched from other lanes (ds_bpermute).  Nothing before the first patch goes through LDS or
+//     waits at a barrier.
 //   A operand: the input halo patch of the current chunk, gathered once per workgroup into LDS
 //     with buffer loads whose offset is pushed out of range for inactive / out-of-image sites:
 //     the hardware bounds check returns zeros without a memory access (conditioned fetch).  The
@@ -55,8 +57,8 @@
 // Vector instructions are kept few throughout: per-lane parts of an address are computed once and
 // kept, per-unit / per-row parts live in scalar registers (buffer instructions with a scalar
 // offset), masks are tested where their bits sit.
-// (This header holds the kernel template and its launchers; one translation unit per operand
-// mode instantiates it, so that the three modes compile in parallel.)
+// (This header holds the kernels and their launchers, conv_mfma_body.h the body of a workgroup; one
+// translation unit per operand mode instantiates them, so that the three modes compile in parallel.)
 #pragma once
 #include <algorithm>
 #include <type_traits>
@@ -76,10 +78,10 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 // define EVK_PHASE expands to nothing.  A record is 32 x u64:
 enum PhaseField {
   kPhStart = 0,            // first instruction of the workgroup
-  kPhOccInLds = 1,         // occupancy words arrived and in LDS (the gather addressing is worked out meanwhile)
+  kPhOccInLds = 1,         // occupancy bytes arrived (the gather addressing is worked out meanwhile)
   kPhBitRows = 2,          // bit rows of the patch built
-  kPhAddressed = 3,        // touched words, old z requested, gather offsets conditioned
-  kPhFirstIssued = 4,      // first patch chunk and first weight fragments requested
+  kPhAddressed = 3,        // first patch chunk requested, touched words, old z requested
+  kPhFirstIssued = 4,      // first weight fragments requested
   kPhFirstPatchInLds = 5,  // first chunk arrived, in LDS (and interpolated), next chunk requested
   kPhChunksDone = 6,       // end of the chunk loop
   kPhFusedRequested = 10,  // operands of the fused stages requested

@@ -18,7 +18,7 @@
 // Workgroups walk tiles with the grid's stride.
 //
 // A tile is one chain of dependent memory round trips, so they are made as few as possible: the
-// occupancy words and the whole halo patch are requested together at the start (the patch
+// occupancy bytes (one row of bits per lane, in every wave) and the whole halo patch are requested together at the start (the patch
 // unconditionally: it is a few KB; inactive and out-of-image sites are zeroed from the masks on
 // the way into LDS), old z values and - once per workgroup - the weights as soon as the tile is
 // known to be touched.  Masks, z read-modify-write, activation increment (Eq.12-14) and
@@ -268,7 +268,8 @@ bool conv_narrow_supported(const ConvParams& p) {
   const int P = 7 * p.stride + p.k;
   return k_tot <= kMaxK && p.gi.c <= 8 && p.go.c >= 16 && p.c_out_pad == (p.go.c + 31) / 32 * 32 && p.n_fused == 0 &&
          P * P * p.gi.c <= kMaxPatchPerThread * 256 &&
-         (long long)p.gi.h * p.gi.w * p.gi.c * 4 < (1ll << 31);  // byte offsets of the gather fit 31 bits
+         (long long)p.gi.h * p.gi.w * p.gi.c * 4 < (1ll << 31) &&  // byte offsets of the gather fit 31 bits,
+         8ll * p.go.w * p.go.c * 4 < (1ll << 31);                  // and those inside a row of output tiles
 }
 
 // re-laid weights: floats for c_out_pad output channels, and the position of W[k][co]
