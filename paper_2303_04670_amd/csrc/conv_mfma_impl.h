@@ -262,6 +262,25 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void c
   conv_workgroup<64, 8, OPM, 1, kPlain, true, 3, true>(args, p.wg_swap ? y : x, p.wg_swap ? x : y, 0, 0, 0);
 }
 
+// Up to four convs of the same tensor and one variant in one launch (see launch_batch): workgroup
+// first[i] is the first of conv i.
+struct ConvBatch { ConvParams p[kMaxConvBatch]; int first[kMaxConvBatch]; int n; };
+template <int OPM>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void conv_mfma_batch_kernel(ConvBatch q) {
+  int i = 0;
+#pragma unroll
+  for (int j = 1; j < kMaxConvBatch; ++j)
+    if (j < q.n && (int)blockIdx.x >= q.first[j]) i = j;
+  const unsigned args = (unsigned)(offsetof(ConvBatch, p) + i * sizeof(ConvParams));
+  touch_params<ConvParams>(args);
+  typedef const char __attribute__((address_space(4))) Byte;
+  Byte* const base = (Byte*)__builtin_amdgcn_kernarg_segment_ptr();
+  const auto& p = *(const ConvParams __attribute__((address_space(4)))*)(base + args);
+  const int wg = (int)blockIdx.x - *(const int __attribute__((address_space(4)))*)(base + offsetof(ConvBatch, first) + i * sizeof(int));
+  const int y = wg / p.grid_x, x = wg - y * p.grid_x;
+  conv_workgroup<32, 4, OPM, 1, kPlain, false, 0, false>(args, p.wg_swap ? y : x, p.wg_swap ? x : y, 0, 0, 0);
+}
+
 inline int chunk_for(const ConvParams& p) {
   // low-resolution layers (few workgroups, always 8 waves): 128-channel chunks halve the number of
   // gather round trips, which is what these latency-bound launches consist of
@@ -464,6 +483,36 @@ void launch_pair(const ConvParams& a, const ConvParams& b, hipStream_t s) {
   const int na = (int)(la.grid.x * la.grid.y), nb = (int)(lb.grid.x * lb.grid.y);
   ConvPair q{la.q, lb.q, na};
   hipLaunchKernelGGL(conv_mfma_pair_kernel<OPM>, dim3(na + nb, 1, a.st.n), dim3(512), std::max(la.lds, lb.lds), s, q);
+}
+
+// The gate convs of a recurrent cell read one tensor.  In one launch the last, partly filled round of
+// workgroups and the start of the next launch come once instead of four times (the four convs of a
+// ConvLSTM cell, 69 -> 64 channels on 256 x 352, fp32: 192 -> 168 us).  For the variant of four-wave half
+// tiles with 32-channel chunks, the one such layers take.  Whole cells, a launch each / one launch, us:
+// fp32, 64 channels on 96 x 88 107 / 89, on 360 x 360 744 / 708, 4 streams on 256 x 352 1206 / 1198; split, 64
+// on 96 x 88 100 / 83, on 256 x 352 381 / 354, on 360 x 360 675 / 662; bf16, 64 on 256 x 352 (5632 workgroups
+// per conv) 327 / 320, on 360 x 360 (8100) 609 / 616: bf16 up to 6144 workgroups, and above those that take
+// the variant for five waves per SIMD.
+inline bool batchable(const ConvParams& p, bool bf16) {
+  if (p.stride != 1 || p.upsample || ksplit_for(p).ks || chunk_for(p) != 32) return false;
+  const long long n2 = (long long)p.go.tiles() * (p.c_out_pad / 32) * p.st.n;
+  const bool halves = !(n2 >= 512 && p.k * p.k * p.gi.c >= 1600) || fill(2 * n2) > fill(n2) + 0.1;
+  return halves && 2 * n2 >= (bf16 ? 2561 : 512) && 2 * n2 <= (bf16 ? 6144 : 1 << 22);
+}
+template <int OPM>
+void launch_batch(const ConvParams* convs, int n, hipStream_t s) {
+  ConvBatch q = {};
+  unsigned blocks = 0;
+  size_t lds = 0;
+  for (int i = 0; i < n; ++i) {
+    const ConvLaunch l = variant_launch<32, 4, OPM, 1, false>(convs[i]);
+    q.p[i] = l.q;
+    q.first[i] = (int)blocks;
+    blocks += l.grid.x * l.grid.y;
+    lds = std::max(lds, l.lds);
+  }
+  q.n = n;
+  hipLaunchKernelGGL(conv_mfma_batch_kernel<OPM>, dim3(blocks, 1, convs[0].st.n), dim3(256), lds, s, q);
 }
 
 // Copies the phase records of this translation unit's kernels to `host` (32 x u64 each, at most

@@ -118,8 +118,10 @@ struct NodePlan {
   int n_fused = 0;          // conv node: ADD nodes it executes, in order
   int fused_nodes[kMaxFusedAdds] = {-1, -1};
   int head_batch = -1;      // prediction head: the head whose launch it runs in (the last one of its batch)
-  int pair = -1;            // conv node: a later conv of the same input that runs in its launch
-  int paired_into = -1;     // that later conv: the node whose launch it runs in
+  int mates[kMaxConvBatch - 1] = {-1, -1, -1};  // conv node: later convs of the same input that run in its launch
+  int n_mates = 0;
+  bool mates_batch = false;  // ... as a batch of one variant (otherwise a shortcut conv)
+  int paired_into = -1;      // such a later conv: the node whose launch it runs in
   int gather_fused_into = -1;  // UPSAMPLE node computed inside the gather of that conv node, never stored
   int upsampled_from = -2;     // conv node: the node (-1: network input) whose x2 up-sampling it reads through
                                // its gather, its in0 being the folded UPSAMPLE node; -2: none
@@ -568,8 +570,16 @@ evconv_status run_pass(evconv_net* net, const float* input, int builder_mode, Pa
           break;
         }
         const ConvParams p = conv_params((int)i);
-        if (n.pair >= 0) {
-          const ConvParams p2 = conv_params(n.pair);
+        if (n.mates_batch) {
+          ConvParams convs[kMaxConvBatch] = {p};
+          for (int m = 0; m < n.n_mates; ++m) convs[1 + m] = conv_params(n.mates[m]);
+          if (n.kernel == kKernConvMfmaF32) launch_conv_mfma_f32_batch(convs, 1 + n.n_mates, s);
+          else if (n.kernel == kKernConvMfmaBf16) launch_conv_mfma_bf16_batch(convs, 1 + n.n_mates, s);
+          else launch_conv_mfma_split_batch(convs, 1 + n.n_mates, s);
+          break;
+        }
+        if (n.n_mates) {
+          const ConvParams p2 = conv_params(n.mates[0]);
           if (n.kernel == kKernConvMfmaF32) launch_conv_mfma_f32_pair(p, p2, s);
           else if (n.kernel == kKernConvMfmaBf16) launch_conv_mfma_bf16_pair(p, p2, s);
           else launch_conv_mfma_split_pair(p, p2, s);
@@ -973,8 +983,9 @@ evconv_status create_impl(const evconv_net_desc* desc, const void* weights, size
   // Fold ADD nodes into the epilogue of the matrix-core conv that produces their later input
   // (residual add + activation, skip adds).  Every buffer of the ADD node is still written.
   const bool fuse = !(net->flags & EVCONV_FLAG_NO_FUSION);
-  // A block's shortcut conv runs in the launch of the block's first conv, which reads the same tensor
-  // (pair_supported says where that keeps both convs' sums as they are).
+  // A block's shortcut conv runs in the launch of the block's first conv, which reads the same tensor, and
+  // the gate convs of a cell in one launch (pair_supported and batchable say where; the sums stay as they
+  // are).
   if (fuse) {
     auto is_mfma = [](const NodePlan& n) {
       return n.kernel == kKernConvMfmaF32 || n.kernel == kKernConvMfmaBf16 || n.kernel == kKernConvMfmaSplit;
@@ -986,18 +997,33 @@ evconv_status create_impl(const evconv_net_desc* desc, const void* weights, size
       return p;
     };
     for (int j = 0; j < (int)L.nodes.size(); ++j) {
-      NodePlan& sc = L.nodes[j];
-      if (!is_mfma(sc) || sc.d.kh != 1) continue;
-      for (int i = 0; i < j && sc.paired_into < 0; ++i) {
+      NodePlan& late = L.nodes[j];
+      if (!is_mfma(late)) continue;
+      for (int i = 0; i < j && late.paired_into < 0; ++i) {
         NodePlan& first = L.nodes[i];
-        if (first.kernel != sc.kernel || first.d.in0 != sc.d.in0 || first.pair >= 0 || first.paired_into >= 0) continue;
-        if (!conv_mfma_pair_supported(probe_of(first), probe_of(sc))) continue;
-        bool delayed_between = false;  // (a DELAY of the shortcut in between must see last step's buffers)
+        if (first.kernel != late.kernel || first.d.in0 != late.d.in0 || first.paired_into >= 0) continue;
+        const ConvParams p = probe_of(first), q = probe_of(late);
+        const bool shortcut = late.d.kh == 1 && first.n_mates == 0 && conv_mfma_pair_supported(p, q);
+        const bool bf16 = late.kernel == kKernConvMfmaBf16;
+        const bool batch = (first.n_mates == 0 || first.mates_batch) && first.n_mates < kMaxConvBatch - 1 &&
+                           conv_mfma_batch_supported(p, bf16) && conv_mfma_batch_supported(q, bf16);
+        if (!shortcut && !batch) continue;
+        bool delayed_between = false;  // (a DELAY of the later one in between must see last step's buffers)
         for (int dn = i + 1; dn < j; ++dn)
           if (L.nodes[dn].d.op == EVCONV_OP_DELAY && L.nodes[dn].d.in0 == j) delayed_between = true;
-        if (delayed_between) continue;
-        first.pair = j;
-        sc.paired_into = i;
+        // (an ADD of two of them would lose its place in the later one's epilogue)
+        bool added = false;
+        auto in_group = [&](int x) {
+          bool in = x == i;
+          for (int m = 0; m < first.n_mates; ++m) in |= x == first.mates[m];
+          return in;
+        };
+        for (const NodePlan& n : L.nodes)
+          added |= n.d.op == EVCONV_OP_ADD && ((n.d.in0 == j && in_group(n.d.in1)) || (n.d.in1 == j && in_group(n.d.in0)));
+        if (delayed_between || added) continue;
+        first.mates[first.n_mates++] = j;
+        first.mates_batch = !shortcut;
+        late.paired_into = i;
       }
     }
   }

@@ -166,6 +166,12 @@ void conv_mfma_split_scratch(const ConvParams& p, size_t* part_floats, size_t* c
 void launch_conv_mfma_f32(const ConvParams& p, hipStream_t s);
 // two convs of the same input in one launch (all three modes by their own launchers)
 bool conv_mfma_pair_supported(const ConvParams& a, const ConvParams& b);
+// up to kMaxConvBatch of them, all of one variant
+constexpr int kMaxConvBatch = 4;
+bool conv_mfma_batch_supported(const ConvParams& p, bool bf16);
+void launch_conv_mfma_f32_batch(const ConvParams* convs, int n, hipStream_t s);
+void launch_conv_mfma_bf16_batch(const ConvParams* convs, int n, hipStream_t s);
+void launch_conv_mfma_split_batch(const ConvParams* convs, int n, hipStream_t s);
 void launch_conv_mfma_f32_pair(const ConvParams& a, const ConvParams& b, hipStream_t s);
 void launch_conv_mfma_bf16_pair(const ConvParams& a, const ConvParams& b, hipStream_t s);
 void launch_conv_mfma_split_pair(const ConvParams& a, const ConvParams& b, hipStream_t s);

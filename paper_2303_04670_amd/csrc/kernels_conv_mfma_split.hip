@@ -7,6 +7,7 @@ namespace evk {
 
 bool conv_mfma_split_supported(const ConvParams& p) { return conv_mfma_f32_supported(p); }
 void launch_conv_mfma_split(const ConvParams& p, hipStream_t s) { launch_any<kOpSplit>(p, s); }
+void launch_conv_mfma_split_batch(const ConvParams* convs, int n, hipStream_t s) { launch_batch<kOpSplit>(convs, n, s); }
 void launch_conv_mfma_split_pair(const ConvParams& a, const ConvParams& b, hipStream_t s) { launch_pair<kOpSplit>(a, b, s); }
 int conv_mfma_split_phase_stamps(unsigned long long* host, int max_records, bool reset) {
   return phase_stamps_read(host, max_records, reset);

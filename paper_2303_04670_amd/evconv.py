@@ -172,8 +172,8 @@ def evconv_query_workspace(desc: NetDesc) -> int:
 class _DeviceBytes:
     """A span of device memory owned by somebody else, for torch.as_tensor (no copy)."""
 
-    def __init__(self, ptr, nbytes):
-        self.__cuda_array_interface__ = {"shape": (nbytes,), "typestr": "|u1", "data": (ptr, False), "version": 2}
+    def __init__(self, ptr, typestr, shape):
+        self.__cuda_array_interface__ = {"shape": shape, "typestr": typestr, "data": (ptr, False), "version": 2}
 
 
 class EvConvNet:
@@ -318,12 +318,11 @@ class EvConvNet:
             # of those would save all of it.)
             torch, base, spans = self.torch, stream * self.stream_stride, []
 
-            def span(ptr, nbytes, dtype, shape):
-                return torch.as_tensor(_DeviceBytes((ptr or 0) + base, nbytes), device=self.device).view(dtype).view(shape)
+            def span(ptr, typestr, *shape):  # (in its type and shape at once: each view would take 1-3 us)
+                return torch.as_tensor(_DeviceBytes((ptr or 0) + base, typestr, shape), device=self.device)
             for o in self._outs:
-                c, h, w = o.c, o.h, o.w
-                spans.append((o.node, span(o.y, c * h * w * 4, torch.float32, (c, h, w)), span(o.dy, c * h * w * 4, torch.float32, (c, h, w)),
-                              span(o.dy_idx, h * w * 4, torch.int32, (h * w,)), span(o.dy_count, 4, torch.int32, (1,))))
+                spans.append((o.node, span(o.y, "<f4", o.c, o.h, o.w), span(o.dy, "<f4", o.c, o.h, o.w),
+                              span(o.dy_idx, "<i4", o.h * o.w), span(o.dy_count, "<i4", 1)))
             # (the pointers are null before the first reset; inference tensors are not for later calls)
             if all(o.y for o in self._outs) and not torch.is_inference_mode_enabled():
                 self._out_spans[stream] = spans

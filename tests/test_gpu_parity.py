@@ -1542,6 +1542,55 @@ def test_prediction_heads_in_one_launch(heads, launches, streams):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("c_in,c_out,h,w,wd,streams,n,launches", [
+    (69, 64, 96, 88, wl.WD_F32, 1, 4, [1, 0, 0, 0]),          # a ConvLSTM cell's gates: ragged channels
+    (32, 40, 61, 75, wl.WD_F32, 2, 5, [1, 0, 0, 0, 1]),       # one more than a batch, ragged blocks and tiles
+    (32, 64, 160, 176, wl.WD_F32_SPLIT, 2, 2, [1, 0]),
+    (36, 64, 160, 176, wl.WD_BF16, 2, 3, [1, 0, 0]),
+    (32, 32, 24, 24, wl.WD_F32, 1, 2, [1, 1]),                # too few workgroups: another variant
+])
+def test_convs_of_one_tensor_in_one_launch(c_in, c_out, h, w, wd, streams, n, launches):
+    """Gate convs that read the same tensor run in one launch: every sum, set and result bit for bit as
+    with separate launches, through a reset and steps; an ADD of two of them keeps its place in the
+    later one's epilogue (and these two their own launches)."""
+    b = wl._NetBuilder("gates", c_in, h, w, c_in + c_out, bias=True, bf16=wd == wl.WD_BF16)
+    acts = (wl.ACT_SIGMOID, wl.ACT_TANH, wl.ACT_RELU, wl.ACT_SIGMOID, wl.ACT_NONE)
+    gates = [b.conv(-1, c_out, 3, 1, act=acts[i]) for i in range(n)]
+    prod = b.simple(wl.OP_MUL, gates[0], gates[1])
+    b.simple(wl.OP_ADD, prod, gates[-1], act=wl.ACT_RELU, out=1)
+    net = wl.with_weight_dtype(b.finish(), wd)
+    one, apart = ev.EvConvNet(net, n_streams=streams), ev.EvConvNet(net, n_streams=streams, flags=ev.FLAG_NO_FUSION)
+    rng = np.random.default_rng(c_in + n)
+    shape = (c_in, h, w) if streams == 1 else (streams, c_in, h, w)
+    x0 = _dev(rng.standard_normal(shape))
+    for g in (one, apart):
+        g.profile_begin(100)
+        g.reset(x0)
+        g.profile_end()
+    assert [int(one.node_time(i)[1]) for i in gates] == launches
+    assert all(apart.node_time(i)[1] == 1 for i in gates)
+    for share in (None, 0.01, 0.4, 1.0, 0.0):
+        if share is not None:
+            d = _dev(rng.standard_normal(shape) * (rng.random(shape[:-3] + (1, h, w)) < share))
+            for g in (one, apart):
+                g.step(d)
+        for q in range(streams):
+            for i in range(len(net.nodes)):
+                kinds = (ev.STATE_Z, ev.STATE_OCC, ev.STATE_OCC_TOUCHED, ev.STATE_COUNT)
+                for kind in kinds:
+                    np.testing.assert_array_equal(one.state(i, kind, q), apart.state(i, kind, q), err_msg=f"share {share} node {i} state {kind}")
+            for key in ("y", "dy"):
+                np.testing.assert_array_equal(one.outputs(q)[0][key].cpu().numpy(), apart.outputs(q)[0][key].cpu().numpy())
+    one.destroy()
+    apart.destroy()
+    # an ADD of two of the convs
+    b = wl._NetBuilder("sum", c_in, h, w, 3)
+    x, y = b.conv(-1, c_out, 3, 1, act=wl.ACT_NONE), b.conv(-1, c_out, 3, 1, act=wl.ACT_NONE)
+    total = b.simple(wl.OP_ADD, x, y, act=wl.ACT_RELU, out=1)
+    assert ev.EvConvNet(b.finish()).kernel_name(total) == "fused_into_conv_epilogue"
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("c,h,w", [
     (4, 5, 9),     # one vector per thread
     (3, 9, 13),    # channels that are not whole vectors
