@@ -221,6 +221,7 @@ evconv_status make_layout(const evconv_net_desc* desc, size_t weight_bytes, bool
     }
     const bool two = d.op == EVCONV_OP_ADD || d.op == EVCONV_OP_CONCAT || d.op == EVCONV_OP_MUL;
     if (two && (d.in1 < -1 || d.in1 >= i)) return fail(err, EVCONV_ERR_BAD_DESC, std::string(where) + "in1 is not an earlier node");
+    if (!two && !delay) n.d.in1 = -1;  // (ignored, and not an index: the description may hold anything there)
     if (delay) {
       n.ga = d.in1 < 0 ? L->gin : L->nodes[d.in1].go;
       n.ga = make_geo(d.c_out, n.ga.h, n.ga.w);

@@ -1591,6 +1591,40 @@ def test_convs_of_one_tensor_in_one_launch(c_in, c_out, h, w, wd, streams, n, la
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("make", [lambda: wl.net_flow(5, h=48, w=64), lambda: wl.net_resnet18(6, h=64, w=64)], ids=["flow", "resnet18"])
+def test_in1_of_one_input_operators_is_ignored(monkeypatch, make):
+    """The description's in1 belongs to operators with two inputs: whatever the others hold there (an index
+    far beyond the nodes, one of a real node), the plan and the results are the same."""
+    net = make()
+    marshal, rng = ev.marshal_desc, np.random.default_rng(2)
+    shape = (net.in_c, net.in_h, net.in_w)
+    x0 = _dev(rng.standard_normal(shape))
+    d = _dev(rng.standard_normal(shape) * (rng.random((1,) + shape[1:]) < 0.05))
+    seen = []
+    for other in (-1, 1 << 20, -(1 << 30), 0):
+        def with_in1(*a, **kw):
+            desc, nodes = marshal(*a, **kw)
+            for n in nodes:
+                if n.op not in (wl.OP_ADD, wl.OP_CONCAT, wl.OP_MUL, wl.OP_DELAY):
+                    n.in1 = other
+            return desc, nodes
+        monkeypatch.setattr(ev, "marshal_desc", with_in1)
+        g = ev.EvConvNet(net)
+        g.profile_begin(2 * len(net.nodes) + 8)
+        g.reset(x0)
+        g.step(d)
+        g.profile_end()
+        seen.append(([g.node_time(i)[1] for i in range(len(net.nodes))],
+                     [(o["y"].cpu().numpy(), o["dy"].cpu().numpy()) for o in g.outputs()]))
+        g.destroy()
+    for launches, outs in seen[1:]:
+        assert launches == seen[0][0]
+        for (y, dy), (y0, dy0) in zip(outs, seen[0][1]):
+            np.testing.assert_array_equal(y, y0)
+            np.testing.assert_array_equal(dy, dy0)
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("c,h,w", [
     (4, 5, 9),     # one vector per thread
     (3, 9, 13),    # channels that are not whole vectors
