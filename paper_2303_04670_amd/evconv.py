@@ -308,7 +308,8 @@ class EvConvNet:
 
     def outputs(self, stream=0):
         """Per output node: dict of torch views (y, dy as C x H x W; idx; count) of one stream, valid
-        until the next call on this net.  The caller synchronises the stream before reading."""
+        until the next call on this net.  The caller synchronises the stream before reading.  Before the
+        first reset there are none: EvConvError(ERR_STATE)."""
         spans = self._out_spans.get(stream)
         if spans is None:
             # The tensors lie where they are for the life of the net; making a torch tensor of a bare
@@ -316,14 +317,16 @@ class EvConvNet:
             # aliases of its own (`.data`: with a version counter of their own, too), whose shape, strides
             # or autograd state the caller may change.  (Not views of the workspace tensor: saving one
             # of those would save all of it.)
+            if not all(o.y for o in self._outs):
+                raise EvConvError(ERR_STATE, "outputs before reset")
             torch, base, spans = self.torch, stream * self.stream_stride, []
 
             def span(ptr, typestr, *shape):  # (in its type and shape at once: each view would take 1-3 us)
-                return torch.as_tensor(_DeviceBytes((ptr or 0) + base, typestr, shape), device=self.device)
+                return torch.as_tensor(_DeviceBytes(ptr + base, typestr, shape), device=self.device)
             for o in self._outs:
                 spans.append((o.node, span(o.y, "<f4", o.c, o.h, o.w), span(o.dy, "<f4", o.c, o.h, o.w),
                               span(o.dy_idx, "<i4", o.h * o.w), span(o.dy_count, "<i4", 1)))
-            # (the pointers are null before the first reset; inference tensors are not for later calls)
-            if all(o.y for o in self._outs) and not torch.is_inference_mode_enabled():
+            # (inference tensors are not for later calls)
+            if not torch.is_inference_mode_enabled():
                 self._out_spans[stream] = spans
         return [dict(node=node, y=y.data, dy=dy.data, idx=idx.data, count=count.data) for node, y, dy, idx, count in spans]

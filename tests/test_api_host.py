@@ -113,6 +113,33 @@ def test_null_handles():
     assert L.evconv_current_mode(None) == -1
 
 
+class _HostTorch:
+    """What EvConvNet.outputs needs of torch, on the CPU: every tensor is one that `make` returns."""
+
+    def __init__(self, make):
+        self.as_tensor = lambda span, device: make(span)
+
+    @staticmethod
+    def is_inference_mode_enabled():
+        return False
+
+
+def _net_without_a_gpu(make):
+    net = object.__new__(ev.EvConvNet)
+    net.torch, net.device, net._outs, net._out_spans, net.stream_stride, net._h = _HostTorch(make), "cuda:0", (ev.Out * 1)(), {}, 4096, None
+    return net
+
+
+@pytest.mark.parametrize("stream", [0, 3])
+def test_outputs_before_the_first_reset_are_refused(stream):
+    """The output pointers are null until then: no tensor may be made of them."""
+    made = []
+    net = _net_without_a_gpu(made.append)
+    with pytest.raises(ev.EvConvError) as e:
+        net.outputs(stream)
+    assert e.value.status == ev.ERR_STATE and not made
+
+
 def test_measurement_aids_reject_bad_arguments_before_any_gpu_work():
     L = ev.lib()
     out = (ctypes.c_float * ev.CHIP_PROBE_VALUES)()
