@@ -319,14 +319,18 @@ class EvConvNet:
             # of those would save all of it.)
             if not all(o.y for o in self._outs):
                 raise EvConvError(ERR_STATE, "outputs before reset")
-            torch, base, spans = self.torch, stream * self.stream_stride, []
+            torch, base, spans, in_place = self.torch, stream * self.stream_stride, [], True
 
             def span(ptr, typestr, *shape):  # (in its type and shape at once: each view would take 1-3 us)
-                return torch.as_tensor(_DeviceBytes(ptr + base, typestr, shape), device=self.device)
+                nonlocal in_place
+                t = torch.as_tensor(_DeviceBytes(ptr + base, typestr, shape), device=self.device)
+                in_place &= t.data_ptr() == ptr + base
+                return t
             for o in self._outs:
                 spans.append((o.node, span(o.y, "<f4", o.c, o.h, o.w), span(o.dy, "<f4", o.c, o.h, o.w),
                               span(o.dy_idx, "<i4", o.h * o.w), span(o.dy_count, "<i4", 1)))
-            # (inference tensors are not for later calls)
-            if not torch.is_inference_mode_enabled():
+            # (not for later calls: inference tensors, and copies, which a device without an index makes when
+            # the current device is not the net's)
+            if in_place and not torch.is_inference_mode_enabled():
                 self._out_spans[stream] = spans
         return [dict(node=node, y=y.data, dy=dy.data, idx=idx.data, count=count.data) for node, y, dy, idx, count in spans]

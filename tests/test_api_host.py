@@ -140,6 +140,34 @@ def test_outputs_before_the_first_reset_are_refused(stream):
     assert e.value.status == ev.ERR_STATE and not made
 
 
+class _HostTensor:
+    def __init__(self, ptr, value):
+        self.ptr, self.data = ptr, value
+
+    def data_ptr(self):
+        return self.ptr
+
+
+@pytest.mark.parametrize("copies", [False, True])
+def test_outputs_keeps_tensors_over_the_net_s_memory_only(copies):
+    """Where torch makes a copy of the outputs (a net on another device than the current one) every call
+    makes a new one; tensors over the memory itself are made once."""
+    made = []
+
+    def make(span):
+        a = span.__cuda_array_interface__
+        made.append((a["data"][0], a["typestr"], a["shape"]))
+        return _HostTensor(a["data"][0] + (64 if copies else 0), len(made))
+    net = _net_without_a_gpu(make)
+    o = net._outs[0]
+    o.node, o.c, o.h, o.w, o.y, o.dy, o.dy_idx, o.dy_count = 2, 3, 5, 7, 1 << 20, 1 << 21, 1 << 22, 1 << 23
+    first, again, other = net.outputs(1), net.outputs(1), net.outputs(0)
+    assert made[:4] == [((1 << 20) + 4096, "<f4", (3, 5, 7)), ((1 << 21) + 4096, "<f4", (3, 5, 7)),
+                        ((1 << 22) + 4096, "<i4", (35,)), ((1 << 23) + 4096, "<i4", (1,))]
+    assert first[0] == dict(node=2, y=1, dy=2, idx=3, count=4)
+    assert (again == first) == (not copies) and other != first and len(made) == (12 if copies else 8)
+
+
 def test_measurement_aids_reject_bad_arguments_before_any_gpu_work():
     L = ev.lib()
     out = (ctypes.c_float * ev.CHIP_PROBE_VALUES)()
