@@ -303,13 +303,14 @@ __device__ __forceinline__ unsigned row_of_lane(unsigned rows, int lane) {
   return (unsigned)__builtin_amdgcn_ds_bpermute(lane * 4, (int)rows);
 }
 
-// The operator and the elements of a thread (N, known at compile time) leave no loop and no branch on
-// the way: all loads of a thread are in flight together, and no wave waits for another before its
-// last step.  With the operator looked up per element and a list of the touched sites in LDS, a tile
+// The operator and the elements that a thread has in flight (N) are known at compile time: their loads go
+// out together, and no wave waits for another before its last step.  With the operator looked up per element and a list of the touched sites in LDS, a tile
 // was a chain of up to four round trips (concatenation of an up-sampled tensor, 16 x 16 to 256 x 256: 5.8 /
 // 7.4 / 8.4 / 9.8 us, now 4.9 / 6.0 / 7.0 / 9.1; 5 + 64 channels on 256 x 352 15.4, now 10.2; max-pool of ResNet-18, two
 // launches, 10.9, now 7.7).
-// Element `it` of a thread is (site e / cv, vector e % cv), e = tid + it * 256, of the tile's 64 sites.
+// Element e is vector e % cv of touched site number e / cv: where few sites are touched, few waves have
+// work (64 channels on 256 x 352, 2 % of the sites active, tanh / product: 11.4 / 7.6 us with an element
+// for each of the 64 sites, now 7.5 / 6.3).
 template <int OP, int VEC, int N>
 __global__ __launch_bounds__(256) void elementwise_kernel(EwParams p) {
   touch_params<EwParams>();
@@ -368,89 +369,98 @@ __global__ __launch_bounds__(256) void elementwise_kernel(EwParams p) {
   // channel vectors [v0, v0 + cv) of every touched site belong to this workgroup
   const int v0 = blockIdx.y * p.vec_per_block, cv = min(p.vec_per_block, C / VEC - v0);
   const int cv_magic = (65536 + cv - 1) / cv;  // e / cv == (e * cv_magic) >> 16 for e < 1024 (cv <= 16)
-  int site[N], c[N];
-  size_t q[N];
-  bool on[N];
-#pragma unroll
-  for (int it = 0; it < N; ++it) {
-    const int e = tid + it * 256, r = __umul24(e, cv_magic) >> 16;
-    site[it] = r & 63;
-    c[it] = (v0 + (e - __umul24(r, cv))) * VEC;
-    on[it] = r < 64 && ((word >> site[it]) & 1ull);
-    q[it] = (size_t)(tile_y * 8 + (site[it] >> 3)) * p.go.w + (tile_x * 8 + (site[it] & 7));
+  const int n_sites = __popcll(word), total = n_sites * cv;
+  uint64_t nz_sites = 0;  // sites at which this thread produced a nonzero element
+  const int first = __builtin_amdgcn_readfirstlane(tid >> 6) * 64;  // of this wave
+  int nth = 0;
+  if (first < total) {
+    // lane r: the r-th touched site (the sites that are not touched follow: a permutation of the lanes)
+    const int below = __builtin_amdgcn_mbcnt_hi((unsigned)(word >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)word, 0u));
+    nth = __builtin_amdgcn_ds_permute((((word >> lane) & 1ull) ? below : n_sites + lane - below) * 4, lane);
   }
+  for (int e0 = first; e0 < total; e0 += N * 256) {
+    int site[N], c[N];
+    size_t q[N];
+    bool on[N];
+#pragma unroll
+    for (int it = 0; it < N; ++it) {
+      const int e = e0 + lane + it * 256, r = __umul24(e, cv_magic) >> 16;
+      site[it] = __builtin_amdgcn_ds_bpermute(r * 4, nth);  // (r counts modulo 64)
+      c[it] = (v0 + (e - __umul24(r, cv))) * VEC;
+      on[it] = r < n_sites;
+      q[it] = (size_t)(tile_y * 8 + (site[it] >> 3)) * p.go.w + (tile_x * 8 + (site[it] & 7));
+    }
 
-  // ---- loads: the operands' increments (full values in a regular forward pass) and the old state
-  VecT<VEC> lin[N], lin_b[N], z_old[N], z2_old[N];
-#pragma unroll
-  for (int it = 0; it < N; ++it) {
-    const bool on_a = on[it] && ((wa >> site[it]) & 1ull), on_b = on[it] && ((wb >> site[it]) & 1ull);
-    lin_b[it] = zerov<VEC>();
-    if (OP == kEwMul || OP == kEwAdd) {
-      lin[it] = on_a ? ldv<VEC>(&pa[q[it] * C + c[it]]) : zerov<VEC>();
-      lin_b[it] = on_b ? ldv<VEC>(&pb[q[it] * C + c[it]]) : zerov<VEC>();
-    } else if (OP == kEwConcat) {
-      const int ca = p.ga.c, cb = p.gb.c;  // (VEC 4: c_a % 4 == 0, a vector never straddles the two inputs)
-      const bool first = c[it] < ca;
-      lin[it] = (first ? on_a : on_b) ? ldv<VEC>(first ? &pa[q[it] * ca + c[it]] : &pb[q[it] * cb + c[it] - ca]) : zerov<VEC>();
-    } else if (OP == kEwAct || OP == kEwPoolAcc || OP == kEwSparsify) {
-      lin[it] = on[it] ? ldv<VEC>(&pa[q[it] * C + c[it]]) : zerov<VEC>();
-    }
-  }
-  constexpr bool STATE = OP == kEwMul || OP == kEwPoolMax || OP == kEwPoolAcc || OP == kEwAdd || OP == kEwAct;
-  const float sp_k = OP == kEwSparsify && !dense ? *at_stream(p.step, so) : 0.0f;
-  const bool reads_z = OP == kEwPoolMax || (OP == kEwSparsify ? sp_k > 0.0f : STATE && !dense && (OP == kEwMul || OP == kEwPoolAcc || p.keeps_z));
-  if (STATE || OP == kEwSparsify) {
-#pragma unroll
-    for (int it = 0; it < N; ++it) z_old[it] = on[it] && reads_z ? ldv<VEC>(&pz[q[it] * C + c[it]]) : zerov<VEC>();
-  }
-  if (OP == kEwMul) {
-#pragma unroll
-    for (int it = 0; it < N; ++it) z2_old[it] = on[it] && !dense ? ldv<VEC>(&pz2[q[it] * C + c[it]]) : zerov<VEC>();
-  }
-  if (UP) {
-    // bilinear x2 of the stored tensor (half-pixel centres, clamped borders): the four sources of a site
-    const int CA = p.ga.c;  // channels of the stored tensor (== C for a bare up-sampling)
+    // ---- loads: the operands' increments (full values in a regular forward pass) and the old state
+    VecT<VEC> lin[N], lin_b[N], z_old[N], z2_old[N];
 #pragma unroll
     for (int it = 0; it < N; ++it) {
-      const int ly = site[it] >> 3, lx = site[it] & 7;
-      const int oy = tile_y * 8 + ly, ox = tile_x * 8 + lx;
-      const int iy = oy >> 1, ix = ox >> 1;
-      const int y0 = (oy & 1) ? iy : max(iy - 1, 0), y1 = (oy & 1) ? min(iy + 1, p.ga.h - 1) : iy;
-      const int x0 = (ox & 1) ? ix : max(ix - 1, 0), x1 = (ox & 1) ? min(ix + 1, p.ga.w - 1) : ix;
-      const float wy0 = (oy & 1) ? 0.75f : 0.25f, wy1 = 1.0f - wy0;
-      const float wx0 = (ox & 1) ? 0.75f : 0.25f, wx1 = 1.0f - wx0;
-      const int by = tile_y * 4 - 1, bx = tile_x * 4 - 1;
-      // (the exchange between lanes stands before the branch: it needs all of them)
-      const unsigned s0 = row_of_lane(src_rows, y0 - by), s1 = row_of_lane(src_rows, y1 - by);
-      const unsigned r0 = dense ? ~0u : s0, r1 = dense ? ~0u : s1;
-      if (OP == kEwConcatUp && c[it] >= CA) {  // the second operand's channels (VEC 4: c_a % 4 == 0, a vector is on one side)
-        const bool on_b = on[it] && ((wb >> site[it]) & 1ull);
-        lin[it] = on_b ? ldv<VEC>(&pb[q[it] * p.gb.c + c[it] - CA]) : zerov<VEC>();
-        continue;
+      const bool on_a = on[it] && ((wa >> site[it]) & 1ull), on_b = on[it] && ((wb >> site[it]) & 1ull);
+      lin_b[it] = zerov<VEC>();
+      if (OP == kEwMul || OP == kEwAdd) {
+        lin[it] = on_a ? ldv<VEC>(&pa[q[it] * C + c[it]]) : zerov<VEC>();
+        lin_b[it] = on_b ? ldv<VEC>(&pb[q[it] * C + c[it]]) : zerov<VEC>();
+      } else if (OP == kEwConcat) {
+        const int ca = p.ga.c, cb = p.gb.c;  // (VEC 4: c_a % 4 == 0, a vector never straddles the two inputs)
+        const bool of_a = c[it] < ca;
+        lin[it] = (of_a ? on_a : on_b) ? ldv<VEC>(of_a ? &pa[q[it] * ca + c[it]] : &pb[q[it] * cb + c[it] - ca]) : zerov<VEC>();
+      } else if (OP == kEwAct || OP == kEwPoolAcc || OP == kEwSparsify) {
+        lin[it] = on[it] ? ldv<VEC>(&pa[q[it] * C + c[it]]) : zerov<VEC>();
       }
-      auto source = [&](unsigned row, int y, int x) {
-        return on[it] && ((row >> (x - bx)) & 1u) ? ldv<VEC>(&pa[((size_t)y * p.ga.w + x) * CA + c[it]]) : zerov<VEC>();
-      };
-      const VecT<VEC> v00 = source(r0, y0, x0), v01 = source(r0, y0, x1), v10 = source(r1, y1, x0), v11 = source(r1, y1, x1);
-#pragma unroll
-      for (int i = 0; i < VEC; ++i)
-        lin[it].v[i] = wy0 * (wx0 * v00.v[i] + wx1 * v01.v[i]) + wy1 * (wx0 * v10.v[i] + wx1 * v11.v[i]);
     }
-  }
-  if (OP == kEwPoolMax) {  // pa is the accumulated pool input, pz the cached window maximum
+    constexpr bool STATE = OP == kEwMul || OP == kEwPoolMax || OP == kEwPoolAcc || OP == kEwAdd || OP == kEwAct;
+    const float sp_k = OP == kEwSparsify && !dense ? *at_stream(p.step, so) : 0.0f;
+    const bool reads_z = OP == kEwPoolMax || (OP == kEwSparsify ? sp_k > 0.0f : STATE && !dense && (OP == kEwMul || OP == kEwPoolAcc || p.keeps_z));
+    if (STATE || OP == kEwSparsify) {
 #pragma unroll
-    for (int it = 0; it < N; ++it) {
-      const int oy = tile_y * 8 + (site[it] >> 3), ox = tile_x * 8 + (site[it] & 7);
+      for (int it = 0; it < N; ++it) z_old[it] = on[it] && reads_z ? ldv<VEC>(&pz[q[it] * C + c[it]]) : zerov<VEC>();
+    }
+    if (OP == kEwMul) {
 #pragma unroll
-      for (int i = 0; i < VEC; ++i) lin[it].v[i] = -INFINITY;
-      if (!on[it]) continue;
-      if (p.k == 3) {
+      for (int it = 0; it < N; ++it) z2_old[it] = on[it] && !dense ? ldv<VEC>(&pz2[q[it] * C + c[it]]) : zerov<VEC>();
+    }
+    if (UP) {
+      // bilinear x2 of the stored tensor (half-pixel centres, clamped borders): the four sources of a site
+      const int CA = p.ga.c;  // channels of the stored tensor (== C for a bare up-sampling)
+#pragma unroll
+      for (int it = 0; it < N; ++it) {
+        const int ly = site[it] >> 3, lx = site[it] & 7;
+        const int oy = tile_y * 8 + ly, ox = tile_x * 8 + lx;
+        const int iy = oy >> 1, ix = ox >> 1;
+        const int y0 = (oy & 1) ? iy : max(iy - 1, 0), y1 = (oy & 1) ? min(iy + 1, p.ga.h - 1) : iy;
+        const int x0 = (ox & 1) ? ix : max(ix - 1, 0), x1 = (ox & 1) ? min(ix + 1, p.ga.w - 1) : ix;
+        const float wy0 = (oy & 1) ? 0.75f : 0.25f, wy1 = 1.0f - wy0;
+        const float wx0 = (ox & 1) ? 0.75f : 0.25f, wx1 = 1.0f - wx0;
+        const int by = tile_y * 4 - 1, bx = tile_x * 4 - 1;
+        // (the exchange between lanes stands before the branch: it needs all of them)
+        const unsigned s0 = row_of_lane(src_rows, y0 - by), s1 = row_of_lane(src_rows, y1 - by);
+        const unsigned r0 = dense ? ~0u : s0, r1 = dense ? ~0u : s1;
+        if (OP == kEwConcatUp && c[it] >= CA) {  // the second operand's channels (VEC 4: c_a % 4 == 0, a vector is on one side)
+          const bool on_b = on[it] && ((wb >> site[it]) & 1ull);
+          lin[it] = on_b ? ldv<VEC>(&pb[q[it] * p.gb.c + c[it] - CA]) : zerov<VEC>();
+          continue;
+        }
+        auto source = [&](unsigned row, int y, int x) {
+          return on[it] && ((row >> (x - bx)) & 1u) ? ldv<VEC>(&pa[((size_t)y * p.ga.w + x) * CA + c[it]]) : zerov<VEC>();
+        };
+        const VecT<VEC> v00 = source(r0, y0, x0), v01 = source(r0, y0, x1), v10 = source(r1, y1, x0), v11 = source(r1, y1, x1);
+#pragma unroll
+        for (int i = 0; i < VEC; ++i)
+          lin[it].v[i] = wy0 * (wx0 * v00.v[i] + wx1 * v01.v[i]) + wy1 * (wx0 * v10.v[i] + wx1 * v11.v[i]);
+      }
+    }
+    if (OP == kEwPoolMax) {  // pa is the accumulated pool input, pz the cached window maximum
+#pragma unroll
+      for (int it = 0; it < N; ++it) {
+        const int oy = tile_y * 8 + (site[it] >> 3), ox = tile_x * 8 + (site[it] & 7);
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) lin[it].v[i] = -INFINITY;
+        if (!on[it] || p.k != 3) continue;
         // the usual window: nine loads requested together (an out-of-image tap reads the window's
         // centre instead and is left out of the maximum), then the maxima in the same order
+        const int cy = min(max(oy * p.stride - p.pad + 1, 0), p.ga.h - 1), cx = min(max(ox * p.stride - p.pad + 1, 0), p.ga.w - 1);
         VecT<VEC> t[9];
         bool ok[9];
-        const int cy = min(max(oy * p.stride - p.pad + 1, 0), p.ga.h - 1), cx = min(max(ox * p.stride - p.pad + 1, 0), p.ga.w - 1);
 #pragma unroll
         for (int j = 0; j < 9; ++j) {
           const int iy = oy * p.stride - p.pad + j / 3, ix = ox * p.stride - p.pad + j % 3;
@@ -461,97 +471,102 @@ __global__ __launch_bounds__(256) void elementwise_kernel(EwParams p) {
         for (int j = 0; j < 9; ++j)
 #pragma unroll
           for (int i = 0; i < VEC; ++i) lin[it].v[i] = ok[j] ? fmaxf(lin[it].v[i], t[j].v[i]) : lin[it].v[i];
-      } else {
-        for (int ky = 0; ky < p.k; ++ky) {
-          const int iy = oy * p.stride - p.pad + ky;
-          if ((unsigned)iy >= (unsigned)p.ga.h) continue;
+      }
+      // other windows: tap by tap, the elements of a thread together
+      if (p.k != 3) {
+        for (int ky = 0; ky < p.k; ++ky)
           for (int kx = 0; kx < p.k; ++kx) {
-            const int ix = ox * p.stride - p.pad + kx;
-            if ((unsigned)ix >= (unsigned)p.ga.w) continue;
-            const VecT<VEC> t = ldv<VEC>(&pa[((size_t)iy * p.ga.w + ix) * C + c[it]]);
+            VecT<VEC> t[N];
+            bool ok[N];
 #pragma unroll
-            for (int i = 0; i < VEC; ++i) lin[it].v[i] = fmaxf(lin[it].v[i], t.v[i]);
+            for (int it = 0; it < N; ++it) {
+              const int iy = (tile_y * 8 + (site[it] >> 3)) * p.stride - p.pad + ky, ix = (tile_x * 8 + (site[it] & 7)) * p.stride - p.pad + kx;
+              ok[it] = on[it] && (unsigned)iy < (unsigned)p.ga.h && (unsigned)ix < (unsigned)p.ga.w;
+              t[it] = ok[it] ? ldv<VEC>(&pa[((size_t)iy * p.ga.w + ix) * C + c[it]]) : zerov<VEC>();
+            }
+#pragma unroll
+            for (int it = 0; it < N; ++it)
+#pragma unroll
+              for (int i = 0; i < VEC; ++i) lin[it].v[i] = ok[it] ? fmaxf(lin[it].v[i], t[it].v[i]) : lin[it].v[i];
           }
-        }
       }
     }
-  }
 
-  // ---- results, state, and the sites at which this thread produced a nonzero element
-  uint64_t nz_sites = 0;
+    // ---- results, state, and the sites at which this thread produced a nonzero element
 #pragma unroll
-  for (int it = 0; it < N; ++it) {
-    if (!on[it]) continue;
-    float* const zq = &pz[q[it] * C + c[it]];
-    VecT<VEC> o = lin[it];
-    if (OP == kEwAdd) {
+    for (int it = 0; it < N; ++it) {
+      if (!on[it]) continue;
+      float* const zq = &pz[q[it] * C + c[it]];
+      VecT<VEC> o = lin[it];
+      if (OP == kEwAdd) {
 #pragma unroll
-      for (int i = 0; i < VEC; ++i) o.v[i] = lin[it].v[i] + lin_b[it].v[i];
-    }
-    if (OP == kEwPoolAcc) {
-      // (a regular pass stores the value as it is: x + 0 is not x for x = -0)
-#pragma unroll
-      for (int i = 0; i < VEC; ++i) o.v[i] = dense ? lin[it].v[i] : z_old[it].v[i] + lin[it].v[i];
-      stv<VEC>(zq, o);
-      continue;
-    }
-    if (OP == kEwMul) {
-      // Eq.15-17: y_inc = (x1acc + x1_inc) * x2_inc + x2acc * x1_inc, then both accumulators
-      // advance.  Explicitly rounded operations: no fused multiply-add, so the result is the
-      // same single-rounded sequence on any implementation.
-#pragma clang fp contract(off)
-      VecT<VEC> n1 = lin[it], n2 = lin_b[it];
-#pragma unroll
-      for (int i = 0; i < VEC; ++i) {
-        if (dense) {
-          o.v[i] = lin[it].v[i] * lin_b[it].v[i];
-        } else {
-          n1.v[i] = z_old[it].v[i] + lin[it].v[i];
-          n2.v[i] = z2_old[it].v[i] + lin_b[it].v[i];
-          const float t1 = n1.v[i] * lin_b[it].v[i], t2 = z2_old[it].v[i] * lin[it].v[i];
-          o.v[i] = t1 + t2;
-        }
+        for (int i = 0; i < VEC; ++i) o.v[i] = lin[it].v[i] + lin_b[it].v[i];
       }
-      stv<VEC>(zq, n1);
-      stv<VEC>(&pz2[q[it] * C + c[it]], n2);
-    } else if (OP == kEwSparsify) {
-      // Eq.3-8: x_corr = delta + x_inc; y_inc = k floor(0.5 + x_corr / k); delta = x_corr - y_inc
-      VecT<VEC> d_new = zerov<VEC>();
-      if (sp_k > 0.0f) {
-#pragma clang fp contract(off)  // the residual is x_corr minus the rounded product, not a fused form
+      if (OP == kEwPoolAcc) {
+        // (a regular pass stores the value as it is: x + 0 is not x for x = -0)
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) o.v[i] = dense ? lin[it].v[i] : z_old[it].v[i] + lin[it].v[i];
+        stv<VEC>(zq, o);
+        continue;
+      }
+      if (OP == kEwMul) {
+        // Eq.15-17: y_inc = (x1acc + x1_inc) * x2_inc + x2acc * x1_inc, then both accumulators
+        // advance.  Explicitly rounded operations: no fused multiply-add, so the result is the
+        // same single-rounded sequence on any implementation.
+#pragma clang fp contract(off)
+        VecT<VEC> n1 = lin[it], n2 = lin_b[it];
 #pragma unroll
         for (int i = 0; i < VEC; ++i) {
-          // (an element with a zero increment emits nothing and keeps its residual: |delta| <= k/2)
-          const float x_corr = z_old[it].v[i] + lin[it].v[i];
-          const bool moved = lin[it].v[i] != 0.0f;
-          o.v[i] = moved ? sp_k * floorf(0.5f + x_corr / sp_k) : 0.0f;
-          d_new.v[i] = moved ? x_corr - o.v[i] : z_old[it].v[i];
+          if (dense) {
+            o.v[i] = lin[it].v[i] * lin_b[it].v[i];
+          } else {
+            n1.v[i] = z_old[it].v[i] + lin[it].v[i];
+            n2.v[i] = z2_old[it].v[i] + lin_b[it].v[i];
+            const float t1 = n1.v[i] * lin_b[it].v[i], t2 = z2_old[it].v[i] * lin[it].v[i];
+            o.v[i] = t1 + t2;
+          }
         }
-      }
-      if (dense || sp_k > 0.0f) stv<VEC>(zq, d_new);  // a refresh clears the residual
-    } else if (OP == kEwPoolMax) {
-      stv<VEC>(zq, lin[it]);
+        stv<VEC>(zq, n1);
+        stv<VEC>(&pz2[q[it] * C + c[it]], n2);
+      } else if (OP == kEwSparsify) {
+        // Eq.3-8: x_corr = delta + x_inc; y_inc = k floor(0.5 + x_corr / k); delta = x_corr - y_inc
+        VecT<VEC> d_new = zerov<VEC>();
+        if (sp_k > 0.0f) {
+#pragma clang fp contract(off)  // the residual is x_corr minus the rounded product, not a fused form
 #pragma unroll
-      for (int i = 0; i < VEC; ++i) o.v[i] = dense ? lin[it].v[i] : lin[it].v[i] - z_old[it].v[i];
-    } else if ((OP == kEwAdd || OP == kEwAct) && p.keeps_z) {
-      VecT<VEC> z_new = o;
-#pragma unroll
-      for (int i = 0; i < VEC; ++i) {
-        const float x = o.v[i];
-        if (dense) {
-          o.v[i] = apply_act(p.act, x);
-        } else {
-          z_new.v[i] = z_old[it].v[i] + x;
-          o.v[i] = (p.act == kActNone) ? x : apply_act(p.act, z_new.v[i]) - apply_act(p.act, z_old[it].v[i]);
+          for (int i = 0; i < VEC; ++i) {
+            // (an element with a zero increment emits nothing and keeps its residual: |delta| <= k/2)
+            const float x_corr = z_old[it].v[i] + lin[it].v[i];
+            const bool moved = lin[it].v[i] != 0.0f;
+            o.v[i] = moved ? sp_k * floorf(0.5f + x_corr / sp_k) : 0.0f;
+            d_new.v[i] = moved ? x_corr - o.v[i] : z_old[it].v[i];
+          }
         }
+        if (dense || sp_k > 0.0f) stv<VEC>(zq, d_new);  // a refresh clears the residual
+      } else if (OP == kEwPoolMax) {
+        stv<VEC>(zq, lin[it]);
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) o.v[i] = dense ? lin[it].v[i] : lin[it].v[i] - z_old[it].v[i];
+      } else if ((OP == kEwAdd || OP == kEwAct) && p.keeps_z) {
+        VecT<VEC> z_new = o;
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) {
+          const float x = o.v[i];
+          if (dense) {
+            o.v[i] = apply_act(p.act, x);
+          } else {
+            z_new.v[i] = z_old[it].v[i] + x;
+            o.v[i] = (p.act == kActNone) ? x : apply_act(p.act, z_new.v[i]) - apply_act(p.act, z_old[it].v[i]);
+          }
+        }
+        stv<VEC>(zq, z_new);
       }
-      stv<VEC>(zq, z_new);
+      stv<VEC>(&pout[q[it] * C + c[it]], o);
+      bool nz = false;
+#pragma unroll
+      for (int i = 0; i < VEC; ++i) nz |= (o.v[i] != 0.0f);
+      if (nz) nz_sites |= 1ull << site[it];
     }
-    stv<VEC>(&pout[q[it] * C + c[it]], o);
-    bool nz = false;
-#pragma unroll
-    for (int i = 0; i < VEC; ++i) nz |= (o.v[i] != 0.0f);
-    if (nz) nz_sites |= 1ull << site[it];
   }
   if (OP == kEwPoolAcc) return;
   if (p.structural || dense) {
@@ -579,12 +594,16 @@ __global__ __launch_bounds__(256) void elementwise_kernel(EwParams p) {
   }
 }
 
+// Four elements of a thread in flight, where that leaves the registers of six waves per SIMD: sums, products,
+// maxima and up-samplings of whole vectors take two at a time (sum with an activation, 64 channels on 256 x
+// 352, every site active: 30.6 us with four, 25.0 with two; product, 2 % of the sites active, 7.8 and 6.3).
 template <int OP, int VEC>
 void launch_ew(const EwParams& q, const dim3& grid, hipStream_t s) {
-  const int n = (std::min(q.vec_per_block, q.go.c / VEC) * 64 + 255) / 256;  // elements of a thread
+  constexpr int kMax = VEC == 4 && (OP == kEwAdd || OP == kEwMul || OP == kEwPoolMax || OP == kEwUp2x) ? 2 : 4;
+  const int n = std::min((std::min(q.vec_per_block, q.go.c / VEC) * 64 + 255) / 256, kMax);  // elements of a thread
   if (n <= 1) hipLaunchKernelGGL((elementwise_kernel<OP, VEC, 1>), grid, dim3(256), 0, s, q);
   else if (n <= 2) hipLaunchKernelGGL((elementwise_kernel<OP, VEC, 2>), grid, dim3(256), 0, s, q);
-  else hipLaunchKernelGGL((elementwise_kernel<OP, VEC, 4>), grid, dim3(256), 0, s, q);
+  else hipLaunchKernelGGL((elementwise_kernel<OP, VEC, kMax>), grid, dim3(256), 0, s, q);
 }
 
 void launch_elementwise(const EwParams& p, hipStream_t s) {

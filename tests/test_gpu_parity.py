@@ -1626,11 +1626,15 @@ def test_in1_of_one_input_operators_is_ignored(monkeypatch, make):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("c,h,w", [
-    (4, 5, 9),     # one vector per thread
+    (4, 5, 9),     # one vector per thread (as on all maps of few tiles: the channels are split over workgroups)
     (3, 9, 13),    # channels that are not whole vectors
-    (20, 8, 8),    # two vectors per thread, the second one beyond the tile for most
-    (64, 7, 11),   # four vectors per thread
+    (20, 8, 8),
+    (64, 7, 11),
     (76, 3, 5),    # several workgroups per tile, the last one narrower
+    (32, 71, 87),  # 396 tiles of the up-sampled map: two vectors per thread
+    (44, 71, 87),  # four, or twice two; the last ones beyond the tile's sites for some threads
+    (72, 71, 87),  # as many, and a second, narrower workgroup per tile
+    (18, 71, 87),  # 16 single channels, and two
 ])
 def test_elementwise_operators_by_channel_count(c, h, w):
     """Up-sampling stored and inside a concatenation, concatenation, sum, product and activation over the
@@ -1651,6 +1655,22 @@ def test_elementwise_operators_by_channel_count(c, h, w):
     incs = [(rng.standard_normal((c, h, w)) * (rng.random((1, h, w)) < p)).astype(np.float32) for p in (0.05, 0.0, 1.0, 0.2)]
     # (a value-pruned set may differ where an increment is rounded to nothing on one side only)
     run_stream(net, x0, incs, "increment", tol=1e-5, label=f"elementwise {c} x {h} x {w}", max_flips=4)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("c", [3, 20, 68])
+def test_pooling_windows_on_many_tiles(c):
+    """Windows of 2, 3 and 5 sites where a thread has several elements (more than 384 tiles), whole vectors and
+    single channels, at the ragged borders of the map."""
+    h, w = 141, 179
+    b = wl._NetBuilder("pools", c, h, w, c)
+    for k, pad in ((2, 1), (3, 1), (5, 2)):
+        b.simple(wl.OP_MAXPOOL, -1, k=k, stride=1, pad=pad, out=1)
+    net = b.finish()
+    rng = np.random.default_rng(c)
+    x0 = rng.standard_normal((c, h, w)).astype(np.float32)
+    incs = [(rng.standard_normal((c, h, w)) * (rng.random((1, h, w)) < p)).astype(np.float32) for p in (0.01, 0.0, 1.0)]
+    run_stream(net, x0, incs, "increment", tol=1e-6, label=f"pools {c}", max_flips=0)
 
 
 @pytest.mark.parametrize("ci,co,k,s,hw,streams", [
