@@ -30,15 +30,16 @@ __device__ __forceinline__ float act_p(int act, float v) {
 }
 
 // z read-modify-write and output increment of one (site, channel) element
-template <class P>
-__device__ __forceinline__ float finish_element(const P& p, float* z, float* out, size_t q, int co, float v, float z_old) {
+// (old_z: returns the old z)
+template <class P, class F>
+__device__ __forceinline__ float finish_element(const P& p, float* z, float* out, size_t q, int co, float v, F&& old_z) {
   float o;
   if (p.dense) {
     const float zn = v + (p.bias ? p.bias[co] : 0.0f);
     z[q] = zn;
     o = act_p(p.act, zn);
   } else {
-    const float z_new = z_old + v;
+    const float z_old = old_z(), z_new = z_old + v;
     z[q] = z_new;
     o = (p.act == kActNone) ? v : act_p(p.act, z_new) - act_p(p.act, z_old);
   }
@@ -53,7 +54,12 @@ __device__ __forceinline__ float finish_element(const P& p, float* z, float* out
 // launches that fill the chip (more than 1024 tiles) need more; those take two, and exactly c_out
 // rows (256 x 352: 16 -> 8 channels 17.9 us before, 25.2 with four pieces, 17.5 with two; 256 -> 5
 // channels 34.6, 38.9, 30.4; 64 x 88, 88 tiles: 512 -> 8 channels 53.7, 25.6, 27.5).
-template <int NOUT, int UNROLL, class P>
+// EARLY: the old values are requested before the dot products.  That keeps two more registers per row (four
+// rows: 60 against 76, eight: 62 against 120), so it is not for regular passes, which read none
+// (64 -> 8 channels on 512 x 700: 60.2 us early, 50.8 late), nor, on many tiles, for short dot products of
+// more than two rows (30 -> 8 channels on 512 x 700, 2 % of the sites active: 40.1 and 33.5; 64 -> 8: 40.0
+// early, 43.7 late).
+template <int NOUT, int UNROLL, bool EARLY, class P>
 __device__ __forceinline__ void few_tile(const P& p, const int tile) {
   asm volatile("" ::"s"(p.go.h), "s"(p.go.w), "s"(p.go.c), "s"(p.go.tx), "s"(p.gi.c), "s"(p.dense), "s"(p.occ_in), "s"(p.in), "s"(p.w), "s"(p.z),
                "s"(p.out), "s"(p.y), "s"(p.dy), "s"(p.int_mode), "s"(p.act), "s"(p.bias), "s"(p.st.stride), "s"(p.tx_magic));
@@ -84,17 +90,17 @@ __device__ __forceinline__ void few_tile(const P& p, const int tile) {
     return;
   }
 
-  // old values of the elements this thread finishes, requested before the dot products
+  // old values of the elements this thread finishes, requested before the dot products (EARLY)
   const bool mine = inb && q4 == 0;
   float* const z = at_stream(p.z, so);
   float* const out = at_stream(p.out, so);
   const size_t q0 = ((size_t)oy * p.go.w + ox) * Cout, e0 = (size_t)oy * p.go.w + ox;
   const bool reads_y = pub_y && (p.int_mode == kIntStep ? on : p.int_mode != kIntReset);
-  float z_old[NOUT], y_old[NOUT];
+  float z_early[NOUT], y_early[NOUT];
 #pragma unroll
   for (int j = 0; j < NOUT; ++j) {
-    z_old[j] = mine && on && !dense && j < Cout ? z[q0 + j] : 0.0f;
-    y_old[j] = mine && reads_y && j < Cout ? pub_y[(size_t)j * hw + e0] : 0.0f;
+    z_early[j] = EARLY && mine && on && !dense && j < Cout ? z[q0 + j] : 0.0f;
+    y_early[j] = EARLY && mine && reads_y && j < Cout ? pub_y[(size_t)j * hw + e0] : 0.0f;
   }
 
   float acc[NOUT];
@@ -139,19 +145,20 @@ __device__ __forceinline__ void few_tile(const P& p, const int tile) {
       if (j >= Cout) break;
       float o = 0.0f;
       if (on) {
-        o = finish_element(p, z, out, q0 + j, j, acc[j], z_old[j]);
+        o = finish_element(p, z, out, q0 + j, j, acc[j], [&] { return EARLY ? z_early[j] : z[q0 + j]; });
         nz |= o != 0.0f;
       }
       if (pub_y) {  // the step's output and its increment, as the stand-alone integration writes them
         const size_t e = (size_t)j * hw + e0;
+        auto old_y = [&] { return EARLY ? y_early[j] : pub_y[e]; };
         if (p.int_mode == kIntStep) {
-          if (on) pub_y[e] = y_old[j] + o;
+          if (on) pub_y[e] = old_y() + o;
           pub_dy[e] = o;
         } else if (p.int_mode == kIntReset) {
           pub_y[e] = o;
           pub_dy[e] = 0.0f;
         } else {
-          pub_dy[e] = o - y_old[j];
+          pub_dy[e] = o - old_y();
           pub_y[e] = o;
         }
       }
@@ -171,17 +178,17 @@ __device__ __forceinline__ void few_tile(const P& p, const int tile) {
   }
 }
 
-template <int NOUT, int UNROLL>
+template <int NOUT, int UNROLL, bool EARLY>
 __global__ __launch_bounds__(256) void conv_pointwise_few_kernel(ConvParams p) {
   touch_params<ConvParams>();
-  few_tile<NOUT, UNROLL>(p, blockIdx.x);
+  few_tile<NOUT, UNROLL, EARLY>(p, blockIdx.x);
 }
 
 // Several heads in one launch: workgroups first[i] .. first[i + 1] - 1 are head i's tiles.  Nothing reads a
 // prediction, so the heads of an encoder-decoder's scales need not stand between its layers: four
 // launches of 6.2, 5.2, 5.0 and 6.2 us (32 x 32 to 256 x 256), in one 9.0.
 struct HeadBatch { ConvParams p[kMaxHeadBatch]; int first[kMaxHeadBatch]; int n; };
-template <int NOUT, int UNROLL>
+template <int NOUT, int UNROLL, bool EARLY>
 __global__ __launch_bounds__(256) void conv_pointwise_batch_kernel(HeadBatch q) {
   int i = 0;
 #pragma unroll
@@ -192,7 +199,7 @@ __global__ __launch_bounds__(256) void conv_pointwise_batch_kernel(HeadBatch q) 
   typedef const char __attribute__((address_space(4))) Byte;
   Byte* const base = (Byte*)__builtin_amdgcn_kernarg_segment_ptr();
   const int first = *(const int __attribute__((address_space(4)))*)(base + offsetof(HeadBatch, first) + i * sizeof(int));
-  few_tile<NOUT, UNROLL>(*(const ConvParams __attribute__((address_space(4)))*)(base + args), (int)blockIdx.x - first);
+  few_tile<NOUT, UNROLL, EARLY>(*(const ConvParams __attribute__((address_space(4)))*)(base + args), (int)blockIdx.x - first);
 }
 
 // one wavefront per output channel: the lanes stride through c_in (coalesced weight row), then a
@@ -224,7 +231,7 @@ __global__ __launch_bounds__(256) void linear_site_kernel(ConvParams p) {
 #pragma unroll
   for (int m = 1; m < 64; m <<= 1) acc += __shfl_xor(acc, m);
   if (lane == 0) {
-    const bool nz = finish_element(p, at_stream(p.z, so), at_stream(p.out, so), (size_t)co, co, acc, z_old) != 0.0f;
+    const bool nz = finish_element(p, at_stream(p.z, so), at_stream(p.out, so), (size_t)co, co, acc, [&] { return z_old; }) != 0.0f;
     // pre-zeroed words; the wavefronts of one launch OR their share in
     if (p.dense || nz) atomicOr((unsigned long long*)at_stream(p.occ_out, so), 1ull);
     if (co == 0) at_stream(p.occ_touched, so)[0] = 1ull;
@@ -250,19 +257,26 @@ ConvParams with_magic(ConvParams p) {
   return p;
 }
 
-// calls f(rows, pieces in flight) with the variant that takes p, as compile-time numbers
+// calls f(rows, pieces in flight, old values early) with the variant that takes p, as compile-time values
+// (the first two are the same in every pass of a net)
 template <class F>
 void with_few_variant(const ConvParams& p, F&& f) {
   using std::integral_constant;
   const bool many = (long long)p.go.tiles() * p.st.n > 1024;
-  if (p.go.c == 1) f(integral_constant<int, 1>{}, integral_constant<int, 4>{});
-  else if (p.go.c == 2) f(integral_constant<int, 2>{}, integral_constant<int, 4>{});
-  else if (p.go.c <= 4) f(integral_constant<int, 4>{}, integral_constant<int, 4>{});
-  else if (!many) f(integral_constant<int, 8>{}, integral_constant<int, 4>{});
-  else if (p.go.c == 5) f(integral_constant<int, 5>{}, integral_constant<int, 2>{});
-  else if (p.go.c == 6) f(integral_constant<int, 6>{}, integral_constant<int, 2>{});
-  else if (p.go.c == 7) f(integral_constant<int, 7>{}, integral_constant<int, 2>{});
-  else f(integral_constant<int, 8>{}, integral_constant<int, 2>{});
+  auto variant = [&](auto rows, auto pieces) {
+    if (p.dense || (many && p.go.c > 2 && (p.gi.c % 4 != 0 || p.gi.c < 32))) f(rows, pieces, std::false_type{});
+    else f(rows, pieces, std::true_type{});
+  };
+  if (p.go.c == 1) variant(integral_constant<int, 1>{}, integral_constant<int, 4>{});
+  else if (p.go.c == 2) variant(integral_constant<int, 2>{}, integral_constant<int, 4>{});
+  else if (!many && p.go.c <= 4) variant(integral_constant<int, 4>{}, integral_constant<int, 4>{});
+  else if (!many) variant(integral_constant<int, 8>{}, integral_constant<int, 4>{});
+  else if (p.go.c == 3) variant(integral_constant<int, 3>{}, integral_constant<int, 2>{});
+  else if (p.go.c == 4) variant(integral_constant<int, 4>{}, integral_constant<int, 2>{});
+  else if (p.go.c == 5) variant(integral_constant<int, 5>{}, integral_constant<int, 2>{});
+  else if (p.go.c == 6) variant(integral_constant<int, 6>{}, integral_constant<int, 2>{});
+  else if (p.go.c == 7) variant(integral_constant<int, 7>{}, integral_constant<int, 2>{});
+  else variant(integral_constant<int, 8>{}, integral_constant<int, 2>{});
 }
 
 }  // namespace
@@ -273,15 +287,15 @@ void launch_conv_pointwise(const ConvParams& q, hipStream_t s) {
     hipLaunchKernelGGL(linear_site_kernel, dim3((p.go.c + 3) / 4, 1, p.st.n), dim3(256), 0, s, p);
     return;
   }
-  with_few_variant(p, [&](auto rows, auto pieces) {
-    hipLaunchKernelGGL((conv_pointwise_few_kernel<decltype(rows)::value, decltype(pieces)::value>), dim3(p.go.tiles(), 1, p.st.n),
-                       dim3(256), 0, s, p);
+  with_few_variant(p, [&](auto rows, auto pieces, auto early) {
+    hipLaunchKernelGGL((conv_pointwise_few_kernel<decltype(rows)::value, decltype(pieces)::value, decltype(early)::value>),
+                       dim3(p.go.tiles(), 1, p.st.n), dim3(256), 0, s, p);
   });
 }
 
 int conv_pointwise_variant(const ConvParams& p) {
   int v = 0;
-  with_few_variant(p, [&](auto rows, auto pieces) { v = rows() * 16 + pieces(); });
+  with_few_variant(p, [&](auto rows, auto pieces, auto) { v = rows() * 16 + pieces(); });
   return v;
 }
 
@@ -294,9 +308,9 @@ void launch_conv_pointwise_batch(const ConvParams* heads, int n, hipStream_t s) 
     blocks += heads[i].go.tiles();
   }
   q.n = n;
-  with_few_variant(heads[0], [&](auto rows, auto pieces) {
-    hipLaunchKernelGGL((conv_pointwise_batch_kernel<decltype(rows)::value, decltype(pieces)::value>), dim3(blocks, 1, heads[0].st.n),
-                       dim3(256), 0, s, q);
+  with_few_variant(heads[0], [&](auto rows, auto pieces, auto early) {
+    hipLaunchKernelGGL((conv_pointwise_batch_kernel<decltype(rows)::value, decltype(pieces)::value, decltype(early)::value>),
+                       dim3(blocks, 1, heads[0].st.n), dim3(256), 0, s, q);
   });
 }
 

@@ -2157,9 +2157,10 @@ def test_launches_of_five_workgroups_per_cu(mode, ci, co, k, hw):
     many.destroy()
 
 
-@pytest.mark.parametrize("ci,co", [(20, 5), (19, 6), (64, 7), (36, 8), (20, 4)])
+@pytest.mark.parametrize("ci,co", [(20, 5), (19, 6), (64, 7), (36, 8), (20, 4), (20, 3), (40, 3), (64, 4), (33, 5)])
 def test_pointwise_heads_on_many_tiles(ci, co):
-    """Prediction heads of more than 1024 tiles: the variants of exactly five to eight channels."""
+    """Prediction heads of more than 1024 tiles: the variants of exactly three to eight channels, with the old
+    values requested before and after dot products of fewer and more than 32 channels."""
     _say(f"pointwise head on many tiles: {ci} -> {co}")
     h, w = 257, 259
     b = wl._NetBuilder("heads", ci, h, w, ci + co, bias=True)
