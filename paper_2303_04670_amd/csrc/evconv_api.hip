@@ -802,6 +802,63 @@ evconv_status evconv_query_workspace(const evconv_net_desc* desc, size_t* bytes)
 }  // extern "C"
 
 namespace {
+bool is_mfma(const NodePlan& n) {
+  return n.kernel == kKernConvMfmaF32 || n.kernel == kKernConvMfmaBf16 || n.kernel == kKernConvMfmaSplit;
+}
+
+// Folds ADD and SPARSIFY nodes into the epilogues of matrix-core convs.  Returns how many.
+int plan_epilogues(std::vector<NodePlan>& nodes) {
+  int folded = 0;
+  // where in a pass a node is computed
+  auto pos = [&](int i) { return i >= 0 && nodes[i].paired_into >= 0 ? nodes[i].paired_into : i; };
+  // A DELAY of node i that stands between the conv and i reads i's buffers as the previous step left
+  // them; computed in the conv's epilogue they would already hold this step's values.
+  auto delayed_between = [&](int host, int i) {
+    for (int dn = pos(host) + 1; dn < i; ++dn)
+      if (nodes[dn].d.op == EVCONV_OP_DELAY && nodes[dn].d.in0 == i) return true;
+    return false;
+  };
+  // An ADD goes to the conv that produces the later one of its inputs (residual add + activation, skip
+  // adds).  Every buffer of the ADD node is still written.
+  for (int i = 0; i < (int)nodes.size(); ++i) {
+    NodePlan& a_node = nodes[i];
+    if (a_node.d.op != EVCONV_OP_ADD) continue;
+    const bool in0_later = pos(a_node.d.in0) > pos(a_node.d.in1);
+    const int later = in0_later ? a_node.d.in0 : a_node.d.in1;
+    const int other = in0_later ? a_node.d.in1 : a_node.d.in0;
+    if (later < 0 || later == other) continue;
+    const int host = nodes[later].fused_into >= 0 ? nodes[later].fused_into : later;
+    NodePlan& c_node = nodes[host];
+    if (!is_mfma(c_node) || c_node.n_fused >= kMaxFusedAdds) continue;
+    if (host != later && c_node.fused_nodes[c_node.n_fused - 1] != later) continue;  // chain must be contiguous
+    if (pos(other) >= pos(host)) continue;  // the other input must exist before the conv runs
+    if (delayed_between(host, i)) continue;
+    c_node.fused_nodes[c_node.n_fused++] = i;
+    a_node.fused_into = host;
+    ++folded;
+  }
+  // A sparsification layer goes to the matrix-core conv that produces its input, directly or through the
+  // last ADD folded into that conv: the layer then reads the increment where it is made (no launch, no
+  // re-read).  One layer per conv; every buffer of the layer is still written.
+  for (int i = 0; i < (int)nodes.size(); ++i) {
+    NodePlan& s_node = nodes[i];
+    if (s_node.d.op != EVCONV_OP_SPARSIFY || s_node.d.in0 < 0 || s_node.d.is_output) continue;
+    const NodePlan& x = nodes[s_node.d.in0];
+    int host = -1;
+    if (x.fused_into >= 0) {
+      const NodePlan& h = nodes[x.fused_into];
+      if (x.d.op == EVCONV_OP_ADD && h.n_fused > 0 && h.fused_nodes[h.n_fused - 1] == s_node.d.in0) host = x.fused_into;
+    } else if (x.n_fused == 0 && is_mfma(x)) {
+      host = s_node.d.in0;
+    }
+    if (host < 0 || nodes[host].fused_sp >= 0 || delayed_between(host, i)) continue;
+    nodes[host].fused_sp = i;
+    s_node.fused_into = host;
+    ++folded;
+  }
+  return folded;
+}
+
 evconv_status create_impl(const evconv_net_desc* desc, const void* weights, size_t weight_bytes,
                           void* workspace, size_t workspace_bytes, void* hip_stream, evconv_net** out) {
   if (!out || !workspace || (!weights && weight_bytes)) {
@@ -981,15 +1038,17 @@ evconv_status create_impl(const evconv_net_desc* desc, const void* weights, size
   if (e == hipSuccess) e = hipStreamSynchronize(net->stream);
   if (e != hipSuccess) { g_create_error = std::string("upload: ") + hipGetErrorString(e); delete net; return EVCONV_ERR_HIP; }
   if (net->outputs.empty()) { g_create_error = "no output node"; delete net; return EVCONV_ERR_BAD_DESC; }
-  // Fold ADD nodes into the epilogue of the matrix-core conv that produces their later input
-  // (residual add + activation, skip adds).  Every buffer of the ADD node is still written.
   const bool fuse = !(net->flags & EVCONV_FLAG_NO_FUSION);
   // A block's shortcut conv runs in the launch of the block's first conv, which reads the same tensor, and
   // the gate convs of a cell in one launch (pair_supported and batchable say where; the sums stay as they
   // are).
   if (fuse) {
-    auto is_mfma = [](const NodePlan& n) {
-      return n.kernel == kKernConvMfmaF32 || n.kernel == kKernConvMfmaBf16 || n.kernel == kKernConvMfmaSplit;
+    // (a conv that runs earlier may no longer host an ADD whose other input is computed in between, or an ADD
+    // of two convs of its launch: such a conv stays where it is)
+    auto folds = [&](int late, int into) {
+      std::vector<NodePlan> plan = L.nodes;
+      if (into >= 0) plan[late].paired_into = into;
+      return plan_epilogues(plan);
     };
     auto probe_of = [&](const NodePlan& n) {
       ConvParams p = {};
@@ -1012,16 +1071,7 @@ evconv_status create_impl(const evconv_net_desc* desc, const void* weights, size
         bool delayed_between = false;  // (a DELAY of the later one in between must see last step's buffers)
         for (int dn = i + 1; dn < j; ++dn)
           if (L.nodes[dn].d.op == EVCONV_OP_DELAY && L.nodes[dn].d.in0 == j) delayed_between = true;
-        // (an ADD of two of them would lose its place in the later one's epilogue)
-        bool added = false;
-        auto in_group = [&](int x) {
-          bool in = x == i;
-          for (int m = 0; m < first.n_mates; ++m) in |= x == first.mates[m];
-          return in;
-        };
-        for (const NodePlan& n : L.nodes)
-          added |= n.d.op == EVCONV_OP_ADD && ((n.d.in0 == j && in_group(n.d.in1)) || (n.d.in1 == j && in_group(n.d.in0)));
-        if (delayed_between || added) continue;
+        if (delayed_between || folds(j, i) < folds(j, -1)) continue;
         first.mates[first.n_mates++] = j;
         first.mates_batch = !shortcut;
         late.paired_into = i;
@@ -1056,59 +1106,7 @@ evconv_status create_impl(const evconv_net_desc* desc, const void* weights, size
       for (int k = 0; k < n && n > 1; ++k) L.nodes[members[k]].head_batch = members[n - 1];
     }
   }
-  // where in a pass a node is computed
-  auto pos = [&](int i) { return i >= 0 && L.nodes[i].paired_into >= 0 ? L.nodes[i].paired_into : i; };
-  if (fuse) {
-    for (size_t i = 0; i < L.nodes.size(); ++i) {
-      NodePlan& a_node = L.nodes[i];
-      if (a_node.d.op != EVCONV_OP_ADD) continue;
-      const bool in0_later = pos(a_node.d.in0) > pos(a_node.d.in1);
-      const int later = in0_later ? a_node.d.in0 : a_node.d.in1;
-      const int other = in0_later ? a_node.d.in1 : a_node.d.in0;
-      if (later < 0 || later == other) continue;
-      const int host = L.nodes[later].fused_into >= 0 ? L.nodes[later].fused_into : later;
-      NodePlan& c_node = L.nodes[host];
-      if ((c_node.kernel != kKernConvMfmaF32 && c_node.kernel != kKernConvMfmaBf16 &&
-           c_node.kernel != kKernConvMfmaSplit) ||
-          c_node.n_fused >= kMaxFusedAdds) continue;
-      if (host != later && c_node.fused_nodes[c_node.n_fused - 1] != later) continue;  // chain must be contiguous
-      if (pos(other) >= pos(host)) continue;  // the other input must exist before the conv runs
-      // A DELAY node between the conv and the ADD that delays this ADD reads the ADD's buffers as
-      // the previous step left them; computed in the conv's epilogue they would already hold
-      // this step's values.
-      bool delayed_between = false;
-      for (size_t dn = (size_t)pos(host) + 1; dn < i; ++dn)
-        if (L.nodes[dn].d.op == EVCONV_OP_DELAY && L.nodes[dn].d.in0 == (int)i) delayed_between = true;
-      if (delayed_between) continue;
-      c_node.fused_nodes[c_node.n_fused++] = (int)i;
-      a_node.fused_into = host;
-    }
-  }
-  // Fold a sparsification layer into the epilogue of the matrix-core conv that produces its input,
-  // directly or through the last ADD folded into that conv: the layer then reads the increment
-  // where it is made (no launch, no re-read).  One layer per conv; every buffer of the layer is
-  // still written.
-  if (fuse) {
-    for (size_t i = 0; i < L.nodes.size(); ++i) {
-      NodePlan& s_node = L.nodes[i];
-      if (s_node.d.op != EVCONV_OP_SPARSIFY || s_node.d.in0 < 0 || s_node.d.is_output) continue;
-      const NodePlan& x = L.nodes[s_node.d.in0];
-      int host = -1;
-      if (x.fused_into >= 0) {
-        const NodePlan& h = L.nodes[x.fused_into];
-        if (x.d.op == EVCONV_OP_ADD && h.n_fused > 0 && h.fused_nodes[h.n_fused - 1] == s_node.d.in0) host = x.fused_into;
-      } else if (x.n_fused == 0 && (x.kernel == kKernConvMfmaF32 || x.kernel == kKernConvMfmaBf16 || x.kernel == kKernConvMfmaSplit)) {
-        host = s_node.d.in0;
-      }
-      if (host < 0 || L.nodes[host].fused_sp >= 0) continue;
-      bool delayed_between = false;  // (a DELAY of this layer placed before it must see last step's buffers)
-      for (size_t dn = (size_t)pos(host) + 1; dn < i; ++dn)
-        if (L.nodes[dn].d.op == EVCONV_OP_DELAY && L.nodes[dn].d.in0 == (int)i) delayed_between = true;
-      if (delayed_between) continue;
-      L.nodes[host].fused_sp = (int)i;
-      s_node.fused_into = host;
-    }
-  }
+  if (fuse) plan_epilogues(L.nodes);
   // Fold a bilinear x2 up-sampling into the gather of the matrix-core conv that is its only
   // consumer: the up-sampled tensor is then never written (its node keeps no state).
   if (fuse) {

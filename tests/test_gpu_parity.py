@@ -1496,6 +1496,53 @@ def test_shortcut_conv_in_the_first_convs_launch(c_in, c_out, h, w, wd, streams,
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("c_in,c_out,h,w,k2,stride,between", [
+    (64, 128, 40, 40, 1, 2, "act"),      # a block's shortcut; its ADD's other input is an activation of the first conv
+    (64, 64, 120, 112, 3, 1, "mul"),     # two gate convs, the other input a product of the first one
+    (64, 64, 120, 112, 3, 1, "concat"),  # the other input a narrow conv's
+    (64, 64, 120, 112, 3, 1, "sum"),     # ADD of both
+])
+def test_a_conv_that_hosts_an_add_is_not_moved_away_from_it(c_in, c_out, h, w, k2, stride, between):
+    """A conv that could run in an earlier conv's launch, but whose epilogue computes an ADD with an input that
+    exists only after that launch, keeps its own: the ADD is no launch of its own, results are those of
+    separate launches."""
+    b = wl._NetBuilder("host", c_in, h, w, c_in + k2, bias=True)
+    first = b.conv(-1, c_out, 3, stride)
+    if between == "act":
+        other = b.simple(wl.OP_ACT, first, act=wl.ACT_TANH)
+    elif between == "mul":
+        other = b.simple(wl.OP_MUL, first, first)
+    elif between == "concat":
+        other = b.simple(wl.OP_CONCAT, b.conv(first, c_out - 8, 1, 1, 0), b.conv(first, 8, 1, 1, 0))
+    else:
+        other = first
+    late = b.conv(-1, c_out, k2, stride, act=wl.ACT_NONE)
+    total = b.simple(wl.OP_ADD, other, late, act=wl.ACT_RELU, out=1)
+    net = b.finish()
+    one, apart = ev.EvConvNet(net), ev.EvConvNet(net, flags=ev.FLAG_NO_FUSION)
+    assert one.kernel_name(total) == "fused_into_conv_epilogue"
+    rng = np.random.default_rng(c_in)
+    x0 = rng.standard_normal((c_in, h, w)).astype(np.float32)
+    for g in (one, apart):
+        g.profile_begin(100)
+        g.reset(_dev(x0))
+        g.profile_end()
+    assert one.node_time(late)[1] == 1 and one.node_time(total)[1] == 0
+    for share in (0.02, 1.0, 0.0, 0.3):
+        d = _dev(rng.standard_normal(x0.shape) * (rng.random((1, h, w)) < share))
+        for g in (one, apart):
+            g.step(d)
+        for i in range(len(net.nodes)):
+            for kind in (ev.STATE_Z, ev.STATE_OCC, ev.STATE_OCC_TOUCHED, ev.STATE_COUNT):
+                if kind != ev.STATE_Z or net.nodes[i].op not in (wl.OP_CONCAT,):
+                    np.testing.assert_array_equal(one.state(i, kind), apart.state(i, kind), err_msg=f"share {share} node {i} state {kind}")
+        for key in ("y", "dy"):
+            np.testing.assert_array_equal(one.outputs()[0][key].cpu().numpy(), apart.outputs()[0][key].cpu().numpy())
+    one.destroy()
+    apart.destroy()
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("heads,launches,streams", [
     ([2, 2], [0, 1], 1),
     ([2, 2, 2, 2, 2], [0, 0, 0, 1, 1], 1),   # more than a batch holds
