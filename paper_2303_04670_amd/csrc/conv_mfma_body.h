@@ -1,11 +1,12 @@
 // The body of a matrix-core conv workgroup (conv_mfma_impl.h includes it into functions; no include
 // guard).  What the including function declares: the template parameters CHUNK, NW, OPM, MB, MODE, UPS, KSP,
-// S2K, FIVE and PAIR, the arguments p, this workgroup's stream offset so, its tile (or list entry) and channel
+// S2K and PAIR, the arguments p, this workgroup's stream offset so, its tile (or list entry) and channel
 // block wg_tile and wg_ck, and for UPS the stored or up-sampled tile tile_arg with its phase fpy, fpx.
   const bool dense = p.dense != 0;
   constexpr int PARTS = op_parts(OPM);     // bf16 parts of an operand
   constexpr int NB = 32;                   // output channels per workgroup
   constexpr int NT = NW * 64;
+  static_assert(MB == 1 || NW == 4, "whole tiles are for launches that fill the chip with four waves each");
   // LDS site stride in 4-byte words; stride / 4 is odd (the eight sites of a patch row fall into
   // eight distinct 16-byte slots of the banks).  A site holds one plane of CHUNK bf16 per part.
   constexpr int CS = patch_site_words(CHUNK, OPM);
@@ -22,7 +23,6 @@
   static_assert(EP_ITERS >= 1 && EP_SITES <= 32, "epilogue mapping");
   constexpr int NACC = MB * 16;  // accumulator registers of a lane
   constexpr int SLOT = NACC * 64;     // floats per partial-sum slot
-  constexpr int SLOTS = sum_slots(NW, MB);
   constexpr int CSL = CHUNK + 4;      // UPS: site stride of the low-resolution fp32 buffer
   constexpr int LPMAX = 10;           // UPS: a 14-row patch has sources in at most 14 / 2 + 3 rows
   // gathered float4 per thread (a weight-folded workgroup: an (NROWS + 3) x 11 patch, 4 x 4 taps)
@@ -327,7 +327,7 @@
     for (int it = 0; it < EP_ITERS; ++it) z_old[it] = ep_load(z_rsrc, !dense && has(touched_mine, it), it);
   };
   // (variants without registers to spare: after it)
-  constexpr bool LATE_Z = FIVE || (PARTS == 3 && NW == 4 && S2K != 0);
+  constexpr bool LATE_Z = PARTS == 3 && NW == 4 && S2K != 0;
   if (!KSP && !LATE_Z) request_z();
 
   // one float4 of patch channels into the patch buffer, as the operand mode's bf16 parts
@@ -664,7 +664,7 @@
   if (!KSP && LATE_Z) request_z();
   if (!KSP) request_fused();
   EVK_PHASE(kPhFusedRequested);
-  // ---- reduce the NW partial sums through LDS: slots [SLOTS][block*16 + reg][lane]
+  // ---- reduce the NW partial sums through LDS: slots [NW][block*16 + reg][lane]
   // (fp32 mode: the weights are stored times a power of two, those of the odd waves' units negated;
   // see conv_mfma_negated and ConvParams::w_unscale)
   const float unscale = (fold ? p.w_fold_unscale : p.w_unscale) * (pair ? 0.5f : 1.0f);
@@ -676,21 +676,7 @@
     }
   };
   __syncthreads();
-  if (SLOTS == NW) {
-    spill(s_mem + wave * SLOT, wave & 1 ? -unscale : unscale);
-  } else {  // (eight waves of whole tiles: in two steps, for the LDS)
-    if (wave >= 4) spill(s_mem + (wave - 4) * SLOT, 1.0f);
-    __syncthreads();
-    if (wave < 4) {
-      const float* part = s_mem + wave * SLOT;
-#pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        acc0[i] += part[i * 64 + lane];
-        if (MB == 2) acc1[i] += part[(16 + i) * 64 + lane];
-      }
-      spill(s_mem + wave * SLOT, wave & 1 ? -unscale : unscale);
-    }
-  }
+  spill(s_mem + wave * SLOT, wave & 1 ? -unscale : unscale);
   __syncthreads();
   EVK_PHASE(kPhReduced);
 #ifdef EVCONV_PHASE_STAMPS
@@ -720,7 +706,7 @@
     const int off = off_mine + (((it * kRow) >> 2) * 16 + ((it * kRow) & 3) * 4) * 64;
     float part[4];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) part[q] = SLOTS == 8 ? s_mem[off + q * SLOT] + s_mem[off + (q + 4) * SLOT] : s_mem[off + q * SLOT];
+    for (int q = 0; q < 4; ++q) part[q] = NW == 8 ? s_mem[off + q * SLOT] + s_mem[off + (q + 4) * SLOT] : s_mem[off + q * SLOT];
     v_sum[it] = (part[0] + part[1]) + (part[2] + part[3]);
   }
   if (KSP) {

@@ -154,9 +154,6 @@ constexpr int op_parts(int opm) { return opm == kOpF32 ? 3 : opm == kOpSplit ? 2
 // 4-byte words of a patch site in LDS
 constexpr int patch_site_words(int chunk, int opm) { return chunk / 2 * op_parts(opm) + 4; }
 
-// partial-sum slots of a workgroup in LDS
-constexpr int sum_slots(int nw, int mb) { return mb == 2 ? 4 : nw; }
-
 // The three parts of a value beyond the bf16 rounding range, into bits [shift, shift + 16) of h, m,
 // l.  A finite one: the high part is cut off instead of rounded up to infinity.  An infinity goes
 // into the low part alone: the low part is multiplied with the weight's high part only, which is
@@ -190,18 +187,26 @@ __device__ __forceinline__ void split3_large(float x, int shift, unsigned& h, un
 // site is active where one of its four sources is.
 //
 // KSP: the channels are split over p.ks workgroups as well (chunk ranges of p.ks_chunks chunks).
-// FIVE: registers for five waves per SIMD instead of four (see launch_shape).
 // What a workgroup gathers:
 constexpr int kPlain = 0;        // the stored tensor
 constexpr int kInterpolate = 1;  // UPS: the up-sampled tensor, interpolated from the stored one
 constexpr int kFolded = 2;       // UPS: the stored tensor, under weights that hold the up-sampling
 
+// Waves per SIMD that the registers of a variant are held to.  Five where the plain four-wave half tiles reach
+// them (bf16, and split mode in chunks of 64 channels: 88 to 96 registers): launches of 1024 to 1280 and of
+// 2048 to 2560 workgroups are then one round on the chip less.
+constexpr int min_waves(int chunk, int nw, int opm, int mb, int mode, bool ksp, int s2k) {
+  if (mb == 2 || (mode != kPlain && nw == 4)) return 3;
+  if (mode == kPlain && !ksp && s2k == 0 && nw == 4 && (opm == kOpBf16 || (opm == kOpSplit && chunk == 64))) return 5;
+  return 4;
+}
+
 // The body of a workgroup is text that is included twice: into the kernel of the plain convs, whose
 // arguments the compiler knows where they are (through a reference it keeps more of them in scalar
 // registers than there are, 0.2-0.5 us a layer), and into a function for the kernels that choose between
 // bodies.
-template <int CHUNK, int NW, int OPM, int MB, int MODE, bool KSP, int S2K, bool FIVE>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(FIVE ? 5 : MB == 1 && !(MODE != kPlain && NW == 4) ? 4 : 3)))
+template <int CHUNK, int NW, int OPM, int MB, int MODE, bool KSP, int S2K>
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(min_waves(CHUNK, NW, OPM, MB, MODE, KSP, S2K))))
 void conv_mfma_kernel(ConvParams p) {
   touch_params<ConvParams>();
   // (what the prologue needs is loaded together, too: on demand it was a dozen loads, each waited for)
@@ -229,7 +234,7 @@ __device__ __forceinline__ void conv_workgroup(const unsigned args, const int wg
   typedef const char __attribute__((address_space(4))) Byte;
   const auto& p = *(const ConvParams __attribute__((address_space(4)))*)((Byte*)__builtin_amdgcn_kernarg_segment_ptr() + args);
   const size_t so = (size_t)blockIdx.z * p.st.stride;
-  constexpr bool UPS = MODE != kPlain, FIVE = false;
+  constexpr bool UPS = MODE != kPlain;
 #include "conv_mfma_body.h"
 }
 
@@ -312,7 +317,7 @@ ConvLaunch variant_launch(const ConvParams& p) {
   const int PH = (4 * MB - 1) * p.stride + p.k, PW = 7 * p.stride + p.k;
   // (rows of the patch are padded to a pitch of 32 modulo 64 words: at most 64 more per row)
   size_t lds = (size_t)PH * (PW * patch_site_words(CHUNK, OPM) + 64) * sizeof(float);
-  const size_t part = (size_t)sum_slots(NW, MB) * MB * 16 * 64 * sizeof(float);  // partial sums reuse the patch
+  const size_t part = (size_t)NW * MB * 16 * 64 * sizeof(float);  // partial sums reuse the patch
   // The operand that is read by every XCD in full should be the smaller one: the weights of the
   // high-resolution layers, the input of the low-resolution ones (k * k * c_out weights per input
   // channel against one value per stored site per input channel).  Measured on the 32 x 44 -> 64 x
@@ -343,10 +348,10 @@ ConvLaunch variant_launch(const ConvParams& p) {
   return ConvLaunch{q, grid, std::max(lds, part)};
 }
 
-template <int CHUNK, int NW, int OPM, int MB, bool KSP = false, int S2K = 0, bool FIVE = false>
+template <int CHUNK, int NW, int OPM, int MB, bool KSP = false, int S2K = 0>
 void launch_variant(const ConvParams& p, hipStream_t s) {
   const ConvLaunch l = variant_launch<CHUNK, NW, OPM, MB, KSP>(p);
-  if constexpr (CHUNK == 32 && !KSP && S2K == 0 && !FIVE) {
+  if constexpr (CHUNK == 32 && !KSP && S2K == 0) {
     if (p.upsample) {
       if constexpr (OPM != kOpBf16) {  // (weights declared as bf16 are not folded)
         if (p.fold_list) {
@@ -354,50 +359,46 @@ void launch_variant(const ConvParams& p, hipStream_t s) {
           return;
         }
       }
-      hipLaunchKernelGGL((conv_mfma_kernel<CHUNK, NW, OPM, MB, kInterpolate, false, 0, false>), l.grid, dim3(NW * 64), l.lds, s, l.q);
+      hipLaunchKernelGGL((conv_mfma_kernel<CHUNK, NW, OPM, MB, kInterpolate, false, 0>), l.grid, dim3(NW * 64), l.lds, s, l.q);
       return;
     }
   }
-  hipLaunchKernelGGL((conv_mfma_kernel<CHUNK, NW, OPM, MB, kPlain, KSP, S2K, FIVE>), l.grid, dim3(NW * 64), l.lds, s, l.q);
+  hipLaunchKernelGGL((conv_mfma_kernel<CHUNK, NW, OPM, MB, kPlain, KSP, S2K>), l.grid, dim3(NW * 64), l.lds, s, l.q);
 }
 
 // share of the chip's 256 CUs kept busy when n equally long workgroups run at once
 inline double fill(long long n) { return (double)n / 256.0 / (double)((n + 255) / 256); }
 
-template <int CHUNK, int OPM>
-void launch_shape(const ConvParams& p, hipStream_t s) {
+// The variant that a conv takes which does not split its channels: channels per chunk, half or whole tiles, four
+// or eight waves.
+struct Shape { int chunk; bool halves, eight; };
+inline Shape shape_for(const ConvParams& p) {
+  const int chunk = chunk_for(p);
   const long long n2 = (long long)p.go.tiles() * (p.c_out_pad / 32) * p.st.n;  // workgroups with whole tiles
+  if (chunk == 128) return {chunk, true, true};  // chosen only for few workgroups
+  if (p.stride == 2 && chunk != 16) return {chunk, true, 2 * n2 < 512};
   // Whole tiles (two accumulators per wave, every weight fragment used twice) pay off only when
   // the launch fills the chip several times over and a workgroup has a long contraction; measured
   // on the layers of the evaluation networks, half tiles win everywhere else (more, shorter
   // workgroups: shorter prologues and patches, better balance)
-  bool halves = !(n2 >= 512 && p.k * p.k * p.gi.c >= 1600) || fill(2 * n2) > fill(n2) + 0.1;
-  const long long n = halves ? 2 * n2 : n2;
-  bool eight = n < 512;  // few workgroups: 8 waves each split K further
-  if (p.stride == 2 && (CHUNK == 32 || CHUNK == 64)) {
-    constexpr int C2 = CHUNK == 32 ? 32 : 64, K2 = CHUNK == 32 ? 5 : 3;
-    if (2 * n2 < 512) launch_variant<C2, 8, OPM, 1, false, K2>(p, s);
-    else launch_variant<32, 4, OPM, 1, false, 5>(p, s);
-    return;
-  }
-  if (CHUNK == 128) {  // chosen only for few workgroups: other variants are not built
+  const bool halves = !(n2 >= 512 && p.k * p.k * p.gi.c >= 1600) || fill(2 * n2) > fill(n2) + 0.1;
+  return {chunk, halves, halves && 2 * n2 < 512};  // few workgroups: 8 waves each split K further
+}
+
+template <int CHUNK, int OPM>
+void launch_shape(const ConvParams& p, const Shape& shape, hipStream_t s) {
+  if constexpr (CHUNK == 128) {
     launch_variant<CHUNK, 8, OPM, 1>(p, s);
-    return;
-  }
-  constexpr int NW4 = CHUNK == 128 ? 8 : 4, MB2 = CHUNK == 128 ? 1 : 2;
-  // Four-wave half tiles with the shorter contractions are 5 registers above what five workgroups per
-  // CU leave.  A variant that requests the old z values after the contraction instead of before it fits;
-  // it takes the launches of 1024 to 1280 workgroups, which are then one round on the chip instead of
-  // two, and those of 2048 to 2560, two instead of three (bf16, 5 x 5: 320 -> 320 on 64 x 64, 1280 workgroups,
-  // 60.0 -> 46.1 us; split, 3 x 3: 320 -> 320 on 64 x 64 44.3 -> 37.7).
-  constexpr bool kFive = (OPM == kOpBf16 && CHUNK == 32) || (OPM == kOpSplit && CHUNK == 64);
-  const bool five = kFive && !p.upsample && n <= 2560 && (n + 1279) / 1280 < (n + 1023) / 1024;
-  if (halves) {
-    if (eight) launch_variant<CHUNK, 8, OPM, 1>(p, s);
-    else if (five) launch_variant<CHUNK, NW4, OPM, 1, false, 0, kFive>(p, s);
-    else launch_variant<CHUNK, NW4, OPM, 1>(p, s);
   } else {
-    if (eight) launch_variant<CHUNK, 8, OPM, MB2>(p, s); else launch_variant<CHUNK, NW4, OPM, MB2>(p, s);
+    if (p.stride == 2 && CHUNK != 16) {
+      constexpr int C2 = CHUNK == 32 ? 32 : 64, K2 = CHUNK == 32 ? 5 : 3;
+      if (shape.eight) launch_variant<C2, 8, OPM, 1, false, K2>(p, s);
+      else launch_variant<32, 4, OPM, 1, false, 5>(p, s);
+      return;
+    }
+    if (shape.eight) launch_variant<CHUNK, 8, OPM, 1>(p, s);
+    else if (shape.halves) launch_variant<CHUNK, 4, OPM, 1>(p, s);
+    else launch_variant<CHUNK, 4, OPM, 2>(p, s);
   }
 }
 
@@ -447,11 +448,12 @@ void launch_any(const ConvParams& p, hipStream_t s) {
     else launch_variant<32, 8, OPM, 1, true, 5>(q, s);
     return;
   }
-  switch (chunk_for(p)) {
-    case 128: launch_shape<128, OPM>(p, s); break;
-    case 64: launch_shape<64, OPM>(p, s); break;
-    case 32: launch_shape<32, OPM>(p, s); break;
-    default: launch_shape<16, OPM>(p, s); break;
+  const Shape shape = shape_for(p);
+  switch (shape.chunk) {
+    case 128: launch_shape<128, OPM>(p, shape, s); break;
+    case 64: launch_shape<64, OPM>(p, shape, s); break;
+    case 32: launch_shape<32, OPM>(p, shape, s); break;
+    default: launch_shape<16, OPM>(p, shape, s); break;
   }
 }
 
@@ -465,7 +467,8 @@ inline bool pairable(const ConvParams& p) {
   if (p.stride != 2 || p.upsample) return false;
   const KSplit r = ksplit_for(p);
   if (r.ks) return r.chunk == 64;
-  return chunk_for(p) == 64 && 2ll * p.go.tiles() * (p.c_out_pad / 32) * p.st.n < 512;
+  const Shape shape = shape_for(p);
+  return shape.chunk == 64 && shape.eight;
 }
 inline bool pair_supported(const ConvParams& a, const ConvParams& b) {
   return pairable(a) && pairable(b) && !(ksplit_for(a).ks && ksplit_for(b).ks) && a.st.n == b.st.n;
@@ -488,16 +491,15 @@ void launch_pair(const ConvParams& a, const ConvParams& b, hipStream_t s) {
 // The gate convs of a recurrent cell read one tensor.  In one launch the last, partly filled round of
 // workgroups and the start of the next launch come once instead of four times (the four convs of a
 // ConvLSTM cell, 69 -> 64 channels on 256 x 352, fp32: 192 -> 168 us).  For the variant of four-wave half
-// tiles with 32-channel chunks, the one such layers take.  Whole cells, a launch each / one launch, us:
+// tiles with 32-channel chunks, the one such layers take; whole cells, a launch each / one launch, us:
 // fp32, 64 channels on 96 x 88 107 / 89, on 360 x 360 744 / 708, 4 streams on 256 x 352 1206 / 1198; split, 64
 // on 96 x 88 100 / 83, on 256 x 352 381 / 354, on 360 x 360 675 / 662; bf16, 64 on 256 x 352 (5632 workgroups
-// per conv) 327 / 320, on 360 x 360 (8100) 609 / 616: bf16 up to 6144 workgroups, and above those that take
-// the variant for five waves per SIMD.
+// per conv) 327 / 320, on 360 x 360 (8100) 609 / 616: bf16 up to 6144 workgroups.
 inline bool batchable(const ConvParams& p, bool bf16) {
-  if (p.stride != 1 || p.upsample || ksplit_for(p).ks || chunk_for(p) != 32) return false;
-  const long long n2 = (long long)p.go.tiles() * (p.c_out_pad / 32) * p.st.n;
-  const bool halves = !(n2 >= 512 && p.k * p.k * p.gi.c >= 1600) || fill(2 * n2) > fill(n2) + 0.1;
-  return halves && 2 * n2 >= (bf16 ? 2561 : 512) && 2 * n2 <= (bf16 ? 6144 : 1 << 22);
+  if (p.stride != 1 || p.upsample || ksplit_for(p).ks) return false;
+  const Shape shape = shape_for(p);
+  const long long n = 2ll * p.go.tiles() * (p.c_out_pad / 32) * p.st.n;
+  return shape.chunk == 32 && shape.halves && !shape.eight && (!bf16 || (n > 2560 && n <= 6144));
 }
 template <int OPM>
 void launch_batch(const ConvParams* convs, int n, hipStream_t s) {
