@@ -1,6 +1,6 @@
 // The body of a matrix-core conv workgroup (conv_mfma_impl.h includes it into functions; no include
 // guard).  What the including function declares: the template parameters CHUNK, NW, OPM, MB, MODE, UPS, KSP,
-// S2K and PAIR, the arguments p, this workgroup's stream offset so, its tile (or list entry) and channel
+// S2K, PAIR and LATE, the arguments p, this workgroup's stream offset so, its tile (or list entry) and channel
 // block wg_tile and wg_ck, and for UPS the stored or up-sampled tile tile_arg with its phase fpy, fpx.
   const bool dense = p.dense != 0;
   constexpr int PARTS = op_parts(OPM);     // bf16 parts of an operand
@@ -327,7 +327,7 @@
     for (int it = 0; it < EP_ITERS; ++it) z_old[it] = ep_load(z_rsrc, !dense && has(touched_mine, it), it);
   };
   // (variants without registers to spare: after it)
-  constexpr bool LATE_Z = PARTS == 3 && NW == 4 && S2K != 0;
+  constexpr bool LATE_Z = LATE || (PARTS == 3 && NW == 4 && S2K != 0);
   if (!KSP && !LATE_Z) request_z();
 
   // one float4 of patch channels into the patch buffer, as the operand mode's bf16 parts

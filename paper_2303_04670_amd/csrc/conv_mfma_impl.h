@@ -221,14 +221,15 @@ void conv_mfma_kernel(ConvParams p) {
   // output channels (wg_swap): an XCD sees all tiles and one in eight (four, two) of the weight
   // blocks.  The launcher picks whichever of the two operands is larger to be split.
   const int wg_tile = p.wg_swap ? blockIdx.y : blockIdx.x, wg_ck = p.wg_swap ? blockIdx.x : blockIdx.y;
-  constexpr bool UPS = MODE != kPlain, PAIR = false;
+  constexpr bool UPS = MODE != kPlain, PAIR = false, LATE = false;
   const int tile_arg = wg_tile / (2 / MB);
   constexpr int fpy = 0, fpx = 0;
 #include "conv_mfma_body.h"
 }
 
 // args: byte offset of this workgroup's ConvParams in the kernel arguments
-template <int CHUNK, int NW, int OPM, int MB, int MODE, bool KSP, int S2K, bool PAIR>
+// LATE: old z values are requested after the contraction, which leaves registers for one more wave per SIMD
+template <int CHUNK, int NW, int OPM, int MB, int MODE, bool KSP, int S2K, bool PAIR, bool LATE = false>
 __device__ __forceinline__ void conv_workgroup(const unsigned args, const int wg_tile, const int wg_ck, const int tile_arg,
                                                const int fpy, const int fpx) {
   typedef const char __attribute__((address_space(4))) Byte;
@@ -271,7 +272,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void c
 // first[i] is the first of conv i.
 struct ConvBatch { ConvParams p[kMaxConvBatch]; int first[kMaxConvBatch]; int n; };
 template <int OPM>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void conv_mfma_batch_kernel(ConvBatch q) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(OPM == kOpBf16 ? 5 : 4))) void conv_mfma_batch_kernel(ConvBatch q) {
   int i = 0;
 #pragma unroll
   for (int j = 1; j < kMaxConvBatch; ++j)
@@ -283,7 +284,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void c
   const auto& p = *(const ConvParams __attribute__((address_space(4)))*)(base + args);
   const int wg = (int)blockIdx.x - *(const int __attribute__((address_space(4)))*)(base + offsetof(ConvBatch, first) + i * sizeof(int));
   const int y = wg / p.grid_x, x = wg - y * p.grid_x;
-  conv_workgroup<32, 4, OPM, 1, kPlain, false, 0, false>(args, p.wg_swap ? y : x, p.wg_swap ? x : y, 0, 0, 0);
+  conv_workgroup<32, 4, OPM, 1, kPlain, false, 0, false, OPM == kOpBf16>(args, p.wg_swap ? y : x, p.wg_swap ? x : y, 0, 0, 0);
 }
 
 inline int chunk_for(const ConvParams& p) {
@@ -491,15 +492,15 @@ void launch_pair(const ConvParams& a, const ConvParams& b, hipStream_t s) {
 // The gate convs of a recurrent cell read one tensor.  In one launch the last, partly filled round of
 // workgroups and the start of the next launch come once instead of four times (the four convs of a
 // ConvLSTM cell, 69 -> 64 channels on 256 x 352, fp32: 192 -> 168 us).  For the variant of four-wave half
-// tiles with 32-channel chunks, the one such layers take; whole cells, a launch each / one launch, us:
-// fp32, 64 channels on 96 x 88 107 / 89, on 360 x 360 744 / 708, 4 streams on 256 x 352 1206 / 1198; split, 64
-// on 96 x 88 100 / 83, on 256 x 352 381 / 354, on 360 x 360 675 / 662; bf16, 64 on 256 x 352 (5632 workgroups
-// per conv) 327 / 320, on 360 x 360 (8100) 609 / 616: bf16 up to 6144 workgroups.
-inline bool batchable(const ConvParams& p, bool bf16) {
+// tiles with 32-channel chunks, the one such layers take.  A launch each / one launch, over 612 cells of two to
+// four convs with equal and with different kernels (1 x 1 to 7 x 7, 64 x 72 to 480 x 640), ms in all: fp32 87.4 /
+// 84.7, split 75.0 / 72.4, bf16 65.0 / 62.5; none is slower by more than the spread.  (bf16 takes old z late
+// here, 91 registers instead of 99 and five waves per SIMD as alone: with four, cells of more than 8000
+// workgroups per conv were up to 7 % slower than a launch each.)
+inline bool batchable(const ConvParams& p) {
   if (p.stride != 1 || p.upsample || ksplit_for(p).ks) return false;
   const Shape shape = shape_for(p);
-  const long long n = 2ll * p.go.tiles() * (p.c_out_pad / 32) * p.st.n;
-  return shape.chunk == 32 && shape.halves && !shape.eight && (!bf16 || (n > 2560 && n <= 6144));
+  return shape.chunk == 32 && shape.halves && !shape.eight;
 }
 template <int OPM>
 void launch_batch(const ConvParams* convs, int n, hipStream_t s) {

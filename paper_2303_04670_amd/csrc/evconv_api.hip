@@ -1064,9 +1064,8 @@ evconv_status create_impl(const evconv_net_desc* desc, const void* weights, size
         if (first.kernel != late.kernel || first.d.in0 != late.d.in0 || first.paired_into >= 0) continue;
         const ConvParams p = probe_of(first), q = probe_of(late);
         const bool shortcut = late.d.kh == 1 && first.n_mates == 0 && conv_mfma_pair_supported(p, q);
-        const bool bf16 = late.kernel == kKernConvMfmaBf16;
         const bool batch = (first.n_mates == 0 || first.mates_batch) && first.n_mates < kMaxConvBatch - 1 &&
-                           conv_mfma_batch_supported(p, bf16) && conv_mfma_batch_supported(q, bf16);
+                           conv_mfma_batch_supported(p) && conv_mfma_batch_supported(q);
         if (!shortcut && !batch) continue;
         bool delayed_between = false;  // (a DELAY of the later one in between must see last step's buffers)
         for (int dn = i + 1; dn < j; ++dn)

@@ -1495,12 +1495,89 @@ def test_shortcut_conv_in_the_first_convs_launch(c_in, c_out, h, w, wd, streams,
     apart.destroy()
 
 
+def _merged_net(kind):
+    """(net, {conv: launches of its own}, {node: how it is run}) for launches that hold several convs."""
+    if kind == "lstm":             # gates of a real cell
+        net = wl.net_convlstm(1008, h=96, w=88, hidden=64)
+        gates = [i for i, n in enumerate(net.nodes) if n.op == wl.OP_CONV2D][:4]
+        return net, dict(zip(gates, (1, 0, 0, 0))), {}
+    pair = kind.startswith("pair")
+    c, h, w = (64, 56, 50) if pair else (32, 136, 124)
+    b = wl._NetBuilder(kind, c, h, w, 11, bias=True, sparsify="sparsify" in kind, sparsify_k=0.05)
+    if kind == "delay":            # a delay of the second conv between the two: it must see the previous step's
+        x = b.conv(-1, c, 3)
+        prev = b.delay(c, like=x)
+        y = b.conv(-1, c, 3, act=wl.ACT_TANH)
+        b.close_delay(prev, y)
+        b.simple(wl.OP_ADD, b.simple(wl.OP_MUL, x, prev), y, act=wl.ACT_RELU, out=1)
+        return b.finish(), {x: 1, y: 1}, {}
+    if kind == "mixed":            # different kernels
+        ids = [b.conv(-1, c, k, act=wl.ACT_RELU, out=1) for k in (3, 1, 5, 7)]
+        return b.finish(), dict(zip(ids, (1, 0, 0, 0))), {}
+    early = b.simple(wl.OP_MAXPOOL, -1, k=3, stride=2, pad=1) if pair else b.simple(wl.OP_ACT, -1, act=wl.ACT_TANH)
+    x = b.conv(-1, c, 3, 2 if pair else 1, act=wl.ACT_RELU)
+    y = b.conv(-1, c, 1 if pair else 3, 2 if pair else 1, act=wl.ACT_NONE)
+    if "add" in kind:              # both convs host an ADD with an earlier tensor, the second one two
+        sx, sy = b.simple(wl.OP_ADD, x, early, act=wl.ACT_RELU, out=1), b.simple(wl.OP_ADD, early, y)
+        sy2 = b.simple(wl.OP_ADD, sy, early, act=wl.ACT_TANH, out=1)
+        fused = (sx, sy, sy2)
+    else:                          # both host a sparsification layer, the second one behind an ADD
+        sy = b.simple(wl.OP_ADD, y, early, act=wl.ACT_RELU)
+        b.conv(x, 16, 1, 1, 0, out=1)
+        b.conv(sy, 16, 1, 1, 0, out=1)
+        fused = [sy] + [i for i, n in enumerate(b.nodes) if n.op == wl.OP_SPARSIFY]
+        assert len(fused) == 3
+    return b.finish(), {x: 1, y: 0}, {i: "fused_into_conv_epilogue" for i in fused}
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("kind", ["lstm", "delay", "mixed", "batch_add", "batch_sparsify", "pair_add", "pair_sparsify"])
+def test_merged_convs_with_epilogues_and_delays(kind):
+    """Convs in one launch that host ADDs and sparsification layers, of different kernels, beside DELAY nodes:
+    every sum, set and result bit for bit as with a launch per node, through sparse and dense steps, a dense
+    recompute and a refresh."""
+    net, launches, names = _merged_net(kind)
+    one, apart = ev.EvConvNet(net), ev.EvConvNet(net, flags=ev.FLAG_NO_FUSION)
+    rng = np.random.default_rng(len(kind))
+    shape = (net.in_c, net.in_h, net.in_w)
+    x0 = _dev(rng.standard_normal(shape))
+    for g in (one, apart):
+        g.profile_begin(200)
+        g.reset(x0)
+        g.profile_end()
+    assert {i: one.node_time(i)[1] for i in launches} == launches
+    assert {i: one.kernel_name(i) for i in names} == names
+    for step, (share, mode) in enumerate(((0.01, ev.MODE_INCREMENTAL), (0.4, ev.MODE_INCREMENTAL), (0.1, ev.MODE_DENSE_RECOMPUTE),
+                                          (0.02, ev.MODE_INCREMENTAL), (0.0, ev.MODE_INCREMENTAL), (1.0, ev.MODE_INCREMENTAL),
+                                          (0.02, ev.MODE_INCREMENTAL))):
+        d = _dev(rng.standard_normal(shape) * (rng.random((1,) + shape[1:]) < share))
+        for g in (one, apart):
+            g.set_refresh_period(1 if step == 3 else 0)
+            g.set_mode(mode)
+            g.step(d)
+        for i, n in enumerate(net.nodes):
+            kinds = [ev.STATE_DY, ev.STATE_OCC, ev.STATE_OCC_TOUCHED, ev.STATE_COUNT]
+            if n.op in (wl.OP_CONV2D, wl.OP_MUL, wl.OP_SPARSIFY, wl.OP_DELAY) or n.act != wl.ACT_NONE:
+                kinds.append(ev.STATE_Z)
+            for k in kinds:
+                u, v = one.state(i, k), apart.state(i, k)
+                if k == ev.STATE_DY and share < 1.0 and mode == ev.MODE_INCREMENTAL and step != 3:
+                    touched = one.site_list(i)   # (an increment is defined at the active sites only)
+                    u, v = u.reshape(-1, u.shape[-1])[touched], v.reshape(-1, v.shape[-1])[touched]
+                np.testing.assert_array_equal(u, v, err_msg=f"step {step} node {i} state {k}")
+        for o, r in zip(one.outputs(), apart.outputs()):
+            for key in ("y", "dy"):
+                np.testing.assert_array_equal(o[key].cpu().numpy(), r[key].cpu().numpy(), err_msg=f"step {step} node {o['node']} {key}")
+    one.destroy()
+    apart.destroy()
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("c_in,c_out,h,w,k2,stride,between", [
     (64, 128, 40, 40, 1, 2, "act"),      # a block's shortcut; its ADD's other input is an activation of the first conv
-    (64, 64, 120, 112, 3, 1, "mul"),     # two gate convs, the other input a product of the first one
-    (64, 64, 120, 112, 3, 1, "concat"),  # the other input a narrow conv's
-    (64, 64, 120, 112, 3, 1, "sum"),     # ADD of both
+    (36, 64, 120, 112, 3, 1, "mul"),     # two gate convs, the other input a product of the first one
+    (36, 64, 120, 112, 3, 1, "concat"),  # the other input a narrow conv's
+    (36, 64, 120, 112, 3, 1, "sum"),     # ADD of both
 ])
 def test_a_conv_that_hosts_an_add_is_not_moved_away_from_it(c_in, c_out, h, w, k2, stride, between):
     """A conv that could run in an earlier conv's launch, but whose epilogue computes an ADD with an input that
@@ -1594,6 +1671,8 @@ def test_prediction_heads_in_one_launch(heads, launches, streams):
     (32, 40, 61, 75, wl.WD_F32, 2, 5, [1, 0, 0, 0, 1]),       # one more than a batch, ragged blocks and tiles
     (32, 64, 160, 176, wl.WD_F32_SPLIT, 2, 2, [1, 0]),
     (36, 64, 160, 176, wl.WD_BF16, 2, 3, [1, 0, 0]),
+    (36, 64, 96, 96, wl.WD_BF16, 1, 2, [1, 0]),               # 576 workgroups per conv
+    (36, 64, 320, 328, wl.WD_BF16, 1, 2, [1, 0]),             # 6560
     (32, 32, 24, 24, wl.WD_F32, 1, 2, [1, 1]),                # too few workgroups: another variant
 ])
 def test_convs_of_one_tensor_in_one_launch(c_in, c_out, h, w, wd, streams, n, launches):
