@@ -106,12 +106,12 @@ def hbm_rows(np, ev, wl, g, net, n_streams):
     write + increment write + the occupancy words it clears; narrow conv and 1x1 head = per touched
     output site c_in x 4 x halo factor read + c_out x 12 (old z, new z, increment) [+ c_out x 8 for
     the public y / dy of an output head]; list compaction = 8 bytes per tile read + 4 bytes per
-    listed site + counts and bitmaps."""
-    rows = []
+    listed site + counts and bitmaps.  Where heads share a launch, one row holds all of them."""
+    rows, passes = [], g.node_time(len(net.nodes))[1]
     shapes = [g.shape(i) for i in range(len(net.nodes))]
 
-    def row(name, node, nbytes):
-        ms, n = g.node_time(node)
+    def row(name, node, nbytes, timed=None):
+        ms, n = timed or g.node_time(node)
         if n == 0 or ms <= 0:
             return
         us = ms / n * 1e3
@@ -121,7 +121,7 @@ def hbm_rows(np, ev, wl, g, net, n_streams):
     c, h, w = net.in_c, net.in_h, net.in_w
     tiles_all = sum(-(-s[1] // 8) * -(-s[2] // 8) for s in shapes)
     row("builder_kernel", -1, 4 * c * h * w * 4 + 2 * tiles_all * 8 + -(-h // 8) * -(-w // 8) * 8)
-    listed = 0
+    listed, heads = 0, []
     for i, nd in enumerate(net.nodes):
         name = g.kernel_name(i)
         if name.startswith("fused_into_conv_g") or name.startswith("fused_into_conv_w") or name.startswith("fused_into_concat"):
@@ -131,7 +131,16 @@ def hbm_rows(np, ev, wl, g, net, n_streams):
         if name in ("conv_narrow_mfma_f32", "conv_pointwise_f32"):
             halo = ((8 - 1) * nd.stride + nd.k) ** 2 / 64.0
             per_site = nd.c_in * 4 * halo + nd.c_out * 12 + (nd.c_out * 8 if nd.is_output else 0)
-            row(name, i, per_site * st.n_touched + nd.k * nd.k * nd.c_in * nd.c_out * 4)
+            nbytes = per_site * st.n_touched + nd.k * nd.k * nd.c_in * nd.c_out * 4
+            if name == "conv_pointwise_f32":
+                heads.append((i, nbytes))
+            else:
+                row(name, i, nbytes)
+    if all(g.node_time(i)[1] for i, _ in heads):
+        for i, nbytes in heads:
+            row("conv_pointwise_f32", i, nbytes)
+    else:
+        row("conv_pointwise_f32", heads[-1][0], sum(b for _, b in heads), (sum(g.node_time(i)[0] for i, _ in heads), passes))
     listed += int(g.state(-1, ev.STATE_COUNT)[0])
     n_sets = len(net.nodes) + 1
     row("build_lists_kernel", len(net.nodes), (tiles_all + -(-h // 8) * -(-w // 8)) * 8 + listed * 4 + n_sets * 4 + (tiles_all // 64 + n_sets) * 8)
@@ -166,10 +175,13 @@ def run_variant(args, np, torch, ev, wl, variant, dframes, with_dense, with_laye
     torch.cuda.synchronize()
     dt_prof = time.perf_counter() - t0
     g.profile_end()
-    fam, layers = {}, []
+    fam, layers, passes = {}, [], g.node_time(len(net.nodes))[1]
     for i, nd in enumerate(net.nodes):
         ms, n = g.node_time(i)
         name = g.kernel_name(i)
+        # (a conv that runs in another node's launch: its work is done in every pass, its time is that node's)
+        merged = n == 0 and name.startswith("conv")
+        runs = passes if merged else n
         st = g.stats(i)
         per_site = 2.0 * nd.k * nd.k * nd.c_in * nd.c_out if nd.op in (wl.OP_CONV2D, wl.OP_LINEAR) else 0.0
         flops = per_site * st.n_touched            # algorithmic: touched output sites of the last step
@@ -188,11 +200,11 @@ def run_variant(args, np, torch, ev, wl, variant, dframes, with_dense, with_laye
         f = fam.setdefault(name, dict(ms=0.0, launches=0, flops=0.0, executed=0.0))
         f["ms"] += ms
         f["launches"] += n
-        f["flops"] += flops * n
-        f["executed"] += executed * n
+        f["flops"] += flops * runs
+        f["executed"] += executed * runs
         layers.append(dict(node=i, kernel=name, ms_avg=ms / max(n, 1), touched=st.n_touched, sites=st.n_sites,
                            active=st.n_active, touched_tiles=st.n_touched_tiles, tiles=st.n_tiles,
-                           gflop_alg=flops / 1e9))
+                           gflop_alg=flops / 1e9, in_another_launch=merged))
     dom = max((k for k in fam if k.startswith("conv")), key=lambda k: fam[k]["ms"])
     bound, peak, unit, products = PEAKS[dom]
     achieved = fam[dom]["flops"] / (fam[dom]["ms"] * 1e-3) / 1e12 if fam[dom]["ms"] > 0 else 0.0
@@ -453,7 +465,7 @@ def phase_time_tables(args, np, torch, ev, wl, dev):
     csrc/conv_mfma_impl.h), the workgroup's life and the span of the launch."""
     frames = [torch.from_numpy(f).to(dev) for f in wl.stream_voxel(1003, 256, 352, 10, args.density)]
     order = [0, 1, 2, 3, 4, 5, 6, 10, 7, 14, 8, 11, 12, 13, 9]   # the stamps in program order
-    names = ["occupancy words", "bit rows", "touched set, old z, gather predicates", "first requests",
+    names = ["occupancy bytes", "bit rows", "first patch requested, touched set, old z", "first weights requested",
              "first patch in LDS", "chunk loop", "fused operands requested", "partial sums reduced", "operands arrived",
              "epilogue passes", "flag ballots", "flags to LDS", "barrier", "tile words"]
     out = []
