@@ -327,7 +327,7 @@
     for (int it = 0; it < EP_ITERS; ++it) z_old[it] = ep_load(z_rsrc, !dense && has(touched_mine, it), it);
   };
   // (variants without registers to spare: after it)
-  constexpr bool LATE_Z = LATE || (PARTS == 3 && NW == 4 && S2K != 0);
+  constexpr bool LATE_Z = LATE || (PARTS == 3 && NW == 4 && S2K == 5);
   if (!KSP && !LATE_Z) request_z();
 
   // one float4 of patch channels into the patch buffer, as the operand mode's bf16 parts
@@ -442,13 +442,13 @@
   // Units of a chunk: (tap u / kgn, channel group u % kgn), kgn = KG groups of 16 channels or, with
   // p.tail_units in a last chunk that c_in does not fill, as many as hold channels; unit
   // u_j = wave + j * NW is this wave's j-th.
-  constexpr bool TAIL = !UPS && !KSP && S2K == 0 && CHUNK == 32;  // the other variants' chunks are full or one group
+  constexpr bool TAIL = !UPS && !KSP && S2K <= 0 && CHUNK == 32;  // the other variants' chunks are full or one group
   // bf16 and split modes, stride 2: the order of the sums is that of chunks of 16 channels (the taps
   // dealt to the waves, one group of 16 channels after the other), whichever chunk the launcher
   // takes.  The rounding of the next layer's operands turns a last-bit difference of an fp32 sum
   // into one of 16 (8) bits, so a launch shape that reordered them would show: the depth net in bf16
   // by 3.5e-3.
-  const bool groups_in_order = S2K != 0 && PARTS != 3 && (!KSP || (PAIR && p.ks == 1));
+  const bool groups_in_order = S2K > 0 && PARTS != 3 && (!KSP || (PAIR && p.ks == 1));
   // fp32 mode, chunks of one unit (1 x 1 taps, 16 channels): waves 0 and 1 contract all of them, wave 1
   // with the weights negated in registers, and half of their difference is the sum (conv_mfma_negated)
   const bool pair = PARTS == 3 && CHUNK == 16 && K == 1;

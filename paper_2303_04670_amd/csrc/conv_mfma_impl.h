@@ -137,10 +137,11 @@ __device__ __forceinline__ unsigned pack_bf16x2(float lo, float hi) {
 
 // Largest halo patch (sites) a variant can meet: 64- and 128-channel chunks are used with stride 1
 // and taps <= 3, 32-channel chunks with stride 1 (taps <= 7), 16-channel chunks also with stride 2.
-// (s2k: 0, or the largest kernel of a stride-2 variant with chunks of more than 16 channels)
+// (s2k: 0, or the largest kernel of a variant for stride 2, or minus that of one for stride 1)
 constexpr int max_patch_sites(int chunk, int mb, int s2k) {
   const int rows = 4 * mb - 1;
-  if (s2k) return (rows * 2 + s2k) * (14 + s2k);
+  if (s2k > 0) return (rows * 2 + s2k) * (14 + s2k);
+  if (s2k < 0) return (rows - s2k) * (7 - s2k);
   return chunk >= 64 ? (rows + 3) * 10 : chunk == 32 ? (rows + 7) * 14 : (rows * 2 + 7) * 21;
 }
 
@@ -187,6 +188,7 @@ __device__ __forceinline__ void split3_large(float x, int shift, unsigned& h, un
 // site is active where one of its four sources is.
 //
 // KSP: the channels are split over p.ks workgroups as well (chunk ranges of p.ks_chunks chunks).
+// S2K: the largest kernel of a variant for stride 2, minus that of one for stride 1, or 0: any (launch_shape).
 // What a workgroup gathers:
 constexpr int kPlain = 0;        // the stored tensor
 constexpr int kInterpolate = 1;  // UPS: the up-sampled tensor, interpolated from the stored one
@@ -197,7 +199,7 @@ constexpr int kFolded = 2;       // UPS: the stored tensor, under weights that h
 // 2048 to 2560 workgroups are then one round on the chip less.
 constexpr int min_waves(int chunk, int nw, int opm, int mb, int mode, bool ksp, int s2k) {
   if (mb == 2 || (mode != kPlain && nw == 4)) return 3;
-  if (mode == kPlain && !ksp && s2k == 0 && nw == 4 && (opm == kOpBf16 || (opm == kOpSplit && chunk == 64))) return 5;
+  if (mode == kPlain && !ksp && s2k <= 0 && nw == 4 && (opm == kOpBf16 || (opm == kOpSplit && chunk == 64))) return 5;
   return 4;
 }
 
@@ -271,7 +273,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void c
 // Up to four convs of the same tensor and one variant in one launch (see launch_batch): workgroup
 // first[i] is the first of conv i.
 struct ConvBatch { ConvParams p[kMaxConvBatch]; int first[kMaxConvBatch]; int n; };
-template <int OPM>
+template <int OPM, int S2K>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(OPM == kOpBf16 ? 5 : 4))) void conv_mfma_batch_kernel(ConvBatch q) {
   int i = 0;
 #pragma unroll
@@ -284,7 +286,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(OPM == kOpB
   const auto& p = *(const ConvParams __attribute__((address_space(4)))*)(base + args);
   const int wg = (int)blockIdx.x - *(const int __attribute__((address_space(4)))*)(base + offsetof(ConvBatch, first) + i * sizeof(int));
   const int y = wg / p.grid_x, x = wg - y * p.grid_x;
-  conv_workgroup<32, 4, OPM, 1, kPlain, false, 0, false, OPM == kOpBf16>(args, p.wg_swap ? y : x, p.wg_swap ? x : y, 0, 0, 0);
+  conv_workgroup<32, 4, OPM, 1, kPlain, false, S2K, false, OPM == kOpBf16>(args, p.wg_swap ? y : x, p.wg_swap ? x : y, 0, 0, 0);
 }
 
 inline int chunk_for(const ConvParams& p) {
@@ -386,21 +388,41 @@ inline Shape shape_for(const ConvParams& p) {
   return {chunk, halves, halves && 2 * n2 < 512};  // few workgroups: 8 waves each split K further
 }
 
+// Variants for the small kernels: what a thread gathers of a patch is then as many registers and conversions as
+// the patch needs.  In the variants for any kernel a thread takes its items in pairs, also where it has one
+// (1 x 1) or three (3 x 3 at stride 2), and holds the registers of a 7 x 7 patch.  us, in those / in these, fp32: 1 x 1,
+// 288 -> 288 on 256 x 352 322 / 244, 160 -> 64 on 128 x 128 15.2 / 13.3; 3 x 3 at stride 2, 128 -> 128 on 256 x 352 61.7 /
+// 56.4; 3 x 3, 69 -> 64 on 64 x 88 13.9 / 13.0.
+template <int CHUNK, int OPM, int S2K>
+void launch_bound(const ConvParams& p, const Shape& shape, hipStream_t s) {
+  if (shape.eight) launch_variant<CHUNK, 8, OPM, 1, false, S2K>(p, s);
+  else if constexpr (CHUNK < 128) {
+    if (shape.halves) launch_variant<CHUNK, 4, OPM, 1, false, S2K>(p, s);
+    else launch_variant<CHUNK, 4, OPM, 2, false, S2K>(p, s);
+  }
+}
 template <int CHUNK, int OPM>
 void launch_shape(const ConvParams& p, const Shape& shape, hipStream_t s) {
-  if constexpr (CHUNK == 128) {
-    launch_variant<CHUNK, 8, OPM, 1>(p, s);
-  } else {
-    if (p.stride == 2 && CHUNK != 16) {
-      constexpr int C2 = CHUNK == 32 ? 32 : 64, K2 = CHUNK == 32 ? 5 : 3;
-      if (shape.eight) launch_variant<C2, 8, OPM, 1, false, K2>(p, s);
+  if constexpr (CHUNK == 32 || CHUNK == 64) {
+    if (p.stride == 2) {
+      constexpr int K2 = CHUNK == 32 ? 5 : 3;
+      if (p.k == 1 && shape.eight) launch_variant<CHUNK, 8, OPM, 1, false, 1>(p, s);
+      else if (p.k == 1) launch_variant<32, 4, OPM, 1, false, 1>(p, s);
+      else if (shape.eight) launch_variant<CHUNK, 8, OPM, 1, false, K2>(p, s);
       else launch_variant<32, 4, OPM, 1, false, 5>(p, s);
       return;
     }
-    if (shape.eight) launch_variant<CHUNK, 8, OPM, 1>(p, s);
-    else if (shape.halves) launch_variant<CHUNK, 4, OPM, 1>(p, s);
-    else launch_variant<CHUNK, 4, OPM, 2>(p, s);
   }
+  if constexpr (CHUNK == 16) {
+    if (p.stride == 2 && p.k <= 3 && shape.halves && !shape.eight) {
+      launch_variant<16, 4, OPM, 1, false, 3>(p, s);
+      return;
+    }
+  }
+  const bool stride1 = p.stride == 1 && !p.upsample;
+  if (stride1 && p.k == 1) launch_bound<CHUNK, OPM, -1>(p, shape, s);
+  else if (CHUNK <= 32 && stride1 && p.k <= 3) launch_bound<CHUNK, OPM, CHUNK <= 32 ? -3 : 0>(p, shape, s);
+  else launch_bound<CHUNK, OPM, 0>(p, shape, s);
 }
 
 // Launches with few workgroups (maps of a few tiles) are bound by what one workgroup does in
@@ -443,7 +465,8 @@ void launch_any(const ConvParams& p, hipStream_t s) {
   if (r.ks) {
     ConvParams q = p;
     q.ks = r.ks; q.ks_chunks = r.chunks_each;
-    if (r.chunk == 64 && p.stride == 1) launch_variant<64, 8, OPM, 1, true, 0>(q, s);
+    if (r.chunk == 64 && p.stride == 1 && p.k == 1) launch_variant<64, 8, OPM, 1, true, -1>(q, s);
+    else if (r.chunk == 64 && p.stride == 1) launch_variant<64, 8, OPM, 1, true, 0>(q, s);
     else if (r.chunk == 64) launch_variant<64, 8, OPM, 1, true, 3>(q, s);
     else if (p.stride == 1) launch_variant<32, 8, OPM, 1, true, OPM == kOpF32 ? 0 : 5>(q, s);  // (fp32 mode only)
     else launch_variant<32, 8, OPM, 1, true, 5>(q, s);
@@ -492,16 +515,18 @@ void launch_pair(const ConvParams& a, const ConvParams& b, hipStream_t s) {
 // The gate convs of a recurrent cell read one tensor.  In one launch the last, partly filled round of
 // workgroups and the start of the next launch come once instead of four times (the four convs of a
 // ConvLSTM cell, 69 -> 64 channels on 256 x 352, fp32: 192 -> 168 us).  For the variant of four-wave half
-// tiles with 32-channel chunks, the one such layers take.  A launch each / one launch, over 612 cells of two to
-// four convs with equal and with different kernels (1 x 1 to 7 x 7, 64 x 72 to 480 x 640), ms in all: fp32 87.4 /
-// 84.7, split 75.0 / 72.4, bf16 65.0 / 62.5; none is slower by more than the spread.  (bf16 takes old z late
-// here, 91 registers instead of 99 and five waves per SIMD as alone: with four, cells of more than 8000
-// workgroups per conv were up to 7 % slower than a launch each.)
+// tiles with 32-channel chunks, the one such layers take, and kernels of one size: a launch takes the variant and
+// the LDS of its largest (3 x 3 beside 1 x 1, 33 -> 40 channels on 480 x 640, fp32: 311 us apart, 331 together).
+// 1 x 1 kernels up to 4096 workgroups each (96 -> 96 on 480 x 640, split: 498 / 531).  A launch each / one launch, over
+// 824 cells of two to four convs, 64 x 72 to 480 x 640, ms in all: fp32 131.1 / 129.0, split 111.1 / 109.0, bf16 97.6 /
+// 96.0; none is slower by more than the spread.  (bf16 takes old z late here and holds five waves per SIMD.)
 inline bool batchable(const ConvParams& p) {
   if (p.stride != 1 || p.upsample || ksplit_for(p).ks) return false;
   const Shape shape = shape_for(p);
-  return shape.chunk == 32 && shape.halves && !shape.eight;
+  const long long n = 2ll * p.go.tiles() * (p.c_out_pad / 32) * p.st.n;
+  return shape.chunk == 32 && shape.halves && !shape.eight && (p.k > 1 || n <= 4096);
 }
+inline bool batch_supported(const ConvParams& a, const ConvParams& b) { return batchable(a) && batchable(b) && a.k == b.k; }
 template <int OPM>
 void launch_batch(const ConvParams* convs, int n, hipStream_t s) {
   ConvBatch q = {};
@@ -515,7 +540,10 @@ void launch_batch(const ConvParams* convs, int n, hipStream_t s) {
     lds = std::max(lds, l.lds);
   }
   q.n = n;
-  hipLaunchKernelGGL(conv_mfma_batch_kernel<OPM>, dim3(blocks, 1, convs[0].st.n), dim3(256), lds, s, q);
+  const dim3 grid(blocks, 1, convs[0].st.n);
+  if (convs[0].k == 1) hipLaunchKernelGGL((conv_mfma_batch_kernel<OPM, -1>), grid, dim3(256), lds, s, q);
+  else if (convs[0].k <= 3) hipLaunchKernelGGL((conv_mfma_batch_kernel<OPM, -3>), grid, dim3(256), lds, s, q);
+  else hipLaunchKernelGGL((conv_mfma_batch_kernel<OPM, 0>), grid, dim3(256), lds, s, q);
 }
 
 // Copies the phase records of this translation unit's kernels to `host` (32 x u64 each, at most

@@ -1065,7 +1065,7 @@ evconv_status create_impl(const evconv_net_desc* desc, const void* weights, size
         const ConvParams p = probe_of(first), q = probe_of(late);
         const bool shortcut = late.d.kh == 1 && first.n_mates == 0 && conv_mfma_pair_supported(p, q);
         const bool batch = (first.n_mates == 0 || first.mates_batch) && first.n_mates < kMaxConvBatch - 1 &&
-                           conv_mfma_batch_supported(p) && conv_mfma_batch_supported(q);
+                           conv_mfma_batch_supported(p, q);
         if (!shortcut && !batch) continue;
         bool delayed_between = false;  // (a DELAY of the later one in between must see last step's buffers)
         for (int dn = i + 1; dn < j; ++dn)

@@ -168,7 +168,7 @@ void launch_conv_mfma_f32(const ConvParams& p, hipStream_t s);
 bool conv_mfma_pair_supported(const ConvParams& a, const ConvParams& b);
 // up to kMaxConvBatch of them, all of one variant
 constexpr int kMaxConvBatch = 4;
-bool conv_mfma_batch_supported(const ConvParams& p);
+bool conv_mfma_batch_supported(const ConvParams& a, const ConvParams& b);
 void launch_conv_mfma_f32_batch(const ConvParams* convs, int n, hipStream_t s);
 void launch_conv_mfma_bf16_batch(const ConvParams* convs, int n, hipStream_t s);
 void launch_conv_mfma_split_batch(const ConvParams* convs, int n, hipStream_t s);

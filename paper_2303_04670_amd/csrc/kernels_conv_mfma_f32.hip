@@ -46,7 +46,7 @@ void conv_mfma_split_scratch(const ConvParams& p, size_t* part_floats, size_t* c
   *part_floats = r.ks ? blocks * r.ks * 32 * 32 : 0;
   *counters = r.ks ? blocks : 0;
 }
-bool conv_mfma_batch_supported(const ConvParams& p) { return batchable(p); }
+bool conv_mfma_batch_supported(const ConvParams& a, const ConvParams& b) { return batch_supported(a, b); }
 bool conv_mfma_pair_supported(const ConvParams& a, const ConvParams& b) { return pair_supported(a, b); }
 void launch_conv_mfma_f32(const ConvParams& p, hipStream_t s) { launch_any<kOpF32>(p, s); }
 void launch_conv_mfma_f32_batch(const ConvParams* convs, int n, hipStream_t s) { launch_batch<kOpF32>(convs, n, s); }

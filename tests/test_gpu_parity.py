@@ -1511,9 +1511,9 @@ def _merged_net(kind):
         b.close_delay(prev, y)
         b.simple(wl.OP_ADD, b.simple(wl.OP_MUL, x, prev), y, act=wl.ACT_RELU, out=1)
         return b.finish(), {x: 1, y: 1}, {}
-    if kind == "mixed":            # different kernels
-        ids = [b.conv(-1, c, k, act=wl.ACT_RELU, out=1) for k in (3, 1, 5, 7)]
-        return b.finish(), dict(zip(ids, (1, 0, 0, 0))), {}
+    if kind == "mixed":            # kernels of different size, and two of each: a launch per size
+        ids = [b.conv(-1, c, k, act=wl.ACT_RELU, out=1) for k in (3, 1, 5, 7, 5, 1, 3, 7)]
+        return b.finish(), dict(zip(ids, (1, 1, 1, 1, 0, 0, 0, 0))), {}
     early = b.simple(wl.OP_MAXPOOL, -1, k=3, stride=2, pad=1) if pair else b.simple(wl.OP_ACT, -1, act=wl.ACT_TANH)
     x = b.conv(-1, c, 3, 2 if pair else 1, act=wl.ACT_RELU)
     y = b.conv(-1, c, 1 if pair else 3, 2 if pair else 1, act=wl.ACT_NONE)
@@ -1533,7 +1533,7 @@ def _merged_net(kind):
 @pytest.mark.gpu
 @pytest.mark.parametrize("kind", ["lstm", "delay", "mixed", "batch_add", "batch_sparsify", "pair_add", "pair_sparsify"])
 def test_merged_convs_with_epilogues_and_delays(kind):
-    """Convs in one launch that host ADDs and sparsification layers, of different kernels, beside DELAY nodes:
+    """Convs in one launch that host ADDs and sparsification layers, of each kernel's variant, beside DELAY nodes:
     every sum, set and result bit for bit as with a launch per node, through sparse and dense steps, a dense
     recompute and a refresh."""
     net, launches, names = _merged_net(kind)
@@ -2252,9 +2252,8 @@ def test_large_stride2_1x1_convs(mode, ci, co, hw, streams):
 @pytest.mark.parametrize("mode,ci,co,k,hw", [("bf16", 96, 96, 5, (100, 109)), ("bf16", 33, 64, 3, (136, 139)),
                                              ("split", 64, 128, 3, (95, 90)), ("split", 128, 96, 1, (159, 160))])
 def test_launches_of_five_workgroups_per_cu(mode, ci, co, k, hw):
-    """Four-wave half tiles whose launch takes one round less with five workgroups per CU run a variant
-    held to fewer registers: bit for bit what four per CU give (more streams: another number of
-    rounds), and within rounding of 64 bits."""
+    """Four-wave half tiles whose launch takes one round less with five workgroups per CU: bit for bit
+    what launches of another number of rounds (more streams) give, and within rounding of 64 bits."""
     _say(f"five workgroups per CU: {ci} -> {co}, {k} x {k}, {hw}, {mode}")
     h, w = hw
     n = -(-h // 8) * -(-w // 8) * -(-co // 32) * 2
@@ -2281,6 +2280,47 @@ def test_launches_of_five_workgroups_per_cu(mode, ci, co, k, hw):
         many.step(_dev(np.stack([d] * streams)))
     one.destroy()
     many.destroy()
+
+
+def _sums_against_64_bits(mode, ci, co, k, s, h, w):
+    b = wl._NetBuilder("small", ci, h, w, ci + k, bf16=mode == "bf16")
+    b.conv(-1, co, k, s, act=wl.ACT_NONE, out=1)
+    net = b.finish()
+    if mode == "split":
+        net = wl.with_weight_dtype(net, wl.WD_F32_SPLIT)
+    rng = np.random.default_rng(ci + 10 * k + s)
+    x = wl.round_to_bf16(rng.standard_normal((ci, h, w)).astype(np.float32))
+    d = wl.round_to_bf16((rng.standard_normal(x.shape) * (rng.random((1, h, w)) < 0.05)).astype(np.float32))
+    gpu = ev.EvConvNet(net)
+    assert gpu.kernel_name(0).startswith("conv_mfma")
+    gpu.reset(_dev(x))
+    ref, absolute = _conv64(net, x, co, ci, k, s)
+    bound = 2.0 ** -15 if mode == "split" else 2.0 ** -20   # of the sum of the absolute products
+    err = np.abs(gpu.state(0, ev.STATE_Z).astype(np.float64).transpose(2, 0, 1) - ref)
+    assert (err <= bound * absolute).all(), (h, w, float((err / absolute).max()))
+    gpu.step(_dev(d))
+    ref_d, absolute_d = _conv64(net, d, co, ci, k, s)
+    err = np.abs(gpu.state(0, ev.STATE_Z).astype(np.float64).transpose(2, 0, 1) - ref - ref_d)
+    assert (err <= bound * (absolute + absolute_d)).all(), (h, w, float((err / absolute).max()))
+    gpu.destroy()
+
+
+@pytest.mark.parametrize("k,s", [(1, 1), (2, 1), (3, 1), (1, 2), (2, 2), (3, 2)])
+@pytest.mark.parametrize("mode,ci", [("f32", 24), ("f32", 48), ("f32", 69), ("f32", 96), ("f32", 128),
+                                     ("split", 69), ("split", 128), ("bf16", 48), ("bf16", 96)])
+def test_variants_for_small_kernels(mode, ci, k, s):
+    """Kernels of one to three sites have variants that hold no more of a patch than they need: chunks of 16, 32
+    (full and ragged), 64 and 128 channels, eight and four waves, channels split over workgroups; every
+    site of odd maps against 64 bits, in a regular pass and a sparse step."""
+    for h, w in ((13, 21), (201, 197)):
+        _sums_against_64_bits(mode, ci, 40, k, s, h, w)
+
+
+@pytest.mark.parametrize("mode,ci,co,k,hw", [("f32", 1632, 512, 1, (64, 30)), ("split", 1616, 512, 1, (61, 32)), ("f32", 224, 256, 3, (64, 61)),
+                                             ("bf16", 208, 256, 3, (59, 64)), ("split", 1600, 512, 1, (64, 32))])
+def test_variants_for_small_kernels_on_whole_tiles(mode, ci, co, k, hw):
+    """... and long contractions of many blocks, which take whole tiles."""
+    _sums_against_64_bits(mode, ci, co, k, 1, *hw)
 
 
 @pytest.mark.parametrize("ci,co", [(20, 5), (19, 6), (64, 7), (36, 8), (20, 4), (20, 3), (40, 3), (64, 4), (33, 5)])
