@@ -303,11 +303,18 @@ __device__ __forceinline__ unsigned row_of_lane(unsigned rows, int lane) {
   return (unsigned)__builtin_amdgcn_ds_bpermute(lane * 4, (int)rows);
 }
 
+// Four elements of a thread in flight, where that leaves the registers of six waves per SIMD: sums, products,
+// maxima and up-samplings of whole vectors take two at a time (sum with an activation, 64 channels on 256 x
+// 352, every site active: 30.6 us with four, 25.0 with two; product, 2 % of the sites active, 7.8 and 6.3).
+constexpr int ew_in_flight(int op, int vec) {
+  return vec == 4 && (op == kEwAdd || op == kEwMul || op == kEwPoolMax || op == kEwUp2x) ? 2 : 4;
+}
+
 // The operator and the elements that a thread has in flight (N) are known at compile time: their loads go
-// out together, and no wave waits for another before its last step.  With the operator looked up per element and a list of the touched sites in LDS, a tile
-// was a chain of up to four round trips (concatenation of an up-sampled tensor, 16 x 16 to 256 x 256: 5.8 /
-// 7.4 / 8.4 / 9.8 us, now 4.9 / 6.0 / 7.0 / 9.1; 5 + 64 channels on 256 x 352 15.4, now 10.2; max-pool of ResNet-18, two
-// launches, 10.9, now 7.7).
+// out together, and no wave waits for another before its last step.  With the operator looked up per element
+// and a list of the touched sites in LDS, a tile was a chain of up to four round trips (concatenation of an
+// up-sampled tensor, 16 x 16 to 256 x 256: 5.8 / 7.4 / 8.4 / 9.8 us, now 5.0 / 6.0 / 6.8 / 9.0; 5 + 64 channels on
+// 256 x 352 15.4, now 10.2; max-pool of ResNet-18, two launches, 10.9, now 7.7).
 // Element e is vector e % cv of touched site number e / cv: where few sites are touched, few waves have
 // work (64 channels on 256 x 352, 2 % of the sites active, tanh / product: 11.4 / 7.6 us with an element
 // for each of the 64 sites, now 7.5 / 6.3).
@@ -369,11 +376,14 @@ __global__ __launch_bounds__(256) void elementwise_kernel(EwParams p) {
   // channel vectors [v0, v0 + cv) of every touched site belong to this workgroup
   const int v0 = blockIdx.y * p.vec_per_block, cv = min(p.vec_per_block, C / VEC - v0);
   const int cv_magic = (65536 + cv - 1) / cv;  // e / cv == (e * cv_magic) >> 16 for e < 1024 (cv <= 16)
-  const int n_sites = __popcll(word), total = n_sites * cv;
+  // (a concatenation of an up-sampling, whose tiles are mostly full, takes all 64 sites as they are: 64 + 64
+  // channels on 64 x 64 6.0 us, 6.4 with the list)
+  constexpr bool LISTED = OP != kEwConcatUp;
+  const int n_sites = LISTED ? __popcll(word) : 64, total = n_sites * cv;
   uint64_t nz_sites = 0;  // sites at which this thread produced a nonzero element
   const int first = __builtin_amdgcn_readfirstlane(tid >> 6) * 64;  // of this wave
   int nth = 0;
-  if (first < total) {
+  if (LISTED && first < total) {
     // lane r: the r-th touched site (the sites that are not touched follow: a permutation of the lanes)
     const int below = __builtin_amdgcn_mbcnt_hi((unsigned)(word >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)word, 0u));
     nth = __builtin_amdgcn_ds_permute((((word >> lane) & 1ull) ? below : n_sites + lane - below) * 4, lane);
@@ -385,9 +395,9 @@ __global__ __launch_bounds__(256) void elementwise_kernel(EwParams p) {
 #pragma unroll
     for (int it = 0; it < N; ++it) {
       const int e = e0 + lane + it * 256, r = __umul24(e, cv_magic) >> 16;
-      site[it] = __builtin_amdgcn_ds_bpermute(r * 4, nth);  // (r counts modulo 64)
+      site[it] = LISTED ? __builtin_amdgcn_ds_bpermute(r * 4, nth) : r & 63;  // (r counts modulo 64)
       c[it] = (v0 + (e - __umul24(r, cv))) * VEC;
-      on[it] = r < n_sites;
+      on[it] = r < n_sites && (LISTED || ((word >> site[it]) & 1ull));
       q[it] = (size_t)(tile_y * 8 + (site[it] >> 3)) * p.go.w + (tile_x * 8 + (site[it] & 7));
     }
 
@@ -567,6 +577,7 @@ __global__ __launch_bounds__(256) void elementwise_kernel(EwParams p) {
       for (int i = 0; i < VEC; ++i) nz |= (o.v[i] != 0.0f);
       if (nz) nz_sites |= 1ull << site[it];
     }
+    if (N != 2 || ew_in_flight(OP, VEC) != 2) break;  // (a workgroup has no more)
   }
   if (OP == kEwPoolAcc) return;
   if (p.structural || dense) {
@@ -594,12 +605,9 @@ __global__ __launch_bounds__(256) void elementwise_kernel(EwParams p) {
   }
 }
 
-// Four elements of a thread in flight, where that leaves the registers of six waves per SIMD: sums, products,
-// maxima and up-samplings of whole vectors take two at a time (sum with an activation, 64 channels on 256 x
-// 352, every site active: 30.6 us with four, 25.0 with two; product, 2 % of the sites active, 7.8 and 6.3).
 template <int OP, int VEC>
 void launch_ew(const EwParams& q, const dim3& grid, hipStream_t s) {
-  constexpr int kMax = VEC == 4 && (OP == kEwAdd || OP == kEwMul || OP == kEwPoolMax || OP == kEwUp2x) ? 2 : 4;
+  constexpr int kMax = ew_in_flight(OP, VEC);
   const int n = std::min((std::min(q.vec_per_block, q.go.c / VEC) * 64 + 255) / 256, kMax);  // elements of a thread
   if (n <= 1) hipLaunchKernelGGL((elementwise_kernel<OP, VEC, 1>), grid, dim3(256), 0, s, q);
   else if (n <= 2) hipLaunchKernelGGL((elementwise_kernel<OP, VEC, 2>), grid, dim3(256), 0, s, q);
