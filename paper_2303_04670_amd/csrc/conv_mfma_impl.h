@@ -406,10 +406,15 @@ void launch_shape(const ConvParams& p, const Shape& shape, hipStream_t s) {
   if constexpr (CHUNK == 32 || CHUNK == 64) {
     if (p.stride == 2) {
       constexpr int K2 = CHUNK == 32 ? 5 : 3;
-      if (p.k == 1 && shape.eight) launch_variant<CHUNK, 8, OPM, 1, false, 1>(p, s);
-      else if (p.k == 1) launch_variant<32, 4, OPM, 1, false, 1>(p, s);
-      else if (shape.eight) launch_variant<CHUNK, 8, OPM, 1, false, K2>(p, s);
-      else launch_variant<32, 4, OPM, 1, false, 5>(p, s);
+      if (shape.eight) {
+        if (p.k == 1) launch_variant<CHUNK, 8, OPM, 1, false, 1>(p, s);
+        else if (p.k <= 3) launch_variant<CHUNK, 8, OPM, 1, false, 3>(p, s);
+        else launch_variant<CHUNK, 8, OPM, 1, false, K2>(p, s);
+      } else {
+        if (p.k == 1) launch_variant<32, 4, OPM, 1, false, 1>(p, s);
+        else if (p.k <= 3) launch_variant<32, 4, OPM, 1, false, 3>(p, s);
+        else launch_variant<32, 4, OPM, 1, false, 5>(p, s);
+      }
       return;
     }
   }
