@@ -156,7 +156,7 @@ struct Layout {
   size_t off_x_prev = 0, off_dx = 0, off_occ_in = 0, off_idx_in = 0, off_count_in = 0, off_bitmap_in = 0;
   size_t off_occ_nodes = 0, n_occ_words = 0;  // contiguous occupancy region of all nodes
   size_t off_sets = 0, off_rms = 0, off_int = 0;
-  size_t off_tile_or = 0, off_tile_count = 0;  // scratch of the increment builder (wide inputs)
+  size_t off_row_or = 0;  // scratch of the increment builder (wide inputs)
   size_t off_ks_part = 0, off_ks_count = 0;  // scratch of convs whose channels are split over workgroups
   size_t stride = 0;   // bytes of one stream's state (the weights live in stream 0's copy)
   int n_streams = 1;
@@ -378,10 +378,9 @@ evconv_status make_layout(const evconv_net_desc* desc, size_t weight_bytes, bool
       n.off_dy = b.take(elems * 4);
     }
   }
-  L->off_tile_or = b.take((size_t)L->gin.tiles() * 8);
-  L->off_tile_count = b.take((size_t)L->gin.tiles() * 4);
-  L->off_ks_part = b.take(ks_floats * sizeof(float));
+  L->off_row_or = b.take(builder_scratch_words(L->gin) * sizeof(uint64_t));
   L->off_rms = b.take(sizeof(float) * kRmsBlocks);
+  L->off_ks_part = b.take(ks_floats * sizeof(float));
   L->off_int = b.take(sizeof(IntegrateDesc) * (size_t)desc->n_nodes);
   L->off_sets = b.take(sizeof(SetDesc) * (size_t)(desc->n_nodes + 1));
   L->stride = (b.cur + 255) / 256 * 256;  // one stream's copy of everything
@@ -452,7 +451,7 @@ evconv_status run_pass(evconv_net* net, const float* input, int builder_mode, Pa
   const int int_mode = pass == kPassStep ? kIntStep : pass == kPassReset ? kIntReset : kIntRecompute;
   BuilderParams bp;
   bp.in = input; bp.x_prev = net->x_prev; bp.dx = net->dx; bp.occ = net->occ_in;
-  bp.tile_or = (uint64_t*)(net->ws + net->L.off_tile_or); bp.tile_count = (unsigned*)(net->ws + net->L.off_tile_count);
+  bp.row_or = (uint64_t*)(net->ws + net->L.off_row_or);
   bp.clear = net->occ_nodes; bp.n_clear = (int)net->L.n_occ_words;
   bp.g = net->L.gin; bp.mode = builder_mode;
   bp.st = net->st; bp.in_stride = net->in_stride;

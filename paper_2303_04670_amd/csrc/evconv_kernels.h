@@ -66,13 +66,13 @@ struct BuilderParams {
   uint64_t* occ;      // per-tile occupancy of the input increment
   uint64_t* clear;    // words to zero before the layers run (all nodes' occupancy), or null
   int n_clear;
-  uint64_t* tile_or;   // wide inputs: per-tile scratch word and counter, zero between launches
-  unsigned* tile_count;
+  uint64_t* row_or;    // wide inputs: builder_scratch_words scratch words, zero between launches
   Geo g;
   int mode;
   Streams st;
   size_t in_stride;   // bytes between the streams' inputs (contiguous [n][C][H][W])
 };
+size_t builder_scratch_words(const Geo& g);
 void launch_builder(const BuilderParams& p, hipStream_t s);
 
 // ---- sparse incremental convolution (Eq.10 at touched tiles, fused Eq.12-14) ------------

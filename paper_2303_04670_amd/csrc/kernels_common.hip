@@ -88,10 +88,9 @@ __device__ __forceinline__ void clear_words(const BuilderParams& p) {
 }
 
 // Strips: one workgroup = 8 wavefronts = an 8-row x 64-column strip (8 tiles).  Wave r reads row r with
-// 256-byte coalesced loads per channel, N channels in flight; its ballot is the 64-column activity of
+// 256-byte coalesced loads per channel, all N in flight; its ballot is the 64-column activity of
 // that row.  The eight ballots are transposed through LDS into eight tile occupancy words.
-// ALL: the input has exactly N channels.
-template <int N, bool ALL>
+template <int N>
 __global__ __launch_bounds__(512) void builder_kernel(BuilderParams p) {
   touch_params<BuilderParams>();
   {
@@ -110,22 +109,19 @@ __global__ __launch_bounds__(512) void builder_kernel(BuilderParams p) {
   bool any = false;
   if (inb) {
     const int site = y * p.g.w + x;
-    const int C = ALL ? N : p.g.c;
-    for (int c0 = 0; c0 < C; c0 += N) {
-      int e[N];
-      bool ok[N];
-      float d[N];
+    int e[N];
+    bool ok[N];
+    float d[N];
 #pragma unroll
-      for (int j = 0; j < N; ++j) {
-        ok[j] = c0 + j < C;
-        e[j] = (c0 + j) * hw + site;
-      }
-      build_elements<N>(p, e, ok, d);
+    for (int j = 0; j < N; ++j) {
+      ok[j] = true;
+      e[j] = j * hw + site;
+    }
+    build_elements<N>(p, e, ok, d);
 #pragma unroll
-      for (int j = 0; j < N; ++j) {
-        if (ok[j]) p.dx[(size_t)site * C + c0 + j] = d[j];
-        any |= ok[j] && d[j] != 0.0f;
-      }
+    for (int j = 0; j < N; ++j) {
+      p.dx[(size_t)site * N + j] = d[j];
+      any |= d[j] != 0.0f;
     }
   }
   const uint64_t row_mask = __ballot(any);
@@ -144,14 +140,14 @@ __global__ __launch_bounds__(512) void builder_kernel(BuilderParams p) {
   clear_words(p);
 }
 
-// Wide inputs (a network that starts inside another one): workgroup = one 8 x 8 tile x 64 channels,
-// lane = site, the channels dealt to the 8 waves.  They pass through LDS, so that the channel-major
-// input is read row by row of the tile and the site-major increment is written in runs of 64
-// channels; with one thread per site the channels were a serial loop of 4-byte stores a site's
-// length apart (256 x 32 x 44, four workgroups: 260 us; a workgroup per tile: 15 us; this way 10 us).
-// The tile's word is the OR over its workgroups: they meet in p.tile_or, and the last to arrive
-// (p.tile_count) writes it and leaves both zero for the next launch.
-constexpr int kWideChunk = 64;
+// Wide inputs (a network that starts inside another one): workgroup = 64 sites of one row x 8 N channels,
+// lane = site, the channels dealt to the 8 waves, so that the channel-major input is read in runs of 256
+// bytes.  The increments are turned through LDS and written in runs of the workgroup's channels.  A row's
+// activity is the OR over its channel blocks: 32 sites and a bit per block that has arrived share a
+// scratch word (p.row_or), so that one atomic both adds a block's share and tells the last one that it is
+// the last; that one writes the sites' bytes and leaves the word zero for the next launch.
+constexpr int kWideBlocks = 32;  // channel blocks at most: arrival bits of a scratch word
+template <int N>
 __global__ __launch_bounds__(512) void builder_wide_kernel(BuilderParams p) {
   touch_params<BuilderParams>();
   {
@@ -159,96 +155,116 @@ __global__ __launch_bounds__(512) void builder_wide_kernel(BuilderParams p) {
     p.in = at_stream(p.in, (size_t)blockIdx.z * p.in_stride);
     p.x_prev = at_stream(p.x_prev, so); p.dx = at_stream(p.dx, so);
     p.occ = at_stream(p.occ, so); p.clear = at_stream(p.clear, so);
-    p.tile_or = at_stream(p.tile_or, so); p.tile_count = at_stream(p.tile_count, so);
+    p.row_or = at_stream(p.row_or, so);
   }
-  __shared__ float s_d[64][kWideChunk + 1];
+  constexpr int CB = 8 * N;
+  // (pitch 66: the reads below are of eight sites x eight channel groups, 8 banks apart)
+  __shared__ float s_d[CB][66];
   __shared__ uint64_t s_any[8];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int ty = blockIdx.x / p.g.tx, tx = blockIdx.x - ty * p.g.tx;
-  const int y = ty * 8 + (lane >> 3), x = tx * 8 + (lane & 7);
-  const int hw = p.g.h * p.g.w, C = p.g.c;
-  const int c0 = blockIdx.y * kWideChunk, nc = min(kWideChunk, C - c0);
-  const bool inb = y < p.g.h && x < p.g.w;
-  constexpr int N = kWideChunk / 8;
-  int e[N];
-  bool ok[N], any = false;
-  float d[N];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int strips = (p.g.w + 63) >> 6;
+  const int y = blockIdx.x / strips, strip = blockIdx.x - y * strips;
+  const int x0 = strip * 64, x = x0 + lane, hw = p.g.h * p.g.w, C = p.g.c;
+  const bool inb = y < p.g.h && x < p.g.w;  // (the rows of the last tiles that lie below the image: bytes of zeros)
+  const int row = y * p.g.w + x0;
+  bool any = false;
+  for (int c0 = blockIdx.y * CB; c0 < C; c0 += gridDim.y * CB) {
+    if (c0 != (int)blockIdx.y * CB) __syncthreads();
+    const int nc = min(CB, C - c0);
+    int e[N];
+    bool ok[N];
+    float d[N];
 #pragma unroll
-  for (int j = 0; j < N; ++j) {
-    const int c = wave + 8 * j;
-    ok[j] = inb && c < nc;
-    e[j] = (c0 + c) * hw + y * p.g.w + x;
-  }
-  build_elements<N>(p, e, ok, d);
-#pragma unroll
-  for (int j = 0; j < N; ++j)
-    if (ok[j]) {
-      s_d[lane][wave + 8 * j] = d[j];
-      any |= d[j] != 0.0f;
+    for (int j = 0; j < N; ++j) {
+      const int c = wave * N + j;
+      ok[j] = inb && c < nc;
+      e[j] = (c0 + c) * hw + row + lane;
     }
+    build_elements<N>(p, e, ok, d);
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      s_d[wave * N + j][lane] = d[j];
+      any |= ok[j] && d[j] != 0.0f;
+    }
+    __syncthreads();
+    if (y < p.g.h) {
+      if ((C & 3) == 0) {
+#pragma unroll
+        for (int i = tid; i < 64 * (CB / 4); i += 512) {
+          const int q = i / (CB / 4), c = i % (CB / 4) * 4;
+          if (x0 + q < p.g.w && c < nc)
+            *(float4*)&p.dx[(size_t)(row + q) * C + c0 + c] = make_float4(s_d[c][q], s_d[c + 1][q], s_d[c + 2][q], s_d[c + 3][q]);
+        }
+      } else {
+#pragma unroll
+        for (int i = tid; i < 64 * CB; i += 512) {
+          const int q = i / CB, c = i % CB;
+          if (x0 + q < p.g.w && c < nc) p.dx[(size_t)(row + q) * C + c0 + c] = s_d[c][q];
+        }
+      }
+    }
+  }
   const uint64_t b = __ballot(any);
   if (lane == 0) s_any[wave] = b;
   __syncthreads();
-  // wave w writes sites w, w + 8, ..: lanes along the channels
-#pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    const int q = wave + 8 * j;
-    const int qy = ty * 8 + (q >> 3), qx = tx * 8 + (q & 7);
-    if (qy < p.g.h && qx < p.g.w && lane < nc) p.dx[(size_t)(qy * p.g.w + qx) * C + c0 + lane] = s_d[q][lane];
-  }
-  if (threadIdx.x == 0) {
+  if (tid < 2) {  // lane h: columns x0 + 32 h on
     uint64_t word = 0;
+#pragma unroll
     for (int i = 0; i < 8; ++i) word |= s_any[i];
+    unsigned bits = (unsigned)(word >> (32 * tid));
+    bool last = true;
+    uint64_t* const acc = p.row_or + (size_t)blockIdx.x * 2 + tid;
     if (p.mode >= kBuildReset) {  // no active set; scratch as a launch of another kind expects it
-      if (blockIdx.y == 0) {
-        p.occ[blockIdx.x] = 0;
-        p.tile_or[blockIdx.x] = 0;
-        p.tile_count[blockIdx.x] = 0;
-      }
-    } else if (gridDim.y == 1) {
-      p.occ[blockIdx.x] = word;
-    } else {
-      // (the OR's result is waited for before the counter is touched)
-      unsigned long long* const acc = (unsigned long long*)&p.tile_or[blockIdx.x];
-      const unsigned long long old = __hip_atomic_fetch_or(acc, (unsigned long long)word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      asm volatile("s_waitcnt vmcnt(0)" ::"v"((unsigned)old) : "memory");
-      if (__hip_atomic_fetch_add(&p.tile_count[blockIdx.x], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.y - 1) {
-        p.occ[blockIdx.x] = __hip_atomic_exchange(acc, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(&p.tile_count[blockIdx.x], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      }
+      bits = 0;
+      if (blockIdx.y == 0) *acc = 0;
+    } else if (gridDim.y > 1) {
+      const unsigned long long mine = bits | (1ull << (32 + blockIdx.y));
+      const unsigned long long all = mine | __hip_atomic_fetch_or((unsigned long long*)acc, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      last = (unsigned)(all >> 32) == (unsigned)((1ull << gridDim.y) - 1ull);
+      bits = (unsigned)all;
+      if (last) __hip_atomic_store(acc, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    if (last) {
+      const int tx0 = strip * 8 + 4 * tid;
+      unsigned char* const bytes = (unsigned char*)(p.occ + (size_t)(y >> 3) * p.g.tx + tx0) + (y & 7);
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if (tx0 + j < p.g.tx) bytes[8 * j] = (unsigned char)(bits >> (8 * j));
     }
   }
   clear_words(p);
 }
+size_t builder_scratch_words(const Geo& g) { return (size_t)g.ty * 8 * ((g.w + 63) / 64) * 2; }
+
+template <int N>
+void launch_builder_wide(const BuilderParams& p, hipStream_t s) {
+  const dim3 rows(p.g.ty * 8 * ((p.g.w + 63) / 64), std::min((p.g.c + 8 * N - 1) / (8 * N), kWideBlocks), p.st.n);
+  hipLaunchKernelGGL(builder_wide_kernel<N>, rows, dim3(512), 0, s, p);
+}
 
 void launch_builder(const BuilderParams& p, hipStream_t s) {
   dim3 grid((p.g.w + 63) / 64, (p.g.h + 7) / 8, p.st.n);
-  // Strips for up to 8 channels, and for more where there are enough of them (each is a serial chain over
-  // the channels) and the site-major increments, written 4 bytes at a time, stay in the caches until
-  // their lines are full; otherwise tiles x 64 channels.  Measured, strips / tiles, us: 9 channels on 100 x
-  // 100 (26 strips) 8.1 / 6.8 and on 260 x 346 (198) 9.7 / 14.4; 24 on 480 x 640 (600) 49 / 57; 32 there 99 / 81; 100 on
-  // 260 x 346 70 / 81; 256 there 260 / 188.
-  const long long strips = (long long)grid.x * grid.y * p.st.n;
-  const bool enough = strips >= (p.g.c <= 12 ? 64 : 128);
-  const bool cached = p.g.c <= 24 || (p.g.c <= 128 && strips <= 400);
-  if (p.g.c > 8 && !(enough && cached)) {
-    const dim3 tiles(p.g.tiles(), (p.g.c + kWideChunk - 1) / kWideChunk, p.st.n);
-    hipLaunchKernelGGL(builder_wide_kernel, tiles, dim3(512), 0, s, p);
+  // Strips for up to 8 channels, all of them in flight (with rows, whose waves are mostly idle there, 5 on 256 x
+  // 352 3.7 / 7.1 us, 8 on 480 x 640 9.1 / 13.9).  Rows for more.  Before, strips that walked the channels 8 at a
+  // time or tiles x 64 channels, read in pieces of 32 bytes (12 on 64 x 64 6.0, now 3.4 us; 24 on 480 x 640 47.8 / 21.7; 64
+  // on 91 x 121 11.4 / 6.1; 256 on 32 x 44 8.4 / 5.0; 256 on 260 x 346 186 / 78.5, 4.7 TB/s; 9 on 260 x 346 8.3 / 8.7).
+  // 16 channels a workgroup up to 16 channels, else 32, a line of 128 bytes (24 on 480 x 640 in blocks of 16, 32
+  // and 64: 28.8 / 21.7 / 35.2; 256 on 260 x 346 97 / 78 / 86; 16 on 480 x 640 16.6 / 19.4).
+  if (p.g.c > 8) {
+    if (p.g.c <= 16) launch_builder_wide<2>(p, s);
+    else launch_builder_wide<4>(p, s);
     return;
   }
   switch (p.g.c) {
-    case 1: hipLaunchKernelGGL((builder_kernel<1, true>), grid, dim3(512), 0, s, p); return;
-    case 2: hipLaunchKernelGGL((builder_kernel<2, true>), grid, dim3(512), 0, s, p); return;
-    case 3: hipLaunchKernelGGL((builder_kernel<3, true>), grid, dim3(512), 0, s, p); return;
-    case 4: hipLaunchKernelGGL((builder_kernel<4, true>), grid, dim3(512), 0, s, p); return;
-    case 5: hipLaunchKernelGGL((builder_kernel<5, true>), grid, dim3(512), 0, s, p); return;
-    case 6: hipLaunchKernelGGL((builder_kernel<6, true>), grid, dim3(512), 0, s, p); return;
-    case 7: hipLaunchKernelGGL((builder_kernel<7, true>), grid, dim3(512), 0, s, p); return;
-    case 8: hipLaunchKernelGGL((builder_kernel<8, true>), grid, dim3(512), 0, s, p); return;
+    case 1: hipLaunchKernelGGL((builder_kernel<1>), grid, dim3(512), 0, s, p); return;
+    case 2: hipLaunchKernelGGL((builder_kernel<2>), grid, dim3(512), 0, s, p); return;
+    case 3: hipLaunchKernelGGL((builder_kernel<3>), grid, dim3(512), 0, s, p); return;
+    case 4: hipLaunchKernelGGL((builder_kernel<4>), grid, dim3(512), 0, s, p); return;
+    case 5: hipLaunchKernelGGL((builder_kernel<5>), grid, dim3(512), 0, s, p); return;
+    case 6: hipLaunchKernelGGL((builder_kernel<6>), grid, dim3(512), 0, s, p); return;
+    case 7: hipLaunchKernelGGL((builder_kernel<7>), grid, dim3(512), 0, s, p); return;
+    case 8: hipLaunchKernelGGL((builder_kernel<8>), grid, dim3(512), 0, s, p); return;
   }
-  // (the number in flight that leaves fewer loads without a channel)
-  if ((p.g.c - 1) % 8 < 4) hipLaunchKernelGGL((builder_kernel<4, false>), grid, dim3(512), 0, s, p);
-  else hipLaunchKernelGGL((builder_kernel<8, false>), grid, dim3(512), 0, s, p);
 }
 
 // =============================================================================== elementwise

@@ -2387,6 +2387,44 @@ def test_wide_inputs_in_strips(c, hw):
     gpu.destroy()
 
 
+@pytest.mark.parametrize("c,hw,streams", [(9, (9, 63), 1), (16, (8, 64), 1), (17, (23, 65), 1), (20, (1, 130), 2), (32, (7, 7), 1),
+                                          (36, (17, 96), 1), (66, (10, 97), 2), (1028, (3, 129), 1), (1063, (9, 10), 1)])
+def test_wide_inputs_in_rows(c, hw, streams):
+    """The increment builder for more than 8 channels (64 sites of a row x 16 or 32 channels, blocks of
+    channels that meet in a scratch word, several blocks to a workgroup beyond 1024 channels): cached
+    frame, increment and words are those of the same subtraction and comparison in numpy, bit for bit."""
+    h, w = hw
+    _say(f"wide inputs in rows: {c} channels, {h} x {w}, {streams} streams")
+    b = wl._NetBuilder("rows", c, h, w, c)
+    b.conv(-1, 2, 1, 1, 0, act=wl.ACT_RELU, out=1)
+    rng = np.random.default_rng(c)
+    gpu = ev.EvConvNet(b.finish(), n_streams=streams)
+    dev = lambda a: _dev(a if streams > 1 else a[0])
+    x = rng.standard_normal((streams, c, h, w)).astype(np.float32)
+    gpu.reset(dev(x))
+    for t in range(5):
+        d = np.zeros_like(x)
+        for s in range(streams):
+            for _ in range(2 + 20 * (t == 3)):  # single elements: a site's bit comes from one block only
+                d[s, rng.integers(c), rng.integers(h), rng.integers(w)] = rng.standard_normal()
+        if t % 2:
+            gpu.step(dev(d))
+            x, inc = x + d, d
+        else:
+            inc = (x + d) - x
+            x = x + d
+            gpu.step_frame(dev(x))
+        for s in range(streams):
+            mask = cmp.words_to_mask(gpu.state(-1, ev.STATE_OCC, s), h, w) != 0
+            np.testing.assert_array_equal(mask, (inc[s] != 0).any(0))
+            np.testing.assert_array_equal(gpu.state(-1, ev.STATE_DY, s), inc[s].transpose(1, 2, 0))
+            np.testing.assert_array_equal(gpu.state(-1, ev.STATE_X_PREV, s), x[s])
+            np.testing.assert_array_equal(gpu.site_list(-1, s), np.flatnonzero(mask))
+    gpu.reset(dev(x))
+    assert not any(gpu.state(-1, ev.STATE_OCC, s).any() for s in range(streams))
+    gpu.destroy()
+
+
 @pytest.mark.parametrize("mode", ["step", "dense"])
 def test_large_wide_outputs_read_active_sites_only(mode):
     """An output of more than 12 Mi values (97 channels on 352 x 370, ragged in both): y and dy bit for bit
