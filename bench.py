@@ -185,18 +185,20 @@ def run_variant(args, np, torch, ev, wl, variant, dframes, with_dense, with_laye
         st = g.stats(i)
         per_site = 2.0 * nd.k * nd.k * nd.c_in * nd.c_out if nd.op in (wl.OP_CONV2D, wl.OP_LINEAR) else 0.0
         flops = per_site * st.n_touched            # algorithmic: touched output sites of the last step
-        # Executed: a 5 x 5 conv reading a x2 up-sampling that the library folded into its weights
-        # runs 4 x 4 taps on the output tiles over stored tiles whose sites all lie 2 or more from
-        # the border of the stored tensor (the other tiles run all 25 taps)
+        # Executed: a 5 x 5 conv reading a x2 up-sampling that the library folded into its weights runs 4 x 4 taps;
+        # workgroups with sites of a border of the stored tensor run one more row (column) of them.  (Rows of stored
+        # sites per workgroup: see launch_fold.)
         executed = flops
         if nd.op == wl.OP_CONV2D and nd.in0 >= 0 and g.kernel_name(nd.in0) == "fused_into_conv_weights":
             c, h, w = g.shape(i)
+            lo_h, lo_w = h // 2, w // 2
+            rows = 8 if 4 * -(-lo_h // 8) * -(-lo_w // 8) * -(-c // 32) >= 512 else 4
             words = g.state(i, ev.STATE_OCC_TOUCHED).reshape(-(-h // 8), -(-w // 8))
-            inner = lambda t, n_sites: (8 * t >= 2) & (8 * t + 7 <= n_sites - 3)
-            ty, tx = np.indices(words.shape)
-            folded_tiles = inner(ty // 2, h // 2) & inner(tx // 2, w // 2)
-            pop = np.array([bin(int(x)).count("1") for x in words.ravel()]).reshape(words.shape)
-            executed = per_site * (pop[~folded_tiles].sum() + pop[folded_tiles].sum() * 16.0 / 25.0)
+            touched = (words[:, :, None, None] >> np.arange(64, dtype=np.uint64).reshape(8, 8)) & np.uint64(1)
+            touched = touched.transpose(0, 2, 1, 3).reshape(words.shape[0] * 8, -1)[:h, :w]
+            edge = lambda n, per: 4 + ((np.arange(n) // per == 0) | (np.arange(n) // per == (n - 1) // per))
+            taps = np.outer(np.repeat(edge(lo_h, rows), 2), np.repeat(edge(lo_w, 8), 2))
+            executed = per_site * float((touched * taps).sum()) / 25.0
         f = fam.setdefault(name, dict(ms=0.0, launches=0, flops=0.0, executed=0.0))
         f["ms"] += ms
         f["launches"] += n

@@ -232,7 +232,7 @@ evconv_status evconv_create(const evconv_net_desc* desc, const void* weights, si
  * would overwrite each other.  The array keeps the previous net's contents; the part a new net
  * uses is cleared by this call.  The pointers in evconv_out point into the array.  Otherwise as
  * evconv_create. */
-#define EVCONV_STATIC_WORKSPACE_BYTES (52u << 20)
+#define EVCONV_STATIC_WORKSPACE_BYTES (120u << 20)
 evconv_status evconv_create_static(const evconv_net_desc* desc, const void* weights, size_t weight_bytes,
                                    void* hip_stream, evconv_net** out);
 

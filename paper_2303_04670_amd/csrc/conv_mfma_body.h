@@ -1,7 +1,7 @@
 // The body of a matrix-core conv workgroup (conv_mfma_impl.h includes it into functions; no include
 // guard).  What the including function declares: the template parameters CHUNK, NW, OPM, MB, MODE, UPS, KSP,
 // S2K, PAIR and LATE, the arguments p, this workgroup's stream offset so, its tile (or list entry) and channel
-// block wg_tile and wg_ck, and for UPS the stored or up-sampled tile tile_arg with its phase fpy, fpx.
+// block wg_tile and wg_ck.
   const bool dense = p.dense != 0;
   constexpr int PARTS = op_parts(OPM);     // bf16 parts of an operand
   constexpr int NB = 32;                   // output channels per workgroup
@@ -25,48 +25,25 @@
   constexpr int SLOT = NACC * 64;     // floats per partial-sum slot
   constexpr int CSL = CHUNK + 4;      // UPS: site stride of the low-resolution fp32 buffer
   constexpr int LPMAX = 10;           // UPS: a 14-row patch has sources in at most 14 / 2 + 3 rows
-  // gathered float4 per thread (a weight-folded workgroup: an (NROWS + 3) x 11 patch, 4 x 4 taps)
-  constexpr int MAXG = MODE == kInterpolate ? (LPMAX * LPMAX * NV + NT - 1) / NT
-                       : MODE == kFolded ? ((4 * MB + 3) * 11 * NV + NT - 1) / NT : MAXV;
+  // gathered float4 per thread
+  constexpr int MAXG = MODE == kInterpolate ? (LPMAX * LPMAX * NV + NT - 1) / NT : MAXV;
   extern __shared__ __align__(16) float s_mem[];
   __shared__ unsigned s_arrived;  // KSP: shares of the block that were there before this one
   __shared__ uint64_t s_nz[(2 + kMaxFusedAdds) * NW];  // nonzero-site bits per wave: conv, each fused ADD, fused sparsification
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-#ifdef EVCONV_PHASE_STAMPS
-  unsigned ph_slot = 0xffffffffu;
-  if (tid == 0) {
-    ph_slot = atomicAdd(&g_phase_n, 1u);
-    if (ph_slot < kPhaseRecords) {
-      unsigned long long* r = g_phase[ph_slot];
-      for (int i = 1; i < 24; ++i) r[i] = 0;
-      r[kPhGrid] = (unsigned long long)gridDim.x * gridDim.y;
-      r[kPhBlock] = blockIdx.x + (unsigned long long)blockIdx.y * gridDim.x;
-      r[kPhHwId] = __builtin_amdgcn_s_getreg(4 | (31 << 11)) | ((unsigned long long)__builtin_amdgcn_s_getreg(20 | (31 << 11)) << 32);
-      r[kPhLayer] = (unsigned long long)p.go.h | ((unsigned long long)p.gi.c << 16) | ((unsigned long long)p.k << 32) |
-                    ((unsigned long long)p.go.c << 40);
-    }
-  }
-#endif
-  EVK_PHASE(kPhStart);
+  EVK_PHASE_OPEN();
   const int n_co = p.c_out_pad / NB;
   const int ks = KSP ? fast_div(wg_ck, n_co, p.co_magic) : 0, wg_co = KSP ? wg_ck - ks * n_co : wg_ck;
   const int sub = wg_tile % SUBS;
-  const int tile = UPS ? tile_arg : wg_tile / SUBS;
-  // Weight-folded workgroup (UPS variants with a fold list): its 8 x 8 "tile" is a tile of stored
-  // sites, its outputs are the up-sampled sites of one phase, (2 * row + fpy, 2 * column + fpx);
-  // it gathers the stored tensor directly (no interpolation) under a fold_k x fold_k window that
-  // starts fold_base[parity] rows / columns from the site, and takes that phase's weight set.
-  constexpr bool fold = MODE == kFolded;
+  const int tile = wg_tile / SUBS;
   constexpr bool ups = MODE == kInterpolate;  // this workgroup interpolates its patch
   const int r0 = sub * NROWS;  // first tile row of this workgroup
   const uint64_t row_mask = MB == 2 ? ~0ull : (0xffffffffull << (32 * sub));
-  const int n_tx = fold ? (p.lo_w + 7) >> 3 : p.go.tx;
-  const int tile_y = fast_div(tile, n_tx, fold ? p.lo_tx_magic : p.tx_magic), tile_x = tile - tile_y * n_tx;
-  const int s = p.stride, K = fold ? p.fold_k : p.k;
+  const int tile_y = fast_div(tile, p.go.tx, p.tx_magic), tile_x = tile - tile_y * p.go.tx;
+  const int s = p.stride, K = p.k;
   const int H = p.gi.h, W = p.gi.w, Cin = p.gi.c, Cout = p.go.c;
-  const int iy0 = fold ? tile_y * 8 + r0 + p.fold_base[fpy] : (tile_y * 8 + r0) * s - p.pad;
-  const int ix0 = fold ? tile_x * 8 + p.fold_base[fpx] : tile_x * 8 * s - p.pad;
+  const int iy0 = (tile_y * 8 + r0) * s - p.pad, ix0 = tile_x * 8 * s - p.pad;
   const int PH = (NROWS - 1) * s + K, PW = 7 * s + K;
   // The region whose stored occupancy is read: the patch itself, or (UPS) the low-resolution
   // sources of the patch: rows (iy0 >> 1) - 1 .. and columns likewise, PH / 2 + 3 by PW / 2 + 3
@@ -101,14 +78,7 @@
   for (int f = 0; f < kMaxFusedAdds; ++f) {
     skip_raw[f] = 0;
     if (f >= p.n_fused || dense) continue;
-    if (fold) {
-      // per lane (= site of the stored tile) the word of the up-sampled tile its output lies in;
-      // turned into this phase's site bits further down
-      const int ly = lane >> 3, lx = lane & 7;
-      skip_raw[f] = at_stream(p.fused[f].occ_skip, so)[(2 * tile_y + (ly >> 2)) * p.go.tx + 2 * tile_x + (lx >> 2)];
-    } else {
-      skip_raw[f] = at_stream(p.fused[f].occ_skip, so)[tile];
-    }
+    skip_raw[f] = at_stream(p.fused[f].occ_skip, so)[tile];
   }
   // While the occupancy words are on their way: everything about the gather that depends on the
   // tile's position only.
@@ -125,7 +95,7 @@
   const int RP = s == 1 ? ((PW * CS + 31) / 64) * 64 + 32 : PW * CS;
   float* const s_low = s_mem + PH * RP;  // UPS only
   const int last_site = GH * GW - 1;
-  const int gw_magic = p.gw_magic[fold ? 1 : ups ? 2 : 0];  // site / GW == (site * gw_magic) >> 16 for site < 441
+  const int gw_magic = p.gw_magic[ups ? 1 : 0];  // site / GW == (site * gw_magic) >> 16 for site < 441
   const unsigned row_bytes = (unsigned)(SW * Cin) * 4u, g_origin = (unsigned)gy0 * row_bytes + (unsigned)(gx0 * Cin) * 4u;
   // (a thread whose j-th item lies beyond the region repeats the last site's: the same value goes to
   // the same place twice, and no item needs a test of its own, only one that is the same for the
@@ -265,9 +235,8 @@
       const unsigned row = of_lane(lr * s + ky, bits);
       rows |= ky < K ? row : 0u;
     }
-    // (a weight-folded workgroup's tile lies inside the stored image, all of its outputs exist)
     // (no short circuits: they would become branches)
-    const bool exists = ((unsigned)lr < (unsigned)NROWS) & (fold | ((oy < p.go.h) & (ox < p.go.w)));
+    const bool exists = ((unsigned)lr < (unsigned)NROWS) & (oy < p.go.h) & (ox < p.go.w);
     const bool touched = exists & (dense | (((rows >> (lx * s)) & ((1u << K) - 1u)) != 0));
     touched_word = __ballot(touched);
   }
@@ -277,8 +246,6 @@
 #pragma unroll
   for (int f = 0; f < kMaxFusedAdds; ++f) {
     skip_word[f] = 0;
-    if (f < p.n_fused && fold && !dense)
-      skip_raw[f] = __ballot(((skip_raw[f] >> ((2 * ((lane >> 3) & 3) + fpy) * 8 + 2 * (lane & 3) + fpx)) & 1ull) != 0);
     if (f < p.n_fused) skip_word[f] = dense ? touched_word : (skip_raw[f] & row_mask);
     site_word |= skip_word[f];
   }
@@ -297,11 +264,12 @@
   const int co = tid & (NB - 1);
   const int co0 = wg_co * NB;
   const int es = tid / NB;
-  // (weight-folded: site (y, x) of the stored tile is output site (2y + fpy, 2x + fpx))
   const int ey = tile_y * 8 + r0 + (es >> 3), ex = tile_x * 8 + (es & 7);
   const unsigned ep_voff =
-      (unsigned)((((fold ? 2 * ey + fpy : ey) * p.go.w + (fold ? 2 * ex + fpx : ex)) * Cout + co0 + co) * 4);
-  const unsigned ep_step = (unsigned)((EP_SITES / 8) * p.go.w * Cout * 4) << (fold ? 1 : 0);
+      (unsigned)(((ey * p.go.w + ex) * Cout + co0 + co) * 4);
+  const unsigned ep_step = (unsigned)((EP_SITES / 8) * p.go.w * Cout * 4);
+  auto ep_at = [&](int it) { return (unsigned)it * ep_step; };
+  auto ep_bit = [](int it) { return it * EP_SITES; };
   const int out_bytes = p.go.h * p.go.w * Cout * 4;
   constexpr unsigned kSkipAccess = 0x80000000u;
   constexpr uint64_t kMine = EP_SITES == 8 ? 0x0101010101010101ull : EP_SITES == 16 ? 0x0001000100010001ull : 0x1ull;
@@ -314,7 +282,7 @@
     return __builtin_amdgcn_make_buffer_rsrc((void*)ptr, 0, out_bytes, 0x00020000);
   };
   auto ep_load = [&](const __amdgpu_buffer_rsrc_t& r, bool on, int it) {
-    return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, on ? ep_voff : kSkipAccess, it * ep_step, 0));
+    return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, on ? ep_voff : kSkipAccess, ep_at(it), 0));
   };
   const uint64_t touched_mine = mine(touched_word), site_mine = mine(site_word);
   const __amdgpu_buffer_rsrc_t z_rsrc = out_rsrc(at_stream(p.z, so));
@@ -461,9 +429,7 @@
   // B: buffer load with the lane part as vector offset and the unit part as scalar offset
   // (bytes; the launcher checks that the re-laid weights stay below 2 GiB).
   const unsigned w_plane = (unsigned)(K * K * cin_rows * cop) * 16u;  // the planes of the parts follow each other
-  const unsigned w_set = w_plane * PARTS;  // one weight set; a folded workgroup takes its phase's
-  const char* const w_base = fold ? (const char*)p.w_fold + (size_t)(fpy * 2 + fpx) * w_set : (const char*)p.w;
-  const __amdgpu_buffer_rsrc_t w_rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)w_base, 0, (int)w_set, 0x00020000);
+  const __amdgpu_buffer_rsrc_t w_rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)p.w, 0, (int)(w_plane * PARTS), 0x00020000);
   const unsigned w_lane = (unsigned)(half * cop + co0 + m) * 16u;
   unsigned w_table = 0;  // byte offset of unit `lane`'s weight rows in a chunk that starts at channel 0
   int a_table = 0;       // offset of its patch sites, words
@@ -483,7 +449,7 @@
       n_mine = n_taps * KG;
     }
     if (pair) n_mine = wave < 2 ? 1 : 0;
-    const int ky = __umul24(tap, p.k_magic[fold ? 1 : 0]) >> 16, kx = tap - __umul24(ky, K);  // tap < 49
+    const int ky = __umul24(tap, p.k_magic) >> 16, kx = tap - __umul24(ky, K);  // tap < 49
     a_table = __umul24(ky, RP) + kx * CS + kg * 8;  // a unit's 16 bf16 are 8 words
     w_table = (__umul24(tap, cin_rows) + kg * (UCH / 8)) * (unsigned)(cop * 16);  // 16-byte rows of 8 bf16
   };
@@ -631,31 +597,7 @@
   float sp_delta[EP_ITERS];  // residuals and rounding step of a fused sparsification layer
   float sp_k = 0.0f;
   auto request_fused = [&]() {
-#pragma unroll
-  for (int f = 0; f < kMaxFusedAdds; ++f) {
-#pragma unroll
-    for (int it = 0; it < EP_ITERS; ++it) f_skip[f][it] = f_zold[f][it] = 0.0f;
-    if (f >= p.n_fused) continue;
-    const uint64_t skip_mine = mine(skip_word[f]);
-    const __amdgpu_buffer_rsrc_t skip_rsrc = out_rsrc(at_stream(p.fused[f].skip, so));
-#pragma unroll
-    for (int it = 0; it < EP_ITERS; ++it) f_skip[f][it] = ep_load(skip_rsrc, has(skip_mine, it), it);
-    if (p.fused[f].keeps_z && !dense) {
-      const __amdgpu_buffer_rsrc_t fz_rsrc = out_rsrc(at_stream(p.fused[f].z, so));
-#pragma unroll
-      for (int it = 0; it < EP_ITERS; ++it) f_zold[f][it] = ep_load(fz_rsrc, has(site_mine, it), it);
-    }
-  }
-
-#pragma unroll
-  for (int it = 0; it < EP_ITERS; ++it) sp_delta[it] = 0.0f;
-  if (p.sp.delta && !dense) {
-    sp_k = *at_stream(p.sp.step, so);
-    const __amdgpu_buffer_rsrc_t d_rsrc = out_rsrc(at_stream(p.sp.delta, so));
-#pragma unroll
-    for (int it = 0; it < EP_ITERS; ++it) sp_delta[it] = ep_load(d_rsrc, sp_k > 0.0f && has(site_mine, it), it);
-  }
-
+#include "conv_mfma_fused_loads.h"
   };
   // (the arguments of the epilogue, loaded together)
   asm volatile("" ::"s"(p.out), "s"(p.bias), "s"(p.act), "s"(p.occ_out), "s"(p.occ_touched), "s"(p.sp.delta), "s"(p.fused[0].skip),
@@ -667,7 +609,7 @@
   // ---- reduce the NW partial sums through LDS: slots [NW][block*16 + reg][lane]
   // (fp32 mode: the weights are stored times a power of two, those of the odd waves' units negated;
   // see conv_mfma_negated and ConvParams::w_unscale)
-  const float unscale = (fold ? p.w_fold_unscale : p.w_unscale) * (pair ? 0.5f : 1.0f);
+  const float unscale = p.w_unscale * (pair ? 0.5f : 1.0f);
   auto spill = [&](float* part, float factor) {
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
@@ -762,155 +704,7 @@
       request_fused();
     }
   }
-  auto ep_store_at = [&](const __amdgpu_buffer_rsrc_t& r, unsigned voff, int it, float v) {
-    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), r, voff, it * ep_step, 0);
-  };
-  // Activations other than none / ReLU need branches (exp, tanh); nets made of the two simple
-  // ones, the usual case, take a loop without any: every decision that is the same for the whole
-  // workgroup becomes a select, so that the passes can be interleaved freely (a branch per
-  // decision and pass made each pass a chain of kernel-argument loads and waits).
-  bool simple_acts = p.act == kActNone || p.act == kActRelu;
-#pragma unroll
-  for (int f = 0; f < kMaxFusedAdds; ++f)
-    if (f < p.n_fused && p.fused[f].keeps_z && !(p.fused[f].act == kActNone || p.fused[f].act == kActRelu))
-      simple_acts = false;
-  // (one copy per number of fused ADDs, for one ADD with and without an accumulated tensor: a stage
-  // that does not exist would still issue its stores)
-  auto epilogue_simple = [&](auto sp_tag, auto nf_tag, auto kz_tag) {
-    constexpr bool HAS_SP = decltype(sp_tag)::value;
-    constexpr int NF = decltype(nf_tag)::value;   // fused ADDs
-    constexpr int KZ = decltype(kz_tag)::value;   // they keep a z: 0 no, 1 yes, 2 looked up
-    const bool relu0 = p.act == kActRelu;
-    bool f_kz[kMaxFusedAdds], f_relu[kMaxFusedAdds];
-    __amdgpu_buffer_rsrc_t f_out_r[kMaxFusedAdds], f_z_r[kMaxFusedAdds];
-#pragma unroll
-    for (int f = 0; f < NF; ++f) {
-      f_kz[f] = KZ == 2 ? p.fused[f].keeps_z != 0 : KZ == 1;
-      f_relu[f] = f_kz[f] && p.fused[f].act == kActRelu;
-      // (a z that does not exist is stored nowhere: its offsets are out of range)
-      f_out_r[f] = out_rsrc(at_stream(p.fused[f].out, so));
-      f_z_r[f] = out_rsrc(at_stream(f_kz[f] ? p.fused[f].z : p.out, so));
-    }
-    const __amdgpu_buffer_rsrc_t sp_delta_r = out_rsrc(at_stream(HAS_SP ? p.sp.delta : p.out, so));
-    const __amdgpu_buffer_rsrc_t sp_out_r = out_rsrc(at_stream(HAS_SP ? p.sp.out : p.out, so));
-#pragma unroll
-    for (int it = 0; it < EP_ITERS; ++it) {
-      const bool on_site = has(site_mine, it), on_conv = has(touched_mine, it);
-      const unsigned at_site = on_site ? ep_voff : kSkipAccess, at_conv = on_conv ? ep_voff : kSkipAccess;
-      // regular pass: z = v + bias, o = act(z); incremental: z += v, o = act(z_new) - act(z_old)
-      // (z_old reads as 0 in a regular pass, so ReLU's difference form serves both)
-      const float v = v_sum[it];
-      const float z_new = (dense ? bias : z_old[it]) + v;
-      ep_store_at(z_rsrc, at_conv, it, z_new);
-      float o = relu0 ? fmaxf(z_new, 0.0f) - fmaxf(z_old[it], 0.0f) : (dense ? z_new : v);
-      o = on_conv ? o : 0.0f;
-      ep_store_at(o_rsrc, at_conv, it, o);
-      if (o != 0.0f) nz_mine |= 1ull << (it * EP_SITES);
-      // fused ADD nodes (Eq.11 followed by Eq.12-14): a = the value just produced, b = skip input
-#pragma unroll
-      for (int f = 0; f < NF; ++f) {
-        const float lin = o + f_skip[f][it];
-        float o2 = lin;
-        if (KZ != 0) {
-          const float z2_new = dense ? lin : f_zold[f][it] + lin;
-          ep_store_at(f_z_r[f], f_kz[f] ? at_site : kSkipAccess, it, z2_new);
-          o2 = f_relu[f] ? fmaxf(z2_new, 0.0f) - fmaxf(f_zold[f][it], 0.0f) : lin;
-        }
-        o2 = on_site ? o2 : 0.0f;
-        ep_store_at(f_out_r[f], at_site, it, o2);
-        if (o2 != 0.0f) nz_fused_mine[f] |= 1ull << (it * EP_SITES);
-        o = o2;
-      }
-      // fused sparsification layer on the last stage's increment (Eq.3-8): x_corr = delta + x_inc,
-      // y_inc = k floor(0.5 + x_corr / k), delta = x_corr - y_inc where x_inc is nonzero; elsewhere
-      // y_inc = 0 and the residual stays.  A regular pass: identity, residual cleared.
-      if (HAS_SP) {
-#pragma clang fp contract(off)  // the residual is x_corr minus the rounded product, not a fused form
-        const bool sp_on = sp_k > 0.0f, moved = o != 0.0f;   // (sp_k is 0 in a regular pass)
-        const float x_corr = sp_delta[it] + o;
-        const float q = sp_k * floorf(0.5f + x_corr / sp_k);
-        const float y = sp_on ? (moved ? q : 0.0f) : o;
-        ep_store_at(sp_delta_r, (dense || (sp_on && moved)) ? at_site : kSkipAccess, it, dense ? 0.0f : x_corr - y);
-        ep_store_at(sp_out_r, at_site, it, y);
-        if (y != 0.0f) nz_sp_mine |= 1ull << (it * EP_SITES);
-      }
-    }
-  };
-  if (simple_acts) {
-    using std::integral_constant;
-    if (p.sp.delta) {
-      if (p.n_fused == 0) epilogue_simple(std::true_type{}, integral_constant<int, 0>{}, integral_constant<int, 0>{});
-      else if (p.n_fused == 1) epilogue_simple(std::true_type{}, integral_constant<int, 1>{}, integral_constant<int, 2>{});
-      else epilogue_simple(std::true_type{}, integral_constant<int, 2>{}, integral_constant<int, 2>{});
-    } else {
-      if (p.n_fused == 0) epilogue_simple(std::false_type{}, integral_constant<int, 0>{}, integral_constant<int, 0>{});
-      else if (p.n_fused == 1 && !p.fused[0].keeps_z) epilogue_simple(std::false_type{}, integral_constant<int, 1>{}, integral_constant<int, 0>{});
-      else if (p.n_fused == 1) epilogue_simple(std::false_type{}, integral_constant<int, 1>{}, integral_constant<int, 1>{});
-      else epilogue_simple(std::false_type{}, integral_constant<int, 2>{}, integral_constant<int, 2>{});
-    }
-  } else {
-#pragma unroll
-  for (int it = 0; it < EP_ITERS; ++it) {
-    const bool on_site = has(site_mine, it), on_conv = has(touched_mine, it);
-    const unsigned at_site = on_site ? ep_voff : kSkipAccess, at_conv = on_conv ? ep_voff : kSkipAccess;
-    float o;
-    {
-      const float v = v_sum[it];
-      if (dense) {
-        const float z = v + bias;
-        ep_store_at(z_rsrc, at_conv, it, z);
-        o = act_m(p.act, z);
-      } else {
-        const float z_new = z_old[it] + v;
-        ep_store_at(z_rsrc, at_conv, it, z_new);
-        o = (p.act == kActNone) ? v : act_m(p.act, z_new) - act_m(p.act, z_old[it]);
-      }
-      o = on_conv ? o : 0.0f;
-      ep_store_at(o_rsrc, at_conv, it, o);
-      if (o != 0.0f) nz_mine |= 1ull << (it * EP_SITES);
-    }
-    // fused ADD nodes (Eq.11 followed by Eq.12-14): a = the value just produced, b = skip input
-#pragma unroll
-    for (int f = 0; f < kMaxFusedAdds; ++f) {
-      if (f >= p.n_fused) break;
-      const auto& fa = p.fused[f];
-      const float lin = o + f_skip[f][it];
-      if (fa.keeps_z) {
-        const __amdgpu_buffer_rsrc_t fz_rsrc = out_rsrc(at_stream(fa.z, so));
-        if (dense) {
-          ep_store_at(fz_rsrc, at_site, it, lin);
-          o = act_m(fa.act, lin);
-        } else {
-          const float z2_old = f_zold[f][it];
-          const float z2_new = z2_old + lin;
-          ep_store_at(fz_rsrc, at_site, it, z2_new);
-          o = (fa.act == kActNone) ? lin : act_m(fa.act, z2_new) - act_m(fa.act, z2_old);
-        }
-      } else {
-        o = lin;
-      }
-      o = on_site ? o : 0.0f;
-      ep_store_at(out_rsrc(at_stream(fa.out, so)), at_site, it, o);
-      if (o != 0.0f) nz_fused_mine[f] |= 1ull << (it * EP_SITES);
-    }
-    // fused sparsification layer on the last stage's increment (Eq.3-8): x_corr = delta + x_inc,
-    // y_inc = k floor(0.5 + x_corr / k), delta = x_corr - y_inc where x_inc is nonzero; elsewhere
-    // y_inc = 0 and the residual stays.  A regular pass: identity, residual cleared.
-    if (p.sp.delta) {
-#pragma clang fp contract(off)  // the residual is x_corr minus the rounded product, not a fused form
-      float y = o;
-      if (dense) {
-        ep_store_at(out_rsrc(at_stream(p.sp.delta, so)), at_site, it, 0.0f);
-      } else if (sp_k > 0.0f) {
-        const float x_corr = sp_delta[it] + o;
-        y = (o != 0.0f) ? sp_k * floorf(0.5f + x_corr / sp_k) : 0.0f;
-        ep_store_at(out_rsrc(at_stream(p.sp.delta, so)), (o != 0.0f) ? at_site : kSkipAccess, it, x_corr - y);
-      }
-      ep_store_at(out_rsrc(at_stream(p.sp.out, so)), at_site, it, y);
-      if (y != 0.0f) nz_sp_mine |= 1ull << (it * EP_SITES);
-    }
-  }
-  }
+#include "conv_mfma_epilogue.h"
   EVK_PHASE(kPhEpilogueDone);
   // A site is nonzero where one of its 32 channels is: lanes 0-31 of a wave hold site es = 2 * wave
   // of every pass, lanes 32-63 site 2 * wave + 1, so one ballot per pass gives the wave's two site
@@ -940,51 +734,9 @@
   EVK_PHASE(kPhFlagsInLds);
   __syncthreads();
   EVK_PHASE(kPhFlagsBarrier);
-  if (tid < 4 * (4 + 2 * kMaxFusedAdds)) {
-    // Site bits of this workgroup into the words of up to 4 + 2 * (fused ADDs) sets: S and T of the
-    // conv, then T and S of each fused ADD (Eq.11b), then T and S of a fused sparsification layer
-    // (its T is the active set of the stage it reads).  All words of those sets are pre-zeroed and
-    // the other workgroups of a tile OR their share in.  Four lanes per set: a weight-folded
-    // workgroup's bits go to the words of the four up-sampled tiles over its stored tile, where
-    // site (y, x) is bit (2 * (y % 4) + fpy, 2 * (x % 4) + fpx) of tile (y / 4, x / 4), one of them
-    // per lane; otherwise the first of the four lanes writes the tile's own word.
-    const int set = tid >> 2, part = tid & 3;
-    // S of the producer as seen by this workgroup's rows and channels
-    uint64_t s_prev = dense ? touched_word : nz_word(0);
-    uint64_t bits = set == 0 ? s_prev : (set == 1 && wg_co == 0) ? touched_word : 0ull;
-    uint64_t* words = set == 0 ? p.occ_out : set == 1 ? p.occ_touched : nullptr;
-#pragma unroll
-    for (int f = 0; f < kMaxFusedAdds; ++f) {
-      if (f >= p.n_fused) break;
-      const auto& fa = p.fused[f];
-      const uint64_t t_f = s_prev | skip_word[f];  // Eq.11b
-      const uint64_t nz_f = nz_word(1 + f);
-      const uint64_t s_f = (fa.structural || dense) ? t_f : nz_f;
-      if (set == 2 + 2 * f) { bits = t_f; words = fa.occ_touched; }
-      if (set == 3 + 2 * f) { bits = s_f; words = fa.occ_out; }
-      s_prev = s_f;
-    }
-    if (p.sp.delta) {
-      const uint64_t nz_sp = nz_word(1 + kMaxFusedAdds);
-      if (set == 2 + 2 * kMaxFusedAdds) { bits = s_prev; words = p.sp.occ_touched; }
-      if (set == 3 + 2 * kMaxFusedAdds) { bits = dense ? s_prev : nz_sp; words = p.sp.occ_out; }
-    }
-    if (bits && words) {
-      words = at_stream(words, so);
-      if (!fold) {
-        if (part == 0) atomicOr((unsigned long long*)&words[tile], (unsigned long long)bits);
-      } else {
-        const int a = part >> 1, b = part & 1;
-        uint64_t spread = 0;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const unsigned nib = (unsigned)(bits >> ((4 * a + r) * 8 + 4 * b)) & 0xfu;
-          const unsigned wide = (nib & 1u) | ((nib & 2u) << 1) | ((nib & 4u) << 2) | ((nib & 8u) << 3);
-          spread |= (uint64_t)wide << ((2 * r + fpy) * 8 + fpx);
-        }
-        if (spread)
-          atomicOr((unsigned long long*)&words[(2 * tile_y + a) * p.go.tx + 2 * tile_x + b], (unsigned long long)spread);
-      }
-    }
+  if (tid < 4 + 2 * kMaxFusedAdds) {  // a lane per set
+    const int set = tid;
+#include "conv_mfma_set_words.h"
+    if (bits && words) atomicOr((unsigned long long*)&at_stream(words, so)[tile], (unsigned long long)bits);
   }
   EVK_PHASE(kPhEnd);

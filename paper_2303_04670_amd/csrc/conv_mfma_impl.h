@@ -46,13 +46,9 @@
 // old z values are requested before the contraction starts.  ADD nodes that consume the conv
 // output (residual add + activation, skip adds) run here as well, writing their own buffers.
 //
-// A bilinear x2 up-sampling in front of the conv (Eq.9-10: both linear) never exists in memory
-// (UPS variants).  Along the image border the patch is interpolated from the stored tensor on
-// its way into LDS.  Away from the border the up-sampling is folded into the weights: the
-// outputs of one phase (row parity, column parity) are a conv of the stored tensor with fewer
-// taps (4 x 4 for 5 x 5), so a workgroup takes one phase of one tile of stored sites, gathers
-// the stored tensor directly and writes its 64 outputs two sites apart.  Which workgroup does
-// which is read from a list made at set-up (ConvParams::fold_list).
+// A bilinear x2 up-sampling in front of the conv (Eq.9-10: both linear) never exists in memory: the patch is
+// interpolated from the stored tensor on its way into LDS (UPS variants), or the up-sampling is folded into the
+// weights (5 x 5, fp32 and split modes: conv_fold_impl.h).
 //
 // Vector instructions are kept few throughout: per-lane parts of an address are computed once and
 // kept, per-unit / per-row parts live in scalar registers (buffer instructions with a scalar
@@ -100,9 +96,31 @@ enum PhaseField {
 #ifdef EVCONV_PHASE_STAMPS
 constexpr unsigned kPhaseRecords = 1u << 15;
 static __device__ unsigned long long g_phase[kPhaseRecords][32];
-static __device__ unsigned g_phase_n;
+// (a counter for each of 64 classes of workgroups, in lines of their own: with one for all of them 704 workgroups
+// started 8 us apart, a queue at the counter)
+constexpr unsigned kPhaseClasses = 64, kPhaseClassRecords = kPhaseRecords / kPhaseClasses;
+static __device__ unsigned g_phase_n[kPhaseClasses][32];
+#define EVK_PHASE_OPEN() const unsigned ph_slot = tid == 0 ? phase_record(p) : 0xffffffffu
 #define EVK_PHASE(i) do { if (tid == 0 && ph_slot < kPhaseRecords) g_phase[ph_slot][i] = wall_clock64(); } while (0)
+template <class P>
+static __device__ unsigned phase_record(const P& p) {  // a record for this workgroup
+  const unsigned long long now = wall_clock64();
+  const unsigned cls = (blockIdx.x + blockIdx.y * gridDim.x) % kPhaseClasses, nth = atomicAdd(&g_phase_n[cls][0], 1u);
+  const unsigned slot = nth < kPhaseClassRecords ? cls * kPhaseClassRecords + nth : kPhaseRecords;
+  if (slot < kPhaseRecords) {
+    unsigned long long* r = g_phase[slot];
+    for (int i = 1; i < 24; ++i) r[i] = 0;
+    r[kPhStart] = now;
+    r[kPhGrid] = (unsigned long long)gridDim.x * gridDim.y;
+    r[kPhBlock] = blockIdx.x + (unsigned long long)blockIdx.y * gridDim.x;
+    r[kPhHwId] = __builtin_amdgcn_s_getreg(4 | (31 << 11)) | ((unsigned long long)__builtin_amdgcn_s_getreg(20 | (31 << 11)) << 32);
+    r[kPhLayer] = (unsigned long long)p.go.h | ((unsigned long long)p.gi.c << 16) | ((unsigned long long)p.k << 32) |
+                  ((unsigned long long)p.go.c << 40);
+  }
+  return slot;
+}
 #else
+#define EVK_PHASE_OPEN() do {} while (0)
 #define EVK_PHASE(i) do {} while (0)
 #endif
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -192,7 +210,6 @@ __device__ __forceinline__ void split3_large(float x, int shift, unsigned& h, un
 // What a workgroup gathers:
 constexpr int kPlain = 0;        // the stored tensor
 constexpr int kInterpolate = 1;  // UPS: the up-sampled tensor, interpolated from the stored one
-constexpr int kFolded = 2;       // UPS: the stored tensor, under weights that hold the up-sampling
 
 // Waves per SIMD that the registers of a variant are held to.  Five where the plain four-wave half tiles reach
 // them (bf16, and split mode in chunks of 64 channels: 88 to 96 registers): launches of 1024 to 1280 and of
@@ -214,7 +231,7 @@ void conv_mfma_kernel(ConvParams p) {
   // (what the prologue needs is loaded together, too: on demand it was a dozen loads, each waited for)
   if (MODE == kPlain) asm volatile("" ::"s"(p.gi.h), "s"(p.gi.w), "s"(p.gi.c), "s"(p.go.h), "s"(p.go.w), "s"(p.go.c), "s"(p.go.tx), "s"(p.k),
                "s"(p.stride), "s"(p.pad), "s"(p.dense), "s"(p.n_fused), "s"(p.c_out_pad), "s"(p.occ_in), "s"(p.in), "s"(p.z),
-               "s"(p.w), "s"(p.st.stride), "s"(p.wg_swap), "s"(p.tx_magic), "s"(p.gw_magic[0]), "s"(p.k_magic[0]));
+               "s"(p.w), "s"(p.st.stride), "s"(p.wg_swap), "s"(p.tx_magic), "s"(p.gw_magic[0]), "s"(p.k_magic));
   // this workgroup's stream: every state pointer of p is used through at_stream(.., so); p itself
   // stays untouched so that it remains in the kernel-argument segment
   const size_t so = (size_t)blockIdx.z * p.st.stride;
@@ -224,35 +241,18 @@ void conv_mfma_kernel(ConvParams p) {
   // blocks.  The launcher picks whichever of the two operands is larger to be split.
   const int wg_tile = p.wg_swap ? blockIdx.y : blockIdx.x, wg_ck = p.wg_swap ? blockIdx.x : blockIdx.y;
   constexpr bool UPS = MODE != kPlain, PAIR = false, LATE = false;
-  const int tile_arg = wg_tile / (2 / MB);
-  constexpr int fpy = 0, fpx = 0;
 #include "conv_mfma_body.h"
 }
 
 // args: byte offset of this workgroup's ConvParams in the kernel arguments
 // LATE: old z values are requested after the contraction, which leaves registers for one more wave per SIMD
 template <int CHUNK, int NW, int OPM, int MB, int MODE, bool KSP, int S2K, bool PAIR, bool LATE = false>
-__device__ __forceinline__ void conv_workgroup(const unsigned args, const int wg_tile, const int wg_ck, const int tile_arg,
-                                               const int fpy, const int fpx) {
+__device__ __forceinline__ void conv_workgroup(const unsigned args, const int wg_tile, const int wg_ck) {
   typedef const char __attribute__((address_space(4))) Byte;
   const auto& p = *(const ConvParams __attribute__((address_space(4)))*)((Byte*)__builtin_amdgcn_kernarg_segment_ptr() + args);
   const size_t so = (size_t)blockIdx.z * p.st.stride;
   constexpr bool UPS = MODE != kPlain;
 #include "conv_mfma_body.h"
-}
-
-// The input is a bilinear x2 up-sampling with folded weights: interpolating and weight-folded workgroups, a
-// body each, so that the loops of one do not carry the registers and branches of the other (256 -> 128 channels, 5 x 5
-// behind 32 x 44, fp32: 57.0 -> 53.4 us).
-template <int NW, int OPM, int MB>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(MB == 1 && NW != 4 ? 4 : 3)))
-void conv_mfma_up_kernel(ConvParams p) {
-  touch_params<ConvParams>();
-  const int wg_tile = p.wg_swap ? blockIdx.y : blockIdx.x, wg_ck = p.wg_swap ? blockIdx.x : blockIdx.y;
-  const int tile = wg_tile / (2 / MB);
-  const int e = p.fold_list[tile];
-  if (e < 0) conv_workgroup<32, NW, OPM, MB, kFolded, false, 0, false>(0, wg_tile, wg_ck, (-1 - e) >> 2, ((-1 - e) >> 1) & 1, (-1 - e) & 1);
-  else conv_workgroup<32, NW, OPM, MB, kInterpolate, false, 0, false>(0, wg_tile, wg_ck, e, 0, 0);
 }
 
 // Two convs that read the same tensor, in one launch (see launch_pair): the first n_first workgroups
@@ -267,7 +267,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void c
   const auto& p = *(const ConvParams __attribute__((address_space(4)))*)((Byte*)__builtin_amdgcn_kernarg_segment_ptr() + args);
   const int wg = (int)blockIdx.x - (second ? q.n_first : 0);
   const int y = wg / p.grid_x, x = wg - y * p.grid_x;
-  conv_workgroup<64, 8, OPM, 1, kPlain, true, 3, true>(args, p.wg_swap ? y : x, p.wg_swap ? x : y, 0, 0, 0);
+  conv_workgroup<64, 8, OPM, 1, kPlain, true, 3, true>(args, p.wg_swap ? y : x, p.wg_swap ? x : y);
 }
 
 // Up to four convs of the same tensor and one variant in one launch (see launch_batch): workgroup
@@ -286,7 +286,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(OPM == kOpB
   const auto& p = *(const ConvParams __attribute__((address_space(4)))*)(base + args);
   const int wg = (int)blockIdx.x - *(const int __attribute__((address_space(4)))*)(base + offsetof(ConvBatch, first) + i * sizeof(int));
   const int y = wg / p.grid_x, x = wg - y * p.grid_x;
-  conv_workgroup<32, 4, OPM, 1, kPlain, false, S2K, false, OPM == kOpBf16>(args, p.wg_swap ? y : x, p.wg_swap ? x : y, 0, 0, 0);
+  conv_workgroup<32, 4, OPM, 1, kPlain, false, S2K, false, OPM == kOpBf16>(args, p.wg_swap ? y : x, p.wg_swap ? x : y);
 }
 
 inline int chunk_for(const ConvParams& p) {
@@ -313,6 +313,12 @@ inline int chunk_for(const ConvParams& p) {
   return 16;
 }
 
+// divisors of the kernels' index arithmetic
+inline unsigned magic32(long long n, int d) {  // for dividends below n
+  return d == 1 || n * d >= (1ll << 32) ? 0u : (unsigned)((0x100000000ull + (unsigned)d - 1) / (unsigned)d);
+}
+inline int magic16(int d) { return (65536 + d - 1) / d; }
+
 // A variant's launch: its arguments, grid and dynamic LDS
 struct ConvLaunch { ConvParams q; dim3 grid; size_t lds; };
 template <int CHUNK, int NW, int OPM, int MB, bool KSP>
@@ -329,19 +335,11 @@ ConvLaunch variant_launch(const ConvParams& p) {
   const long long in_sites = p.upsample ? (long long)p.lo_h * p.lo_w : (long long)p.gi.h * p.gi.w;
   q.wg_swap = (long long)p.k * p.k * p.go.c > in_sites && p.go.tiles() * (2 / MB) <= 65535;
   const int n_ck = p.c_out_pad / 32 * (KSP ? p.ks : 1);
-  // divisors of the kernel's index arithmetic
-  auto magic32 = [](long long n, int d) {  // for dividends below n
-    return d == 1 || n * d >= (1ll << 32) ? 0u : (unsigned)((0x100000000ull + (unsigned)d - 1) / (unsigned)d);
-  };
-  auto magic16 = [](int d) { return (65536 + d - 1) / d; };
   q.tx_magic = magic32(p.go.tiles(), p.go.tx);
-  q.lo_tx_magic = p.upsample ? magic32(p.go.tiles(), (p.lo_w + 7) >> 3) : 0u;
   q.co_magic = magic32(n_ck, p.c_out_pad / 32);
-  q.k_magic[0] = magic16(p.k);
-  q.k_magic[1] = p.fold_list ? magic16(p.fold_k) : 0;
+  q.k_magic = magic16(p.k);
   q.gw_magic[0] = magic16(PW);
-  q.gw_magic[1] = p.fold_list ? magic16(7 + p.fold_k) : 0;
-  q.gw_magic[2] = magic16(PW / 2 + 3);
+  q.gw_magic[1] = magic16(PW / 2 + 3);
   q.nbx_magic = magic16(((PW - p.pad - 2) >> 1) - ((-p.pad - 1) >> 1) + 1);  // (a tile's first column is even)
   dim3 grid(p.go.tiles() * (2 / MB), n_ck, p.st.n);
   if (q.wg_swap) grid = dim3(n_ck, p.go.tiles() * (2 / MB), p.st.n);
@@ -356,12 +354,6 @@ void launch_variant(const ConvParams& p, hipStream_t s) {
   const ConvLaunch l = variant_launch<CHUNK, NW, OPM, MB, KSP>(p);
   if constexpr (CHUNK == 32 && !KSP && S2K == 0) {
     if (p.upsample) {
-      if constexpr (OPM != kOpBf16) {  // (weights declared as bf16 are not folded)
-        if (p.fold_list) {
-          hipLaunchKernelGGL((conv_mfma_up_kernel<NW, OPM, MB>), l.grid, dim3(NW * 64), l.lds, s, l.q);
-          return;
-        }
-      }
       hipLaunchKernelGGL((conv_mfma_kernel<CHUNK, NW, OPM, MB, kInterpolate, false, 0>), l.grid, dim3(NW * 64), l.lds, s, l.q);
       return;
     }
@@ -464,8 +456,16 @@ inline KSplit ksplit_for(const ConvParams& p) {
   return r;
 }
 
+#include "conv_fold_impl.h"
+
 template <int OPM>
 void launch_any(const ConvParams& p, hipStream_t s) {
+  if constexpr (OPM != kOpBf16) {  // (weights declared as bf16 are not folded)
+    if (p.upsample && p.fold_list) {
+      launch_fold<OPM>(p, s);
+      return;
+    }
+  }
   const KSplit r = p.upsample ? KSplit() : ksplit_for(p);
   if (r.ks) {
     ConvParams q = p;
@@ -556,14 +556,21 @@ void launch_batch(const ConvParams* convs, int n, hipStream_t s) {
 // build without phase stamps.
 inline int phase_stamps_read(unsigned long long* host, int max_records, bool reset) {
 #ifdef EVCONV_PHASE_STAMPS
-  unsigned n = 0;
+  static unsigned counts[kPhaseClasses][32];
   if (hipDeviceSynchronize() != hipSuccess) return -2;
-  if (hipMemcpyFromSymbol(&n, HIP_SYMBOL(g_phase_n), sizeof(n)) != hipSuccess) return -2;
-  const unsigned take = std::min(std::min(n, kPhaseRecords), (unsigned)std::max(max_records, 0));
-  if (host && take && hipMemcpyFromSymbol(host, HIP_SYMBOL(g_phase), sizeof(unsigned long long) * 32 * take) != hipSuccess) return -2;
+  if (hipMemcpyFromSymbol(counts, HIP_SYMBOL(g_phase_n), sizeof(counts)) != hipSuccess) return -2;
+  unsigned n = 0, taken = 0;
+  for (unsigned c = 0; c < kPhaseClasses; ++c) {
+    const unsigned take = std::min(std::min(counts[c][0], kPhaseClassRecords), (unsigned)std::max(max_records, 0) - taken);
+    if (host && take &&
+        hipMemcpyFromSymbol(host + (size_t)taken * 32, HIP_SYMBOL(g_phase), sizeof(unsigned long long) * 32 * take,
+                            sizeof(unsigned long long) * 32 * kPhaseClassRecords * c) != hipSuccess) return -2;
+    n += counts[c][0];
+    taken += take;
+  }
   if (reset) {
-    const unsigned zero = 0;
-    if (hipMemcpyToSymbol(HIP_SYMBOL(g_phase_n), &zero, sizeof(zero)) != hipSuccess) return -2;
+    static const unsigned zero[kPhaseClasses][32] = {};
+    if (hipMemcpyToSymbol(HIP_SYMBOL(g_phase_n), zero, sizeof(zero)) != hipSuccess) return -2;
   }
   return (int)n;
 #else

@@ -105,6 +105,11 @@ float weight_scale(const float* w, size_t n, bool* fits) {
 }
 int weight_part_count(int wdtype) { return wdtype == EVCONV_F32 ? 3 : wdtype == EVCONV_F32_SPLIT ? 2 : 1; }
 
+// Whether a 5 x 5 conv (stride 1, padding 2) behind a bilinear x2 up-sampling of lo_h x lo_w stored sites has the
+// up-sampling folded into its weights: where some 8 x 8 tile of stored sites lies wholly two sites or more away
+// from the border (smaller maps, half of whose taps would be those of a border, keep the interpolating gather).
+bool fold_pays(int lo_h, int lo_w) { return lo_h >= 18 && lo_w >= 18; }
+
 struct NodePlan {
   evconv_node_desc d;
   Geo ga, gb, go;
@@ -131,7 +136,6 @@ struct NodePlan {
   size_t off_w_fold = 0, off_fold_list = 0;
   void* w_fold = nullptr;
   int* fold_list = nullptr;
-  int fold_k = 0, fold_base[2] = {0, 0};
   // workspace offsets (bytes); resolved to pointers at create
   size_t off_step = 0;      // SPARSIFY: device scalar k
   size_t off_z2 = 0;        // MUL: accumulated second factor
@@ -367,9 +371,10 @@ evconv_status make_layout(const evconv_net_desc* desc, size_t weight_bytes, bool
                                 conv_narrow_weight_floats(n.c_out_pad) * 4));
       if (n.d.bias_off >= 0) n.off_bias = b.take((size_t)n.d.c_out * 4);
       if (n.d.op == EVCONV_OP_CONV2D && k == 5 && n.d.stride == 1 && n.d.pad == 2 && n.d.in0 >= 0 &&
-          L->nodes[n.d.in0].d.op == EVCONV_OP_UPSAMPLE_BILINEAR2X) {
-        // four phases x (4 x 4 taps) x input channels padded to 32 (see the planner in evconv_create)
-        n.off_w_fold = b.take((size_t)4 * 16 * ((n.d.c_in + 31) / 32 * 32) * n.c_out_pad * (n.d.wdtype == EVCONV_F32 ? 6 : 4));
+          L->nodes[n.d.in0].d.op == EVCONV_OP_UPSAMPLE_BILINEAR2X && fold_pays(n.ga.h / 2, n.ga.w / 2)) {
+        // four phases of taps (see prepare_fold) x input channels padded to 32
+        n.off_w_fold = b.take((size_t)4 * kFoldVectors * kFoldVectors * ((n.d.c_in + 31) / 32 * 32) * n.c_out_pad *
+                              (n.d.wdtype == EVCONV_F32 ? 6 : 4));
         n.off_fold_list = b.take((size_t)n.go.tiles() * 4);
       }
     }
@@ -492,8 +497,7 @@ evconv_status run_pass(evconv_net* net, const float* input, int builder_mode, Pa
     p.ks_part = (float*)(net->ws + net->L.off_ks_part);
     p.ks_count = (unsigned*)(net->ws + net->L.off_ks_count);
     p.y = nullptr; p.dy = nullptr; p.int_mode = 0;
-    p.fold_list = n.fold_list; p.w_fold = n.w_fold; p.fold_k = n.fold_k; p.wg_swap = 0;
-    p.fold_base[0] = n.fold_base[0]; p.fold_base[1] = n.fold_base[1];
+    p.fold_list = n.fold_list; p.w_fold = n.w_fold; p.wg_swap = 0;
     if (n.upsampled_from != -2) {
       // read the stored low-resolution tensor; p.gi stays the up-sampled geometry
       const int src = n.upsampled_from;
@@ -690,67 +694,46 @@ void fill_outputs(evconv_net* net, evconv_out* out) {
   }
 }
 
-// Weight folding for a conv (k x k, pad k/2, stride 1) that reads through a bilinear x2
-// up-sampling (half-pixel centres: row 2q of the up-sampled tensor is 0.75 * stored row q + 0.25 *
-// row q - 1, row 2q + 1 is 0.75 * row q + 0.25 * row q + 1).  Both are linear (Eq.9), so for
-// outputs of one parity the composition is a conv on the stored tensor with kf < k taps per
-// dimension.  That holds where the window meets neither the clamped first / last up-sampled row
-// nor the conv's zero padding: stored sites `edge` or more away from the border.  Tiles of stored
-// sites made of such sites only are computed per phase with the folded weights; the up-sampled
-// tiles over all other stored tiles go through the interpolating gather.  Writes the four weight
-// sets and the tile list into the workspace.  `lo` is the stored tensor's geometry.
+// The weight sets of the four phases and the list of tiles (conv_fold_impl.h), into the workspace.  `lo` is the
+// stored tensor's geometry.
 hipError_t prepare_fold(evconv_net* net, NodePlan& n, const void* weights, const Geo& lo) {
-  const int k = n.d.kh, pad = n.d.pad, ci_n = n.d.c_in, co_n = n.d.c_out, cop = n.c_out_pad;
-  int base[2], main_row[2][8], other_row[2][8], kf = 0;
-  for (int par = 0; par < 2; ++par) {
-    int first = 1 << 20, last = -(1 << 20);
+  constexpr int k = 5, taps = kFoldVectors * kFoldVectors;
+  const int ci_n = n.d.c_in, co_n = n.d.c_out, cop = n.c_out_pad;
+  if (!fold_pays(lo.h, lo.w)) return hipSuccess;
+  // vec[parity][vector][kernel row]: what the up-sampled row under a kernel row contributes to the vector's stored
+  // row (columns likewise).  Half-pixel centres: row 2q of the up-sampled tensor is 0.75 * stored row q + 0.25 * row q -
+  // 1, row 2q + 1 is 0.75 * row q + 0.25 * row q + 1.  On the first stored row up-sampled rows from 0 on exist, and
+  // their sources before row 0 are row 0 (the last row: mirrored).
+  double vec[2][kFoldVectors][k] = {};
+  for (int par = 0; par < 2; ++par)
     for (int ky = 0; ky < k; ++ky) {
-      const int r = par + ky - pad;                       // up-sampled row relative to 2 * (stored row)
-      const int q = r >= 0 ? r / 2 : -((1 - r) / 2);      // floor(r / 2)
-      main_row[par][ky] = q;
-      other_row[par][ky] = (r - 2 * q) ? q + 1 : q - 1;
-      first = std::min(first, std::min(main_row[par][ky], other_row[par][ky]));
-      last = std::max(last, std::max(main_row[par][ky], other_row[par][ky]));
+      const int r = par + ky - 2;                      // up-sampled row relative to 2 * (stored row)
+      const int q = r >= 0 ? r / 2 : -((1 - r) / 2);   // floor(r / 2)
+      const int src[2] = {q, (r - 2 * q) ? q + 1 : q - 1};
+      for (int e = 0; e < 2; ++e) {
+        const double coef = e ? 0.25 : 0.75;
+        vec[par][src[e] + 2 - par][ky] += coef;
+        if (r >= 0 && src[e] <= 0) vec[par][kFoldTop][ky] += coef;
+        if (r <= 1 && src[e] >= 0) vec[par][kFoldBottom][ky] += coef;
+      }
     }
-    base[par] = first;
-    kf = std::max(kf, last - first + 1);
-  }
-  const int edge = (pad + 2) / 2;
-  auto interior = [&](int t, int n_sites) { return 8 * t >= edge && 8 * t + 7 <= n_sites - 1 - edge; };
-  std::vector<int> list;
-  for (int ty = 0; ty < n.go.ty; ++ty)
-    for (int tx = 0; tx < n.go.tx; ++tx)
-      if (!(interior(ty / 2, lo.h) && interior(tx / 2, lo.w))) list.push_back(ty * n.go.tx + tx);
-  // (the border tiles' workgroups run longest: they come first; interleaving them with the folded
-  // ones measured 3.5 % slower)
-  if ((int)list.size() == n.go.tiles()) return hipSuccess;  // nothing away from the border: no folding
-  // Consecutive workgroups go to the chip's 8 XCDs in turn, each with an L2 of its own.  With the
-  // four phases of a tile next to each other an XCD runs one phase only and so reads one of the
-  // four weight sets (measured: placing a tile's phases on one XCD instead, to share the patch,
-  // raises the HBM fetch of the launches by 12 %: the weights outweigh the patches).
-  for (int ty = 0; ty < lo.ty; ++ty)
-    for (int tx = 0; tx < lo.tx; ++tx)
-      if (interior(ty, lo.h) && interior(tx, lo.w))
-        for (int ph = 0; ph < 4; ++ph) list.push_back(-(1 + 4 * (ty * lo.tx + tx) + ph));
-  if ((int)list.size() != n.go.tiles() || kf != 4) return hipSuccess;  // (room was reserved for 4 x 4 taps)
-
-  const float* src = (const float*)((const char*)weights + n.d.weight_off);
-  const int taps = kf * kf;
   std::vector<double> folded((size_t)4 * taps * ci_n * co_n, 0.0);
-  for (int py = 0; py < 2; ++py)
-    for (int px = 0; px < 2; ++px)
+  const float* src = (const float*)((const char*)weights + n.d.weight_off);
+  std::vector<double> w((size_t)k * k * ci_n * co_n);  // [tap][ci][co]
+  for (int co = 0; co < co_n; ++co)
+    for (int ci = 0; ci < ci_n; ++ci)
+      for (int t = 0; t < k * k; ++t) w[((size_t)t * ci_n + ci) * co_n + co] = src[((size_t)co * ci_n + ci) * k * k + t];
+  for (int ph = 0; ph < 4; ++ph)
+    for (int t = 0; t < taps; ++t) {
+      double* dst = &folded[((size_t)ph * taps + t) * ci_n * co_n];
       for (int ky = 0; ky < k; ++ky)
-        for (int kx = 0; kx < k; ++kx)
-          for (int sy = 0; sy < 2; ++sy)
-            for (int sx = 0; sx < 2; ++sx) {
-              const int ty = (sy ? other_row[py][ky] : main_row[py][ky]) - base[py];
-              const int tx = (sx ? other_row[px][kx] : main_row[px][kx]) - base[px];
-              const double coef = (sy ? 0.25 : 0.75) * (sx ? 0.25 : 0.75);
-              double* dst = &folded[((size_t)(py * 2 + px) * taps + ty * kf + tx) * ci_n * co_n];
-              for (int co = 0; co < co_n; ++co)
-                for (int ci = 0; ci < ci_n; ++ci)
-                  dst[(size_t)ci * co_n + co] += coef * (double)src[((size_t)co * ci_n + ci) * k * k + ky * k + kx];
-            }
+        for (int kx = 0; kx < k; ++kx) {
+          const double coef = vec[ph >> 1][t / kFoldVectors][ky] * vec[ph & 1][t % kFoldVectors][kx];
+          const double* from = &w[(size_t)(ky * k + kx) * ci_n * co_n];
+          if (coef != 0.0)
+            for (size_t e = 0; e < (size_t)ci_n * co_n; ++e) dst[e] += coef * from[e];
+        }
+    }
   const std::vector<float> values(folded.begin(), folded.end());
   const int parts = weight_part_count(n.d.wdtype);
   bool fits = true;
@@ -758,16 +741,13 @@ hipError_t prepare_fold(evconv_net* net, NodePlan& n, const void* weights, const
   if (!fits) return hipSuccess;  // (a sum of finite weights can overflow: not folded then)
   if (parts == 3) n.w_fold_scale = scale;
   const int ci_p = (ci_n + 31) / 32 * 32;
-  ConvParams probe;
-  probe.gi = n.ga; probe.go = n.go; probe.k = k; probe.stride = n.d.stride; probe.c_out_pad = cop; probe.n_fused = 0;
-  probe.pad = pad; probe.st = Streams{net->L.stride, net->L.n_streams}; probe.tail_units = n.tail_units;
-  probe.fp32 = n.d.wdtype == EVCONV_F32;
   const size_t plane = (size_t)taps * ci_p * cop;  // values per part and phase; a phase's planes follow each other
   std::vector<uint16_t> staging(4 * parts * plane, 0);
   for (int ph = 0; ph < 4; ++ph)
     for (int t = 0; t < taps; ++t)
       for (int c8 = 0; c8 < ci_n; c8 += 8) {
-        const float factor = parts == 3 && conv_mfma_negated(probe, t, c8) ? -n.w_fold_scale : n.w_fold_scale;
+        // (fp32 mode: every second group of 16 channels negated, those of the odd partial sums; see conv_mfma_negated)
+        const float factor = parts == 3 && (c8 / 16) % 2 ? -n.w_fold_scale : n.w_fold_scale;
         for (int co = 0; co < co_n; ++co) {
           float v[8];
           for (int e = 0; e < 8; ++e)
@@ -775,11 +755,14 @@ hipError_t prepare_fold(evconv_net* net, NodePlan& n, const void* weights, const
           weight_parts8(v, parts, staging.data() + ph * parts * plane + (((size_t)t * (ci_p / 8) + c8 / 8) * cop + co) * 8, plane);
         }
       }
+  // Tiles of the border first: their workgroups contract more taps.
+  std::vector<int> list, inner;
+  for (int ty = 0; ty < lo.ty; ++ty)
+    for (int tx = 0; tx < lo.tx; ++tx)
+      (ty == 0 || tx == 0 || ty == lo.ty - 1 || tx == lo.tx - 1 ? list : inner).push_back(ty * lo.tx + tx);
+  list.insert(list.end(), inner.begin(), inner.end());
   n.w_fold = net->ws + n.off_w_fold;
   n.fold_list = (int*)(net->ws + n.off_fold_list);
-  n.fold_k = kf;
-  n.fold_base[0] = base[0];
-  n.fold_base[1] = base[1];
   hipError_t e = hipMemcpy(n.w_fold, staging.data(), staging.size() * 2, hipMemcpyHostToDevice);
   if (e == hipSuccess) e = hipMemcpy(n.fold_list, list.data(), list.size() * 4, hipMemcpyHostToDevice);
   return e;

@@ -100,6 +100,11 @@ struct FusedSparsify {
   const float* step;        // device scalar: the rounding step k (0 = identity)
 };
 
+// Folded 5 x 5 behind an up-sampling: vectors of stored rows (columns) that an output site's rows (columns) of taps
+// come down to: four for a site away from the border, and one instead of some of them for a site of the first
+// and of the last stored row (column).
+constexpr int kFoldVectors = 6, kFoldTop = 4, kFoldBottom = 5;
+
 struct ConvParams {
   const float* in;          // H x W x C increment of the input node (full values if dense)
   const uint64_t* occ_in;   // its occupancy words
@@ -121,15 +126,10 @@ struct ConvParams {
   // matrix-core kernel only: the input is the bilinear x2 up-sampling of `in` (lo_h x lo_w stored
   // sites, occ_in their occupancy words); gi describes the up-sampled tensor
   int upsample, lo_h, lo_w;
-  // up-sampling variant, optional (null = off): weight folding.  conv o bilinear x2 is, for each
-  // output phase (row parity, column parity), a fold_k x fold_k stride-1 conv on the stored tensor
-  // wherever the window stays clear of the clamped image border (Eq.9: both are linear).
-  // fold_list has one entry per 8 x 8 tile of the output: v >= 0 = that up-sampled tile, run
-  // through the interpolating gather; v < 0 = -(1 + 4 * stored_tile + 2 * row parity + column
-  // parity): the 64 outputs of one phase over one 8 x 8 tile of stored sites.  w_fold: the four
-  // phases' weight sets, each in the layout of w with fold_k x fold_k taps.  fold_base[parity]:
-  // first row (column) of the window relative to the stored site.
-  const int* fold_list; const void* w_fold; int fold_k; int fold_base[2];
+  // 5 x 5 behind an up-sampling, optional (null = off): weight folding (conv_fold_impl.h).  fold_list: the 8 x 8
+  // tiles of the stored tensor in the order of their workgroups.  w_fold: the weight sets of the four
+  // output phases, kFoldVectors x kFoldVectors taps each, otherwise in the layout of w.
+  const int* fold_list; const void* w_fold;
   // matrix-core kernel only, set by its launcher: the grid's x dimension runs over the blocks of
   // 32 output channels and y over the tiles, instead of the other way round
   int wg_swap;
@@ -144,10 +144,10 @@ struct ConvParams {
   // conv_mfma_split_scratch gives
   int ks, ks_chunks;
   // divisors of the kernel's index arithmetic as magic factors, set by its launcher: tiles per row of
-  // the output and of the stored tensor, blocks of output channels, taps per row [plain, folded],
-  // gathered sites per row [plain, folded, up-sampled], 2 x 2 blocks per row of an up-sampled patch
-  unsigned tx_magic, lo_tx_magic, co_magic;
-  int k_magic[2], gw_magic[3], nbx_magic;
+  // the output (folded up-sampling: of the stored tensor), blocks of output channels, taps per row, gathered sites
+  // per row [plain, up-sampled], 2 x 2 blocks per row of an up-sampled patch
+  unsigned tx_magic, co_magic;
+  int k_magic, gw_magic[2], nbx_magic;
   int grid_x;  // matrix-core kernel only, set by its launcher: workgroups along the grid's x
   float* ks_part; unsigned* ks_count;
   // few-channel pointwise kernel only: the node is a network output and the kernel keeps the

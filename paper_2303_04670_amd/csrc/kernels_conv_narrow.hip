@@ -50,7 +50,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MAXE <= 3 ?
   touch_params<ConvParams>();
   asm volatile("" ::"s"(p.gi.h), "s"(p.gi.w), "s"(p.gi.c), "s"(p.gi.tx), "s"(p.gi.ty), "s"(p.go.h), "s"(p.go.w), "s"(p.go.c), "s"(p.go.tx),
                "s"(p.go.ty), "s"(p.k), "s"(p.stride), "s"(p.pad), "s"(p.dense), "s"(p.occ_in), "s"(p.in), "s"(p.z), "s"(p.out), "s"(p.w),
-               "s"(p.st.stride), "s"(p.tx_magic), "s"(p.k_magic[0]), "s"(p.k_magic[1]), "s"(p.gw_magic[0]));
+               "s"(p.st.stride), "s"(p.tx_magic), "s"(p.k_magic), "s"(p.co_magic), "s"(p.gw_magic[0]));
   const size_t so = (size_t)blockIdx.z * p.st.stride;  // this workgroup's stream
   constexpr int NT = 256;
   extern __shared__ __align__(16) float s_patch[];
@@ -64,9 +64,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MAXE <= 3 ?
   const int P = 7 * s + K;  // patch edge, <= 21
   const int CS = Cin | 1;   // odd LDS site stride
   const int k_tot = K * K * Cin, n_steps = (k_tot + 3) >> 2;
-  const int cin_magic = p.k_magic[1];  // e / Cin == (e * cin_magic) >> 16 for e < 3600 (Cin <= 8)
+  const int cin_magic = (int)p.co_magic;  // e / Cin == (e * cin_magic) >> 16 for e < 3600 (Cin <= 8)
   const int p_magic = p.gw_magic[0];   // site / P likewise for site < 441
-  const int k_magic = p.k_magic[0];    // tap / K likewise for tap < 49
+  const int k_magic = p.k_magic;    // tap / K likewise for tap < 49
   __shared__ __align__(16) int s_koff[4][kMaxSteps];  // [k % 4][step]
 
   // once per workgroup: the LDS position of the patch element that operand k multiplies, relative to the
@@ -292,8 +292,8 @@ void launch_conv_narrow(const ConvParams& p, hipStream_t s) {
   // divisors of the kernel's index arithmetic (tiles per row: exact while the product fits 32 bits)
   ConvParams q = p;
   q.tx_magic = p.go.tx == 1 || (long long)p.go.tiles() * p.go.tx >= (1ll << 32) ? 0u : (unsigned)((0x100000000ull + (unsigned)p.go.tx - 1) / (unsigned)p.go.tx);
-  q.k_magic[0] = (65536 + p.k - 1) / p.k;
-  q.k_magic[1] = (65536 + p.gi.c - 1) / p.gi.c;
+  q.k_magic = (65536 + p.k - 1) / p.k;
+  q.co_magic = (65536 + p.gi.c - 1) / p.gi.c;
   q.gw_magic[0] = (65536 + P - 1) / P;
   if (P * P * p.gi.c <= 3 * 256) hipLaunchKernelGGL(conv_narrow_kernel<3>, grid, dim3(256), lds, s, q);
   else hipLaunchKernelGGL(conv_narrow_kernel<kMaxPatchPerThread>, grid, dim3(256), lds, s, q);

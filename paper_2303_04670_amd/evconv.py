@@ -31,7 +31,7 @@ EXPORTS = ["evconv_query_workspace", "evconv_create", "evconv_num_outputs", "evc
            "evconv_profile_end", "evconv_get_node_time", "evconv_set_refresh_period", "evconv_get_state_stream",
            "evconv_stream_stride", "evconv_current_mode", "evconv_create_static", "evconv_debug_chip_probes",
            "evconv_debug_phase_stamps"]
-STATIC_WORKSPACE_BYTES = 52 << 20
+STATIC_WORKSPACE_BYTES = 120 << 20
 
 
 class NodeDesc(ctypes.Structure):

@@ -1311,6 +1311,51 @@ def test_folded_upsampling_smallest_interiors(h, w, ci, co):
     run_stream(net, frames[0], frames[1:], "frame", label=f"fold{h}x{w}", max_flips=10)
 
 
+@pytest.mark.parametrize("h,w,ci,co,mode", [(18, 18, 32, 32, "f32"), (20, 45, 64, 40, "split"), (59, 68, 32, 64, "f32"), (60, 66, 96, 64, "split"),
+                                            (64, 65, 32, 64, "f32"), (57, 72, 33, 64, "f32"), (66, 63, 40, 50, "split")])
+def test_folded_upsampling_borders(h, w, ci, co, mode):
+    """The folded kernel's border taps, in half tiles (the first two) and in whole ones: last tiles of one to
+    eight rows and columns (one block of the upper rows or of eight rows of four columns where the image
+    holds no more), ragged channels.  Against the oracle at every step; then infinite and NaN increments on
+    the border: not a site further than the oracle's."""
+    _say(f"folded up-sampling, borders: stored tensor {h}x{w}, {ci} -> {co} channels, {mode}")
+    b = wl._NetBuilder("fold_border", ci, h, w, 11 * h + w, bias=True)
+    u = b.simple(wl.OP_UPSAMPLE2X, -1)
+    c = b.conv(u, co, 5, 1, act=wl.ACT_NONE, out=1)
+    net = b.finish()
+    if mode == "split":
+        net = wl.with_weight_dtype(net, wl.WD_F32_SPLIT)
+    gpu, ora = ev.EvConvNet(net), Oracle(net)
+    assert gpu.kernel_name(u) == "fused_into_conv_weights"
+    rng = np.random.default_rng(h)
+    x0 = rng.standard_normal((ci, h, w)).astype(np.float32)
+    edge = np.zeros((1, h, w), bool)
+    edge[:, [0, 1, -2, -1]] = edge[:, :, [0, 1, -2, -1]] = True
+    rep = cmp.Report()
+    gpu.reset(_dev(x0))
+    ora.reset(x0)
+    # fp32 sums of at most 25 * 96 products (2^-24 each, random) and 16-bit parts (2^-16 a product)
+    tol = 2e-6 if mode == "f32" else 4e-5
+    for q in (1.0, 0.1, 0.02):
+        d = (rng.standard_normal(x0.shape) * ((rng.random((1, h, w)) < q) & (edge | (q > 0.05)))).astype(np.float32)
+        gpu.step(_dev(d))
+        ora.step_increment(d)
+        z, zr = gpu.state(c, ev.STATE_Z).astype(np.float64), ora.z(c)
+        assert np.abs(z - zr).max() <= tol * np.abs(zr).max(), np.abs(z - zr).max() / np.abs(zr).max()
+        cmp.compare_outputs(gpu, ora, rep)
+        cmp.compare_node(gpu, ora, c, rep, tol=tol, act_scale=np.abs(zr).max())
+    if mode == "f32":
+        d = np.zeros_like(x0)
+        d[0, 0, 3], d[1, h - 1, 0], d[2, h // 2, w - 1], d[3, h - 1, w - 2], d[4, 1, w // 2] = np.inf, -np.inf, np.inf, np.nan, -np.inf
+        gpu.step(_dev(d))
+        ora.step_increment(d)
+        # (which of infinity and NaN depends on whether the taps of a source meet before or after its products)
+        z, zr = gpu.state(c, ev.STATE_Z), ora.z(c)
+        np.testing.assert_array_equal(np.isfinite(z), np.isfinite(zr))
+        assert 0 < np.isfinite(zr).sum() < zr.size
+    gpu.destroy()
+
+
 # --------------------------------------------------------------------------- recurrent state
 
 def _running_sum_net(c, h, w):
