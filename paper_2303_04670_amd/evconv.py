@@ -170,9 +170,10 @@ def evconv_query_workspace(desc: NetDesc) -> int:
 
 
 class _DeviceBytes:
-    """A span of device memory owned by somebody else, for torch.as_tensor (no copy)."""
+    """A span of device memory, for torch.as_tensor (no copy); the tensor keeps its owner alive."""
 
-    def __init__(self, ptr, typestr, shape):
+    def __init__(self, ptr, typestr, shape, owner):
+        self.owner = owner
         self.__cuda_array_interface__ = {"shape": shape, "typestr": typestr, "data": (ptr, False), "version": 2}
 
 
@@ -308,7 +309,7 @@ class EvConvNet:
 
     def outputs(self, stream=0):
         """Per output node: dict of torch views (y, dy as C x H x W; idx; count) of one stream, valid
-        until the next call on this net.  The caller synchronises the stream before reading.  Before the
+        until the next call on this net; they keep its workspace alive.  The caller synchronises the stream before reading.  Before the
         first reset there are none: EvConvError(ERR_STATE)."""
         spans = self._out_spans.get(stream)
         if spans is None:
@@ -323,7 +324,7 @@ class EvConvNet:
 
             def span(ptr, typestr, *shape):  # (in its type and shape at once: each view would take 1-3 us)
                 nonlocal in_place
-                t = torch.as_tensor(_DeviceBytes(ptr + base, typestr, shape), device=self.device)
+                t = torch.as_tensor(_DeviceBytes(ptr + base, typestr, shape, self.workspace), device=self.device)
                 in_place &= t.data_ptr() == ptr + base
                 return t
             for o in self._outs:

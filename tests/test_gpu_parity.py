@@ -2504,6 +2504,23 @@ def test_large_wide_outputs_read_active_sites_only(mode):
     gpu.destroy()
 
 
+def test_outputs_keep_the_workspace():
+    """Outputs that outlive their net: its workspace is not given to the next allocation under them."""
+    import gc
+    import torch
+    net = wl.net_single_conv(3, 16, 40, 48)
+    rng = np.random.default_rng(3)
+    gpu = ev.EvConvNet(net)
+    gpu.reset(_dev(rng.standard_normal((16, 40, 48)).astype(np.float32)))
+    out, size = gpu.outputs()[0], gpu.workspace.numel()
+    want = out["y"].clone()
+    del gpu
+    gc.collect()
+    for _ in range(4):
+        torch.full((size,), 255, dtype=torch.uint8, device="cuda")
+    assert torch.equal(out["y"], want)
+
+
 def test_reset_clears_arrival_counters():
     """Counters that a pass cut short leaves behind (here: written by hand, behind the last node's
     occupancy words and behind the last output) are cleared by a reset, those of the channel split by
