@@ -356,8 +356,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, MB == 2 
           ring[1 - i] = b_load(cs, j + i + 1);
           // (left to itself the compiler requests it among the unit's last MFMAs: half tiles 10-20 % slower)
           __builtin_amdgcn_sched_barrier(0);
-          unit(acc[0], a_load(j + i, at, 0), ring[i]);
-          if (TWO) unit(acc[MB - 1], a_load(j + i, at, MB - 1), ring[i]);
+          const BF a0 = a_load(j + i, at, 0), a1 = TWO ? a_load(j + i, at, MB - 1) : a0;
+          __builtin_amdgcn_sched_barrier(0);
+          unit(acc[0], a0, ring[i]);
+          if (TWO) unit(acc[MB - 1], a1, ring[i]);
         };
         for (; j + 2 <= n_mine; j += 2) {
           step(0);
