@@ -386,6 +386,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, MB == 2 
   }
 #endif
 
+  // ---- epilogue: its operands are requested before the waves' sums meet
+  const __amdgpu_buffer_rsrc_t z_rsrc = out_rsrc(at_stream(p.z, so)), o_rsrc = out_rsrc(at_stream(p.out, so));
+  float z_old[EP_ITERS], f_skip[kMaxFusedAdds][EP_ITERS], f_zold[kMaxFusedAdds][EP_ITERS], sp_delta[EP_ITERS];
+  float sp_k = 0.0f;
+#pragma unroll
+  for (int it = 0; it < EP_ITERS; ++it) z_old[it] = ep_load(z_rsrc, !dense && has(touched_mine, it), it);
+  {
+#include "conv_mfma_fused_loads.h"
+  }
+  EVK_PHASE(kPhFusedRequested);
   float v_sum[EP_ITERS];
   // (fp32 mode: the weights are stored times a power of two, those of the odd units negated)
   const float unscale = p.w_fold_unscale;
@@ -403,16 +413,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, MB == 2 
   }
 
   EVK_PHASE(kPhReduced);
-  // ---- epilogue
-  const __amdgpu_buffer_rsrc_t z_rsrc = out_rsrc(at_stream(p.z, so)), o_rsrc = out_rsrc(at_stream(p.out, so));
-  float z_old[EP_ITERS], f_skip[kMaxFusedAdds][EP_ITERS], f_zold[kMaxFusedAdds][EP_ITERS], sp_delta[EP_ITERS];
-  float sp_k = 0.0f;
-#pragma unroll
-  for (int it = 0; it < EP_ITERS; ++it) z_old[it] = ep_load(z_rsrc, !dense && has(touched_mine, it), it);
-  {
-#include "conv_mfma_fused_loads.h"
-  }
-  EVK_PHASE(kPhFusedRequested);
 #ifdef EVCONV_PHASE_STAMPS
   __builtin_amdgcn_s_waitcnt(0);
   EVK_PHASE(kPhArrived);
