@@ -621,6 +621,77 @@ __global__ __launch_bounds__(256) void elementwise_kernel(EwParams p) {
   }
 }
 
+// Concatenation of operands whose channel counts are not multiples of four (Eq.11: the structural OR of the
+// two active sets).  An operand's channels are taken four at a time all the same: 16-byte accesses need dword
+// alignment only, and the last one to three channels of a site go singly.  A site's run of floats is one
+// workgroup's, up to kConcatItems pieces.  Bound by HBM; with single floats, in runs of 16 channels that begin
+// anywhere in a line, 5 + 64 channels on 256 x 352, every site active, 21.2 us, now 13.3 (3.7 TB/s).
+constexpr int kConcatItems = 32;
+typedef float floatx4u __attribute__((ext_vector_type(4), aligned(4)));
+__global__ __launch_bounds__(256) void concat_ragged_kernel(EwParams p) {
+  touch_params<EwParams>();
+  const size_t so = (size_t)blockIdx.z * p.st.stride;
+  const float* const pa = at_stream(p.a, so);
+  const float* const pb = at_stream(p.b, so);
+  float* const pout = at_stream(p.out, so);
+  const bool dense = p.dense != 0;
+  const int tid = threadIdx.x, lane = tid & 63, tile = blockIdx.x;
+  const int tile_y = p.tx_magic ? (int)__umulhi((unsigned)tile, p.tx_magic) : tile / p.go.tx, tile_x = tile - tile_y * p.go.tx;
+  const uint64_t inb = inbounds_word(p.go.h, p.go.w, tile_y, tile_x);
+  const uint64_t wa = dense ? ~0ull : at_stream(p.occ_a, so)[tile], wb = dense ? ~0ull : at_stream(p.occ_b, so)[tile];
+  const uint64_t word = dense ? inb : wa | wb;
+  if (word == 0) return;
+  const int ca = p.ga.c, cb = p.gb.c, C = p.go.c, na = (ca + 3) >> 2;
+  // pieces [i0, i0 + ni) of every touched site belong to this workgroup
+  const int i0 = blockIdx.y * p.vec_per_block, ni = min(p.vec_per_block, na + ((cb + 3) >> 2) - i0);
+  const int ni_magic = (65536 + ni - 1) / ni;  // e / ni == (e * ni_magic) >> 16 for e < 2048 (ni <= 32)
+  const int n_sites = __popcll(word), total = n_sites * ni;
+  // lane r: the r-th touched site
+  const int below = __builtin_amdgcn_mbcnt_hi((unsigned)(word >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)word, 0u));
+  const int nth = __builtin_amdgcn_ds_permute((((word >> lane) & 1ull) ? below : n_sites + lane - below) * 4, lane);
+  constexpr int N = 4;
+  for (int e0 = __builtin_amdgcn_readfirstlane(tid >> 6) * 64; e0 < total; e0 += N * 256) {
+    float4 v[N];
+    float* to[N];
+    int n[N];  // floats of the piece, 0: none
+#pragma unroll
+    for (int it = 0; it < N; ++it) {
+      const int e = e0 + lane + it * 256, r = (int)(__umul24(e, ni_magic) >> 16);
+      const int site = __builtin_amdgcn_ds_bpermute(r * 4, nth);  // (r counts modulo 64)
+      const int i = i0 + e - __umul24(r, ni), q = (tile_y * 8 + (site >> 3)) * p.go.w + tile_x * 8 + (site & 7);
+      const bool of_a = i < na;
+      const int c = (of_a ? i : i - na) * 4, cn = of_a ? ca : cb;
+      const float* const from = (of_a ? pa : pb) + ((size_t)q * cn + c);
+      const bool on = e < total && (((of_a ? wa : wb) >> site) & 1ull);
+      n[it] = e < total ? min(4, cn - c) : 0;
+      to[it] = pout + ((size_t)q * C + (of_a ? c : ca + c));
+      v[it] = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (on && n[it] == 4) {
+        const floatx4u x = *(const floatx4u*)from;
+        v[it] = make_float4(x.x, x.y, x.z, x.w);
+      } else if (on) {
+        v[it].x = from[0];
+        if (n[it] > 1) v[it].y = from[1];
+        if (n[it] > 2) v[it].z = from[2];
+      }
+    }
+#pragma unroll
+    for (int it = 0; it < N; ++it) {
+      if (n[it] == 4) {
+        *(floatx4u*)to[it] = floatx4u{v[it].x, v[it].y, v[it].z, v[it].w};
+      } else {
+        if (n[it] > 0) to[it][0] = v[it].x;
+        if (n[it] > 1) to[it][1] = v[it].y;
+        if (n[it] > 2) to[it][2] = v[it].z;
+      }
+    }
+  }
+  if (tid == 0 && blockIdx.y == 0) {
+    at_stream(p.occ_out, so)[tile] = word;
+    at_stream(p.occ_touched, so)[tile] = word;
+  }
+}
+
 template <int OP, int VEC>
 void launch_ew(const EwParams& q, const dim3& grid, hipStream_t s) {
   constexpr int kMax = ew_in_flight(OP, VEC);
@@ -633,24 +704,30 @@ void launch_ew(const EwParams& q, const dim3& grid, hipStream_t s) {
 void launch_elementwise(const EwParams& p, hipStream_t s) {
   bool vec4 = (p.go.c % 4) == 0;
   if (p.op == kEwConcat || p.op == kEwConcatUp) vec4 = vec4 && (p.ga.c % 4) == 0;
-  const int cv_all = p.go.c / (vec4 ? 4 : 1);
   // Maps of few tiles are split over the channels, down to one pass of the 256 threads over a full tile
   // (4 vectors of 64 sites), until there are 384 workgroups: ResNet-18's 56 x 56 x 64 max-pool, 49
   // workgroups of four passes in sequence, 11.8 -> 6.8 us.  More cost sparse steps more than they give
   // dense ones (three nodes on 32 x 44 x 512 with 5 % of the sites active: 21.5 us in 192 workgroups, 22.8 in 384,
   // 26.8 in 768; on 64 x 88 x 128, all sites: 37.5 in 176, 28.9 in 352, 25.8 in 704).
   EwParams q = p;
-  q.vec_per_block = kEwVecPerBlock;
+  const bool ragged_concat = p.op == kEwConcat && !vec4;
+  const int cv_all = ragged_concat ? (p.ga.c + 3) / 4 + (p.gb.c + 3) / 4 : p.go.c / (vec4 ? 4 : 1);
+  q.vec_per_block = ragged_concat ? kConcatItems : kEwVecPerBlock;
   while (q.vec_per_block > kEwVecPerBlock / 4 &&
          (long long)p.go.tiles() * ((cv_all + q.vec_per_block - 1) / q.vec_per_block) * p.st.n < 384)
     q.vec_per_block /= 2;
   dim3 grid(p.go.tiles(), (cv_all + q.vec_per_block - 1) / q.vec_per_block, p.st.n);
   q.tx_magic = p.go.tx == 1 || (long long)p.go.tiles() * p.go.tx >= (1ll << 32)
                    ? 0u : (unsigned)((0x100000000ull + (unsigned)p.go.tx - 1) / (unsigned)p.go.tx);
+  if (ragged_concat) {
+    hipLaunchKernelGGL(concat_ragged_kernel, grid, dim3(256), 0, s, q);
+    return;
+  }
 #define EVK_EW(OP) case OP: if (vec4) launch_ew<OP, 4>(q, grid, s); else launch_ew<OP, 1>(q, grid, s); break;
   switch (p.op) {
-    EVK_EW(kEwAdd) EVK_EW(kEwAct) EVK_EW(kEwConcat) EVK_EW(kEwUp2x) EVK_EW(kEwPoolAcc) EVK_EW(kEwPoolMax) EVK_EW(kEwSparsify)
+    EVK_EW(kEwAdd) EVK_EW(kEwAct) EVK_EW(kEwUp2x) EVK_EW(kEwPoolAcc) EVK_EW(kEwPoolMax) EVK_EW(kEwSparsify)
     EVK_EW(kEwMul) EVK_EW(kEwConcatUp)
+    case kEwConcat: launch_ew<kEwConcat, 4>(q, grid, s); break;  // (the others: above)
   }
 #undef EVK_EW
 }

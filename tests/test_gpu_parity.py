@@ -2504,6 +2504,35 @@ def test_large_wide_outputs_read_active_sites_only(mode):
     gpu.destroy()
 
 
+@pytest.mark.parametrize("ca,cb,hw", [(5, 64, (17, 20)), (1, 1, (9, 7)), (6, 3, (8, 33)), (4, 7, (25, 12)), (130, 9, (16, 24)), (67, 66, (72, 80))])
+def test_concat_of_ragged_channel_counts(ca, cb, hw):
+    """Concatenations whose operands are not whole vectors of four channels, one to three pieces of a site
+    left over, several workgroups to a tile where a site has more than 32 pieces: copies of the operands'
+    increments where these are active and zeros elsewhere, the OR of their sets, bit for bit."""
+    h, w = hw
+    _say(f"concat {ca} + {cb} channels on {h} x {w}")
+    b = wl._NetBuilder("cat", ca, h, w, ca + cb)
+    x = b.conv(-1, cb, 1, 1, 0, act=wl.ACT_RELU)
+    y = b.simple(wl.OP_CONCAT, -1, x)
+    b.conv(y, 2, 1, 1, 0, act=wl.ACT_NONE, out=1)
+    gpu = ev.EvConvNet(b.finish(), flags=ev.FLAG_NO_FUSION)
+    rng = np.random.default_rng(ca)
+    gpu.reset(_dev(rng.standard_normal((ca, h, w)).astype(np.float32)))
+    for q in (0.02, 1.0, 0.3):
+        gpu.step(_dev((rng.standard_normal((ca, h, w)) * (rng.random((1, h, w)) < q)).astype(np.float32)))
+        sets = [cmp.words_to_mask(gpu.state(n, ev.STATE_OCC), h, w) != 0 for n in (-1, x)]
+        want = np.concatenate([np.where(s[..., None], gpu.state(n, ev.STATE_DY), np.float32(0)) for n, s in zip((-1, x), sets)], axis=2)
+        both = sets[0] | sets[1]
+        np.testing.assert_array_equal(cmp.words_to_mask(gpu.state(y, ev.STATE_OCC), h, w) != 0, both)
+        np.testing.assert_array_equal(cmp.words_to_mask(gpu.state(y, ev.STATE_OCC_TOUCHED), h, w) != 0, both)
+        np.testing.assert_array_equal(gpu.state(y, ev.STATE_DY)[both], want[both])
+    x1 = rng.standard_normal((ca, h, w)).astype(np.float32)
+    gpu.reset(_dev(x1))   # a regular pass: the values at every site
+    np.testing.assert_array_equal(gpu.state(y, ev.STATE_DY)[..., :ca], x1.transpose(1, 2, 0))
+    np.testing.assert_array_equal(gpu.state(y, ev.STATE_DY)[..., ca:], gpu.state(x, ev.STATE_DY))
+    gpu.destroy()
+
+
 def test_outputs_keep_the_workspace():
     """Outputs that outlive their net: its workspace is not given to the next allocation under them."""
     import gc
