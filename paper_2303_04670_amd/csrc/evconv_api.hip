@@ -655,7 +655,6 @@ evconv_status run_pass(evconv_net* net, const float* input, int builder_mode, Pa
     if (n.kernel == kKernDelay && !(save_in_lists && n.saved_in_lists)) launch_copy_u64(n.occ_saved, net->L.nodes[n.d.in0].occ, (size_t)n.go.tiles(), net->st, s);
   }
   net->last_dense = dense != 0;
-  if (pass == kPassReset) launch_fill_u64(net->occ_nodes, net->L.n_occ_words, 0, net->st, s);
   if (pass == kPassRefresh) {
     // the nodes' buffers hold values, not increments: every set is emptied, except the active sets of
     // the output nodes, whose dy = y(n) - y(n-1) is a genuine increment at every site
@@ -673,6 +672,7 @@ evconv_status run_pass(evconv_net* net, const float* input, int builder_mode, Pa
     FinishParams fp;
     fp.sets = net->sets_dev; fp.n_sets = (int)net->L.nodes.size() + 1; fp.max_ty = net->L.max_ty;
     fp.save = save_in_lists;
+    fp.empty = pass == kPassReset;  // (the nodes' buffers hold values, not increments)
     fp.outputs = net->int_dev; fp.n_outputs = net->n_int; fp.int_blocks = net->int_blocks; fp.int_mode = int_mode;
     fp.int_large = net->int_large;
     fp.st = net->st;
@@ -881,7 +881,7 @@ evconv_status create_impl(const evconv_net_desc* desc, const void* weights, size
   if (e != hipSuccess) { g_create_error = std::string("clearing the workspace: ") + hipGetErrorString(e); delete net; return EVCONV_ERR_HIP; }
 
   std::vector<SetDesc> sets(L.nodes.size() + 1);
-  sets[0] = SetDesc{net->occ_in, net->idx_in, net->count_in, net->bitmap_in, L.gin.h, L.gin.w, L.gin.tx, L.gin.ty, nullptr};
+  sets[0] = SetDesc{net->occ_in, net->idx_in, net->count_in, net->bitmap_in, L.gin.h, L.gin.w, L.gin.tx, L.gin.ty, nullptr, nullptr};
   std::vector<float> staging;
   for (size_t i = 0; i < L.nodes.size(); ++i) {
     NodePlan& n = L.nodes[i];
@@ -914,7 +914,7 @@ evconv_status create_impl(const evconv_net_desc* desc, const void* weights, size
       n.dy = (float*)(ws + n.off_dy);
       net->outputs.push_back((int)i);
     }
-    sets[i + 1] = SetDesc{n.occ, n.idx, n.count, n.bitmap, n.go.h, n.go.w, n.go.tx, n.go.ty, nullptr};
+    sets[i + 1] = SetDesc{n.occ, n.idx, n.count, n.bitmap, n.go.h, n.go.w, n.go.tx, n.go.ty, nullptr, n.occ};
     if (n.d.op == EVCONV_OP_CONV2D || n.d.op == EVCONV_OP_LINEAR) {
       const int k = n.d.kh, ci_n = n.d.c_in, co_n = n.d.c_out, cop = n.c_out_pad;
       ConvParams probe;

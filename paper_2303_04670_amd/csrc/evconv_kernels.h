@@ -277,11 +277,13 @@ struct SetDesc {
   const uint64_t* occ; int32_t* idx; int32_t* count; uint64_t* bitmap;
   int h, w, tx, ty;
   uint64_t* save;  // copy of the words for the next pass (a node that a DELAY reads), or null
+  uint64_t* words; // a node's S words, T words behind them; null: the input
 };
 // ---- end of a pass: output integrations, then the lists of all sets, in one launch ----------------
 struct FinishParams {
   const SetDesc* sets; int n_sets, max_ty;  // DEVICE array; tile rows of the tallest set
   int save;                                 // copy the words of sets with a SetDesc::save
+  int empty;                                // every set ends up empty: words, count and bitmap are zeroed (reset)
   const IntegrateDesc* outputs; int n_outputs, int_blocks, int_mode;  // DEVICE array, ascending first_block
   int int_large;                            // one of them is integrate_large
   Streams st;

@@ -965,13 +965,27 @@ int integrate_blocks(int c, int sites) {
 // inside the strip wave r owns image row r and scans the per-tile byte popcounts with a
 // wave-wide prefix sum, so indices come out strictly ascending in y*W + x.
 // A recurrent net's delayed nodes have their words copied to SetDesc::save on the way.
-__device__ __forceinline__ void lists_block(const SetDesc& d, int strip, size_t so, int save) {
+// empty: the strip's words, and the set's count and bitmap become zeros.
+__device__ __forceinline__ void lists_block(const SetDesc& d, int strip, size_t so, int save, int empty) {
   __shared__ int s_part[8];
   __shared__ int s_rowcnt[8];
   if (strip >= d.ty) return;
   const auto occ = as_global(at_stream(d.occ, so));
   const auto idx = as_global(at_stream(d.idx, so));
   const int tid = threadIdx.x, lane = tid & 63, r = tid >> 6;
+  if (empty) {
+    const int n_tiles = d.tx * d.ty;
+    if (d.words) {
+      const auto words = as_global(at_stream(d.words, so));
+      for (int t = tid; t < d.tx; t += 512) words[strip * d.tx + t] = words[n_tiles + strip * d.tx + t] = 0;
+    }
+    if (strip == 0) {
+      const auto bitmap = as_global(at_stream(d.bitmap, so));
+      for (int t = tid; t < (n_tiles + 63) >> 6; t += 512) bitmap[t] = 0;
+      if (tid == 0) *as_global(at_stream(d.count, so)) = 0;
+    }
+    return;
+  }
   if (save && d.save) {
     const auto copy = as_global(at_stream(d.save, so));
     for (int t = tid; t < d.tx; t += 512) copy[strip * d.tx + t] = occ[strip * d.tx + t];
@@ -1054,7 +1068,7 @@ __global__ __launch_bounds__(512) void finish_kernel(FinishParams p) {
       integrate_block<LARGE>(at, p.int_mode, blk - d.first_block);
     } else {
       const int b = blk - p.int_blocks, set = b / p.max_ty;
-      lists_block(p.sets[set], b - set * p.max_ty, so, p.save);
+      lists_block(p.sets[set], b - set * p.max_ty, so, p.save, p.empty);
     }
     __syncthreads();  // (the next block reuses the shared memory)
   }
@@ -1062,13 +1076,13 @@ __global__ __launch_bounds__(512) void finish_kernel(FinishParams p) {
 
 // The lists alone, for nets whose outputs are all integrated by their own kernels: 31 sets of 32
 // strips 7.2 us, against 8.2 through the kernel above.
-__global__ __launch_bounds__(512) void build_lists_kernel(const SetDesc* sets, size_t stream_stride, int save) {
-  lists_block(sets[blockIdx.y], blockIdx.x, (size_t)blockIdx.z * stream_stride, save);
+__global__ __launch_bounds__(512) void build_lists_kernel(const SetDesc* sets, size_t stream_stride, int save, int empty) {
+  lists_block(sets[blockIdx.y], blockIdx.x, (size_t)blockIdx.z * stream_stride, save, empty);
 }
 
 void launch_finish(const FinishParams& p, hipStream_t s) {
   if (p.int_blocks == 0) {
-    hipLaunchKernelGGL(build_lists_kernel, dim3(p.max_ty, p.n_sets, p.st.n), dim3(512), 0, s, p.sets, p.st.stride, p.save);
+    hipLaunchKernelGGL(build_lists_kernel, dim3(p.max_ty, p.n_sets, p.st.n), dim3(512), 0, s, p.sets, p.st.stride, p.save, p.empty);
     return;
   }
   // (a launch holds less than 2^32 threads; the loop takes what is left of a very tall input)

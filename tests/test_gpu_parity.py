@@ -2533,6 +2533,39 @@ def test_concat_of_ragged_channel_counts(ca, cb, hw):
     gpu.destroy()
 
 
+@pytest.mark.parametrize("h,w,streams", [(20, 28, 1), (9, 4200, 1), (33, 60, 2)])
+def test_reset_leaves_every_set_empty(h, w, streams):
+    """After a reset in mid-stream every node's S and T words, count and bitmap are zero (a row of more than 512
+    tiles, two streams), and the next step starts from there."""
+    _say(f"reset empties the sets: {h} x {w}, {streams} streams")
+    b = wl._NetBuilder("empty", 3, h, w, 5)
+    x = b.conv(-1, 16, 3, act=wl.ACT_RELU)
+    y = b.conv(x, 32, 3, act=wl.ACT_NONE)
+    z = b.simple(wl.OP_ADD, y, y, act=wl.ACT_RELU)
+    b.conv(z, 5, 1, 1, 0, act=wl.ACT_RELU, out=1)
+    net = b.finish()
+    rng = np.random.default_rng(w)
+    gpu, fresh = ev.EvConvNet(net, n_streams=streams), ev.EvConvNet(net, n_streams=streams)
+    dev = lambda a: _dev(a if streams > 1 else a[0])
+    x0, x1, x2 = rng.standard_normal((3, streams, 3, h, w)).astype(np.float32)
+    gpu.reset(dev(x0))
+    gpu.step_frame(dev(x1))
+    assert gpu.state(z, ev.STATE_OCC).any()
+    gpu.reset(dev(x2))
+    fresh.reset(dev(x2))
+    for s in range(streams):
+        for n in range(-1, len(net.nodes)):
+            for kind in (ev.STATE_OCC, ev.STATE_COUNT, ev.STATE_BITMAP) + ((ev.STATE_OCC_TOUCHED,) if n >= 0 else ()):
+                assert not gpu.state(n, kind, s).any(), (n, kind, s)
+    for g in (gpu, fresh):
+        g.step_frame(dev(x1))
+    for s in range(streams):
+        np.testing.assert_array_equal(gpu.state(z, ev.STATE_Z, s), fresh.state(z, ev.STATE_Z, s))
+        np.testing.assert_array_equal(gpu.site_list(z, s), fresh.site_list(z, s))
+    gpu.destroy()
+    fresh.destroy()
+
+
 def test_outputs_keep_the_workspace():
     """Outputs that outlive their net: its workspace is not given to the next allocation under them."""
     import gc
