@@ -554,21 +554,24 @@
     AFrag aq0 = a_load(0), aq1 = aq0, aq2 = aq0;
     // Requests first, then the unit's matrix instructions: left to itself the compiler moves the weight loads of a unit
     // among its last MFMAs and the patch reads next to their uses, and the wave waits for both (depth net
-    // in bf16 206 -> 202 us, flow net 280 -> 272, ConvLSTM cell 381 -> 367).
+    // in bf16 206 -> 202 us, flow net 280 -> 272).  Not in the variants for any kernel that are held to five waves, whose
+    // registers it takes.
+    constexpr bool FRONT = !(min_waves(CHUNK, NW, OPM, MB, MODE, KSP, S2K) == 5 && S2K == 0);
+    auto in_front = []() __attribute__((always_inline)) { if (FRONT) __builtin_amdgcn_sched_barrier(0); };
     auto step = [&](AFrag& cur, AFrag& nxt, int jj, const BFrag& b) {
       if (APIPE) nxt = a_load(jj + 1); else cur = a_load(jj);
-      __builtin_amdgcn_sched_barrier(0);
+      in_front();
       unit(cur, b);
     };
     for (; j + 3 <= n_mine; j += 3) {
       bq2 = b_load(c0, j + 2);
-      __builtin_amdgcn_sched_barrier(0);
+      in_front();
       step(aq0, aq1, j, bq0);
       bq0 = b_load(c0, j + 3);
-      __builtin_amdgcn_sched_barrier(0);
+      in_front();
       step(aq1, aq2, j + 1, bq1);
       bq1 = b_load(c0, j + 4);
-      __builtin_amdgcn_sched_barrier(0);
+      in_front();
       step(aq2, aq0, j + 2, bq2);
     }
     if (pair && wave == 1) {  // (uniform; its only unit)

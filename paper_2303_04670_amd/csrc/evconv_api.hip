@@ -699,7 +699,9 @@ void fill_outputs(evconv_net* net, evconv_out* out) {
 hipError_t prepare_fold(evconv_net* net, NodePlan& n, const void* weights, const Geo& lo) {
   constexpr int k = 5, taps = kFoldVectors * kFoldVectors;
   const int ci_n = n.d.c_in, co_n = n.d.c_out, cop = n.c_out_pad;
-  if (!fold_pays(lo.h, lo.w)) return hipSuccess;
+  // (the kernel's byte offsets into a phase's weight set fit 31 bits)
+  const long long set_bytes = (long long)taps * ((ci_n + 31) / 32 * 32) * cop * 2 * weight_part_count(n.d.wdtype);
+  if (!fold_pays(lo.h, lo.w) || set_bytes >= (1ll << 31)) return hipSuccess;
   // vec[parity][vector][kernel row]: what the up-sampled row under a kernel row contributes to the vector's stored
   // row (columns likewise).  Half-pixel centres: row 2q of the up-sampled tensor is 0.75 * stored row q + 0.25 * row q -
   // 1, row 2q + 1 is 0.75 * row q + 0.25 * row q + 1.  On the first stored row up-sampled rows from 0 on exist, and

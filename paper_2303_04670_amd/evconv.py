@@ -321,10 +321,11 @@ class EvConvNet:
             if not all(o.y for o in self._outs):
                 raise EvConvError(ERR_STATE, "outputs before reset")
             torch, base, spans, in_place = self.torch, stream * self.stream_stride, [], True
+            owner = getattr(self, "workspace", None)  # (None: the library's own array)
 
             def span(ptr, typestr, *shape):  # (in its type and shape at once: each view would take 1-3 us)
                 nonlocal in_place
-                t = torch.as_tensor(_DeviceBytes(ptr + base, typestr, shape, self.workspace), device=self.device)
+                t = torch.as_tensor(_DeviceBytes(ptr + base, typestr, shape, owner), device=self.device)
                 in_place &= t.data_ptr() == ptr + base
                 return t
             for o in self._outs:
