@@ -82,9 +82,8 @@ __device__ __forceinline__ void build_elements(const BuilderParams& p, const int
 // clear the per-node occupancy words that the layer kernels OR into
 __device__ __forceinline__ void clear_words(const BuilderParams& p) {
   if (!p.clear) return;
-  const int nthreads = gridDim.x * gridDim.y * blockDim.x;
-  const int gtid = (blockIdx.y * gridDim.x + blockIdx.x) * blockDim.x + threadIdx.x;
-  for (int i = gtid; i < p.n_clear; i += nthreads) p.clear[i] = 0;
+  const ClearShare mine = clear_share(gridDim.x, gridDim.y, blockDim.x, blockIdx.x, blockIdx.y, threadIdx.x);
+  for (long long i = mine.first; i < p.n_clear; i += mine.step) p.clear[i] = 0;
 }
 
 // Strips: one workgroup = 8 wavefronts = an 8-row x 64-column strip (8 tiles).  Wave r reads row r with
