@@ -457,7 +457,7 @@ evconv_status run_pass(evconv_net* net, const float* input, int builder_mode, Pa
   BuilderParams bp;
   bp.in = input; bp.x_prev = net->x_prev; bp.dx = net->dx; bp.occ = net->occ_in;
   bp.row_or = (uint64_t*)(net->ws + net->L.off_row_or);
-  bp.clear = net->occ_nodes; bp.n_clear = (long long)net->L.n_occ_words;
+  bp.clear = net->occ_nodes; bp.n_clear = (unsigned)net->L.n_occ_words;
   bp.g = net->L.gin; bp.mode = builder_mode;
   bp.st = net->st; bp.in_stride = net->in_stride;
   // per-launch timing (evconv_profile_begin): record r is an event pair around the launches of

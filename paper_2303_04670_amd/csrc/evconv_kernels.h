@@ -67,7 +67,7 @@ struct BuilderParams {
   float* dx;          // H x W x C increment (full frame in reset mode)
   uint64_t* occ;      // per-tile occupancy of the input increment
   uint64_t* clear;    // words to zero before the layers run (all nodes' occupancy), or null
-  long long n_clear;
+  unsigned n_clear;
   uint64_t* row_or;    // wide inputs: builder_scratch_words scratch words, zero between launches
   Geo g;
   int mode;

@@ -83,7 +83,7 @@ __device__ __forceinline__ void build_elements(const BuilderParams& p, const int
 __device__ __forceinline__ void clear_words(const BuilderParams& p) {
   if (!p.clear) return;
   const ClearShare mine = clear_share(gridDim.x, gridDim.y, blockDim.x, blockIdx.x, blockIdx.y, threadIdx.x);
-  for (long long i = mine.first; i < p.n_clear; i += mine.step) p.clear[i] = 0;
+  for (long long i = mine.first; i < (long long)p.n_clear; i += mine.step) p.clear[i] = 0;
 }
 
 // Strips: one workgroup = 8 wavefronts = an 8-row x 64-column strip (8 tiles).  Wave r reads row r with
@@ -139,14 +139,14 @@ __global__ __launch_bounds__(512) void builder_kernel(BuilderParams p) {
   clear_words(p);
 }
 
-// Wide inputs (a network that starts inside another one): workgroup = 64 sites of one row x 8 N channels,
-// lane = site, the channels dealt to the 8 waves, so that the channel-major input is read in runs of 256
-// bytes.  The increments are turned through LDS and written in runs of the workgroup's channels.  A row's
-// activity is the OR over its channel blocks: 32 sites and a bit per block that has arrived share a
-// scratch word (p.row_or), so that one atomic both adds a block's share and tells the last one that it is
-// the last; that one writes the sites' bytes and leaves the word zero for the next launch.
+// Wide inputs (a network that starts inside another one): workgroup = 64 sites, 2^LS columns x 64 / 2^LS
+// rows, x 8 N channels, lane = site, the channels dealt to the 8 waves, so that the channel-major input is read in
+// runs of up to 256 bytes.  The increments are turned through LDS and written in runs of the workgroup's
+// channels.  The sites' activity is the OR over their channel blocks: 32 sites and a bit per block that has
+// arrived share a scratch word (p.row_or), so that one atomic both adds a block's share and tells the last one
+// that it is the last; that one writes the tile rows' bytes and leaves the word zero for the next launch.
 constexpr int kWideBlocks = 32;  // channel blocks at most: arrival bits of a scratch word
-template <int N>
+template <int N, int LS>
 __global__ __launch_bounds__(512) void builder_wide_kernel(BuilderParams p) {
   touch_params<BuilderParams>();
   {
@@ -156,16 +156,18 @@ __global__ __launch_bounds__(512) void builder_wide_kernel(BuilderParams p) {
     p.occ = at_stream(p.occ, so); p.clear = at_stream(p.clear, so);
     p.row_or = at_stream(p.row_or, so);
   }
-  constexpr int CB = 8 * N;
+  constexpr int CB = 8 * N, COLS = 1 << LS;
   // (pitch 66: the reads below are of eight sites x eight channel groups, 8 banks apart)
   __shared__ float s_d[CB][66];
   __shared__ uint64_t s_any[8];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int strips = (p.g.w + 63) >> 6;
-  const int y = blockIdx.x / strips, strip = blockIdx.x - y * strips;
-  const int x0 = strip * 64, x = x0 + lane, hw = p.g.h * p.g.w, C = p.g.c;
-  const bool inb = y < p.g.h && x < p.g.w;  // (the rows of the last tiles that lie below the image: bytes of zeros)
-  const int row = y * p.g.w + x0;
+  const int strips = (p.g.w + COLS - 1) >> LS;
+  const int group = blockIdx.x / strips, strip = blockIdx.x - group * strips;
+  const int y0 = group * (64 >> LS), x0 = strip * COLS, hw = p.g.h * p.g.w, C = p.g.c;
+  auto exists = [&](int site) { return y0 + (site >> LS) < p.g.h && x0 + (site & (COLS - 1)) < p.g.w; };
+  auto index = [&](int site) { return (y0 + (site >> LS)) * p.g.w + x0 + (site & (COLS - 1)); };
+  const bool inb = exists(lane);  // (the rows of the last tiles that lie below the image: bytes of zeros)
+  const int own = index(lane);
   bool any = false;
   for (int c0 = blockIdx.y * CB; c0 < C; c0 += gridDim.y * CB) {
     if (c0 != (int)blockIdx.y * CB) __syncthreads();
@@ -177,7 +179,7 @@ __global__ __launch_bounds__(512) void builder_wide_kernel(BuilderParams p) {
     for (int j = 0; j < N; ++j) {
       const int c = wave * N + j;
       ok[j] = inb && c < nc;
-      e[j] = (c0 + c) * hw + row + lane;
+      e[j] = (c0 + c) * hw + own;
     }
     build_elements<N>(p, e, ok, d);
 #pragma unroll
@@ -186,19 +188,19 @@ __global__ __launch_bounds__(512) void builder_wide_kernel(BuilderParams p) {
       any |= ok[j] && d[j] != 0.0f;
     }
     __syncthreads();
-    if (y < p.g.h) {
+    if (LS < 6 || y0 < p.g.h) {  // (uniform; rows of 64 columns lie below the image as a whole)
       if ((C & 3) == 0) {
 #pragma unroll
         for (int i = tid; i < 64 * (CB / 4); i += 512) {
           const int q = i / (CB / 4), c = i % (CB / 4) * 4;
-          if (x0 + q < p.g.w && c < nc)
-            *(float4*)&p.dx[(size_t)(row + q) * C + c0 + c] = make_float4(s_d[c][q], s_d[c + 1][q], s_d[c + 2][q], s_d[c + 3][q]);
+          if (exists(q) && c < nc)
+            *(float4*)&p.dx[(size_t)index(q) * C + c0 + c] = make_float4(s_d[c][q], s_d[c + 1][q], s_d[c + 2][q], s_d[c + 3][q]);
         }
       } else {
 #pragma unroll
         for (int i = tid; i < 64 * CB; i += 512) {
           const int q = i / CB, c = i % CB;
-          if (x0 + q < p.g.w && c < nc) p.dx[(size_t)(row + q) * C + c0 + c] = s_d[c][q];
+          if (exists(q) && c < nc) p.dx[(size_t)index(q) * C + c0 + c] = s_d[c][q];
         }
       }
     }
@@ -206,7 +208,7 @@ __global__ __launch_bounds__(512) void builder_wide_kernel(BuilderParams p) {
   const uint64_t b = __ballot(any);
   if (lane == 0) s_any[wave] = b;
   __syncthreads();
-  if (tid < 2) {  // lane h: columns x0 + 32 h on
+  if (tid < 2) {  // lane h: sites 32 h on
     uint64_t word = 0;
 #pragma unroll
     for (int i = 0; i < 8; ++i) word |= s_any[i];
@@ -224,21 +226,26 @@ __global__ __launch_bounds__(512) void builder_wide_kernel(BuilderParams p) {
       if (last) __hip_atomic_store(acc, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     if (last) {
-      const int tx0 = strip * 8 + 4 * tid;
-      unsigned char* const bytes = (unsigned char*)(p.occ + (size_t)(y >> 3) * p.g.tx + tx0) + (y & 7);
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
-        if (tx0 + j < p.g.tx) bytes[8 * j] = (unsigned char)(bits >> (8 * j));
+      for (int j = 0; j < 4; ++j) {  // eight sites: a row of a tile
+        const int site = (4 * tid + j) * 8, y = y0 + (site >> LS), tx = (x0 + (site & (COLS - 1))) >> 3;
+        if (tx < p.g.tx) ((unsigned char*)(p.occ + (size_t)(y >> 3) * p.g.tx + tx))[y & 7] = (unsigned char)(bits >> (8 * j));
+      }
     }
   }
   clear_words(p);
 }
-size_t builder_scratch_words(const Geo& g) { return (size_t)g.ty * 8 * ((g.w + 63) / 64) * 2; }
+size_t builder_scratch_words(const Geo& g) { return (size_t)builder_wide_groups(g.h, g.w) * 2; }
 
 template <int N>
 void launch_builder_wide(const BuilderParams& p, hipStream_t s) {
-  const dim3 rows(p.g.ty * 8 * ((p.g.w + 63) / 64), std::min((p.g.c + 8 * N - 1) / (8 * N), kWideBlocks), p.st.n);
-  hipLaunchKernelGGL(builder_wide_kernel<N>, rows, dim3(512), 0, s, p);
+  const dim3 grid((unsigned)builder_wide_groups(p.g.h, p.g.w), std::min((p.g.c + 8 * N - 1) / (8 * N), kWideBlocks), p.st.n);
+  switch (builder_wide_ls(p.g.w)) {
+    case 6: hipLaunchKernelGGL((builder_wide_kernel<N, 6>), grid, dim3(512), 0, s, p); return;
+    case 5: hipLaunchKernelGGL((builder_wide_kernel<N, 5>), grid, dim3(512), 0, s, p); return;
+    case 4: hipLaunchKernelGGL((builder_wide_kernel<N, 4>), grid, dim3(512), 0, s, p); return;
+    default: hipLaunchKernelGGL((builder_wide_kernel<N, 3>), grid, dim3(512), 0, s, p); return;
+  }
 }
 
 void launch_builder(const BuilderParams& p, hipStream_t s) {
@@ -247,6 +254,9 @@ void launch_builder(const BuilderParams& p, hipStream_t s) {
   // 352 3.7 / 7.1 us, 8 on 480 x 640 9.1 / 13.9).  Rows for more.  Before, strips that walked the channels 8 at a
   // time or tiles x 64 channels, read in pieces of 32 bytes (12 on 64 x 64 6.0, now 3.4 us; 24 on 480 x 640 47.8 / 21.7; 64
   // on 91 x 121 11.4 / 6.1; 256 on 32 x 44 8.4 / 5.0; 256 on 260 x 346 186 / 78.5, 4.7 TB/s; 9 on 260 x 346 8.3 / 8.7).
+  // Several rows to a workgroup on narrow images (eight streams: 64 channels on 2000 x 6 in rows of 64 columns,
+  // mostly idle, 114 us, in tiles x 64 channels 20.0, now 22.1; 32 on 300 x 20 13.5 / 17.8 / 8.9, on 400 x 14 15.9 / 15.5 / 7.8;
+  // beyond 32 columns 64 are best: 32 on 64 x 36 5.7, in rows of 32 5.9, on 300 x 40 14.8 / 16.7, on 400 x 60 22.4 / 26.9).
   // 16 channels a workgroup up to 16 channels, else 32, a line of 128 bytes (24 on 480 x 640 in blocks of 16, 32
   // and 64: 28.8 / 21.7 / 35.2; 256 on 260 x 346 97 / 78 / 86; 16 on 480 x 640 16.6 / 19.4).
   if (p.g.c > 8) {

@@ -2433,11 +2433,13 @@ def test_wide_inputs_in_strips(c, hw):
 
 
 @pytest.mark.parametrize("c,hw,streams", [(9, (9, 63), 1), (16, (8, 64), 1), (17, (23, 65), 1), (20, (1, 130), 2), (32, (7, 7), 1),
-                                          (36, (17, 96), 1), (66, (10, 97), 2), (1028, (3, 129), 1), (1063, (9, 10), 1)])
+                                          (36, (17, 96), 1), (66, (10, 97), 2), (1028, (3, 129), 1), (1063, (9, 10), 1),
+                                          (9, (37, 5), 2), (68, (21, 8), 1), (33, (21, 9), 1), (20, (6, 16), 2), (40, (9, 17), 1), (13, (19, 32), 1),
+                                          (16, (130, 33), 1)])
 def test_wide_inputs_in_rows(c, hw, streams):
-    """The increment builder for more than 8 channels (64 sites of a row x 16 or 32 channels, blocks of
-    channels that meet in a scratch word, several blocks to a workgroup beyond 1024 channels): cached
-    frame, increment and words are those of the same subtraction and comparison in numpy, bit for bit."""
+    """The increment builder for more than 8 channels (64 sites of a row, or of two to eight rows of a narrow
+    image, x 16 or 32 channels, blocks of channels that meet in a scratch word, several blocks to a workgroup beyond 1024
+    channels): cached frame, increment and words are those of the same subtraction and comparison in numpy, bit for bit."""
     h, w = hw
     _say(f"wide inputs in rows: {c} channels, {h} x {w}, {streams} streams")
     b = wl._NetBuilder("rows", c, h, w, c)
