@@ -251,15 +251,17 @@ void launch_builder_wide(const BuilderParams& p, hipStream_t s) {
 void launch_builder(const BuilderParams& p, hipStream_t s) {
   dim3 grid((p.g.w + 63) / 64, (p.g.h + 7) / 8, p.st.n);
   // Strips for up to 8 channels, all of them in flight (with rows, whose waves are mostly idle there, 5 on 256 x
-  // 352 3.7 / 7.1 us, 8 on 480 x 640 9.1 / 13.9).  Rows for more.  Before, strips that walked the channels 8 at a
-  // time or tiles x 64 channels, read in pieces of 32 bytes (12 on 64 x 64 6.0, now 3.4 us; 24 on 480 x 640 47.8 / 21.7; 64
-  // on 91 x 121 11.4 / 6.1; 256 on 32 x 44 8.4 / 5.0; 256 on 260 x 346 186 / 78.5, 4.7 TB/s; 9 on 260 x 346 8.3 / 8.7).
+  // 352 3.7 / 7.1 us, 8 on 480 x 640 9.1 / 13.9), and for up to 12 from 32768 sites on, where there are waves
+  // enough beside a thread's longer chain (rows / strips: 9 on 480 x 640 16.2 / 9.8, eight streams 117 / 63; 12 there 15.9 / 12.2;
+  // 12 on 260 x 346 8.7 / 6.8, on 200 x 200 5.8 / 5.2, on 100 x 100 3.6 / 3.8; 9 on 64 x 64 3.2 / 3.5).
+  // Rows for more.  Before, strips that walked the channels 8 at a time or tiles x 64 channels, read in pieces of 32 bytes (12 on 64 x 64 6.0, now 3.4 us; 24 on 480 x 640 47.8 / 21.7; 64
+  // on 91 x 121 11.4 / 6.1; 256 on 32 x 44 8.4 / 5.0; 256 on 260 x 346 186 / 78.5, 4.7 TB/s).
   // Several rows to a workgroup on narrow images (eight streams: 64 channels on 2000 x 6 in rows of 64 columns,
   // mostly idle, 114 us, in tiles x 64 channels 20.0, now 22.1; 32 on 300 x 20 13.5 / 17.8 / 8.9, on 400 x 14 15.9 / 15.5 / 7.8;
   // beyond 32 columns 64 are best: 32 on 64 x 36 5.7, in rows of 32 5.9, on 300 x 40 14.8 / 16.7, on 400 x 60 22.4 / 26.9).
   // 16 channels a workgroup up to 16 channels, else 32, a line of 128 bytes (24 on 480 x 640 in blocks of 16, 32
   // and 64: 28.8 / 21.7 / 35.2; 256 on 260 x 346 97 / 78 / 86; 16 on 480 x 640 16.6 / 19.4).
-  if (p.g.c > 8) {
+  if (p.g.c > 12 || (p.g.c > 8 && (long long)p.g.sites() * p.st.n < 32768)) {
     if (p.g.c <= 16) launch_builder_wide<2>(p, s);
     else launch_builder_wide<4>(p, s);
     return;
@@ -273,6 +275,10 @@ void launch_builder(const BuilderParams& p, hipStream_t s) {
     case 6: hipLaunchKernelGGL((builder_kernel<6>), grid, dim3(512), 0, s, p); return;
     case 7: hipLaunchKernelGGL((builder_kernel<7>), grid, dim3(512), 0, s, p); return;
     case 8: hipLaunchKernelGGL((builder_kernel<8>), grid, dim3(512), 0, s, p); return;
+    case 9: hipLaunchKernelGGL((builder_kernel<9>), grid, dim3(512), 0, s, p); return;
+    case 10: hipLaunchKernelGGL((builder_kernel<10>), grid, dim3(512), 0, s, p); return;
+    case 11: hipLaunchKernelGGL((builder_kernel<11>), grid, dim3(512), 0, s, p); return;
+    case 12: hipLaunchKernelGGL((builder_kernel<12>), grid, dim3(512), 0, s, p); return;
   }
 }
 

@@ -2401,10 +2401,10 @@ def test_elementwise_maps_split_over_the_channels(c, hw):
     run_stream(net, x0, incs, "increment", label=f"elementwise {c}", max_flips=6, tol=1e-5)
 
 
-@pytest.mark.parametrize("c,hw", [(9, (70, 1030)), (12, (1030, 65)), (16, (130, 513)), (33, (500, 130)), (2, (40, 70)), (4, (33, 129))])
+@pytest.mark.parametrize("c,hw", [(9, (70, 1030)), (10, (131, 261)), (11, (4700, 7)), (12, (1030, 65)), (16, (130, 513)), (33, (500, 130)), (2, (40, 70)), (4, (33, 129))])
 def test_wide_inputs_in_strips(c, hw):
-    """Inputs of more than 8 channels on maps of 128 strips and more go through the strip form of the
-    increment builder, 4 or 8 channels at a time: cached frame, increment, words and lists bit-exact
+    """Inputs of 9 to 12 channels on maps of 32768 sites and more (and of up to 8 on any) go through the strip form
+    of the increment builder, all channels in flight; 16 and 33 channels on such maps in rows: cached frame, increment, words and lists bit-exact
     through frames and supplied increments, elements in single channels."""
     h, w = hw
     _say(f"wide inputs in strips: {c} channels, {h} x {w}")
