@@ -349,7 +349,8 @@ constexpr int ew_in_flight(int op, int vec) {
 // Element e is vector e % cv of touched site number e / cv: where few sites are touched, few waves have
 // work (64 channels on 256 x 352, 2 % of the sites active, tanh / product: 11.4 / 7.6 us with an element
 // for each of the 64 sites, now 7.5 / 6.3).
-template <int OP, int VEC, int N>
+// ACT: a concatenation or an up-sampling with an activation (Eq.12-14 behind Eq.11 or Eq.10), which keeps state.
+template <int OP, int VEC, int N, bool ACT = false>
 __global__ __launch_bounds__(256) void elementwise_kernel(EwParams p) {
   touch_params<EwParams>();
   const size_t so = (size_t)blockIdx.z * p.st.stride;
@@ -449,7 +450,7 @@ __global__ __launch_bounds__(256) void elementwise_kernel(EwParams p) {
         lin[it] = on[it] ? ldv<VEC>(&pa[q[it] * C + c[it]]) : zerov<VEC>();
       }
     }
-    constexpr bool STATE = OP == kEwMul || OP == kEwPoolMax || OP == kEwPoolAcc || OP == kEwAdd || OP == kEwAct;
+    constexpr bool STATE = OP == kEwMul || OP == kEwPoolMax || OP == kEwPoolAcc || OP == kEwAdd || OP == kEwAct || ACT;
     const float sp_k = OP == kEwSparsify && !dense ? *at_stream(p.step, so) : 0.0f;
     const bool reads_z = OP == kEwPoolMax || (OP == kEwSparsify ? sp_k > 0.0f : STATE && !dense && (OP == kEwMul || OP == kEwPoolAcc || p.keeps_z));
     if (STATE || OP == kEwSparsify) {
@@ -588,7 +589,7 @@ __global__ __launch_bounds__(256) void elementwise_kernel(EwParams p) {
         stv<VEC>(zq, lin[it]);
 #pragma unroll
         for (int i = 0; i < VEC; ++i) o.v[i] = dense ? lin[it].v[i] : lin[it].v[i] - z_old[it].v[i];
-      } else if ((OP == kEwAdd || OP == kEwAct) && p.keeps_z) {
+      } else if (ACT || ((OP == kEwAdd || OP == kEwAct) && p.keeps_z)) {
         VecT<VEC> z_new = o;
 #pragma unroll
         for (int i = 0; i < VEC; ++i) {
@@ -636,8 +637,8 @@ __global__ __launch_bounds__(256) void elementwise_kernel(EwParams p) {
   }
 }
 
-// Concatenation of operands whose channel counts are not multiples of four (Eq.11: the structural OR of the
-// two active sets).  An operand's channels are taken four at a time all the same: 16-byte accesses need dword
+// Concatenation, without an activation, of operands whose channel counts are not multiples of four (Eq.11: the
+// structural OR of the two active sets).  An operand's channels are taken four at a time all the same: 16-byte accesses need dword
 // alignment only, and the last one to three channels of a site go singly.  A site's run of floats is one
 // workgroup's, up to kConcatItems pieces.  Bound by HBM; with single floats, in runs of 16 channels that begin
 // anywhere in a line, 5 + 64 channels on 256 x 352, every site active, 21.2 us, now 13.3 (3.7 TB/s).
@@ -716,6 +717,11 @@ void launch_ew(const EwParams& q, const dim3& grid, hipStream_t s) {
   else hipLaunchKernelGGL((elementwise_kernel<OP, VEC, kMax>), grid, dim3(256), 0, s, q);
 }
 
+template <int OP, int VEC>
+void launch_ew_act(const EwParams& q, const dim3& grid, hipStream_t s) {
+  hipLaunchKernelGGL((elementwise_kernel<OP, VEC, ew_in_flight(OP, VEC), true>), grid, dim3(256), 0, s, q);
+}
+
 void launch_elementwise(const EwParams& p, hipStream_t s) {
   bool vec4 = (p.go.c % 4) == 0;
   if (p.op == kEwConcat || p.op == kEwConcatUp) vec4 = vec4 && (p.ga.c % 4) == 0;
@@ -725,7 +731,8 @@ void launch_elementwise(const EwParams& p, hipStream_t s) {
   // dense ones (three nodes on 32 x 44 x 512 with 5 % of the sites active: 21.5 us in 192 workgroups, 22.8 in 384,
   // 26.8 in 768; on 64 x 88 x 128, all sites: 37.5 in 176, 28.9 in 352, 25.8 in 704).
   EwParams q = p;
-  const bool ragged_concat = p.op == kEwConcat && !vec4;
+  const bool act = (p.op == kEwConcat || p.op == kEwConcatUp || p.op == kEwUp2x) && p.act != kActNone;
+  const bool ragged_concat = p.op == kEwConcat && !vec4 && !act;
   const int cv_all = ragged_concat ? (p.ga.c + 3) / 4 + (p.gb.c + 3) / 4 : p.go.c / (vec4 ? 4 : 1);
   q.vec_per_block = ragged_concat ? kConcatItems : kEwVecPerBlock;
   while (q.vec_per_block > kEwVecPerBlock / 4 &&
@@ -736,6 +743,13 @@ void launch_elementwise(const EwParams& p, hipStream_t s) {
                    ? 0u : (unsigned)((0x100000000ull + (unsigned)p.go.tx - 1) / (unsigned)p.go.tx);
   if (ragged_concat) {
     hipLaunchKernelGGL(concat_ragged_kernel, grid, dim3(256), 0, s, q);
+    return;
+  }
+  if (act) {
+    // (one variant each: such nodes are rare)
+#define EVK_EW_ACT(OP) case OP: if (vec4) launch_ew_act<OP, 4>(q, grid, s); else launch_ew_act<OP, 1>(q, grid, s); break;
+    switch (p.op) { EVK_EW_ACT(kEwConcat) EVK_EW_ACT(kEwConcatUp) EVK_EW_ACT(kEwUp2x) }
+#undef EVK_EW_ACT
     return;
   }
 #define EVK_EW(OP) case OP: if (vec4) launch_ew<OP, 4>(q, grid, s); else launch_ew<OP, 1>(q, grid, s); break;

@@ -2404,8 +2404,8 @@ def test_elementwise_maps_split_over_the_channels(c, hw):
 @pytest.mark.parametrize("c,hw", [(9, (70, 1030)), (10, (131, 261)), (11, (4700, 7)), (12, (1030, 65)), (16, (130, 513)), (33, (500, 130)), (2, (40, 70)), (4, (33, 129))])
 def test_wide_inputs_in_strips(c, hw):
     """Inputs of 9 to 12 channels on maps of 32768 sites and more (and of up to 8 on any) go through the strip form
-    of the increment builder, all channels in flight; 16 and 33 channels on such maps in rows: cached frame, increment, words and lists bit-exact
-    through frames and supplied increments, elements in single channels."""
+    of the increment builder, all channels in flight; 16 and 33 channels on such maps in rows: cached frame,
+    increment, words and lists bit-exact through frames and supplied increments, elements in single channels."""
     h, w = hw
     _say(f"wide inputs in strips: {c} channels, {h} x {w}")
     b = wl._NetBuilder("strips", c, h, w, c)
@@ -2532,6 +2532,54 @@ def test_concat_of_ragged_channel_counts(ca, cb, hw):
     gpu.reset(_dev(x1))   # a regular pass: the values at every site
     np.testing.assert_array_equal(gpu.state(y, ev.STATE_DY)[..., :ca], x1.transpose(1, 2, 0))
     np.testing.assert_array_equal(gpu.state(y, ev.STATE_DY)[..., ca:], gpu.state(x, ev.STATE_DY))
+    gpu.destroy()
+
+
+@pytest.mark.parametrize("flags", [0, ev.FLAG_NO_FUSION])
+@pytest.mark.parametrize("act", [wl.ACT_RELU, wl.ACT_SIGMOID, wl.ACT_TANH, wl.ACT_ONE_MINUS])
+@pytest.mark.parametrize("kind,ca,cb", [("concat", 8, 24), ("concat", 5, 7), ("concat", 68, 33), ("concat", 2, 2), ("up", 8, 0), ("up", 36, 0),
+                                        ("up", 7, 0), ("up_concat", 8, 16), ("up_concat", 3, 6)])
+def test_concatenations_and_up_samplings_with_an_activation(kind, ca, cb, act, flags):
+    """CONCAT and UPSAMPLE_BILINEAR2X with an activation, whole vectors of channels and ragged ones: accumulated
+    tensor, increments and value-pruned sets are the oracle's, through steps, a regular pass in mid-stream
+    and a reset (in exact arithmetic where the activation has it: no flip of a set then)."""
+    h, w = 21, 19
+    _say(f"{kind} {ca} + {cb} channels, activation {act}, flags {flags}")
+    b = wl._NetBuilder("cat_act", ca, h, w, ca + cb)
+    if kind == "concat":
+        x = b.conv(-1, cb, 1, 1, 0, act=wl.ACT_NONE)
+        y = b.simple(wl.OP_CONCAT, -1, x, act=act)
+    elif kind == "up":
+        y = b.simple(wl.OP_UPSAMPLE2X, -1, act=act)
+    else:
+        u = b.simple(wl.OP_UPSAMPLE2X, -1)
+        v = b.simple(wl.OP_UPSAMPLE2X, -1)
+        x = b.conv(v, cb, 1, 1, 0, act=wl.ACT_NONE)
+        y = b.simple(wl.OP_CONCAT, u, x, act=act)
+    b.simple(wl.OP_ACT, y, act=wl.ACT_NONE, out=1)
+    b.conv(y, 2, 1, 1, 0, act=wl.ACT_NONE, out=1)
+    net = b.finish()
+    exact = act in (wl.ACT_RELU, wl.ACT_ONE_MINUS)
+    rng = np.random.default_rng(ca)
+    wts = net.weights.copy()
+    wts[:] = rng.integers(-2, 3, wts.size) / 4.0
+    net.weights = wts
+    value = lambda q: (rng.integers(-8, 9, (ca, h, w)) / 4.0 * (rng.random((1, h, w)) < q)).astype(np.float32)
+    gpu, ora, rep = ev.EvConvNet(net, flags=flags), Oracle(net), cmp.Report()
+    tol = 1e-7 if exact else 1e-5
+    for x0 in (value(1.0), value(1.0)):
+        gpu.reset(_dev(x0))
+        ora.reset(x0)
+        cmp.compare_outputs(gpu, ora, rep, tol)
+        for q in (0.05, 1.0, 0.3, 0.02):
+            d = value(q)
+            gpu.step(_dev(d))
+            ora.step_increment(d)
+            cmp.compare_outputs(gpu, ora, rep, tol)
+            for i in range(len(net.nodes)):
+                cmp.compare_node(gpu, ora, i, rep, tol=tol)
+            assert ora.z(y).size and gpu.state(y, ev.STATE_Z).size == ora.z(y).size
+    assert rep.flips <= (0 if exact else 60), rep.flips_by_node
     gpu.destroy()
 
 
