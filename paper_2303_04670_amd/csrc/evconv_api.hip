@@ -130,9 +130,8 @@ struct NodePlan {
   int gather_fused_into = -1;  // UPSAMPLE node computed inside the gather of that conv node, never stored
   int upsampled_from = -2;     // conv node: the node (-1: network input) whose x2 up-sampling it reads through
                                // its gather, its in0 being the folded UPSAMPLE node; -2: none
-  // conv node reading through an up-sampling: the up-sampling folded into per-phase weights
-  // away from the image border (ConvParams::fold_list); room is reserved whenever in0 is an
-  // up-sampling and the taps are 5 x 5, used if the planner folds that up-sampling into this conv
+  // conv node reading through an up-sampling that is folded into per-phase weights
+  // (ConvParams::fold_list); room is reserved where fold_set_bytes says so
   size_t off_w_fold = 0, off_fold_list = 0;
   void* w_fold = nullptr;
   int* fold_list = nullptr;
@@ -178,6 +177,36 @@ struct Bump {
     return o;
   }
 };
+
+// Nodes that read each node.
+std::vector<int> consumer_counts(const std::vector<NodePlan>& nodes) {
+  std::vector<int> n(nodes.size(), 0);
+  for (const NodePlan& x : nodes) {
+    const evconv_node_desc& d = x.d;
+    if (d.in0 >= 0) ++n[d.in0];
+    const bool two = d.op == EVCONV_OP_ADD || d.op == EVCONV_OP_CONCAT || d.op == EVCONV_OP_MUL;
+    if (two && d.in1 >= 0 && d.in1 != d.in0) ++n[d.in1];
+  }
+  return n;
+}
+
+// Bytes of the weight sets that hold the up-sampling in front of conv node n (four phases of taps, see prepare_fold, x
+// input channels padded to 32); 0 where it is not folded: bf16-declared weights (they would be rounded a second
+// time), maps on which it does not pay, sets in which the kernel's byte offsets do not fit 31 bits, an up-sampling that
+// something else reads or applies to, flags.
+size_t fold_set_bytes(const std::vector<NodePlan>& nodes, const std::vector<int>& consumers, const NodePlan& n, uint32_t flags, int n_streams) {
+  const evconv_node_desc& d = n.d;
+  if (d.op != EVCONV_OP_CONV2D || d.kh != 5 || d.stride != 1 || d.pad != 2 || d.in0 < 0 || d.wdtype == EVCONV_BF16) return 0;
+  if (flags & (EVCONV_FLAG_NO_FUSION | EVCONV_FLAG_NO_FOLD | EVCONV_FLAG_FORCE_VALU)) return 0;
+  const evconv_node_desc& u = nodes[d.in0].d;
+  if (u.op != EVCONV_OP_UPSAMPLE_BILINEAR2X || u.act != EVCONV_ACT_NONE || u.is_output || consumers[d.in0] != 1) return 0;
+  ConvParams probe = {};
+  probe.gi = n.ga; probe.go = n.go; probe.k = d.kh; probe.stride = d.stride; probe.pad = d.pad; probe.c_out_pad = n.c_out_pad;
+  probe.st = Streams{0, n_streams}; probe.fp32 = d.wdtype == EVCONV_F32;
+  if (!conv_mfma_upsample_supported(probe) || !fold_pays(n.ga.h / 2, n.ga.w / 2)) return 0;
+  const size_t phase = (size_t)kFoldVectors * kFoldVectors * ((d.c_in + 31) / 32 * 32) * n.c_out_pad * 2 * weight_part_count(d.wdtype);
+  return phase < (size_t)1 << 31 ? 4 * phase : 0;
+}
 
 evconv_status fail(std::string* err, evconv_status st, const std::string& msg) {
   if (err) *err = msg;
@@ -342,6 +371,7 @@ evconv_status make_layout(const evconv_net_desc* desc, size_t weight_bytes, bool
     n.off_occ = L->off_occ_nodes + occ_word_off[i] * sizeof(uint64_t);
     n.off_touched = n.off_occ + (size_t)n.go.tiles() * sizeof(uint64_t);
   }
+  const std::vector<int> consumers = consumer_counts(L->nodes);
   // input stage
   const size_t in_elems = (size_t)L->gin.c * L->gin.sites();
   L->off_x_prev = b.take(in_elems * 4);
@@ -370,12 +400,9 @@ evconv_status make_layout(const evconv_net_desc* desc, size_t weight_bytes, bool
                                     (n.d.wdtype == EVCONV_F32 ? 6 : 4),
                                 conv_narrow_weight_floats(n.c_out_pad) * 4));
       if (n.d.bias_off >= 0) n.off_bias = b.take((size_t)n.d.c_out * 4);
-      if (n.d.op == EVCONV_OP_CONV2D && k == 5 && n.d.stride == 1 && n.d.pad == 2 && n.d.in0 >= 0 &&
-          L->nodes[n.d.in0].d.op == EVCONV_OP_UPSAMPLE_BILINEAR2X && fold_pays(n.ga.h / 2, n.ga.w / 2)) {
-        // four phases of taps (see prepare_fold) x input channels padded to 32
-        n.off_w_fold = b.take((size_t)4 * kFoldVectors * kFoldVectors * ((n.d.c_in + 31) / 32 * 32) * n.c_out_pad *
-                              (n.d.wdtype == EVCONV_F32 ? 6 : 4));
-        n.off_fold_list = b.take((size_t)n.go.tiles() * 4);
+      if (const size_t fold = fold_set_bytes(L->nodes, consumers, n, desc->flags, desc->n_streams > 0 ? desc->n_streams : 1)) {
+        n.off_w_fold = b.take(fold);
+        n.off_fold_list = b.take((size_t)((n.ga.h / 2 + 7) / 8) * ((n.ga.w / 2 + 7) / 8) * sizeof(int));
       }
     }
     if (n.d.is_output) {
@@ -699,9 +726,6 @@ void fill_outputs(evconv_net* net, evconv_out* out) {
 hipError_t prepare_fold(evconv_net* net, NodePlan& n, const void* weights, const Geo& lo) {
   constexpr int k = 5, taps = kFoldVectors * kFoldVectors;
   const int ci_n = n.d.c_in, co_n = n.d.c_out, cop = n.c_out_pad;
-  // (the kernel's byte offsets into a phase's weight set fit 31 bits)
-  const long long set_bytes = (long long)taps * ((ci_n + 31) / 32 * 32) * cop * 2 * weight_part_count(n.d.wdtype);
-  if (!fold_pays(lo.h, lo.w) || set_bytes >= (1ll << 31)) return hipSuccess;
   // vec[parity][vector][kernel row]: what the up-sampled row under a kernel row contributes to the vector's stored
   // row (columns likewise).  Half-pixel centres: row 2q of the up-sampled tensor is 0.75 * stored row q + 0.25 * row q -
   // 1, row 2q + 1 is 0.75 * row q + 0.25 * row q + 1.  On the first stored row up-sampled rows from 0 on exist, and
@@ -1093,13 +1117,7 @@ evconv_status create_impl(const evconv_net_desc* desc, const void* weights, size
   // Fold a bilinear x2 up-sampling into the gather of the matrix-core conv that is its only
   // consumer: the up-sampled tensor is then never written (its node keeps no state).
   if (fuse) {
-    std::vector<int> n_consumers(L.nodes.size(), 0);
-    for (size_t i = 0; i < L.nodes.size(); ++i) {
-      const evconv_node_desc& d = L.nodes[i].d;
-      if (d.in0 >= 0) ++n_consumers[d.in0];
-      const bool two = d.op == EVCONV_OP_ADD || d.op == EVCONV_OP_CONCAT || d.op == EVCONV_OP_MUL;
-      if (two && d.in1 >= 0 && d.in1 != d.in0) ++n_consumers[d.in1];
-    }
+    const std::vector<int> n_consumers = consumer_counts(L.nodes);
     for (size_t i = 0; i < L.nodes.size(); ++i) {
       NodePlan& c_node = L.nodes[i];
       if (c_node.d.op != EVCONV_OP_CONV2D || c_node.d.in0 < 0) continue;
@@ -1116,9 +1134,8 @@ evconv_status create_impl(const evconv_net_desc* desc, const void* weights, size
       if (!conv_mfma_upsample_supported(probe)) continue;
       u_node.gather_fused_into = (int)i;
       c_node.upsampled_from = u_node.d.in0;
-      // away from the image border the up-sampling goes into the weights instead (fp32 products only:
-      // bf16-declared weights would be rounded a second time)
-      if (c_node.off_fold_list && c_node.kernel != kKernConvMfmaBf16 && !(net->flags & EVCONV_FLAG_NO_FOLD)) {
+      // where that pays the up-sampling goes into the weights instead
+      if (c_node.off_fold_list) {
         const Geo& lo = u_node.d.in0 < 0 ? L.gin : L.nodes[u_node.d.in0].go;
         e = prepare_fold(net, c_node, weights, lo);
         if (e != hipSuccess) { g_create_error = std::string("folded weights upload: ") + hipGetErrorString(e); delete net; return EVCONV_ERR_HIP; }
@@ -1447,7 +1464,6 @@ const char* evconv_node_kernel(const evconv_net* net, int32_t node) {
   if (net->L.nodes[node].gather_fused_into >= 0) {
     const NodePlan& consumer = net->L.nodes[net->L.nodes[node].gather_fused_into];
     if (consumer.d.op == EVCONV_OP_CONCAT) return "fused_into_concat_gather";
-    // (folded into the conv's weights away from the image border, into its gather along the border)
     return consumer.fold_list ? "fused_into_conv_weights" : "fused_into_conv_gather";
   }
   return kKernelNames[net->L.nodes[node].kernel];

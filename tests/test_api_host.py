@@ -210,6 +210,30 @@ def test_static_workspace_holds_what_four_bytes_per_weight_and_32_mib_held():
     assert query(nodes) <= ev.STATIC_WORKSPACE_BYTES
 
 
+def _decoder(h, w, wdtype, up_act=wl.ACT_NONE, up_out=0, reader=False):
+    nodes = [wl.Node(wl.OP_UPSAMPLE2X, up_act, -1, -2, 64, 64, is_output=up_out),
+             wl.Node(wl.OP_CONV2D, wl.ACT_RELU, 0, -2, 64, 32, 5, 1, 2, 0, -1, 1, wdtype=wdtype)]
+    if reader:
+        nodes.append(wl.Node(wl.OP_ACT, wl.ACT_TANH, 0, -2, 64, 64, is_output=1))
+    return wl.Net("decoder", 64, h, w, nodes, np.zeros(0, np.float32))
+
+
+def test_folded_weights_take_room_only_where_they_are_used():
+    """A conv whose up-sampling is folded into its weights: four phases of 6 x 6 taps, two bytes a part.  No room for
+    them with bf16-declared weights, on small maps, under the flags that forbid it, or where the
+    up-sampled tensor is needed itself."""
+    query = lambda *a, flags=0, **k: ev.evconv_query_workspace(ev.marshal_desc(_decoder(*a, **k), flags=flags)[0])
+    extra = lambda *a, flags=0, **k: query(*a, flags=flags, **k) - query(*a, flags=flags | ev.FLAG_NO_FOLD, **k)
+    sets = 4 * 36 * 64 * 32 * 2
+    for wdtype, parts in ((wl.WD_F32, 3), (wl.WD_F32_SPLIT, 2)):
+        assert sets * parts <= extra(40, 56, wdtype) <= sets * parts + 1024
+    assert extra(40, 56, wl.WD_BF16) == 0
+    assert extra(17, 56, wl.WD_F32) == 0
+    assert extra(40, 56, wl.WD_F32, flags=ev.FLAG_NO_FUSION) == 0 and extra(40, 56, wl.WD_F32, flags=ev.FLAG_FORCE_VALU) == 0
+    assert extra(40, 56, wl.WD_F32, up_act=wl.ACT_RELU) == 0 and extra(40, 56, wl.WD_F32, up_out=1) == 0
+    assert extra(40, 56, wl.WD_F32, reader=True) == 0
+
+
 def test_no_kernel_uses_scratch_memory():
     """Registers spilled to scratch would make the runtime allocate device memory at a kernel's first
     launch, which the library promises not to: the metadata of every kernel in the built library
