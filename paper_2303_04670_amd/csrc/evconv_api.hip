@@ -132,6 +132,7 @@ struct NodePlan {
                                // its gather, its in0 being the folded UPSAMPLE node; -2: none
   // conv node reading through an up-sampling that is folded into per-phase weights
   // (ConvParams::fold_list); room is reserved where fold_set_bytes says so
+  bool folds = false;
   size_t off_w_fold = 0, off_fold_list = 0;
   void* w_fold = nullptr;
   int* fold_list = nullptr;
@@ -161,7 +162,7 @@ struct Layout {
   size_t off_sets = 0, off_rms = 0, off_int = 0;
   size_t off_row_or = 0;  // scratch of the increment builder (wide inputs)
   size_t off_ks_part = 0, off_ks_count = 0;  // scratch of convs whose channels are split over workgroups
-  size_t stride = 0;   // bytes of one stream's state (the weights live in stream 0's copy)
+  size_t stride = 0;   // bytes of one stream's state; what all streams share (weights, descriptors) lies behind the last one
   int n_streams = 1;
   size_t total = 0;
   int max_ty = 0;
@@ -372,6 +373,7 @@ evconv_status make_layout(const evconv_net_desc* desc, size_t weight_bytes, bool
     n.off_touched = n.off_occ + (size_t)n.go.tiles() * sizeof(uint64_t);
   }
   const std::vector<int> consumers = consumer_counts(L->nodes);
+  Bump shared;  // offsets behind the streams' states until these are known
   // input stage
   const size_t in_elems = (size_t)L->gin.c * L->gin.sites();
   L->off_x_prev = b.take(in_elems * 4);
@@ -396,13 +398,14 @@ evconv_status make_layout(const evconv_net_desc* desc, size_t weight_bytes, bool
       const int k = n.d.kh;
       // room for input channels padded to whole chunks (at most 64), three bf16 parts each at most,
       // or a padded flattened contraction (the narrow-input kernel's per-lane layout)
-      n.off_w = b.take(std::max(((size_t)k * k * ((n.d.c_in + 63) / 64 * 64) + 16) * n.c_out_pad *
+      n.off_w = shared.take(std::max(((size_t)k * k * ((n.d.c_in + 63) / 64 * 64) + 16) * n.c_out_pad *
                                     (n.d.wdtype == EVCONV_F32 ? 6 : 4),
                                 conv_narrow_weight_floats(n.c_out_pad) * 4));
-      if (n.d.bias_off >= 0) n.off_bias = b.take((size_t)n.d.c_out * 4);
+      if (n.d.bias_off >= 0) n.off_bias = shared.take((size_t)n.d.c_out * 4);
       if (const size_t fold = fold_set_bytes(L->nodes, consumers, n, desc->flags, desc->n_streams > 0 ? desc->n_streams : 1)) {
-        n.off_w_fold = b.take(fold);
-        n.off_fold_list = b.take((size_t)((n.ga.h / 2 + 7) / 8) * ((n.ga.w / 2 + 7) / 8) * sizeof(int));
+        n.folds = true;
+        n.off_w_fold = shared.take(fold);
+        n.off_fold_list = shared.take((size_t)((n.ga.h / 2 + 7) / 8) * ((n.ga.w / 2 + 7) / 8) * sizeof(int));
       }
     }
     if (n.d.is_output) {
@@ -413,11 +416,16 @@ evconv_status make_layout(const evconv_net_desc* desc, size_t weight_bytes, bool
   L->off_row_or = b.take(builder_scratch_words(L->gin) * sizeof(uint64_t));
   L->off_rms = b.take(sizeof(float) * kRmsBlocks);
   L->off_ks_part = b.take(ks_floats * sizeof(float));
-  L->off_int = b.take(sizeof(IntegrateDesc) * (size_t)desc->n_nodes);
-  L->off_sets = b.take(sizeof(SetDesc) * (size_t)(desc->n_nodes + 1));
-  L->stride = (b.cur + 255) / 256 * 256;  // one stream's copy of everything
+  L->off_int = shared.take(sizeof(IntegrateDesc) * (size_t)desc->n_nodes);
+  L->off_sets = shared.take(sizeof(SetDesc) * (size_t)(desc->n_nodes + 1));
+  L->stride = b.cur;
   L->n_streams = desc->n_streams > 0 ? desc->n_streams : 1;
-  L->total = L->stride * (size_t)L->n_streams;
+  const size_t states = L->stride * (size_t)L->n_streams;
+  for (NodePlan& n : L->nodes)
+    for (size_t* off : {&n.off_w, &n.off_bias, &n.off_w_fold, &n.off_fold_list}) *off += states;
+  L->off_int += states;
+  L->off_sets += states;
+  L->total = states + shared.cur;
   return EVCONV_OK;
 }
 
@@ -1135,7 +1143,7 @@ evconv_status create_impl(const evconv_net_desc* desc, const void* weights, size
       u_node.gather_fused_into = (int)i;
       c_node.upsampled_from = u_node.d.in0;
       // where that pays the up-sampling goes into the weights instead
-      if (c_node.off_fold_list) {
+      if (c_node.folds) {
         const Geo& lo = u_node.d.in0 < 0 ? L.gin : L.nodes[u_node.d.in0].go;
         e = prepare_fold(net, c_node, weights, lo);
         if (e != hipSuccess) { g_create_error = std::string("folded weights upload: ") + hipGetErrorString(e); delete net; return EVCONV_ERR_HIP; }

@@ -234,6 +234,17 @@ def test_folded_weights_take_room_only_where_they_are_used():
     assert extra(40, 56, wl.WD_F32, reader=True) == 0
 
 
+def test_streams_share_their_weights():
+    """Every further stream of a net takes the same room, and none for the weights (8 conv layers of 128 channels on
+    a map of 4 x 4: nearly all weights)."""
+    nodes = [wl.Node(wl.OP_CONV2D, wl.ACT_RELU, i - 1, -2, 128, 128, 3, 1, 1, 0, -1, int(i == 7)) for i in range(8)]
+    net = wl.Net("weights", 128, 4, 4, nodes, np.zeros(0, np.float32))
+    query = lambda n: ev.evconv_query_workspace(ev.marshal_desc(net, n_streams=n)[0])
+    weights = 8 * 9 * 128 * 128 * 6
+    assert query(1) >= weights
+    assert query(3) - query(2) == query(2) - query(1) < weights // 4
+
+
 def test_no_kernel_uses_scratch_memory():
     """Registers spilled to scratch would make the runtime allocate device memory at a kernel's first
     launch, which the library promises not to: the metadata of every kernel in the built library
