@@ -1356,6 +1356,82 @@ def test_folded_upsampling_borders(h, w, ci, co, mode):
     gpu.destroy()
 
 
+class _Stream:
+    """One stream of a net, for the comparisons with an oracle."""
+
+    def __init__(self, gpu, stream):
+        self._gpu, self._stream = gpu, stream
+
+    def state(self, node, kind):
+        return self._gpu.state(node, kind, self._stream)
+
+    def site_list(self, node):
+        return self._gpu.site_list(node, self._stream)
+
+    def outputs(self):
+        return self._gpu.outputs(self._stream)
+
+    def __getattr__(self, name):
+        return getattr(self._gpu, name)
+
+
+@pytest.mark.parametrize("h,w,ci,co,streams,mode,kind", [
+    (60, 66, 32, 64, 1, "f32", "add"), (62, 65, 32, 64, 1, "split", "add"), (64, 65, 32, 64, 1, "f32", "two adds"),
+    (59, 68, 32, 64, 1, "split", "two adds"), (60, 67, 32, 64, 1, "f32", "sparsify"), (63, 66, 32, 64, 1, "split", "sparsify"),
+    (57, 67, 32, 64, 1, "f32", "sigmoid"), (66, 60, 32, 64, 1, "split", "tanh"), (28, 35, 32, 96, 3, "f32", "add"),
+    (34, 36, 32, 64, 3, "split", "sparsify"), (20, 27, 32, 32, 2, "f32", "two adds")])
+def test_folded_upsampling_epilogue_stages(h, w, ci, co, streams, mode, kind):
+    """What runs in the folded kernel's epilogue (ADDs whose other input is active beyond the conv's touched sites,
+    a sparsification layer, activations other than ReLU) on the sites of whole tiles, with last tiles of
+    one to eight columns and rows (eight rows of four columns where there are no more) and with streams whose
+    number decides between whole and half tiles (the last case: half).  Exact arithmetic (dyadic weights and
+    increments): sets, lists and sums equal the fp64 oracle's; with sigmoid and tanh to fp32 accuracy."""
+    _say(f"folded up-sampling, epilogue: {kind}, stored tensor {h}x{w}, {ci} -> {co} channels, {mode}, {streams} streams")
+    smooth = kind in ("sigmoid", "tanh")
+    b = wl._NetBuilder("fold_stages", ci, h, w, 3, sparsify=kind == "sparsify", sparsify_k=0.5)
+    u2 = b.simple(wl.OP_UPSAMPLE2X, -1)
+    s = b.conv(u2, co, 7, act=wl.ACT_NONE, sparsify_input=False)
+    u = b.simple(wl.OP_UPSAMPLE2X, -1)
+    c = b.conv(u, co, 5, act=wl.ACT_SIGMOID if kind == "sigmoid" else wl.ACT_NONE, out=int(kind == "sigmoid"), sparsify_input=False)
+    stages = []
+    if kind != "sigmoid":
+        stages.append(b.simple(wl.OP_ADD, s, c, act={"tanh": wl.ACT_TANH, "two adds": wl.ACT_NONE}.get(kind, wl.ACT_RELU), out=1))
+    if kind == "two adds":
+        stages.append(b.simple(wl.OP_ADD, stages[0], s, act=wl.ACT_RELU, out=1))
+    if kind == "sparsify":
+        b.conv(stages[0], 16, 1, 1, 0, act=wl.ACT_NONE, out=1)
+        stages.append(stages[0] + 1)
+    net = b.finish()
+    rng = np.random.default_rng(h * w)
+    wts = net.weights.copy()
+    for nd in net.nodes:
+        if nd.op == wl.OP_CONV2D:
+            n = nd.c_out * nd.c_in * nd.k * nd.k
+            wts[nd.w_off:nd.w_off + n] = rng.integers(-1, 2, n) * (rng.random(n) < 2.0 / (nd.k * nd.k)) / 8.0
+    net.weights = wts
+    if mode == "split":
+        net = wl.with_weight_dtype(net, wl.WD_F32_SPLIT)
+    gpu = ev.EvConvNet(net, n_streams=streams)
+    assert gpu.kernel_name(u) == "fused_into_conv_weights" and [gpu.kernel_name(i) for i in stages] == ["fused_into_conv_epilogue"] * len(stages)
+    oras = [Oracle(net) for _ in range(streams)]
+    dev = lambda a: _dev(a if streams > 1 else a[0])
+    value = lambda q: (rng.integers(-8, 9, (streams, ci, h, w)) / 4.0 * (rng.random((streams, 1, h, w)) < q)).astype(np.float32)
+    x0, rep, tol = value(1.0), cmp.Report(), 1e-5 if smooth else 1e-7
+    gpu.reset(dev(x0))
+    for k, ora in enumerate(oras):
+        ora.reset(x0[k])
+    for q in (0.004, 1.0, 0.002, 0.05):
+        d = value(q)
+        gpu.step(dev(d))
+        for k, ora in enumerate(oras):
+            ora.step_increment(d[k])
+            cmp.compare_outputs(_Stream(gpu, k), ora, rep, tol)
+            for i in range(len(net.nodes)):
+                cmp.compare_node(_Stream(gpu, k), ora, i, rep, tol=tol, exact_sets=not smooth)
+    assert rep.flips <= (200 if smooth else 0), rep.flips_by_node
+    gpu.destroy()
+
+
 # --------------------------------------------------------------------------- recurrent state
 
 def _running_sum_net(c, h, w):
@@ -2634,9 +2710,9 @@ def test_outputs_keep_the_workspace():
 
 
 def test_reset_clears_arrival_counters():
-    """Counters that a pass cut short leaves behind (here: written by hand, behind the last node's
-    occupancy words and behind the last output) are cleared by a reset, those of the channel split by
-    every pass: the results are those of a fresh net."""
+    """Counters that a pass cut short leaves behind (here: written by hand, those of the channel split behind the
+    last node's occupancy words, the increment builder's scratch words behind the last output) are cleared by a
+    reset, those of the channel split by every pass: the results are those of a fresh net."""
     import torch
     c, h, w = 256, 11, 20
     b = wl._NetBuilder("counters", c, h, w, 3)
@@ -2655,16 +2731,17 @@ def test_reset_clears_arrival_counters():
     counters = gpu.workspace.cpu().numpy().tobytes().index(words) + len(words)
     align = lambda p: (p + 255) // 256 * 256
     dy = gpu.outputs()[0]["dy"]
-    tile_or = align(dy.data_ptr() + dy.numel() * 4) - gpu.workspace.data_ptr()
-    tile_count = align(tile_or + gpu.workspace.data_ptr() + tiles * 8) - gpu.workspace.data_ptr()
+    at = align(dy.data_ptr() + dy.numel() * 4) - gpu.workspace.data_ptr()
+    groups = -(-h // 8) * 8 // 2   # of two rows (17 to 32 columns), rows below the image among them: two words each
     split = gpu.workspace[counters:counters + 8 * tiles].view(torch.int32)      # one per half tile and block of 32 channels
-    builder = [gpu.workspace[tile_or:tile_or + 8 * tiles].view(torch.int32), gpu.workspace[tile_count:tile_count + 4 * tiles].view(torch.int32)]
-    assert not any(int(t.abs().sum()) for t in [split] + builder)
+    builder = gpu.workspace[at:at + 16 * groups].view(torch.int64)
+    assert not int(split.abs().sum()) and not int(builder.abs().sum())
     split.fill_(1)
-    for t in builder:
-        t.fill_(1)
+    builder.fill_(-1)              # every site and every arrival bit
     for g in (gpu, clean):
         g.reset(_dev(x0))
+    torch.cuda.synchronize()
+    assert not int(builder.abs().sum())
     np.testing.assert_array_equal(gpu.state(n, ev.STATE_Z), clean.state(n, ev.STATE_Z))
     for k, d in enumerate(incs):
         split.fill_(1 + k)
@@ -2675,6 +2752,7 @@ def test_reset_clears_arrival_counters():
             np.testing.assert_array_equal(gpu.state(n, kind), clean.state(n, kind))
         np.testing.assert_array_equal(gpu.state(-1, ev.STATE_OCC), clean.state(-1, ev.STATE_OCC))
         assert torch.equal(gpu.outputs()[0]["y"], clean.outputs()[0]["y"])
+        assert not int(builder.abs().sum())
     gpu.destroy()
     clean.destroy()
 
