@@ -33,7 +33,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, MB == 2 
                "s"(p.wg_swap), "s"(p.tx_magic));
   const size_t so = (size_t)blockIdx.z * p.st.stride;
   constexpr int PARTS = op_parts(OPM), NB = 32, NT = 256;
-  constexpr int NW = 4, NROWS = 4 * MB, SUBS = 2 / MB;  // waves; rows of stored sites; workgroups of a tile and phase
+  constexpr int NW = 4, NROWS = 4 * MB;  // waves; rows of stored sites
   constexpr int PH = NROWS + 3, PW = 11;               // patch
   constexpr int CS = patch_site_words(CHUNK, OPM), LO = CHUNK / 2;
   constexpr int RP = ((PW * CS + 31) / 64) * 64 + 32;  // row pitch, see conv_mfma_body.h
@@ -48,15 +48,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, MB == 2 
   EVK_PHASE_OPEN();
   const bool dense = p.dense != 0;
   const int H = p.lo_h, W = p.lo_w, Cin = p.gi.c, Cout = p.go.c;
-  // workgroup -> list entry, upper or lower half of the tile, phase; phases vary fastest, so that an XCD (every
-  // eighth workgroup) reads one of the four weight sets
+  // workgroup -> list entry (a tile, or a tile and which half of it), phase; phases vary fastest, so that an XCD
+  // (every eighth workgroup) reads one of the four weight sets
   const int wg_tile = p.wg_swap ? blockIdx.y : blockIdx.x, wg_co = p.wg_swap ? blockIdx.x : blockIdx.y;
-  const int phase = wg_tile & 3, r0 = (wg_tile >> 2) % SUBS * 4;
-  const int tile = p.fold_list[(wg_tile >> 2) / SUBS];
+  const int phase = wg_tile & 3, entry = p.fold_list[wg_tile >> 2];
+  const int tile = MB == 1 ? entry >> 1 : entry, r0 = MB == 1 ? (entry & 1) * 4 : 0;
   const int s_tx = (W + 7) >> 3;
   const int tile_y = fast_div(tile, s_tx, p.tx_magic), tile_x = tile - tile_y * s_tx;
   const int y0 = tile_y * 8 + r0, x0 = tile_x * 8;
-  if (y0 >= H) return;
   const int fpy = phase >> 1, fpx = phase & 1;
   const int iy0 = y0 - 2 + fpy, ix0 = x0 - 2 + fpx;
   const bool flat = MB == 1 || y0 + 4 >= H;      // the first block holds all rows
@@ -474,8 +473,10 @@ template <int CHUNK, int MB, int OPM>
 void launch_fold_variant(const ConvParams& p, hipStream_t s) {
   constexpr int PH = 4 * MB + 3, PW = 11, CS = patch_site_words(CHUNK, OPM);
   constexpr size_t patch = (size_t)PH * (((PW * CS + 31) / 64) * 64 + 32) + CS, sums = MB * 4096;
-  const int tiles = ((p.lo_h + 7) >> 3) * ((p.lo_w + 7) >> 3), wgs = tiles * (2 / MB) * 4, n_co = p.c_out_pad / 32;
+  const int tiles = ((p.lo_h + 7) >> 3) * ((p.lo_w + 7) >> 3), n_co = p.c_out_pad / 32;
+  const int wgs = (MB == 1 ? ((p.lo_h + 3) >> 2) * ((p.lo_w + 7) >> 3) : tiles) * 4;
   ConvParams q = p;
+  if (MB == 1) q.fold_list += tiles;  // (the half tiles stand behind the tiles)
   q.tx_magic = magic32(tiles, (p.lo_w + 7) >> 3);
   // (which operand every XCD reads in full: see variant_launch)
   q.wg_swap = (long long)p.k * p.k * p.go.c > (long long)p.lo_h * p.lo_w && wgs <= 65535;

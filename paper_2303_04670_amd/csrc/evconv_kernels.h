@@ -129,7 +129,7 @@ struct ConvParams {
   // sites, occ_in their occupancy words); gi describes the up-sampled tensor
   int upsample, lo_h, lo_w;
   // 5 x 5 behind an up-sampling, optional (null = off): weight folding (conv_fold_impl.h).  fold_list: the 8 x 8
-  // tiles of the stored tensor in the order of their workgroups.  w_fold: the weight sets of the four
+  // tiles of the stored tensor in the order of their workgroups, then their halves.  w_fold: the weight sets of the four
   // output phases, kFoldVectors x kFoldVectors taps each, otherwise in the layout of w.
   const int* fold_list; const void* w_fold;
   // matrix-core kernel only, set by its launcher: the grid's x dimension runs over the blocks of
