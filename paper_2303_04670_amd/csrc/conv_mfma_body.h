@@ -555,8 +555,14 @@
     // Requests first, then the unit's matrix instructions: left to itself the compiler moves the weight loads of a unit
     // among its last MFMAs and the patch reads next to their uses, and the wave waits for both (depth net
     // in bf16 206 -> 202 us, flow net 280 -> 272).  Not in the variants for any kernel that are held to five waves, whose
-    // registers it takes.
-    constexpr bool FRONT = !(min_waves(CHUNK, NW, OPM, MB, MODE, KSP, S2K) == 5 && S2K == 0);
+    // registers it takes.  Nor where a wave has few units of a chunk (a four-wave half tile's 1 x 1 kernels, 3 x 3 in
+    // chunks of 16 channels) or short ones (3 x 3 in bf16), so that it holds up the way to the next chunk, nor in
+    // fp32 convs split over workgroups in chunks of 32: barrier / none, 1 x 1, 16 -> 32 on 180 x 240, split 10.9 / 9.8 us;
+    // 3 x 3, 96 -> 33 there, bf16 25.8 / 23.4; 7 x 7, 320 -> 320 on 14 x 14, fp32 34.1 / 31.8.
+    constexpr bool FEW = NW == 4 && MB == 1 && !KSP &&
+                         (S2K == 1 || (S2K == -1 && CHUNK <= 32) || (S2K == -3 && (CHUNK == 16 || OPM == kOpBf16)));
+    constexpr bool SPLIT32 = KSP && OPM == kOpF32 && CHUNK == 32 && S2K == 0;
+    constexpr bool FRONT = !FEW && !SPLIT32 && !(min_waves(CHUNK, NW, OPM, MB, MODE, KSP, S2K) == 5 && S2K == 0);
     auto in_front = []() __attribute__((always_inline)) { if (FRONT) __builtin_amdgcn_sched_barrier(0); };
     auto step = [&](AFrag& cur, AFrag& nxt, int jj, const BFrag& b) {
       if (APIPE) nxt = a_load(jj + 1); else cur = a_load(jj);
