@@ -732,7 +732,11 @@ void launch_elementwise(const EwParams& p, hipStream_t s) {
   // 26.8 in 768; on 64 x 88 x 128, all sites: 37.5 in 176, 28.9 in 352, 25.8 in 704).
   EwParams q = p;
   const bool act = (p.op == kEwConcat || p.op == kEwConcatUp || p.op == kEwUp2x) && p.act != kActNone;
-  const bool ragged_concat = p.op == kEwConcat && !vec4 && !act;
+  // Ragged concatenations in pieces of four channels from 2 Mi values on: below that the latency of a workgroup
+  // counts, which is longer (single floats / pieces, every site active and 2 % of them: 5 + 64 channels on 256 x 352
+  // 18.5 / 10.8 and 6.4 / 4.2 us, 33 + 31 14.8 / 12.2 and 5.7 / 4.6; 6 + 10 there 5.6 / 6.2 and 3.7 / 4.3, 3 + 3 4.6 / 5.5 and 3.4 / 4.8,
+  // 255 + 2 on 64 x 88 5.9 / 6.0 and 4.0 / 4.0, 33 + 31 3.6 / 4.1 and 3.0 / 3.7).
+  const bool ragged_concat = p.op == kEwConcat && !vec4 && !act && (long long)p.go.sites() * p.st.n * p.go.c >= 2 << 20;
   const int cv_all = ragged_concat ? (p.ga.c + 3) / 4 + (p.gb.c + 3) / 4 : p.go.c / (vec4 ? 4 : 1);
   q.vec_per_block = ragged_concat ? kConcatItems : kEwVecPerBlock;
   while (q.vec_per_block > kEwVecPerBlock / 4 &&
@@ -754,9 +758,8 @@ void launch_elementwise(const EwParams& p, hipStream_t s) {
   }
 #define EVK_EW(OP) case OP: if (vec4) launch_ew<OP, 4>(q, grid, s); else launch_ew<OP, 1>(q, grid, s); break;
   switch (p.op) {
-    EVK_EW(kEwAdd) EVK_EW(kEwAct) EVK_EW(kEwUp2x) EVK_EW(kEwPoolAcc) EVK_EW(kEwPoolMax) EVK_EW(kEwSparsify)
+    EVK_EW(kEwAdd) EVK_EW(kEwAct) EVK_EW(kEwConcat) EVK_EW(kEwUp2x) EVK_EW(kEwPoolAcc) EVK_EW(kEwPoolMax) EVK_EW(kEwSparsify)
     EVK_EW(kEwMul) EVK_EW(kEwConcatUp)
-    case kEwConcat: launch_ew<kEwConcat, 4>(q, grid, s); break;  // (the others: above)
   }
 #undef EVK_EW
 }

@@ -2582,10 +2582,12 @@ def test_large_wide_outputs_read_active_sites_only(mode):
     gpu.destroy()
 
 
-@pytest.mark.parametrize("ca,cb,hw", [(5, 64, (17, 20)), (1, 1, (9, 7)), (6, 3, (8, 33)), (4, 7, (25, 12)), (130, 9, (16, 24)), (67, 66, (72, 80))])
+@pytest.mark.parametrize("ca,cb,hw", [(5, 64, (17, 20)), (1, 1, (9, 7)), (6, 3, (8, 33)), (4, 7, (25, 12)), (130, 9, (16, 24)), (67, 66, (72, 80)),
+                                      (5, 64, (153, 207)), (130, 9, (97, 160)), (1, 6, (547, 551)), (34, 67, (145, 145))])
 def test_concat_of_ragged_channel_counts(ca, cb, hw):
-    """Concatenations whose operands are not whole vectors of four channels, one to three pieces of a site
-    left over, several workgroups to a tile where a site has more than 32 pieces: copies of the operands'
+    """Concatenations whose operands are not whole vectors of four channels, single floats below 2 Mi values and
+    pieces of four from there on (the last four), one to three channels of a site left over, several
+    workgroups to a tile where a site has more than 32 pieces: copies of the operands'
     increments where these are active and zeros elsewhere, the OR of their sets, bit for bit."""
     h, w = hw
     _say(f"concat {ca} + {cb} channels on {h} x {w}")
