@@ -147,6 +147,12 @@ def hbm_rows(np, ev, wl, g, net, n_streams):
     return rows
 
 
+def fold_whole_tiles():
+    """Workgroups from which on the folded up-sampling convs take whole tiles (a constant of the library's source)."""
+    src = os.path.join(ROOT, "paper_2303_04670_amd", "csrc", "evconv_kernels.h")
+    return int(re.search(r"kFoldWholeTiles = (\d+);", open(src).read()).group(1))
+
+
 def run_variant(args, np, torch, ev, wl, variant, dframes, with_dense, with_layers):
     net = make_net(wl, variant)
     n_frames = args.warmup + args.steps
@@ -186,13 +192,12 @@ def run_variant(args, np, torch, ev, wl, variant, dframes, with_dense, with_laye
         per_site = 2.0 * nd.k * nd.k * nd.c_in * nd.c_out if nd.op in (wl.OP_CONV2D, wl.OP_LINEAR) else 0.0
         flops = per_site * st.n_touched            # algorithmic: touched output sites of the last step
         # Executed: a 5 x 5 conv reading a x2 up-sampling that the library folded into its weights runs 4 x 4 taps;
-        # workgroups with sites of a border of the stored tensor run one more row (column) of them.  (Rows of stored
-        # sites per workgroup: see launch_fold.)
+        # workgroups with sites of a border of the stored tensor run one more row (column) of them.
         executed = flops
         if nd.op == wl.OP_CONV2D and nd.in0 >= 0 and g.kernel_name(nd.in0) == "fused_into_conv_weights":
             c, h, w = g.shape(i)
             lo_h, lo_w = h // 2, w // 2
-            rows = 8 if 4 * -(-lo_h // 8) * -(-lo_w // 8) * -(-c // 32) >= 512 else 4
+            rows = 8 if 4 * -(-lo_h // 8) * -(-lo_w // 8) * -(-c // 32) * g.n_streams >= fold_whole_tiles() else 4
             words = g.state(i, ev.STATE_OCC_TOUCHED).reshape(-(-h // 8), -(-w // 8))
             touched = (words[:, :, None, None] >> np.arange(64, dtype=np.uint64).reshape(8, 8)) & np.uint64(1)
             touched = touched.transpose(0, 2, 1, 3).reshape(words.shape[0] * 8, -1)[:h, :w]

@@ -19,11 +19,11 @@
 // weights (conv_mfma_negated).  A tile of which the image holds four rows or four columns at most is one
 // block: the upper rows, or eight rows of four columns.
 //
-// Bound by the matrix pipe (busy 0.65-0.7 of the cycles in which a CU holds waves with 16 streams, at clocks that the
-// power limit holds at 1.85 GHz) and, in small launches, by the phases of a workgroup.  Before, tiles with border sites
-// interpolated the up-sampled tensor and contracted all 25 taps: the depth net's decoders in fp32 57.0 / 47.9 / 47.2
+// Bound by the matrix pipe in large launches (with 16 streams busy 0.72 / 0.71 / 0.56 of the cycles in which a CU holds
+// waves in the depth net's three decoders, at 1.9 to 2.0 GHz) and, in small ones, by the phases of a workgroup.  Before, tiles with border
+// sites interpolated the up-sampled tensor and contracted all 25 taps: the decoders in fp32 57.0 / 47.9 / 47.2
 // us, now 47.4 / 42.1 / 43.7; split 39.3 / 31.6 / 35.3, now 32.7 / 27.5 / 32.8; 16 streams 609 / 564 / 603, now 538 / 497 / 560; 128
-// -> 64 behind 30 x 40 20.6, now 18.1.  (All four phases of half a tile in one workgroup, which gathers once for them,
+// -> 64 behind 30 x 40 20.7, now 17.5.  (All four phases of half a tile in one workgroup, which gathers once for them,
 // are slower than a workgroup each: 85 / 55 / 44 us, the fragments of four weight sets pass through one L1.)
 template <int CHUNK, int MB, int OPM>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, MB == 2 ? 3 : 8))) void conv_fold_kernel(ConvParams p) {
@@ -484,15 +484,17 @@ void launch_fold_variant(const ConvParams& p, hipStream_t s) {
   hipLaunchKernelGGL((conv_fold_kernel<CHUNK, MB, OPM>), grid, dim3(256), std::max(patch, sums) * sizeof(float), s, q);
 }
 
-// Whole tiles use a weight fragment twice; half tiles are twice the workgroups.  Measured, whole / half tiles, us
-// (workgroups in whole tiles): fp32, 256 -> 128 channels behind 20 x 23 42 / 30 (144), 32 x 44 52.8 / 47.4 (384), 64 -> 32 behind
-// 80 x 92 20.8 / 19.7 (480), 256 -> 128 behind 45 x 45 73.2 / 73.2 (576), 128 -> 64 behind 64 x 88 42.1 / 44.7 (704), 64 -> 32
-// behind 128 x 176 43.7 / 45.9 (1408), with 16 streams 538 / 615, 497 / 553 and 560 / 634.  Half tiles are bound by
-// round trips: chunks of 64 channels where there are any (32: 49.3, 64: 47.4 behind 32 x 44).
+// Whole tiles use a weight fragment twice; half tiles are twice the workgroups.  Measured, whole / half tiles, us, fp32 and
+// split mode (workgroups in whole tiles): 128 -> 64 channels behind 30 x 40 23.0 / 17.5, 16.9 / 12.9 (160); 256 -> 128 behind
+// 32 x 44 49.8 / 46.3, 31.7 / 30.7 (384); 64 -> 32 behind 80 x 92 18.7 / 18.6, 14.0 / 14.0 (480); 128 -> 64 behind 57 x 66 36.6 /
+// 37.9, 23.9 / 25.7 (576); 256 -> 128 behind 45 x 45 70.8 / 68.9, 41.7 / 44.4 (576); 128 -> 64 behind 64 x 88 41.5 / 42.8, 26.3 / 31.0
+// (704); 64 -> 32 behind 91 x 121 25.0 / 27.9, 17.7 / 21.5 (768); 256 -> 128 behind 32 x 44, four streams 153 / 166, 87 / 104 (1536); 16
+// streams 609 / 686, 373 / 449.  Half tiles are bound by round trips: chunks of 64 channels where there are any (64 / 32: 46.3 /
+// 46.5, 30.7 / 31.5 behind 32 x 44, 29.1 / 30.2, 20.6 / 21.9 behind 20 x 23).
 template <int OPM>
 void launch_fold(const ConvParams& p, hipStream_t s) {
   const long long whole = 4ll * ((p.lo_h + 7) >> 3) * ((p.lo_w + 7) >> 3) * (p.c_out_pad / 32) * p.st.n;
-  if (whole >= 512) launch_fold_variant<32, 2, OPM>(p, s);
+  if (whole >= kFoldWholeTiles) launch_fold_variant<32, 2, OPM>(p, s);
   else if (p.gi.c % 64 == 0) launch_fold_variant<64, 1, OPM>(p, s);
   else launch_fold_variant<32, 1, OPM>(p, s);
 }

@@ -106,6 +106,8 @@ struct FusedSparsify {
 // come down to: four for a site away from the border, and one instead of some of them for a site of the first
 // and of the last stored row (column).
 constexpr int kFoldVectors = 6, kFoldTop = 4, kFoldBottom = 5;
+// Workgroups from which on they are whole tiles of stored sites (eight rows), below that half tiles (launch_fold).
+constexpr int kFoldWholeTiles = 512;
 
 struct ConvParams {
   const float* in;          // H x W x C increment of the input node (full values if dense)
@@ -146,8 +148,8 @@ struct ConvParams {
   // conv_mfma_split_scratch gives
   int ks, ks_chunks;
   // divisors of the kernel's index arithmetic as magic factors, set by its launcher: tiles per row of
-  // the output (folded up-sampling: of the stored tensor), blocks of output channels, taps per row, gathered sites
-  // per row [plain, up-sampled], 2 x 2 blocks per row of an up-sampled patch
+  // the output (folded up-sampling: of the stored tensor), blocks of output channels (narrow-input kernel: input
+  // channels), taps per row, gathered sites per row [plain, up-sampled], 2 x 2 blocks per row of an up-sampled patch
   unsigned tx_magic, co_magic;
   int k_magic, gw_magic[2], nbx_magic;
   int grid_x;  // matrix-core kernel only, set by its launcher: workgroups along the grid's x
