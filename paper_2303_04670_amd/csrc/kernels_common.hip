@@ -254,8 +254,9 @@ void launch_builder(const BuilderParams& p, hipStream_t s) {
   // 352 3.7 / 7.1 us, 8 on 480 x 640 9.1 / 13.9), and for up to 12 from 32768 sites on, where there are waves
   // enough beside a thread's longer chain (rows / strips: 9 on 480 x 640 16.2 / 9.8, eight streams 117 / 63; 12 there 15.9 / 12.2;
   // 12 on 260 x 346 8.7 / 6.8, on 200 x 200 5.8 / 5.2, on 100 x 100 3.6 / 3.8; 9 on 64 x 64 3.2 / 3.5).
-  // Rows for more.  Before, strips that walked the channels 8 at a time or tiles x 64 channels, read in pieces of 32 bytes (12 on 64 x 64 6.0, now 3.4 us; 24 on 480 x 640 47.8 / 21.7; 64
-  // on 91 x 121 11.4 / 6.1; 256 on 32 x 44 8.4 / 5.0; 256 on 260 x 346 186 / 78.5, 4.7 TB/s).
+  // Rows for more.  Before, strips that walked the channels 8 at a time or tiles x 64 channels, read in pieces of
+  // 32 bytes (12 on 64 x 64 6.0, now 3.4 us; 24 on 480 x 640 47.8 / 21.7; 64 on 91 x 121 11.4 / 6.1; 256 on 32 x 44
+  // 8.4 / 5.0; 256 on 260 x 346 186 / 78.5, 4.7 TB/s).
   // Several rows to a workgroup on narrow images (eight streams: 64 channels on 2000 x 6 in rows of 64 columns,
   // mostly idle, 114 us, in tiles x 64 channels 20.0, now 22.1; 32 on 300 x 20 13.5 / 17.8 / 8.9, on 400 x 14 15.9 / 15.5 / 7.8;
   // beyond 32 columns 64 are best: 32 on 64 x 36 5.7, in rows of 32 5.9, on 300 x 40 14.8 / 16.7, on 400 x 60 22.4 / 26.9).
@@ -638,10 +639,11 @@ __global__ __launch_bounds__(256) void elementwise_kernel(EwParams p) {
 }
 
 // Concatenation, without an activation, of operands whose channel counts are not multiples of four (Eq.11: the
-// structural OR of the two active sets).  An operand's channels are taken four at a time all the same: 16-byte accesses need dword
-// alignment only, and the last one to three channels of a site go singly.  A site's run of floats is one
-// workgroup's, up to kConcatItems pieces.  Bound by HBM; with single floats, in runs of 16 channels that begin
-// anywhere in a line, 5 + 64 channels on 256 x 352, every site active, 21.2 us, now 13.3 (3.7 TB/s).
+// structural OR of the two active sets).  An operand's channels are taken four at a time all the same: 16-byte
+// accesses need dword alignment only, and the last one to three channels of a site go singly.  A site's run of floats is
+// one workgroup's, up to kConcatItems pieces.  Bound by HBM; with single floats, in runs of 16 channels that begin
+// anywhere in a line, 5 + 64 channels on 256 x 352, every site active, 18.5 us, now 10.8 (4.6 TB/s; in a ConvLSTM's
+// step 12.8).
 constexpr int kConcatItems = 32;
 typedef float floatx4u __attribute__((ext_vector_type(4), aligned(4)));
 __global__ __launch_bounds__(256) void concat_ragged_kernel(EwParams p) {
