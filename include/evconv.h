@@ -320,8 +320,8 @@ evconv_status evconv_get_state_stream(evconv_net* net, int32_t stream, int32_t n
                                       size_t bytes);
 
 /* Bytes between the copies of any state or output pointer of consecutive streams, and the number
- * of streams (n_streams may be NULL).  The workspace holds n_streams such copies back to back and,
- * behind them, what the streams share (weights). */
+ * of streams (n_streams may be NULL).  The workspace holds n_streams such copies back to back and, with
+ * more than one, behind them what the streams share (weights). */
 evconv_status evconv_stream_stride(const evconv_net* net, size_t* bytes /* HOST */, int32_t* n_streams /* HOST */);
 
 /* Sparsity and work of a node in the last step (stream 0): sizes of its touched and active sets
