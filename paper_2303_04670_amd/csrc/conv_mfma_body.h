@@ -558,7 +558,8 @@
     // registers it takes.  Nor where a wave has few units of a chunk (a four-wave half tile's 1 x 1 kernels, 3 x 3 in
     // chunks of 16 channels) or short ones (3 x 3 in bf16), so that it holds up the way to the next chunk, nor in
     // fp32 convs split over workgroups in chunks of 32: barrier / none, 1 x 1, 16 -> 32 on 180 x 240, split 10.9 / 9.8 us;
-    // 3 x 3, 96 -> 33 there, bf16 25.8 / 23.4; 7 x 7, 320 -> 320 on 14 x 14, fp32 34.1 / 31.8.
+    // 3 x 3, 96 -> 33 there, bf16 25.8 / 23.4 (where these have a single chunk it costs a little: 31 -> 26 on 82 x 260 8.6 /
+    // 8.8); 7 x 7, 320 -> 320 on 14 x 14, fp32 34.1 / 31.8.
     constexpr bool FEW = NW == 4 && MB == 1 && !KSP &&
                          (S2K == 1 || (S2K == -1 && CHUNK <= 32) || (S2K == -3 && (CHUNK == 16 || OPM == kOpBf16)));
     constexpr bool SPLIT32 = KSP && OPM == kOpF32 && CHUNK == 32 && S2K == 0;
